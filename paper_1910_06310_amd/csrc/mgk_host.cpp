@@ -40,8 +40,8 @@ struct JobList {
     MgkJob* dev = nullptr;
     int64_t n = 0;
     std::vector<JobBin> bins;
-    // pairs whose vectors do not fit on chip: [outer graph from X / from Y][sparse / dense tile path]
-    std::vector<MgkLargePair> large[2][2];
+    // pairs whose vectors do not fit on chip: [outer graph from X / from Y]
+    std::vector<MgkLargePair> large[2];
 };
 
 // growable device allocation owned by a context
@@ -66,6 +66,11 @@ struct mgk_batch {
     std::vector<int32_t> perm;     // [n_vertices], perm[voff + old] = new
     std::vector<int64_t> vtx_off;  // [G+1]
     std::vector<MgkSellDesc> sell_desc;   // per graph, for the planner
+    float label_lo = 0.f, label_hi = 0.f; // range of attribute 0 of the edge labels
+    int32_t max_n = 0;
+    int32_t packets[2] = {0, 0};          // packet steps of the whole batch with 2 / 8 nonzeros per packet
+    const int32_t* gptr_dev[2] = {nullptr, nullptr};
+    int64_t dense_floats = 0;             // sum of (n rounded up to 64)^2
     // device
     void* blob = nullptr;
     MgkBatchDev dev{};
@@ -73,7 +78,6 @@ struct mgk_batch {
     int gram_jobs_waves = 0;       // waves_per_pair setting the list was built for
     int gram_jobs_max_iter = 0;    // max_iter setting the list was built for
     int gram_jobs_limit = 0;       // on-chip limit the list was built for
-    int gram_jobs_tile_path = 0;   // tile path setting the list was built for
     int gram_jobs_cache = 0;       // product-cache setting the list was built for
     int gram_jobs_sorted = 0;      // schedule setting the list was built for
     int gram_jobs_attr_dim = -1;   // label attributes of the edge kernel it was built for (LDS plan)
@@ -104,6 +108,11 @@ struct mgk_ctx {
     // scratch of the global-memory solver
     DevBuf exp_outer[2], exp_inner[2];  // expanded entry lists of batch X / batch Y
     DevBuf dense_tiles[2][3];           // dense 8x8 expansions (weight, label, log2 weight)
+    DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
+    DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
+    MgkSepBasis sep_basis{};            // of the last label range and edge kernel, see sep_basis_for
+    float sep_lo = 0.f, sep_hi = -1.f, sep_param = 0.f;
+    int sep_kernel = -1;
     DevBuf vec, lpairs, lstate, lactive, nodal_off, diag;
     int* active_host = nullptr;         // pinned: {pairs still iterating, most iterations needed}
     void* pin = nullptr;                // pinned staging of the pair records of a call
@@ -555,6 +564,133 @@ bool use_dense_tiles(const mgk_ctx* ctx, const MgkGraphDesc& a, const MgkGraphDe
            (int64_t)b.nnz >= (int64_t)kDenseMinNnzPerTile * b.n_tiles;
 }
 
+// Separable form of the edge kernel on the label range [lo, hi] (see MgkSepBasis).  rank 0:
+// the kernel has none of at most MGK_SEP_MAX_RANK terms (short length scale against the range, or
+// a kernel that is not smooth).  Kept with the context until kernel or range change.
+const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
+    const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
+    if (ctx->sep_kernel == ctx->edge_kernel && ctx->sep_param == param && ctx->sep_lo == lo && ctx->sep_hi == hi)
+        return ctx->sep_basis;
+    MgkSepBasis& S = ctx->sep_basis;
+    S = MgkSepBasis{};
+    ctx->sep_kernel = ctx->edge_kernel;
+    ctx->sep_param = param;
+    ctx->sep_lo = lo;
+    ctx->sep_hi = hi;
+    if (ctx->edge_kernel == MGK_EK_CONST) {
+        S.rank = 1;
+        S.coef[0] = (float)std::sqrt((double)ctx->ke_const);
+        return S;
+    }
+    if (ctx->edge_kernel != MGK_EK_SE) return S;
+    S.center = (float)(0.5 * ((double)lo + (double)hi));
+    const double R = std::max((double)hi - (double)S.center, (double)S.center - (double)lo);
+    const double l = (double)ctx->length_scale, t = R * R / (l * l);
+    S.inv_r = R > 0.0 ? (float)(1.0 / R) : 0.f;
+    S.e_scale = (float)(std::sqrt(0.5 * 1.4426950408889634) / l);
+    // |exp(t s s') - its Chebyshev sum below degree r| falls like (t / 2)^r / r!: hopeless beyond this
+    if (!(t <= 12.0)) return S;
+    // Chebyshev coefficients of exp(t s s') from its values on a grid of nodes, both variables
+    constexpr int N = 40, D = MGK_SEP_MAX_RANK;
+    static const double pi = 3.14159265358979323846;
+    std::vector<double> cosm((size_t)D * N), half((size_t)D * N);
+    double node[N];
+    for (int i = 0; i < N; ++i) node[i] = std::cos(pi * (i + 0.5) / N);
+    for (int m = 0; m < D; ++m)
+        for (int i = 0; i < N; ++i) cosm[(size_t)m * N + i] = std::cos(pi * m * (i + 0.5) / N) * (m ? 2.0 : 1.0) / N;
+    for (int i = 0; i < N; ++i) {
+        double row[N];
+        for (int j = 0; j < N; ++j) row[j] = std::exp(t * node[i] * node[j]);
+        for (int m = 0; m < D; ++m) {
+            double v = 0.0;
+            for (int j = 0; j < N; ++j) v += row[j] * cosm[(size_t)m * N + j];
+            half[(size_t)m * N + i] = v;
+        }
+    }
+    double Cm[D][D], Lm[D][D] = {};
+    for (int m = 0; m < D; ++m)
+        for (int n = 0; n <= m; ++n) {
+            double v = 0.0;
+            if (((m + n) & 1) == 0)   // the function is even in (s, s') together
+                for (int i = 0; i < N; ++i) v += half[(size_t)m * N + i] * cosm[(size_t)n * N + i];
+            Cm[m][n] = Cm[n][m] = v;
+        }
+    // Cholesky row by row; after row r - 1 the rank-r sum is complete: its error on a grid
+    constexpr int E = 17;
+    double feat[E][D] = {};   // phi without the Gaussian, at the grid points
+    double T[E][D];
+    for (int e = 0; e < E; ++e) {
+        const double s = std::cos(pi * e / (E - 1));
+        for (int m = 0; m < D; ++m) T[e][m] = m == 0 ? 1.0 : m == 1 ? s : 2.0 * s * T[e][m - 1] - T[e][m - 2];
+    }
+    for (int r = 0; r < D; ++r) {
+        for (int k = 0; k < r; ++k) {
+            double v = Cm[r][k];
+            for (int q = 0; q < k; ++q) v -= Lm[r][q] * Lm[k][q];
+            Lm[r][k] = v / Lm[k][k];
+        }
+        double d = Cm[r][r];
+        for (int q = 0; q < r; ++q) d -= Lm[r][q] * Lm[r][q];
+        if (!(d > 0.0)) d = 0.0;
+        Lm[r][r] = std::sqrt(d);
+        for (int e = 0; e < E; ++e)
+            for (int k = 0; k <= r; ++k) feat[e][k] += Lm[r][k] * T[e][r];
+        double err = 0.0;
+        for (int e = 0; e < E; ++e)
+            for (int f = 0; f <= e; ++f) {
+                const double se = T[e][1], sf = T[f][1];
+                double v = std::exp(t * se * sf);
+                for (int k = 0; k <= r; ++k) v -= feat[e][k] * feat[f][k];
+                err = std::max(err, std::fabs(v) * std::exp(-0.5 * t * (se * se + sf * sf)));
+            }
+        if (err <= MGK_SEP_TOLERANCE) {
+            S.rank = r + 1;
+            for (int m = 0; m <= r; ++m)
+                for (int k = 0; k <= m; ++k) S.coef[m * MGK_SEP_MAX_RANK + k] = (float)Lm[m][k];
+            return S;
+        }
+        if (d == 0.0) return S;   // no further degree can be resolved in double
+    }
+    return S;
+}
+
+// How the sparse separable product of a pair with n2 columns divides its rank: the fewest
+// features executed, then the fewest passes; rk = 0 when no column count fits in LDS.
+MgkSepLayout sep_layout(int rank, int n2) {
+    MgkSepLayout L{0, 0, 0, 0};
+    for (int rk : {7, 6, 5, 4, 1}) {
+        if (mgk_sep_lds_bytes(rk, n2) > MGK_LDS_LIMIT_BYTES || (rk == 1) != (rank == 1)) continue;
+        const int passes = (rank + rk - 1) / rk;
+        if (L.rk == 0 || passes * rk < L.passes * L.rk || (passes * rk == L.passes * L.rk && passes < L.passes))
+            L = MgkSepLayout{rk, passes, mgk_sep_per_packet(rk), MGK_SEP_SLAB(rk) * 4};
+    }
+    return L;
+}
+
+// Product of the global-memory solver for one pair.
+enum LargePath { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
+
+// Estimated clocks per compute unit of one product, from measured rates: the row-staged product
+// evaluates about 7.5 entries per clk, the sparse separable product does about 30 multiply-adds per
+// clk and the dense one 100 (of the 128 the matrix cores can do).
+LargePath large_path(const mgk_ctx* ctx, const MgkSepBasis& S, bool dense_fits, const MgkGraphDesc& o, const MgkGraphDesc& i) {
+    const LargePath direct = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
+    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) return direct;
+    double best = (double)o.nnz * i.nnz / 7.5;
+    LargePath path = direct;
+    const MgkSepLayout L = sep_layout(S.rank, i.n);
+    if (L.rk > 0) {
+        const double c = (double)L.rk * L.passes * ((double)o.nnz * i.n + (double)o.n * i.nnz) / 30.0;
+        if (c < best) { best = c; path = kPathSep; }
+    }
+    const double op = (o.n + 31) & ~31, ip = (i.n + 63) & ~63;
+    if (dense_fits && ip <= MGK_SEP_DENSE_MAX_N) {
+        const double c = S.rank * (op * ip * o.n + op * ip * i.n) / 100.0;
+        if (c < best) { best = c; path = kPathSepDense; }
+    }
+    return path;
+}
+
 // Plan of one pair for the global-memory solver (any size).
 MgkLargePair plan_large(const MgkGraphDesc& a, const MgkGraphDesc& b, int32_t ia, int32_t ib, bool* swap,
                         int max_iter_param) {
@@ -576,6 +712,24 @@ MgkLargePair plan_large(const MgkGraphDesc& a, const MgkGraphDesc& b, int32_t ia
     P.nsteps = i.max_deg <= 1 ? 0 : i.max_deg <= 2 ? 1 : i.max_deg <= 4 ? 2 : i.max_deg <= 8 ? 3 : 4;
     P.atomic_rows = i.max_deg > MGK_LANE_GROUP ? 1 : 0;
     return P;
+}
+
+// Staging buffer of a call's records in pinned memory owned by the context; the previous use of
+// it is waited for (long finished).
+mgk_status pinned(mgk_ctx* ctx, size_t bytes) {
+    if (ctx->pin_busy) {
+        MGK_HIP(ctx, hipEventSynchronize(ctx->pin_event));
+        ctx->pin_busy = false;
+    }
+    if (bytes > ctx->pin_cap) {
+        if (ctx->pin) MGK_HIP(ctx, hipHostFree(ctx->pin));
+        ctx->pin = nullptr;
+        ctx->pin_cap = 0;
+        MGK_HIP(ctx, hipHostMalloc(&ctx->pin, bytes, hipHostMallocDefault));
+        ctx->pin_cap = bytes;
+    }
+    if (!ctx->pin_event) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->pin_event, hipEventDisableTiming));
+    return MGK_OK;
 }
 
 // Run Alg. 1 with global-memory vectors for a list of pairs (outer graphs from
@@ -671,21 +825,10 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
     int* dactive = (int*)ctx->lactive.p;
     float* vec = (float*)ctx->vec.p;
     // The pair records go through pinned memory owned by the context, so that the copy needs
-    // no wait; the previous use of that buffer is waited for instead (long finished).
+    // no wait.
     {
         const size_t bytes = (size_t)n_pairs * sizeof(MgkLargePair);
-        if (ctx->pin_busy) {
-            MGK_HIP(ctx, hipEventSynchronize(ctx->pin_event));
-            ctx->pin_busy = false;
-        }
-        if (bytes > ctx->pin_cap) {
-            if (ctx->pin) MGK_HIP(ctx, hipHostFree(ctx->pin));
-            ctx->pin = nullptr;
-            ctx->pin_cap = 0;
-            MGK_HIP(ctx, hipHostMalloc(&ctx->pin, bytes, hipHostMallocDefault));
-            ctx->pin_cap = bytes;
-        }
-        if (!ctx->pin_event) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->pin_event, hipEventDisableTiming));
+        if ((st = pinned(ctx, bytes)) != MGK_OK) return st;
         memcpy(ctx->pin, pairs.data(), bytes);
         MGK_HIP(ctx, hipMemcpyAsync(dpairs, ctx->pin, bytes, hipMemcpyHostToDevice, stream));
     }
@@ -727,6 +870,102 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
     return MGK_OK;
 }
 
+// Alg. 1 with global-memory vectors and the separable product (mgk_sep.hip) for a list of pairs
+// (outer graphs from A, inner from Bb).  Three launches per iteration (product with p^T a, update,
+// new direction); the outputs are formed behind the iterations the last such call needed, before
+// the host looks whether any pair still iterates, so that the GPU does not wait for that.
+mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, bool dense,
+                     const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, const MgkParams& prm) {
+    const int n_pairs = (int)pairs.size();
+    if (n_pairs == 0) return MGK_OK;
+    int64_t total = 0;
+    int max_npad = 0, max_iter = 0, max_n1 = 1, max_n2 = 1;
+    for (MgkLargePair& P : pairs) {
+        max_n1 = std::max(max_n1, P.n1);
+        max_n2 = std::max(max_n2, P.n2);
+        P.vec = total;
+        total += 5 * (int64_t)P.npad;
+        max_npad = std::max(max_npad, P.npad);
+        max_iter = std::max(max_iter, P.max_iter);
+    }
+    const int vec_blocks = std::max(1, std::min(2048, (max_npad + 1023) / 1024));
+    // pair records, their zeroed states and the counters of a call are one block and one copy
+    const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
+    const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
+    const size_t rec_bytes = active_at + 64;
+    mgk_status st;
+    if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
+    if ((st = ensure(ctx, ctx->lpairs, rec_bytes)) != MGK_OK) return st;
+    if (!ctx->active_host) MGK_HIP(ctx, hipHostMalloc((void**)&ctx->active_host, 64, hipHostMallocDefault));
+
+    // features of the batches' nonzeros (they depend on the edge kernel's parameters)
+    const mgk_batch* bt[2] = {A, Bb};
+    MgkSepList sl[2] = {};
+    const float* F[2] = {};
+    const int gi = L.per_packet == 8 ? 1 : 0;
+    for (int k = 0; k < 2; ++k) {
+        if (k == 1 && Bb == A) { sl[1] = sl[0]; F[1] = F[0]; break; }
+        hipError_t e;
+        if (dense) {
+            if ((st = ensure(ctx, ctx->sep_dense[k], (size_t)bt[k]->dense_floats * S.rank * sizeof(float))) != MGK_OK) return st;
+            F[k] = (const float*)ctx->sep_dense[k].p;
+            e = mgk_launch_sep_dense_pack(bt[k]->dev, S, bt[k]->max_n, (float*)ctx->sep_dense[k].p, stream);
+        } else {
+            sl[k].total = bt[k]->packets[gi];
+            sl[k].gptr = bt[k]->gptr_dev[gi];
+            if ((st = ensure(ctx, ctx->sep_packets[k], std::max<size_t>(256, (size_t)L.passes * sl[k].total * 64 * sizeof(float)))) != MGK_OK) return st;
+            sl[k].packets = (const float*)ctx->sep_packets[k].p;
+            e = mgk_launch_sep_pack(bt[k]->dev, S, L, bt[k]->max_n, sl[k].gptr, sl[k].total, (float*)ctx->sep_packets[k].p, stream);
+        }
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
+    }
+
+    if ((st = pinned(ctx, rec_bytes)) != MGK_OK) return st;
+    char* rec = static_cast<char*>(ctx->pin);
+    memset(rec, 0, rec_bytes);
+    memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
+    reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
+    MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, rec_bytes, hipMemcpyHostToDevice, stream));
+    MGK_HIP(ctx, hipEventRecord(ctx->pin_event, stream));
+    ctx->pin_busy = true;
+    MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
+    MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
+    int* dactive = (int*)((char*)ctx->lpairs.p + active_at);
+    float* vec = (float*)ctx->vec.p;
+
+    auto product = [&](int it, bool check_only) {
+        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, F[0], F[1], S.rank, dpairs, dstate, vec, prm, n_pairs,
+                                            max_n1, max_n2, it, check_only, stream)
+                     : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dstate, vec, prm, n_pairs,
+                                          max_n1, max_n2, it, check_only, stream);
+    };
+    hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, stream);
+    if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "init launch failed: %s", hipGetErrorString(e));
+    int it = 0;
+    const int first_batch = std::max(1, std::min(max_iter, ctx->large_iter_guess));
+    ctx->active_host[0] = n_pairs;
+    while (it < max_iter && ctx->active_host[0] > 0) {
+        const int upto = it == 0 ? first_batch : std::min(max_iter, it + 4);
+        for (; it < upto; ++it) {
+            if ((e = product(it, false)) == hipSuccess)
+                e = mgk_launch_large_vectors(dpairs, dstate, vec, n_pairs, vec_blocks, it, prm.rtol2, dactive, stream);
+            if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "iteration launch failed: %s", hipGetErrorString(e));
+        }
+        e = mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 0, stream);
+        if (e == hipSuccess) e = product(0, true);
+        if (e == hipSuccess)
+            e = mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 1, stream);
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
+        MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
+        MGK_HIP(ctx, hipStreamSynchronize(stream));
+        ctx->pin_busy = false;
+    }
+    if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
+    log_launch(ctx, "%s rank=%d pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)",
+               dense ? "mgk_sep_dense_kernel" : "mgk_sep_xmv_kernel", S.rank, n_pairs, it);
+    return MGK_OK;
+}
+
 mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl,
                        const MgkOutputs& out, hipStream_t stream) {
     const MgkParams prm = make_params(ctx, X);
@@ -759,26 +998,54 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             done += chunk;
         }
     }
-    // Pairs with vectors in global memory go in groups: the pair index is a grid dimension
-    // (at most 65535) and every pair of a group holds 5 vectors of scratch at the same time.
+    if (jl.large[0].empty() && jl.large[1].empty()) return MGK_OK;
+    // ---- pairs with vectors in global memory: the product of each from the current edge kernel
+    const MgkSepBasis none{};
+    const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
+    const MgkSepBasis& S = may_sep ? sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi)) : none;
+    constexpr int64_t kMaxDenseBytes = (int64_t)8 << 30;   // both batches' dense F_k
+    const bool dense_fits = (X->dense_floats + (X == Y ? 0 : Y->dense_floats)) * S.rank * 4 <= kMaxDenseBytes;
+    std::vector<MgkLargePair> lists[2][kPaths];
+    for (int swapped = 0; swapped < 2; ++swapped)
+        for (const MgkLargePair& asked : jl.large[swapped]) {
+            MgkLargePair P = asked;
+            int sw = swapped;
+            if (S.rank > 0 && P.n2 > P.n1) {   // separable product: T has a column per inner vertex
+                std::swap(P.g1, P.g2);
+                std::swap(P.n1, P.n2);
+                if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
+                if (X != Y) sw = 1 - sw;
+            }
+            const mgk_batch* A = sw ? Y : X;
+            const mgk_batch* B = sw ? X : Y;
+            const LargePath path = large_path(ctx, S, dense_fits, A->graphs[P.g1], B->graphs[P.g2]);
+            if (path == kPathSep || path == kPathSepDense) lists[sw][path].push_back(P);
+            else lists[swapped][path].push_back(asked);
+        }
+    // In groups: the pair index is a grid dimension (at most 65535) and every pair of a group
+    // holds 5 vectors of scratch at the same time.
     constexpr size_t kMaxPairsPerGroup = 4096;
     constexpr int64_t kMaxScratchFloats = (int64_t)1 << 31;   // 8 GiB
-    for (int dense = 0; dense < 2; ++dense)
+    for (int path = 0; path < kPaths; ++path)
         for (int swapped = 0; swapped < 2; ++swapped) {
-            const std::vector<MgkLargePair>& all = jl.large[swapped][dense];
+            std::vector<MgkLargePair>& all = lists[swapped][path];
+            const mgk_batch* A = swapped ? Y : X;
+            const mgk_batch* B = swapped ? X : Y;
             size_t first = 0;
             while (first < all.size()) {
                 size_t last = first;
                 int64_t floats = 0;
+                int max_n2 = 1;
                 while (last < all.size() && last - first < kMaxPairsPerGroup &&
                        (last == first || floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats)) {
                     floats += 5 * (int64_t)all[last].npad;
+                    max_n2 = std::max(max_n2, all[last].n2);
                     ++last;
                 }
                 std::vector<MgkLargePair> group(all.begin() + (std::ptrdiff_t)first, all.begin() + (std::ptrdiff_t)last);
-                const mgk_status st = swapped
-                    ? solve_large(ctx, Y, X, 1, 0, std::move(group), dense != 0, out, stream, prm, weighted)
-                    : solve_large(ctx, X, Y, 0, 1, std::move(group), dense != 0, out, stream, prm, weighted);
+                const mgk_status st = path == kPathSep || path == kPathSepDense
+                    ? solve_sep(ctx, A, B, std::move(group), path == kPathSepDense, S, sep_layout(S.rank, max_n2), out, stream, prm)
+                    : solve_large(ctx, A, B, swapped, 1 - swapped, std::move(group), path == kPathDenseTiles, out, stream, prm, weighted);
                 if (st != MGK_OK) return st;
                 first = last;
             }
@@ -812,7 +1079,7 @@ void mgk_destroy(mgk_ctx* ctx) {
     if (!ctx) return;
     if (ctx->pair_jobs.dev) (void)hipFree(ctx->pair_jobs.dev);
     for (DevBuf* b : {&ctx->exp_outer[0], &ctx->exp_outer[1], &ctx->exp_inner[0], &ctx->exp_inner[1],
-                      &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
+                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
                       &ctx->dense_tiles[0][0], &ctx->dense_tiles[0][1], &ctx->dense_tiles[0][2],
                       &ctx->dense_tiles[1][0], &ctx->dense_tiles[1][1], &ctx->dense_tiles[1][2]})
         if (b->p) (void)hipFree(b->p);
@@ -1028,6 +1295,13 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     std::vector<MgkSellNbr> sell_nbr;
     B->sell_desc.reserve((size_t)n_graphs);
     std::vector<MgkEntry> list_outer, list_inner;   // nonzero lists for the register-resident solver
+    std::vector<int32_t> gptr[2], deg_order;       // packets of the separable product, rows by degree
+    std::vector<int64_t> dense_off((size_t)n_graphs);
+    constexpr int kPerPacket[2] = {2, 8};
+    for (auto& v : gptr) v.reserve((size_t)(tot_v / 4 + 2 * (int64_t)n_graphs));
+    deg_order.resize((size_t)tot_v);
+    B->label_lo = INFINITY;
+    B->label_hi = -INFINITY;
     std::vector<int32_t> regs_split;                // its division of every graph's rows among wavefronts
     list_outer.reserve((size_t)(2 * tot_e));
     // label attributes in the order of the two lists, attribute-major; filled after the loop
@@ -1168,6 +1442,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             const float ev = edge_label ? edge_label[k * D] : 0.f;
             if (wv != 1.f) B->weighted = true;
             label_sum += 2.0 * ev;
+            B->label_lo = std::min(B->label_lo, ev);
+            B->label_hi = std::max(B->label_hi, ev);
             const int a = perm[src[k]], b = perm[dst[k]];
             for (int dir = 0; dir < 2; ++dir) {
                 const int i = dir ? b : a, j = dir ? a : b;
@@ -1224,6 +1500,26 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         }
         gd.max_deg = max_deg;
         gd.lane_len = (slot + 63) & ~63;
+        // rows by descending degree (counting sort), packets per row
+        {
+            cursor.assign((size_t)max_deg + 2, 0);
+            for (int i = 0; i < n; ++i) cursor[(size_t)(max_deg - deg[i]) + 1]++;
+            for (int d = 0; d <= max_deg; ++d) cursor[(size_t)d + 1] += cursor[(size_t)d];
+            for (int i = 0; i < n; ++i) deg_order[(size_t)v0 + cursor[(size_t)(max_deg - deg[i])]++] = i;
+            gd.qoff = (int32_t)gptr[0].size();
+            for (int i = 0; i < n; i += 4) {   // four rows of adjacent degrees: the first has the most packets
+                const int d = deg[deg_order[(size_t)v0 + i]];
+                for (int q = 0; q < 2; ++q) {
+                    gptr[q].push_back(B->packets[q]);
+                    B->packets[q] += (d + kPerPacket[q] - 1) / kPerPacket[q];
+                }
+            }
+            for (int q = 0; q < 2; ++q) gptr[q].push_back(B->packets[q]);
+            dense_off[(size_t)g] = B->dense_floats;
+            const int64_t np = (n + 63) & ~63;
+            B->dense_floats += np * np;
+            B->max_n = std::max(B->max_n, n);
+        }
         gd.loff = (int32_t)lanes_total;
         {
             int32_t bounds[MGK_REGS_SPLIT_STRIDE];
@@ -1302,6 +1598,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             B->sell_desc.push_back(sd);
         }
     }
+    if (!(B->label_lo <= B->label_hi)) B->label_lo = B->label_hi = 0.f;   // no edges
     B->n_vertices = tot_v;
     B->nnz = (int64_t)B->w.size();
     B->n_tiles = (int64_t)B->tiles.size();
@@ -1337,6 +1634,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     }
     const size_t o_ao = append_bytes(blob, attr_outer);
     const size_t o_ai = append_bytes(blob, attr_inner);
+    const size_t o_pk[2] = {append_bytes(blob, gptr[0]), append_bytes(blob, gptr[1])};
+    const size_t o_do = append_bytes(blob, deg_order);
+    const size_t o_df = append_bytes(blob, dense_off);
     const size_t o_sd = append_bytes(blob, B->sell_desc);
     const size_t o_sv = append_bytes(blob, sell_vtx);
     const size_t o_sn = append_bytes(blob, sell_nbr);
@@ -1372,6 +1672,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->dev.regs_split = reinterpret_cast<const int32_t*>(base + o_sp);
     B->dev.attr_outer = reinterpret_cast<const float*>(base + o_ao);
     B->dev.attr_inner = reinterpret_cast<const float*>(base + o_ai);
+    for (int q = 0; q < 2; ++q) B->gptr_dev[q] = reinterpret_cast<const int32_t*>(base + o_pk[q]);
+    B->dev.deg_order = reinterpret_cast<const int32_t*>(base + o_do);
+    B->dev.dense_off = reinterpret_cast<const int64_t*>(base + o_df);
     B->dev.sell_desc = reinterpret_cast<const MgkSellDesc*>(base + o_sd);
     B->dev.sell_vtx = reinterpret_cast<const MgkSellVertex*>(base + o_sv);
     B->dev.sell_nbr = reinterpret_cast<const MgkSellNbr*>(base + o_sn);
@@ -1446,7 +1749,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     if (G * G >= (int64_t)1 << 31) return fail(ctx, MGK_ELIMIT, "Gram matrix too large for 32-bit output indices");
     if (batch->gram_jobs.dev != nullptr &&
         (batch->gram_jobs_waves != ctx->waves || batch->gram_jobs_max_iter != ctx->max_iter ||
-         batch->gram_jobs_limit != ctx->onchip_limit || batch->gram_jobs_tile_path != ctx->tile_path ||
+         batch->gram_jobs_limit != ctx->onchip_limit ||
          batch->gram_jobs_cache != ctx->product_cache || batch->gram_jobs_sorted != ctx->cost_sorted ||
          batch->gram_jobs_attr_dim != attr_dim_of(ctx))) {
         MGK_HIP(ctx, hipStreamSynchronize(stream));  // launch shape changed: rebuild the job list
@@ -1457,7 +1760,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         // a4: job list, one job per unordered pair, kept with the batch
         std::vector<HostJob> jobs;
         jobs.reserve((size_t)(G * (G + 1) / 2));
-        for (auto& a : batch->gram_jobs.large) for (auto& v : a) v.clear();
+        for (auto& v : batch->gram_jobs.large) v.clear();
         // the plans of the G (G + 1) / 2 pairs are independent: rows of the triangle in turn on
         // several threads, row i starting at pair i G - i (i - 1) / 2
         std::vector<PairPlan> plans((size_t)(G * (G + 1) / 2));
@@ -1503,7 +1806,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                     MgkLargePair P = plan_large(batch->graphs[i], batch->graphs[j], (int32_t)i, (int32_t)j, &sw, ctx->max_iter);
                     P.out0 = hj.job.out0;
                     P.out1 = hj.job.out1;
-                    batch->gram_jobs.large[0][use_dense_tiles(ctx, batch->graphs[i], batch->graphs[j]) ? 1 : 0].push_back(P);
+                    batch->gram_jobs.large[0].push_back(P);
                     continue;
                 }
                 jobs.push_back(hj);
@@ -1512,7 +1815,6 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         batch->gram_jobs_waves = ctx->waves;
         batch->gram_jobs_max_iter = ctx->max_iter;
         batch->gram_jobs_limit = ctx->onchip_limit;
-        batch->gram_jobs_tile_path = ctx->tile_path;
         batch->gram_jobs_cache = ctx->product_cache;
         batch->gram_jobs_sorted = ctx->cost_sorted;
         batch->gram_jobs_attr_dim = attr_dim_of(ctx);
@@ -1541,7 +1843,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     // Either graph of a pair may be the outer operand; jobs whose outer graph
     // comes from Y are launched with the batch arguments exchanged.
     std::vector<HostJob> jobs((size_t)n_pairs);
-    std::vector<MgkLargePair> large[2][2];
+    std::vector<MgkLargePair> large[2];
     for (int64_t k = 0; k < n_pairs; ++k) {
         const int32_t i = i_host[k], j = j_host[k];
         if (i < 0 || i >= X->n_graphs || j < 0 || j >= Y->n_graphs)
@@ -1571,7 +1873,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
             MgkLargePair P = plan_large(X->graphs[i], Y->graphs[j], i, j, &sw, ctx->max_iter);
             P.out0 = (int32_t)k;
             P.out1 = sw ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
-            large[(sw && X != Y) ? 1 : 0][use_dense_tiles(ctx, X->graphs[i], Y->graphs[j]) ? 1 : 0].push_back(P);
+            large[(sw && X != Y) ? 1 : 0].push_back(P);
             hj.waves = 0;
         }
     }
@@ -1602,8 +1904,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     }
     mgk_status st = build_job_list(ctx, jobs, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
     if (st != MGK_OK) return st;
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b) ctx->pair_jobs.large[a][b] = std::move(large[a][b]);
+    for (int a = 0; a < 2; ++a) ctx->pair_jobs.large[a] = std::move(large[a]);
     ctx->pair_jobs_stream = stream;
     ctx->pair_jobs_busy = true;
     if (x_dev) {

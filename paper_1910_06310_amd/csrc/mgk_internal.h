@@ -11,7 +11,7 @@
 #define MGK_HD
 #endif
 
-// One graph of a batch, as the device sees it (40 bytes).  All offsets index
+// One graph of a batch, as the device sees it.  All offsets index
 // the batch-wide arrays of MgkBatchDev.
 struct MgkGraphDesc {
     int32_t n;            // vertices
@@ -27,6 +27,7 @@ struct MgkGraphDesc {
     int32_t loff;         // first lane slot of the graph in batch-wide expanded inner lists
     int32_t regs_runs;    // longest run of outer nonzeros of one wavefront under regs_split:
                           // 4 wavefronts in bits 0-15, 8 wavefronts in bits 16-31
+    int32_t qoff;         // first entry in the packet group pointers (one per four vertices)
 };
 
 // Lane layout of a graph used as the inner operand of the on-chip XMV: the
@@ -86,6 +87,8 @@ struct MgkBatchDev {
     const struct MgkSellDesc* sell_desc;    // per graph, see MgkSellDesc
     const struct MgkSellVertex* sell_vtx;   // records of the owner-computes solver
     const struct MgkSellNbr* sell_nbr;
+    const int32_t* deg_order;   // per graph (index voff): its vertices by descending number of nonzeros
+    const int64_t* dense_off;   // per graph: sum over the graphs before it of (n rounded up to 64)^2
     int32_t n_graphs, n_tiles_total, nnz_total, lanes_total;
     int32_t label_dim;        // attributes per edge label (1 for plain scalar labels)
     int32_t uniform_start;    // 1: no starting probabilities were given, p_i = 1/n on every graph
@@ -360,6 +363,43 @@ static inline int32_t mgk_sell_need(const MgkSellDesc& o, const MgkSellDesc& i, 
     return need;
 }
 
+// ---- separable edge kernel (mgk_sep.hip) --------------------------------------
+// kappa_e(e, e') = sum_{k < rank} phi_k(e) phi_k(e') on the label range of the batches, with
+//   phi_k(e) = exp2(-(e_scale u)^2) sum_m coef[m][k] T_m(u / R),  u = e - center,
+// T_m the Chebyshev polynomials: exp(-(e - e')^2 / 2 l^2) is the product of two Gaussians and
+// exp(u u' / l^2), whose Chebyshev coefficients on [-R, R]^2 form a positive definite matrix
+// that falls off faster than geometrically; coef is its Cholesky factor.  The constant kernel
+// is rank 1.  The host takes the smallest rank whose error over the range is at most
+// MGK_SEP_TOLERANCE, half a unit in the last place of the largest value of kappa_e.
+#define MGK_SEP_MAX_RANK 20
+#define MGK_SEP_TOLERANCE 3e-8
+struct MgkSepBasis {
+    int32_t rank;
+    float center, inv_r, e_scale;
+    float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];   // [m][k]
+};
+// How the rank is divided for the sparse product: `passes` passes of `rk` (1, 4, 5, 6 or 7)
+// features each, per_packet nonzeros to a packet of 16 words (rk coefficients and one offset
+// per nonzero).  slab_bytes: LDS bytes of one column of T.
+struct MgkSepLayout {
+    int32_t rk, passes, per_packet, slab_bytes;
+};
+#define MGK_SEP_ROWS 16       // outer rows per workgroup: one row of 16 lanes
+#define MGK_SEP_SLAB(rk) ((rk) == 1 ? 17 : 64 * (((rk) + 3) / 4) + 4)   // words per column of T
+#define MGK_SEP_DENSE_MAX_N 1024
+static inline MGK_HD int32_t mgk_sep_per_packet(int32_t rk) { return rk == 1 ? 8 : 2; }
+static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
+    return 4 * ((int64_t)MGK_SEP_SLAB(rk) * n2 + (int64_t)MGK_SEP_ROWS * (n2 | 1));
+}
+// Packets of a batch, in steps of 64 words (four rows of adjacent rank in deg_order, one packet
+// each): pass q at packets + q total 64; group t of graph g has steps gptr[qoff + t] ..
+// gptr[qoff + t + 1].  At least one step per batch is allocated.
+struct MgkSepList {
+    const float* packets;
+    const int32_t* gptr;
+    int32_t total;
+};
+
 // ---- solver with vectors in global memory (pairs too large for LDS) ---------
 // Expanded nonzero lists of a whole batch, rebuilt per call because the label
 // scaling depends on the edge-kernel parameters:
@@ -425,6 +465,7 @@ struct MgkPairState {
     float bb;       // b^T b
     float kval;
     int32_t iters, done, flag;
+    int32_t check;  // a stopped pair whose true residual is being formed
     int32_t growth; // bits of max_i x_i / (M^{-1} b)_i >= 1: how far the solution exceeds the Jacobi guess
 };
 

@@ -705,6 +705,8 @@ __global__ __launch_bounds__(256) void mgk_large_update_kernel(const MgkLargePai
 // Every workgroup takes the same decision from the sums of this iteration, which no one
 // writes during this kernel; one thread per pair records it (a workgroup that starts after
 // that and sees the pair marked done would have stopped anyway).
+// CLEAR: the next product adds to y or leaves parts of it alone.
+template <bool CLEAR>
 __global__ __launch_bounds__(256) void mgk_large_pupdate_kernel(const MgkLargePair* pairs,
                                                                 MgkPairState* state, float* vec, int it,
                                                                 float rtol2, int* n_active) {
@@ -729,7 +731,7 @@ __global__ __launch_bounds__(256) void mgk_large_pupdate_kernel(const MgkLargePa
     float* y = p + 2 * (int64_t)P.npad;
     for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
         p[idx] = __builtin_fmaf(beta, p[idx], y[idx]);
-        y[idx] = 0.f;
+        if (CLEAR) y[idx] = 0.f;
     }
 }
 
@@ -767,12 +769,13 @@ __global__ __launch_bounds__(256) void mgk_large_final_kernel(MgkBatchDev X, Mgk
 }
 
 // ---- check of pairs with a large growth factor: y = XMV(x), true residual b - (M x - y) ----
-// Marks those pairs as running again (done = 0) with p = x and y = 0, so that the product
-// kernels of one more launch take them; all other pairs stay done.
+// Marks those pairs (check = 1) with p = x and y = 0, so that one more product takes them;
+// rerun: the product goes by `done`, which is cleared for them until the outputs are stored
+// (only where no pair still iterates).
 __global__ __launch_bounds__(256) void mgk_large_verify_prepare_kernel(const MgkLargePair* pairs,
-                                                                       MgkPairState* state, float* vec) {
+                                                                       MgkPairState* state, float* vec, int rerun) {
     MgkPairState& st = state[blockIdx.y];
-    if (__int_as_float(st.growth) <= MGK_VERIFY_GROWTH) return;
+    if (__int_as_float(st.growth) <= MGK_VERIFY_GROWTH || (!rerun && !st.done)) return;
     const MgkLargePair P = pairs[blockIdx.y];
     const float* x = vec + P.vec;
     float* p = vec + P.vec + 2 * (int64_t)P.npad;
@@ -782,7 +785,11 @@ __global__ __launch_bounds__(256) void mgk_large_verify_prepare_kernel(const Mgk
         y[idx] = 0.f;
     }
     // every workgroup of the pair writes the same values; the product kernels come later
-    if (threadIdx.x == 0) { st.done = 0; st.rr[0] = 0.f; }
+    if (threadIdx.x == 0) {
+        st.check = 1;
+        st.rr[0] = 0.f;
+        if (rerun) st.done = 0;
+    }
 }
 
 __global__ __launch_bounds__(256) void mgk_large_verify_residual_kernel(MgkBatchDev X, MgkBatchDev Y,
@@ -791,7 +798,7 @@ __global__ __launch_bounds__(256) void mgk_large_verify_residual_kernel(MgkBatch
                                                                         MgkParams prm) {
     __shared__ float red[8];
     MgkPairState& st = state[blockIdx.y];
-    if (st.done) return;   // only the pairs under check are marked as running
+    if (!st.check) return;
     const MgkLargePair P = pairs[blockIdx.y];
     const int N = P.n1 * P.n2;
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
@@ -823,16 +830,19 @@ __global__ void mgk_large_store_kernel(const MgkLargePair* pairs, MgkPairState* 
     const MgkLargePair P = pairs[k];
     MgkPairState& s = state[k];
     int flag = s.flag;
-    if (!s.done) {   // was under check
+    if (s.check) {
         const float growth = __int_as_float(s.growth);
         const float rel = sqrtf(s.rr[0] / s.bb);
         if (flag == 0 && rel * growth > MGK_VERIFY_ACCURACY) flag = 3;
         s.done = 1;
+        s.check = 0;
     }
     K[P.out0] = s.kval;
     if (P.out1 >= 0) K[P.out1] = s.kval;
     if (iters) { iters[P.out0] = s.iters; if (P.out1 >= 0) iters[P.out1] = s.iters; }
     if (flags) { flags[P.out0] = flag; if (P.out1 >= 0) flags[P.out1] = flag; }
+    s.kval = 0.f;   // outputs of a pair that still iterates are formed again
+    s.growth = 0;
 }
 
 // ---- normalised Gram matrix: K_ij / sqrt(K_ii K_jj) --------------------------------------
@@ -913,7 +923,7 @@ hipError_t mgk_launch_large_iteration(const MgkBatchDev& X, const MgkBatchDev& Y
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mgk_large_dot_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
     hipLaunchKernelGGL(mgk_large_update_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
-    hipLaunchKernelGGL(mgk_large_pupdate_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it, prm.rtol2, n_active);
+    hipLaunchKernelGGL(mgk_large_pupdate_kernel<true>, gv, dim3(256), 0, stream, pairs, state, vec, it, prm.rtol2, n_active);
     return hipGetLastError();
 }
 
@@ -986,13 +996,35 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
     hipLaunchKernelGGL(mgk_large_final_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, out, prm);
     // one more product and the true residual for the pairs whose solution grew far beyond the
     // Jacobi guess (none on well-conditioned workloads: these launches then return at once)
-    hipLaunchKernelGGL(mgk_large_verify_prepare_kernel, gv, dim3(256), 0, stream, pairs, state, vec);
+    hipLaunchKernelGGL(mgk_large_verify_prepare_kernel, gv, dim3(256), 0, stream, pairs, state, vec, 1);
     hipError_t e = launch_large_xmv(X, Y, EX, EY, pairs, state, vec, prm, weighted, n_pairs, xmv_blocks, DX, DY,
                                     rows_threads, rows_lds_bytes, rows_chunks, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mgk_large_verify_residual_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, prm);
     hipLaunchKernelGGL(mgk_large_store_kernel, dim3((n_pairs + 63) / 64), dim3(64), 0, stream, pairs, state,
                        n_pairs, out);
+    return hipGetLastError();
+}
+
+hipError_t mgk_launch_large_vectors(const MgkLargePair* pairs, MgkPairState* state, float* vec, int n_pairs, int vec_blocks,
+                                    int it, float rtol2, int* n_active, hipStream_t stream) {
+    const dim3 gv(vec_blocks, n_pairs);
+    hipLaunchKernelGGL(mgk_large_update_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
+    hipLaunchKernelGGL(mgk_large_pupdate_kernel<false>, gv, dim3(256), 0, stream, pairs, state, vec, it, rtol2, n_active);
+    return hipGetLastError();
+}
+
+hipError_t mgk_launch_large_outputs(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair* pairs, MgkPairState* state,
+                                    float* vec, const MgkParams& prm, int n_pairs, int vec_blocks, const MgkOutputs& out,
+                                    int part, hipStream_t stream) {
+    const dim3 gv(vec_blocks, n_pairs);
+    if (part == 0) {
+        hipLaunchKernelGGL(mgk_large_final_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, out, prm);
+        hipLaunchKernelGGL(mgk_large_verify_prepare_kernel, gv, dim3(256), 0, stream, pairs, state, vec, 0);
+    } else {
+        hipLaunchKernelGGL(mgk_large_verify_residual_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, prm);
+        hipLaunchKernelGGL(mgk_large_store_kernel, dim3((n_pairs + 63) / 64), dim3(64), 0, stream, pairs, state, n_pairs, out);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,451 @@
+// Off-diagonal product of the global-memory solver through a separable edge kernel
+// (mgk_sep_dev.h): y = sum_k F_k P F'_k^T instead of one kappa_e evaluation per pair of
+// nonzeros.  Two forms:
+//
+//  * mgk_sep_xmv_kernel: sparse.  One workgroup takes 16 outer rows.  Stage 1,
+//    T_k[i, j'] = sum_j F_k[i, j] P[j, j']: lanes are columns j', the nonzeros of row i are
+//    uniform operands.  Stage 2, y[i, i'] = sum_j' sum_k F'_k[i', j'] T_k[i, j']: lanes are
+//    16 rows x 4 columns, T comes from LDS as 16-byte reads and the coefficients of a
+//    column's nonzeros are shared by its 16 lanes.  Both stages take their coefficients
+//    from packets of 16 words that hold whole nonzeros.
+//  * mgk_sep_dense_kernel: well-filled graphs.  F_k and F'_k as dense matrices, both
+//    stages on the matrix cores (v_mfma_f32_32x32x2_f32), T_k of 32 outer rows in LDS.
+//
+// Both also form the workgroup's share of p^T (M p - y).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "mgk_internal.h"
+#include "mgk_launch.h"
+#include "mgk_sep_dev.h"
+#include "mgk_wave.h"
+
+namespace {
+
+// phi_k(e) for the label e (see MgkSepBasis), in double so that the features are correctly
+// rounded: they are made once per call and used in every iteration.
+__device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const float* coef, float label, int k) {
+    const double u = (double)label - (double)S.center;
+    const double s = u * (double)S.inv_r, g = u * (double)S.e_scale;
+    double t0 = 1.0, t1 = s, v = 0.0;
+    for (int m = 0; m < S.rank; ++m) {
+        v = fma((double)coef[m * MGK_SEP_MAX_RANK + k], t0, v);
+        const double t2 = fma(2.0 * s, t1, -t0);
+        t0 = t1;
+        t1 = t2;
+    }
+    return (float)(v * exp2(-g * g));
+}
+
+// Packets of the graphs of a batch: the vertices of a graph in order of descending degree, in
+// groups of four; step t of a group holds packet t of its four rows, 16 words each.  A
+// packet holds per_packet nonzeros of its row: rk coefficients A_ij phi_k and the byte offset of
+// the slab of column j each; absent nonzeros have coefficients 0 and offset 0.  One wavefront
+// per group.
+__global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepLayout L,
+                                                           const int32_t* gptr, int total, float* out) {
+    __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
+    for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
+    __syncthreads();
+    const MgkGraphDesc g = B.graphs[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int slot = lane & 15, u = slot / (L.rk + 1), kk = slot - u * (L.rk + 1);
+    for (int grp = blockIdx.x * 4 + wave; grp * 4 < g.n; grp += gridDim.x * 4) {
+        const int p0 = gptr[g.qoff + grp], p1 = gptr[g.qoff + grp + 1];
+        const int pos = grp * 4 + (lane >> 4);
+        const int row = B.deg_order[g.voff + min(pos, g.n - 1)];
+        const int z0 = B.rowptr[g.voff + row];
+        const int z1 = pos >= g.n ? z0 : row + 1 < g.n ? B.rowptr[g.voff + row + 1] : g.nnz;
+        for (int p = p0; p < p1; ++p) {
+            const int z = z0 + (p - p0) * L.per_packet + u;
+            const bool on = u < L.per_packet && z < z1;
+            const MgkEntry e = B.list_outer[g.zoff + (on ? z : 0)];
+            const float w = __uint_as_float(e.w & 0x7fffffffu);
+            for (int q = 0; q < L.passes; ++q) {
+                const int k = q * L.rk + kk;
+                float v = 0.f;
+                if (on && kk < L.rk && k < S.rank) v = w * sep_feature(S, coef, __uint_as_float(e.z), k);
+                if (on && kk == L.rk) v = __uint_as_float(e.y * (uint32_t)L.slab_bytes);
+                out[((int64_t)q * total + p) * 64 + lane] = v;
+            }
+        }
+    }
+}
+
+// Dense F_k of every graph: F[(dense_off[g] * rank) + (k np + i) np + j], np = n rounded up to 64,
+// zero where there is no edge.  One wavefront per (row, graph): clears the row, then fills it.
+__global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, float* out) {
+    __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
+    for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
+    __syncthreads();
+    const MgkGraphDesc g = B.graphs[blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int np = (g.n + 63) & ~63;
+    float* F = out + B.dense_off[blockIdx.y] * S.rank;
+    for (int row = blockIdx.x * 4 + wave; row < np; row += gridDim.x * 4) {
+        for (int k = 0; k < S.rank; ++k)
+            for (int c = lane; c < np; c += 64) F[((int64_t)k * np + row) * np + c] = 0.f;
+        if (row >= g.n) continue;
+        __threadfence_block();   // the stores below go to addresses other lanes have just cleared
+        __builtin_amdgcn_wave_barrier();
+        const int z0 = B.rowptr[g.voff + row];
+        const int z1 = row + 1 < g.n ? B.rowptr[g.voff + row + 1] : g.nnz;
+        for (int z = z0 + lane; z < z1; z += 64) {
+            const MgkEntry e = B.list_outer[g.zoff + z];
+            const float w = __uint_as_float(e.w & 0x7fffffffu);
+            for (int k = 0; k < S.rank; ++k)
+                F[((int64_t)k * np + row) * np + e.y] = w * sep_feature(S, coef, __uint_as_float(e.z), k);
+        }
+    }
+}
+
+// Workgroup b of a 1-D grid -> (pair, block of the pair).  Consecutive workgroups go to the
+// eight XCDs in turn: all blocks of a pair get the same b mod 8, so that its vectors and its
+// graphs' coefficients are fetched into one XCD's L2 only.
+__device__ __forceinline__ void sep_block(int b, int blocks, int* pair, int* blk) {
+    const int slot = b >> 3;
+    const int q = slot / blocks;
+    *pair = q * 8 + (b & 7);
+    *blk = slot - q * blocks;
+}
+
+// One partial sum per wavefront into *dst (several wavefronts of the pair add to it).
+__device__ __forceinline__ void wave_accumulate(float v, float* dst, int lane) {
+    v = wave_sum(v);
+    if (lane == 0) atomicAdd(dst, v);
+}
+
+// Clears the accumulators of r^T z and r^T r that the update of this iteration adds to (their
+// values, from two iterations ago, were last read by the kernel before this one).
+__device__ __forceinline__ void clear_sums(MgkPairState& st, int it) {
+    st.rz[it & 1] = 0.f;
+    st.rr[it & 1] = 0.f;
+}
+
+// Bound by the vector ALUs and the LDS about equally: per nonzero and 64 results RK
+// multiply-adds (1.15 RK clk per CU) against 4 RK bytes x 64 from LDS in stage 2.
+template <int RK, int G>
+__global__ __launch_bounds__(1024) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY,
+                                                           MgkSepLayout L, const MgkLargePair* pairs,
+                                                           MgkPairState* state, float* vec, MgkParams prm,
+                                                           int n_pairs, int blocks, int it, int check_only) {
+    extern __shared__ __align__(16) float lds[];
+    constexpr int SLAB = MGK_SEP_SLAB(RK);            // words
+    int pair, blk;
+    sep_block(blockIdx.x, blocks, &pair, &blk);
+    if (pair >= n_pairs) return;
+    MgkPairState& st = state[pair];
+    if (check_only ? !st.check : st.done) return;
+    const MgkLargePair P = pairs[pair];
+    const int i0 = blk * MGK_SEP_ROWS;
+    if (i0 >= P.n1) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NW = 16;
+    if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
+    const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
+    const int n1 = P.n1, n2 = P.n2, rows = min(MGK_SEP_ROWS, n1 - i0);
+    const float* p = vec + P.vec + 2 * (int64_t)P.npad;
+    float* y = vec + P.vec + 4 * (int64_t)P.npad;
+    const int32_t* order1 = X.deg_order + g1.voff;
+    const int32_t* order2 = Y.deg_order + g2.voff;
+    float* tile = lds + SLAB * n2;                    // y of the 16 rows, row stride n2 | 1
+    const int tp = n2 | 1;
+    char* slabs = reinterpret_cast<char*>(lds);
+    const int groups2 = (n2 + 3) >> 2;
+    const int32_t* gp1 = SX.gptr + g1.qoff;
+    const int32_t* gp2 = SY.gptr + g2.qoff;
+    for (int q = 0; q < L.passes; ++q) {
+        // ---- stage 1: one row per wavefront (rows of a workgroup have similar degrees)
+        for (int ii = wave; ii < rows; ii += NW) {
+            const int grp = (i0 + ii) >> 2;
+            const int gb = gp1[grp];
+            const float* pk = SX.packets + ((int64_t)q * SX.total + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
+            stage1_row<RK, G>(pk, gp1[grp + 1] - gb, PGlobal{reinterpret_cast<const char*>(p), (uint32_t)n2 * 4u}, n2, lane,
+                              slabs, (RK == 1 ? 4u : 16u) * (uint32_t)ii);
+        }
+        __syncthreads();
+        // ---- stage 2: 16 rows x 4 columns per task; the packets of the next task are in
+        //      flight during this one
+        const float* pk2 = SY.packets + (int64_t)q * SY.total * 64 + lane;
+        const uint32_t lbase = (RK == 1 ? 4u : 16u) * (uint32_t)(lane & 15);
+        float cn[8];
+        int gb = gp2[min(wave, groups2 - 1)], steps = gp2[min(wave, groups2 - 1) + 1] - gb;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) cn[a] = pk2[(int64_t)(gb + max(min(a, steps - 1), 0)) * 64];
+        for (int t = wave; t < groups2; t += NW) {
+            float c[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a) c[a] = cn[a];
+            const float* pk = pk2 + (int64_t)gb * 64;
+            const int now = steps;
+            if (t + NW < groups2) {
+                gb = gp2[t + NW];
+                steps = gp2[t + NW + 1] - gb;
+#pragma unroll
+                for (int a = 0; a < 8; ++a) cn[a] = pk2[(int64_t)(gb + max(min(a, steps - 1), 0)) * 64];
+            }
+            const float s = stage2_group<RK, G>(c, pk, now, slabs, lbase);
+            const int cidx = t * 4 + (lane >> 4);
+            if (cidx < n2) {
+                float* dst = tile + (lane & 15) * tp + order2[cidx];
+                *dst = q == 0 ? s : *dst + s;         // the same lane in every pass
+            }
+        }
+        __syncthreads();
+    }
+    // ---- y and this workgroup's share of p^T a, a = M p - y
+    float s_pa = 0.f;
+    const float inv_h = 1.0f / prm.h;
+    for (int ii = wave; ii < rows; ii += NW) {
+        const int i = __builtin_amdgcn_readfirstlane(order1[i0 + ii]);
+        const float d1 = X.rowsum[g1.voff + i] + prm.q;
+        const int lab1 = X.vlabel[g1.voff + i];
+        for (int col = lane; col < n2; col += 64) {
+            const float yv = tile[ii * tp + col];
+            const int64_t at = (int64_t)i * n2 + col;
+            const float pv = p[at];
+            const float dd = d1 * (Y.rowsum[g2.voff + col] + prm.q);
+            const float m = lab1 == Y.vlabel[g2.voff + col] ? dd : dd * inv_h;
+            s_pa = __builtin_fmaf(pv, __builtin_fmaf(m, pv, -yv), s_pa);
+            y[at] = yv;
+        }
+    }
+    if (!check_only) wave_accumulate(s_pa, &st.pa[it & 1], lane);
+}
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// One workgroup (4 wavefronts) takes 32 outer rows and all columns, NT tiles of 64 columns per
+// wavefront.  Per k: T_k[32 x n'] = F_k P on the matrix cores, to LDS; y += T_k F'_k^T.  F_k and F'_k
+// are symmetric, so every operand is read along rows (32 lanes = 128 adjacent bytes).
+// Sums are kept in levels of 64 terms to bound the fp32 rounding bias of long running sums.
+// Bound by the matrix cores: 128 multiply-adds per clk and CU in fp32.
+template <int NT>
+__global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, const float* FX,
+                                                            const float* FY, int rank, const MgkLargePair* pairs,
+                                                            MgkPairState* state, float* vec, MgkParams prm,
+                                                            int n_pairs, int blocks, int it, int check_only) {
+    extern __shared__ __align__(16) float lds[];   // T_k, 32 rows of stride tp
+    int pair, blk;
+    sep_block(blockIdx.x, blocks, &pair, &blk);
+    if (pair >= n_pairs) return;
+    MgkPairState& st = state[pair];
+    if (check_only ? !st.check : st.done) return;
+    const MgkLargePair P = pairs[pair];
+    const int i0 = blk * 32;
+    if (i0 >= P.n1) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
+    const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
+    const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
+    const float* F1 = FX + X.dense_off[P.g1] * rank + i0;
+    const float* F2 = FY + Y.dense_off[P.g2] * rank;
+    const float* p = vec + P.vec + 2 * (int64_t)P.npad;
+    float* y = vec + P.vec + 4 * (int64_t)P.npad;
+    const int tp = np2 + 1;
+    const int r = lane & 31, half = lane >> 5;
+    f32x16 yacc[NT][2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) yacc[t][b][v] = 0.f;
+    for (int k = 0; k < rank; ++k) {
+        const float* A = F1 + (int64_t)k * np1 * np1;
+        // ---- T_k = F_k P; rows of F_k beyond n1 are zero, columns of p beyond n2 are
+        //      harmless (the rows of F'_k they meet are zero)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int c0 = (t * 4 + wave) * 64;
+            if (c0 < np2) {
+                f32x16 acc[2], tot[2];
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) tot[b][v] = 0.f;
+                const int cA = min(c0 + r, n2 - 1), cB = min(c0 + 32 + r, n2 - 1);
+                for (int j0 = 0; j0 < n1; j0 += 64) {
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+                    const int j1 = min(j0 + 64, (n1 + 15) & ~15);
+                    for (int j = j0; j < j1; j += 16) {
+                        float av[8], b0[8], b1[8];
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+                            const int jj = j + 2 * s + half;
+                            const float* prow = p + (int64_t)min(jj, n1 - 1) * n2;
+                            av[s] = A[(int64_t)jj * np1 + r];
+                            b0[s] = prow[cA];
+                            b1[s] = prow[cB];
+                        }
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+                            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], b0[s], acc[0], 0, 0, 0);
+                            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], b1[s], acc[1], 0, 0, 0);
+                        }
+                    }
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) tot[b][v] += acc[b][v];
+                }
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        lds[(8 * (v >> 2) + 4 * half + (v & 3)) * tp + c0 + 32 * b + r] = tot[b][v];
+            }
+        }
+        __syncthreads();
+        // ---- y += T_k F'_k^T
+        const float* Bm = F2 + (int64_t)k * np2 * np2;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int c0 = (t * 4 + wave) * 64;
+            if (c0 < np2) {
+                f32x16 acc[2];
+                for (int j0 = 0; j0 < n2; j0 += 64) {
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+                    const int j1 = min(j0 + 64, (n2 + 15) & ~15);
+                    for (int j = j0; j < j1; j += 16) {
+                        float av[8], b0[8], b1[8];
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+                            const int jj = j + 2 * s + half;
+                            const float* brow = Bm + (int64_t)jj * np2 + c0 + r;
+                            av[s] = lds[r * tp + jj];
+                            b0[s] = brow[0];
+                            b1[s] = brow[32];
+                        }
+#pragma unroll
+                        for (int s = 0; s < 8; ++s) {
+                            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], b0[s], acc[0], 0, 0, 0);
+                            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], b1[s], acc[1], 0, 0, 0);
+                        }
+                    }
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) yacc[t][b][v] += acc[b][v];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // ---- y and this workgroup's share of p^T a, a = M p - y
+    float s_pa = 0.f;
+    const float inv_h = 1.0f / prm.h;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int col = (t * 4 + wave) * 64 + 32 * b + r;
+            if (col >= n2) continue;
+            const float d2 = Y.rowsum[g2.voff + col] + prm.q;
+            const int lab2 = Y.vlabel[g2.voff + col];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int i = i0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                if (i < n1) {
+                    const int64_t at = (int64_t)i * n2 + col;
+                    const float yv = yacc[t][b][v], pv = p[at];
+                    const float dd = (X.rowsum[g1.voff + i] + prm.q) * d2;
+                    const float m = lab2 == X.vlabel[g1.voff + i] ? dd : dd * inv_h;
+                    s_pa = __builtin_fmaf(pv, __builtin_fmaf(m, pv, -yv), s_pa);
+                    y[at] = yv;
+                }
+            }
+        }
+    if (!check_only) wave_accumulate(s_pa, &st.pa[it & 1], lane);
+}
+
+hipError_t set_lds(const void* kern, bool* configured) {
+    if (*configured) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, MGK_LDS_LIMIT_BYTES);
+    if (e == hipSuccess) *configured = true;
+    return e;
+}
+
+}  // namespace
+
+hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L, int max_n,
+                               const int32_t* gptr, int total, float* packets, hipStream_t stream) {
+    if (B.n_graphs <= 0) return hipSuccess;
+    // the graph index is a grid dimension of at most 65535: batches of more graphs go in parts
+    const int gx = (max_n + 15) / 16;
+    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535) {
+        MgkBatchDev part = B;
+        part.graphs += g0;
+        hipLaunchKernelGGL(mgk_sep_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
+                           stream, part, S, L, gptr, total, packets);
+    }
+    return hipGetLastError();
+}
+
+hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, int max_n, float* F, hipStream_t stream) {
+    if (B.n_graphs <= 0) return hipSuccess;
+    const int gx = (max_n + 63) / 16;
+    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535) {
+        MgkBatchDev part = B;
+        part.graphs += g0;
+        part.dense_off += g0;
+        hipLaunchKernelGGL(mgk_sep_dense_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
+                           stream, part, S, F);
+    }
+    return hipGetLastError();
+}
+
+hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
+                              const MgkSepLayout& L, const MgkLargePair* pairs, MgkPairState* state, float* vec,
+                              const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
+    const int blocks = (max_n1 + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
+    const dim3 grid((unsigned)(((n_pairs + 7) / 8) * 8 * blocks));
+    const size_t bytes = mgk_sep_lds_bytes(L.rk, max_n2);
+    if (bytes > MGK_LDS_LIMIT_BYTES) return hipErrorInvalidValue;
+#define MGK_SEP_GO(RK, G) \
+    case RK: { \
+        auto kern = mgk_sep_xmv_kernel<RK, G>; \
+        static bool configured = false; \
+        hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
+        if (e != hipSuccess) return e; \
+        hipLaunchKernelGGL(kern, grid, dim3(1024), bytes, stream, X, Y, SX, SY, L, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        break; \
+    }
+    switch (L.rk) {
+        MGK_SEP_GO(1, 8) MGK_SEP_GO(4, 2) MGK_SEP_GO(5, 2) MGK_SEP_GO(6, 2) MGK_SEP_GO(7, 2)
+        default: return hipErrorInvalidValue;
+    }
+#undef MGK_SEP_GO
+    return hipGetLastError();
+}
+
+hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const float* FX, const float* FY, int rank,
+                                const MgkLargePair* pairs, MgkPairState* state, float* vec, const MgkParams& prm,
+                                int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
+    const int blocks = (max_n1 + 31) / 32;
+    const dim3 grid((unsigned)(((n_pairs + 7) / 8) * 8 * blocks));
+    const int np2 = (max_n2 + 63) & ~63;
+    const size_t bytes = (size_t)32 * (np2 + 1) * sizeof(float);
+    if (np2 > MGK_SEP_DENSE_MAX_N) return hipErrorInvalidValue;
+#define MGK_SEP_DENSE_GO(NT) \
+    { \
+        auto kern = mgk_sep_dense_kernel<NT>; \
+        static bool configured = false; \
+        hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
+        if (e != hipSuccess) return e; \
+        hipLaunchKernelGGL(kern, grid, dim3(256), bytes, stream, X, Y, FX, FY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+    }
+    if (np2 <= 256) MGK_SEP_DENSE_GO(1)
+    else if (np2 <= 512) MGK_SEP_DENSE_GO(2)
+    else MGK_SEP_DENSE_GO(4)
+#undef MGK_SEP_DENSE_GO
+    return hipGetLastError();
+}
