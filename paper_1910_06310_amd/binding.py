@@ -326,9 +326,9 @@ class Solver:
         if len(jj) != n or len(off) != n:
             raise ValueError("index arrays differ in length")
         need = 0
-        for k in range(n):
-            nx = int(X.vtx_off[ii[k] + 1] - X.vtx_off[ii[k]]) * int(Y.vtx_off[jj[k] + 1] - Y.vtx_off[jj[k]])
-            need = max(need, int(off[k]) + nx)
+        if n:
+            nx = (X.vtx_off[ii + 1] - X.vtx_off[ii]) * (Y.vtx_off[jj + 1] - Y.vtx_off[jj])
+            need = max(0, int((off + nx).max()))
         self._check(load_library().mgk_pairs_nodal(
             self._h, X._h, Y._h, n, pi, pj, _dev_ptr(K, "float32", n), _dev_ptr(x, "float32", need), po,
             _dev_ptr(iters, "int32", n), _dev_ptr(flags, "int32", n), _stream_ptr(stream)))

@@ -5,9 +5,12 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <stdexcept>
@@ -50,6 +53,95 @@ struct DevBuf {
     size_t cap = 0;
 };
 
+// Pinned host memory for what a call copies to the device without waiting: two slots in turn,
+// each reused once the copies out of it have been made.
+struct Staging {
+    struct Slot {
+        void* p = nullptr;
+        size_t cap = 0;
+        hipEvent_t event = nullptr;   // recorded after the last copy out of the slot
+        bool busy = false;
+    } slot[2];
+    int next = 0;
+};
+
+// Device memory of freed batches, kept for the next ones (at most kMaxBlobs blocks of at most
+// kMaxBlobBytes).  A block is handed out again when the events recorded on the streams
+// that used its batch have completed.
+constexpr size_t kMaxBlobs = 4, kMaxBlobBytes = (size_t)16 << 20;
+struct FreeBlob {
+    void* p = nullptr;
+    size_t cap = 0;
+    std::vector<hipEvent_t> readers;
+};
+
+// Threads of a context for the host work of a call.  run(n, f, helpers) calls f(0) .. f(n - 1), on
+// the calling thread and on at most `helpers` (and kMaxWorkers) others, and returns when all have
+// returned; f must not throw.  The threads sleep in between and end with the pool.
+class WorkerPool {
+public:
+    ~WorkerPool() {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            stop_ = true;
+        }
+        wake_.notify_all();
+        for (std::thread& t : threads_) t.join();
+    }
+    void run(int n, const std::function<void(int)>& f, int helpers = kMaxWorkers) {
+        const int want = std::min({n - 1, helpers, kMaxWorkers, (int)std::thread::hardware_concurrency() - 1});
+        if (want > 0) {
+            try {
+                while ((int)threads_.size() < want) threads_.emplace_back([this] { work(); });
+            } catch (...) {   // fewer threads, then
+            }
+        }
+        if (want <= 0 || threads_.empty()) {
+            for (int i = 0; i < n; ++i) f(i);
+            return;
+        }
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            f_ = &f;
+            n_ = n;
+            taken_ = 0;
+            left_ = n;
+        }
+        for (int k = 0; k < want; ++k) wake_.notify_one();
+        std::unique_lock<std::mutex> lock(m_);
+        take(lock);
+        done_.wait(lock, [this] { return left_ == 0; });
+        f_ = nullptr;
+    }
+
+private:
+    static constexpr int kMaxWorkers = 15;
+    void take(std::unique_lock<std::mutex>& lock) {   // tasks until none is left to take
+        while (f_ && taken_ < n_) {
+            const int i = taken_++;
+            const std::function<void(int)>* f = f_;
+            lock.unlock();
+            (*f)(i);
+            lock.lock();
+            if (--left_ == 0) done_.notify_one();
+        }
+    }
+    void work() {
+        std::unique_lock<std::mutex> lock(m_);
+        while (true) {
+            wake_.wait(lock, [this] { return stop_ || (f_ && taken_ < n_); });
+            if (stop_) return;
+            take(lock);
+        }
+    }
+    std::mutex m_;
+    std::condition_variable wake_, done_;
+    std::vector<std::thread> threads_;
+    const std::function<void(int)>* f_ = nullptr;
+    int n_ = 0, taken_ = 0, left_ = 0;
+    bool stop_ = false;
+};
+
 }  // namespace
 
 struct mgk_batch {
@@ -69,10 +161,12 @@ struct mgk_batch {
     float label_lo = 0.f, label_hi = 0.f; // range of attribute 0 of the edge labels
     int32_t max_n = 0;
     int32_t packets[2] = {0, 0};          // packet steps of the whole batch with 2 / 8 nonzeros per packet
-    const int32_t* gptr_dev[2] = {nullptr, nullptr};
+    MgkSepList sep[2] = {};               // the batch's part of it for the two packet sizes
     int64_t dense_floats = 0;             // sum of (n rounded up to 64)^2
     // device
     void* blob = nullptr;
+    size_t blob_cap = 0;
+    std::vector<hipStream_t> used_on;   // streams with calls that read the batch
     MgkBatchDev dev{};
     JobList gram_jobs;
     int gram_jobs_waves = 0;       // waves_per_pair setting the list was built for
@@ -115,10 +209,11 @@ struct mgk_ctx {
     int sep_kernel = -1;
     DevBuf vec, lpairs, lstate, lactive, nodal_off, diag;
     int* active_host = nullptr;         // pinned: {pairs still iterating, most iterations needed}
-    void* pin = nullptr;                // pinned staging of the pair records of a call
-    size_t pin_cap = 0;
-    hipEvent_t pin_event = nullptr;     // recorded after the last copy out of `pin`
-    bool pin_busy = false;
+    Staging staging;                    // pair records, job lists and offsets of a call on their way to the device
+    std::vector<FreeBlob> blobs;
+    int64_t calls = 0;                  // solver calls so far
+    hipStream_t upload = nullptr;       // loading a batch does not wait for the caller's streams
+    WorkerPool workers;
     int large_iter_guess = 12;          // iterations the last call of the global-memory solver needed
     std::string launch_log;             // kernels the last solve call enqueued, one line each
 };
@@ -179,23 +274,23 @@ mgk_status guarded(mgk_ctx* ctx, F&& body) noexcept {
     return st;
 }
 
-// Worker threads that are always joined, also when starting one of them throws.
-struct JoiningThreads {
-    std::vector<std::thread> t;
-    ~JoiningThreads() { join(); }
-    void join() {
-        for (std::thread& th : t)
-            if (th.joinable()) th.join();
+// Arrays of a batch on their way into one block of memory, 256-byte aligned each.
+struct BlobPlan {
+    struct Part { size_t at; const void* src; size_t bytes; };
+    std::vector<Part> parts;
+    size_t total = 0;
+    template <class T>
+    size_t add(const std::vector<T>& v) {
+        const size_t at = (total + 255) & ~(size_t)255;
+        total = at + std::max<size_t>(v.size() * sizeof(T), 16);
+        parts.push_back({at, v.data(), v.size() * sizeof(T)});
+        return at;
+    }
+    void copy_to(char* dst) const {
+        for (const Part& p : parts)
+            if (p.bytes) memcpy(dst + p.at, p.src, p.bytes);
     }
 };
-
-template <class T>
-size_t append_bytes(std::vector<char>& blob, const std::vector<T>& v) {
-    size_t off = (blob.size() + 255) & ~(size_t)255;
-    blob.resize(off + std::max<size_t>(v.size() * sizeof(T), 16));
-    if (!v.empty()) memcpy(blob.data() + off, v.data(), v.size() * sizeof(T));
-    return off;
-}
 
 // Contiguous division of the rows of a graph among `waves` wavefronts for the
 // register-resident solver: bounds[w] .. bounds[w+1] are wavefront w's rows.  A row of
@@ -236,6 +331,10 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
 // scalar labels); the streaming on-chip solver keeps them in LDS for the outer graph
 int attr_dim_of(const mgk_ctx* ctx) {
     return ctx->edge_kernel == MGK_EK_KRON_SE || ctx->edge_kernel == MGK_EK_RCONV_SE ? ctx->label_dim : 0;
+}
+
+void note_use(mgk_batch* b, hipStream_t stream) {
+    if (std::find(b->used_on.begin(), b->used_on.end(), stream) == b->used_on.end()) b->used_on.push_back(stream);
 }
 
 // the batches must carry the number of label attributes the edge kernel reads
@@ -300,7 +399,7 @@ int64_t regs_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves) {
     const int run = waves == 4 ? (o.regs_runs & 0xffff) : (int)((uint32_t)o.regs_runs >> 16);
     if (run > smax) return -1;
     const int64_t N = (int64_t)o.n * i.n;
-    const int64_t ept = std::max<int64_t>(1, (N + waves * 64 - 1) / (waves * 64));
+    const int64_t ept = std::max<int64_t>(1, (N + waves * 64 - 1) >> (waves == 4 ? 8 : 9));
     // register blocks that keep four wavefronts per SIMD resident
     if (ept > MGK_REGS_MAX_EPT) return -1;
     return (int64_t)o.nnz * (2 * chunks) + (int64_t)o.n * (1 + 4 * chunks) +
@@ -408,116 +507,156 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
     return pl;
 }
 
+// A launch shape: jobs of one shape go into one kernel launch.
+struct Shape {
+    int16_t waves = 0, ept = 0, chunks = 0, sell_regs = 0;
+    bool atomic_rows = false, swapped = false;
+    int64_t count = 0;
+    int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
+    int64_t min_cost = INT64_MAX, max_cost = 0;
+    bool same(const Shape& s) const {
+        return waves == s.waves && ept == s.ept && chunks == s.chunks && sell_regs == s.sell_regs &&
+               atomic_rows == s.atomic_rows && swapped == s.swapped;
+    }
+    // padded vectors in the LDS plan of each solver (the owner-computes one also has a
+    // schedule word per wavefront and slot; 4 words of alignment slack)
+    int64_t vector_words() const {
+        const int vectors = sell_regs > 0 ? 3 : chunks > 0 ? 4 : 2;
+        return (int64_t)vectors * waves * 64 * ept + (sell_regs > 0 ? waves * ept + 4 : 0);
+    }
+    int64_t lds_bytes() const { return (base_words + vector_words()) * 4; }
+};
+
 struct HostJob {
     MgkJob job;
     int64_t cost;
-    int32_t lds_words;
-    int16_t waves, ept, chunks;
-    int16_t sell_regs = 0;
-    bool atomic_rows, swapped;
+    int32_t shape;   // index into the list of shapes
+};
+
+// The jobs of a call, planned: every job with its launch shape.
+struct JobPlan {
+    std::vector<HostJob> jobs;
+    std::vector<Shape> shapes;
+    JobPlan() { std::fill(table, table + kTable, (int16_t)-1); }
+    // index of the shape of a planned pair; counts the pair in
+    int shape_of(const PairPlan& pl, bool swapped) {
+        Shape s;
+        s.waves = (int16_t)pl.waves;
+        s.ept = (int16_t)pl.ept;
+        s.chunks = (int16_t)pl.chunks;
+        s.sell_regs = (int16_t)pl.sell_regs;
+        s.atomic_rows = pl.atomic_rows;
+        s.swapped = swapped;
+        const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
+                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21;
+        uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
+        while (table[slot] >= 0 && !shapes[(size_t)table[slot]].same(s)) slot = (slot + 1) % kTable;
+        if (table[slot] < 0) {
+            table[slot] = (int16_t)shapes.size();
+            shapes.push_back(s);
+        }
+        Shape& t = shapes[(size_t)table[slot]];
+        t.count++;
+        t.base_words = std::max(t.base_words, pl.lds_words - t.vector_words());
+        t.min_cost = std::min(t.min_cost, pl.cost);
+        t.max_cost = std::max(t.max_cost, pl.cost);
+        return table[slot];
+    }
+
+private:
+    static constexpr int kTable = 4096;
+    int16_t table[kTable];
 };
 
 // A launch shape with few jobs costs more in launch and drain time than its pairs
 // gain from the exact fit: such jobs move to the closest larger shape that can run
 // them (same solver and workgroup size, at least as many elements per thread and
 // inner chunks).  Only the vector blocks grow, so the LDS need grows by the
-// difference of the padded vector lengths.
+// difference of the padded vector lengths.  Returns the shape each shape's jobs end up in.
 constexpr int64_t kMinJobsPerLaunch = 4096;
 
-void merge_small_shapes(std::vector<HostJob>& jobs) {
-    struct Shape { int waves, ept, chunks, sell_regs; bool atomic_rows, swapped; int64_t count; };
-    auto same = [](const Shape& s, const HostJob& j) {
-        return s.waves == j.waves && s.ept == j.ept && s.chunks == j.chunks && s.sell_regs == j.sell_regs &&
-               s.atomic_rows == j.atomic_rows && s.swapped == j.swapped;
-    };
-    std::vector<Shape> frozen;   // shapes whose jobs would outgrow LDS in the larger shape
-    for (int round = 0; round < 64; ++round) {
-        std::vector<Shape> shapes;
-        for (const HostJob& j : jobs) {
-            auto it = std::find_if(shapes.begin(), shapes.end(), [&](const Shape& s) { return same(s, j); });
-            if (it == shapes.end()) shapes.push_back({j.waves, j.ept, j.chunks, j.sell_regs, j.atomic_rows, j.swapped, 1});
-            else it->count++;
-        }
+std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
+    std::vector<int> into(shapes.size());
+    std::iota(into.begin(), into.end(), 0);
+    std::vector<char> frozen(shapes.size(), 0);   // shapes whose jobs would outgrow LDS in the larger shape
+    while (true) {
         // smallest shape below the threshold that has somewhere to go
-        const Shape* from = nullptr;
-        const Shape* to = nullptr;
-        for (const Shape& a : shapes) {
-            if (a.count >= kMinJobsPerLaunch) continue;
-            if (std::any_of(frozen.begin(), frozen.end(), [&](const Shape& f) {
-                    return f.waves == a.waves && f.ept == a.ept && f.chunks == a.chunks && f.sell_regs == a.sell_regs &&
-                           f.atomic_rows == a.atomic_rows && f.swapped == a.swapped; }))
-                continue;
-            const Shape* best = nullptr;
-            for (const Shape& b : shapes) {
-                if (&a == &b || a.waves != b.waves || a.atomic_rows != b.atomic_rows || a.swapped != b.swapped ||
+        int from = -1, to = -1;
+        for (size_t k = 0; k < shapes.size(); ++k) {
+            const Shape& a = shapes[k];
+            if (a.count == 0 || a.count >= kMinJobsPerLaunch || frozen[k]) continue;
+            int best = -1;
+            auto size = [&](int q) { return shapes[q].ept * 4 + shapes[q].chunks + shapes[q].sell_regs; };
+            for (size_t q = 0; q < shapes.size(); ++q) {
+                const Shape& b = shapes[q];
+                if (q == k || b.count == 0 || a.waves != b.waves || a.atomic_rows != b.atomic_rows || a.swapped != b.swapped ||
                     (a.chunks > 0) != (b.chunks > 0) || b.chunks < a.chunks || b.ept < a.ept ||
                     (a.sell_regs > 0) != (b.sell_regs > 0) || b.sell_regs < a.sell_regs)
                     continue;
-                if (!best || b.ept * 4 + b.chunks + b.sell_regs < best->ept * 4 + best->chunks + best->sell_regs) best = &b;
+                if (best < 0 || size((int)q) < size(best)) best = (int)q;
             }
-            if (best && (!from || a.ept * 4 + a.chunks < from->ept * 4 + from->chunks)) { from = &a; to = best; }
+            if (best >= 0 && (from < 0 || a.ept * 4 + a.chunks < shapes[from].ept * 4 + shapes[from].chunks)) {
+                from = (int)k;
+                to = best;
+            }
         }
-        if (!from) return;
-        // padded vectors in the LDS plan of each solver (the owner-computes one also has a
-        // schedule word per wavefront and slot; 4 words of alignment slack)
-        const int vectors = from->sell_regs > 0 ? 3 : from->chunks > 0 ? 4 : 2;
-        const int extra = from->sell_regs > 0 ? from->waves * (to->ept - from->ept) + 4 : 0;
-        bool fits = true;
-        for (const HostJob& j : jobs)
-            if (same(*from, j) &&
-                ((int64_t)j.lds_words + vectors * j.waves * 64 * (to->ept - j.ept) + extra) * 4 > MGK_LDS_LIMIT_BYTES)
-                fits = false;
-        if (!fits) { frozen.push_back(*from); continue; }
-        for (HostJob& j : jobs)
-            if (same(*from, j)) {
-                j.lds_words += vectors * j.waves * 64 * (to->ept - j.ept) + extra;
-                j.ept = (int16_t)to->ept;
-                j.chunks = (int16_t)to->chunks;
-                j.sell_regs = (int16_t)to->sell_regs;
-            }
+        if (from < 0) break;
+        Shape &a = shapes[from], &b = shapes[to];
+        if ((a.base_words + b.vector_words()) * 4 > MGK_LDS_LIMIT_BYTES) { frozen[from] = 1; continue; }
+        b.count += a.count;
+        b.base_words = std::max(b.base_words, a.base_words);
+        b.min_cost = std::min(b.min_cost, a.min_cost);
+        b.max_cost = std::max(b.max_cost, a.max_cost);
+        a.count = 0;
+        for (int& k : into)
+            if (k == from) k = to;
     }
+    return into;
 }
 
-// `fixed`: the job array is storage the caller provides (`out.dev` set, *capacity jobs);
-// nothing is allocated or freed then.
-mgk_status build_job_list(mgk_ctx* ctx, std::vector<HostJob>& jobs, JobList& out,
+mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::Slot** out);
+mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream);
+constexpr size_t kMaxStagedBytes = (size_t)4 << 20;
+
+// Launch shapes largest first, inside a shape the expensive pairs first (in 256 steps of
+// cost: near enough for balance, and one counting sort).  `fixed`: the job array is storage the
+// caller provides (`out.dev` set, *capacity jobs); nothing is allocated or freed then.
+mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
                           hipStream_t stream, int64_t* capacity, bool fixed = false) {
-    merge_small_shapes(jobs);
-    // group by launch shape (largest first), inside a group big pairs start first
-    const bool by_cost = ctx->cost_sorted != 0;
-    std::stable_sort(jobs.begin(), jobs.end(), [by_cost](const HostJob& a, const HostJob& b) {
+    std::vector<Shape>& shapes = plan.shapes;
+    const std::vector<int> into = merge_small_shapes(shapes);
+    std::vector<int> order;
+    for (size_t k = 0; k < shapes.size(); ++k)
+        if (shapes[k].count > 0) order.push_back((int)k);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+        const Shape &a = shapes[x], &b = shapes[y];
         const int ka = a.waves * 64 * a.ept, kb = b.waves * 64 * b.ept;
         if (ka != kb) return ka > kb;
         if (a.waves != b.waves) return a.waves > b.waves;
         if (a.chunks != b.chunks) return a.chunks > b.chunks;
         if (a.sell_regs != b.sell_regs) return a.sell_regs > b.sell_regs;
         if (a.atomic_rows != b.atomic_rows) return a.atomic_rows;
-        if (a.swapped != b.swapped) return b.swapped;
-        return by_cost && a.cost > b.cost;
+        return !a.swapped && b.swapped;
     });
     out.bins.clear();
-    out.n = (int64_t)jobs.size();
-    std::vector<MgkJob> flat(jobs.size());
-    for (size_t k = 0; k < jobs.size(); ++k) {
-        flat[k] = jobs[k].job;
-        if (out.bins.empty() || jobs[k].waves != out.bins.back().waves ||
-            jobs[k].ept != out.bins.back().ept || jobs[k].chunks != out.bins.back().chunks ||
-            jobs[k].sell_regs != out.bins.back().sell_regs ||
-            jobs[k].atomic_rows != out.bins.back().atomic_rows ||
-            jobs[k].swapped != out.bins.back().swapped) {
-            JobBin b;
-            b.first = (int64_t)k;
-            b.waves = jobs[k].waves;
-            b.ept = jobs[k].ept;
-            b.chunks = jobs[k].chunks;
-            b.sell_regs = jobs[k].sell_regs;
-            b.atomic_rows = jobs[k].atomic_rows;
-            b.swapped = jobs[k].swapped;
-            out.bins.push_back(b);
-        }
-        JobBin& b = out.bins.back();
-        b.count++;
-        b.lds_bytes = std::max(b.lds_bytes, (size_t)jobs[k].lds_words * 4);
+    out.n = (int64_t)plan.jobs.size();
+    std::vector<int> rank(shapes.size(), 0);
+    int64_t first = 0;
+    for (size_t r = 0; r < order.size(); ++r) {
+        const Shape& s = shapes[order[r]];
+        rank[order[r]] = (int)r;
+        JobBin b;
+        b.first = first;
+        b.count = s.count;
+        b.lds_bytes = (size_t)s.lds_bytes();
+        b.waves = s.waves;
+        b.ept = s.ept;
+        b.chunks = s.chunks;
+        b.sell_regs = s.sell_regs;
+        b.atomic_rows = s.atomic_rows;
+        b.swapped = s.swapped;
+        out.bins.push_back(b);
+        first += s.count;
     }
     if (fixed) {
         if (out.n > *capacity) return fail(ctx, MGK_ELIMIT, "job list of %lld pairs exceeds the fixed storage of %lld",
@@ -529,11 +668,30 @@ mgk_status build_job_list(mgk_ctx* ctx, std::vector<HostJob>& jobs, JobList& out
         MGK_HIP(ctx, hipMalloc((void**)&out.dev, (size_t)cap * sizeof(MgkJob)));
         if (capacity) *capacity = cap;
     }
-    if (out.n) {
-        MGK_HIP(ctx, hipMemcpyAsync(out.dev, flat.data(), (size_t)out.n * sizeof(MgkJob),
-                                    hipMemcpyHostToDevice, stream));
-        MGK_HIP(ctx, hipStreamSynchronize(stream));  // `flat` is pageable and dies here
-    }
+    if (out.n == 0) return MGK_OK;
+    constexpr int kSteps = 256;
+    std::vector<int32_t> at((size_t)order.size() * kSteps + 1, 0);
+    auto bucket = [&](const HostJob& j) {
+        const int k = into[j.shape];
+        const Shape& s = shapes[k];
+        int q = 0;
+        if (ctx->cost_sorted && s.max_cost > s.min_cost)
+            q = (int)((s.max_cost - j.cost) * (kSteps - 1) / (s.max_cost - s.min_cost));
+        return (size_t)rank[k] * kSteps + (size_t)q;
+    };
+    std::vector<int32_t> where(plan.jobs.size());
+    for (size_t k = 0; k < plan.jobs.size(); ++k) at[(size_t)(where[k] = (int32_t)bucket(plan.jobs[k])) + 1]++;
+    for (size_t k = 1; k < at.size(); ++k) at[k] += at[k - 1];
+    const size_t bytes = (size_t)out.n * sizeof(MgkJob);
+    Staging::Slot* slot = nullptr;
+    if (bytes <= kMaxStagedBytes && capacity)   // lists kept with a batch are made once
+        if (mgk_status st = staging_slot(ctx, bytes, !fixed, &slot)) return st;
+    std::vector<MgkJob> pageable(slot ? 0 : plan.jobs.size());
+    MgkJob* flat = slot ? static_cast<MgkJob*>(slot->p) : pageable.data();
+    for (size_t k = 0; k < plan.jobs.size(); ++k) flat[at[(size_t)where[k]]++] = plan.jobs[k].job;
+    MGK_HIP(ctx, hipMemcpyAsync(out.dev, flat, bytes, hipMemcpyHostToDevice, stream));
+    if (slot) return staging_done(ctx, slot, stream);
+    MGK_HIP(ctx, hipStreamSynchronize(stream));  // `pageable` dies here
     return MGK_OK;
 }
 
@@ -714,22 +872,78 @@ MgkLargePair plan_large(const MgkGraphDesc& a, const MgkGraphDesc& b, int32_t ia
     return P;
 }
 
-// Staging buffer of a call's records in pinned memory owned by the context; the previous use of
-// it is waited for (long finished).
-mgk_status pinned(mgk_ctx* ctx, size_t bytes) {
-    if (ctx->pin_busy) {
-        MGK_HIP(ctx, hipEventSynchronize(ctx->pin_event));
-        ctx->pin_busy = false;
+// The next slot of pinned memory, of at least `bytes`; waits for the copies of its last use (long
+// made).  Without may_allocate a slot that is too small leaves *out null.
+mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::Slot** out) {
+    Staging::Slot& s = ctx->staging.slot[ctx->staging.next];
+    *out = nullptr;
+    if (bytes > s.cap && !may_allocate) return MGK_OK;
+    ctx->staging.next ^= 1;
+    if (s.busy) {
+        MGK_HIP(ctx, hipEventSynchronize(s.event));
+        s.busy = false;
     }
-    if (bytes > ctx->pin_cap) {
-        if (ctx->pin) MGK_HIP(ctx, hipHostFree(ctx->pin));
-        ctx->pin = nullptr;
-        ctx->pin_cap = 0;
-        MGK_HIP(ctx, hipHostMalloc(&ctx->pin, bytes, hipHostMallocDefault));
-        ctx->pin_cap = bytes;
+    if (!s.event) MGK_HIP(ctx, hipEventCreateWithFlags(&s.event, hipEventDisableTiming));
+    if (bytes > s.cap) {
+        if (s.p) MGK_HIP(ctx, hipHostFree(s.p));
+        s.p = nullptr;
+        s.cap = 0;
+        const size_t cap = std::max<size_t>(bytes, 64 * 1024);
+        MGK_HIP(ctx, hipHostMalloc(&s.p, cap, hipHostMallocDefault));
+        s.cap = cap;
     }
-    if (!ctx->pin_event) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->pin_event, hipEventDisableTiming));
+    *out = &s;
     return MGK_OK;
+}
+
+mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream) {
+    MGK_HIP(ctx, hipEventRecord(slot->event, stream));
+    slot->busy = true;
+    return MGK_OK;
+}
+
+// Device memory for a batch: a freed batch's block that nothing reads any more, or a new one.
+mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
+    for (size_t k = 0; k < ctx->blobs.size(); ++k) {
+        FreeBlob& f = ctx->blobs[k];
+        if (f.cap < bytes || f.cap > 4 * bytes + 65536) continue;
+        bool idle = true;
+        for (hipEvent_t e : f.readers) idle = idle && hipEventQuery(e) == hipSuccess;
+        if (!idle) {
+            (void)hipGetLastError();   // "not ready" is no error of a later launch
+            continue;
+        }
+        for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+        *p = f.p;
+        *cap = f.cap;
+        ctx->blobs.erase(ctx->blobs.begin() + (std::ptrdiff_t)k);
+        return MGK_OK;
+    }
+    const size_t want = bytes <= kMaxBlobBytes ? (bytes + bytes / 4 + 65535) & ~(size_t)65535 : bytes;
+    MGK_HIP(ctx, hipMalloc(p, want));
+    *cap = want;
+    return MGK_OK;
+}
+
+// Keeps the block of a batch that is being freed, unless there are enough or it is large.
+bool keep_blob(mgk_ctx* ctx, mgk_batch* b) {
+    if (ctx->blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes) return false;
+    FreeBlob f;
+    f.p = b->blob;
+    f.cap = b->blob_cap;
+    bool ok = true;
+    for (hipStream_t s : b->used_on) {
+        hipEvent_t e = nullptr;
+        ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (e) f.readers.push_back(e);
+        ok = ok && hipEventRecord(e, s) == hipSuccess;   // fails for a stream that is gone
+    }
+    if (ok) {
+        try { ctx->blobs.push_back(f); return true; } catch (...) {}
+    }
+    for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+    (void)hipGetLastError();
+    return false;
 }
 
 // Run Alg. 1 with global-memory vectors for a list of pairs (outer graphs from
@@ -828,16 +1042,16 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
     // no wait.
     {
         const size_t bytes = (size_t)n_pairs * sizeof(MgkLargePair);
-        if ((st = pinned(ctx, bytes)) != MGK_OK) return st;
-        memcpy(ctx->pin, pairs.data(), bytes);
-        MGK_HIP(ctx, hipMemcpyAsync(dpairs, ctx->pin, bytes, hipMemcpyHostToDevice, stream));
+        Staging::Slot* slot;
+        if ((st = staging_slot(ctx, bytes, true, &slot)) != MGK_OK) return st;
+        memcpy(slot->p, pairs.data(), bytes);
+        MGK_HIP(ctx, hipMemcpyAsync(dpairs, slot->p, bytes, hipMemcpyHostToDevice, stream));
+        if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
     }
     MGK_HIP(ctx, hipMemsetAsync(dstate, 0, (size_t)n_pairs * sizeof(MgkPairState), stream));
     ctx->active_host[0] = n_pairs;   // pairs still iterating
     ctx->active_host[1] = 0;         // most iterations any pair needed
     MGK_HIP(ctx, hipMemcpyAsync(dactive, ctx->active_host, 2 * sizeof(int), hipMemcpyHostToDevice, stream));
-    MGK_HIP(ctx, hipEventRecord(ctx->pin_event, stream));
-    ctx->pin_busy = true;
     hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, stream);
     if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "init launch failed: %s", hipGetErrorString(e));
     // The kernels of an iteration return at once for pairs that have stopped, so iterations
@@ -856,7 +1070,6 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
         }
         MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
-        ctx->pin_busy = false;
         if (ctx->active_host[0] <= 0) break;
     }
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
@@ -901,40 +1114,35 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     // features of the batches' nonzeros (they depend on the edge kernel's parameters)
     const mgk_batch* bt[2] = {A, Bb};
     MgkSepList sl[2] = {};
-    const float* F[2] = {};
     const int gi = L.per_packet == 8 ? 1 : 0;
     for (int k = 0; k < 2; ++k) {
-        if (k == 1 && Bb == A) { sl[1] = sl[0]; F[1] = F[0]; break; }
+        if (k == 1 && Bb == A) { sl[1] = sl[0]; break; }
         hipError_t e;
-        if (dense) {
-            if ((st = ensure(ctx, ctx->sep_dense[k], (size_t)bt[k]->dense_floats * S.rank * sizeof(float))) != MGK_OK) return st;
-            F[k] = (const float*)ctx->sep_dense[k].p;
-            e = mgk_launch_sep_dense_pack(bt[k]->dev, S, bt[k]->max_n, (float*)ctx->sep_dense[k].p, stream);
-        } else {
-            sl[k].total = bt[k]->packets[gi];
-            sl[k].gptr = bt[k]->gptr_dev[gi];
-            if ((st = ensure(ctx, ctx->sep_packets[k], std::max<size_t>(256, (size_t)L.passes * sl[k].total * 64 * sizeof(float)))) != MGK_OK) return st;
-            sl[k].packets = (const float*)ctx->sep_packets[k].p;
-            e = mgk_launch_sep_pack(bt[k]->dev, S, L, bt[k]->max_n, sl[k].gptr, sl[k].total, (float*)ctx->sep_packets[k].p, stream);
-        }
+        sl[k] = bt[k]->sep[gi];
+        DevBuf& buf = dense ? ctx->sep_dense[k] : ctx->sep_packets[k];
+        const size_t floats = dense ? (size_t)bt[k]->dense_floats * S.rank : (size_t)L.passes * sl[k].total * 64;
+        if ((st = ensure(ctx, buf, std::max<size_t>(256, floats * sizeof(float)))) != MGK_OK) return st;
+        (dense ? sl[k].dense : sl[k].packets) = (const float*)buf.p;
+        e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, sl[k], bt[k]->max_n, (float*)buf.p, stream)
+                  : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], bt[k]->max_n, (float*)buf.p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
 
-    if ((st = pinned(ctx, rec_bytes)) != MGK_OK) return st;
-    char* rec = static_cast<char*>(ctx->pin);
+    Staging::Slot* slot;
+    if ((st = staging_slot(ctx, rec_bytes, true, &slot)) != MGK_OK) return st;
+    char* rec = static_cast<char*>(slot->p);
     memset(rec, 0, rec_bytes);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, rec_bytes, hipMemcpyHostToDevice, stream));
-    MGK_HIP(ctx, hipEventRecord(ctx->pin_event, stream));
-    ctx->pin_busy = true;
+    if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
     MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
     int* dactive = (int*)((char*)ctx->lpairs.p + active_at);
     float* vec = (float*)ctx->vec.p;
 
     auto product = [&](int it, bool check_only) {
-        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, F[0], F[1], S.rank, dpairs, dstate, vec, prm, n_pairs,
+        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dstate, vec, prm, n_pairs,
                                             max_n1, max_n2, it, check_only, stream)
                      : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dstate, vec, prm, n_pairs,
                                           max_n1, max_n2, it, check_only, stream);
@@ -958,7 +1166,6 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
         MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
-        ctx->pin_busy = false;
     }
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
     log_launch(ctx, "%s rank=%d pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)",
@@ -970,6 +1177,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                        const MgkOutputs& out, hipStream_t stream) {
     const MgkParams prm = make_params(ctx, X);
     const bool weighted = X->weighted || Y->weighted;
+    ctx->calls++;
     ctx->launch_log.clear();
     for (const JobBin& b : jl.bins) {
         if (b.sell_regs > 0)
@@ -1084,8 +1292,18 @@ void mgk_destroy(mgk_ctx* ctx) {
                       &ctx->dense_tiles[1][0], &ctx->dense_tiles[1][1], &ctx->dense_tiles[1][2]})
         if (b->p) (void)hipFree(b->p);
     if (ctx->active_host) (void)hipHostFree(ctx->active_host);
-    if (ctx->pin) (void)hipHostFree(ctx->pin);
-    if (ctx->pin_event) (void)hipEventDestroy(ctx->pin_event);
+    for (Staging::Slot& s : ctx->staging.slot) {
+        if (s.event) {
+            if (s.busy) (void)hipEventSynchronize(s.event);
+            (void)hipEventDestroy(s.event);
+        }
+        if (s.p) (void)hipHostFree(s.p);
+    }
+    for (FreeBlob& f : ctx->blobs) {
+        (void)hipFree(f.p);   // waits for the work that reads it
+        for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+    }
+    if (ctx->upload) (void)hipStreamDestroy(ctx->upload);
     delete ctx;
 }
 
@@ -1297,6 +1515,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     std::vector<MgkEntry> list_outer, list_inner;   // nonzero lists for the register-resident solver
     std::vector<int32_t> gptr[2], deg_order;       // packets of the separable product, rows by degree
     std::vector<int64_t> dense_off((size_t)n_graphs);
+    std::vector<int32_t> qoff((size_t)n_graphs);
     constexpr int kPerPacket[2] = {2, 8};
     for (auto& v : gptr) v.reserve((size_t)(tot_v / 4 + 2 * (int64_t)n_graphs));
     deg_order.resize((size_t)tot_v);
@@ -1322,45 +1541,51 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     // The vertex orders are by far the most expensive part of loading and independent per
     // graph: they are computed first, on several threads, for every graph whose edge list is
     // sound.  The loop below validates each graph in full (so errors are reported as before,
-    // for the first bad graph) and only then takes the order computed here.
+    // for the first bad graph) and only then takes the order computed here.  Few graphs: the
+    // starting partitions of a graph are tasks of their own.
     std::vector<std::vector<int32_t>> pre_perm((size_t)n_graphs);
-    if ((reorder == MGK_REORDER_PBR || reorder == MGK_REORDER_RCM) && n_graphs >= 8) {
-        const int T = (int)std::max(1u, std::min({std::thread::hardware_concurrency(), 16u, (unsigned)n_graphs / 4u}));
-        auto order_worker = [&](int t) {
-          try {   // a worker that runs out of memory stops; the loop below orders what it left
-            MgkAdj a;
-            std::vector<int32_t> cur;
-            for (int32_t g = t; g < n_graphs; g += T) {
-                const int64_t v0 = vtx_off[g], v1 = vtx_off[g + 1], e0 = edge_off[g], e1 = edge_off[g + 1];
-                if (v1 <= v0 || e1 < e0 || v1 - v0 > 65535 * (int64_t)kTile) continue;
-                const int n = (int)(v1 - v0);
-                bool sound = true;
-                a.n = n;
-                a.ptr.assign(n + 1, 0);
-                for (int64_t k = e0; k < e1 && sound; ++k) {
-                    const int32_t sv = src[k], dv = dst[k];
-                    if (sv < 0 || sv >= n || dv < 0 || dv >= n || sv == dv) { sound = false; break; }
-                    a.ptr[sv + 1]++;
-                    a.ptr[dv + 1]++;
-                }
-                if (!sound) continue;
-                for (int i = 0; i < n; ++i) a.ptr[i + 1] += a.ptr[i];
-                a.idx.assign((size_t)(2 * (e1 - e0)), 0);
-                cur.assign(a.ptr.begin(), a.ptr.end() - 1);
-                for (int64_t k = e0; k < e1; ++k) {
-                    a.idx[cur[src[k]]++] = dst[k];
-                    a.idx[cur[dst[k]]++] = src[k];
-                }
-                for (int i = 0; i < n; ++i) std::sort(a.idx.begin() + a.ptr[i], a.idx.begin() + a.ptr[i + 1]);
-                pre_perm[(size_t)g] = reorder == MGK_REORDER_PBR ? mgk_order_pbr(a, kTile) : mgk_order_rcm(a);
+    if (reorder == MGK_REORDER_PBR || reorder == MGK_REORDER_RCM) {
+        auto adjacency = [&](int32_t g, MgkAdj& a, std::vector<int32_t>& cur) {
+            const int64_t v0 = vtx_off[g], v1 = vtx_off[g + 1], e0 = edge_off[g], e1 = edge_off[g + 1];
+            if (v1 <= v0 || e1 < e0 || v1 - v0 > 65535 * (int64_t)kTile) return false;
+            const int n = (int)(v1 - v0);
+            a.n = n;
+            a.ptr.assign(n + 1, 0);
+            for (int64_t k = e0; k < e1; ++k) {
+                const int32_t sv = src[k], dv = dst[k];
+                if (sv < 0 || sv >= n || dv < 0 || dv >= n || sv == dv) return false;
+                a.ptr[sv + 1]++;
+                a.ptr[dv + 1]++;
             }
-          } catch (...) {
-          }
+            for (int i = 0; i < n; ++i) a.ptr[i + 1] += a.ptr[i];
+            a.idx.assign((size_t)(2 * (e1 - e0)), 0);
+            cur.assign(a.ptr.begin(), a.ptr.end() - 1);
+            for (int64_t k = e0; k < e1; ++k) {
+                a.idx[cur[src[k]]++] = dst[k];
+                a.idx[cur[dst[k]]++] = src[k];
+            }
+            for (int i = 0; i < n; ++i) std::sort(a.idx.begin() + a.ptr[i], a.idx.begin() + a.ptr[i + 1]);
+            return true;
         };
-        JoiningThreads pool;
-        for (int t = 1; t < T; ++t) pool.t.emplace_back(order_worker, t);
-        order_worker(0);
-        pool.join();
+        const int parts = reorder == MGK_REORDER_PBR && n_graphs < 16 ? MGK_PBR_STARTS : 1;
+        std::vector<MgkPbrCandidate> cand((size_t)(parts > 1 ? n_graphs * parts : 0));
+        const int T = parts > 1 ? n_graphs * parts : std::min(n_graphs, 64);
+        ctx->workers.run(T, [&](int t) {
+            try {   // a worker that runs out of memory stops; the loop below orders what it left
+                MgkAdj a;
+                std::vector<int32_t> cur;
+                if (parts > 1) {
+                    if (adjacency(t % n_graphs, a, cur))
+                        cand[(size_t)((t % n_graphs) * parts + t / n_graphs)] = mgk_pbr_candidate(a, kTile, t / n_graphs);
+                    return;
+                }
+                for (int32_t g = t; g < n_graphs; g += T)
+                    if (adjacency(g, a, cur))
+                        pre_perm[(size_t)g] = reorder == MGK_REORDER_PBR ? mgk_order_pbr(a, kTile) : mgk_order_rcm(a);
+            } catch (...) {
+            }
+        }, (int)std::min<int64_t>(64, tot_e / 24));   // an edge takes about 3 us, starting a thread 20
+        for (int32_t g = 0; parts > 1 && g < n_graphs; ++g) pre_perm[(size_t)g] = mgk_pbr_best(&cand[(size_t)g * parts]);
     }
 
     for (int32_t g = 0; g < n_graphs; ++g) {
@@ -1506,7 +1731,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             for (int i = 0; i < n; ++i) cursor[(size_t)(max_deg - deg[i]) + 1]++;
             for (int d = 0; d <= max_deg; ++d) cursor[(size_t)d + 1] += cursor[(size_t)d];
             for (int i = 0; i < n; ++i) deg_order[(size_t)v0 + cursor[(size_t)(max_deg - deg[i])]++] = i;
-            gd.qoff = (int32_t)gptr[0].size();
+            qoff[(size_t)g] = (int32_t)gptr[0].size();
             for (int i = 0; i < n; i += 4) {   // four rows of adjacent degrees: the first has the most packets
                 const int d = deg[deg_order[(size_t)v0 + i]];
                 for (int q = 0; q < 2; ++q) {
@@ -1605,22 +1830,22 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->label_mean = B->nnz ? label_sum / (double)B->nnz : 0.0;
 
     // ---- upload as one allocation
-    std::vector<char> blob;
-    const size_t o_g = append_bytes(blob, B->graphs);
-    const size_t o_t = append_bytes(blob, B->tiles);
-    const size_t o_w = append_bytes(blob, B->w);
-    const size_t o_e = append_bytes(blob, B->e);
-    const size_t o_vl = append_bytes(blob, vlabel);
-    const size_t o_rs = append_bytes(blob, rowsum);
-    const size_t o_st = append_bytes(blob, start);
-    const size_t o_rp = append_bytes(blob, rowptr);
-    const size_t o_lp = append_bytes(blob, lanepos);
-    const size_t o_tr = append_bytes(blob, trow_ptr);
-    const size_t o_tg = append_bytes(blob, tile_graph);
-    const size_t o_ip = append_bytes(blob, iperm);
-    const size_t o_lo = append_bytes(blob, list_outer);
-    const size_t o_li = append_bytes(blob, list_inner);
-    const size_t o_sp = append_bytes(blob, regs_split);
+    BlobPlan blob;
+    const size_t o_g = blob.add(B->graphs);
+    const size_t o_t = blob.add(B->tiles);
+    const size_t o_w = blob.add(B->w);
+    const size_t o_e = blob.add(B->e);
+    const size_t o_vl = blob.add(vlabel);
+    const size_t o_rs = blob.add(rowsum);
+    const size_t o_st = blob.add(start);
+    const size_t o_rp = blob.add(rowptr);
+    const size_t o_lp = blob.add(lanepos);
+    const size_t o_tr = blob.add(trow_ptr);
+    const size_t o_tg = blob.add(tile_graph);
+    const size_t o_ip = blob.add(iperm);
+    const size_t o_lo = blob.add(list_outer);
+    const size_t o_li = blob.add(list_inner);
+    const size_t o_sp = blob.add(regs_split);
     std::vector<float> attr_outer, attr_inner;
     {
         attr_outer.assign((size_t)D * B->w.size(), 0.f);
@@ -1632,14 +1857,14 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             for (int a = 0; a < D; ++a)
                 attr_inner[(size_t)a * (size_t)lanes_total + (size_t)pe.first] = edge_label ? edge_label[pe.second * D + a] : 0.f;
     }
-    const size_t o_ao = append_bytes(blob, attr_outer);
-    const size_t o_ai = append_bytes(blob, attr_inner);
-    const size_t o_pk[2] = {append_bytes(blob, gptr[0]), append_bytes(blob, gptr[1])};
-    const size_t o_do = append_bytes(blob, deg_order);
-    const size_t o_df = append_bytes(blob, dense_off);
-    const size_t o_sd = append_bytes(blob, B->sell_desc);
-    const size_t o_sv = append_bytes(blob, sell_vtx);
-    const size_t o_sn = append_bytes(blob, sell_nbr);
+    const size_t o_ao = blob.add(attr_outer);
+    const size_t o_ai = blob.add(attr_inner);
+    const size_t o_pk[2] = {blob.add(gptr[0]), blob.add(gptr[1])};
+    const size_t o_do = blob.add(deg_order), o_qo = blob.add(qoff);
+    const size_t o_df = blob.add(dense_off);
+    const size_t o_sd = blob.add(B->sell_desc);
+    const size_t o_sv = blob.add(sell_vtx);
+    const size_t o_sn = blob.add(sell_nbr);
     B->dev.label_dim = D;
     B->dev.uniform_start = start_prob ? 0 : 1;
     B->dev.n_graphs = n_graphs;
@@ -1652,8 +1877,19 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         return MGK_OK;
     }
     MGK_HIP(ctx, hipSetDevice(ctx->device));
-    MGK_HIP(ctx, hipMalloc(&B->blob, blob.size()));
-    MGK_HIP(ctx, hipMemcpy(B->blob, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    if (mgk_status st = take_blob(ctx, blob.total, &B->blob, &B->blob_cap)) return st;
+    if (ctx->calls == 0 || blob.total > kMaxStagedBytes) {
+        std::vector<char> flat(blob.total);
+        blob.copy_to(flat.data());
+        MGK_HIP(ctx, hipMemcpy(B->blob, flat.data(), blob.total, hipMemcpyHostToDevice));
+    } else {   // on a stream of the context: waits for its own copy, not for the calls under way
+        Staging::Slot* slot;
+        if (!ctx->upload) MGK_HIP(ctx, hipStreamCreateWithFlags(&ctx->upload, hipStreamNonBlocking));
+        if (mgk_status st = staging_slot(ctx, blob.total, true, &slot)) return st;
+        blob.copy_to(static_cast<char*>(slot->p));
+        MGK_HIP(ctx, hipMemcpyAsync(B->blob, slot->p, blob.total, hipMemcpyHostToDevice, ctx->upload));
+        MGK_HIP(ctx, hipStreamSynchronize(ctx->upload));
+    }
     char* base = static_cast<char*>(B->blob);
     B->dev.graphs = reinterpret_cast<const MgkGraphDesc*>(base + o_g);
     B->dev.tiles = reinterpret_cast<const MgkTile*>(base + o_t);
@@ -1672,9 +1908,13 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->dev.regs_split = reinterpret_cast<const int32_t*>(base + o_sp);
     B->dev.attr_outer = reinterpret_cast<const float*>(base + o_ao);
     B->dev.attr_inner = reinterpret_cast<const float*>(base + o_ai);
-    for (int q = 0; q < 2; ++q) B->gptr_dev[q] = reinterpret_cast<const int32_t*>(base + o_pk[q]);
-    B->dev.deg_order = reinterpret_cast<const int32_t*>(base + o_do);
-    B->dev.dense_off = reinterpret_cast<const int64_t*>(base + o_df);
+    for (int q = 0; q < 2; ++q) {
+        B->sep[q].qoff = reinterpret_cast<const int32_t*>(base + o_qo);
+        B->sep[q].gptr = reinterpret_cast<const int32_t*>(base + o_pk[q]);
+        B->sep[q].deg_order = reinterpret_cast<const int32_t*>(base + o_do);
+        B->sep[q].dense_off = reinterpret_cast<const int64_t*>(base + o_df);
+        B->sep[q].total = B->packets[q];
+    }
     B->dev.sell_desc = reinterpret_cast<const MgkSellDesc*>(base + o_sd);
     B->dev.sell_vtx = reinterpret_cast<const MgkSellVertex*>(base + o_sv);
     B->dev.sell_nbr = reinterpret_cast<const MgkSellNbr*>(base + o_sn);
@@ -1686,10 +1926,13 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
 
 void mgk_free_batch(mgk_ctx* ctx, mgk_batch* batch) {
     if (!batch) return;
-    (void)ctx;
-    if (batch->blob || batch->gram_jobs.dev) (void)hipDeviceSynchronize();
+    bool kept = false;
+    if (ctx && ctx == batch->owner && batch->blob) {
+        try { kept = hipSetDevice(ctx->device) == hipSuccess && keep_blob(ctx, batch); } catch (...) {}
+    }
+    if ((batch->blob && !kept) || batch->gram_jobs.dev) (void)hipDeviceSynchronize();
     if (batch->gram_jobs.dev) (void)hipFree(batch->gram_jobs.dev);
-    if (batch->blob) (void)hipFree(batch->blob);
+    if (batch->blob && !kept) (void)hipFree(batch->blob);
     delete batch;
 }
 
@@ -1758,8 +2001,8 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     }
     if (batch->gram_jobs.dev == nullptr && G > 0) {
         // a4: job list, one job per unordered pair, kept with the batch
-        std::vector<HostJob> jobs;
-        jobs.reserve((size_t)(G * (G + 1) / 2));
+        JobPlan plan;
+        plan.jobs.reserve((size_t)(G * (G + 1) / 2));
         for (auto& v : batch->gram_jobs.large) v.clear();
         // the plans of the G (G + 1) / 2 pairs are independent: rows of the triangle in turn on
         // several threads, row i starting at pair i G - i (i - 1) / 2
@@ -1768,19 +2011,15 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
             const int cache = ctx->product_cache;
             const int attr_dim = attr_dim_of(ctx);
             const int forced = ctx->waves, limit = ctx->onchip_limit;
-            const int T = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)std::thread::hardware_concurrency(), 16, G / 64}));
-            auto plan_worker = [&](int t) {   // allocates nothing, cannot throw
+            const int T = (int)std::max<int64_t>(1, std::min<int64_t>(64, G / 64));
+            ctx->workers.run(T, [&](int t) {   // allocates nothing, cannot throw
                 for (int64_t i = t; i < G; i += T) {
                     PairPlan* row = plans.data() + (i * G - i * (i - 1) / 2);
                     for (int64_t j = i; j < G; ++j)
                         row[j - i] = plan_pair(batch->graphs[i], batch->graphs[j], &batch->sell_desc[(size_t)i],
                                                &batch->sell_desc[(size_t)j], true, forced, limit, cache, attr_dim);
                 }
-            };
-            JoiningThreads pool;
-            for (int t = 1; t < T; ++t) pool.t.emplace_back(plan_worker, t);
-            plan_worker(0);
-            pool.join();
+            });
         }
         size_t next_plan = 0;
         for (int64_t i = 0; i < G; ++i)
@@ -1791,14 +2030,6 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                 hj.job.g2 = (int32_t)(pl.swap ? i : j);
                 hj.job.out0 = (int32_t)(i * G + j);
                 hj.job.out1 = i == j ? -1 : (int32_t)(j * G + i);
-                hj.cost = pl.cost;
-                hj.lds_words = (int32_t)pl.lds_words;
-                hj.waves = (int16_t)pl.waves;
-                hj.ept = (int16_t)pl.ept;
-                hj.chunks = (int16_t)pl.chunks;
-                hj.sell_regs = (int16_t)pl.sell_regs;
-                hj.atomic_rows = pl.atomic_rows;
-                hj.swapped = false;  // one batch: swapping is done through the indices
                 if (pl.waves == 0) {  // vectors do not fit on chip
                     if ((int64_t)batch->graphs[i].n * batch->graphs[j].n >= ((int64_t)1 << 31) - 64)
                         return fail(ctx, MGK_ELIMIT, "pair (%lld, %lld) is too large", (long long)i, (long long)j);
@@ -1809,9 +2040,11 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                     batch->gram_jobs.large[0].push_back(P);
                     continue;
                 }
-                jobs.push_back(hj);
+                hj.cost = pl.cost;
+                hj.shape = plan.shape_of(pl, false);   // one batch: swapping is done through the indices
+                plan.jobs.push_back(hj);
             }
-        mgk_status st = build_job_list(ctx, jobs, batch->gram_jobs, stream, nullptr);
+        mgk_status st = build_job_list(ctx, plan, batch->gram_jobs, stream, nullptr);
         batch->gram_jobs_waves = ctx->waves;
         batch->gram_jobs_max_iter = ctx->max_iter;
         batch->gram_jobs_limit = ctx->onchip_limit;
@@ -1820,6 +2053,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         batch->gram_jobs_attr_dim = attr_dim_of(ctx);
         if (st != MGK_OK) return st;
     }
+    note_use(batch, stream);
     const MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
     return launch_jobs(ctx, batch, batch, batch->gram_jobs, out, stream);
 }
@@ -1842,27 +2076,28 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     MGK_HIP(ctx, hipSetDevice(ctx->device));
     // Either graph of a pair may be the outer operand; jobs whose outer graph
     // comes from Y are launched with the batch arguments exchanged.
-    std::vector<HostJob> jobs((size_t)n_pairs);
+    for (int64_t k = 0; k < n_pairs; ++k)
+        if (i_host[k] < 0 || i_host[k] >= X->n_graphs || j_host[k] < 0 || j_host[k] >= Y->n_graphs)
+            return fail(ctx, MGK_EINVAL, "pair %lld: graph index out of range", (long long)k);
+    std::vector<PairPlan> plans((size_t)n_pairs);
+    {
+        constexpr int64_t kPart = 1024;   // about 20 us of planning
+        const int attr_dim = attr_dim_of(ctx);
+        ctx->workers.run((int)((n_pairs + kPart - 1) / kPart), [&](int t) {   // allocates nothing, cannot throw
+            const int64_t end = std::min(n_pairs, (t + 1) * kPart);
+            for (int64_t k = t * kPart; k < end; ++k) {
+                const int32_t i = i_host[k], j = j_host[k];
+                plans[(size_t)k] = plan_pair(X->graphs[i], Y->graphs[j], &X->sell_desc[(size_t)i], &Y->sell_desc[(size_t)j], true,
+                                             ctx->waves, ctx->onchip_limit, ctx->product_cache, attr_dim);
+            }
+        });
+    }
+    JobPlan plan;
+    plan.jobs.reserve((size_t)n_pairs);
     std::vector<MgkLargePair> large[2];
     for (int64_t k = 0; k < n_pairs; ++k) {
         const int32_t i = i_host[k], j = j_host[k];
-        if (i < 0 || i >= X->n_graphs || j < 0 || j >= Y->n_graphs)
-            return fail(ctx, MGK_EINVAL, "pair %lld: graph index out of range", (long long)k);
-        const PairPlan pl = plan_pair(X->graphs[i], Y->graphs[j], &X->sell_desc[(size_t)i], &Y->sell_desc[(size_t)j], true,
-                                      ctx->waves, ctx->onchip_limit, ctx->product_cache, attr_dim_of(ctx));
-        HostJob& hj = jobs[(size_t)k];
-        hj.job.g1 = pl.swap ? j : i;
-        hj.job.g2 = pl.swap ? i : j;
-        hj.job.out0 = (int32_t)k;
-        hj.job.out1 = pl.swap ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
-        hj.cost = pl.cost;
-        hj.lds_words = (int32_t)pl.lds_words;
-        hj.waves = (int16_t)pl.waves;
-        hj.ept = (int16_t)pl.ept;
-        hj.chunks = (int16_t)pl.chunks;
-        hj.sell_regs = (int16_t)pl.sell_regs;
-        hj.atomic_rows = pl.atomic_rows;
-        hj.swapped = pl.swap && X != Y;
+        const PairPlan& pl = plans[(size_t)k];
         if (pl.waves == 0) {
             if (no_alloc)
                 return fail(ctx, MGK_ELIMIT, "pair %lld (%d x %d vertices) needs the global-memory solver, "
@@ -1874,21 +2109,31 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
             P.out0 = (int32_t)k;
             P.out1 = sw ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
             large[(sw && X != Y) ? 1 : 0].push_back(P);
-            hj.waves = 0;
+            continue;
         }
+        HostJob hj;
+        hj.job.g1 = pl.swap ? j : i;
+        hj.job.g2 = pl.swap ? i : j;
+        hj.job.out0 = (int32_t)k;
+        hj.job.out1 = pl.swap ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
+        hj.cost = pl.cost;
+        hj.shape = plan.shape_of(pl, pl.swap && X != Y);
+        plan.jobs.push_back(hj);
     }
-    if (ctx->pair_jobs_busy) {  // the previous call's kernels may still read the job buffer
+    // The previous call's kernels may still read the job buffer: on the same stream the copy below
+    // is ordered behind them.
+    if (!no_alloc && ctx->pair_jobs_busy && ctx->pair_jobs_stream != stream) {
         MGK_HIP(ctx, hipStreamSynchronize(ctx->pair_jobs_stream));
         ctx->pair_jobs_busy = false;
     }
-    jobs.erase(std::remove_if(jobs.begin(), jobs.end(), [](const HostJob& h) { return h.waves == 0; }),
-               jobs.end());
+    note_use(X, stream);
+    if (Y != X) note_use(Y, stream);
     MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
     if (no_alloc) {
         // Job list in the fixed array of this GPU.  All calls on the GPU share it: a call
         // that overlaps another one's kernels would overwrite the jobs they still read,
-        // so within this context the previous such call is waited for first.
-        if (ctx->fixed_jobs_busy) {
+        // so within this context a previous such call on another stream is waited for first.
+        if (ctx->fixed_jobs_busy && ctx->fixed_jobs_stream != stream) {
             MGK_HIP(ctx, hipStreamSynchronize(ctx->fixed_jobs_stream));
             ctx->fixed_jobs_busy = false;
         }
@@ -1896,22 +2141,25 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         int64_t cap = 0;
         hipError_t e = mgk_noalloc_job_storage(ctx->device, &fixed.dev, &cap);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "fixed job storage: %s", hipGetErrorString(e));
-        mgk_status st = build_job_list(ctx, jobs, fixed, stream, &cap, true);
+        mgk_status st = build_job_list(ctx, plan, fixed, stream, &cap, true);
         if (st != MGK_OK) return st;
         ctx->fixed_jobs_stream = stream;
         ctx->fixed_jobs_busy = true;
         return launch_jobs(ctx, X, Y, fixed, out, stream);
     }
-    mgk_status st = build_job_list(ctx, jobs, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
+    mgk_status st = build_job_list(ctx, plan, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
     if (st != MGK_OK) return st;
     for (int a = 0; a < 2; ++a) ctx->pair_jobs.large[a] = std::move(large[a]);
     ctx->pair_jobs_stream = stream;
     ctx->pair_jobs_busy = true;
     if (x_dev) {
         if ((st = ensure(ctx, ctx->nodal_off, (size_t)n_pairs * sizeof(int64_t))) != MGK_OK) return st;
-        MGK_HIP(ctx, hipMemcpyAsync(ctx->nodal_off.p, x_off_host, (size_t)n_pairs * sizeof(int64_t),
-                                    hipMemcpyHostToDevice, stream));
-        MGK_HIP(ctx, hipStreamSynchronize(stream));  // caller's array may be pageable
+        const size_t bytes = (size_t)n_pairs * sizeof(int64_t);
+        Staging::Slot* slot;
+        if ((st = staging_slot(ctx, bytes, true, &slot)) != MGK_OK) return st;
+        memcpy(slot->p, x_off_host, bytes);
+        MGK_HIP(ctx, hipMemcpyAsync(ctx->nodal_off.p, slot->p, bytes, hipMemcpyHostToDevice, stream));
+        if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
         out.nodal = x_dev;
         out.nodal_off = (const int64_t*)ctx->nodal_off.p;
     }

@@ -27,7 +27,6 @@ struct MgkGraphDesc {
     int32_t loff;         // first lane slot of the graph in batch-wide expanded inner lists
     int32_t regs_runs;    // longest run of outer nonzeros of one wavefront under regs_split:
                           // 4 wavefronts in bits 0-15, 8 wavefronts in bits 16-31
-    int32_t qoff;         // first entry in the packet group pointers (one per four vertices)
 };
 
 // Lane layout of a graph used as the inner operand of the on-chip XMV: the
@@ -87,8 +86,6 @@ struct MgkBatchDev {
     const struct MgkSellDesc* sell_desc;    // per graph, see MgkSellDesc
     const struct MgkSellVertex* sell_vtx;   // records of the owner-computes solver
     const struct MgkSellNbr* sell_nbr;
-    const int32_t* deg_order;   // per graph (index voff): its vertices by descending number of nonzeros
-    const int64_t* dense_off;   // per graph: sum over the graphs before it of (n rounded up to 64)^2
     int32_t n_graphs, n_tiles_total, nnz_total, lanes_total;
     int32_t label_dim;        // attributes per edge label (1 for plain scalar labels)
     int32_t uniform_start;    // 1: no starting probabilities were given, p_i = 1/n on every graph
@@ -391,12 +388,17 @@ static inline MGK_HD int32_t mgk_sep_per_packet(int32_t rk) { return rk == 1 ? 8
 static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
     return 4 * ((int64_t)MGK_SEP_SLAB(rk) * n2 + (int64_t)MGK_SEP_ROWS * (n2 | 1));
 }
-// Packets of a batch, in steps of 64 words (four rows of adjacent rank in deg_order, one packet
-// each): pass q at packets + q total 64; group t of graph g has steps gptr[qoff + t] ..
-// gptr[qoff + t + 1].  At least one step per batch is allocated.
+// What the separable product reads beside MgkBatchDev.  Packets of a batch come in steps of 64
+// words (four rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64;
+// group t of graph g has steps gptr[qoff[g] + t] .. gptr[qoff[g] + t + 1].  At least one step per
+// batch is allocated.
 struct MgkSepList {
+    const int32_t* qoff;        // per graph: first entry in gptr
+    const int32_t* gptr;        // per four vertices of a graph, and one more per graph
+    const int32_t* deg_order;   // per graph (index voff): its vertices by descending number of nonzeros
+    const int64_t* dense_off;   // per graph: sum over the graphs before it of (n rounded up to 64)^2
     const float* packets;
-    const int32_t* gptr;
+    const float* dense;         // dense F_k
     int32_t total;
 };
 

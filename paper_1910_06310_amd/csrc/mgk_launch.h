@@ -154,19 +154,19 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
 // ---- separable product (mgk_sep.hip) ------------------------------------------
 // Weak, so that the host code links without the kernels (host-only contexts never get here).
 #define MGK_KERNELS_OPTIONAL __attribute__((weak))
-// Packets (layout L, gptr and total of that packet size) and dense F_k of every graph of B.
-MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L, int max_n,
-                                                    const int32_t* gptr, int total, float* packets, hipStream_t stream);
-MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, int max_n, float* F,
-                                                          hipStream_t stream);
+// Packets (layout L; gptr and total of that packet size) and dense F_k of every graph of B.
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L,
+                                                    const MgkSepList& list, int max_n, float* packets, hipStream_t stream);
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepList& list, int max_n,
+                                                          float* F, hipStream_t stream);
 // y = XMV(p) and p^T a of iteration `it` for every pair that still iterates (check_only: y alone, for
 // the pairs marked by mgk_launch_large_outputs).  max_n1, max_n2: largest outer and inner graph.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
                                                    const MgkSepLayout& L, const MgkLargePair* pairs, MgkPairState* state,
                                                    float* vec, const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                    bool check_only, hipStream_t stream);
-MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const float* FX, const float* FY, int rank,
-                                                     const MgkLargePair* pairs, MgkPairState* state, float* vec,
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
+                                                     int rank, const MgkLargePair* pairs, MgkPairState* state, float* vec,
                                                      const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                      bool check_only, hipStream_t stream);
 // The two kernels over the vectors that follow a product which has already formed p^T a and

@@ -152,7 +152,11 @@ struct Bisector {
             if (g.ptr[v + 1] - g.ptr[v] < g.ptr[start + 1] - g.ptr[start]) start = v;
         start = bfs_far(g, start, mark, tag, dist, tmp);
         // conn[v] = edges from v into side 0 (only for side-1 vertices of the subset)
-        for (int v : V) gain[v] = 0;
+        for (int v : V) {
+            gain[v] = 0;
+            dist[v] = 0;   // edges inside the subset; -1 again below
+            for (int k = g.ptr[v]; k < g.ptr[v + 1]; ++k) dist[v] += mark[g.idx[k]] == tag;
+        }
         int grown = 0;
         auto add_to_left = [&](int v) {
             side[v] = 0;
@@ -169,13 +173,14 @@ struct Bisector {
                 if (side[v] == 0) continue;
                 // prefer vertices mostly attached to the grown side; among
                 // unattached ones (new component) prefer low degree
-                int in_sub = 0;
-                for (int k = g.ptr[v]; k < g.ptr[v + 1]; ++k) in_sub += mark[g.idx[k]] == tag;
+                const int in_sub = dist[v];
                 int key = gain[v] > 0 ? 1000000 + 2 * gain[v] - in_sub : -in_sub;
                 if (best < 0 || key > best_key) { best = v; best_key = key; }
             }
             add_to_left(best);
         }
+
+        for (int v : V) dist[v] = -1;
 
         refine_bisection(V, tag);
 
@@ -219,13 +224,14 @@ struct Bisector {
                 if (a < 0 || b < 0) break;
                 // look for a better partner among the top candidates of side 1
                 int best_b = b, best_g = -1000000;
+                const int near = gain[b] - 2;
+                for (int k = g.ptr[a]; k < g.ptr[a + 1]; ++k) dist[g.idx[k]] = 0;   // -1 again below
                 for (int v : V) {
-                    if (locked[v] || side[v] != 1 || gain[v] < gain[b] - 2) continue;
-                    int adj = 0;
-                    for (int k = g.ptr[a]; k < g.ptr[a + 1]; ++k) adj += g.idx[k] == v;
-                    int gsum = gain[a] + gain[v] - 2 * adj;
+                    if (gain[v] < near || locked[v] || side[v] != 1) continue;
+                    const int gsum = gain[a] + gain[v] - (dist[v] == 0 ? 2 : 0);
                     if (gsum > best_g) { best_g = gsum; best_b = v; }
                 }
+                for (int k = g.ptr[a]; k < g.ptr[a + 1]; ++k) dist[g.idx[k]] = -1;
                 b = best_b;
                 if (best_g < -4 && cum <= best_cum) break;  // hopeless tail
                 // apply swap
@@ -256,7 +262,7 @@ struct Bisector {
 struct PairCounts {
     int K;
     bool dense;
-    std::vector<int32_t> d;
+    std::vector<int32_t> d;   // symmetric
     std::unordered_map<uint64_t, int32_t> h;
     explicit PairCounts(int K_) : K(K_), dense(K_ <= 1024) {
         if (dense) d.assign((size_t)K * K, 0);
@@ -266,19 +272,28 @@ struct PairCounts {
         return ((uint64_t)(uint32_t)a << 32) | (uint32_t)b;
     }
     int get(int a, int b) const {
-        if (dense) return d[(size_t)std::min(a, b) * K + std::max(a, b)];
+        if (dense) return d[(size_t)a * K + b];
         auto it = h.find(key(a, b));
         return it == h.end() ? 0 : it->second;
     }
     void add(int a, int b, int delta) {
-        if (dense) d[(size_t)std::min(a, b) * K + std::max(a, b)] += delta;
-        else h[key(a, b)] += delta;
+        if (dense) {
+            d[(size_t)a * K + b] += delta;
+            if (a != b) d[(size_t)b * K + a] += delta;
+        } else {
+            h[key(a, b)] += delta;
+        }
     }
 };
 
 // K-way refinement on the objective of Eq. 3: swap two vertices of different
 // parts when that lowers the number of connected part pairs (ties: fewer cut
 // edges).  Part sizes never change.
+//
+// Trading places of v (part A) and u (part B) changes the edge counts of the pairs (A, P) and
+// (B, P) by +d and -d for every other part P, d = (edges of u into P) - (edges of v into P),
+// and that of (A, B) by what is left.  The edges of v into each part are counted once
+// per v and those of u while its few neighbours are walked.
 void kway_refine(const MgkAdj& g, std::vector<int32_t>& part, int K, int max_pass) {
     if (K < 2) return;
     PairCounts C(K);
@@ -290,55 +305,34 @@ void kway_refine(const MgkAdj& g, std::vector<int32_t>& part, int K, int max_pas
     std::vector<std::vector<int32_t>> members(K);
     for (int v = 0; v < g.n; ++v) members[part[v]].push_back(v);
 
-    // Trading places of v (part A) and u (part B) only changes the edge counts
-    // of pairs (A, P) and (B, P): dA[P] / dB[P] hold those changes.
-    std::vector<int> dA(K, 0), dB(K, 0), touched;
-    std::vector<char> seen(K, 0);
-    auto touch = [&](int P) {
-        if (!seen[P]) { seen[P] = 1; touched.push_back(P); }
-    };
-    auto collect = [&](int v, int u) {
-        const int A = part[v], B = part[u];
-        for (int P : touched) { dA[P] = dB[P] = 0; seen[P] = 0; }
-        touched.clear();
+    std::vector<int> cv(K, 0), cu(K, 0);   // edges into each part; zero between uses
+    std::vector<int> pv, pu;               // the parts with edges, each once
+    auto count = [&](int v, std::vector<int>& c, std::vector<int>& parts) {
+        for (int P : parts) c[P] = 0;
+        parts.clear();
         for (int k = g.ptr[v]; k < g.ptr[v + 1]; ++k) {
-            int w = g.idx[k];
-            if (w == u) continue;
-            const int P = part[w];
-            touch(P); dA[P] -= 1; dB[P] += 1;
+            const int P = part[g.idx[k]];
+            if (c[P]++ == 0) parts.push_back(P);
         }
-        for (int k = g.ptr[u]; k < g.ptr[u + 1]; ++k) {
-            int w = g.idx[k];
-            if (w == v) continue;
-            const int P = part[w];
-            touch(P); dB[P] -= 1; dA[P] += 1;
-        }
-        (void)A; (void)B;
+    };
+    auto adjacent = [&](int v, int u) {
+        for (int k = g.ptr[v]; k < g.ptr[v + 1]; ++k)
+            if (g.idx[k] == u) return 1;
+        return 0;
     };
     auto change = [&](int a, int b, int d) { const int c = C.get(a, b); return ((c + d) > 0) - (c > 0); };
-    // change of (connected pairs, cut edges) if v (part A) and u (part B) trade places
-    auto eval_swap = [&](int v, int u, int& dpairs, int& dcut) {
-        const int A = part[v], B = part[u];
-        collect(v, u);
-        dpairs = 0; dcut = 0;
-        for (int P : touched) {
-            if (P == A || P == B) continue;
-            if (dA[P]) { dpairs += change(A, P, dA[P]); dcut += dA[P]; }
-            if (dB[P]) { dpairs += change(B, P, dB[P]); dcut += dB[P]; }
-        }
-        const int dab = dA[B] + dB[A];
-        if (dab) { dpairs += change(A, B, dab); dcut += dab; }
+    // f(P, d) for every part P besides A and B whose counts change; cv and cu are up to date
+    auto for_changes = [&](int A, int B, auto&& f) {
+        for (int P : pv)
+            if (P != A && P != B && cu[P] != cv[P]) f(P, cu[P] - cv[P]);
+        for (int P : pu)
+            if (P != A && P != B && cv[P] == 0) f(P, cu[P]);
     };
     auto apply_swap = [&](int v, int u) {
         const int A = part[v], B = part[u];
-        collect(v, u);
-        for (int P : touched) {
-            if (P != A && P != B) {
-                if (dA[P]) C.add(A, P, dA[P]);
-                if (dB[P]) C.add(B, P, dB[P]);
-            }
-        }
-        const int dab = dA[B] + dB[A];
+        count(u, cu, pu);
+        for_changes(A, B, [&](int P, int d) { C.add(A, P, d); C.add(B, P, -d); });
+        const int dab = cu[B] - cv[B] + cv[A] - cu[A] + 2 * adjacent(v, u);
         if (dab) C.add(A, B, dab);
         // diagonal counts are never read
         part[v] = B; part[u] = A;
@@ -357,18 +351,21 @@ void kway_refine(const MgkAdj& g, std::vector<int32_t>& part, int K, int max_pas
         int64_t gained = 0;
         for (int v = 0; v < g.n; ++v) {
             const int A = part[v];
+            count(v, cv, pv);
             cand_parts.clear();
-            for (int k = g.ptr[v]; k < g.ptr[v + 1]; ++k) {
-                int P = part[g.idx[k]];
-                if (P != A && std::find(cand_parts.begin(), cand_parts.end(), P) == cand_parts.end())
-                    cand_parts.push_back(P);
-            }
+            for (int P : pv)
+                if (P != A) cand_parts.push_back(P);
             if (cand_parts.empty()) continue;
             int best_u = -1, best_dp = 0, best_dc = 0;
             for (int B : cand_parts)
                 for (int u : members[B]) {
-                    int dp, dc;
-                    eval_swap(v, u, dp, dc);
+                    // change of (connected pairs, cut edges) if v and u trade places
+                    count(u, cu, pu);
+                    int dp = 0;
+                    for_changes(A, B, [&](int P, int d) { dp += change(A, P, d) + change(B, P, -d); });
+                    int dc = cu[B] - cv[B] + cv[A] - cu[A];
+                    if (cu[A] > 0) dc += 2 * adjacent(u, v);
+                    if (dc) dp += change(A, B, dc);
                     if (dp < best_dp || (dp == best_dp && dc < best_dc)) {
                         best_dp = dp; best_dc = dc; best_u = u;
                     }
@@ -387,43 +384,46 @@ void kway_refine(const MgkAdj& g, std::vector<int32_t>& part, int K, int max_pas
 
 }  // namespace
 
-std::vector<int32_t> mgk_order_pbr(const MgkAdj& g, int t) {
+// Three starting partitions, each refined on Eq. 3; the best one wins: recursive bisection,
+// blocks of t consecutive vertices in reverse Cuthill-McKee order (strong on banded /
+// lattice-like graphs), and blocks of the given order (strong when the input already has
+// locality).
+MgkPbrCandidate mgk_pbr_candidate(const MgkAdj& g, int t, int start) {
     const int n = g.n;
     const int K = (n + t - 1) / t;
-    if (K <= 1) return mgk_order_identity(n);
     // With an average degree of several tiles' width every pair of parts is
     // connected whatever the order: nothing to gain, and the swap search would
     // cost O(n K t deg^2).
-    if ((int64_t)g.idx.size() > (int64_t)4 * t * n) return mgk_order_identity(n);
-    // Three starting partitions, each refined on Eq. 3; the best one wins:
-    // recursive bisection, blocks of t consecutive vertices in reverse
-    // Cuthill-McKee order (strong on banded / lattice-like graphs), and blocks
-    // of the given order (strong when the input already has locality).
-    auto blocks_of = [&](const std::vector<int32_t>& order) {
-        std::vector<int32_t> part(n);
+    if (K <= 1 || (int64_t)g.idx.size() > (int64_t)4 * t * n) return {mgk_order_identity(n), 0};
+    std::vector<int32_t> part(n);
+    if (start == 0) {
+        Bisector bis(g, t);
+        bis.run();
+        part.swap(bis.part);
+    } else {
+        const std::vector<int32_t> order = start == 1 ? mgk_order_rcm(g) : mgk_order_identity(n);
         for (int v = 0; v < n; ++v) part[v] = order[v] / t;
-        return part;
-    };
-    auto to_perm = [&](const std::vector<int32_t>& part) {
-        std::vector<int32_t> perm(n), fill(K, 0);
-        for (int v = 0; v < n; ++v) perm[v] = part[v] * t + fill[part[v]]++;
-        return perm;
-    };
-    Bisector bis(g, t);
-    bis.run();
-    std::vector<std::vector<int32_t>> starts;
-    starts.push_back(bis.part);
-    starts.push_back(blocks_of(mgk_order_rcm(g)));
-    starts.push_back(blocks_of(mgk_order_identity(n)));
-    std::vector<int32_t> best_perm;
-    int64_t best_count = -1;
-    for (auto& part : starts) {
-        kway_refine(g, part, K, 8);
-        std::vector<int32_t> perm = to_perm(part);
-        const int64_t count = mgk_count_offdiag_tiles(g, perm, t);
-        if (best_count < 0 || count < best_count) { best_count = count; best_perm.swap(perm); }
     }
-    return best_perm;
+    kway_refine(g, part, K, 8);
+    std::vector<int32_t> perm(n), fill(K, 0);
+    for (int v = 0; v < n; ++v) perm[v] = part[v] * t + fill[part[v]]++;
+    const int64_t count = mgk_count_offdiag_tiles(g, perm, t);
+    return {std::move(perm), count};
+}
+
+std::vector<int32_t> mgk_pbr_best(MgkPbrCandidate* c) {
+    int best = 0;
+    for (int s = 0; s < MGK_PBR_STARTS; ++s) {
+        if (c[s].perm.empty()) return {};   // not computed
+        if (c[s].offdiag_tiles < c[best].offdiag_tiles) best = s;
+    }
+    return std::move(c[best].perm);
+}
+
+std::vector<int32_t> mgk_order_pbr(const MgkAdj& g, int t) {
+    MgkPbrCandidate c[MGK_PBR_STARTS];
+    for (int s = 0; s < MGK_PBR_STARTS; ++s) c[s] = mgk_pbr_candidate(g, t, s);
+    return mgk_pbr_best(c);
 }
 
 int64_t mgk_count_offdiag_tiles(const MgkAdj& g, const std::vector<int32_t>& perm, int t) {

@@ -23,6 +23,15 @@ std::vector<int32_t> mgk_order_rcm(const MgkAdj& g);
 // pairs of distinct parts joined by an edge (Eq. 3); part k occupies new ids
 // [k t, (k+1) t).
 std::vector<int32_t> mgk_order_pbr(const MgkAdj& g, int t);
+// The same in pieces that can be computed at the same time: the refined partition from starting
+// partition 0 .. MGK_PBR_STARTS - 1, and the choice among all of them (empty if one is missing).
+#define MGK_PBR_STARTS 3
+struct MgkPbrCandidate {
+    std::vector<int32_t> perm;
+    int64_t offdiag_tiles = 0;
+};
+MgkPbrCandidate mgk_pbr_candidate(const MgkAdj& g, int t, int start);
+std::vector<int32_t> mgk_pbr_best(MgkPbrCandidate* candidates);
 
 // Space-filling-curve order for vertices with coordinates (Section IV-A): each of the
 // `dim` (1..3) coordinates is scaled to the graph's bounding box and quantised to 10

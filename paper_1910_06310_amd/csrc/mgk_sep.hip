@@ -43,17 +43,18 @@ __device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const float* 
 // the slab of column j each; absent nonzeros have coefficients 0 and offset 0.  One wavefront
 // per group.
 __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepLayout L,
-                                                           const int32_t* gptr, int total, float* out) {
+                                                           MgkSepList list, int g0, float* out) {
     __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
     for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
-    const MgkGraphDesc g = B.graphs[blockIdx.y];
+    const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
+    const int32_t* gptr = list.gptr + list.qoff[g0 + blockIdx.y];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = lane & 15, u = slot / (L.rk + 1), kk = slot - u * (L.rk + 1);
     for (int grp = blockIdx.x * 4 + wave; grp * 4 < g.n; grp += gridDim.x * 4) {
-        const int p0 = gptr[g.qoff + grp], p1 = gptr[g.qoff + grp + 1];
+        const int p0 = gptr[grp], p1 = gptr[grp + 1];
         const int pos = grp * 4 + (lane >> 4);
-        const int row = B.deg_order[g.voff + min(pos, g.n - 1)];
+        const int row = list.deg_order[g.voff + min(pos, g.n - 1)];
         const int z0 = B.rowptr[g.voff + row];
         const int z1 = pos >= g.n ? z0 : row + 1 < g.n ? B.rowptr[g.voff + row + 1] : g.nnz;
         for (int p = p0; p < p1; ++p) {
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
                 float v = 0.f;
                 if (on && kk < L.rk && k < S.rank) v = w * sep_feature(S, coef, __uint_as_float(e.z), k);
                 if (on && kk == L.rk) v = __uint_as_float(e.y * (uint32_t)L.slab_bytes);
-                out[((int64_t)q * total + p) * 64 + lane] = v;
+                out[((int64_t)q * list.total + p) * 64 + lane] = v;
             }
         }
     }
@@ -74,14 +75,14 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
 
 // Dense F_k of every graph: F[(dense_off[g] * rank) + (k np + i) np + j], np = n rounded up to 64,
 // zero where there is no edge.  One wavefront per (row, graph): clears the row, then fills it.
-__global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, float* out) {
+__global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepList list, int g0, float* out) {
     __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
     for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
-    const MgkGraphDesc g = B.graphs[blockIdx.y];
+    const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int np = (g.n + 63) & ~63;
-    float* F = out + B.dense_off[blockIdx.y] * S.rank;
+    float* F = out + list.dense_off[g0 + blockIdx.y] * S.rank;
     for (int row = blockIdx.x * 4 + wave; row < np; row += gridDim.x * 4) {
         for (int k = 0; k < S.rank; ++k)
             for (int c = lane; c < np; c += 64) F[((int64_t)k * np + row) * np + c] = 0.f;
@@ -147,14 +148,14 @@ __global__ __launch_bounds__(1024) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBat
     const int n1 = P.n1, n2 = P.n2, rows = min(MGK_SEP_ROWS, n1 - i0);
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = vec + P.vec + 4 * (int64_t)P.npad;
-    const int32_t* order1 = X.deg_order + g1.voff;
-    const int32_t* order2 = Y.deg_order + g2.voff;
+    const int32_t* order1 = SX.deg_order + g1.voff;
+    const int32_t* order2 = SY.deg_order + g2.voff;
     float* tile = lds + SLAB * n2;                    // y of the 16 rows, row stride n2 | 1
     const int tp = n2 | 1;
     char* slabs = reinterpret_cast<char*>(lds);
     const int groups2 = (n2 + 3) >> 2;
-    const int32_t* gp1 = SX.gptr + g1.qoff;
-    const int32_t* gp2 = SY.gptr + g2.qoff;
+    const int32_t* gp1 = SX.gptr + SX.qoff[P.g1];
+    const int32_t* gp2 = SY.gptr + SY.qoff[P.g2];
     for (int q = 0; q < L.passes; ++q) {
         // ---- stage 1: one row per wavefront (rows of a workgroup have similar degrees)
         for (int ii = wave; ii < rows; ii += NW) {
@@ -222,8 +223,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // Sums are kept in levels of 64 terms to bound the fp32 rounding bias of long running sums.
 // Bound by the matrix cores: 128 multiply-adds per clk and CU in fp32.
 template <int NT>
-__global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, const float* FX,
-                                                            const float* FY, int rank, const MgkLargePair* pairs,
+__global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
+                                                            MgkSepList SY, int rank, const MgkLargePair* pairs,
                                                             MgkPairState* state, float* vec, MgkParams prm,
                                                             int n_pairs, int blocks, int it, int check_only) {
     extern __shared__ __align__(16) float lds[];   // T_k, 32 rows of stride tp
@@ -240,8 +241,8 @@ __global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBa
     if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
     const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
-    const float* F1 = FX + X.dense_off[P.g1] * rank + i0;
-    const float* F2 = FY + Y.dense_off[P.g2] * rank;
+    const float* F1 = SX.dense + SX.dense_off[P.g1] * rank + i0;
+    const float* F2 = SY.dense + SY.dense_off[P.g2] * rank;
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = vec + P.vec + 4 * (int64_t)P.npad;
     const int tp = np2 + 1;
@@ -376,30 +377,22 @@ hipError_t set_lds(const void* kern, bool* configured) {
 
 }  // namespace
 
-hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L, int max_n,
-                               const int32_t* gptr, int total, float* packets, hipStream_t stream) {
-    if (B.n_graphs <= 0) return hipSuccess;
+hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L, const MgkSepList& list,
+                               int max_n, float* packets, hipStream_t stream) {
     // the graph index is a grid dimension of at most 65535: batches of more graphs go in parts
     const int gx = (max_n + 15) / 16;
-    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535) {
-        MgkBatchDev part = B;
-        part.graphs += g0;
+    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535)
         hipLaunchKernelGGL(mgk_sep_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
-                           stream, part, S, L, gptr, total, packets);
-    }
+                           stream, B, S, L, list, g0, packets);
     return hipGetLastError();
 }
 
-hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, int max_n, float* F, hipStream_t stream) {
-    if (B.n_graphs <= 0) return hipSuccess;
+hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepList& list, int max_n, float* F,
+                                     hipStream_t stream) {
     const int gx = (max_n + 63) / 16;
-    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535) {
-        MgkBatchDev part = B;
-        part.graphs += g0;
-        part.dense_off += g0;
+    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535)
         hipLaunchKernelGGL(mgk_sep_dense_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
-                           stream, part, S, F);
-    }
+                           stream, B, S, list, g0, F);
     return hipGetLastError();
 }
 
@@ -427,7 +420,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
     return hipGetLastError();
 }
 
-hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const float* FX, const float* FY, int rank,
+hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
                                 const MgkLargePair* pairs, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
     const int blocks = (max_n1 + 31) / 32;
@@ -441,7 +434,7 @@ hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, cons
         static bool configured = false; \
         hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
         if (e != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, grid, dim3(256), bytes, stream, X, Y, FX, FY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        hipLaunchKernelGGL(kern, grid, dim3(256), bytes, stream, X, Y, SX, SY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
     }
     if (np2 <= 256) MGK_SEP_DENSE_GO(1)
     else if (np2 <= 512) MGK_SEP_DENSE_GO(2)
