@@ -736,26 +736,25 @@ const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
     ctx->sep_lo = lo;
     ctx->sep_hi = hi;
     if (ctx->edge_kernel == MGK_EK_CONST) {
-        S.rank = 1;
-        S.coef[0] = (float)std::sqrt((double)ctx->ke_const);
+        S.rank = S.terms = 1;
+        S.coef[0] = std::sqrt((double)ctx->ke_const);
         return S;
     }
     if (ctx->edge_kernel != MGK_EK_SE) return S;
-    S.center = (float)(0.5 * ((double)lo + (double)hi));
-    const double R = std::max((double)hi - (double)S.center, (double)S.center - (double)lo);
+    S.center = 0.5 * ((double)lo + (double)hi);
+    const double R = std::max((double)hi - S.center, S.center - (double)lo);
     const double l = (double)ctx->length_scale, t = R * R / (l * l);
-    S.inv_r = R > 0.0 ? (float)(1.0 / R) : 0.f;
-    S.e_scale = (float)(std::sqrt(0.5 * 1.4426950408889634) / l);
-    // |exp(t s s') - its Chebyshev sum below degree r| falls like (t / 2)^r / r!: hopeless beyond this
-    if (!(t <= 12.0)) return S;
-    // Chebyshev coefficients of exp(t s s') from its values on a grid of nodes, both variables
-    constexpr int N = 40, D = MGK_SEP_MAX_RANK;
-    static const double pi = 3.14159265358979323846;
-    std::vector<double> cosm((size_t)D * N), half((size_t)D * N);
+    S.inv_r = R > 0.0 ? 1.0 / R : 0.0;
+    // |exp(t s s') - its Chebyshev sum of rank r| falls like 4 (t / 4)^r / r!: hopeless beyond this
+    if (!(t <= 8.0)) return S;
+    constexpr int N = 48, D = 2 * MGK_SEP_MAX_TERMS, MaxR = MGK_SEP_MAX_RANK;
+    const double pi = 3.14159265358979323846;
     double node[N];
     for (int i = 0; i < N; ++i) node[i] = std::cos(pi * (i + 0.5) / N);
+    std::vector<double> cosm((size_t)D * N), half((size_t)D * N), C((size_t)D * D, 0.0);
     for (int m = 0; m < D; ++m)
         for (int i = 0; i < N; ++i) cosm[(size_t)m * N + i] = std::cos(pi * m * (i + 0.5) / N) * (m ? 2.0 : 1.0) / N;
+    // Chebyshev coefficients of exp(t s s') from its values on a grid of nodes, both variables
     for (int i = 0; i < N; ++i) {
         double row[N];
         for (int j = 0; j < N; ++j) row[j] = std::exp(t * node[i] * node[j]);
@@ -765,49 +764,69 @@ const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
             half[(size_t)m * N + i] = v;
         }
     }
-    double Cm[D][D], Lm[D][D] = {};
     for (int m = 0; m < D; ++m)
-        for (int n = 0; n <= m; ++n) {
+        for (int n = m & 1; n <= m; n += 2) {   // the function is even in (s, s') together
             double v = 0.0;
-            if (((m + n) & 1) == 0)   // the function is even in (s, s') together
-                for (int i = 0; i < N; ++i) v += half[(size_t)m * N + i] * cosm[(size_t)n * N + i];
-            Cm[m][n] = Cm[n][m] = v;
+            for (int i = 0; i < N; ++i) v += half[(size_t)m * N + i] * cosm[(size_t)n * N + i];
+            C[(size_t)m * D + n] = C[(size_t)n * D + m] = v;
         }
-    // Cholesky row by row; after row r - 1 the rank-r sum is complete: its error on a grid
-    constexpr int E = 17;
-    double feat[E][D] = {};   // phi without the Gaussian, at the grid points
-    double T[E][D];
-    for (int e = 0; e < E; ++e) {
-        const double s = std::cos(pi * e / (E - 1));
-        for (int m = 0; m < D; ++m) T[e][m] = m == 0 ? 1.0 : m == 1 ? s : 2.0 * s * T[e][m - 1] - T[e][m - 2];
-    }
-    for (int r = 0; r < D; ++r) {
-        for (int k = 0; k < r; ++k) {
-            double v = Cm[r][k];
-            for (int q = 0; q < k; ++q) v -= Lm[r][q] * Lm[k][q];
-            Lm[r][k] = v / Lm[k][k];
-        }
-        double d = Cm[r][r];
-        for (int q = 0; q < r; ++q) d -= Lm[r][q] * Lm[r][q];
-        if (!(d > 0.0)) d = 0.0;
-        Lm[r][r] = std::sqrt(d);
+    // monomial coefficients of the Chebyshev polynomials
+    std::vector<double> mono((size_t)D * D, 0.0);
+    mono[0] = 1.0;
+    mono[(size_t)D + 1] = 1.0;
+    for (int m = 2; m < D; ++m)
+        for (int j = 0; j <= m; ++j)
+            mono[(size_t)m * D + j] = (j ? 2.0 * mono[(size_t)(m - 1) * D + j - 1] : 0.0) - mono[(size_t)(m - 2) * D + j];
+    constexpr int E = 33;
+    double grid[E], feat[E][MaxR];
+    for (int e = 0; e < E; ++e) grid[e] = std::cos(pi * e / (E - 1));
+    // error of the first r columns with `terms` terms, on the grid
+    auto error = [&](int r, int terms) {
         for (int e = 0; e < E; ++e)
-            for (int k = 0; k <= r; ++k) feat[e][k] += Lm[r][k] * T[e][r];
+            for (int k = 0; k < r; ++k) {
+                double v = 0.0;
+                for (int m = terms - 1; m >= 0; --m) v = v * grid[e] * grid[e] + S.coef[m * MaxR + k];
+                feat[e][k] = k & 1 ? v * grid[e] : v;
+            }
         double err = 0.0;
         for (int e = 0; e < E; ++e)
             for (int f = 0; f <= e; ++f) {
-                const double se = T[e][1], sf = T[f][1];
-                double v = std::exp(t * se * sf);
-                for (int k = 0; k <= r; ++k) v -= feat[e][k] * feat[f][k];
-                err = std::max(err, std::fabs(v) * std::exp(-0.5 * t * (se * se + sf * sf)));
+                double v = std::exp(-0.5 * t * (grid[e] - grid[f]) * (grid[e] - grid[f]));
+                for (int k = 0; k < r; ++k) v -= feat[e][k] * feat[f][k];
+                err = std::max(err, std::fabs(v));
             }
-        if (err <= MGK_SEP_TOLERANCE) {
-            S.rank = r + 1;
-            for (int m = 0; m <= r; ++m)
-                for (int k = 0; k <= m; ++k) S.coef[m * MGK_SEP_MAX_RANK + k] = (float)Lm[m][k];
-            return S;
+        return err;
+    };
+    for (int k = 0; k < MaxR; ++k) {
+        // column k of the Cholesky factor, as a function times the Gaussian, as a polynomial
+        const double d = C[(size_t)k * D + k];
+        if (!(d > 0.0)) return S;   // no further degree can be resolved in double
+        double col[D], cheb[D], poly[D] = {};
+        for (int m = 0; m < D; ++m) col[m] = C[(size_t)m * D + k] / std::sqrt(d);
+        for (int m = 0; m < D; ++m)
+            for (int n = m & 1; n < D; n += 2) C[(size_t)m * D + n] -= col[m] * col[n];
+        double val[N];
+        for (int i = 0; i < N; ++i) {
+            double v = 0.0;
+            for (int m = k & 1; m < D; m += 2) v += col[m] * cosm[(size_t)m * N + i] * (m ? 0.5 * N : N);
+            val[i] = v * std::exp(-0.5 * t * node[i] * node[i]);
         }
-        if (d == 0.0) return S;   // no further degree can be resolved in double
+        for (int m = 0; m < D; ++m) {
+            cheb[m] = 0.0;
+            for (int i = 0; i < N && ((m ^ k) & 1) == 0; ++i) cheb[m] += val[i] * cosm[(size_t)m * N + i];
+        }
+        int last = D - 1;   // what is left above is rounding noise, which the monomials would amplify
+        while (last > 0 && std::fabs(cheb[last]) < 1e-12) --last;
+        for (int m = k & 1; m <= last; m += 2)
+            for (int j = m & 1; j <= m; j += 2) poly[j] += cheb[m] * mono[(size_t)m * D + j];
+        for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m) S.coef[m * MaxR + k] = poly[2 * m + (k & 1)];
+        if (error(k + 1, MGK_SEP_MAX_TERMS) > MGK_SEP_TOLERANCE) continue;
+        S.rank = k + 1;
+        S.terms = 1;
+        for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m)
+            for (int q = 0; q <= k; ++q)
+                if (S.coef[m * MaxR + q] != 0.0) S.terms = m + 1;
+        return S;
     }
     return S;
 }

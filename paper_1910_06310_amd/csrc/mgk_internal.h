@@ -362,18 +362,20 @@ static inline int32_t mgk_sell_need(const MgkSellDesc& o, const MgkSellDesc& i, 
 
 // ---- separable edge kernel (mgk_sep.hip) --------------------------------------
 // kappa_e(e, e') = sum_{k < rank} phi_k(e) phi_k(e') on the label range of the batches, with
-//   phi_k(e) = exp2(-(e_scale u)^2) sum_m coef[m][k] T_m(u / R),  u = e - center,
-// T_m the Chebyshev polynomials: exp(-(e - e')^2 / 2 l^2) is the product of two Gaussians and
-// exp(u u' / l^2), whose Chebyshev coefficients on [-R, R]^2 form a positive definite matrix
-// that falls off faster than geometrically; coef is its Cholesky factor.  The constant kernel
-// is rank 1.  The host takes the smallest rank whose error over the range is at most
-// MGK_SEP_TOLERANCE, half a unit in the last place of the largest value of kappa_e.
-#define MGK_SEP_MAX_RANK 20
-#define MGK_SEP_TOLERANCE 3e-8
+//   phi_k(e) = s^(k mod 2) sum_{m < terms} coef[m][k] s^(2 m),   s = (e - center) / R in [-1, 1].
+// exp(-(e - e')^2 / 2 l^2) is the product of two Gaussians and exp(u u' / l^2), u = e - center,
+// whose Chebyshev coefficients on [-R, R]^2 form a positive definite matrix that falls off faster
+// than geometrically.  The first `rank` columns of its Cholesky factor, all their rows, times the
+// Gaussian are the phi_k; each is even or odd.  The constant kernel is rank 1.  The host takes
+// the smallest rank whose error over the range is at most MGK_SEP_TOLERANCE, half a unit in the
+// last place of the largest value of kappa_e.
+#define MGK_SEP_MAX_RANK 16
+#define MGK_SEP_MAX_TERMS 16
+#define MGK_SEP_TOLERANCE 5.9e-8
 struct MgkSepBasis {
-    int32_t rank;
-    float center, inv_r, e_scale;
-    float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];   // [m][k]
+    int32_t rank, terms;
+    double center, inv_r;
+    double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];   // [m][k]
 };
 // How the rank is divided for the sparse product: `passes` passes of `rk` (1, 4, 5, 6 or 7)
 // features each, per_packet nonzeros to a packet of 16 words (rk coefficients and one offset

@@ -23,18 +23,12 @@
 namespace {
 
 // phi_k(e) for the label e (see MgkSepBasis), in double so that the features are correctly
-// rounded: they are made once per call and used in every iteration.
-__device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const float* coef, float label, int k) {
-    const double u = (double)label - (double)S.center;
-    const double s = u * (double)S.inv_r, g = u * (double)S.e_scale;
-    double t0 = 1.0, t1 = s, v = 0.0;
-    for (int m = 0; m < S.rank; ++m) {
-        v = fma((double)coef[m * MGK_SEP_MAX_RANK + k], t0, v);
-        const double t2 = fma(2.0 * s, t1, -t0);
-        t0 = t1;
-        t1 = t2;
-    }
-    return (float)(v * exp2(-g * g));
+// rounded: they are made once per call and used in every iteration.  coef: S.coef, in LDS.
+__device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const double* coef, float label, int k) {
+    const double s = ((double)label - S.center) * S.inv_r, s2 = s * s;
+    double v = 0.0;
+    for (int m = S.terms - 1; m >= 0; --m) v = fma(v, s2, coef[m * MGK_SEP_MAX_RANK + k]);
+    return (float)(k & 1 ? v * s : v);
 }
 
 // Packets of the graphs of a batch: the vertices of a graph in order of descending degree, in
@@ -44,8 +38,8 @@ __device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const float* 
 // per group.
 __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepLayout L,
                                                            MgkSepList list, int g0, float* out) {
-    __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
-    for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
+    __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
+    for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
     const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
     const int32_t* gptr = list.gptr + list.qoff[g0 + blockIdx.y];
@@ -76,8 +70,8 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
 // Dense F_k of every graph: F[(dense_off[g] * rank) + (k np + i) np + j], np = n rounded up to 64,
 // zero where there is no edge.  One wavefront per (row, graph): clears the row, then fills it.
 __global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepList list, int g0, float* out) {
-    __shared__ float coef[MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK];
-    for (int k = threadIdx.x; k < MGK_SEP_MAX_RANK * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
+    __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
+    for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
     const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
