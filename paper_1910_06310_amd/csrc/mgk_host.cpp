@@ -167,6 +167,7 @@ struct mgk_batch {
     void* blob = nullptr;
     size_t blob_cap = 0;
     std::vector<hipStream_t> used_on;   // streams with calls that read the batch
+    bool captured = false;              // a recorded graph reads it, replayed on streams unknown here
     MgkBatchDev dev{};
     JobList gram_jobs;
     int gram_jobs_waves = 0;       // waves_per_pair setting the list was built for
@@ -333,7 +334,24 @@ int attr_dim_of(const mgk_ctx* ctx) {
     return ctx->edge_kernel == MGK_EK_KRON_SE || ctx->edge_kernel == MGK_EK_RCONV_SE ? ctx->label_dim : 0;
 }
 
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {   // the default stream while another one records
+        (void)hipGetLastError();
+        return true;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
+// Calls that stage their lists in pinned memory are refused while a graph is recorded: a replay would
+// copy what later calls have put there.
+mgk_status refuse_capture(mgk_ctx* ctx, hipStream_t stream) {
+    if (!capturing(stream)) return MGK_OK;
+    return fail(ctx, MGK_EDEVICE, "operation not permitted when stream is capturing");
+}
+
 void note_use(mgk_batch* b, hipStream_t stream) {
+    if (capturing(stream)) b->captured = true;
     if (std::find(b->used_on.begin(), b->used_on.end(), stream) == b->used_on.end()) b->used_on.push_back(stream);
 }
 
@@ -946,7 +964,9 @@ mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
 
 // Keeps the block of a batch that is being freed, unless there are enough or it is large.
 bool keep_blob(mgk_ctx* ctx, mgk_batch* b) {
-    if (ctx->blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes) return false;
+    if (ctx->blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes || b->captured) return false;
+    for (hipStream_t s : b->used_on)
+        if (capturing(s)) return false;   // an event recorded now would never complete
     FreeBlob f;
     f.p = b->blob;
     f.cap = b->blob_cap;
@@ -1139,7 +1159,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         hipError_t e;
         sl[k] = bt[k]->sep[gi];
         DevBuf& buf = dense ? ctx->sep_dense[k] : ctx->sep_packets[k];
-        const size_t floats = dense ? (size_t)bt[k]->dense_floats * S.rank : (size_t)L.passes * sl[k].total * 64;
+        const size_t floats = dense ? (size_t)bt[k]->dense_floats * S.rank : ((size_t)L.passes * sl[k].total + 1) * 64;   // stage 2 may load one step past the last
         if ((st = ensure(ctx, buf, std::max<size_t>(256, floats * sizeof(float)))) != MGK_OK) return st;
         (dense ? sl[k].dense : sl[k].packets) = (const float*)buf.p;
         e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, sl[k], bt[k]->max_n, (float*)buf.p, stream)
@@ -1226,6 +1246,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
         }
     }
     if (jl.large[0].empty() && jl.large[1].empty()) return MGK_OK;
+    if (mgk_status st = refuse_capture(ctx, stream)) return st;
     // ---- pairs with vectors in global memory: the product of each from the current edge kernel
     const MgkSepBasis none{};
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
@@ -2093,6 +2114,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     if (mgk_status st = check_label_dim(ctx, X, Y)) return st;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     MGK_HIP(ctx, hipSetDevice(ctx->device));
+    if (mgk_status st = refuse_capture(ctx, stream)) return st;
     // Either graph of a pair may be the outer operand; jobs whose outer graph
     // comes from Y are launched with the batch arguments exchanged.
     for (int64_t k = 0; k < n_pairs; ++k)

@@ -392,8 +392,8 @@ static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
 }
 // What the separable product reads beside MgkBatchDev.  Packets of a batch come in steps of 64
 // words (four rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64;
-// group t of graph g has steps gptr[qoff[g] + t] .. gptr[qoff[g] + t + 1].  At least one step per
-// batch is allocated.
+// group t of graph g has steps gptr[qoff[g] + t] .. gptr[qoff[g] + t + 1].  One step more than all
+// passes have is allocated: stage 2 loads the first packet of a group before it looks whether it has one.
 struct MgkSepList {
     const int32_t* qoff;        // per graph: first entry in gptr
     const int32_t* gptr;        // per four vertices of a graph, and one more per graph

@@ -1,5 +1,5 @@
-// Device code shared by the kernels that apply the off-diagonal product through a separable
-// edge kernel (mgk_sep.hip, mgk_sepchip.hip).
+// Device code of the kernel that applies the off-diagonal product through a separable edge
+// kernel in its sparse form (mgk_sep.hip).
 //
 // On the labels of a batch the square-exponential (and the constant) edge kernel is a short
 // sum of products, kappa_e(e, e') = sum_k phi_k(e) phi_k(e') to fp32 rounding (the host builds
@@ -129,7 +129,7 @@ __device__ __forceinline__ void packet_each(float (&acc)[RK], float c, const flo
     }
 }
 
-// ---- where stage 1 reads p: rows of n' floats in global memory, or in LDS -----------------
+// ---- where stage 1 reads p: rows of n' floats in global memory --------------------------------
 // row(j): start of row j, wave-uniform; at(row, col4): the element 4-byte offset col4 into it.
 struct PGlobal {
     typedef const char* Row;
@@ -141,15 +141,6 @@ struct PGlobal {
         return r;
     }
     static __device__ __forceinline__ float at(Row r, uint32_t col4) { return *reinterpret_cast<const float*>(r + col4); }
-};
-struct PLds {
-    typedef uint32_t Row;
-    uint32_t base, row_bytes;   // byte offset of p in LDS
-    __device__ __forceinline__ Row row(uint32_t j) const { return base + j * row_bytes; }
-    static __device__ __forceinline__ float at(Row r, uint32_t col4) {
-        extern __shared__ __align__(16) float lds[];
-        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(lds) + (r + col4));
-    }
 };
 
 // One chunk of 64 columns of stage 1: the multiply-adds of NB packets with the values pv.

@@ -1,0 +1,137 @@
+"""Off-diagonal product through a separable edge kernel (global-memory solver): sizes at the edges of
+its tiles and packets, every division of the rank, against the fp64 oracle and the direct product."""
+import dataclasses
+import re
+
+import numpy as np
+import pytest
+
+import mgk_workloads as W
+import paper_1910_06310_amd as M
+from oracle import c_oracle as C
+
+pytestmark = pytest.mark.gpu
+# Values against the oracle: the bound of the kernel values in general.  Two products against each
+# other: both stop at a relative residual of 1e-6, and 2e-5 is what the tile paths are held to.
+RTOL, RTOL_PATHS = 1e-4, 2e-5
+PARAMS = W.KernelParams(q=0.05, h=0.5, length_scale=1.0)
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    return torch
+
+
+@pytest.fixture(scope="module")
+def solver(torch):
+    return M.Solver(0)
+
+
+def er(seed, sizes, density):
+    rng = np.random.default_rng(seed)
+    return W.concat_batches([W.erdos_renyi_batch(rng, 1, n, n, density, (0.1, 1.0), (0.0, 1.0), 4, PARAMS, w_min=1e-3)
+                             for n in sizes], PARAMS, "er")
+
+
+def solve(torch, solver, X, Y, wx, wy, pi, pj, path):
+    """Values and node-wise solutions through the global-memory solver; the kernels that ran."""
+    solver.set_tile_path(path)
+    sx, sy = wx.sizes()[pi], wy.sizes()[pj]
+    off = np.concatenate([[0], np.cumsum(sx * sy)]).astype(np.int64)
+    K = torch.full((len(pi),), float("nan"), dtype=torch.float32, device="cuda")
+    x = torch.full((int(off[-1]),), float("nan"), dtype=torch.float32, device="cuda")
+    fl = torch.full((len(pi),), -1, dtype=torch.int32, device="cuda")
+    solver.pairs_nodal(X, Y, pi, pj, K, x, off[:-1], None, fl)
+    torch.cuda.synchronize()
+    assert (fl.cpu().numpy() == 0).all()
+    return K.cpu().numpy().astype(np.float64), x.cpu().numpy().astype(np.float64), solver.launch_log()
+
+
+def compare(torch, solver, wx, wy, const=False, onchip=0):
+    """All pairs of graphs of two batches: the chosen product against the direct one, node by node."""
+    pi = np.repeat(np.arange(len(wx.sizes())), len(wy.sizes())).astype(np.int32)
+    pj = np.tile(np.arange(len(wy.sizes())), len(wx.sizes())).astype(np.int32)
+    solver.configure(wx.params)
+    if const:
+        solver.set_edge_kernel_const(0.7)
+    solver.set_solver(1e-6, 0)
+    solver.set_onchip_limit(onchip)
+    try:
+        X, Y = solver.load_batch(wx), solver.load_batch(wy)
+        K, x, log = solve(torch, solver, X, Y, wx, wy, pi, pj, M.TILE_AUTO)
+        Kd, xd, direct = solve(torch, solver, X, Y, wx, wy, pi, pj, M.TILE_SPARSE)
+        X.free()
+        Y.free()
+    finally:
+        solver.set_tile_path(M.TILE_AUTO)
+        solver.set_onchip_limit(16384)
+    assert "mgk_sep" in log and "mgk_sep" not in direct
+    np.testing.assert_allclose(K, Kd, rtol=RTOL_PATHS)
+    assert np.linalg.norm(x - xd) <= RTOL_PATHS * np.linalg.norm(xd)
+    return pi, pj, K, log
+
+
+@pytest.mark.parametrize("length_scale", [20.0, 4.0, 1.7, 1.0, 0.7, 0.5, 0.33, 0.22, None])
+def test_every_division_of_the_rank(torch, solver, length_scale):
+    """Short length scales take more features, in passes of 4 to 7; the constant kernel takes one."""
+    wb = er(1, (33, 47, 64), 0.25)
+    wb.params = dataclasses.replace(PARAMS, length_scale=length_scale or 1.0)
+    *_, log = compare(torch, solver, wb, wb, const=length_scale is None)
+    ranks = {int(r) for r in re.findall(r"rank=(\d+)", log)}
+    assert len(ranks) == 1
+    assert ranks == {1} if length_scale is None else min(ranks) >= 2
+
+
+@pytest.mark.parametrize("density", [0.06, 0.3, 1.0])
+@pytest.mark.parametrize("sizes", [(15, 16, 17), (31, 33, 63), (64, 65, 127), (129, 130)])
+def test_edges_of_tiles_against_the_oracle(torch, solver, sizes, density):
+    """Sparse (rows in 16s, columns in 4s and 64s) and dense (32 rows, 64 columns) form; the batch also
+    has a vertex without edges at its very end, whose packets do not exist."""
+    wb = er(sum(sizes), sizes, density)
+    lone = W.erdos_renyi_batch(np.random.default_rng(3), 1, 21, 21, 0.5, (0.5, 1.0), (0.0, 1.0), 4, PARAMS)
+    keep = (lone.src < 16) & (lone.dst < 16)   # five vertices without edges: a whole group of four
+    lone.src, lone.dst, lone.weight, lone.edge_label = (a[keep] for a in (lone.src, lone.dst, lone.weight, lone.edge_label))
+    lone.edge_off = np.array([0, int(keep.sum())], lone.edge_off.dtype)
+    wb = W.concat_batches([wb, lone], PARAMS, "edges")
+    pi, pj, K, log = compare(torch, solver, wb, wb)
+    once = (pi <= pj) & (wb.nnz()[pi] * wb.nnz()[pj] < 2e7)   # the oracle evaluates every pair of nonzeros
+    np.testing.assert_allclose(K[once], C.pairs(wb, pi[once], pj[once], tier=1), rtol=RTOL)
+    if density == 1.0 and max(sizes) >= 64:
+        assert "mgk_sep_dense_kernel" in log
+
+
+def test_two_batches_of_unlike_sizes_and_label_ranges(torch, solver):
+    """Graphs of two batches, the larger one on either side, labels of one outside the other's range."""
+    wx, wy = er(5, (20, 90, 40), 0.2), er(6, (70, 33), 0.4)
+    wy.edge_label = (wy.edge_label + 0.8).astype(np.float32)
+    compare(torch, solver, wx, wy)
+    compare(torch, solver, wy, wx)
+
+
+def test_calls_with_lists_of_their_own_are_refused_while_a_graph_is_recorded(torch, solver):
+    """Their lists are copied from memory that later calls write again, so a replay could not be right."""
+    wb = er(7, (10, 12), 0.4)
+    solver.configure(PARAMS)
+    solver.set_solver(1e-6, 0)
+    B = solver.load_batch(wb)
+    pi, pj = np.array([0, 1], np.int32), np.array([1, 1], np.int32)
+    K = torch.zeros(2, dtype=torch.float32, device="cuda")
+    solver.pairs(B, B, pi, pj, K)
+    torch.cuda.synchronize()
+    before = K.cpu().numpy().copy()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        graph.capture_begin()
+        try:
+            for call in (solver.pairs, solver.pairs_noalloc):
+                with pytest.raises(M.MgkError, match="captur"):
+                    call(B, B, pi, pj, K)
+            K.add_(0.0)
+        finally:
+            graph.capture_end()
+    K.zero_()
+    solver.pairs(B, B, pi, pj, K)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(K.cpu().numpy(), before)
+    B.free()
