@@ -863,27 +863,59 @@ MgkSepLayout sep_layout(int rank, int n2) {
 }
 
 // Product of the global-memory solver for one pair.
-enum LargePath { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
+enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
 
-// Estimated clocks per compute unit of one product, from measured rates: the row-staged product
-// evaluates about 7.5 entries per clk, the sparse separable product does about 30 multiply-adds per
-// clk and the dense one 100 (of the 128 the matrix cores can do).
-LargePath large_path(const mgk_ctx* ctx, const MgkSepBasis& S, bool dense_fits, const MgkGraphDesc& o, const MgkGraphDesc& i) {
-    const LargePath direct = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
-    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) return direct;
-    double best = (double)o.nnz * i.nnz / 7.5;
-    LargePath path = direct;
+// Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
+// run.  Fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01 to 1, ranks 1
+// to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages the rows of
+// p and pays 6 clk per element in dependent loads; the sparse separable product does 20 multiply-adds
+// per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
+// from 256 columns on.  Measured, us per call of 64 pairs, row-staged / sparse / dense: n = 256 density
+// 0.01 2205 / 2162 / 9989 (rank 8: 1990 / 2288 / 13732), 0.02 1905 / 1509 / 6065, 0.2 13896 / 1657 / 2979,
+// 0.45 52148 / 2865 / 3065; n = 128 density 0.014 1224 / 1210 / 4751, 0.03 980 / 817 / 2824.
+struct LargeCost {
+    double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
+    int best = kPathSparse;
+};
+LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, bool dense_fits, const MgkGraphDesc& o, const MgkGraphDesc& i) {
+    LargeCost C;
+    C.best = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
+    const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
+    C.clk[C.best] = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n + 6.0 * N;
+    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) return C;
     const MgkSepLayout L = sep_layout(S.rank, i.n);
-    if (L.rk > 0) {
-        const double c = (double)L.rk * L.passes * ((double)o.nnz * i.n + (double)o.n * i.nnz) / 30.0;
-        if (c < best) { best = c; path = kPathSep; }
+    if (L.rk > 0) C.clk[kPathSep] = (double)L.rk * L.passes * one_sided / 20.0 + 8.0 * N;
+    const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255;
+    if (dense_fits && ip <= MGK_SEP_DENSE_MAX_N) C.clk[kPathSepDense] = S.rank * op * ip * ((double)o.n + i.n) / 42.0;
+    for (int path : {kPathSep, kPathSepDense})
+        if (C.clk[path] < C.clk[C.best]) C.best = path;
+    return C;
+}
+
+// Every path in use is a sequence of launches of its own with a wait at its end: 300 us for a path of
+// half of 64 pairs of 256-vertex graphs at density 0.01, whose products take the same time either way,
+// or 1e7 clk per iteration.  A path that saves less than that goes to the next best one in use.
+void merge_paths(std::vector<LargeCost>& costs) {
+    constexpr double kPathClk = 1e7;
+    while (true) {
+        double move[kPaths][kPaths] = {};
+        bool used[kPaths] = {};
+        for (const LargeCost& C : costs) {
+            used[C.best] = true;
+            for (int to = 0; to < kPaths; ++to)
+                if (to != C.best) move[C.best][to] += C.clk[to] - C.clk[C.best];
+        }
+        int from = -1, into = -1;
+        for (int a = 0; a < kPaths; ++a)
+            for (int b = 0; b < kPaths; ++b)
+                if (a != b && used[a] && used[b] && move[a][b] < kPathClk && (from < 0 || move[a][b] < move[from][into])) {
+                    from = a;
+                    into = b;
+                }
+        if (from < 0) return;
+        for (LargeCost& C : costs)
+            if (C.best == from) C.best = into;
     }
-    const double op = (o.n + 31) & ~31, ip = (i.n + 63) & ~63;
-    if (dense_fits && ip <= MGK_SEP_DENSE_MAX_N) {
-        const double c = S.rank * (op * ip * o.n + op * ip * i.n) / 100.0;
-        if (c < best) { best = c; path = kPathSepDense; }
-    }
-    return path;
 }
 
 // Plan of one pair for the global-memory solver (any size).
@@ -1253,21 +1285,32 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     const MgkSepBasis& S = may_sep ? sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi)) : none;
     constexpr int64_t kMaxDenseBytes = (int64_t)8 << 30;   // both batches' dense F_k
     const bool dense_fits = (X->dense_floats + (X == Y ? 0 : Y->dense_floats)) * S.rank * 4 <= kMaxDenseBytes;
-    std::vector<MgkLargePair> lists[2][kPaths];
+    struct Oriented { MgkLargePair pair; int swapped; };
+    std::vector<Oriented> sep_form;   // the pair as the separable product takes it
+    std::vector<LargeCost> costs;
+    sep_form.reserve(jl.large[0].size() + jl.large[1].size());
+    costs.reserve(sep_form.capacity());
     for (int swapped = 0; swapped < 2; ++swapped)
         for (const MgkLargePair& asked : jl.large[swapped]) {
-            MgkLargePair P = asked;
-            int sw = swapped;
+            Oriented f{asked, swapped};
+            MgkLargePair& P = f.pair;
             if (S.rank > 0 && P.n2 > P.n1) {   // separable product: T has a column per inner vertex
                 std::swap(P.g1, P.g2);
                 std::swap(P.n1, P.n2);
                 if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
-                if (X != Y) sw = 1 - sw;
+                if (X != Y) f.swapped = 1 - swapped;
             }
-            const mgk_batch* A = sw ? Y : X;
-            const mgk_batch* B = sw ? X : Y;
-            const LargePath path = large_path(ctx, S, dense_fits, A->graphs[P.g1], B->graphs[P.g2]);
-            if (path == kPathSep || path == kPathSepDense) lists[sw][path].push_back(P);
+            costs.push_back(large_cost(ctx, S, dense_fits, (f.swapped ? Y : X)->graphs[P.g1], (f.swapped ? X : Y)->graphs[P.g2]));
+            sep_form.push_back(f);
+        }
+    merge_paths(costs);
+    std::vector<MgkLargePair> lists[2][kPaths];
+    size_t at = 0;
+    for (int swapped = 0; swapped < 2; ++swapped)
+        for (const MgkLargePair& asked : jl.large[swapped]) {
+            const int path = costs[at].best;
+            const Oriented& f = sep_form[at++];
+            if (path == kPathSep || path == kPathSepDense) lists[f.swapped][path].push_back(f.pair);
             else lists[swapped][path].push_back(asked);
         }
     // In groups: the pair index is a grid dimension (at most 65535) and every pair of a group
