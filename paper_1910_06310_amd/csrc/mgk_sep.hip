@@ -118,7 +118,10 @@ __device__ __forceinline__ void clear_sums(MgkPairState& st, int it) {
 }
 
 // Bound by the vector ALUs and the LDS about equally: per nonzero and 64 results RK
-// multiply-adds (1.15 RK clk per CU) against 4 RK bytes x 64 from LDS in stage 2.
+// multiply-adds (1.15 RK clk per CU) against 4 RK bytes x 64 from LDS in stage 2.  Measured about 20
+// multiply-adds per clk and CU.  64 pairs of 256-vertex graphs of density 0.2: 13.5 ms with one
+// evaluation per pair of nonzeros, 1.31 ms with this.  16 rows per workgroup so that T of one pass
+// (RK <= 7) fits in LDS up to 276 columns and the coefficients of a column serve a whole row of 16 lanes.
 template <int RK, int G>
 __global__ __launch_bounds__(1024) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY,
                                                            MgkSepLayout L, const MgkLargePair* pairs,
@@ -215,7 +218,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // wavefront.  Per k: T_k[32 x n'] = F_k P on the matrix cores, to LDS; y += T_k F'_k^T.  F_k and F'_k
 // are symmetric, so every operand is read along rows (32 lanes = 128 adjacent bytes).
 // Sums are kept in levels of 64 terms to bound the fp32 rounding bias of long running sums.
-// Bound by the matrix cores: 128 multiply-adds per clk and CU in fp32.
+// Bound by the matrix cores (128 multiply-adds per clk and CU in fp32) and, with two wavefronts per
+// SIMD, by the latency of the operand loads: about 51 per clk measured on 64 pairs of complete
+// 256-vertex graphs, 132 ms per call with the tile-pair kernel, 1.68 ms with this.
 template <int NT>
 __global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
                                                             MgkSepList SY, int rank, const MgkLargePair* pairs,
