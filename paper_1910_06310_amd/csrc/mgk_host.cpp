@@ -19,6 +19,8 @@
 #include <thread>
 #include <vector>
 
+#include <unistd.h>
+
 #include "../../include/mgk.h"
 #include "mgk_internal.h"
 #include "mgk_launch.h"
@@ -77,69 +79,82 @@ struct FreeBlob {
 
 // Threads of a context for the host work of a call.  run(n, f, helpers) calls f(0) .. f(n - 1), on
 // the calling thread and on at most `helpers` (and kMaxWorkers) others, and returns when all have
-// returned; f must not throw.  The threads sleep in between and end with the pool.
+// returned; f must not throw.  The threads sleep in between and end with the pool.  They do not
+// exist in a forked child, where waiting for them would never end: it starts its own, and what
+// the parent's left is abandoned there.
 class WorkerPool {
 public:
     ~WorkerPool() {
-        {
-            std::lock_guard<std::mutex> lock(m_);
-            stop_ = true;
-        }
-        wake_.notify_all();
-        for (std::thread& t : threads_) t.join();
+        if (!crew_ || crew_->process != getpid()) return;
+        crew_->end();
+        delete crew_;
     }
     void run(int n, const std::function<void(int)>& f, int helpers = kMaxWorkers) {
         const int want = std::min({n - 1, helpers, kMaxWorkers, (int)std::thread::hardware_concurrency() - 1});
         if (want > 0) {
             try {
-                while ((int)threads_.size() < want) threads_.emplace_back([this] { work(); });
+                if (!crew_ || crew_->process != getpid()) crew_ = new Crew;
+                while ((int)crew_->threads.size() < want) crew_->threads.emplace_back([c = crew_] { c->work(); });
             } catch (...) {   // fewer threads, then
             }
         }
-        if (want <= 0 || threads_.empty()) {
+        if (want <= 0 || !crew_ || crew_->process != getpid() || crew_->threads.empty()) {
             for (int i = 0; i < n; ++i) f(i);
             return;
         }
-        {
-            std::lock_guard<std::mutex> lock(m_);
-            f_ = &f;
-            n_ = n;
-            taken_ = 0;
-            left_ = n;
-        }
-        for (int k = 0; k < want; ++k) wake_.notify_one();
-        std::unique_lock<std::mutex> lock(m_);
-        take(lock);
-        done_.wait(lock, [this] { return left_ == 0; });
-        f_ = nullptr;
+        crew_->run(n, f, want);
     }
 
 private:
     static constexpr int kMaxWorkers = 15;
-    void take(std::unique_lock<std::mutex>& lock) {   // tasks until none is left to take
-        while (f_ && taken_ < n_) {
-            const int i = taken_++;
-            const std::function<void(int)>* f = f_;
+    struct Crew {
+        const pid_t process = getpid();
+        std::mutex m;
+        std::condition_variable wake, done;
+        std::vector<std::thread> threads;
+        const std::function<void(int)>* f = nullptr;
+        int n = 0, taken = 0, left = 0;
+        bool stop = false;
+        void run(int count, const std::function<void(int)>& task, int want) {
+            std::unique_lock<std::mutex> lock(m);
+            f = &task;
+            n = left = count;
+            taken = 0;
             lock.unlock();
-            (*f)(i);
+            for (int k = 0; k < want; ++k) wake.notify_one();
             lock.lock();
-            if (--left_ == 0) done_.notify_one();
-        }
-    }
-    void work() {
-        std::unique_lock<std::mutex> lock(m_);
-        while (true) {
-            wake_.wait(lock, [this] { return stop_ || (f_ && taken_ < n_); });
-            if (stop_) return;
             take(lock);
+            done.wait(lock, [this] { return left == 0; });
+            f = nullptr;
         }
-    }
-    std::mutex m_;
-    std::condition_variable wake_, done_;
-    std::vector<std::thread> threads_;
-    const std::function<void(int)>* f_ = nullptr;
-    int n_ = 0, taken_ = 0, left_ = 0;
-    bool stop_ = false;
+        void take(std::unique_lock<std::mutex>& lock) {   // tasks until none is left to take
+            while (f && taken < n) {
+                const int i = taken++;
+                const std::function<void(int)>* task = f;
+                lock.unlock();
+                (*task)(i);
+                lock.lock();
+                if (--left == 0) done.notify_one();
+            }
+        }
+        void work() {
+            std::unique_lock<std::mutex> lock(m);
+            while (true) {
+                wake.wait(lock, [this] { return stop || (f && taken < n); });
+                if (stop) return;
+                take(lock);
+            }
+        }
+        void end() {
+            {
+                std::lock_guard<std::mutex> lock(m);
+                stop = true;
+            }
+            wake.notify_all();
+            for (std::thread& t : threads) t.join();
+        }
+    };
+    Crew* crew_ = nullptr;
 };
 
 }  // namespace

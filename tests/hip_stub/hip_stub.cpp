@@ -1,0 +1,257 @@
+// The HIP runtime and the kernel launchers, as far as mgk_host.cpp uses them, on the CPU: device
+// memory is host memory, kernels only leave a line in a log.  Built together with mgk_host.cpp and
+// mgk_reorder.cpp by tests/host_runtime.py, so that the host path of a solve (streams, recording,
+// lifetimes, memory that runs out, how pairs are grouped) can be tested without a GPU.
+//
+// Work on a stream ends at once, unless the test holds the stream: then it ends when something waits
+// for it.  A test can also set a limit on device memory, and mark streams as recording.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdarg>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <set>
+#include <string>
+#include <vector>
+
+#include "../../paper_1910_06310_amd/csrc/mgk_launch.h"
+
+namespace {
+
+struct Event { void* stream; bool done; };
+
+std::map<char*, size_t> device_memory;              // block -> bytes
+size_t in_use = 0, limit = SIZE_MAX, pinned_bytes = 0;
+std::set<void*> held, recording;                    // streams
+int unreachable = 0;                                // work of streams that are gone
+std::map<void*, std::set<char*>> readers;           // held stream -> blocks its work reads
+std::set<char*> unreachable_reads;
+std::set<Event*> events;
+std::string log_text;
+std::vector<std::string> violations;
+std::map<std::string, int> counts;
+int device = 0;
+int converge_after = 3;
+
+void say(const char* fmt, ...) {
+    char buf[256];
+    va_list ap;
+    va_start(ap, fmt);
+    vsnprintf(buf, sizeof buf, fmt, ap);
+    va_end(ap);
+    log_text += buf;
+    log_text += '\n';
+}
+
+char* block_of(const void* p) {
+    auto it = device_memory.upper_bound((char*)p);
+    if (it == device_memory.begin()) return nullptr;
+    --it;
+    return (char*)p < it->first + it->second ? it->first : nullptr;
+}
+
+void finish(void* stream) {
+    held.erase(stream);
+    readers.erase(stream);
+    for (Event* e : events)
+        if (e->stream == stream) e->done = true;
+}
+
+void finish_all() {
+    while (!held.empty()) finish(*held.begin());
+    unreachable = 0;
+    unreachable_reads.clear();
+}
+
+void reads(void* stream, const void* p) {
+    if (char* b = block_of(p))
+        if (held.count(stream)) readers[stream].insert(b);
+}
+
+void check_write(const void* p) {   // a block that unfinished work reads must not be written or freed
+    char* b = block_of(p);
+    if (!b) { violations.push_back("write outside device memory"); return; }
+    for (auto& r : readers)
+        if (r.second.count(b)) violations.push_back("write to a block that work under way reads");
+    if (unreachable_reads.count(b)) violations.push_back("write to a block that work under way reads");
+}
+
+hipError_t launched(const char* name, void* stream, const MgkBatchDev* X = nullptr, const MgkBatchDev* Y = nullptr, int pairs = 0) {
+    say("%s pairs=%d%s", name, pairs, recording.count(stream) ? " recorded" : "");
+    if (X) reads(stream, X->graphs);
+    if (Y) reads(stream, Y->graphs);
+    return hipSuccess;
+}
+
+}  // namespace
+
+extern "C" {
+
+// ---- for the tests
+void stub_reset() {
+    finish_all();
+    recording.clear();
+    log_text.clear();
+    violations.clear();
+    counts.clear();
+    limit = SIZE_MAX;
+    converge_after = 3;
+}
+const char* stub_log() { return log_text.c_str(); }
+int stub_count(const char* what) { return counts[what]; }
+const char* stub_violations() {
+    static std::string all;
+    all.clear();
+    for (const std::string& v : violations) all += v + "\n";
+    return all.c_str();
+}
+void stub_hold(void* stream) { held.insert(stream); }
+void stub_record(void* stream, int on) { if (on) recording.insert(stream); else recording.erase(stream); }
+// The stream is destroyed with work under way and its handle given to a new one.
+void stub_replace_stream(void* stream) {
+    if (!held.count(stream)) return;
+    unreachable++;
+    unreachable_reads.insert(readers[stream].begin(), readers[stream].end());
+    readers.erase(stream);
+    held.erase(stream);
+}
+void stub_set_limit(int64_t bytes) { limit = bytes < 0 ? SIZE_MAX : (size_t)bytes; }
+int64_t stub_in_use() { return (int64_t)in_use; }
+int64_t stub_pinned() { return (int64_t)pinned_bytes; }
+void stub_converge_after(int iterations) { converge_after = iterations; }
+void stub_set_device(int d) { device = d; }
+int stub_device() { return device; }
+
+// ---- the runtime
+hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
+hipError_t hipSetDevice(int d) { device = d; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "stub error"; }
+hipError_t hipMalloc(void** p, size_t bytes) {
+    counts["malloc"]++;
+    if (bytes > limit || in_use + bytes > limit) return hipErrorOutOfMemory;
+    *p = malloc(bytes ? bytes : 1);
+    device_memory[(char*)*p] = bytes;
+    in_use += bytes;
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+hipError_t hipFree(void* p) {
+    finish_all();   // waits for the device
+    counts["free"]++;
+    auto it = device_memory.find((char*)p);
+    if (it == device_memory.end()) { violations.push_back("free of unknown memory"); return hipErrorInvalidValue; }
+    in_use -= it->second;
+    device_memory.erase(it);
+    free(p);
+    return hipSuccess;
+}
+static std::map<void*, size_t> pinned;
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
+    *p = malloc(bytes);
+    pinned[*p] = bytes;
+    pinned_bytes += bytes;
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) { pinned_bytes -= pinned[p]; pinned.erase(p); free(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) {
+    if (k == hipMemcpyHostToDevice) check_write(d);
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
+    if (recording.count(st)) counts["recorded copies"]++;
+    if (k == hipMemcpyHostToDevice) check_write(d);
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { check_write(d); memset(d, v, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    counts["stream waits"]++;
+    if (recording.count(s)) { counts["broken recordings"]++; return hipErrorStreamCaptureUnsupported; }
+    finish(s);
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { counts["device waits"]++; finish_all(); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+    *st = recording.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    Event* ev = new Event{nullptr, true};
+    events.insert(ev);
+    *e = (hipEvent_t)ev;
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) { events.erase((Event*)e); delete (Event*)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    ((Event*)e)->stream = s;
+    ((Event*)e)->done = held.count(s) == 0;
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) { return ((Event*)e)->done ? hipSuccess : hipErrorNotReady; }
+hipError_t hipEventSynchronize(hipEvent_t e) { if (!((Event*)e)->done) finish(((Event*)e)->stream); return hipSuccess; }
+
+}  // extern "C"
+
+// ---- the launchers
+#define STUB_SMALL(NAME)                                                                                          \
+    hipError_t NAME(int, bool, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n, const MgkParams&, \
+                    size_t, const MgkOutputs&, hipStream_t s) { return launched("small", s, &X, &Y, n); }
+STUB_SMALL(mgk_launch_small_w1) STUB_SMALL(mgk_launch_small_w2) STUB_SMALL(mgk_launch_small_w4)
+STUB_SMALL(mgk_launch_small_w8) STUB_SMALL(mgk_launch_small_w16) STUB_SMALL(mgk_launch_small_w4_fine)
+#define STUB_REGS(W, C)                                                                                           \
+    hipError_t mgk_launch_regs_w##W##_c##C(int, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n, \
+                                           const MgkParams&, size_t, const MgkOutputs&, hipStream_t s) { return launched("regs", s, &X, &Y, n); }
+STUB_REGS(4, 1) STUB_REGS(4, 2) STUB_REGS(8, 1) STUB_REGS(8, 2)
+#define STUB_SELL(W)                                                                                              \
+    hipError_t mgk_launch_sell_w##W(int, int, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n,    \
+                                    const MgkParams&, size_t, const MgkOutputs&, hipStream_t s) { return launched("sell", s, &X, &Y, n); }
+STUB_SELL(4) STUB_SELL(8) STUB_SELL(16)
+hipError_t mgk_noalloc_job_storage(int, MgkJob** jobs, int64_t* capacity) {
+    static MgkJob* storage = nullptr;
+    if (!storage) {
+        storage = (MgkJob*)malloc(MGK_NOALLOC_MAX_PAIRS * sizeof(MgkJob));
+        device_memory[(char*)storage] = MGK_NOALLOC_MAX_PAIRS * sizeof(MgkJob);
+    }
+    *jobs = storage;
+    *capacity = MGK_NOALLOC_MAX_PAIRS;
+    return hipSuccess;
+}
+hipError_t mgk_launch_expand(const MgkBatchDev& B, const MgkParams&, MgkEntry*, MgkEntry*, hipStream_t s) { return launched("expand", s, &B); }
+hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams&, float*, float*, float*, hipStream_t s) { return launched("expand_dense", s, &B); }
+hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair*, MgkPairState*, float*,
+                                 const MgkParams&, int n, int, hipStream_t s) { return launched("init", s, &X, &Y, n); }
+hipError_t mgk_launch_large_iteration(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkExpanded&, const MgkExpanded&,
+                                      const MgkLargePair*, MgkPairState*, float*, const MgkParams&, bool, int n, int, int,
+                                      int* n_active, int it, const MgkDenseTiles* D, const MgkDenseTiles*, int rows, int, int, hipStream_t s) {
+    if (it + 1 >= converge_after) { n_active[0] = 0; n_active[1] = it + 1; }
+    return launched(D ? "direct dense" : rows > 0 ? "direct rows" : "direct gather", s, &X, &Y, n);
+}
+hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkExpanded&, const MgkExpanded&,
+                                  const MgkLargePair*, MgkPairState*, float*, const MgkParams&, bool, int n, int, int,
+                                  const MgkDenseTiles*, const MgkDenseTiles*, int, int, int, const MgkOutputs&, hipStream_t s) { return launched("final", s, &X, &Y, n); }
+hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis&, const MgkSepLayout&, const MgkSepList&, int, float*, hipStream_t s) { return launched("sep pack", s, &B, nullptr, B.n_graphs); }
+hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis&, const MgkSepList&, int, float*, hipStream_t s) { return launched("sep dense pack", s, &B, nullptr, B.n_graphs); }
+hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&,
+                              const MgkSepLayout&, const MgkLargePair*, MgkPairState*, float*, const MgkParams&, int n, int max_n1,
+                              int, int, bool, hipStream_t s) {
+    if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 15) / 16) * 1024 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
+    return launched("sep", s, &X, &Y, n);
+}
+hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&, int,
+                                const MgkLargePair*, MgkPairState*, float*, const MgkParams&, int n, int max_n1, int, int, bool, hipStream_t s) {
+    if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 31) / 32) * 256 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
+    return launched("sep dense", s, &X, &Y, n);
+}
+hipError_t mgk_launch_large_vectors(const MgkLargePair*, MgkPairState*, float*, int n, int, int it, float, int* n_active, hipStream_t s) {
+    if (it + 1 >= converge_after) { n_active[0] = 0; n_active[1] = it + 1; }
+    return launched("vectors", s, nullptr, nullptr, n);
+}
+hipError_t mgk_launch_large_outputs(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair*, MgkPairState*, float*,
+                                    const MgkParams&, int n, int, const MgkOutputs&, int, hipStream_t s) { return launched("outputs", s, &X, &Y, n); }
+hipError_t mgk_launch_normalize(float*, float*, int, hipStream_t s) { return launched("normalize", s); }
