@@ -1329,11 +1329,17 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             else lists[swapped][path].push_back(asked);
         }
     // In groups: the pair index is a grid dimension (at most 65535) and every pair of a group
-    // holds 5 vectors of scratch at the same time.
+    // holds 5 vectors of scratch at the same time.  The separable products put pairs and blocks of
+    // outer rows into one dimension, as many blocks for every pair as the largest one has.
     constexpr size_t kMaxPairsPerGroup = 4096;
     constexpr int64_t kMaxScratchFloats = (int64_t)1 << 31;   // 8 GiB
+    constexpr int64_t kMaxGridThreads = (int64_t)1 << 32;     // of a grid dimension, exclusive
     for (int path = 0; path < kPaths; ++path)
         for (int swapped = 0; swapped < 2; ++swapped) {
+            auto grid_threads = [&](int64_t n_pairs, int max_n1) {
+                return path == kPathSep ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS) * MGK_SEP_THREADS
+                     : path == kPathSepDense ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS) * MGK_SEP_DENSE_THREADS : 0;
+            };
             std::vector<MgkLargePair>& all = lists[swapped][path];
             const mgk_batch* A = swapped ? Y : X;
             const mgk_batch* B = swapped ? X : Y;
@@ -1341,10 +1347,12 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             while (first < all.size()) {
                 size_t last = first;
                 int64_t floats = 0;
-                int max_n2 = 1;
+                int max_n1 = 1, max_n2 = 1;
                 while (last < all.size() && last - first < kMaxPairsPerGroup &&
-                       (last == first || floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats)) {
+                       (last == first || (floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats &&
+                                          grid_threads((int64_t)(last - first) + 1, std::max(max_n1, all[last].n1)) < kMaxGridThreads))) {
                     floats += 5 * (int64_t)all[last].npad;
+                    max_n1 = std::max(max_n1, all[last].n1);
                     max_n2 = std::max(max_n2, all[last].n2);
                     ++last;
                 }

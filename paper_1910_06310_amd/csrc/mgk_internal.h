@@ -384,11 +384,18 @@ struct MgkSepLayout {
     int32_t rk, passes, per_packet, slab_bytes;
 };
 #define MGK_SEP_ROWS 16       // outer rows per workgroup: one row of 16 lanes
+#define MGK_SEP_THREADS 1024
+#define MGK_SEP_DENSE_ROWS 32 // the same of the dense form: one tile
+#define MGK_SEP_DENSE_THREADS 256
 #define MGK_SEP_SLAB(rk) ((rk) == 1 ? 17 : 64 * (((rk) + 3) / 4) + 4)   // words per column of T
 #define MGK_SEP_DENSE_MAX_N 1024
 static inline MGK_HD int32_t mgk_sep_per_packet(int32_t rk) { return rk == 1 ? 8 : 2; }
 static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
     return 4 * ((int64_t)MGK_SEP_SLAB(rk) * n2 + (int64_t)MGK_SEP_ROWS * (n2 | 1));
+}
+// Workgroups of a launch: pairs in eights (one per XCD) by blocks of rows of the largest outer graph.
+static inline MGK_HD int64_t mgk_sep_grid(int64_t n_pairs, int32_t max_n1, int32_t rows) {
+    return (n_pairs + 7) / 8 * 8 * ((max_n1 + rows - 1) / rows);
 }
 // What the separable product reads beside MgkBatchDev.  Packets of a batch come in steps of 64
 // words (four rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64;

@@ -123,7 +123,7 @@ __device__ __forceinline__ void clear_sums(MgkPairState& st, int it) {
 // evaluation per pair of nonzeros, 1.31 ms with this.  16 rows per workgroup so that T of one pass
 // (RK <= 7) fits in LDS up to 276 columns and the coefficients of a column serve a whole row of 16 lanes.
 template <int RK, int G>
-__global__ __launch_bounds__(1024) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY,
+__global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY,
                                                            MgkSepLayout L, const MgkLargePair* pairs,
                                                            MgkPairState* state, float* vec, MgkParams prm,
                                                            int n_pairs, int blocks, int it, int check_only) {
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(1024) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBat
     if (i0 >= P.n1) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int NW = 16;
+    constexpr int NW = MGK_SEP_THREADS / 64;
     if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
     const int n1 = P.n1, n2 = P.n2, rows = min(MGK_SEP_ROWS, n1 - i0);
@@ -222,7 +222,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // SIMD, by the latency of the operand loads: about 51 per clk measured on 64 pairs of complete
 // 256-vertex graphs, 132 ms per call with the tile-pair kernel, 1.68 ms with this.
 template <int NT>
-__global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
+__global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
                                                             MgkSepList SY, int rank, const MgkLargePair* pairs,
                                                             MgkPairState* state, float* vec, MgkParams prm,
                                                             int n_pairs, int blocks, int it, int check_only) {
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(256) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBa
     MgkPairState& st = state[pair];
     if (check_only ? !st.check : st.done) return;
     const MgkLargePair P = pairs[pair];
-    const int i0 = blk * 32;
+    const int i0 = blk * MGK_SEP_DENSE_ROWS;
     if (i0 >= P.n1) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -399,7 +399,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
                               const MgkSepLayout& L, const MgkLargePair* pairs, MgkPairState* state, float* vec,
                               const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
     const int blocks = (max_n1 + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
-    const dim3 grid((unsigned)(((n_pairs + 7) / 8) * 8 * blocks));
+    const dim3 grid((unsigned)mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS));
     const size_t bytes = mgk_sep_lds_bytes(L.rk, max_n2);
     if (bytes > MGK_LDS_LIMIT_BYTES) return hipErrorInvalidValue;
 #define MGK_SEP_GO(RK, G) \
@@ -408,7 +408,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
         static bool configured = false; \
         hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
         if (e != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, grid, dim3(1024), bytes, stream, X, Y, SX, SY, L, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_THREADS), bytes, stream, X, Y, SX, SY, L, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
         break; \
     }
     switch (L.rk) {
@@ -422,8 +422,8 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
                                 const MgkLargePair* pairs, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
-    const int blocks = (max_n1 + 31) / 32;
-    const dim3 grid((unsigned)(((n_pairs + 7) / 8) * 8 * blocks));
+    const int blocks = (max_n1 + MGK_SEP_DENSE_ROWS - 1) / MGK_SEP_DENSE_ROWS;
+    const dim3 grid((unsigned)mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS));
     const int np2 = (max_n2 + 63) & ~63;
     const size_t bytes = (size_t)32 * (np2 + 1) * sizeof(float);
     if (np2 > MGK_SEP_DENSE_MAX_N) return hipErrorInvalidValue;
@@ -433,7 +433,7 @@ hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, cons
         static bool configured = false; \
         hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
         if (e != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, grid, dim3(256), bytes, stream, X, Y, SX, SY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_DENSE_THREADS), bytes, stream, X, Y, SX, SY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
     }
     if (np2 <= 256) MGK_SEP_DENSE_GO(1)
     else if (np2 <= 512) MGK_SEP_DENSE_GO(2)

@@ -1,8 +1,10 @@
 """Host path of a solve without a GPU: the library's host code on a stand-in for the HIP runtime."""
 import os
+import re
 import shutil
 import signal
 import time
+import types
 
 import numpy as np
 import pytest
@@ -60,3 +62,40 @@ def test_context_survives_a_fork(so):
     assert in_child(child) == 0
     h.free(h.load(wb, reorder=1))
     h.destroy()
+
+
+def graphs(*parts):
+    """A workload of (n, edges, labels) graphs with unit weights."""
+    off = lambda sizes: np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    edges = [np.asarray(e, np.int32).reshape(-1, 2) for _, e, _ in parts]
+    src, dst = np.concatenate(edges).T
+    return types.SimpleNamespace(
+        vtx_off=off([n for n, _, _ in parts]), vtx_label=np.zeros(sum(n for n, _, _ in parts), np.int32),
+        edge_off=off([len(e) for e in edges]), src=src, dst=dst, weight=np.ones(len(src), np.float32),
+        edge_label=np.concatenate([np.broadcast_to(np.asarray(x, np.float32), len(e)) for (_, _, x), e in zip(parts, edges)]))
+
+
+def path(n, label=0.0):
+    return n, np.stack([np.arange(n - 1), np.arange(1, n)], 1), label
+
+
+def ring(n, k, label=0.0):
+    """Every vertex joined to the k next ones."""
+    i = np.repeat(np.arange(n), k)
+    return n, np.stack([i, (i + 1 + np.tile(np.arange(k), n)) % n], 1), label
+
+
+def launched(log, kernel):
+    """Pairs of every launch of a kernel."""
+    return [int(k) for k in re.findall("^%s pairs=(\\d+)" % kernel, log, re.M)]
+
+
+def test_workgroups_of_a_separable_launch_stay_within_the_grid(host):
+    """Pairs and blocks of rows share a grid dimension of less than 2^32 threads: many pairs beside one
+    with very many rows go in several launches (the stand-in refuses a larger one, as the runtime does)."""
+    B = host.load(graphs(path(16400), ring(150, 6)))
+    i = np.ones(4096, np.int32)
+    i[0] = 0
+    assert host.pairs(B, B, i, np.ones(4096, np.int32)) == 0, host.error()
+    assert sum(launched(host.log(), "init")) == 4096 and max(launched(host.log(), "sep")) > 2000
+    host.free(B)
