@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <numeric>
@@ -75,6 +76,13 @@ struct FreeBlob {
     void* p = nullptr;
     size_t cap = 0;
     std::vector<hipEvent_t> readers;
+};
+// Shared by a context and its batches: a batch may be freed after its context, and by another thread
+// than the one that uses the context.
+struct BatchMemory {
+    std::mutex m;
+    std::vector<FreeBlob> blobs;
+    bool open = true;   // until the context is destroyed
 };
 
 // Threads of a context for the host work of a call.  run(n, f, helpers) calls f(0) .. f(n - 1), on
@@ -161,6 +169,7 @@ private:
 
 struct mgk_batch {
     mgk_ctx* owner = nullptr;
+    std::shared_ptr<BatchMemory> memory;
     int32_t n_graphs = 0;
     int64_t n_vertices = 0, nnz = 0, n_tiles = 0, n_offdiag = 0;
     bool weighted = false;
@@ -179,6 +188,7 @@ struct mgk_batch {
     MgkSepList sep[2] = {};               // the batch's part of it for the two packet sizes
     int64_t dense_floats = 0;             // sum of (n rounded up to 64)^2
     // device
+    int device = 0;
     void* blob = nullptr;
     size_t blob_cap = 0;
     std::vector<hipStream_t> used_on;   // streams with calls that read the batch
@@ -226,7 +236,7 @@ struct mgk_ctx {
     DevBuf vec, lpairs, lstate, lactive, nodal_off, diag;
     int* active_host = nullptr;         // pinned: {pairs still iterating, most iterations needed}
     Staging staging;                    // pair records, job lists and offsets of a call on their way to the device
-    std::vector<FreeBlob> blobs;
+    std::shared_ptr<BatchMemory> memory;
     int64_t calls = 0;                  // solver calls so far
     hipStream_t upload = nullptr;       // loading a batch does not wait for the caller's streams
     WorkerPool workers;
@@ -988,8 +998,10 @@ mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream) {
 
 // Device memory for a batch: a freed batch's block that nothing reads any more, or a new one.
 mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
-    for (size_t k = 0; k < ctx->blobs.size(); ++k) {
-        FreeBlob& f = ctx->blobs[k];
+    std::unique_lock<std::mutex> lock(ctx->memory->m);
+    std::vector<FreeBlob>& blobs = ctx->memory->blobs;
+    for (size_t k = 0; k < blobs.size(); ++k) {
+        FreeBlob& f = blobs[k];
         if (f.cap < bytes || f.cap > 4 * bytes + 65536) continue;
         bool idle = true;
         for (hipEvent_t e : f.readers) idle = idle && hipEventQuery(e) == hipSuccess;
@@ -1000,9 +1012,10 @@ mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
         for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
         *p = f.p;
         *cap = f.cap;
-        ctx->blobs.erase(ctx->blobs.begin() + (std::ptrdiff_t)k);
+        blobs.erase(blobs.begin() + (std::ptrdiff_t)k);
         return MGK_OK;
     }
+    lock.unlock();
     const size_t want = bytes <= kMaxBlobBytes ? (bytes + bytes / 4 + 65535) & ~(size_t)65535 : bytes;
     MGK_HIP(ctx, hipMalloc(p, want));
     *cap = want;
@@ -1010,8 +1023,10 @@ mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
 }
 
 // Keeps the block of a batch that is being freed, unless there are enough or it is large.
-bool keep_blob(mgk_ctx* ctx, mgk_batch* b) {
-    if (ctx->blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes || b->captured) return false;
+bool keep_blob(mgk_batch* b) {
+    std::lock_guard<std::mutex> lock(b->memory->m);
+    std::vector<FreeBlob>& blobs = b->memory->blobs;
+    if (!b->memory->open || blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes || b->captured) return false;
     for (hipStream_t s : b->used_on)
         if (capturing(s)) return false;   // an event recorded now would never complete
     FreeBlob f;
@@ -1025,7 +1040,7 @@ bool keep_blob(mgk_ctx* ctx, mgk_batch* b) {
         ok = ok && hipEventRecord(e, s) == hipSuccess;   // fails for a stream that is gone
     }
     if (ok) {
-        try { ctx->blobs.push_back(f); return true; } catch (...) {}
+        try { blobs.push_back(f); return true; } catch (...) {}
     }
     for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
     (void)hipGetLastError();
@@ -1383,7 +1398,10 @@ mgk_status mgk_create(mgk_ctx** out, int device) {
     mgk_ctx* ctx = new (std::nothrow) mgk_ctx();
     if (!ctx) return MGK_ENOMEM;
     ctx->device = device;
-    try { ctx->err.reserve(512); } catch (...) { delete ctx; return MGK_ENOMEM; }
+    try {
+        ctx->err.reserve(512);
+        ctx->memory = std::make_shared<BatchMemory>();
+    } catch (...) { delete ctx; return MGK_ENOMEM; }
     if (device >= 0 && hipSetDevice(device) != hipSuccess) { delete ctx; return MGK_EDEVICE; }
     *out = ctx;
     return MGK_OK;
@@ -1405,9 +1423,14 @@ void mgk_destroy(mgk_ctx* ctx) {
         }
         if (s.p) (void)hipHostFree(s.p);
     }
-    for (FreeBlob& f : ctx->blobs) {
-        (void)hipFree(f.p);   // waits for the work that reads it
-        for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+    {
+        std::lock_guard<std::mutex> lock(ctx->memory->m);
+        ctx->memory->open = false;
+        for (FreeBlob& f : ctx->memory->blobs) {
+            (void)hipFree(f.p);   // waits for the work that reads it
+            for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+        }
+        ctx->memory->blobs.clear();
     }
     if (ctx->upload) (void)hipStreamDestroy(ctx->upload);
     delete ctx;
@@ -1610,6 +1633,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     } guard{B};
 
     B->owner = ctx;
+    B->memory = ctx->memory;
+    B->device = ctx->device;
     B->n_graphs = n_graphs;
     B->graphs.resize(n_graphs);
     B->vtx_off.assign(vtx_off, vtx_off + n_graphs + 1);
@@ -2030,11 +2055,11 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     return MGK_OK;
 }
 
-void mgk_free_batch(mgk_ctx* ctx, mgk_batch* batch) {
+void mgk_free_batch(mgk_ctx*, mgk_batch* batch) {   // the context may be gone
     if (!batch) return;
     bool kept = false;
-    if (ctx && ctx == batch->owner && batch->blob) {
-        try { kept = hipSetDevice(ctx->device) == hipSuccess && keep_blob(ctx, batch); } catch (...) {}
+    if (batch->blob) {
+        try { kept = hipSetDevice(batch->device) == hipSuccess && keep_blob(batch); } catch (...) {}
     }
     if ((batch->blob && !kept) || batch->gram_jobs.dev) (void)hipDeviceSynchronize();
     if (batch->gram_jobs.dev) (void)hipFree(batch->gram_jobs.dev);

@@ -99,3 +99,17 @@ def test_workgroups_of_a_separable_launch_stay_within_the_grid(host):
     assert host.pairs(B, B, i, np.ones(4096, np.int32)) == 0, host.error()
     assert sum(launched(host.log(), "init")) == 4096 and max(launched(host.log(), "sep")) > 2000
     host.free(B)
+
+
+def test_batch_freed_after_its_context(so):
+    """Destroying the context first was always allowed; the context's memory is not looked at again."""
+    h = host_runtime.Host(so)
+    before, wb = h.lib.stub_in_use(), W.config1(12)
+    X, Y = h.load(wb), h.load(wb)
+    assert h.pairs(X, Y, [0, 1], [2, 3]) == 0, h.error()
+    h.free(Y)   # its block is kept for the next batch
+    gone = h.ctx
+    h.destroy()
+    assert h.lib.stub_in_use() > before
+    h.lib.mgk_free_batch(gone, X)
+    assert h.lib.stub_in_use() == before and h.violations() == ""
