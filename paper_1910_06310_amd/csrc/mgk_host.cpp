@@ -69,20 +69,45 @@ struct Staging {
 };
 
 // Device memory of freed batches, kept for the next ones (at most kMaxBlobs blocks of at most
-// kMaxBlobBytes).  A block is handed out again when the events recorded on the streams
-// that used its batch have completed.
+// kMaxBlobBytes).  A block is handed out again when the calls that read its batch have completed.
 constexpr size_t kMaxBlobs = 4, kMaxBlobBytes = (size_t)16 << 20;
+constexpr size_t kMaxReads = 8;    // calls under way that a batch keeps track of
+struct CallEnd;
 struct FreeBlob {
     void* p = nullptr;
     size_t cap = 0;
-    std::vector<hipEvent_t> readers;
+    std::vector<std::shared_ptr<CallEnd>> reads;
 };
 // Shared by a context and its batches: a batch may be freed after its context, and by another thread
 // than the one that uses the context.
 struct BatchMemory {
     std::mutex m;
     std::vector<FreeBlob> blobs;
-    bool open = true;   // until the context is destroyed
+    std::vector<hipEvent_t> events;   // of the device, not in use
+    bool open = true;                 // until the context is destroyed
+    ~BatchMemory() {
+        for (hipEvent_t e : events) (void)hipEventDestroy(e);
+    }
+};
+// Completes with the kernels of a call.  The event is recorded before the call returns, when its
+// stream is there for certain; the stream is not looked at again.
+struct CallEnd {
+    std::shared_ptr<BatchMemory> memory;
+    hipEvent_t event = nullptr;
+    ~CallEnd() {
+        if (!event) return;
+        try {
+            std::lock_guard<std::mutex> lock(memory->m);
+            if (memory->events.size() < 4 * kMaxReads) { memory->events.push_back(event); return; }
+        } catch (...) {
+        }
+        (void)hipEventDestroy(event);
+    }
+    bool over() const {
+        if (hipEventQuery(event) == hipSuccess) return true;
+        (void)hipGetLastError();   // "not ready" is no error of a later launch
+        return false;
+    }
 };
 
 // Threads of a context for the host work of a call.  run(n, f, helpers) calls f(0) .. f(n - 1), on
@@ -188,11 +213,10 @@ struct mgk_batch {
     MgkSepList sep[2] = {};               // the batch's part of it for the two packet sizes
     int64_t dense_floats = 0;             // sum of (n rounded up to 64)^2
     // device
-    int device = 0;
     void* blob = nullptr;
     size_t blob_cap = 0;
-    std::vector<hipStream_t> used_on;   // streams with calls that read the batch
-    bool captured = false;              // a recorded graph reads it, replayed on streams unknown here
+    std::vector<std::shared_ptr<CallEnd>> reads;   // calls that read the batch and may be under way
+    bool untracked = false;             // others may be: freeing the batch waits for the device
     MgkBatchDev dev{};
     JobList gram_jobs;
     int gram_jobs_waves = 0;       // waves_per_pair setting the list was built for
@@ -375,10 +399,39 @@ mgk_status refuse_capture(mgk_ctx* ctx, hipStream_t stream) {
     return fail(ctx, MGK_EDEVICE, "operation not permitted when stream is capturing");
 }
 
-void note_use(mgk_batch* b, hipStream_t stream) {
-    if (capturing(stream)) b->captured = true;
-    if (std::find(b->used_on.begin(), b->used_on.end(), stream) == b->used_on.end()) b->used_on.push_back(stream);
-}
+// What a call reads.  done() records the end of the call; a batch of a call that fails on the way, that is
+// part of a recorded graph, or that has too many calls under way, is waited for with the whole device.
+class BatchReads {
+public:
+    BatchReads(mgk_batch* X, mgk_batch* Y) : b_{X, Y}, was_{X->untracked, Y->untracked} { X->untracked = Y->untracked = true; }
+    // may_create: else the event is one that an earlier call has left
+    void done(hipStream_t stream, bool may_create) {
+        try {
+            auto end = std::make_shared<CallEnd>();
+            end->memory = b_[0]->memory;
+            for (mgk_batch* b : b_)
+                b->reads.erase(std::remove_if(b->reads.begin(), b->reads.end(), [](const std::shared_ptr<CallEnd>& r) { return r->over(); }),
+                               b->reads.end());
+            {
+                std::lock_guard<std::mutex> lock(end->memory->m);
+                std::vector<hipEvent_t>& spare = end->memory->events;
+                if (!spare.empty()) { end->event = spare.back(); spare.pop_back(); }
+            }
+            if (!end->event && (!may_create || hipEventCreateWithFlags(&end->event, hipEventDisableTiming) != hipSuccess)) return;
+            if (hipEventRecord(end->event, stream) != hipSuccess) { (void)hipGetLastError(); return; }
+            for (int k = 0; k < (b_[0] == b_[1] ? 1 : 2); ++k)
+                if (b_[k]->reads.size() < kMaxReads) {
+                    b_[k]->reads.push_back(end);
+                    b_[k]->untracked = was_[k];
+                }
+        } catch (...) {   // out of memory: untracked
+        }
+    }
+
+private:
+    mgk_batch* b_[2];
+    const bool was_[2];
+};
 
 // the batches must carry the number of label attributes the edge kernel reads
 mgk_status check_label_dim(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y) {
@@ -998,20 +1051,16 @@ mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream) {
 
 // Device memory for a batch: a freed batch's block that nothing reads any more, or a new one.
 mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
+    std::vector<std::shared_ptr<CallEnd>> ended;
     std::unique_lock<std::mutex> lock(ctx->memory->m);
     std::vector<FreeBlob>& blobs = ctx->memory->blobs;
     for (size_t k = 0; k < blobs.size(); ++k) {
         FreeBlob& f = blobs[k];
         if (f.cap < bytes || f.cap > 4 * bytes + 65536) continue;
-        bool idle = true;
-        for (hipEvent_t e : f.readers) idle = idle && hipEventQuery(e) == hipSuccess;
-        if (!idle) {
-            (void)hipGetLastError();   // "not ready" is no error of a later launch
-            continue;
-        }
-        for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
+        if (!std::all_of(f.reads.begin(), f.reads.end(), [](const std::shared_ptr<CallEnd>& r) { return r->over(); })) continue;
         *p = f.p;
         *cap = f.cap;
+        ended.swap(f.reads);   // given back when the lock is
         blobs.erase(blobs.begin() + (std::ptrdiff_t)k);
         return MGK_OK;
     }
@@ -1026,25 +1075,9 @@ mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
 bool keep_blob(mgk_batch* b) {
     std::lock_guard<std::mutex> lock(b->memory->m);
     std::vector<FreeBlob>& blobs = b->memory->blobs;
-    if (!b->memory->open || blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes || b->captured) return false;
-    for (hipStream_t s : b->used_on)
-        if (capturing(s)) return false;   // an event recorded now would never complete
-    FreeBlob f;
-    f.p = b->blob;
-    f.cap = b->blob_cap;
-    bool ok = true;
-    for (hipStream_t s : b->used_on) {
-        hipEvent_t e = nullptr;
-        ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-        if (e) f.readers.push_back(e);
-        ok = ok && hipEventRecord(e, s) == hipSuccess;   // fails for a stream that is gone
-    }
-    if (ok) {
-        try { blobs.push_back(f); return true; } catch (...) {}
-    }
-    for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
-    (void)hipGetLastError();
-    return false;
+    if (!b->memory->open || blobs.size() >= kMaxBlobs || b->blob_cap > kMaxBlobBytes || b->untracked) return false;
+    blobs.push_back(FreeBlob{b->blob, b->blob_cap, b->reads});
+    return true;
 }
 
 // Run Alg. 1 with global-memory vectors for a list of pairs (outer graphs from
@@ -1401,8 +1434,13 @@ mgk_status mgk_create(mgk_ctx** out, int device) {
     try {
         ctx->err.reserve(512);
         ctx->memory = std::make_shared<BatchMemory>();
+        ctx->memory->events.reserve(4 * kMaxReads);
     } catch (...) { delete ctx; return MGK_ENOMEM; }
     if (device >= 0 && hipSetDevice(device) != hipSuccess) { delete ctx; return MGK_EDEVICE; }
+    for (int k = 0; device >= 0 && k < 4; ++k) {   // for calls that may not create any
+        hipEvent_t e = nullptr;
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) ctx->memory->events.push_back(e);
+    }
     *out = ctx;
     return MGK_OK;
 }
@@ -1423,15 +1461,14 @@ void mgk_destroy(mgk_ctx* ctx) {
         }
         if (s.p) (void)hipHostFree(s.p);
     }
+    std::vector<FreeBlob> blobs;
     {
         std::lock_guard<std::mutex> lock(ctx->memory->m);
         ctx->memory->open = false;
-        for (FreeBlob& f : ctx->memory->blobs) {
-            (void)hipFree(f.p);   // waits for the work that reads it
-            for (hipEvent_t e : f.readers) (void)hipEventDestroy(e);
-        }
-        ctx->memory->blobs.clear();
+        blobs.swap(ctx->memory->blobs);
     }
+    for (FreeBlob& f : blobs) (void)hipFree(f.p);   // waits for the work that reads it
+    blobs.clear();
     if (ctx->upload) (void)hipStreamDestroy(ctx->upload);
     delete ctx;
 }
@@ -1634,7 +1671,6 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
 
     B->owner = ctx;
     B->memory = ctx->memory;
-    B->device = ctx->device;
     B->n_graphs = n_graphs;
     B->graphs.resize(n_graphs);
     B->vtx_off.assign(vtx_off, vtx_off + n_graphs + 1);
@@ -2059,7 +2095,7 @@ void mgk_free_batch(mgk_ctx*, mgk_batch* batch) {   // the context may be gone
     if (!batch) return;
     bool kept = false;
     if (batch->blob) {
-        try { kept = hipSetDevice(batch->device) == hipSuccess && keep_blob(batch); } catch (...) {}
+        try { kept = keep_blob(batch); } catch (...) {}
     }
     if ((batch->blob && !kept) || batch->gram_jobs.dev) (void)hipDeviceSynchronize();
     if (batch->gram_jobs.dev) (void)hipFree(batch->gram_jobs.dev);
@@ -2184,7 +2220,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         batch->gram_jobs_attr_dim = attr_dim_of(ctx);
         if (st != MGK_OK) return st;
     }
-    note_use(batch, stream);
+    batch->untracked = true;   // its job list has freeing wait as well
     const MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
     return launch_jobs(ctx, batch, batch, batch->gram_jobs, out, stream);
 }
@@ -2258,8 +2294,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         MGK_HIP(ctx, hipStreamSynchronize(ctx->pair_jobs_stream));
         ctx->pair_jobs_busy = false;
     }
-    note_use(X, stream);
-    if (Y != X) note_use(Y, stream);
+    BatchReads reads(X, Y);
     MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
     if (no_alloc) {
         // Job list in the fixed array of this GPU.  All calls on the GPU share it: a call
@@ -2277,7 +2312,8 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if (st != MGK_OK) return st;
         ctx->fixed_jobs_stream = stream;
         ctx->fixed_jobs_busy = true;
-        return launch_jobs(ctx, X, Y, fixed, out, stream);
+        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(stream, false);
+        return st;
     }
     mgk_status st = build_job_list(ctx, plan, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
     if (st != MGK_OK) return st;
@@ -2295,7 +2331,8 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         out.nodal = x_dev;
         out.nodal_off = (const int64_t*)ctx->nodal_off.p;
     }
-    return launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream);
+    if ((st = launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream)) == MGK_OK) reads.done(stream, true);
+    return st;
 }
 
 mgk_status mgk_pairs(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n_pairs,

@@ -25,9 +25,7 @@ struct Event { void* stream; bool done; };
 std::map<char*, size_t> device_memory;              // block -> bytes
 size_t in_use = 0, limit = SIZE_MAX, pinned_bytes = 0;
 std::set<void*> held, recording;                    // streams
-int unreachable = 0;                                // work of streams that are gone
 std::map<void*, std::set<char*>> readers;           // held stream -> blocks its work reads
-std::set<char*> unreachable_reads;
 std::set<Event*> events;
 std::string log_text;
 std::vector<std::string> violations;
@@ -61,8 +59,6 @@ void finish(void* stream) {
 
 void finish_all() {
     while (!held.empty()) finish(*held.begin());
-    unreachable = 0;
-    unreachable_reads.clear();
 }
 
 void reads(void* stream, const void* p) {
@@ -75,7 +71,6 @@ void check_write(const void* p) {   // a block that unfinished work reads must n
     if (!b) { violations.push_back("write outside device memory"); return; }
     for (auto& r : readers)
         if (r.second.count(b)) violations.push_back("write to a block that work under way reads");
-    if (unreachable_reads.count(b)) violations.push_back("write to a block that work under way reads");
 }
 
 hipError_t launched(const char* name, void* stream, const MgkBatchDev* X = nullptr, const MgkBatchDev* Y = nullptr, int pairs = 0) {
@@ -109,13 +104,15 @@ const char* stub_violations() {
 }
 void stub_hold(void* stream) { held.insert(stream); }
 void stub_record(void* stream, int on) { if (on) recording.insert(stream); else recording.erase(stream); }
-// The stream is destroyed with work under way and its handle given to a new one.
+// The stream is destroyed with work under way and its handle given to a new one: the work goes on
+// under a name that nothing else has.
 void stub_replace_stream(void* stream) {
-    if (!held.count(stream)) return;
-    unreachable++;
-    unreachable_reads.insert(readers[stream].begin(), readers[stream].end());
-    readers.erase(stream);
-    held.erase(stream);
+    if (!held.erase(stream)) return;
+    void* name = new char;
+    held.insert(name);
+    readers[name].swap(readers[stream]);
+    for (Event* e : events)
+        if (e->stream == stream && !e->done) e->stream = name;
 }
 void stub_set_limit(int64_t bytes) { limit = bytes < 0 ? SIZE_MAX : (size_t)bytes; }
 int64_t stub_in_use() { return (int64_t)in_use; }

@@ -1,4 +1,5 @@
 """Host path of a solve without a GPU: the library's host code on a stand-in for the HIP runtime."""
+import ctypes as C
 import os
 import re
 import shutil
@@ -113,3 +114,41 @@ def test_batch_freed_after_its_context(so):
     assert h.lib.stub_in_use() > before
     h.lib.mgk_free_batch(gone, X)
     assert h.lib.stub_in_use() == before and h.violations() == ""
+
+
+@pytest.mark.parametrize("entry", ["mgk_pairs", "mgk_pairs_noalloc"])
+def test_block_of_a_freed_batch_waits_for_calls_on_streams_that_are_gone(host, entry):
+    """A stream may be destroyed with work under way, and its handle given to a new one, before the batch is
+    freed: the block must not go to the next batch while that work reads it."""
+    wb = W.config1(12)
+    host.free(host.load(wb))
+    for _ in range(3):
+        B = host.load(wb)
+        host.hold(5)
+        assert host.pairs(B, B, [0, 1], [2, 3], stream=5, entry=entry) == 0, host.error()
+        host.lib.stub_replace_stream(C.c_void_p(5))
+        host.free(B)
+        host.free(host.load(wb))
+        assert host.violations() == ""
+
+
+@pytest.mark.parametrize("entry", ["mgk_pairs", "mgk_pairs_noalloc"])
+def test_block_of_a_freed_batch_is_used_again(host, entry):
+    """Loading, comparing and freeing in turn neither allocates nor waits for the device."""
+    wb = W.config1(12)
+    for k in range(6):
+        if k == 2:
+            before = host.count("malloc"), host.count("device waits")
+        B = host.load(wb)
+        assert host.pairs(B, B, [0, 1], [2, 3], entry=entry) == 0, host.error()
+        host.free(B)
+    assert (host.count("malloc"), host.count("device waits")) == before
+
+
+def test_freeing_a_batch_leaves_the_current_device(host):
+    B = host.load(W.config1(12))
+    assert host.pairs(B, B, [0, 1], [2, 3]) == 0, host.error()
+    host.lib.stub_set_device(1)
+    host.free(B)
+    assert host.lib.stub_device() == 1
+    host.lib.stub_set_device(0)
