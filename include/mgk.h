@@ -25,6 +25,9 @@
  *  - Kernels are enqueued on the HIP stream passed as `stream` (a hipStream_t
  *    cast to void*, NULL = the null stream).  Results are valid once the caller
  *    has synchronised that stream.
+ *  - While a graph is recorded on `stream`, mgk_gram on a batch whose job list an
+ *    earlier call has built, with all pairs solved on chip, becomes part of it; the
+ *    other solve calls return MGK_EDEVICE and leave the recording as it was.
  *  - A ctx is bound to one device and is not thread-safe.  Batches belong to
  *    the ctx that loaded them.
  *  - Calls that include pairs too large for the on-chip solver synchronise the

@@ -1311,6 +1311,9 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                        const MgkOutputs& out, hipStream_t stream) {
     const MgkParams prm = make_params(ctx, X);
     const bool weighted = X->weighted || Y->weighted;
+    const bool any_large = !jl.large[0].empty() || !jl.large[1].empty();
+    if (any_large)   // before anything is recorded
+        if (mgk_status st = refuse_capture(ctx, stream)) return st;
     ctx->calls++;
     ctx->launch_log.clear();
     for (const JobBin& b : jl.bins) {
@@ -1340,8 +1343,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             done += chunk;
         }
     }
-    if (jl.large[0].empty() && jl.large[1].empty()) return MGK_OK;
-    if (mgk_status st = refuse_capture(ctx, stream)) return st;
+    if (!any_large) return MGK_OK;
     // ---- pairs with vectors in global memory: the product of each from the current edge kernel
     const MgkSepBasis none{};
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
@@ -2162,11 +2164,13 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
          batch->gram_jobs_limit != ctx->onchip_limit ||
          batch->gram_jobs_cache != ctx->product_cache || batch->gram_jobs_sorted != ctx->cost_sorted ||
          batch->gram_jobs_attr_dim != attr_dim_of(ctx))) {
+        if (mgk_status st = refuse_capture(ctx, stream)) return st;
         MGK_HIP(ctx, hipStreamSynchronize(stream));  // launch shape changed: rebuild the job list
         MGK_HIP(ctx, hipFree(batch->gram_jobs.dev));
         batch->gram_jobs.dev = nullptr;
     }
     if (batch->gram_jobs.dev == nullptr && G > 0) {
+        if (mgk_status st = refuse_capture(ctx, stream)) return st;   // the list is copied and waited for
         // a4: job list, one job per unordered pair, kept with the batch
         JobPlan plan;
         plan.jobs.reserve((size_t)(G * (G + 1) / 2));
@@ -2355,6 +2359,7 @@ mgk_status mgk_pairs_dev(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n_pai
         // the launch shape of a pair is chosen on the host from the sizes of its graphs
         hipStream_t stream = static_cast<hipStream_t>(stream_);
         MGK_HIP(ctx, hipSetDevice(ctx->device));
+        if (mgk_status st = refuse_capture(ctx, stream)) return st;   // before the copies are recorded
         std::vector<int32_t> ij((size_t)(2 * n_pairs));
         MGK_HIP(ctx, hipMemcpyAsync(ij.data(), i_dev, (size_t)n_pairs * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         MGK_HIP(ctx, hipMemcpyAsync(ij.data() + n_pairs, j_dev, (size_t)n_pairs * sizeof(int32_t), hipMemcpyDeviceToHost, stream));

@@ -152,3 +152,26 @@ def test_freeing_a_batch_leaves_the_current_device(host):
     host.free(B)
     assert host.lib.stub_device() == 1
     host.lib.stub_set_device(0)
+
+
+def test_refused_calls_leave_a_recording_as_it_was(host):
+    """A call that cannot be part of a graph is refused before it records or waits for anything: lists of
+    its own, and pairs of the global-memory solver."""
+    host.set("onchip_limit", 400)
+    small, mixed = host.load(graphs(path(10), path(12))), host.load(graphs(path(10), path(30)))
+    assert host.gram(mixed) == 0 and host.gram(small) == 0
+    new = host.load(graphs(path(10), path(12)))
+    device = (C.c_int32 * 2)(0, 1)   # the stand-in's device memory is host memory
+    calls = [lambda: host.pairs(small, small, [0, 1], [1, 1], stream=3),
+             lambda: host.pairs(small, small, [0, 1], [1, 1], stream=3, entry="mgk_pairs_noalloc"),
+             lambda: host.lib.mgk_pairs_dev(host.ctx, small, small, C.c_int64(2), device, device, host.out(), None, None, C.c_void_p(3)),
+             lambda: host.gram(mixed, stream=3), lambda: host.gram(new, stream=3)]
+    host.lib.stub_reset()
+    with host.recording(3):
+        for call in calls:
+            assert call() == 3 and "captur" in host.error()
+            assert "recorded" not in host.log() and host.count("recorded copies") == host.count("broken recordings") == 0
+        assert host.gram(small, stream=3) == 0
+        assert "recorded" in host.log()
+    for call in calls:
+        assert call() == 0, host.error()
