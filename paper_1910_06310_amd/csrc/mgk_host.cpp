@@ -208,10 +208,8 @@ struct mgk_batch {
     std::vector<int64_t> vtx_off;  // [G+1]
     std::vector<MgkSellDesc> sell_desc;   // per graph, for the planner
     float label_lo = 0.f, label_hi = 0.f; // range of attribute 0 of the edge labels
-    int32_t max_n = 0;
-    int32_t packets[2] = {0, 0};          // packet steps of the whole batch with 2 / 8 nonzeros per packet
+    std::vector<int32_t> packet_off[2];   // [G+1], packet steps before each graph with 2 / 8 nonzeros per packet
     MgkSepList sep[2] = {};               // the batch's part of it for the two packet sizes
-    int64_t dense_floats = 0;             // sum of (n rounded up to 64)^2
     // device
     void* blob = nullptr;
     size_t blob_cap = 0;
@@ -955,16 +953,28 @@ struct LargeCost {
     double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
 };
-LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, bool dense_fits, const MgkGraphDesc& o, const MgkGraphDesc& i) {
+// Bytes the features of a graph take at most, whatever the layout.
+constexpr int64_t kMaxFeatureBytes = (int64_t)8 << 30;   // of the pairs solved together
+int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
+    const int64_t np = (b->graphs[(size_t)g].n + 63) & ~63;
+    const auto& off = b->packet_off[rank == 1 ? 1 : 0];
+    return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
+}
+
+// Forming the features is left out: only the graphs of the pairs get them, which takes 1 % of what the
+// products of a pair take.
+LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb) {
+    const MgkGraphDesc &o = A->graphs[(size_t)ga], &i = B->graphs[(size_t)gb];
+    auto fits = [&](bool dense) { return feature_bytes(A, ga, S.rank, dense) + feature_bytes(B, gb, S.rank, dense) <= kMaxFeatureBytes; };
     LargeCost C;
     C.best = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
     C.clk[C.best] = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n + 6.0 * N;
     if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) return C;
     const MgkSepLayout L = sep_layout(S.rank, i.n);
-    if (L.rk > 0) C.clk[kPathSep] = (double)L.rk * L.passes * one_sided / 20.0 + 8.0 * N;
+    if (L.rk > 0 && fits(false)) C.clk[kPathSep] = (double)L.rk * L.passes * one_sided / 20.0 + 8.0 * N;
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255;
-    if (dense_fits && ip <= MGK_SEP_DENSE_MAX_N) C.clk[kPathSepDense] = S.rank * op * ip * ((double)o.n + i.n) / 42.0;
+    if (ip <= MGK_SEP_DENSE_MAX_N && fits(true)) C.clk[kPathSepDense] = S.rank * op * ip * ((double)o.n + i.n) / 42.0;
     for (int path : {kPathSep, kPathSepDense})
         if (C.clk[path] < C.clk[C.best]) C.best = path;
     return C;
@@ -1236,31 +1246,48 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         max_iter = std::max(max_iter, P.max_iter);
     }
     const int vec_blocks = std::max(1, std::min(2048, (max_npad + 1023) / 1024));
-    // pair records, their zeroed states and the counters of a call are one block and one copy
+    // the graphs in use and where their features go, from A and from Bb (the same list when it is A)
+    const int gi = L.per_packet == 8 ? 1 : 0, sides = Bb == A ? 1 : 2;
+    const mgk_batch* bt[2] = {A, Bb};
+    std::vector<MgkSepGraph> used[2];
+    std::vector<int32_t> entry[2];   // of each graph in that list
+    int64_t size[2] = {0, 0};        // floats of dense F_k, or packet steps of a pass
+    int32_t max_n[2] = {1, 1};
+    for (int k = 0; k < sides; ++k) entry[k].assign((size_t)bt[k]->n_graphs, -1);
+    auto features = [&](int k, int32_t g) {
+        if (entry[k][(size_t)g] < 0) {
+            const int32_t n = bt[k]->graphs[(size_t)g].n;
+            const int64_t np = (n + 63) & ~63, steps0 = bt[k]->packet_off[gi][(size_t)g], steps1 = bt[k]->packet_off[gi][(size_t)g + 1];
+            entry[k][(size_t)g] = (int32_t)used[k].size();
+            used[k].push_back({dense ? size[k] : size[k] - steps0, g, 0});
+            size[k] += dense ? np * np * S.rank : steps1 - steps0;
+            max_n[k] = std::max(max_n[k], n);
+        }
+        return used[k][(size_t)entry[k][(size_t)g]].at;
+    };
+    for (MgkLargePair& P : pairs) {
+        P.f1 = features(0, P.g1);
+        P.f2 = features(sides - 1, P.g2);
+    }
+    // pair records, their zeroed states, the counters and the graph lists of a call are one block and one copy
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
     const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
-    const size_t rec_bytes = active_at + 64;
+    const size_t used_at[2] = {active_at + 64, active_at + 64 + used[0].size() * sizeof(MgkSepGraph)};
+    const size_t rec_bytes = used_at[1] + used[1].size() * sizeof(MgkSepGraph);
     mgk_status st;
     if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
     if ((st = ensure(ctx, ctx->lpairs, rec_bytes)) != MGK_OK) return st;
     if (!ctx->active_host) MGK_HIP(ctx, hipHostMalloc((void**)&ctx->active_host, 64, hipHostMallocDefault));
-
-    // features of the batches' nonzeros (they depend on the edge kernel's parameters)
-    const mgk_batch* bt[2] = {A, Bb};
     MgkSepList sl[2] = {};
-    const int gi = L.per_packet == 8 ? 1 : 0;
-    for (int k = 0; k < 2; ++k) {
-        if (k == 1 && Bb == A) { sl[1] = sl[0]; break; }
-        hipError_t e;
+    for (int k = 0; k < sides; ++k) {
         sl[k] = bt[k]->sep[gi];
+        sl[k].total = dense ? 0 : (int32_t)size[k];
         DevBuf& buf = dense ? ctx->sep_dense[k] : ctx->sep_packets[k];
-        const size_t floats = dense ? (size_t)bt[k]->dense_floats * S.rank : ((size_t)L.passes * sl[k].total + 1) * 64;   // stage 2 may load one step past the last
+        const size_t floats = dense ? (size_t)size[k] : ((size_t)L.passes * size[k] + 1) * 64;   // stage 2 may load one step past the last
         if ((st = ensure(ctx, buf, std::max<size_t>(256, floats * sizeof(float)))) != MGK_OK) return st;
         (dense ? sl[k].dense : sl[k].packets) = (const float*)buf.p;
-        e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, sl[k], bt[k]->max_n, (float*)buf.p, stream)
-                  : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], bt[k]->max_n, (float*)buf.p, stream);
-        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
+    if (sides == 1) sl[1] = sl[0];
 
     Staging::Slot* slot;
     if ((st = staging_slot(ctx, rec_bytes, true, &slot)) != MGK_OK) return st;
@@ -1268,8 +1295,16 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     memset(rec, 0, rec_bytes);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
+    for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
     MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, rec_bytes, hipMemcpyHostToDevice, stream));
     if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
+    // features of the graphs' nonzeros (they depend on the edge kernel's parameters)
+    for (int k = 0; k < sides; ++k) {
+        const MgkSepGraph* list = (const MgkSepGraph*)((char*)ctx->lpairs.p + used_at[k]);
+        hipError_t e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, list, (int)used[k].size(), max_n[k], (float*)ctx->sep_dense[k].p, stream)
+                             : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], list, (int)used[k].size(), max_n[k], (float*)ctx->sep_packets[k].p, stream);
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
+    }
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
     MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
     int* dactive = (int*)((char*)ctx->lpairs.p + active_at);
@@ -1348,8 +1383,6 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     const MgkSepBasis none{};
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
     const MgkSepBasis& S = may_sep ? sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi)) : none;
-    constexpr int64_t kMaxDenseBytes = (int64_t)8 << 30;   // both batches' dense F_k
-    const bool dense_fits = (X->dense_floats + (X == Y ? 0 : Y->dense_floats)) * S.rank * 4 <= kMaxDenseBytes;
     struct Oriented { MgkLargePair pair; int swapped; };
     std::vector<Oriented> sep_form;   // the pair as the separable product takes it
     std::vector<LargeCost> costs;
@@ -1365,7 +1398,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                 if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
                 if (X != Y) f.swapped = 1 - swapped;
             }
-            costs.push_back(large_cost(ctx, S, dense_fits, (f.swapped ? Y : X)->graphs[P.g1], (f.swapped ? X : Y)->graphs[P.g2]));
+            costs.push_back(large_cost(ctx, S, f.swapped ? Y : X, P.g1, f.swapped ? X : Y, P.g2));
             sep_form.push_back(f);
         }
     merge_paths(costs);
@@ -1396,12 +1429,17 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             size_t first = 0;
             while (first < all.size()) {
                 size_t last = first;
-                int64_t floats = 0;
+                int64_t floats = 0, features = 0;
                 int max_n1 = 1, max_n2 = 1;
+                auto bytes = [&](const MgkLargePair& P) {   // of its features; graphs that pairs share are counted for each
+                    return path != kPathSep && path != kPathSepDense ? 0
+                        : feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
+                };
                 while (last < all.size() && last - first < kMaxPairsPerGroup &&
-                       (last == first || (floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats &&
+                       (last == first || (floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats && features + bytes(all[last]) <= kMaxFeatureBytes &&
                                           grid_threads((int64_t)(last - first) + 1, std::max(max_n1, all[last].n1)) < kMaxGridThreads))) {
                     floats += 5 * (int64_t)all[last].npad;
+                    features += bytes(all[last]);
                     max_n1 = std::max(max_n1, all[last].n1);
                     max_n2 = std::max(max_n2, all[last].n2);
                     ++last;
@@ -1683,10 +1721,11 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->sell_desc.reserve((size_t)n_graphs);
     std::vector<MgkEntry> list_outer, list_inner;   // nonzero lists for the register-resident solver
     std::vector<int32_t> gptr[2], deg_order;       // packets of the separable product, rows by degree
-    std::vector<int64_t> dense_off((size_t)n_graphs);
     std::vector<int32_t> qoff((size_t)n_graphs);
     constexpr int kPerPacket[2] = {2, 8};
     for (auto& v : gptr) v.reserve((size_t)(tot_v / 4 + 2 * (int64_t)n_graphs));
+    for (auto& v : B->packet_off) v.assign((size_t)n_graphs + 1, 0);
+    int32_t packets[2] = {0, 0};
     deg_order.resize((size_t)tot_v);
     B->label_lo = INFINITY;
     B->label_hi = -INFINITY;
@@ -1904,15 +1943,14 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             for (int i = 0; i < n; i += 4) {   // four rows of adjacent degrees: the first has the most packets
                 const int d = deg[deg_order[(size_t)v0 + i]];
                 for (int q = 0; q < 2; ++q) {
-                    gptr[q].push_back(B->packets[q]);
-                    B->packets[q] += (d + kPerPacket[q] - 1) / kPerPacket[q];
+                    gptr[q].push_back(packets[q]);
+                    packets[q] += (d + kPerPacket[q] - 1) / kPerPacket[q];
                 }
             }
-            for (int q = 0; q < 2; ++q) gptr[q].push_back(B->packets[q]);
-            dense_off[(size_t)g] = B->dense_floats;
-            const int64_t np = (n + 63) & ~63;
-            B->dense_floats += np * np;
-            B->max_n = std::max(B->max_n, n);
+            for (int q = 0; q < 2; ++q) {
+                gptr[q].push_back(packets[q]);
+                B->packet_off[q][(size_t)g + 1] = packets[q];
+            }
         }
         gd.loff = (int32_t)lanes_total;
         {
@@ -2030,7 +2068,6 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     const size_t o_ai = blob.add(attr_inner);
     const size_t o_pk[2] = {blob.add(gptr[0]), blob.add(gptr[1])};
     const size_t o_do = blob.add(deg_order), o_qo = blob.add(qoff);
-    const size_t o_df = blob.add(dense_off);
     const size_t o_sd = blob.add(B->sell_desc);
     const size_t o_sv = blob.add(sell_vtx);
     const size_t o_sn = blob.add(sell_nbr);
@@ -2081,8 +2118,6 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         B->sep[q].qoff = reinterpret_cast<const int32_t*>(base + o_qo);
         B->sep[q].gptr = reinterpret_cast<const int32_t*>(base + o_pk[q]);
         B->sep[q].deg_order = reinterpret_cast<const int32_t*>(base + o_do);
-        B->sep[q].dense_off = reinterpret_cast<const int64_t*>(base + o_df);
-        B->sep[q].total = B->packets[q];
     }
     B->dev.sell_desc = reinterpret_cast<const MgkSellDesc*>(base + o_sd);
     B->dev.sell_vtx = reinterpret_cast<const MgkSellVertex*>(base + o_sv);

@@ -397,18 +397,23 @@ static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
 static inline MGK_HD int64_t mgk_sep_grid(int64_t n_pairs, int32_t max_n1, int32_t rows) {
     return (n_pairs + 7) / 8 * 8 * ((max_n1 + rows - 1) / rows);
 }
-// What the separable product reads beside MgkBatchDev.  Packets of a batch come in steps of 64
-// words (four rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64;
-// group t of graph g has steps gptr[qoff[g] + t] .. gptr[qoff[g] + t + 1].  One step more than all
-// passes have is allocated: stage 2 loads the first packet of a group before it looks whether it has one.
+// What the separable product reads beside MgkBatchDev.  Packets come in steps of 64 words (four
+// rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64; group t of graph g
+// has steps at + gptr[qoff[g] + t] .. at + gptr[qoff[g] + t + 1], gptr counting over the whole batch and
+// `at` the graph's MgkSepGraph::at.  One step more than all passes have is allocated: stage 2 loads the
+// first packet of a group before it looks whether it has one.
 struct MgkSepList {
     const int32_t* qoff;        // per graph: first entry in gptr
     const int32_t* gptr;        // per four vertices of a graph, and one more per graph
     const int32_t* deg_order;   // per graph (index voff): its vertices by descending number of nonzeros
-    const int64_t* dense_off;   // per graph: sum over the graphs before it of (n rounded up to 64)^2
     const float* packets;
     const float* dense;         // dense F_k
     int32_t total;
+};
+// A graph whose features a call forms, and where they are: dense F_k from float `at` on, packets see above.
+struct MgkSepGraph {
+    int64_t at;
+    int32_t graph, unused;
 };
 
 // ---- solver with vectors in global memory (pairs too large for LDS) ---------
@@ -462,6 +467,7 @@ struct MgkLargePair {
     int32_t max_iter;
     int32_t nsteps;        // DPP steps for the inner row sums
     int32_t atomic_rows;   // inner graph has rows longer than a lane group
+    int64_t f1, f2;        // MgkSepGraph::at of the two graphs (separable product)
 };
 
 // Scalars of one pair in the global-memory solver.  The three sums of iteration `it` go

@@ -154,11 +154,13 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
 // ---- separable product (mgk_sep.hip) ------------------------------------------
 // Weak, so that the host code links without the kernels (host-only contexts never get here).
 #define MGK_KERNELS_OPTIONAL __attribute__((weak))
-// Packets (layout L; gptr and total of that packet size) and dense F_k of every graph of B.
+// Packets (layout L; gptr and total of that packet size) and dense F_k of the n_used graphs of B listed
+// in device memory at `used`, the largest of max_n vertices.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L,
-                                                    const MgkSepList& list, int max_n, float* packets, hipStream_t stream);
-MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepList& list, int max_n,
-                                                          float* F, hipStream_t stream);
+                                                    const MgkSepList& list, const MgkSepGraph* used, int n_used, int max_n,
+                                                    float* packets, hipStream_t stream);
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph* used,
+                                                          int n_used, int max_n, float* F, hipStream_t stream);
 // y = XMV(p) and p^T a of iteration `it` for every pair that still iterates (check_only: y alone, for
 // the pairs marked by mgk_launch_large_outputs).  max_n1, max_n2: largest outer and inner graph.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,

@@ -31,18 +31,19 @@ __device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const double*
     return (float)(k & 1 ? v * s : v);
 }
 
-// Packets of the graphs of a batch: the vertices of a graph in order of descending degree, in
+// Packets of the graphs a call uses: the vertices of a graph in order of descending degree, in
 // groups of four; step t of a group holds packet t of its four rows, 16 words each.  A
 // packet holds per_packet nonzeros of its row: rk coefficients A_ij phi_k and the byte offset of
 // the slab of column j each; absent nonzeros have coefficients 0 and offset 0.  One wavefront
 // per group.
 __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepLayout L,
-                                                           MgkSepList list, int g0, float* out) {
+                                                           MgkSepList list, const MgkSepGraph* used, float* out) {
     __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
     for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
-    const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
-    const int32_t* gptr = list.gptr + list.qoff[g0 + blockIdx.y];
+    const MgkSepGraph sg = used[blockIdx.y];
+    const MgkGraphDesc g = B.graphs[sg.graph];
+    const int32_t* gptr = list.gptr + list.qoff[sg.graph];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = lane & 15, u = slot / (L.rk + 1), kk = slot - u * (L.rk + 1);
     for (int grp = blockIdx.x * 4 + wave; grp * 4 < g.n; grp += gridDim.x * 4) {
@@ -61,22 +62,23 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
                 float v = 0.f;
                 if (on && kk < L.rk && k < S.rank) v = w * sep_feature(S, coef, __uint_as_float(e.z), k);
                 if (on && kk == L.rk) v = __uint_as_float(e.y * (uint32_t)L.slab_bytes);
-                out[((int64_t)q * list.total + p) * 64 + lane] = v;
+                out[((int64_t)q * list.total + sg.at + p) * 64 + lane] = v;
             }
         }
     }
 }
 
-// Dense F_k of every graph: F[(dense_off[g] * rank) + (k np + i) np + j], np = n rounded up to 64,
+// Dense F_k of the graphs a call uses: F[at + (k np + i) np + j], np = n rounded up to 64,
 // zero where there is no edge.  One wavefront per (row, graph): clears the row, then fills it.
-__global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepList list, int g0, float* out) {
+__global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, const MgkSepGraph* used, float* out) {
     __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
     for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
-    const MgkGraphDesc g = B.graphs[g0 + blockIdx.y];
+    const MgkSepGraph sg = used[blockIdx.y];
+    const MgkGraphDesc g = B.graphs[sg.graph];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int np = (g.n + 63) & ~63;
-    float* F = out + list.dense_off[g0 + blockIdx.y] * S.rank;
+    float* F = out + sg.at;
     for (int row = blockIdx.x * 4 + wave; row < np; row += gridDim.x * 4) {
         for (int k = 0; k < S.rank; ++k)
             for (int c = lane; c < np; c += 64) F[((int64_t)k * np + row) * np + c] = 0.f;
@@ -158,14 +160,14 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
         for (int ii = wave; ii < rows; ii += NW) {
             const int grp = (i0 + ii) >> 2;
             const int gb = gp1[grp];
-            const float* pk = SX.packets + ((int64_t)q * SX.total + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
+            const float* pk = SX.packets + ((int64_t)q * SX.total + P.f1 + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
             stage1_row<RK, G>(pk, gp1[grp + 1] - gb, PGlobal{reinterpret_cast<const char*>(p), (uint32_t)n2 * 4u}, n2, lane,
                               slabs, (RK == 1 ? 4u : 16u) * (uint32_t)ii);
         }
         __syncthreads();
         // ---- stage 2: 16 rows x 4 columns per task; the packets of the next task are in
         //      flight during this one
-        const float* pk2 = SY.packets + (int64_t)q * SY.total * 64 + lane;
+        const float* pk2 = SY.packets + ((int64_t)q * SY.total + P.f2) * 64 + lane;
         const uint32_t lbase = (RK == 1 ? 4u : 16u) * (uint32_t)(lane & 15);
         float cn[8];
         int gb = gp2[min(wave, groups2 - 1)], steps = gp2[min(wave, groups2 - 1) + 1] - gb;
@@ -240,8 +242,8 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
     if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
     const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
-    const float* F1 = SX.dense + SX.dense_off[P.g1] * rank + i0;
-    const float* F2 = SY.dense + SY.dense_off[P.g2] * rank;
+    const float* F1 = SX.dense + P.f1 + i0;
+    const float* F2 = SY.dense + P.f2;
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = vec + P.vec + 4 * (int64_t)P.npad;
     const int tp = np2 + 1;
@@ -376,22 +378,22 @@ hipError_t set_lds(const void* kern, bool* configured) {
 
 }  // namespace
 
+// the graph index is a grid dimension of at most 65535: more graphs go in parts
 hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L, const MgkSepList& list,
-                               int max_n, float* packets, hipStream_t stream) {
-    // the graph index is a grid dimension of at most 65535: batches of more graphs go in parts
+                               const MgkSepGraph* used, int n_used, int max_n, float* packets, hipStream_t stream) {
     const int gx = (max_n + 15) / 16;
-    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535)
-        hipLaunchKernelGGL(mgk_sep_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
-                           stream, B, S, L, list, g0, packets);
+    for (int g0 = 0; g0 < n_used; g0 += 65535)
+        hipLaunchKernelGGL(mgk_sep_pack_kernel, dim3(gx, n_used - g0 < 65535 ? n_used - g0 : 65535), dim3(256), 0,
+                           stream, B, S, L, list, used + g0, packets);
     return hipGetLastError();
 }
 
-hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepList& list, int max_n, float* F,
-                                     hipStream_t stream) {
+hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph* used, int n_used, int max_n,
+                                     float* F, hipStream_t stream) {
     const int gx = (max_n + 63) / 16;
-    for (int g0 = 0; g0 < B.n_graphs; g0 += 65535)
-        hipLaunchKernelGGL(mgk_sep_dense_pack_kernel, dim3(gx, B.n_graphs - g0 < 65535 ? B.n_graphs - g0 : 65535), dim3(256), 0,
-                           stream, B, S, list, g0, F);
+    for (int g0 = 0; g0 < n_used; g0 += 65535)
+        hipLaunchKernelGGL(mgk_sep_dense_pack_kernel, dim3(gx, n_used - g0 < 65535 ? n_used - g0 : 65535), dim3(256), 0,
+                           stream, B, S, used + g0, F);
     return hipGetLastError();
 }
 

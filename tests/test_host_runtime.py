@@ -175,3 +175,15 @@ def test_refused_calls_leave_a_recording_as_it_was(host):
         assert "recorded" in host.log()
     for call in calls:
         assert call() == 0, host.error()
+
+
+@pytest.mark.parametrize("k,kernel", [(6, "sep"), (75, "sep dense")])
+def test_features_are_formed_for_the_graphs_of_the_pairs(host, k, kernel):
+    """Not for the rest of the batch, however large it is."""
+    B = host.load(graphs(*[ring(151, k)] * 9))
+    in_use = host.lib.stub_in_use()
+    assert host.pairs(B, B, [2, 2, 7], [7, 2, 4]) == 0, host.error()
+    assert launched(host.log(), kernel) and launched(host.log(), kernel + " pack") == [3]
+    one = 192 * 192 * 4 if kernel == "sep dense" else 151 * k * 256   # a 192 x 192 matrix; a step of 64 words to two nonzeros of four rows
+    assert host.lib.stub_in_use() - in_use < 3 * one + 5 * 3 * 4 * 151 * 151 + (1 << 20)
+    host.free(B)
