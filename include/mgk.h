@@ -34,9 +34,14 @@
  *    stream before returning (iterations are enqueued without waiting, as many
  *    as the previous such call needed; then the host reads how many pairs still
  *    iterate, normally once per call)
- *    and allocate device scratch owned by the ctx (5 vectors of n n' floats per
- *    such pair, plus expanded nonzero lists of the batches).  Such pairs are
- *    solved in groups of at most 4096 pairs and 8 GiB of vectors.
+ *    and allocate device scratch owned by the ctx: 5 vectors of n n' floats per
+ *    such pair, plus expanded nonzero lists of the batches or, where the edge
+ *    kernel is used in its separable form, features of the graphs of the pairs
+ *    (up to 128 bytes per nonzero and four terms, or one n x n matrix per term).
+ *    Such pairs are solved in groups of at most 4096 pairs, 8 GiB of vectors and
+ *    8 GiB of features.  Between calls at most 1 GiB of features of one kind and
+ *    side is kept; where memory for features is short the pairs are solved
+ *    without them.
  *  - Non-convergence is data, not an error: the pair's flag is set to 1 and the
  *    value of the last iterate is still written.  Flag 2 with a NaN value marks
  *    a pair that a kernel refused because it did not fit the launch shape the

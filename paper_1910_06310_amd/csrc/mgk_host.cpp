@@ -252,6 +252,7 @@ struct mgk_ctx {
     DevBuf dense_tiles[2][3];           // dense 8x8 expansions (weight, label, log2 weight)
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
+    bool features_in_use = false;       // by the call under way
     MgkSepBasis sep_basis{};            // of the last label range and edge kernel, see sep_basis_for
     float sep_lo = 0.f, sep_hi = -1.f, sep_param = 0.f;
     int sep_kernel = -1;
@@ -712,6 +713,7 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
 
 mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::Slot** out);
 mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream);
+hipError_t device_alloc(mgk_ctx* ctx, void** p, size_t bytes);
 constexpr size_t kMaxStagedBytes = (size_t)4 << 20;
 
 // Launch shapes largest first, inside a shape the expensive pairs first (in 256 steps of
@@ -761,7 +763,7 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
         if (out.dev) MGK_HIP(ctx, hipFree(out.dev));
         out.dev = nullptr;
         const int64_t cap = std::max<int64_t>(out.n, 1);
-        MGK_HIP(ctx, hipMalloc((void**)&out.dev, (size_t)cap * sizeof(MgkJob)));
+        MGK_HIP(ctx, device_alloc(ctx, (void**)&out.dev, (size_t)cap * sizeof(MgkJob)));
         if (capacity) *capacity = cap;
     }
     if (out.n == 0) return MGK_OK;
@@ -791,12 +793,40 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
     return MGK_OK;
 }
 
+// Gives back what the context keeps for later calls: features and blocks of freed batches.
+bool release_spare(mgk_ctx* ctx) {
+    bool any = false;
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1]})
+        if (b->p && !ctx->features_in_use) {
+            (void)hipFree(b->p);   // waits for the work that reads it
+            *b = DevBuf{};
+            any = true;
+        }
+    std::vector<FreeBlob> blobs;
+    {
+        std::lock_guard<std::mutex> lock(ctx->memory->m);
+        blobs.swap(ctx->memory->blobs);
+    }
+    for (FreeBlob& f : blobs) (void)hipFree(f.p);
+    return any || !blobs.empty();
+}
+
+// hipMalloc; where memory has run out, again without what the context keeps for later calls.
+hipError_t device_alloc(mgk_ctx* ctx, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // no error of a later launch
+        if (release_spare(ctx) && (e = hipMalloc(p, bytes)) != hipSuccess) (void)hipGetLastError();
+    }
+    return e;
+}
+
 mgk_status ensure(mgk_ctx* ctx, DevBuf& b, size_t bytes) {
     if (bytes <= b.cap) return MGK_OK;
     if (b.p) MGK_HIP(ctx, hipFree(b.p));
     b.p = nullptr;
     b.cap = 0;
-    hipError_t e = hipMalloc(&b.p, bytes);
+    hipError_t e = device_alloc(ctx, &b.p, bytes);
     if (e != hipSuccess)
         return fail(ctx, MGK_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
     b.cap = bytes;
@@ -942,6 +972,7 @@ MgkSepLayout sep_layout(int rank, int n2) {
 
 // Product of the global-memory solver for one pair.
 enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
+bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
 // run.  Fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01 to 1, ranks 1
@@ -1077,9 +1108,10 @@ mgk_status take_blob(mgk_ctx* ctx, size_t bytes, void** p, size_t* cap) {
         return MGK_OK;
     }
     lock.unlock();
-    const size_t want = bytes <= kMaxBlobBytes ? (bytes + bytes / 4 + 65535) & ~(size_t)65535 : bytes;
-    MGK_HIP(ctx, hipMalloc(p, want));
-    *cap = want;
+    *cap = bytes <= kMaxBlobBytes ? (bytes + bytes / 4 + 65535) & ~(size_t)65535 : bytes;   // room for others, later
+    if (*cap > bytes && device_alloc(ctx, p, *cap) == hipSuccess) return MGK_OK;
+    *cap = bytes;
+    MGK_HIP(ctx, device_alloc(ctx, p, bytes));
     return MGK_OK;
 }
 
@@ -1280,6 +1312,11 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
     if ((st = ensure(ctx, ctx->lpairs, rec_bytes)) != MGK_OK) return st;
     if (!ctx->active_host) MGK_HIP(ctx, hipHostMalloc((void**)&ctx->active_host, 64, hipHostMallocDefault));
+    struct InUse {
+        bool& flag;
+        ~InUse() { flag = false; }
+    } in_use{ctx->features_in_use};
+    ctx->features_in_use = true;
     MgkSepList sl[2] = {};
     for (int k = 0; k < sides; ++k) {
         sl[k] = bt[k]->sep[gi];
@@ -1385,34 +1422,38 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     const MgkSepBasis none{};
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
     const MgkSepBasis& S = may_sep ? sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi)) : none;
-    struct Oriented { MgkLargePair pair; int swapped; };
-    std::vector<Oriented> sep_form;   // the pair as the separable product takes it
+    struct Choice {
+        MgkLargePair asked, sep;   // the pair as the direct product takes it, and the separable one
+        int swapped, sep_swapped;
+    };
+    std::vector<Choice> choices;
     std::vector<LargeCost> costs;
-    sep_form.reserve(jl.large[0].size() + jl.large[1].size());
-    costs.reserve(sep_form.capacity());
+    choices.reserve(jl.large[0].size() + jl.large[1].size());
+    costs.reserve(choices.capacity());
     for (int swapped = 0; swapped < 2; ++swapped)
         for (const MgkLargePair& asked : jl.large[swapped]) {
-            Oriented f{asked, swapped};
-            MgkLargePair& P = f.pair;
+            Choice c{asked, asked, swapped, swapped};
+            MgkLargePair& P = c.sep;
             if (S.rank > 0 && P.n2 > P.n1) {   // separable product: T has a column per inner vertex
                 std::swap(P.g1, P.g2);
                 std::swap(P.n1, P.n2);
                 if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
-                if (X != Y) f.swapped = 1 - swapped;
+                if (X != Y) c.sep_swapped = 1 - swapped;
             }
-            costs.push_back(large_cost(ctx, S, f.swapped ? Y : X, P.g1, f.swapped ? X : Y, P.g2));
-            sep_form.push_back(f);
+            costs.push_back(large_cost(ctx, S, c.sep_swapped ? Y : X, P.g1, c.sep_swapped ? X : Y, P.g2));
+            choices.push_back(c);
         }
     merge_paths(costs);
-    std::vector<MgkLargePair> lists[2][kPaths];
-    size_t at = 0;
-    for (int swapped = 0; swapped < 2; ++swapped)
-        for (const MgkLargePair& asked : jl.large[swapped]) {
-            const int path = costs[at].best;
-            const Oriented& f = sep_form[at++];
-            if (path == kPathSep || path == kPathSepDense) lists[f.swapped][path].push_back(f.pair);
-            else lists[swapped][path].push_back(asked);
-        }
+    std::vector<const Choice*> lists[2][kPaths];
+    for (size_t k = 0; k < choices.size(); ++k) {
+        const Choice& c = choices[k];
+        const int path = costs[k].best;
+        lists[is_sep(path) ? c.sep_swapped : c.swapped][path].push_back(&c);
+    }
+    auto direct = [&](const std::vector<MgkLargePair>& pairs, int swapped, bool dense) {
+        return swapped ? solve_large(ctx, Y, X, 1, 0, pairs, dense, out, stream, prm, weighted)
+                       : solve_large(ctx, X, Y, 0, 1, pairs, dense, out, stream, prm, weighted);
+    };
     // In groups: the pair index is a grid dimension (at most 65535) and every pair of a group
     // holds 5 vectors of scratch at the same time.  The separable products put pairs and blocks of
     // outer rows into one dimension, as many blocks for every pair as the largest one has.
@@ -1425,34 +1466,54 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                 return path == kPathSep ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS) * MGK_SEP_THREADS
                      : path == kPathSepDense ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS) * MGK_SEP_DENSE_THREADS : 0;
             };
-            std::vector<MgkLargePair>& all = lists[swapped][path];
+            const std::vector<const Choice*>& all = lists[swapped][path];
+            auto pair = [&](size_t k) -> const MgkLargePair& { return is_sep(path) ? all[k]->sep : all[k]->asked; };
             const mgk_batch* A = swapped ? Y : X;
             const mgk_batch* B = swapped ? X : Y;
             size_t first = 0;
             while (first < all.size()) {
+                std::vector<MgkLargePair> group;
                 size_t last = first;
                 int64_t floats = 0, features = 0;
                 int max_n1 = 1, max_n2 = 1;
-                auto bytes = [&](const MgkLargePair& P) {   // of its features; graphs that pairs share are counted for each
-                    return path != kPathSep && path != kPathSepDense ? 0
-                        : feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
-                };
-                while (last < all.size() && last - first < kMaxPairsPerGroup &&
-                       (last == first || (floats + 5 * (int64_t)all[last].npad <= kMaxScratchFloats && features + bytes(all[last]) <= kMaxFeatureBytes &&
-                                          grid_threads((int64_t)(last - first) + 1, std::max(max_n1, all[last].n1)) < kMaxGridThreads))) {
-                    floats += 5 * (int64_t)all[last].npad;
-                    features += bytes(all[last]);
-                    max_n1 = std::max(max_n1, all[last].n1);
-                    max_n2 = std::max(max_n2, all[last].n2);
-                    ++last;
+                for (; last < all.size() && last - first < kMaxPairsPerGroup; ++last) {
+                    const MgkLargePair& P = pair(last);
+                    floats += 5 * (int64_t)P.npad;
+                    if (is_sep(path))   // graphs that pairs share are counted for each
+                        features += feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
+                    max_n1 = std::max(max_n1, P.n1);
+                    if (last > first && (floats > kMaxScratchFloats || features > kMaxFeatureBytes ||
+                                         grid_threads((int64_t)(last - first) + 1, max_n1) >= kMaxGridThreads))
+                        break;
+                    max_n2 = std::max(max_n2, P.n2);
+                    group.push_back(P);
                 }
-                std::vector<MgkLargePair> group(all.begin() + (std::ptrdiff_t)first, all.begin() + (std::ptrdiff_t)last);
-                const mgk_status st = path == kPathSep || path == kPathSepDense
-                    ? solve_sep(ctx, A, B, std::move(group), path == kPathSepDense, S, sep_layout(S.rank, max_n2), out, stream, prm)
-                    : solve_large(ctx, A, B, swapped, 1 - swapped, std::move(group), path == kPathDenseTiles, out, stream, prm, weighted);
+                mgk_status st;
+                if (is_sep(path)) {
+                    st = solve_sep(ctx, A, B, std::move(group), path == kPathSepDense, S, sep_layout(S.rank, max_n2), out, stream, prm);
+                    if (st == MGK_ENOMEM) {   // the direct product needs less
+                        std::vector<MgkLargePair> again[2][2];
+                        for (size_t k = first; k < last; ++k) {
+                            const MgkLargePair& P = all[k]->asked;
+                            const bool s = all[k]->swapped != 0;
+                            again[s][use_dense_tiles(ctx, (s ? Y : X)->graphs[P.g1], (s ? X : Y)->graphs[P.g2])].push_back(P);
+                        }
+                        st = MGK_OK;
+                        for (int s = 0; s < 2; ++s)
+                            for (int d = 0; d < 2 && st == MGK_OK; ++d) st = direct(again[s][d], s, d != 0);
+                    }
+                } else {
+                    st = direct(group, swapped, path == kPathDenseTiles);
+                }
                 if (st != MGK_OK) return st;
                 first = last;
             }
+        }
+    constexpr size_t kKeptFeatureBytes = (size_t)1 << 30;   // of each buffer; forming more takes longer than allocating it
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1]})
+        if (b->cap > kKeptFeatureBytes) {
+            (void)hipFree(b->p);
+            *b = DevBuf{};
         }
     return MGK_OK;
 }

@@ -187,3 +187,53 @@ def test_features_are_formed_for_the_graphs_of_the_pairs(host, k, kernel):
     one = 192 * 192 * 4 if kernel == "sep dense" else 151 * k * 256   # a 192 x 192 matrix; a step of 64 words to two nonzeros of four rows
     assert host.lib.stub_in_use() - in_use < 3 * one + 5 * 3 * 4 * 151 * 151 + (1 << 20)
     host.free(B)
+
+
+def test_pairs_are_solved_without_features_where_memory_is_short(host):
+    """Features of the separable product are an addition to what the direct product needs: neither forming
+    them nor keeping them may make a call fail that the direct product can do."""
+    labels = np.linspace(0, 1, 151 * 75)
+    host.set("edge_kernel_se", 0.3)   # a high rank
+    X, Y = host.load(graphs(ring(151, 75, labels))), host.load(graphs(ring(140, 69, labels[:140 * 69])))
+    before, small = host.lib.stub_in_use(), 2 << 20
+    try:
+        host.lib.stub_set_limit(C.c_int64(before + small))
+        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert launched(host.log(), "direct dense") and not launched(host.log(), "sep dense")
+        host.lib.stub_set_limit(C.c_int64(-1))
+        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert launched(host.log(), "sep dense") and host.lib.stub_in_use() > before + small
+        # what the context keeps is given back for the lists of the direct product, and for a batch
+        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use() + 65536))
+        host.set("tile_path", 1)
+        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        host.set("tile_path", 0)
+        host.lib.stub_set_limit(C.c_int64(-1))
+        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use() + 65536))
+        host.free(host.load(graphs(ring(151, 75, labels))))
+        assert host.violations() == ""
+    finally:
+        host.lib.stub_set_limit(C.c_int64(-1))
+
+
+def test_a_freed_batch_is_no_reason_to_run_out_of_memory(so):
+    """A block that is kept is given back for a batch that it is too small for."""
+    one = W.config1(200)
+    nine = W.concat_batches([one] * 9, one.params, "nine")
+    need = []
+    for wb in (one, nine):   # of a batch whose block is not kept
+        h = host_runtime.Host(so)
+        empty = h.lib.stub_in_use()
+        B = h.load(wb)
+        need.append(h.lib.stub_in_use() - empty)
+        h.free(B)
+        h.destroy()
+    h = host_runtime.Host(so)
+    h.free(h.load(one))
+    try:
+        h.lib.stub_set_limit(C.c_int64(empty + need[1] - need[1] // 8))   # blocks are a quarter larger than asked for
+        h.free(h.load(nine))
+    finally:
+        h.lib.stub_set_limit(C.c_int64(-1))
+        h.destroy()
