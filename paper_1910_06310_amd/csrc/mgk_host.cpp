@@ -1264,7 +1264,8 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
 // Alg. 1 with global-memory vectors and the separable product (mgk_sep.hip) for a list of pairs
 // (outer graphs from A, inner from Bb).  Three launches per iteration (product with p^T a, update,
 // new direction); the outputs are formed behind the iterations the last such call needed, before
-// the host looks whether any pair still iterates, so that the GPU does not wait for that.
+// the host looks whether any pair still iterates, so that the GPU does not wait for that.  If any does,
+// they are formed once more when none does.
 mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, bool dense,
                      const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, const MgkParams& prm) {
     const int n_pairs = (int)pairs.size();
@@ -1360,19 +1361,25 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     int it = 0;
     const int first_batch = std::max(1, std::min(max_iter, ctx->large_iter_guess));
     ctx->active_host[0] = n_pairs;
+    auto outputs = [&] {
+        hipError_t f = mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 0, stream);
+        if (f == hipSuccess) f = product(0, true);
+        return f != hipSuccess ? f : mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 1, stream);
+    };
     while (it < max_iter && ctx->active_host[0] > 0) {
-        const int upto = it == 0 ? first_batch : std::min(max_iter, it + 4);
+        const bool foreseen = it == 0;
+        const int upto = foreseen ? first_batch : std::min(max_iter, it + 4);
         for (; it < upto; ++it) {
             if ((e = product(it, false)) == hipSuccess)
                 e = mgk_launch_large_vectors(dpairs, dstate, vec, n_pairs, vec_blocks, it, prm.rtol2, dactive, stream);
             if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "iteration launch failed: %s", hipGetErrorString(e));
         }
-        e = mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 0, stream);
-        if (e == hipSuccess) e = product(0, true);
-        if (e == hipSuccess)
-            e = mgk_launch_large_outputs(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, out, 1, stream);
-        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
+        if (foreseen && (e = outputs()) != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
         MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
+        MGK_HIP(ctx, hipStreamSynchronize(stream));
+    }
+    if (it > first_batch) {   // more iterations than foreseen
+        if ((e = outputs()) != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
     }
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);

@@ -94,6 +94,7 @@ void stub_reset() {
     limit = SIZE_MAX;
     converge_after = 3;
 }
+void stub_clear_log() { log_text.clear(); }
 const char* stub_log() { return log_text.c_str(); }
 int stub_count(const char* what) { return counts[what]; }
 const char* stub_violations() {

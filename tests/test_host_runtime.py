@@ -237,3 +237,15 @@ def test_a_freed_batch_is_no_reason_to_run_out_of_memory(so):
     finally:
         h.lib.stub_set_limit(C.c_int64(-1))
         h.destroy()
+
+
+def test_outputs_are_formed_twice_at_most(host):
+    """Once behind the iterations foreseen, and once more if pairs still iterate then, however long."""
+    B = host.load(graphs(ring(151, 6), ring(140, 6)))
+    host.lib.stub_converge_after(90)   # the first call of a context foresees fewer
+    for foreseen in (False, True):
+        host.lib.stub_clear_log()
+        assert host.pairs(B, B, [0], [1]) == 0, host.error()
+        assert len(launched(host.log(), "vectors")) >= 90
+        assert len(launched(host.log(), "outputs")) == (2 if foreseen else 4)   # two launches each
+    host.free(B)
