@@ -975,13 +975,20 @@ enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kP
 bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
-// run.  Fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01 to 1, ranks 1
-// to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages the rows of
-// p and pays 6 clk per element in dependent loads; the sparse separable product does 20 multiply-adds
-// per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
-// from 256 columns on.  Measured, us per call of 64 pairs, row-staged / sparse / dense: n = 256 density
-// 0.01 2205 / 2162 / 9989 (rank 8: 1990 / 2288 / 13732), 0.02 1905 / 1509 / 6065, 0.2 13896 / 1657 / 2979,
-// 0.45 52148 / 2865 / 3065; n = 128 density 0.014 1224 / 1210 / 4751, 0.03 980 / 817 / 2824.
+// run.  Two bounds, the larger counts.  Throughput of a full chip, fitted to iterations of 64 pairs of random
+// graphs (n = 128 to 256, densities 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product
+// evaluates 7 entries per clk, stages the rows of p and pays 6 clk per element in dependent loads; the sparse
+// separable product does 20 multiply-adds per clk and writes and reads T; the dense one does 42 per clk and has
+// work for all four of its wavefronts from 256 columns on.  And the time of one workgroup, in which all others
+// of the call can run where it has few pairs: a row of the outer graph (row-staged; 1.2 times its share of the
+// work, or 3200 clk per nonzero of the row in dependent loads, and then the throughput bound on top), 16 rows
+// (sparse; 10 000 clk and 0.9 times its share), 32 rows (dense, alone on its compute unit 60 multiply-adds per
+// clk).  Measured, us per call, row-staged / sparse / dense, rank 5: 1 pair of n = 256 density 0.01
+// 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs 2090 / 1842 / 7344,
+// 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  n = 480 density 0.03, 1, 2, 16 pairs:
+// 478 / 530, 629 / 557, 2488 / 1122.  n = 600 density 0.1, 1, 2, 4, 16 pairs, row-staged / dense: 2515 / 5206,
+// 4112 / 5264, 7394 / 5294, 26957 / 10472; n = 1000 density 0.05: 4592 / 11290, 8246 / 11366, 15217 / 11569,
+// 56425 / 25971.
 struct LargeCost {
     double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
@@ -994,22 +1001,33 @@ int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
     return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
 }
 
-// Forming the features is left out: only the graphs of the pairs get them, which takes 1 % of what the
-// products of a pair take.
-LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb) {
+// n_pairs: pairs of the call that may run beside this one.  Forming the features is left out: only the
+// graphs of the pairs get them, which takes 1 % of what the products of a pair take.
+LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb,
+                     int64_t n_pairs) {
+    constexpr double kComputeUnits = 256;
     const MgkGraphDesc &o = A->graphs[(size_t)ga], &i = B->graphs[(size_t)gb];
     auto fits = [&](bool dense) { return feature_bytes(A, ga, S.rank, dense) + feature_bytes(B, gb, S.rank, dense) <= kMaxFeatureBytes; };
     LargeCost C;
     C.best = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
+    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) {
+        C.clk[C.best] = 0.0;   // no choice
+        return C;
+    }
+    const double alone = kComputeUnits / (double)n_pairs;   // compute units a pair has to itself
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
-    C.clk[C.best] = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n + 6.0 * N;
-    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) return C;
+    const double entries = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n;
+    C.clk[C.best] = entries + 6.0 * N + alone * std::max(1.2 * entries, 3200.0 * o.nnz) / o.n;
     const MgkSepLayout L = sep_layout(S.rank, i.n);
-    if (L.rk > 0 && fits(false)) C.clk[kPathSep] = (double)L.rk * L.passes * one_sided / 20.0 + 8.0 * N;
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255;
-    if (ip <= MGK_SEP_DENSE_MAX_N && fits(true)) C.clk[kPathSepDense] = S.rank * op * ip * ((double)o.n + i.n) / 42.0;
-    for (int path : {kPathSep, kPathSepDense})
-        if (C.clk[path] < C.clk[C.best]) C.best = path;
+    const double sparse = (double)L.rk * L.passes * one_sided / 20.0, dense = S.rank * op * ip * ((double)o.n + i.n);
+    const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
+    if (may_sparse) C.clk[kPathSep] = std::max(sparse + 8.0 * N, alone * (10000.0 + 0.9 * sparse / ((o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS)));
+    if (may_dense) C.clk[kPathSepDense] = std::max(dense / 42.0, alone * dense / 60.0 / (op / MGK_SEP_DENSE_ROWS));
+    if (!may_sparse && !may_dense) return C;
+    // of the two forms the one with the higher throughput
+    const int form = may_dense && (!may_sparse || dense / 42.0 < sparse + 8.0 * N) ? kPathSepDense : kPathSep;
+    if (C.clk[form] < C.clk[C.best]) C.best = form;
     return C;
 }
 
@@ -1447,7 +1465,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                 if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
                 if (X != Y) c.sep_swapped = 1 - swapped;
             }
-            costs.push_back(large_cost(ctx, S, c.sep_swapped ? Y : X, P.g1, c.sep_swapped ? X : Y, P.g2));
+            costs.push_back(large_cost(ctx, S, c.sep_swapped ? Y : X, P.g1, c.sep_swapped ? X : Y, P.g2, (int64_t)choices.capacity()));
             choices.push_back(c);
         }
     merge_paths(costs);

@@ -182,10 +182,10 @@ def test_features_are_formed_for_the_graphs_of_the_pairs(host, k, kernel):
     """Not for the rest of the batch, however large it is."""
     B = host.load(graphs(*[ring(151, k)] * 9))
     in_use = host.lib.stub_in_use()
-    assert host.pairs(B, B, [2, 2, 7], [7, 2, 4]) == 0, host.error()
+    assert host.pairs(B, B, [2, 2, 7] * 20, [7, 2, 4] * 20) == 0, host.error()
     assert launched(host.log(), kernel) and launched(host.log(), kernel + " pack") == [3]
     one = 192 * 192 * 4 if kernel == "sep dense" else 151 * k * 256   # a 192 x 192 matrix; a step of 64 words to two nonzeros of four rows
-    assert host.lib.stub_in_use() - in_use < 3 * one + 5 * 3 * 4 * 151 * 151 + (1 << 20)
+    assert host.lib.stub_in_use() - in_use < 3 * one + 60 * 5 * 4 * (151 * 151 + 63) + (1 << 20)
     host.free(B)
 
 
@@ -195,21 +195,22 @@ def test_pairs_are_solved_without_features_where_memory_is_short(host):
     labels = np.linspace(0, 1, 151 * 75)
     host.set("edge_kernel_se", 0.3)   # a high rank
     X, Y = host.load(graphs(ring(151, 75, labels))), host.load(graphs(ring(140, 69, labels[:140 * 69])))
-    before, small = host.lib.stub_in_use(), 2 << 20
+    pairs = [0] * 64
+    before, small = host.lib.stub_in_use(), 64 * 5 * 4 * 151 * 140 + (2 << 20)   # the vectors, and room for the lists of the direct product
     try:
         host.lib.stub_set_limit(C.c_int64(before + small))
-        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert host.pairs(X, Y, pairs, pairs) == 0, host.error()
         assert launched(host.log(), "direct dense") and not launched(host.log(), "sep dense")
         host.lib.stub_set_limit(C.c_int64(-1))
-        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert host.pairs(X, Y, pairs, pairs) == 0, host.error()
         assert launched(host.log(), "sep dense") and host.lib.stub_in_use() > before + small
         # what the context keeps is given back for the lists of the direct product, and for a batch
         host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use() + 65536))
         host.set("tile_path", 1)
-        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert host.pairs(X, Y, pairs, pairs) == 0, host.error()
         host.set("tile_path", 0)
         host.lib.stub_set_limit(C.c_int64(-1))
-        assert host.pairs(X, Y, [0], [0]) == 0, host.error()
+        assert host.pairs(X, Y, pairs, pairs) == 0, host.error()
         host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use() + 65536))
         host.free(host.load(graphs(ring(151, 75, labels))))
         assert host.violations() == ""
@@ -248,4 +249,16 @@ def test_outputs_are_formed_twice_at_most(host):
         assert host.pairs(B, B, [0], [1]) == 0, host.error()
         assert len(launched(host.log(), "vectors")) >= 90
         assert len(launched(host.log(), "outputs")) == (2 if foreseen else 4)   # two launches each
+    host.free(B)
+
+
+@pytest.mark.parametrize("n,k,pairs,kernel", [(600, 30, 1, "direct dense"), (600, 30, 16, "sep dense"), (256, 26, 1, "sep"),
+                                              (480, 7, 1, "direct rows"), (480, 7, 16, "sep")])
+def test_few_pairs_take_the_product_that_fills_the_chip(host, n, k, pairs, kernel):
+    """One pair of 600 vertices has 19 workgroups in the dense separable product and 600 in the row-staged one:
+    5.2 ms and 2.5 ms per call; with 16 pairs 10.5 and 27 ms."""
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(ring(n, k, np.linspace(0, 1, n * k))))
+    assert host.pairs(B, B, [0] * pairs, [0] * pairs) == 0, host.error()
+    assert launched(host.log(), kernel), host.log()
     host.free(B)
