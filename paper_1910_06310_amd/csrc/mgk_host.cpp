@@ -56,15 +56,20 @@ struct DevBuf {
     size_t cap = 0;
 };
 
-// Pinned host memory for what a call copies to the device without waiting: two slots in turn,
-// each reused once the copies out of it have been made.
+// Pinned host memory for what a call copies to the device without waiting: slots in turn, each used
+// again when the call that copied out of it has completed.  All start in one block, allocated with the context.
+struct CallEnd;
+constexpr size_t kSlotBytes = (size_t)128 << 10;
 struct Staging {
     struct Slot {
         void* p = nullptr;
         size_t cap = 0;
-        hipEvent_t event = nullptr;   // recorded after the last copy out of the slot
-        bool busy = false;
-    } slot[2];
+        bool own = false;                // an allocation of its own, not part of the block
+        bool open = false;               // copied from by a call whose end is not recorded (yet)
+        hipStream_t stream = nullptr;    // of that call
+        std::shared_ptr<CallEnd> end;    // of the last call
+    } slot[4];
+    void* block = nullptr;
     int next = 0;
 };
 
@@ -72,7 +77,6 @@ struct Staging {
 // kMaxBlobBytes).  A block is handed out again when the calls that read its batch have completed.
 constexpr size_t kMaxBlobs = 4, kMaxBlobBytes = (size_t)16 << 20;
 constexpr size_t kMaxReads = 8;    // calls under way that a batch keeps track of
-struct CallEnd;
 struct FreeBlob {
     void* p = nullptr;
     size_t cap = 0;
@@ -103,11 +107,13 @@ struct CallEnd {
         }
         (void)hipEventDestroy(event);
     }
-    bool over() const {
-        if (hipEventQuery(event) == hipSuccess) return true;
-        (void)hipGetLastError();   // "not ready" is no error of a later launch
-        return false;
+    bool over() {
+        if (seen_over) return true;
+        seen_over = hipEventQuery(event) == hipSuccess;
+        if (!seen_over) (void)hipGetLastError();   // "not ready" is no error of a later launch
+        return seen_over;
     }
+    bool seen_over = false;
 };
 
 // Threads of a context for the host work of a call.  run(n, f, helpers) calls f(0) .. f(n - 1), on
@@ -398,14 +404,16 @@ mgk_status refuse_capture(mgk_ctx* ctx, hipStream_t stream) {
     return fail(ctx, MGK_EDEVICE, "operation not permitted when stream is capturing");
 }
 
-// What a call reads.  done() records the end of the call; a batch of a call that fails on the way, that is
-// part of a recorded graph, or that has too many calls under way, is waited for with the whole device.
+// What a call reads.  done() records its end, one event a call (4 us; a second one, behind the copies of the
+// lists, took as long again); a batch of a call that fails on the way, that is part of a recorded graph, or
+// that has too many calls under way, is waited for with the whole device.
 class BatchReads {
 public:
     BatchReads(mgk_batch* X, mgk_batch* Y) : b_{X, Y}, was_{X->untracked, Y->untracked} { X->untracked = Y->untracked = true; }
     // may_create: else the event is one that an earlier call has left
-    void done(hipStream_t stream, bool may_create) {
-        if (was_[0] && was_[1]) return;   // a resident batch with many calls under way: 4 us a call saved
+    void done(Staging& staging, hipStream_t stream, bool may_create) {
+        const bool staged = std::any_of(std::begin(staging.slot), std::end(staging.slot), [](const Staging::Slot& s) { return s.open; });
+        if (was_[0] && was_[1] && !staged) return;
         try {
             auto end = std::make_shared<CallEnd>();
             end->memory = b_[0]->memory;
@@ -420,6 +428,11 @@ public:
             }
             if (!end->event && (!may_create || hipEventCreateWithFlags(&end->event, hipEventDisableTiming) != hipSuccess)) return;
             if (hipEventRecord(end->event, stream) != hipSuccess) { (void)hipGetLastError(); return; }
+            for (Staging::Slot& s : staging.slot)
+                if (s.open && s.stream == stream) {
+                    s.open = false;
+                    s.end = end;
+                }
             for (int k = 0; k < (b_[0] == b_[1] ? 1 : 2); ++k)
                 if (b_[k]->reads.size() < kMaxReads) {
                     b_[k]->reads.push_back(end);
@@ -711,8 +724,8 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
     return into;
 }
 
-mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::Slot** out);
-mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream);
+mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, hipStream_t stream, Staging::Slot** out);
+void staging_copied(Staging::Slot* slot, hipStream_t stream);
 hipError_t device_alloc(mgk_ctx* ctx, void** p, size_t bytes);
 constexpr size_t kMaxStagedBytes = (size_t)4 << 20;
 
@@ -783,13 +796,13 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
     const size_t bytes = (size_t)out.n * sizeof(MgkJob);
     Staging::Slot* slot = nullptr;
     if (bytes <= kMaxStagedBytes && capacity)   // lists kept with a batch are made once
-        if (mgk_status st = staging_slot(ctx, bytes, !fixed, &slot)) return st;
+        if (mgk_status st = staging_slot(ctx, bytes, !fixed, stream, &slot)) return st;
     std::vector<MgkJob> pageable(slot ? 0 : plan.jobs.size());
     MgkJob* flat = slot ? static_cast<MgkJob*>(slot->p) : pageable.data();
     for (size_t k = 0; k < plan.jobs.size(); ++k) flat[at[(size_t)where[k]]++] = plan.jobs[k].job;
     MGK_HIP(ctx, hipMemcpyAsync(out.dev, flat, bytes, hipMemcpyHostToDevice, stream));
-    if (slot) return staging_done(ctx, slot, stream);
-    MGK_HIP(ctx, hipStreamSynchronize(stream));  // `pageable` dies here
+    if (slot) staging_copied(slot, stream);
+    else MGK_HIP(ctx, hipStreamSynchronize(stream));  // `pageable` dies here
     return MGK_OK;
 }
 
@@ -1080,23 +1093,35 @@ MgkLargePair plan_large(const MgkGraphDesc& a, const MgkGraphDesc& b, int32_t ia
     return P;
 }
 
-// The next slot of pinned memory, of at least `bytes`; waits for the copies of its last use (long
-// made).  Without may_allocate a slot that is too small leaves *out null.
-mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::Slot** out) {
-    Staging::Slot& s = ctx->staging.slot[ctx->staging.next];
+// A slot of pinned memory, of at least `bytes`, for copies on `stream`: the next one that is large enough
+// and not in use, else the next one, waited for and grown.  Without may_allocate *out is null where that
+// would allocate.
+mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, hipStream_t stream, Staging::Slot** out) {
+    Staging& S = ctx->staging;
+    constexpr int kSlots = sizeof(S.slot) / sizeof(S.slot[0]);
     *out = nullptr;
-    if (bytes > s.cap && !may_allocate) return MGK_OK;
-    ctx->staging.next ^= 1;
-    if (s.busy) {
-        MGK_HIP(ctx, hipEventSynchronize(s.event));
-        s.busy = false;
+    int pick = S.next;
+    for (int k = 0; k < kSlots; ++k) {
+        Staging::Slot& s = S.slot[(S.next + k) % kSlots];
+        if (s.cap >= bytes && !s.open && (!s.end || s.end->over())) { pick = (S.next + k) % kSlots; break; }
     }
-    if (!s.event) MGK_HIP(ctx, hipEventCreateWithFlags(&s.event, hipEventDisableTiming));
+    Staging::Slot& s = S.slot[pick];
+    if (bytes > s.cap && !may_allocate) return MGK_OK;
+    S.next = (pick + 1) % kSlots;
+    if (s.open) {   // by a call that failed, or by this one, which has used all slots
+        if (s.stream == stream) MGK_HIP(ctx, hipStreamSynchronize(stream));
+        MGK_HIP(ctx, hipDeviceSynchronize());
+        s.open = false;
+    } else if (s.end && !s.end->over()) {
+        MGK_HIP(ctx, hipEventSynchronize(s.end->event));
+    }
+    s.end.reset();
     if (bytes > s.cap) {
-        if (s.p) MGK_HIP(ctx, hipHostFree(s.p));
+        if (s.own) MGK_HIP(ctx, hipHostFree(s.p));
         s.p = nullptr;
         s.cap = 0;
-        const size_t cap = std::max<size_t>(bytes, 64 * 1024);
+        s.own = true;
+        const size_t cap = std::max(bytes + bytes / 4, kSlotBytes);
         MGK_HIP(ctx, hipHostMalloc(&s.p, cap, hipHostMallocDefault));
         s.cap = cap;
     }
@@ -1104,10 +1129,9 @@ mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, Staging::
     return MGK_OK;
 }
 
-mgk_status staging_done(mgk_ctx* ctx, Staging::Slot* slot, hipStream_t stream) {
-    MGK_HIP(ctx, hipEventRecord(slot->event, stream));
-    slot->busy = true;
-    return MGK_OK;
+void staging_copied(Staging::Slot* slot, hipStream_t stream) {   // a copy out of it is on the stream
+    slot->open = true;
+    slot->stream = stream;
 }
 
 // Device memory for a batch: a freed batch's block that nothing reads any more, or a new one.
@@ -1236,13 +1260,13 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
     float* vec = (float*)ctx->vec.p;
     // The pair records go through pinned memory owned by the context, so that the copy needs
     // no wait.
+    Staging::Slot* slot_p;
     {
         const size_t bytes = (size_t)n_pairs * sizeof(MgkLargePair);
-        Staging::Slot* slot;
-        if ((st = staging_slot(ctx, bytes, true, &slot)) != MGK_OK) return st;
-        memcpy(slot->p, pairs.data(), bytes);
-        MGK_HIP(ctx, hipMemcpyAsync(dpairs, slot->p, bytes, hipMemcpyHostToDevice, stream));
-        if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
+        if ((st = staging_slot(ctx, bytes, true, stream, &slot_p)) != MGK_OK) return st;
+        memcpy(slot_p->p, pairs.data(), bytes);
+        MGK_HIP(ctx, hipMemcpyAsync(dpairs, slot_p->p, bytes, hipMemcpyHostToDevice, stream));
+        staging_copied(slot_p, stream);
     }
     MGK_HIP(ctx, hipMemsetAsync(dstate, 0, (size_t)n_pairs * sizeof(MgkPairState), stream));
     ctx->active_host[0] = n_pairs;   // pairs still iterating
@@ -1266,6 +1290,7 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
         }
         MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
+        slot_p->open = false;
         if (ctx->active_host[0] <= 0) break;
     }
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
@@ -1348,14 +1373,14 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     if (sides == 1) sl[1] = sl[0];
 
     Staging::Slot* slot;
-    if ((st = staging_slot(ctx, rec_bytes, true, &slot)) != MGK_OK) return st;
+    if ((st = staging_slot(ctx, rec_bytes, true, stream, &slot)) != MGK_OK) return st;
     char* rec = static_cast<char*>(slot->p);
     memset(rec, 0, rec_bytes);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
     MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, rec_bytes, hipMemcpyHostToDevice, stream));
-    if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
+    staging_copied(slot, stream);
     // features of the graphs' nonzeros (they depend on the edge kernel's parameters)
     for (int k = 0; k < sides; ++k) {
         const MgkSepGraph* list = (const MgkSepGraph*)((char*)ctx->lpairs.p + used_at[k]);
@@ -1395,6 +1420,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         if (foreseen && (e = outputs()) != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
         MGK_HIP(ctx, hipMemcpyAsync(ctx->active_host, dactive, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
+        slot->open = false;
     }
     if (it > first_batch) {   // more iterations than foreseen
         if ((e = outputs()) != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
@@ -1565,9 +1591,19 @@ mgk_status mgk_create(mgk_ctx** out, int device) {
         ctx->memory->events.reserve(4 * kMaxReads);
     } catch (...) { delete ctx; return MGK_ENOMEM; }
     if (device >= 0 && hipSetDevice(device) != hipSuccess) { delete ctx; return MGK_EDEVICE; }
-    for (int k = 0; device >= 0 && k < 4; ++k) {   // for calls that may not create any
-        hipEvent_t e = nullptr;
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) ctx->memory->events.push_back(e);
+    if (device >= 0) {   // what the first calls would have to create, and some may not
+        Staging& S = ctx->staging;
+        if (hipHostMalloc(&S.block, sizeof(S.slot) / sizeof(S.slot[0]) * kSlotBytes, hipHostMallocDefault) == hipSuccess)
+            for (Staging::Slot& s : S.slot) {
+                s.p = (char*)S.block + (size_t)(&s - S.slot) * kSlotBytes;
+                s.cap = kSlotBytes;
+            }
+        else S.block = nullptr;
+        for (size_t k = 0; k < kMaxReads; ++k) {
+            hipEvent_t e = nullptr;
+            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) ctx->memory->events.push_back(e);
+        }
+        (void)hipGetLastError();
     }
     *out = ctx;
     return MGK_OK;
@@ -1583,12 +1619,12 @@ void mgk_destroy(mgk_ctx* ctx) {
         if (b->p) (void)hipFree(b->p);
     if (ctx->active_host) (void)hipHostFree(ctx->active_host);
     for (Staging::Slot& s : ctx->staging.slot) {
-        if (s.event) {
-            if (s.busy) (void)hipEventSynchronize(s.event);
-            (void)hipEventDestroy(s.event);
-        }
-        if (s.p) (void)hipHostFree(s.p);
+        if (s.open) (void)hipDeviceSynchronize();
+        if (s.end) (void)hipEventSynchronize(s.end->event);
+        s.end.reset();
+        if (s.own && s.p) (void)hipHostFree(s.p);
     }
+    if (ctx->staging.block) (void)hipHostFree(ctx->staging.block);
     std::vector<FreeBlob> blobs;
     {
         std::lock_guard<std::mutex> lock(ctx->memory->m);
@@ -2179,7 +2215,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     } else {   // on a stream of the context: waits for its own copy, not for the calls under way
         Staging::Slot* slot;
         if (!ctx->upload) MGK_HIP(ctx, hipStreamCreateWithFlags(&ctx->upload, hipStreamNonBlocking));
-        if (mgk_status st = staging_slot(ctx, blob.total, true, &slot)) return st;
+        if (mgk_status st = staging_slot(ctx, blob.total, true, ctx->upload, &slot)) return st;
         blob.copy_to(static_cast<char*>(slot->p));
         MGK_HIP(ctx, hipMemcpyAsync(B->blob, slot->p, blob.total, hipMemcpyHostToDevice, ctx->upload));
         MGK_HIP(ctx, hipStreamSynchronize(ctx->upload));
@@ -2439,7 +2475,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if (st != MGK_OK) return st;
         ctx->fixed_jobs_stream = stream;
         ctx->fixed_jobs_busy = true;
-        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(stream, false);
+        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, false);
         return st;
     }
     mgk_status st = build_job_list(ctx, plan, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
@@ -2451,14 +2487,14 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if ((st = ensure(ctx, ctx->nodal_off, (size_t)n_pairs * sizeof(int64_t))) != MGK_OK) return st;
         const size_t bytes = (size_t)n_pairs * sizeof(int64_t);
         Staging::Slot* slot;
-        if ((st = staging_slot(ctx, bytes, true, &slot)) != MGK_OK) return st;
+        if ((st = staging_slot(ctx, bytes, true, stream, &slot)) != MGK_OK) return st;
         memcpy(slot->p, x_off_host, bytes);
         MGK_HIP(ctx, hipMemcpyAsync(ctx->nodal_off.p, slot->p, bytes, hipMemcpyHostToDevice, stream));
-        if ((st = staging_done(ctx, slot, stream)) != MGK_OK) return st;
+        staging_copied(slot, stream);
         out.nodal = x_dev;
         out.nodal_off = (const int64_t*)ctx->nodal_off.p;
     }
-    if ((st = launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream)) == MGK_OK) reads.done(stream, true);
+    if ((st = launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, true);
     return st;
 }
 

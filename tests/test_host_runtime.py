@@ -262,3 +262,17 @@ def test_few_pairs_take_the_product_that_fills_the_chip(host, n, k, pairs, kerne
     assert host.pairs(B, B, [0] * pairs, [0] * pairs) == 0, host.error()
     assert launched(host.log(), kernel), host.log()
     host.free(B)
+
+
+def test_pinned_memory_is_allocated_with_the_context(so):
+    """Not inside the first calls, which are as short as any."""
+    h = host_runtime.Host(so)
+    pinned, wb = h.lib.stub_pinned(), W.config1(12)
+    for entry in ("mgk_pairs", "mgk_pairs_noalloc"):
+        for _ in range(6):
+            B = h.load(wb)
+            assert h.pairs(B, B, [0, 1, 2], [2, 3, 4], entry=entry) == 0, h.error()
+            h.free(B)
+    assert h.lib.stub_pinned() == pinned > 0
+    h.destroy()
+    assert h.lib.stub_pinned() == 0
