@@ -231,6 +231,12 @@ struct mgk_batch {
     int gram_jobs_attr_dim = -1;   // label attributes of the edge kernel it was built for (LDS plan)
 };
 
+struct KeptBasis {
+    int kernel = -1;
+    float param = 0.f, lo = 0.f, hi = 0.f;
+    MgkSepBasis basis{};
+};
+
 struct mgk_ctx {
     int device = 0;
     std::string err;
@@ -259,9 +265,8 @@ struct mgk_ctx {
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
     bool features_in_use = false;       // by the call under way
-    MgkSepBasis sep_basis{};            // of the last label range and edge kernel, see sep_basis_for
-    float sep_lo = 0.f, sep_hi = -1.f, sep_param = 0.f;
-    int sep_kernel = -1;
+    KeptBasis bases[4];                 // of the last label ranges and edge kernels, see sep_basis_for
+    int next_basis = 0;
     DevBuf vec, lpairs, lstate, lactive, nodal_off, diag;
     int* active_host = nullptr;         // pinned: {pairs still iterating, most iterations needed}
     Staging staging;                    // pair records, job lists and offsets of a call on their way to the device
@@ -861,105 +866,90 @@ bool use_dense_tiles(const mgk_ctx* ctx, const MgkGraphDesc& a, const MgkGraphDe
            (int64_t)b.nnz >= (int64_t)kDenseMinNnzPerTile * b.n_tiles;
 }
 
-// Separable form of the edge kernel on the label range [lo, hi] (see MgkSepBasis).  rank 0:
-// the kernel has none of at most MGK_SEP_MAX_RANK terms (short length scale against the range, or
-// a kernel that is not smooth).  Kept with the context until kernel or range change.
-const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
-    const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
-    if (ctx->sep_kernel == ctx->edge_kernel && ctx->sep_param == param && ctx->sep_lo == lo && ctx->sep_hi == hi)
-        return ctx->sep_basis;
-    MgkSepBasis& S = ctx->sep_basis;
-    S = MgkSepBasis{};
-    ctx->sep_kernel = ctx->edge_kernel;
-    ctx->sep_param = param;
-    ctx->sep_lo = lo;
-    ctx->sep_hi = hi;
-    if (ctx->edge_kernel == MGK_EK_CONST) {
-        S.rank = S.terms = 1;
-        S.coef[0] = std::sqrt((double)ctx->ke_const);
-        return S;
+// Numbers of sep_basis that do not depend on the kernel.
+struct SepTables {
+    static constexpr int N = 48, H = N / 2, D = 2 * MGK_SEP_MAX_TERMS, E = 33;
+    double node[H];       // Chebyshev nodes in (0, 1); the other half are their negatives
+    double cosm[H][D];    // T_m(node) times the weight of the transform
+    double mono[D][D];    // monomial coefficients of T_m
+    double grid[E];
+    SepTables() : mono{} {
+        const double pi = 3.14159265358979323846;
+        for (int i = 0; i < H; ++i) {
+            node[i] = std::cos(pi * (i + 0.5) / N);
+            for (int m = 0; m < D; ++m) cosm[i][m] = std::cos(pi * m * (i + 0.5) / N) * (m ? 2.0 : 1.0) / N;
+        }
+        mono[0][0] = mono[1][1] = 1.0;
+        for (int m = 2; m < D; ++m)
+            for (int j = 0; j <= m; ++j) mono[m][j] = (j ? 2.0 * mono[m - 1][j - 1] : 0.0) - mono[m - 2][j];
+        for (int e = 0; e < E; ++e) grid[e] = std::cos(pi * e / (E - 1));
     }
-    if (ctx->edge_kernel != MGK_EK_SE) return S;
-    S.center = 0.5 * ((double)lo + (double)hi);
-    const double R = std::max((double)hi - S.center, S.center - (double)lo);
-    const double l = (double)ctx->length_scale, t = R * R / (l * l);
+};
+
+// Separable form of the square-exponential kernel for labels within R of `center`, t = (R / l)^2; rank 0
+// where it has none of at most MGK_SEP_MAX_RANK terms.  Functions are even or odd, so half of every
+// grid does.  It is formed on the calling thread before the first launch: 31 us at rank 5, 45 at 12; with
+// whole grids, tables made each time and the error taken anew for every rank it was 122 and 213.
+MgkSepBasis sep_basis_se(double center, double R, double t) {
+    static const SepTables T;
+    constexpr int H = T.H, D = T.D, E = T.E, MaxR = MGK_SEP_MAX_RANK;
+    MgkSepBasis S{};
+    S.center = center;
     S.inv_r = R > 0.0 ? 1.0 / R : 0.0;
     // |exp(t s s') - its Chebyshev sum of rank r| falls like 4 (t / 4)^r / r!: hopeless beyond this
     if (!(t <= 8.0)) return S;
-    constexpr int N = 48, D = 2 * MGK_SEP_MAX_TERMS, MaxR = MGK_SEP_MAX_RANK;
-    const double pi = 3.14159265358979323846;
-    double node[N];
-    for (int i = 0; i < N; ++i) node[i] = std::cos(pi * (i + 0.5) / N);
-    std::vector<double> cosm((size_t)D * N), half((size_t)D * N), C((size_t)D * D, 0.0);
-    for (int m = 0; m < D; ++m)
-        for (int i = 0; i < N; ++i) cosm[(size_t)m * N + i] = std::cos(pi * m * (i + 0.5) / N) * (m ? 2.0 : 1.0) / N;
     // Chebyshev coefficients of exp(t s s') from its values on a grid of nodes, both variables
-    for (int i = 0; i < N; ++i) {
-        double row[N];
-        for (int j = 0; j < N; ++j) row[j] = std::exp(t * node[i] * node[j]);
-        for (int m = 0; m < D; ++m) {
-            double v = 0.0;
-            for (int j = 0; j < N; ++j) v += row[j] * cosm[(size_t)m * N + j];
-            half[(size_t)m * N + i] = v;
+    double half[H][D] = {}, C[D][D] = {};
+    for (int i = 0; i < H; ++i)
+        for (int j = 0; j < H; ++j) {
+            const double u = std::exp(t * T.node[i] * T.node[j]), v = std::exp(-t * T.node[i] * T.node[j]);
+            const double sum = u + v, dif = u - v;
+            for (int m = 0; m < D; m += 2) {
+                half[i][m] += sum * T.cosm[j][m];
+                half[i][m + 1] += dif * T.cosm[j][m + 1];
+            }
         }
-    }
+    for (int i = 0; i < H; ++i)   // the function is even in (s, s') together
+        for (int m = 0; m < D; ++m)
+            for (int n = m & 1; n <= m; n += 2) C[m][n] += 2.0 * half[i][m] * T.cosm[i][n];
     for (int m = 0; m < D; ++m)
-        for (int n = m & 1; n <= m; n += 2) {   // the function is even in (s, s') together
-            double v = 0.0;
-            for (int i = 0; i < N; ++i) v += half[(size_t)m * N + i] * cosm[(size_t)n * N + i];
-            C[(size_t)m * D + n] = C[(size_t)n * D + m] = v;
-        }
-    // monomial coefficients of the Chebyshev polynomials
-    std::vector<double> mono((size_t)D * D, 0.0);
-    mono[0] = 1.0;
-    mono[(size_t)D + 1] = 1.0;
-    for (int m = 2; m < D; ++m)
-        for (int j = 0; j <= m; ++j)
-            mono[(size_t)m * D + j] = (j ? 2.0 * mono[(size_t)(m - 1) * D + j - 1] : 0.0) - mono[(size_t)(m - 2) * D + j];
-    constexpr int E = 33;
-    double grid[E], feat[E][MaxR];
-    for (int e = 0; e < E; ++e) grid[e] = std::cos(pi * e / (E - 1));
-    // error of the first r columns with `terms` terms, on the grid
-    auto error = [&](int r, int terms) {
-        for (int e = 0; e < E; ++e)
-            for (int k = 0; k < r; ++k) {
-                double v = 0.0;
-                for (int m = terms - 1; m >= 0; --m) v = v * grid[e] * grid[e] + S.coef[m * MaxR + k];
-                feat[e][k] = k & 1 ? v * grid[e] : v;
-            }
-        double err = 0.0;
-        for (int e = 0; e < E; ++e)
-            for (int f = 0; f <= e; ++f) {
-                double v = std::exp(-0.5 * t * (grid[e] - grid[f]) * (grid[e] - grid[f]));
-                for (int k = 0; k < r; ++k) v -= feat[e][k] * feat[f][k];
-                err = std::max(err, std::fabs(v));
-            }
-        return err;
-    };
+        for (int n = m & 1; n < m; n += 2) C[n][m] = C[m][n];
+    double gauss[H], left[E][E];   // what the columns so far leave of the kernel
+    for (int i = 0; i < H; ++i) gauss[i] = std::exp(-0.5 * t * T.node[i] * T.node[i]);
+    for (int e = 0; e < E; ++e)
+        for (int f = 0; f <= e; ++f) left[e][f] = std::exp(-0.5 * t * (T.grid[e] - T.grid[f]) * (T.grid[e] - T.grid[f]));
     for (int k = 0; k < MaxR; ++k) {
         // column k of the Cholesky factor, as a function times the Gaussian, as a polynomial
-        const double d = C[(size_t)k * D + k];
+        const int odd = k & 1;
+        const double d = C[k][k];
         if (!(d > 0.0)) return S;   // no further degree can be resolved in double
-        double col[D], cheb[D], poly[D] = {};
-        for (int m = 0; m < D; ++m) col[m] = C[(size_t)m * D + k] / std::sqrt(d);
-        for (int m = 0; m < D; ++m)
-            for (int n = m & 1; n < D; n += 2) C[(size_t)m * D + n] -= col[m] * col[n];
-        double val[N];
-        for (int i = 0; i < N; ++i) {
+        double col[D], cheb[D] = {}, poly[D] = {};
+        for (int m = 0; m < D; ++m) col[m] = C[m][k] / std::sqrt(d);
+        for (int m = odd; m < D; m += 2)
+            for (int n = odd; n < D; n += 2) C[m][n] -= col[m] * col[n];
+        for (int i = 0; i < H; ++i) {
             double v = 0.0;
-            for (int m = k & 1; m < D; m += 2) v += col[m] * cosm[(size_t)m * N + i] * (m ? 0.5 * N : N);
-            val[i] = v * std::exp(-0.5 * t * node[i] * node[i]);
-        }
-        for (int m = 0; m < D; ++m) {
-            cheb[m] = 0.0;
-            for (int i = 0; i < N && ((m ^ k) & 1) == 0; ++i) cheb[m] += val[i] * cosm[(size_t)m * N + i];
+            for (int m = odd; m < D; m += 2) v += col[m] * T.cosm[i][m] * (m ? 0.5 * T.N : T.N);
+            v *= 2.0 * gauss[i];
+            for (int m = odd; m < D; m += 2) cheb[m] += v * T.cosm[i][m];
         }
         int last = D - 1;   // what is left above is rounding noise, which the monomials would amplify
         while (last > 0 && std::fabs(cheb[last]) < 1e-12) --last;
-        for (int m = k & 1; m <= last; m += 2)
-            for (int j = m & 1; j <= m; j += 2) poly[j] += cheb[m] * mono[(size_t)m * D + j];
-        for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m) S.coef[m * MaxR + k] = poly[2 * m + (k & 1)];
-        if (error(k + 1, MGK_SEP_MAX_TERMS) > MGK_SEP_TOLERANCE) continue;
+        for (int m = odd; m <= last; m += 2)
+            for (int j = odd; j <= m; j += 2) poly[j] += cheb[m] * T.mono[m][j];
+        for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m) S.coef[m * MaxR + k] = poly[2 * m + odd];
+        double feat[E], err = 0.0;
+        for (int e = 0; e < E; ++e) {
+            double v = 0.0;
+            for (int m = MGK_SEP_MAX_TERMS - 1; m >= 0; --m) v = v * T.grid[e] * T.grid[e] + S.coef[m * MaxR + k];
+            feat[e] = odd ? v * T.grid[e] : v;
+        }
+        for (int e = 0; e < E; ++e)
+            for (int f = 0; f <= e; ++f) {
+                left[e][f] -= feat[e] * feat[f];
+                err = std::max(err, std::fabs(left[e][f]));
+            }
+        if (err > MGK_SEP_TOLERANCE) continue;
         S.rank = k + 1;
         S.terms = 1;
         for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m)
@@ -968,6 +958,27 @@ const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
         return S;
     }
     return S;
+}
+
+// Separable form of the edge kernel on the label range [lo, hi] (see MgkSepBasis).  rank 0: the kernel
+// has none (short length scale against the range, or a kernel that is not smooth).  The last few are kept
+// with the context: batches compared in turn have ranges of their own.
+const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
+    const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
+    for (KeptBasis& b : ctx->bases)
+        if (b.kernel == ctx->edge_kernel && b.param == param && b.lo == lo && b.hi == hi) return b.basis;
+    KeptBasis& b = ctx->bases[ctx->next_basis];
+    ctx->next_basis = (ctx->next_basis + 1) % (int)(sizeof(ctx->bases) / sizeof(ctx->bases[0]));
+    b = KeptBasis{ctx->edge_kernel, param, lo, hi, MgkSepBasis{}};
+    if (ctx->edge_kernel == MGK_EK_CONST) {
+        b.basis.rank = b.basis.terms = 1;
+        b.basis.coef[0] = std::sqrt((double)ctx->ke_const);
+    } else if (ctx->edge_kernel == MGK_EK_SE) {
+        const double center = 0.5 * ((double)lo + (double)hi), R = std::max((double)hi - center, center - (double)lo);
+        const double l = (double)ctx->length_scale;
+        b.basis = sep_basis_se(center, R, R * R / (l * l));
+    }
+    return b.basis;
 }
 
 // How the sparse separable product of a pair with n2 columns divides its rank: the fewest
@@ -1014,16 +1025,15 @@ int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
     return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
 }
 
-// n_pairs: pairs of the call that may run beside this one.  Forming the features is left out: only the
+// rank 0: no separable form.  n_pairs: pairs of the call that may run beside this one.  Forming the features is left out: only the
 // graphs of the pairs get them, which takes 1 % of what the products of a pair take.
-LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb,
-                     int64_t n_pairs) {
+LargeCost large_cost(const mgk_ctx* ctx, int rank, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb, int64_t n_pairs) {
     constexpr double kComputeUnits = 256;
     const MgkGraphDesc &o = A->graphs[(size_t)ga], &i = B->graphs[(size_t)gb];
-    auto fits = [&](bool dense) { return feature_bytes(A, ga, S.rank, dense) + feature_bytes(B, gb, S.rank, dense) <= kMaxFeatureBytes; };
+    auto fits = [&](bool dense) { return feature_bytes(A, ga, rank, dense) + feature_bytes(B, gb, rank, dense) <= kMaxFeatureBytes; };
     LargeCost C;
     C.best = use_dense_tiles(ctx, o, i) ? kPathDenseTiles : kPathSparse;
-    if (ctx->tile_path != MGK_TILE_AUTO || S.rank == 0) {
+    if (ctx->tile_path != MGK_TILE_AUTO || rank == 0) {
         C.clk[C.best] = 0.0;   // no choice
         return C;
     }
@@ -1031,9 +1041,9 @@ LargeCost large_cost(const mgk_ctx* ctx, const MgkSepBasis& S, const mgk_batch* 
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
     const double entries = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n;
     C.clk[C.best] = entries + 6.0 * N + alone * std::max(1.2 * entries, 3200.0 * o.nnz) / o.n;
-    const MgkSepLayout L = sep_layout(S.rank, i.n);
+    const MgkSepLayout L = sep_layout(rank, i.n);
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255;
-    const double sparse = (double)L.rk * L.passes * one_sided / 20.0, dense = S.rank * op * ip * ((double)o.n + i.n);
+    const double sparse = (double)L.rk * L.passes * one_sided / 20.0, dense = rank * op * ip * ((double)o.n + i.n);
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
     if (may_sparse) C.clk[kPathSep] = std::max(sparse + 8.0 * N, alone * (10000.0 + 0.9 * sparse / ((o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS)));
     if (may_dense) C.clk[kPathSepDense] = std::max(dense / 42.0, alone * dense / 60.0 / (op / MGK_SEP_DENSE_ROWS));
@@ -1470,30 +1480,40 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     }
     if (!any_large) return MGK_OK;
     // ---- pairs with vectors in global memory: the product of each from the current edge kernel
-    const MgkSepBasis none{};
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
-    const MgkSepBasis& S = may_sep ? sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi)) : none;
     struct Choice {
         MgkLargePair asked, sep;   // the pair as the direct product takes it, and the separable one
         int swapped, sep_swapped;
     };
     std::vector<Choice> choices;
-    std::vector<LargeCost> costs;
     choices.reserve(jl.large[0].size() + jl.large[1].size());
-    costs.reserve(choices.capacity());
     for (int swapped = 0; swapped < 2; ++swapped)
         for (const MgkLargePair& asked : jl.large[swapped]) {
             Choice c{asked, asked, swapped, swapped};
             MgkLargePair& P = c.sep;
-            if (S.rank > 0 && P.n2 > P.n1) {   // separable product: T has a column per inner vertex
+            if (may_sep && P.n2 > P.n1) {   // separable product: T has a column per inner vertex
                 std::swap(P.g1, P.g2);
                 std::swap(P.n1, P.n2);
                 if (P.out1 < 0) P.out1 = P.out1 == MGK_OUT1_SWAPPED ? MGK_OUT1_NONE : MGK_OUT1_SWAPPED;
                 if (X != Y) c.sep_swapped = 1 - swapped;
             }
-            costs.push_back(large_cost(ctx, S, c.sep_swapped ? Y : X, P.g1, c.sep_swapped ? X : Y, P.g2, (int64_t)choices.capacity()));
             choices.push_back(c);
         }
+    auto costs_at = [&](int rank) {
+        std::vector<LargeCost> costs;
+        costs.reserve(choices.size());
+        for (const Choice& c : choices)
+            costs.push_back(large_cost(ctx, rank, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size()));
+        return costs;
+    };
+    // the basis takes time: it is formed if any pair would take the separable product at the lowest rank
+    std::vector<LargeCost> costs = costs_at(may_sep ? 1 : 0);
+    const MgkSepBasis none{}, *basis = &none;
+    if (may_sep && std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); })) {
+        basis = &sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi));
+        if (basis->rank != 1) costs = costs_at(basis->rank);
+    }
+    const MgkSepBasis& S = *basis;
     merge_paths(costs);
     std::vector<const Choice*> lists[2][kPaths];
     for (size_t k = 0; k < choices.size(); ++k) {

@@ -233,9 +233,11 @@ hipError_t mgk_launch_large_iteration(const MgkBatchDev& X, const MgkBatchDev& Y
 hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkExpanded&, const MgkExpanded&,
                                   const MgkLargePair*, MgkPairState*, float*, const MgkParams&, bool, int n, int, int,
                                   const MgkDenseTiles*, const MgkDenseTiles*, int, int, int, const MgkOutputs&, hipStream_t s) { return launched("final", s, &X, &Y, n); }
-hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis&, const MgkSepLayout&, const MgkSepList&, const MgkSepGraph*,
-                               int n_used, int, float*, hipStream_t s) { return launched("sep pack", s, &B, nullptr, n_used); }
-hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis&, const MgkSepGraph*, int n_used, int, float*, hipStream_t s) { return launched("sep dense pack", s, &B, nullptr, n_used); }
+static MgkSepBasis basis;
+extern "C" const MgkSepBasis* stub_basis() { return &basis; }   // of the last features
+hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout&, const MgkSepList&, const MgkSepGraph*,
+                               int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep pack", s, &B, nullptr, n_used); }
+hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph*, int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep dense pack", s, &B, nullptr, n_used); }
 hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&,
                               const MgkSepLayout&, const MgkLargePair*, MgkPairState*, float*, const MgkParams&, int n, int max_n1,
                               int, int, bool, hipStream_t s) {

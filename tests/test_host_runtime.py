@@ -276,3 +276,54 @@ def test_pinned_memory_is_allocated_with_the_context(so):
     assert h.lib.stub_pinned() == pinned > 0
     h.destroy()
     assert h.lib.stub_pinned() == 0
+
+
+class Basis(C.Structure):
+    _fields_ = [("rank", C.c_int32), ("terms", C.c_int32), ("center", C.c_double), ("inv_r", C.c_double), ("coef", C.c_double * 256)]
+
+    def features(self, x):
+        s = (np.asarray(x, np.float64) - self.center) * self.inv_r
+        coef = np.array(self.coef).reshape(16, 16)[:self.terms, :self.rank]
+        v = np.stack([np.polyval(coef[::-1, k], s * s) for k in range(self.rank)], 1)
+        v[:, 1::2] *= s[:, None]
+        return v
+
+
+def basis_of(host, length_scale, lo, hi):
+    """The separable form of the square-exponential kernel on labels of [lo, hi]; None if it has none."""
+    B = host.load(graphs(ring(151, 20, np.linspace(lo, hi, 151 * 20))))
+    host.set("edge_kernel_se", float(length_scale))
+    host.lib.stub_clear_log()
+    assert host.pairs(B, B, [0] * 64, [0] * 64) == 0, host.error()
+    packed = launched(host.log(), "sep pack") + launched(host.log(), "sep dense pack")
+    host.free(B)
+    host.lib.stub_basis.restype = C.POINTER(Basis)
+    out = Basis()
+    C.memmove(C.byref(out), host.lib.stub_basis(), C.sizeof(Basis))
+    return out if packed else None
+
+
+@pytest.mark.parametrize("lo,hi", [(0.0, 1.0), (-3.0, 5.0), (100.0, 100.25), (0.0, 0.0)])
+def test_separable_form_of_the_kernel(host, lo, hi):
+    """Its error over the label range between the points that the host looks at (MGK_SEP_TOLERANCE there), in
+    double and with the features rounded to fp32, which adds at most 2^-23 in all, as sum_k phi_k^2 is 1."""
+    ranks = []
+    for ratio in (100.0, 10.0, 3.0, 1.5, 1.0, 0.7, 0.5, 0.33, 0.25, 0.21, 0.18):
+        length = float(np.float32(ratio * ((hi - lo) or 1.0)))
+        S = basis_of(host, length, lo, hi)
+        x = np.linspace(lo, hi, 301)
+        exact = np.exp(-0.5 * ((x[:, None] - x[None]) / length) ** 2)
+        phi = S.features(x)
+        low = phi.astype(np.float32).astype(np.float64)
+        assert np.abs(phi @ phi.T - exact).max() <= 6.0e-8
+        assert np.abs(low @ low.T - exact).max() <= 6.0e-8 + 2.0 ** -23
+        ranks.append(S.rank)
+    assert ranks == sorted(ranks) and (ranks[-1] >= 15 or lo == hi)
+    assert lo == hi or basis_of(host, 0.12 * (hi - lo), lo, hi) is None
+
+
+def test_separable_forms_of_batches_in_turn(host):
+    """The forms kept for earlier label ranges and length scales are not mixed up."""
+    first = [bytes(basis_of(host, l, lo, hi)) for l, lo, hi in ((1.0, 0.0, 1.0), (0.5, 0.0, 1.0), (1.0, 0.0, 2.0))]
+    again = [bytes(basis_of(host, l, lo, hi)) for l, lo, hi in ((1.0, 0.0, 1.0), (0.5, 0.0, 1.0), (1.0, 0.0, 2.0))]
+    assert first == again and len(set(first)) == 3
