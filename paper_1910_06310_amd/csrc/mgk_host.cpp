@@ -272,6 +272,7 @@ struct mgk_ctx {
     Staging staging;                    // pair records, job lists and offsets of a call on their way to the device
     std::shared_ptr<BatchMemory> memory;
     int64_t calls = 0;                  // solver calls so far
+    bool idle = false;                  // the last call has waited for all of its kernels
     hipStream_t upload = nullptr;       // loading a batch does not wait for the caller's streams
     WorkerPool workers;
     int large_iter_guess = 12;          // iterations the last call of the global-memory solver needed
@@ -416,7 +417,13 @@ class BatchReads {
 public:
     BatchReads(mgk_batch* X, mgk_batch* Y) : b_{X, Y}, was_{X->untracked, Y->untracked} { X->untracked = Y->untracked = true; }
     // may_create: else the event is one that an earlier call has left
-    void done(Staging& staging, hipStream_t stream, bool may_create) {
+    void done(Staging& staging, hipStream_t stream, bool may_create, bool idle) {
+        if (idle) {   // the call has waited for its kernels
+            for (Staging::Slot& s : staging.slot)
+                if (s.stream == stream) s.open = false;
+            for (int k = 0; k < 2; ++k) b_[k]->untracked = was_[k];
+            return;
+        }
         const bool staged = std::any_of(std::begin(staging.slot), std::end(staging.slot), [](const Staging::Slot& s) { return s.open; });
         if (was_[0] && was_[1] && !staged) return;
         try {
@@ -963,10 +970,14 @@ MgkSepBasis sep_basis_se(double center, double R, double t) {
 // Separable form of the edge kernel on the label range [lo, hi] (see MgkSepBasis).  rank 0: the kernel
 // has none (short length scale against the range, or a kernel that is not smooth).  The last few are kept
 // with the context: batches compared in turn have ranges of their own.
-const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
+const MgkSepBasis* kept_basis(const mgk_ctx* ctx, float lo, float hi) {
     const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
-    for (KeptBasis& b : ctx->bases)
-        if (b.kernel == ctx->edge_kernel && b.param == param && b.lo == lo && b.hi == hi) return b.basis;
+    for (const KeptBasis& b : ctx->bases)
+        if (b.kernel == ctx->edge_kernel && b.param == param && b.lo == lo && b.hi == hi) return &b.basis;
+    return nullptr;
+}
+const MgkSepBasis* make_basis(mgk_ctx* ctx, float lo, float hi) {
+    const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
     KeptBasis& b = ctx->bases[ctx->next_basis];
     ctx->next_basis = (ctx->next_basis + 1) % (int)(sizeof(ctx->bases) / sizeof(ctx->bases[0]));
     b = KeptBasis{ctx->edge_kernel, param, lo, hi, MgkSepBasis{}};
@@ -978,7 +989,7 @@ const MgkSepBasis& sep_basis_for(mgk_ctx* ctx, float lo, float hi) {
         const double l = (double)ctx->length_scale;
         b.basis = sep_basis_se(center, R, R * R / (l * l));
     }
-    return b.basis;
+    return &b.basis;
 }
 
 // How the sparse separable product of a pair with n2 columns divides its rank: the fewest
@@ -1311,6 +1322,7 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
                                vec_blocks, dense ? &dt[0] : nullptr, dense ? &dt[1] : nullptr, rows_threads,
                                rows_lds_bytes, rows_chunks, out, stream);
     if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
+    ctx->idle = false;
     return MGK_OK;
 }
 
@@ -1323,6 +1335,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
                      const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, const MgkParams& prm) {
     const int n_pairs = (int)pairs.size();
     if (n_pairs == 0) return MGK_OK;
+    if (!mgk_launch_sep_xmv) return fail(ctx, MGK_ESTATE, "the library was linked without the kernels of the separable product");
     int64_t total = 0;
     int max_npad = 0, max_iter = 0, max_n1 = 1, max_n2 = 1;
     for (MgkLargePair& P : pairs) {
@@ -1357,14 +1370,15 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         P.f1 = features(0, P.g1);
         P.f2 = features(sides - 1, P.g2);
     }
-    // pair records, their zeroed states, the counters and the graph lists of a call are one block and one copy
+    // pair records, their zeroed states and the counters of a call are one block and one copy; the graph lists
+    // follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
     const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
     const size_t used_at[2] = {active_at + 64, active_at + 64 + used[0].size() * sizeof(MgkSepGraph)};
     const size_t rec_bytes = used_at[1] + used[1].size() * sizeof(MgkSepGraph);
     mgk_status st;
     if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
-    if ((st = ensure(ctx, ctx->lpairs, rec_bytes)) != MGK_OK) return st;
+    if ((st = ensure(ctx, ctx->lpairs, used_at[0])) != MGK_OK) return st;
     if (!ctx->active_host) MGK_HIP(ctx, hipHostMalloc((void**)&ctx->active_host, 64, hipHostMallocDefault));
     struct InUse {
         bool& flag;
@@ -1389,15 +1403,16 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
-    MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, rec_bytes, hipMemcpyHostToDevice, stream));
     staging_copied(slot, stream);
-    // features of the graphs' nonzeros (they depend on the edge kernel's parameters)
+    // features of the graphs' nonzeros (they depend on the edge kernel's parameters); the kernels read the
+    // graph lists where they are, in pinned memory, so that they do not wait for the copy
     for (int k = 0; k < sides; ++k) {
-        const MgkSepGraph* list = (const MgkSepGraph*)((char*)ctx->lpairs.p + used_at[k]);
+        const MgkSepGraph* list = (const MgkSepGraph*)(rec + used_at[k]);
         hipError_t e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, list, (int)used[k].size(), max_n[k], (float*)ctx->sep_dense[k].p, stream)
                              : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], list, (int)used[k].size(), max_n[k], (float*)ctx->sep_packets[k].p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
+    MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, used_at[0], hipMemcpyHostToDevice, stream));
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
     MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
     int* dactive = (int*)((char*)ctx->lpairs.p + active_at);
@@ -1436,9 +1451,12 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         if ((e = outputs()) != hipSuccess) return fail(ctx, MGK_EDEVICE, "final launch failed: %s", hipGetErrorString(e));
         MGK_HIP(ctx, hipStreamSynchronize(stream));
     }
+    ctx->idle = true;
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
-    log_launch(ctx, "%s rank=%d pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)",
-               dense ? "mgk_sep_dense_kernel" : "mgk_sep_xmv_kernel", S.rank, n_pairs, it);
+    char form[64];
+    if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
+    else snprintf(form, sizeof form, "mgk_sep_xmv_kernel<%d> rank=%d passes=%d", L.rk, S.rank, L.passes);
+    log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)", form, n_pairs, it);
     return MGK_OK;
 }
 
@@ -1450,6 +1468,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     if (any_large)   // before anything is recorded
         if (mgk_status st = refuse_capture(ctx, stream)) return st;
     ctx->calls++;
+    ctx->idle = false;
     ctx->launch_log.clear();
     for (const JobBin& b : jl.bins) {
         if (b.sell_regs > 0)
@@ -1506,13 +1525,17 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             costs.push_back(large_cost(ctx, rank, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size()));
         return costs;
     };
-    // the basis takes time: it is formed if any pair would take the separable product at the lowest rank
-    std::vector<LargeCost> costs = costs_at(may_sep ? 1 : 0);
     const MgkSepBasis none{}, *basis = &none;
-    if (may_sep && std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); })) {
-        basis = &sep_basis_for(ctx, std::min(X->label_lo, Y->label_lo), std::max(X->label_hi, Y->label_hi));
-        if (basis->rank != 1) costs = costs_at(basis->rank);
+    std::vector<LargeCost> costs;
+    if (may_sep) {
+        const float lo = std::min(X->label_lo, Y->label_lo), hi = std::max(X->label_hi, Y->label_hi);
+        basis = kept_basis(ctx, lo, hi);
+        if (!basis) {   // it takes time: made if any pair would take the separable product at the lowest rank
+            costs = costs_at(1);
+            basis = std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); }) ? make_basis(ctx, lo, hi) : &none;
+        }
     }
+    costs = costs_at(basis->rank);
     const MgkSepBasis& S = *basis;
     merge_paths(costs);
     std::vector<const Choice*> lists[2][kPaths];
@@ -2495,7 +2518,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if (st != MGK_OK) return st;
         ctx->fixed_jobs_stream = stream;
         ctx->fixed_jobs_busy = true;
-        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, false);
+        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, false, ctx->idle);
         return st;
     }
     mgk_status st = build_job_list(ctx, plan, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);
@@ -2514,7 +2537,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         out.nodal = x_dev;
         out.nodal_off = (const int64_t*)ctx->nodal_off.p;
     }
-    if ((st = launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, true);
+    if ((st = launch_jobs(ctx, X, Y, ctx->pair_jobs, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, true, ctx->idle);
     return st;
 }
 

@@ -397,6 +397,8 @@ static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
 static inline MGK_HD int64_t mgk_sep_grid(int64_t n_pairs, int32_t max_n1, int32_t rows) {
     return (n_pairs + 7) / 8 * 8 * ((max_n1 + rows - 1) / rows);
 }
+// Tiles of 64 columns per wavefront of the dense form, 4 wavefronts: 1, 2 or 4.
+static inline MGK_HD int32_t mgk_sep_dense_tiles(int32_t max_n2) { return max_n2 <= 256 ? 1 : max_n2 <= 512 ? 2 : 4; }
 // What the separable product reads beside MgkBatchDev.  Packets come in steps of 64 words (four
 // rows of adjacent rank in deg_order, one packet each): pass q at packets + q total 64; group t of graph g
 // has steps at + gptr[qoff[g] + t] .. at + gptr[qoff[g] + t + 1], gptr counting over the whole batch and

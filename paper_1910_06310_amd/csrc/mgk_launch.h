@@ -152,10 +152,11 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
                                   int rows_threads, int rows_lds_bytes, int rows_chunks, const MgkOutputs& out,
                                   hipStream_t stream);
 // ---- separable product (mgk_sep.hip) ------------------------------------------
-// Weak, so that the host code links without the kernels (host-only contexts never get here).
+// Weak, so that the host code links without the kernels (host-only contexts never get here; elsewhere the
+// call fails).
 #define MGK_KERNELS_OPTIONAL __attribute__((weak))
 // Packets (layout L; gptr and total of that packet size) and dense F_k of the n_used graphs of B listed
-// in device memory at `used`, the largest of max_n vertices.
+// at `used` (memory the device can read), the largest of max_n vertices.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L,
                                                     const MgkSepList& list, const MgkSepGraph* used, int n_used, int max_n,
                                                     float* packets, hipStream_t stream);

@@ -437,9 +437,11 @@ hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, cons
         if (e != hipSuccess) return e; \
         hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_DENSE_THREADS), bytes, stream, X, Y, SX, SY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
     }
-    if (np2 <= 256) MGK_SEP_DENSE_GO(1)
-    else if (np2 <= 512) MGK_SEP_DENSE_GO(2)
-    else MGK_SEP_DENSE_GO(4)
+    switch (mgk_sep_dense_tiles(max_n2)) {
+        case 1: MGK_SEP_DENSE_GO(1) break;
+        case 2: MGK_SEP_DENSE_GO(2) break;
+        default: MGK_SEP_DENSE_GO(4)
+    }
 #undef MGK_SEP_DENSE_GO
     return hipGetLastError();
 }

@@ -72,23 +72,28 @@ def compare(torch, solver, wx, wy, const=False, onchip=0):
     return pi, pj, K, log
 
 
-@pytest.mark.parametrize("length_scale", [20.0, 4.0, 1.7, 1.0, 0.7, 0.5, 0.33, 0.22, None])
-def test_every_division_of_the_rank(torch, solver, length_scale):
+def forms(log):
+    """Features per pass (sparse form) or tiles per wavefront (dense form), rank and passes of every launch."""
+    return {(k, int(a), int(r), int(p or 1)) for k, a, r, p in
+            re.findall(r"mgk_sep_(xmv|dense)_kernel<(\d+)> rank=(\d+)(?: passes=(\d+))?", log)}
+
+
+@pytest.mark.parametrize("length_scale,division", [(20.0, (4, 2, 1)), (4.0, (4, 3, 1)), (1.7, (4, 4, 1)), (1.0, (5, 5, 1)), (0.7, (6, 6, 1)),
+                                                   (0.5, (7, 7, 1)), (0.44, (4, 8, 2)), (0.33, (5, 10, 2)), (0.25, (6, 12, 2)),
+                                                   (0.22, (7, 13, 2)), (0.185, (5, 15, 3)), (None, (1, 1, 1))])
+def test_every_division_of_the_rank(torch, solver, length_scale, division):
     """Short length scales take more features, in passes of 4 to 7; the constant kernel takes one."""
     wb = er(1, (33, 47, 64), 0.25)
     wb.params = dataclasses.replace(PARAMS, length_scale=length_scale or 1.0)
     *_, log = compare(torch, solver, wb, wb, const=length_scale is None)
-    assert "mgk_sep" in log
-    ranks = {int(r) for r in re.findall(r"rank=(\d+)", log)}
-    assert len(ranks) == 1
-    assert ranks == {1} if length_scale is None else min(ranks) >= 2
+    assert forms(log) == {("xmv",) + division}
 
 
 @pytest.mark.parametrize("density", [0.06, 0.5, 1.0])
 @pytest.mark.parametrize("sizes", [(15, 16, 17), (31, 33, 63), (64, 65, 127), (129, 130)])
 def test_edges_of_tiles_against_the_oracle(torch, solver, sizes, density):
     """Rows in 16s, columns in 4s and 64s; the batch ends with vertices without edges, which have no
-    packets.  At the low density the direct product is the cheaper one for graphs this small."""
+    packets.  At the low density the direct product is the cheaper one for the smaller of these graphs."""
     wb = er(sum(sizes), sizes, density)
     lone = W.erdos_renyi_batch(np.random.default_rng(3), 1, 21, 21, 0.5, (0.5, 1.0), (0.0, 1.0), 4, PARAMS)
     keep = (lone.src < 16) & (lone.dst < 16)   # five vertices without edges: a whole group of four
@@ -98,24 +103,64 @@ def test_edges_of_tiles_against_the_oracle(torch, solver, sizes, density):
     pi, pj, K, log = compare(torch, solver, wb, wb)
     once = (pi <= pj) & (wb.nnz()[pi] * wb.nnz()[pj] < 2e7)   # the oracle evaluates every pair of nonzeros
     np.testing.assert_allclose(K[once], C.pairs(wb, pi[once], pj[once], tier=1), rtol=RTOL)
-    if density >= 0.5:
-        assert "mgk_sep" in log
+    assert forms(log) == (set() if density < 0.5 and max(sizes) < 100 else {("xmv", 5, 5, 1)})
 
 
-@pytest.mark.parametrize("sizes,const", [((145, 159, 161), False), ((192, 193), False), ((290,), False), ((191, 225), True)])
-def test_dense_form_at_edges_of_its_tiles(torch, solver, sizes, const):
-    """32 rows by 64 columns; one and two tiles of columns per wavefront."""
-    wb = er(sum(sizes), sizes, 1.0)
+@pytest.mark.parametrize("sizes,const,tiles", [((145, 159, 161), False, 1), ((192, 193), False, 1), ((290,), False, 2), ((191, 225), True, 1),
+                                               ((511, 449), False, 2), ((513,), False, 4), ((600, 577), True, 4)])
+def test_dense_form_at_edges_of_its_tiles(torch, solver, sizes, const, tiles):
+    """32 rows by 64 columns; one, two and four tiles of columns per wavefront."""
+    wb = er(sum(sizes), sizes, 1.0 if max(sizes) < 500 else 0.6)
     *_, log = compare(torch, solver, wb, wb, const=const)
-    assert "mgk_sep_dense_kernel" in log
+    assert forms(log) == {("dense", tiles, 1 if const else 5, 1)}
+
+
+def test_dense_form_at_its_largest_size(torch, solver):
+    """1024 columns: all four tiles of every wavefront, the most LDS.  One column more has no dense form."""
+    wx, wy = er(11, (1030,), 0.2), er(12, (1024, 1025), 0.2)
+    *_, log = compare(torch, solver, wx, wy)
+    assert forms(log) == {("dense", 4, 5, 1)} and "mgk_large_xmv_rows" in log
+
+
+@pytest.mark.parametrize("sizes,length_scale,division", [((276,), 1.0, (5, 5, 1)), ((277, 300), 1.0, (4, 5, 2)), ((486, 487), 1.0, (4, 5, 2)),
+                                                         ((300,), 0.25, (4, 12, 3)), ((480,), 0.185, (4, 15, 4))])
+def test_sparse_form_where_few_features_fit(torch, solver, sizes, length_scale, division):
+    """T of more than 276 columns leaves room for four features a pass; 487 columns are the most."""
+    wb = er(sum(sizes), sizes, 0.2)
+    wb.params = dataclasses.replace(PARAMS, length_scale=length_scale)
+    *_, log = compare(torch, solver, wb, wb)
+    assert forms(log) == {("xmv",) + division}
+
+
+def test_features_of_some_graphs_of_a_batch(torch, solver):
+    """Pairs of a few graphs among others, each graph in several pairs and on both sides."""
+    wx, wy = er(21, (40, 70, 150, 33, 64, 129), 0.3), er(22, (48, 150, 100, 35), 0.3)
+    solver.configure(PARAMS)
+    solver.set_solver(1e-6, 0)
+    solver.set_onchip_limit(0)
+    try:
+        X, Y = solver.load_batch(wx), solver.load_batch(wy)
+        for pi, pj in (([4, 1, 4, 5], [3, 3, 0, 2]), ([2], [1]), ([5, 0], [0, 3])):
+            pi, pj = np.array(pi, np.int32), np.array(pj, np.int32)
+            K, x, log = solve(torch, solver, X, Y, wx, wy, pi, pj, M.TILE_AUTO)
+            Kd, xd, _ = solve(torch, solver, X, Y, wx, wy, pi, pj, M.TILE_SPARSE)
+            assert forms(log) == {("xmv", 5, 5, 1)}
+            np.testing.assert_allclose(K, Kd, rtol=RTOL_PATHS)
+            assert np.linalg.norm(x - xd) <= RTOL_PATHS * np.linalg.norm(xd)
+        X.free()
+        Y.free()
+    finally:
+        solver.set_tile_path(M.TILE_AUTO)
+        solver.set_onchip_limit(16384)
 
 
 def test_two_batches_of_unlike_sizes_and_label_ranges(torch, solver):
     """Graphs of two batches, the larger one on either side, labels of one outside the other's range."""
     wx, wy = er(5, (20, 90, 40), 0.2), er(6, (70, 33), 0.4)
     wy.edge_label = (wy.edge_label + 0.8).astype(np.float32)
-    compare(torch, solver, wx, wy)
-    compare(torch, solver, wy, wx)
+    for a, b in ((wx, wy), (wy, wx)):
+        *_, log = compare(torch, solver, a, b)
+        assert forms(log) == {("xmv", 7, 7, 1)}
 
 
 def test_calls_with_lists_of_their_own_are_refused_while_a_graph_is_recorded(torch, solver):
@@ -125,6 +170,8 @@ def test_calls_with_lists_of_their_own_are_refused_while_a_graph_is_recorded(tor
     solver.set_solver(1e-6, 0)
     B = solver.load_batch(wb)
     pi, pj = np.array([0, 1], np.int32), np.array([1, 1], np.int32)
+    i_dev, j_dev = torch.from_numpy(pi).cuda(), torch.from_numpy(pj).cuda()
+    pairs_dev = lambda X, Y, i, j, K: solver.pairs_dev(X, Y, i_dev, j_dev, K)
     K = torch.zeros(2, dtype=torch.float32, device="cuda")
     solver.pairs(B, B, pi, pj, K)
     torch.cuda.synchronize()
@@ -133,7 +180,7 @@ def test_calls_with_lists_of_their_own_are_refused_while_a_graph_is_recorded(tor
     with torch.cuda.stream(stream):
         graph.capture_begin()
         try:
-            for call in (solver.pairs, solver.pairs_noalloc):
+            for call in (solver.pairs, solver.pairs_noalloc, pairs_dev):
                 with pytest.raises(M.MgkError, match="captur"):
                     call(B, B, pi, pj, K)
             K.add_(0.0)
