@@ -425,7 +425,8 @@ public:
             return;
         }
         const bool staged = std::any_of(std::begin(staging.slot), std::end(staging.slot), [](const Staging::Slot& s) { return s.open; });
-        if (was_[0] && was_[1] && !staged) return;
+        // nothing to gain: freeing waits already, or the batch is compared with itself, hardly just once
+        if (!staged && ((was_[0] && was_[1]) || b_[0] == b_[1])) return;
         try {
             auto end = std::make_shared<CallEnd>();
             end->memory = b_[0]->memory;
@@ -1366,19 +1367,22 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         }
         return used[k][(size_t)entry[k][(size_t)g]].at;
     };
-    for (MgkLargePair& P : pairs) {
-        P.f1 = features(0, P.g1);
-        P.f2 = features(sides - 1, P.g2);
+    std::vector<MgkSepAt> feat;
+    feat.reserve(pairs.size());
+    for (const MgkLargePair& P : pairs) {
+        const int64_t f1 = features(0, P.g1);
+        feat.push_back({f1, features(sides - 1, P.g2)});
     }
-    // pair records, their zeroed states and the counters of a call are one block and one copy; the graph lists
-    // follow them in pinned memory
+    // pair records, their zeroed states, the counters and the places of the features are one block and one copy;
+    // the graph lists follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
     const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
-    const size_t used_at[2] = {active_at + 64, active_at + 64 + used[0].size() * sizeof(MgkSepGraph)};
+    const size_t feat_at = active_at + 64, copied = feat_at + feat.size() * sizeof(MgkSepAt);
+    const size_t used_at[2] = {copied, copied + used[0].size() * sizeof(MgkSepGraph)};
     const size_t rec_bytes = used_at[1] + used[1].size() * sizeof(MgkSepGraph);
     mgk_status st;
     if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
-    if ((st = ensure(ctx, ctx->lpairs, used_at[0])) != MGK_OK) return st;
+    if ((st = ensure(ctx, ctx->lpairs, copied)) != MGK_OK) return st;
     if (!ctx->active_host) MGK_HIP(ctx, hipHostMalloc((void**)&ctx->active_host, 64, hipHostMallocDefault));
     struct InUse {
         bool& flag;
@@ -1399,8 +1403,9 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     Staging::Slot* slot;
     if ((st = staging_slot(ctx, rec_bytes, true, stream, &slot)) != MGK_OK) return st;
     char* rec = static_cast<char*>(slot->p);
-    memset(rec, 0, rec_bytes);
+    memset(rec, 0, feat_at);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
+    memcpy(rec + feat_at, feat.data(), feat.size() * sizeof(MgkSepAt));
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
     staging_copied(slot, stream);
@@ -1412,16 +1417,17 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
                              : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], list, (int)used[k].size(), max_n[k], (float*)ctx->sep_packets[k].p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
-    MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, used_at[0], hipMemcpyHostToDevice, stream));
+    MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, copied, hipMemcpyHostToDevice, stream));
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
     MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
     int* dactive = (int*)((char*)ctx->lpairs.p + active_at);
     float* vec = (float*)ctx->vec.p;
 
+    const MgkSepAt* dfeat = (const MgkSepAt*)((char*)ctx->lpairs.p + feat_at);
     auto product = [&](int it, bool check_only) {
-        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dstate, vec, prm, n_pairs,
+        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                             max_n1, max_n2, it, check_only, stream)
-                     : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dstate, vec, prm, n_pairs,
+                     : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                           max_n1, max_n2, it, check_only, stream);
     };
     hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, stream);

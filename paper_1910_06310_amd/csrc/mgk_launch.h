@@ -165,11 +165,11 @@ MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, 
 // y = XMV(p) and p^T a of iteration `it` for every pair that still iterates (check_only: y alone, for
 // the pairs marked by mgk_launch_large_outputs).  max_n1, max_n2: largest outer and inner graph.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
-                                                   const MgkSepLayout& L, const MgkLargePair* pairs, MgkPairState* state,
+                                                   const MgkSepLayout& L, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state,
                                                    float* vec, const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                    bool check_only, hipStream_t stream);
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
-                                                     int rank, const MgkLargePair* pairs, MgkPairState* state, float* vec,
+                                                     int rank, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec,
                                                      const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                      bool check_only, hipStream_t stream);
 // The two kernels over the vectors that follow a product which has already formed p^T a and

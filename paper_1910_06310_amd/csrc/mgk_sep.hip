@@ -126,7 +126,7 @@ __device__ __forceinline__ void clear_sums(MgkPairState& st, int it) {
 // (RK <= 7) fits in LDS up to 276 columns and the coefficients of a column serve a whole row of 16 lanes.
 template <int RK, int G>
 __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY,
-                                                           MgkSepLayout L, const MgkLargePair* pairs,
+                                                           MgkSepLayout L, const MgkLargePair* pairs, const MgkSepAt* feat,
                                                            MgkPairState* state, float* vec, MgkParams prm,
                                                            int n_pairs, int blocks, int it, int check_only) {
     extern __shared__ __align__(16) float lds[];
@@ -137,6 +137,7 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
     MgkPairState& st = state[pair];
     if (check_only ? !st.check : st.done) return;
     const MgkLargePair P = pairs[pair];
+    const MgkSepAt F = feat[pair];
     const int i0 = blk * MGK_SEP_ROWS;
     if (i0 >= P.n1) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -160,14 +161,14 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
         for (int ii = wave; ii < rows; ii += NW) {
             const int grp = (i0 + ii) >> 2;
             const int gb = gp1[grp];
-            const float* pk = SX.packets + ((int64_t)q * SX.total + P.f1 + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
+            const float* pk = SX.packets + ((int64_t)q * SX.total + F.f1 + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
             stage1_row<RK, G>(pk, gp1[grp + 1] - gb, PGlobal{reinterpret_cast<const char*>(p), (uint32_t)n2 * 4u}, n2, lane,
                               slabs, (RK == 1 ? 4u : 16u) * (uint32_t)ii);
         }
         __syncthreads();
         // ---- stage 2: 16 rows x 4 columns per task; the packets of the next task are in
         //      flight during this one
-        const float* pk2 = SY.packets + ((int64_t)q * SY.total + P.f2) * 64 + lane;
+        const float* pk2 = SY.packets + ((int64_t)q * SY.total + F.f2) * 64 + lane;
         const uint32_t lbase = (RK == 1 ? 4u : 16u) * (uint32_t)(lane & 15);
         float cn[8];
         int gb = gp2[min(wave, groups2 - 1)], steps = gp2[min(wave, groups2 - 1) + 1] - gb;
@@ -225,7 +226,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // 256-vertex graphs, 132 ms per call with the tile-pair kernel, 1.68 ms with this.
 template <int NT>
 __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
-                                                            MgkSepList SY, int rank, const MgkLargePair* pairs,
+                                                            MgkSepList SY, int rank, const MgkLargePair* pairs, const MgkSepAt* feat,
                                                             MgkPairState* state, float* vec, MgkParams prm,
                                                             int n_pairs, int blocks, int it, int check_only) {
     extern __shared__ __align__(16) float lds[];   // T_k, 32 rows of stride tp
@@ -235,6 +236,7 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
     MgkPairState& st = state[pair];
     if (check_only ? !st.check : st.done) return;
     const MgkLargePair P = pairs[pair];
+    const MgkSepAt F = feat[pair];
     const int i0 = blk * MGK_SEP_DENSE_ROWS;
     if (i0 >= P.n1) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -242,8 +244,8 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
     if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
     const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
-    const float* F1 = SX.dense + P.f1 + i0;
-    const float* F2 = SY.dense + P.f2;
+    const float* F1 = SX.dense + F.f1 + i0;
+    const float* F2 = SY.dense + F.f2;
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = vec + P.vec + 4 * (int64_t)P.npad;
     const int tp = np2 + 1;
@@ -398,7 +400,7 @@ hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S,
 }
 
 hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
-                              const MgkSepLayout& L, const MgkLargePair* pairs, MgkPairState* state, float* vec,
+                              const MgkSepLayout& L, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec,
                               const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
     const int blocks = (max_n1 + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
     const dim3 grid((unsigned)mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS));
@@ -410,7 +412,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
         static bool configured = false; \
         hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
         if (e != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_THREADS), bytes, stream, X, Y, SX, SY, L, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_THREADS), bytes, stream, X, Y, SX, SY, L, pairs, feat, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
         break; \
     }
     switch (L.rk) {
@@ -422,7 +424,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
 }
 
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
-                                const MgkLargePair* pairs, MgkPairState* state, float* vec, const MgkParams& prm,
+                                const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
     const int blocks = (max_n1 + MGK_SEP_DENSE_ROWS - 1) / MGK_SEP_DENSE_ROWS;
     const dim3 grid((unsigned)mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS));
@@ -435,7 +437,7 @@ hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, cons
         static bool configured = false; \
         hipError_t e = set_lds(reinterpret_cast<const void*>(kern), &configured); \
         if (e != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_DENSE_THREADS), bytes, stream, X, Y, SX, SY, rank, pairs, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
+        hipLaunchKernelGGL(kern, grid, dim3(MGK_SEP_DENSE_THREADS), bytes, stream, X, Y, SX, SY, rank, pairs, feat, state, vec, prm, n_pairs, blocks, it, check_only ? 1 : 0); \
     }
     switch (mgk_sep_dense_tiles(max_n2)) {
         case 1: MGK_SEP_DENSE_GO(1) break;

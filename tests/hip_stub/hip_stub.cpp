@@ -239,13 +239,13 @@ hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const
                                int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep pack", s, &B, nullptr, n_used); }
 hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph*, int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep dense pack", s, &B, nullptr, n_used); }
 hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&,
-                              const MgkSepLayout&, const MgkLargePair*, MgkPairState*, float*, const MgkParams&, int n, int max_n1,
+                              const MgkSepLayout&, const MgkLargePair*, const MgkSepAt*, MgkPairState*, float*, const MgkParams&, int n, int max_n1,
                               int, int, bool, hipStream_t s) {
     if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 15) / 16) * 1024 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
     return launched("sep", s, &X, &Y, n);
 }
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&, int,
-                                const MgkLargePair*, MgkPairState*, float*, const MgkParams&, int n, int max_n1, int, int, bool, hipStream_t s) {
+                                const MgkLargePair*, const MgkSepAt*, MgkPairState*, float*, const MgkParams&, int n, int max_n1, int, int, bool, hipStream_t s) {
     if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 31) / 32) * 256 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
     return launched("sep dense", s, &X, &Y, n);
 }
