@@ -1011,20 +1011,23 @@ enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kP
 bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
-// run.  Two bounds, the larger counts.  Throughput of a full chip, fitted to iterations of 64 pairs of random
-// graphs (n = 128 to 256, densities 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product
-// evaluates 7 entries per clk, stages the rows of p and pays 6 clk per element in dependent loads; the sparse
-// separable product does 20 multiply-adds per clk and writes and reads T; the dense one does 42 per clk and has
-// work for all four of its wavefronts from 256 columns on.  And the time of one workgroup, in which all others
-// of the call can run where it has few pairs: a row of the outer graph (row-staged; 1.2 times its share of the
-// work, or 3200 clk per nonzero of the row in dependent loads, and then the throughput bound on top), 16 rows
-// (sparse; 10 000 clk and 0.9 times its share), 32 rows (dense, alone on its compute unit 60 multiply-adds per
-// clk).  Measured, us per call, row-staged / sparse / dense, rank 5: 1 pair of n = 256 density 0.01
-// 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs 2090 / 1842 / 7344,
-// 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  n = 480 density 0.03, 1, 2, 16 pairs:
-// 478 / 530, 629 / 557, 2488 / 1122.  n = 600 density 0.1, 1, 2, 4, 16 pairs, row-staged / dense: 2515 / 5206,
-// 4112 / 5264, 7394 / 5294, 26957 / 10472; n = 1000 density 0.05: 4592 / 11290, 8246 / 11366, 15217 / 11569,
-// 56425 / 25971.
+// run.  Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities
+// 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages
+// the rows of p and pays 6 clk per element in dependent loads; the sparse separable product does 20 multiply-adds
+// per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
+// from 256 columns on.  A few pairs leave the chip idle: then the time of a workgroup counts, as many times as
+// workgroups follow each other on a compute unit.  It is a row of the outer graph (row-staged: 5000 clk and 1.6
+// times its share of the work, behind the rest), 16 rows (sparse: 45 clk per column and pass and 1.05 times its
+// share), 32 rows (dense: 60 multiply-adds per clk).  The direct products expand the lists of both batches, whichever
+// graphs the pairs have: 0.4 ns per nonzero or 1.2 per octile, over about 12 iterations.
+// Measured, us per call, row-staged / sparse / dense, rank 5, one batch of 128 graphs: 1 pair of n = 256 density
+// 0.01 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs 2090 / 1842 /
+// 7344, 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  8 graphs of n = 600 density 0.1, 1, 2, 4, 16
+// pairs, row-staged / dense: 2515 / 5206, 4112 / 5264, 7394 / 5294, 26957 / 10472; n = 1000 density 0.05: 4592 /
+// 11290, 8246 / 11366, 15217 / 11569, 56425 / 25971.  Geometric graphs of degree 12, row-staged / sparse, 2, 4, 8,
+// 16 pairs: n = 140 rank 9 220 / 305, 233 / 311, 281 / 319, 352 / 327; n = 300 rank 5 358 / 439, 454 / 454, 622 / 486,
+// 934 / 686, rank 13 307 / 569, 381 / 583, 515 / 616, 741 / 816; n = 480 rank 11 516 / 704, 773 / 744, 1207 / 913,
+// 2091 / 1403.
 struct LargeCost {
     double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
@@ -1037,10 +1040,12 @@ int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
     return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
 }
 
-// rank 0: no separable form.  n_pairs: pairs of the call that may run beside this one.  Forming the features is left out: only the
-// graphs of the pairs get them, which takes 1 % of what the products of a pair take.
-LargeCost large_cost(const mgk_ctx* ctx, int rank, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb, int64_t n_pairs) {
-    constexpr double kComputeUnits = 256;
+// rank 0: no separable form.  L: sep_layout of the pair.  n_pairs: pairs of the call that may run beside this one.  n_tiles: octiles of
+// both batches, or a third of the nonzeros where that is less.  Forming the features is left out: only the graphs of the pairs get them, which takes 1 % of
+// what the products of a pair take.
+LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb,
+                     int64_t n_pairs, int64_t n_tiles) {
+    constexpr double kUnits = 256;   // compute units
     const MgkGraphDesc &o = A->graphs[(size_t)ga], &i = B->graphs[(size_t)gb];
     auto fits = [&](bool dense) { return feature_bytes(A, ga, rank, dense) + feature_bytes(B, gb, rank, dense) <= kMaxFeatureBytes; };
     LargeCost C;
@@ -1049,19 +1054,32 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const mgk_batch* A, int32_t g
         C.clk[C.best] = 0.0;   // no choice
         return C;
     }
-    const double alone = kComputeUnits / (double)n_pairs;   // compute units a pair has to itself
+    // Pairs small enough for the on-chip solver come here where the caller has lowered its limit; their
+    // workgroups take less time than the launches of an iteration: throughput alone decides.
+    const double pairs = o.n * (int64_t)i.n <= MGK_SMALL_MAX_N ? INFINITY : (double)n_pairs;
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
-    const double entries = (double)o.nnz * i.nnz / 7.0 + 0.5 * (double)o.nnz * i.n;
-    C.clk[C.best] = entries + 6.0 * N + alone * std::max(1.2 * entries, 3200.0 * o.nnz) / o.n;
-    const MgkSepLayout L = sep_layout(rank, i.n);
-    const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255;
-    const double sparse = (double)L.rk * L.passes * one_sided / 20.0, dense = rank * op * ip * ((double)o.n + i.n);
+    const double entries = (double)o.nnz * i.nnz * (1.0 / 7.0) + 0.5 * (double)o.nnz * i.n;
+    C.clk[C.best] = entries + 6.0 * N + 61.0 * (double)n_tiles / pairs + kUnits / pairs * (5000.0 + 1.6 * entries / o.n);
+    // clocks of a pair's share of all compute units while the workgroups of all pairs run
+    auto workgroups = [&](double blocks, int64_t lds_bytes, int64_t most, double clk) {
+        const double side_by_side = kUnits * (double)std::min<int64_t>(most, MGK_LDS_LIMIT_BYTES / std::max<int64_t>(lds_bytes, 1));
+        return std::isinf(pairs) ? 0.0 : kUnits / pairs * std::ceil(blocks * pairs / side_by_side) * clk;
+    };
+    const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255, np = (i.n + 63) & ~63;
+    const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0), dense = rank * op * ip * ((double)o.n + i.n);
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
-    if (may_sparse) C.clk[kPathSep] = std::max(sparse + 8.0 * N, alone * (10000.0 + 0.9 * sparse / ((o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS)));
-    if (may_dense) C.clk[kPathSepDense] = std::max(dense / 42.0, alone * dense / 60.0 / (op / MGK_SEP_DENSE_ROWS));
+    if (may_sparse) {
+        const double blocks = (o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
+        C.clk[kPathSep] = std::max(sparse + 8.0 * N, workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
+                                                                45.0 * i.n * L.passes + 1.05 * sparse / blocks));
+    }
+    if (may_dense) {
+        const double blocks = op / MGK_SEP_DENSE_ROWS;
+        C.clk[kPathSepDense] = std::max(dense * (1.0 / 42.0), workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, dense / 60.0 / blocks));
+    }
     if (!may_sparse && !may_dense) return C;
     // of the two forms the one with the higher throughput
-    const int form = may_dense && (!may_sparse || dense / 42.0 < sparse + 8.0 * N) ? kPathSepDense : kPathSep;
+    const int form = may_dense && (!may_sparse || dense * (1.0 / 42.0) < sparse + 8.0 * N) ? kPathSepDense : kPathSep;
     if (C.clk[form] < C.clk[C.best]) C.best = form;
     return C;
 }
@@ -1352,27 +1370,28 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     const int gi = L.per_packet == 8 ? 1 : 0, sides = Bb == A ? 1 : 2;
     const mgk_batch* bt[2] = {A, Bb};
     std::vector<MgkSepGraph> used[2];
-    std::vector<int32_t> entry[2];   // of each graph in that list
-    int64_t size[2] = {0, 0};        // floats of dense F_k, or packet steps of a pass
+    std::vector<int64_t> place[2];   // of the features of each graph, -1: not in use
+    int64_t size[2] = {0, 0};        // floats of dense F_k by the rank, or packet steps of a pass
     int32_t max_n[2] = {1, 1};
-    for (int k = 0; k < sides; ++k) entry[k].assign((size_t)bt[k]->n_graphs, -1);
-    auto features = [&](int k, int32_t g) {
-        if (entry[k][(size_t)g] < 0) {
+    for (int k = 0; k < sides; ++k) place[k].assign((size_t)bt[k]->n_graphs, -1);
+    for (const MgkLargePair& P : pairs) {
+        place[0][(size_t)P.g1] = 0;
+        place[sides - 1][(size_t)P.g2] = 0;
+    }
+    for (int k = 0; k < sides; ++k)
+        for (int32_t g = 0; g < bt[k]->n_graphs; ++g) {
+            int64_t& at = place[k][(size_t)g];
+            if (at < 0) continue;
             const int32_t n = bt[k]->graphs[(size_t)g].n;
             const int64_t np = (n + 63) & ~63, steps0 = bt[k]->packet_off[gi][(size_t)g], steps1 = bt[k]->packet_off[gi][(size_t)g + 1];
-            entry[k][(size_t)g] = (int32_t)used[k].size();
-            used[k].push_back({dense ? size[k] : size[k] - steps0, g, 0});
-            size[k] += dense ? np * np * S.rank : steps1 - steps0;
+            at = dense ? size[k] * S.rank : size[k] - steps0;
+            used[k].push_back({dense ? size[k] : at, g, 0});
+            size[k] += dense ? np * np : steps1 - steps0;
             max_n[k] = std::max(max_n[k], n);
         }
-        return used[k][(size_t)entry[k][(size_t)g]].at;
-    };
     std::vector<MgkSepAt> feat;
     feat.reserve(pairs.size());
-    for (const MgkLargePair& P : pairs) {
-        const int64_t f1 = features(0, P.g1);
-        feat.push_back({f1, features(sides - 1, P.g2)});
-    }
+    for (const MgkLargePair& P : pairs) feat.push_back({place[0][(size_t)P.g1], place[sides - 1][(size_t)P.g2]});
     // pair records, their zeroed states, the counters and the places of the features are one block and one copy;
     // the graph lists follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
@@ -1394,7 +1413,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         sl[k] = bt[k]->sep[gi];
         sl[k].total = dense ? 0 : (int32_t)size[k];
         DevBuf& buf = dense ? ctx->sep_dense[k] : ctx->sep_packets[k];
-        const size_t floats = dense ? (size_t)size[k] : ((size_t)L.passes * size[k] + 1) * 64;   // stage 2 may load one step past the last
+        const size_t floats = dense ? (size_t)size[k] * S.rank : ((size_t)L.passes * size[k] + 1) * 64;   // stage 2 may load one step past the last
         if ((st = ensure(ctx, buf, std::max<size_t>(256, floats * sizeof(float)))) != MGK_OK) return st;
         (dense ? sl[k].dense : sl[k].packets) = (const float*)buf.p;
     }
@@ -1403,20 +1422,22 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     Staging::Slot* slot;
     if ((st = staging_slot(ctx, rec_bytes, true, stream, &slot)) != MGK_OK) return st;
     char* rec = static_cast<char*>(slot->p);
-    memset(rec, 0, feat_at);
-    memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
-    memcpy(rec + feat_at, feat.data(), feat.size() * sizeof(MgkSepAt));
-    reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
     staging_copied(slot, stream);
-    // features of the graphs' nonzeros (they depend on the edge kernel's parameters); the kernels read the
-    // graph lists where they are, in pinned memory, so that they do not wait for the copy
+    // features of the graphs' nonzeros (they depend on the edge kernel's parameters).  The kernels do not wait
+    // for the copy: they read the list of all graphs from the batch, or one of some of them from pinned memory
+    // (for all 128 graphs of 64 pairs that took 15 us more).
     for (int k = 0; k < sides; ++k) {
-        const MgkSepGraph* list = (const MgkSepGraph*)(rec + used_at[k]);
+        const bool whole = (int32_t)used[k].size() == bt[k]->n_graphs;
+        const MgkSepGraph* list = whole ? sl[k].whole : (const MgkSepGraph*)(rec + used_at[k]);
         hipError_t e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, list, (int)used[k].size(), max_n[k], (float*)ctx->sep_dense[k].p, stream)
                              : mgk_launch_sep_pack(bt[k]->dev, S, L, sl[k], list, (int)used[k].size(), max_n[k], (float*)ctx->sep_packets[k].p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
+    memset(rec, 0, feat_at);
+    memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
+    memcpy(rec + feat_at, feat.data(), feat.size() * sizeof(MgkSepAt));
+    reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, copied, hipMemcpyHostToDevice, stream));
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;
     MgkPairState* dstate = (MgkPairState*)((char*)ctx->lpairs.p + state_at);
@@ -1524,11 +1545,17 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             }
             choices.push_back(c);
         }
+    const int64_t n_tiles = std::min(X->n_tiles, X->nnz / 3) + (X == Y ? 0 : std::min(Y->n_tiles, Y->nnz / 3));
     auto costs_at = [&](int rank) {
         std::vector<LargeCost> costs;
         costs.reserve(choices.size());
-        for (const Choice& c : choices)
-            costs.push_back(large_cost(ctx, rank, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size()));
+        MgkSepLayout L{};
+        int32_t n2 = -1;   // of L: pairs often come with the same
+        for (const Choice& c : choices) {
+            if (rank > 0 && c.sep.n2 != n2) L = sep_layout(rank, n2 = c.sep.n2);
+            costs.push_back(large_cost(ctx, rank, L, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size(),
+                                       n_tiles));
+        }
         return costs;
     };
     const MgkSepBasis none{}, *basis = &none;
@@ -1548,7 +1575,9 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     for (size_t k = 0; k < choices.size(); ++k) {
         const Choice& c = choices[k];
         const int path = costs[k].best;
-        lists[is_sep(path) ? c.sep_swapped : c.swapped][path].push_back(&c);
+        std::vector<const Choice*>& list = lists[is_sep(path) ? c.sep_swapped : c.swapped][path];
+        if (list.empty()) list.reserve(choices.size() - k);
+        list.push_back(&c);
     }
     auto direct = [&](const std::vector<MgkLargePair>& pairs, int swapped, bool dense) {
         return swapped ? solve_large(ctx, Y, X, 1, 0, pairs, dense, out, stream, prm, weighted)
@@ -1573,6 +1602,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             size_t first = 0;
             while (first < all.size()) {
                 std::vector<MgkLargePair> group;
+                group.reserve(std::min(all.size() - first, kMaxPairsPerGroup));
                 size_t last = first;
                 int64_t floats = 0, features = 0;
                 int max_n1 = 1, max_n2 = 1;
@@ -1895,6 +1925,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     std::vector<MgkEntry> list_outer, list_inner;   // nonzero lists for the register-resident solver
     std::vector<int32_t> gptr[2], deg_order;       // packets of the separable product, rows by degree
     std::vector<int32_t> qoff((size_t)n_graphs);
+    std::vector<MgkSepGraph> whole;
+    whole.reserve((size_t)n_graphs);
+    int64_t dense_floats = 0;
     constexpr int kPerPacket[2] = {2, 8};
     for (auto& v : gptr) v.reserve((size_t)(tot_v / 4 + 2 * (int64_t)n_graphs));
     for (auto& v : B->packet_off) v.assign((size_t)n_graphs + 1, 0);
@@ -2124,6 +2157,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
                 gptr[q].push_back(packets[q]);
                 B->packet_off[q][(size_t)g + 1] = packets[q];
             }
+            const int64_t np = (n + 63) & ~63;
+            whole.push_back({dense_floats, g, 0});
+            dense_floats += np * np;
         }
         gd.loff = (int32_t)lanes_total;
         {
@@ -2240,7 +2276,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     const size_t o_ao = blob.add(attr_outer);
     const size_t o_ai = blob.add(attr_inner);
     const size_t o_pk[2] = {blob.add(gptr[0]), blob.add(gptr[1])};
-    const size_t o_do = blob.add(deg_order), o_qo = blob.add(qoff);
+    const size_t o_do = blob.add(deg_order), o_qo = blob.add(qoff), o_wh = blob.add(whole);
     const size_t o_sd = blob.add(B->sell_desc);
     const size_t o_sv = blob.add(sell_vtx);
     const size_t o_sn = blob.add(sell_nbr);
@@ -2290,6 +2326,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     for (int q = 0; q < 2; ++q) {
         B->sep[q].qoff = reinterpret_cast<const int32_t*>(base + o_qo);
         B->sep[q].gptr = reinterpret_cast<const int32_t*>(base + o_pk[q]);
+        B->sep[q].whole = reinterpret_cast<const MgkSepGraph*>(base + o_wh);
         B->sep[q].deg_order = reinterpret_cast<const int32_t*>(base + o_do);
     }
     B->dev.sell_desc = reinterpret_cast<const MgkSellDesc*>(base + o_sd);

@@ -404,20 +404,23 @@ static inline MGK_HD int32_t mgk_sep_dense_tiles(int32_t max_n2) { return max_n2
 // has steps at + gptr[qoff[g] + t] .. at + gptr[qoff[g] + t + 1], gptr counting over the whole batch and
 // `at` the graph's MgkSepGraph::at.  One step more than all passes have is allocated: stage 2 loads the
 // first packet of a group before it looks whether it has one.
+struct MgkSepGraph;
 struct MgkSepList {
     const int32_t* qoff;        // per graph: first entry in gptr
     const int32_t* gptr;        // per four vertices of a graph, and one more per graph
+    const MgkSepGraph* whole;   // all graphs in order, `at` as for dense F_k (0 for packets)
     const int32_t* deg_order;   // per graph (index voff): its vertices by descending number of nonzeros
     const float* packets;
     const float* dense;         // dense F_k
     int32_t total;
 };
-// A graph whose features a call forms, and where they are: dense F_k from float `at` on, packets see above.
+// A graph whose features a call forms, and where they are: dense F_k from float `at` times the rank on,
+// packets see above.
 struct MgkSepGraph {
     int64_t at;
     int32_t graph, unused;
 };
-// MgkSepGraph::at of the two graphs of a pair; beside the pair's record, which the direct product's kernels
+// Where the features of the two graphs of a pair are (float of F_0, or `at` of the packets); beside the pair's record, which the direct product's kernels
 // read in every workgroup (16 bytes more there: 59.8 -> 60.6 us a product of 64 pairs, n = 256, density 0.01)
 struct MgkSepAt {
     int64_t f1, f2;

@@ -156,7 +156,7 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
 // call fails).
 #define MGK_KERNELS_OPTIONAL __attribute__((weak))
 // Packets (layout L; gptr and total of that packet size) and dense F_k of the n_used graphs of B listed
-// at `used` (memory the device can read), the largest of max_n vertices.
+// at `used` (memory the device can read; list.whole for all of them), the largest of max_n vertices.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout& L,
                                                     const MgkSepList& list, const MgkSepGraph* used, int n_used, int max_n,
                                                     float* packets, hipStream_t stream);

@@ -37,11 +37,12 @@ __device__ __forceinline__ float sep_feature(const MgkSepBasis& S, const double*
 // the slab of column j each; absent nonzeros have coefficients 0 and offset 0.  One wavefront
 // per group.
 __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSepBasis S, MgkSepLayout L,
-                                                           MgkSepList list, const MgkSepGraph* used, float* out) {
+                                                           MgkSepList list, const MgkSepGraph* used, int packed, float* out) {
     __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
     for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
     const MgkSepGraph sg = used[blockIdx.y];
+    const int64_t at = packed ? sg.at : 0;   // packets of the whole batch are in order
     const MgkGraphDesc g = B.graphs[sg.graph];
     const int32_t* gptr = list.gptr + list.qoff[sg.graph];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
                 float v = 0.f;
                 if (on && kk < L.rk && k < S.rank) v = w * sep_feature(S, coef, __uint_as_float(e.z), k);
                 if (on && kk == L.rk) v = __uint_as_float(e.y * (uint32_t)L.slab_bytes);
-                out[((int64_t)q * list.total + sg.at + p) * 64 + lane] = v;
+                out[((int64_t)q * list.total + at + p) * 64 + lane] = v;
             }
         }
     }
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, 
     const MgkGraphDesc g = B.graphs[sg.graph];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int np = (g.n + 63) & ~63;
-    float* F = out + sg.at;
+    float* F = out + sg.at * S.rank;
     for (int row = blockIdx.x * 4 + wave; row < np; row += gridDim.x * 4) {
         for (int k = 0; k < S.rank; ++k)
             for (int c = lane; c < np; c += 64) F[((int64_t)k * np + row) * np + c] = 0.f;
@@ -138,6 +139,8 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
     if (check_only ? !st.check : st.done) return;
     const MgkLargePair P = pairs[pair];
     const MgkSepAt F = feat[pair];
+    const float* packets1 = SX.packets + F.f1 * 64;
+    const float* packets2 = SY.packets + F.f2 * 64;
     const int i0 = blk * MGK_SEP_ROWS;
     if (i0 >= P.n1) return;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -161,14 +164,14 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
         for (int ii = wave; ii < rows; ii += NW) {
             const int grp = (i0 + ii) >> 2;
             const int gb = gp1[grp];
-            const float* pk = SX.packets + ((int64_t)q * SX.total + F.f1 + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
+            const float* pk = packets1 + ((int64_t)q * SX.total + gb) * 64 + ((i0 + ii) & 3) * 16 + (lane & 15);
             stage1_row<RK, G>(pk, gp1[grp + 1] - gb, PGlobal{reinterpret_cast<const char*>(p), (uint32_t)n2 * 4u}, n2, lane,
                               slabs, (RK == 1 ? 4u : 16u) * (uint32_t)ii);
         }
         __syncthreads();
         // ---- stage 2: 16 rows x 4 columns per task; the packets of the next task are in
         //      flight during this one
-        const float* pk2 = SY.packets + ((int64_t)q * SY.total + F.f2) * 64 + lane;
+        const float* pk2 = packets2 + (int64_t)q * SY.total * 64 + lane;
         const uint32_t lbase = (RK == 1 ? 4u : 16u) * (uint32_t)(lane & 15);
         float cn[8];
         int gb = gp2[min(wave, groups2 - 1)], steps = gp2[min(wave, groups2 - 1) + 1] - gb;
@@ -386,7 +389,7 @@ hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const
     const int gx = (max_n + 15) / 16;
     for (int g0 = 0; g0 < n_used; g0 += 65535)
         hipLaunchKernelGGL(mgk_sep_pack_kernel, dim3(gx, n_used - g0 < 65535 ? n_used - g0 : 65535), dim3(256), 0,
-                           stream, B, S, L, list, used + g0, packets);
+                           stream, B, S, L, list, used + g0, used == list.whole ? 0 : 1, packets);
     return hipGetLastError();
 }
 

@@ -246,14 +246,15 @@ def test_outputs_are_formed_twice_at_most(host):
     host.lib.stub_converge_after(90)   # the first call of a context foresees fewer
     for foreseen in (False, True):
         host.lib.stub_clear_log()
-        assert host.pairs(B, B, [0], [1]) == 0, host.error()
+        assert host.pairs(B, B, [0] * 64, [1] * 64) == 0, host.error()
         assert len(launched(host.log(), "vectors")) >= 90
         assert len(launched(host.log(), "outputs")) == (2 if foreseen else 4)   # two launches each
     host.free(B)
 
 
 @pytest.mark.parametrize("n,k,pairs,kernel", [(600, 30, 1, "direct dense"), (600, 30, 16, "sep dense"), (256, 26, 1, "sep"),
-                                              (480, 7, 1, "direct rows"), (480, 7, 16, "sep")])
+                                              (480, 7, 1, "direct rows"), (480, 7, 16, "sep"),
+                                              (300, 6, 2, "direct rows"), (300, 6, 16, "sep")])
 def test_few_pairs_take_the_product_that_fills_the_chip(host, n, k, pairs, kernel):
     """One pair of 600 vertices has 19 workgroups in the dense separable product and 600 in the row-staged one:
     5.2 ms and 2.5 ms per call; with 16 pairs 10.5 and 27 ms."""
