@@ -25,6 +25,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -380,6 +381,15 @@ def main() -> int:
                       + cached_share * (flops_per_element_pair - 2) * zz)
     traffic = hbm_traffic(wl, args)
     cflops = counted_flops(wl, args)
+    ranks = {int(r) for r in re.findall(r"mgk_sep_\S+ rank=(\d+)", "\n".join(launches))}
+    separable = len(ranks) == 1 and all(f.startswith("mgk_sep") for f in families)
+    if ranks:   # the counters were taken with the direct products
+        traffic = cflops = None
+        executed_flops = executed_per_pair_iter = None
+    if separable:   # multiply-adds of the two one-sided products of every term, nonzeros only
+        n_vtx = wb.sizes().astype(np.float64)
+        executed_flops = 2.0 * ranks.pop() * float((it * (z[pi] * n_vtx[pj] + n_vtx[pi] * z[pj])).sum())
+        executed_per_pair_iter = executed_flops / element_pairs
     out["roofline"] = {
         "bound": "alu",
         "kernel": dominant,
@@ -391,7 +401,7 @@ def main() -> int:
         "peak": FP32_VECTOR_PEAK_TFLOPS,
         "unit": "TFLOP/s",
         "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-        "frac_is": "algorithmic: %d flop per element pair and iteration (the paper's cost model for "
+        "frac_is": ("above 1 where the separable product does less than the " if ranks else "") + "algorithmic: %d flop per element pair and iteration (the paper's cost model for "
                    "this edge kernel) x element pairs / kernel time / peak" % flops_per_element_pair,
         "flops_per_element_pair": flops_per_element_pair,
         "executed_flops_per_element_pair": executed_per_pair_iter,

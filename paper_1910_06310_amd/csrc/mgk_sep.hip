@@ -120,9 +120,10 @@ __device__ __forceinline__ void clear_sums(MgkPairState& st, int it) {
     st.rr[it & 1] = 0.f;
 }
 
-// Bound by the vector ALUs and the LDS about equally: per nonzero and 64 results RK
-// multiply-adds (1.15 RK clk per CU) against 4 RK bytes x 64 from LDS in stage 2.  Measured about 20
-// multiply-adds per clk and CU.  64 pairs of 256-vertex graphs of density 0.2: 13.5 ms with one
+// Per nonzero and 64 results RK multiply-adds (1.15 RK clk per CU) against 4 RK bytes x 64 from LDS in
+// stage 2.  Counters at density 0.2, n = 256: vector ALUs 49 % of their issue slots, LDS 61 %, half of that
+// bank conflicts, wavefronts waiting 78 % of their cycles: with one workgroup per CU the stages follow each
+// other behind barriers.  About 20 multiply-adds per clk and CU.  64 such pairs: 13.5 ms per call with one
 // evaluation per pair of nonzeros, 1.31 ms with this.  16 rows per workgroup so that T of one pass
 // (RK <= 7) fits in LDS up to 276 columns and the coefficients of a column serve a whole row of 16 lanes.
 template <int RK, int G>
@@ -224,8 +225,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // wavefront.  Per k: T_k[32 x n'] = F_k P on the matrix cores, to LDS; y += T_k F'_k^T.  F_k and F'_k
 // are symmetric, so every operand is read along rows (32 lanes = 128 adjacent bytes).
 // Sums are kept in levels of 64 terms to bound the fp32 rounding bias of long running sums.
-// Bound by the matrix cores (128 multiply-adds per clk and CU in fp32) and, with two wavefronts per
-// SIMD, by the latency of the operand loads: about 51 per clk measured on 64 pairs of complete
+// Bound by the matrix cores (128 multiply-adds per clk and CU in fp32; 43 % busy) and, with two wavefronts
+// per SIMD, by the latency of the operand loads: about 51 per clk measured on 64 pairs of complete
 // 256-vertex graphs, 132 ms per call with the tile-pair kernel, 1.68 ms with this.
 template <int NT>
 __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX,
