@@ -57,7 +57,8 @@ struct DevBuf {
 };
 
 // Pinned host memory for what a call copies to the device without waiting: slots in turn, each used
-// again when the call that copied out of it has completed.  All start in one block, allocated with the context.
+// again when the call that copied out of it has completed.  All start in one block, allocated by the first
+// call that needs it (30 us or more, and as much to give back: contexts that never do go without).
 struct CallEnd;
 constexpr size_t kSlotBytes = (size_t)128 << 10;
 struct Staging {
@@ -1013,7 +1014,8 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
 // run.  Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities
 // 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages
-// the rows of p and pays 6 clk per element in dependent loads; the sparse separable product does 20 multiply-adds
+// the rows of p and pays 6 clk per element in dependent loads, and for its entries takes a third longer where
+// measured against the sparse form near the line (5 to 64 pairs of n = 256 to 325); the sparse separable product does 20 multiply-adds
 // per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
 // from 256 columns on.  A few pairs leave the chip idle: then the time of a workgroup counts, as many times as
 // workgroups follow each other on a compute unit.  It is a row of the outer graph (row-staged: 5000 clk and 1.6
@@ -1059,18 +1061,20 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     const double pairs = o.n * (int64_t)i.n <= MGK_SMALL_MAX_N ? INFINITY : (double)n_pairs;
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
     const double entries = (double)o.nnz * i.nnz * (1.0 / 7.0) + 0.5 * (double)o.nnz * i.n;
-    C.clk[C.best] = entries + 6.0 * N + 61.0 * (double)n_tiles / pairs + kUnits / pairs * (5000.0 + 1.6 * entries / o.n);
+    C.clk[C.best] = (std::isinf(pairs) ? 1.0 : 1.35) * entries + 6.0 * N + 61.0 * (double)n_tiles / pairs + kUnits / pairs * (5000.0 + 1.6 * entries / o.n);
     // clocks of a pair's share of all compute units while the workgroups of all pairs run
     auto workgroups = [&](double blocks, int64_t lds_bytes, int64_t most, double clk) {
         const double side_by_side = kUnits * (double)std::min<int64_t>(most, MGK_LDS_LIMIT_BYTES / std::max<int64_t>(lds_bytes, 1));
-        return std::isinf(pairs) ? 0.0 : kUnits / pairs * std::ceil(blocks * pairs / side_by_side) * clk;
+        const double rounds = blocks * pairs / side_by_side;   // the last blocks of a pair have its rows of lowest degree
+        return std::isinf(pairs) ? 0.0 : kUnits / pairs * std::max(1.0, 0.5 * (rounds + std::ceil(rounds))) * clk;
     };
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255, np = (i.n + 63) & ~63;
     const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0), dense = rank * op * ip * ((double)o.n + i.n);
+    const double elements = (L.rk == 1 ? 10.0 : 8.0) * N;
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
     if (may_sparse) {
         const double blocks = (o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
-        C.clk[kPathSep] = std::max(sparse + 8.0 * N, workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
+        C.clk[kPathSep] = std::max(sparse + elements, workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
                                                                 45.0 * i.n * L.passes + 1.05 * sparse / blocks));
     }
     if (may_dense) {
@@ -1079,7 +1083,7 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     }
     if (!may_sparse && !may_dense) return C;
     // of the two forms the one with the higher throughput
-    const int form = may_dense && (!may_sparse || dense * (1.0 / 42.0) < sparse + 8.0 * N) ? kPathSepDense : kPathSep;
+    const int form = may_dense && (!may_sparse || dense * (1.0 / 42.0) < sparse + elements) ? kPathSepDense : kPathSep;
     if (C.clk[form] < C.clk[C.best]) C.best = form;
     return C;
 }
@@ -1133,18 +1137,30 @@ MgkLargePair plan_large(const MgkGraphDesc& a, const MgkGraphDesc& b, int32_t ia
     return P;
 }
 
-// A slot of pinned memory, of at least `bytes`, for copies on `stream`: the next one that is large enough
-// and not in use, else the next one, waited for and grown.  Without may_allocate *out is null where that
-// would allocate.
+// A slot of pinned memory, of at least `bytes`, for copies on `stream`: the next one, grown where it is too
+// small; while its last call is under way another one that is large enough and idle.  Without may_allocate one
+// that is large enough, waited for if need be, or none (*out is null).
 mgk_status staging_slot(mgk_ctx* ctx, size_t bytes, bool may_allocate, hipStream_t stream, Staging::Slot** out) {
     Staging& S = ctx->staging;
     constexpr int kSlots = sizeof(S.slot) / sizeof(S.slot[0]);
     *out = nullptr;
-    int pick = S.next;
-    for (int k = 0; k < kSlots; ++k) {
-        Staging::Slot& s = S.slot[(S.next + k) % kSlots];
-        if (s.cap >= bytes && !s.open && (!s.end || s.end->over())) { pick = (S.next + k) % kSlots; break; }
+    if (!S.block && may_allocate) {
+        MGK_HIP(ctx, hipHostMalloc(&S.block, kSlots * kSlotBytes, hipHostMallocDefault));
+        for (Staging::Slot& s : S.slot) {
+            s.p = (char*)S.block + (size_t)(&s - S.slot) * kSlotBytes;
+            s.cap = kSlotBytes;
+        }
     }
+    int pick = S.next, large = -1;
+    for (int k = 0; k < kSlots; ++k) {
+        const int at = (S.next + k) % kSlots;
+        Staging::Slot& s = S.slot[at];
+        const bool fits = s.cap >= bytes;
+        if (!fits && !(may_allocate && k == 0)) continue;
+        if (fits && large < 0) large = at;
+        if (!s.open && (!s.end || s.end->over())) { pick = at; large = -1; break; }
+    }
+    if (!may_allocate && large >= 0) pick = large;   // all that are large enough are in use
     Staging::Slot& s = S.slot[pick];
     if (bytes > s.cap && !may_allocate) return MGK_OK;
     S.next = (pick + 1) % kSlots;
@@ -1670,19 +1686,9 @@ mgk_status mgk_create(mgk_ctx** out, int device) {
         ctx->memory->events.reserve(4 * kMaxReads);
     } catch (...) { delete ctx; return MGK_ENOMEM; }
     if (device >= 0 && hipSetDevice(device) != hipSuccess) { delete ctx; return MGK_EDEVICE; }
-    if (device >= 0) {   // what the first calls would have to create, and some may not
-        Staging& S = ctx->staging;
-        if (hipHostMalloc(&S.block, sizeof(S.slot) / sizeof(S.slot[0]) * kSlotBytes, hipHostMallocDefault) == hipSuccess)
-            for (Staging::Slot& s : S.slot) {
-                s.p = (char*)S.block + (size_t)(&s - S.slot) * kSlotBytes;
-                s.cap = kSlotBytes;
-            }
-        else S.block = nullptr;
-        for (size_t k = 0; k < kMaxReads; ++k) {
-            hipEvent_t e = nullptr;
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) ctx->memory->events.push_back(e);
-        }
-        (void)hipGetLastError();
+    for (int k = 0; device >= 0 && k < 4; ++k) {   // for calls that may not create any; 1 us each
+        hipEvent_t e = nullptr;
+        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess) ctx->memory->events.push_back(e);
     }
     *out = ctx;
     return MGK_OK;

@@ -265,16 +265,18 @@ def test_few_pairs_take_the_product_that_fills_the_chip(host, n, k, pairs, kerne
     host.free(B)
 
 
-def test_pinned_memory_is_allocated_with_the_context(so):
-    """Not inside the first calls, which are as short as any."""
+def test_pinned_memory_is_allocated_once(so):
+    """One block by the first call that stages a list, none by the calls after it or by those that need none."""
     h = host_runtime.Host(so)
-    pinned, wb = h.lib.stub_pinned(), W.config1(12)
-    for entry in ("mgk_pairs", "mgk_pairs_noalloc"):
-        for _ in range(6):
-            B = h.load(wb)
-            assert h.pairs(B, B, [0, 1, 2], [2, 3, 4], entry=entry) == 0, h.error()
-            h.free(B)
+    wb = W.config1(12)
+    B = h.load(wb)
+    assert h.gram(B) == 0 and h.lib.stub_pinned() == 0
+    for k, entry in enumerate(("mgk_pairs", "mgk_pairs", "mgk_pairs_noalloc", "mgk_pairs", "mgk_pairs_noalloc", "mgk_pairs", "mgk_pairs")):
+        assert h.pairs(B, B, [0, 1, 2], [2, 3, 4], entry=entry) == 0, h.error()
+        if k == 0:
+            pinned = h.lib.stub_pinned()
     assert h.lib.stub_pinned() == pinned > 0
+    h.free(B)
     h.destroy()
     assert h.lib.stub_pinned() == 0
 
