@@ -1014,8 +1014,8 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
 // run.  Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities
 // 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages
-// the rows of p and pays 6 clk per element in dependent loads, and for its entries takes a third longer where
-// measured against the sparse form near the line (5 to 64 pairs of n = 256 to 325); the sparse separable product does 20 multiply-adds
+// the rows of p and pays 6 clk per element in dependent loads, and takes a third longer for entries of rows of up
+// to 14 nonzeros (5 to 64 pairs of n = 256 to 480), less for longer ones; the sparse separable product does 20 multiply-adds
 // per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
 // from 256 columns on.  A few pairs leave the chip idle: then the time of a workgroup counts, as many times as
 // workgroups follow each other on a compute unit.  It is a row of the outer graph (row-staged: 5000 clk and 1.6
@@ -1061,7 +1061,8 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     const double pairs = o.n * (int64_t)i.n <= MGK_SMALL_MAX_N ? INFINITY : (double)n_pairs;
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
     const double entries = (double)o.nnz * i.nnz * (1.0 / 7.0) + 0.5 * (double)o.nnz * i.n;
-    C.clk[C.best] = (std::isinf(pairs) ? 1.0 : 1.35) * entries + 6.0 * N + 61.0 * (double)n_tiles / pairs + kUnits / pairs * (5000.0 + 1.6 * entries / o.n);
+    const double short_rows = std::isinf(pairs) ? 0.0 : std::min(0.35, 5.0 * o.n / std::max(o.nnz, 1));
+    C.clk[C.best] = (1.0 + short_rows) * entries + 6.0 * N + 61.0 * (double)n_tiles / pairs + kUnits / pairs * (5000.0 + 1.6 * entries / o.n);
     // clocks of a pair's share of all compute units while the workgroups of all pairs run
     auto workgroups = [&](double blocks, int64_t lds_bytes, int64_t most, double clk) {
         const double side_by_side = kUnits * (double)std::min<int64_t>(most, MGK_LDS_LIMIT_BYTES / std::max<int64_t>(lds_bytes, 1));
@@ -1070,7 +1071,7 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     };
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255, np = (i.n + 63) & ~63;
     const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0), dense = rank * op * ip * ((double)o.n + i.n);
-    const double elements = (L.rk == 1 ? 10.0 : 8.0) * N;
+    const double elements = (ctx->edge_kernel == MGK_EK_CONST ? 10.0 : 8.0) * N;   // rank 1 stays a bound of higher ones
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
     if (may_sparse) {
         const double blocks = (o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;

@@ -252,7 +252,7 @@ def test_outputs_are_formed_twice_at_most(host):
     host.free(B)
 
 
-@pytest.mark.parametrize("n,k,pairs,kernel", [(600, 30, 1, "direct dense"), (600, 30, 16, "sep dense"), (256, 26, 1, "sep"),
+@pytest.mark.parametrize("n,k,pairs,kernel", [(600, 30, 1, "direct dense"), (600, 30, 2, "direct dense"), (600, 30, 16, "sep dense"), (256, 26, 1, "sep"),
                                               (480, 7, 1, "direct rows"), (480, 7, 16, "sep"),
                                               (300, 6, 2, "direct rows"), (300, 6, 16, "sep")])
 def test_few_pairs_take_the_product_that_fills_the_chip(host, n, k, pairs, kernel):
@@ -330,3 +330,16 @@ def test_separable_forms_of_batches_in_turn(host):
     first = [bytes(basis_of(host, l, lo, hi)) for l, lo, hi in ((1.0, 0.0, 1.0), (0.5, 0.0, 1.0), (1.0, 0.0, 2.0))]
     again = [bytes(basis_of(host, l, lo, hi)) for l, lo, hi in ((1.0, 0.0, 1.0), (0.5, 0.0, 1.0), (1.0, 0.0, 2.0))]
     assert first == again and len(set(first)) == 3
+
+
+def test_label_range_at_which_the_form_is_first_looked_for(host):
+    """Whether to make the separable form is decided at rank 1, which must not cost more than the rank it has:
+    the first call on new labels takes the same product as later ones."""
+    B = host.load(graphs(*[ring(256, 1, np.linspace(0, 1, 256))] * 2))
+    paths = []
+    for length in (1.0, 1.0, 0.9, 0.9):
+        host.set("edge_kernel_se", length)
+        assert host.pairs(B, B, [0] * 64, [1] * 64) == 0, host.error()
+        paths.append(host.launch_log().split(" ")[0])
+    assert paths[0] == paths[1] and paths[2] == paths[3], paths
+    host.free(B)
