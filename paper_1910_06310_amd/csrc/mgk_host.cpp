@@ -1011,25 +1011,27 @@ MgkSepLayout sep_layout(int rank, int n2) {
 enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
 bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 
-// Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot
-// run.  Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities
-// 0.01 to 1, ranks 1 to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages
-// the rows of p and pays 6 clk per element in dependent loads, and takes a third longer for entries of rows of up
-// to 14 nonzeros (5 to 64 pairs of n = 256 to 480), less for longer ones; the sparse separable product does 20 multiply-adds
-// per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its wavefronts
-// from 256 columns on.  A few pairs leave the chip idle: then the time of a workgroup counts, as many times as
-// workgroups follow each other on a compute unit.  It is a row of the outer graph (row-staged: 5000 clk and 1.6
-// times its share of the work, behind the rest), 16 rows (sparse: 45 clk per column and pass and 1.05 times its
-// share), 32 rows (dense: 60 multiply-adds per clk).  The direct products expand the lists of both batches, whichever
-// graphs the pairs have: 0.4 ns per nonzero or 1.2 per octile, over about 12 iterations.
-// Measured, us per call, row-staged / sparse / dense, rank 5, one batch of 128 graphs: 1 pair of n = 256 density
-// 0.01 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs 2090 / 1842 /
-// 7344, 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  8 graphs of n = 600 density 0.1, 1, 2, 4, 16
-// pairs, row-staged / dense: 2515 / 5206, 4112 / 5264, 7394 / 5294, 26957 / 10472; n = 1000 density 0.05: 4592 /
-// 11290, 8246 / 11366, 15217 / 11569, 56425 / 25971.  Geometric graphs of degree 12, row-staged / sparse, 2, 4, 8,
-// 16 pairs: n = 140 rank 9 220 / 305, 233 / 311, 281 / 319, 352 / 327; n = 300 rank 5 358 / 439, 454 / 454, 622 / 486,
-// 934 / 686, rank 13 307 / 569, 381 / 583, 515 / 616, 741 / 816; n = 480 rank 11 516 / 704, 773 / 744, 1207 / 913,
-// 2091 / 1403.
+// Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot run.
+// Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01
+// to 1, ranks 1 to 8) and of contact graphs: the row-staged product evaluates 7 entries per clk, stages the
+// rows of p and pays 6 clk per element in dependent loads, and takes a third longer for entries of rows of up
+// to 14 nonzeros (5 to 64 pairs of n = 256 to 480), less for longer ones; the sparse separable product does 20
+// multiply-adds per clk and writes and reads T; the dense one does 42 per clk and has work for all four of its
+// wavefronts from 256 columns on.  A few pairs leave the chip idle: then the time of a workgroup counts, as
+// many times as workgroups follow each other on a compute unit.  It is a row of the outer graph (row-staged:
+// 5000 clk and 1.6 times its share of the work, behind the rest), 16 rows (sparse: 45 clk per column and pass
+// and 1.05 times its share), 32 rows (dense: 60 multiply-adds per clk).  The direct products expand the lists
+// of both batches, whichever graphs the pairs have: 0.4 ns per nonzero or 1.2 per octile, over about 12
+// iterations.
+// Measured, us per call, row-staged / sparse / dense, rank 5, one batch of 128 graphs: 1 pair of n = 256
+// density 0.01 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs
+// 2090 / 1842 / 7344, 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  8 graphs of n = 600
+// density 0.1, 1, 2, 4, 16 pairs, row-staged / dense: 2515 / 5206, 4112 / 5264, 7394 / 5294, 26957 / 10472; n
+// = 1000 density 0.05: 4592 / 11290, 8246 / 11366, 15217 / 11569, 56425 / 25971.  Geometric graphs of degree
+// 12, row-staged / sparse, 2, 4, 8, 16 pairs: n = 140 rank 9 220 / 305, 233 / 311, 281 / 319, 352 / 327; n =
+// 300 rank 5 358 / 439, 454 / 454, 622 / 486, 934 / 686, rank 13 307 / 569, 381 / 583, 515 / 616, 741 / 816; n
+// = 480 rank 11 516 / 704, 773 / 744, 1207 / 913, 2091 / 1403.  Constant kernel, 37 pairs of n = 146 to 162,
+// density 0.011: 711 / 798, whence its 10 clk per element of the sparse form where others have 8.
 struct LargeCost {
     double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
