@@ -156,6 +156,15 @@ mgk_status mgk_set_onchip_limit(mgk_ctx* ctx, int32_t max_product);
  * means 1).  All give the same iterates up to the rounding of the entries.
  * Ignored while mgk_set_launch forces a workgroup size. */
 mgk_status mgk_set_product_cache(mgk_ctx* ctx, int32_t enable);
+/* Pairs whose entries are kept in registers (1 above): one in which about half of
+ * the outer graph's vertices are eliminated first needs fewer iterations to the same
+ * residual.  Its iterates, and their number, are not those of Alg. 1 on the
+ * full system.  1 (default): the reduced system is solved by calls that pass no
+ * iters_dev while max_iter is automatic, the full one by the others (a recorded mgk_gram
+ * takes the job list an earlier call has left).  0: always the full system, 2: always the
+ * reduced one, whose iterations are then counted and limited.  Values agree to
+ * rounding and to what the stop test leaves, flags are the same. */
+mgk_status mgk_set_reduced_system(mgk_ctx* ctx, int32_t mode);
 /* Order of the on-chip jobs inside a launch (Section V-B, dynamic scheduling).
  * 1 (default): most expensive pairs first, so that the hardware dispatcher,
  * which hands workgroups to compute units as they free up, ends the launch with

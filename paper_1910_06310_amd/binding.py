@@ -26,7 +26,7 @@ EXPORTS = [
     "mgk_set_edge_kernel_poly", "mgk_set_edge_kernel_kron_se", "mgk_set_edge_kernel_rconv_se",
     "mgk_load_graphs_attr",
     "mgk_set_stop_prob", "mgk_set_solver", "mgk_set_tile_path", "mgk_set_launch",
-    "mgk_set_onchip_limit", "mgk_set_product_cache", "mgk_set_schedule",
+    "mgk_set_onchip_limit", "mgk_set_product_cache", "mgk_set_reduced_system", "mgk_set_schedule",
     "mgk_load_graphs", "mgk_load_graphs_embedded", "mgk_free_batch", "mgk_batch_stats", "mgk_batch_permutation",
     "mgk_batch_get_tiles", "mgk_gram", "mgk_pairs", "mgk_pairs_dev", "mgk_pairs_noalloc", "mgk_pairs_nodal", "mgk_normalize_gram", "mgk_launch_log",
 ]
@@ -70,6 +70,7 @@ def load_library(path: Optional[str] = None):
     lib.mgk_set_launch.argtypes = [vp, i32]
     lib.mgk_set_onchip_limit.argtypes = [vp, i32]
     lib.mgk_set_product_cache.argtypes = [vp, i32]
+    lib.mgk_set_reduced_system.argtypes = [vp, i32]
     lib.mgk_set_schedule.argtypes = [vp, i32]
     lib.mgk_load_graphs.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, vp, vp, i32, c.POINTER(vp)]
     lib.mgk_load_graphs_embedded.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, vp, vp, i32, vp, c.POINTER(vp)]
@@ -225,6 +226,10 @@ class Solver:
 
     def set_schedule(self, cost_sorted: bool = True):
         self._check(load_library().mgk_set_schedule(self._h, 1 if cost_sorted else 0))
+
+    def set_reduced_system(self, mode: int = 1):
+        """0: small pairs by the full system, 1: by the reduced one in calls without iteration counts, 2: always."""
+        self._check(load_library().mgk_set_reduced_system(self._h, mode))
 
     def set_product_cache(self, enable=True):
         """False / 0: entries regenerated in every product; True / 1: kept in registers for small

@@ -37,6 +37,7 @@ struct JobBin {
     size_t lds_bytes = 0;
     int waves = 0, ept = 0;
     int chunks = 0;            // > 0: register-resident solver with this many inner chunks
+    bool reduced = false;      // of the reduced system
     int sell_regs = 0;         // > 0: owner-computes solver with this many entry registers per lane
     bool atomic_rows = false;  // an inner graph has a row longer than one lane group
     bool swapped = false;      // outer graphs come from batch Y, inner from X
@@ -223,13 +224,15 @@ struct mgk_batch {
     std::vector<std::shared_ptr<CallEnd>> reads;   // calls that read the batch and may be under way
     bool untracked = false;             // others may be: freeing the batch waits for the device
     MgkBatchDev dev{};
-    JobList gram_jobs;
-    int gram_jobs_waves = 0;       // waves_per_pair setting the list was built for
-    int gram_jobs_max_iter = 0;    // max_iter setting the list was built for
-    int gram_jobs_limit = 0;       // on-chip limit the list was built for
-    int gram_jobs_cache = 0;       // product-cache setting the list was built for
-    int gram_jobs_sorted = 0;      // schedule setting the list was built for
-    int gram_jobs_attr_dim = -1;   // label attributes of the edge kernel it was built for (LDS plan)
+    struct GramJobs {
+        JobList list;
+        int waves = 0;       // settings the list was built for: waves_per_pair
+        int max_iter = 0;
+        int limit = 0;       // on-chip limit
+        int cache = 0;       // product cache
+        int sorted = 0;      // schedule
+        int attr_dim = -1;   // label attributes of the edge kernel (LDS plan)
+    } gram_jobs[2];          // small pairs by the full system, by the reduced one
 };
 
 struct KeptBasis {
@@ -252,6 +255,7 @@ struct mgk_ctx {
     int waves = 0;
     int onchip_limit = MGK_SMALL_MAX_N;  // largest n n' given to the on-chip solver
     int product_cache = 1;      // small pairs keep their matrix entries in registers (2, 3: one of the two kernels only)
+    int reduced_system = 1;     // small pairs: 0 full system, 1 reduced one where nobody sees the iterates, 2 reduced one
     int cost_sorted = 1;        // expensive pairs first inside a launch
     int row_staging = 1;        // global-memory sparse product stages rows of p in LDS
     JobList pair_jobs;          // reused by mgk_pairs
@@ -389,11 +393,83 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
     return longest;
 }
 
+// Colours of the vertices of a graph for the reduced solver (see MgkReducedPlan): black[i] = 1 for a
+// set of vertices of which no two are adjacent, found greedily (a vertex with the fewest undecided
+// neighbours next; neighbours of a black vertex are red), at least one vertex red.  Molecule-like graphs have
+// 55 % black vertices, rings 50 %.  Returns the number of red ones.
+int colour_vertices(int n, const std::vector<int32_t>& deg, const int32_t* rowptr, const MgkEntry* list, std::vector<uint8_t>& black,
+                    std::vector<int32_t>& undecided, std::vector<int32_t>& open) {
+    black.assign((size_t)n, 1);   // as those without a neighbour stay
+    undecided.clear();            // vertices
+    open.assign(deg.begin(), deg.end());   // undecided neighbours; -1: decided
+    for (int i = 0; i < n; ++i)
+        if (deg[i] > 0) undecided.push_back(i);
+    int reds = 0;
+    while (!undecided.empty()) {
+        size_t kept = 0, next = 0;
+        for (int32_t v : undecided)
+            if (open[(size_t)v] >= 0) {
+                undecided[kept] = v;
+                if (open[(size_t)v] < open[(size_t)undecided[next]]) next = kept;
+                ++kept;
+            }
+        undecided.resize(kept);
+        if (kept == 0) break;
+        const int v = undecided[next];
+        open[(size_t)v] = -1;
+        for (int a = 0; a < deg[v]; ++a) {
+            const int u = (int)list[rowptr[v] + a].y;
+            if (open[(size_t)u] < 0) continue;
+            open[(size_t)u] = -1;
+            black[(size_t)u] = 0;
+            ++reds;
+            for (int b = 0; b < deg[u]; ++b) {
+                const int t = (int)list[rowptr[u] + b].y;
+                if (open[(size_t)t] > 0) --open[(size_t)t];
+            }
+        }
+    }
+    if (reds == 0) {   // no edges
+        black[0] = 0;
+        reds = 1;
+    }
+    return reds;
+}
+
+// Rows of one colour (by descending number of nonzeros) divided among `waves` wavefronts: each row goes to the
+// one with the least work so far.  A row of deg nonzeros costs about 4 deg + 9 wave instructions of a product
+// (two inner chunks: an address add and a multiply-add per nonzero and chunk, the row sums and the
+// store at its end).  Returns the most nonzeros a wavefront gets.
+int divide_rows(const std::vector<int32_t>& rows, const std::vector<int32_t>& deg, int waves, std::vector<int32_t>* of_wave) {
+    int cost[8] = {}, nnz[8] = {}, most = 0;
+    for (int w = 0; w < waves; ++w) of_wave[w].clear();
+    for (int32_t i : rows) {   // those without any come last: nothing is stored for them
+        const int w = (int)(std::min_element(cost, cost + waves) - cost);
+        cost[w] += 4 * deg[i] + 9;
+        nnz[w] += deg[i];
+        most = std::max(most, nnz[w]);
+        of_wave[w].push_back(i);
+    }
+    return most;
+}
+
 // attributes per edge label that the edge kernel reads (0 for the kernels on plain
 // scalar labels); the streaming on-chip solver keeps them in LDS for the outer graph
 int attr_dim_of(const mgk_ctx* ctx) {
     return ctx->edge_kernel == MGK_EK_KRON_SE || ctx->edge_kernel == MGK_EK_RCONV_SE ? ctx->label_dim : 0;
 }
+
+// Small pairs by the reduced system: its iterates are others than those of Alg. 1 on the full system, so by
+// default only where a call does not show them (iteration counts) or stop at one of them (an iteration limit).
+bool solve_reduced(const mgk_ctx* ctx, const int32_t* iters_dev) {
+    if (!mgk_launch_reduced_w2_c1) return false;   // linked without the kernels
+    return ctx->reduced_system == 2 || (ctx->reduced_system == 1 && !iters_dev && ctx->max_iter <= 0);
+}
+
+// Fewest wavefronts of its pairs.  Two do less work for a pair whose inner graph fits one chunk, but make a launch of their
+// own: 5050 molecule-like pairs (2679 of them with two) 95 us, all with four 111; with fewer than a launch should have
+// (kMinJobsPerLaunch) a launch more costs more.
+int reduced_waves(int64_t n_pairs) { return n_pairs >= 4096 ? 2 : 4; }
 
 bool capturing(hipStream_t stream) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -509,6 +585,7 @@ struct PairPlan {
     int64_t lds_words = 0;
     int waves = 0, ept = 0;  // 0: does not fit
     int chunks = 0;          // > 0: register-resident solver
+    bool reduced = false;    // of the reduced system
     int sell_regs = 0;       // > 0: owner-computes solver
 };
 
@@ -528,6 +605,30 @@ int64_t regs_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves) {
     if (ept > MGK_REGS_MAX_EPT) return -1;
     return (int64_t)o.nnz * (2 * chunks) + (int64_t)o.n * (1 + 4 * chunks) +
            (int64_t)waves * (8 * ept + 45);
+}
+
+// The same for the solver of the reduced system.
+int reduced_ept(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves) {
+    const int64_t N = (int64_t)o.n_red * i.n;
+    return (int)std::min<int64_t>(std::max<int64_t>(1, (N + waves * 64 - 1) >> (waves == 2 ? 7 : waves == 4 ? 8 : 9)), MGK_REGS_MAX_EPT + 1);
+}
+int64_t reduced_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, int chunks) {
+    const uint8_t* need = o.red_need + 2 * MGK_RED_LIST(waves);
+    if (need[0] > MGK_RED_BLACK(waves) || need[1] > MGK_RED_RED(waves) || chunks > MGK_REGS_MAX_CHUNKS || i.max_deg > MGK_REGS_MAX_DEG ||
+        (waves == 2 && chunks > 1))
+        return -1;
+    const int ept = reduced_ept(o, i, waves);
+    if (ept > MGK_REGS_MAX_EPT || waves * 64 * ept + (int64_t)(o.n - o.n_red) * i.n > MGK_RED_MAX_P) return -1;
+    return o.nnz * (2 * chunks) + o.n * (1 + 4 * chunks) + waves * (9 * ept + 90);
+}
+void set_reduced(PairPlan& pl, const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, int chunks, int64_t cost) {
+    pl.reduced = true;
+    pl.atomic_rows = false;
+    pl.waves = waves;
+    pl.chunks = chunks;
+    pl.ept = reduced_ept(o, i, waves);
+    pl.cost = cost * 16;
+    pl.lds_words = mgk_reduced_plan(o.n, o.n_red, i.n, waves, pl.ept).total;
 }
 
 // Owner-computes solver for (outer o, inner i): the cheapest launch shape that holds the
@@ -557,9 +658,9 @@ int64_t sell_cost(const MgkSellDesc& o, const MgkSellDesc& i, int* waves, int* e
 
 // cache: 0 entries regenerated in every product; 1 (and 2) kept in registers by the kernel
 // in which a wavefront owns rows of the outer graph; 3 by the owner-computes kernel where
-// a pair fits it, else as 1
+// a pair fits it, else as 1.  reduced: fewest wavefronts for the solver of the reduced system, 0: the full one
 PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDesc* sa, const MgkSellDesc* sb,
-                   bool may_swap, int forced_waves, int onchip_limit, int cache, int attr_dim) {
+                   bool may_swap, int forced_waves, int onchip_limit, int cache, int attr_dim, int reduced) {
     const bool product_cache = cache != 0;
     // wave iterations of one XMV: outer nonzeros x 64-lane chunks of the inner layout
     auto passes = [](const MgkGraphDesc& o, const MgkGraphDesc& i) {
@@ -599,15 +700,20 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
     }
     if (product_cache && forced_waves == 0) {
         int64_t best = -1;
-        for (int w = 4; w <= 8; w *= 2)
+        for (int w = reduced ? reduced : 4; w <= 8; w *= 2)
             for (int sw = 0; sw < (may_swap ? 2 : 1); ++sw) {
-                const int64_t c = sw ? regs_cost(b, a, w) : regs_cost(a, b, w);
+                const MgkGraphDesc &o = sw ? b : a, &i = sw ? a : b;
+                const int64_t c = reduced ? reduced_cost(o, i, w, std::max(1, i.lane_len / 64)) : regs_cost(o, i, w);
                 if (c >= 0 && (best < 0 || c < best)) { best = c; pl.waves = w; pl.swap = sw != 0; }
             }
         if (best >= 0) {
             const MgkGraphDesc& o = pl.swap ? b : a;
             const MgkGraphDesc& i = pl.swap ? a : b;
             pl.atomic_rows = false;
+            if (reduced) {
+                set_reduced(pl, o, i, pl.waves, std::max(1, i.lane_len / 64), best);
+                return pl;
+            }
             pl.ept = (int)std::max<int64_t>(1, (N + pl.waves * 64 - 1) / (pl.waves * 64));
             pl.chunks = std::max(1, i.lane_len / 64);
             pl.cost = best * 16 + 16 * N;
@@ -631,21 +737,42 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
     return pl;
 }
 
+// Launches of a call follow each other, and one with a few pairs takes as long as a pair does.  Where one of a few
+// pairs needs the streaming solver with one wavefront (n n' <= 256), those of the reduced one go there too if they are
+// as small: 36 + 9 pairs of 8 or 9 vertices 40.8 us in two launches, 25.0 in one.  graphs(k): the two graphs of pair k.
+constexpr size_t kFewPairs = 256;
+template <class Graphs>
+void join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_limit, int attr_dim) {
+    if (plans.size() > kFewPairs) return;
+    bool one_wave[2] = {};   // [atomic rows]
+    for (const PairPlan& pl : plans)
+        if (pl.waves == 1) one_wave[pl.atomic_rows] = true;
+    if (!one_wave[0] && !one_wave[1]) return;
+    std::vector<PairPlan> moved(plans);
+    for (size_t k = 0; k < plans.size(); ++k) {
+        if (!plans[k].reduced) continue;
+        const auto g = graphs(k);
+        moved[k] = plan_pair(*g.first, *g.second, nullptr, nullptr, true, 0, onchip_limit, 0, attr_dim, 0);
+        if (moved[k].waves != 1 || !one_wave[moved[k].atomic_rows]) return;
+    }
+    plans.swap(moved);
+}
+
 // A launch shape: jobs of one shape go into one kernel launch.
 struct Shape {
     int16_t waves = 0, ept = 0, chunks = 0, sell_regs = 0;
-    bool atomic_rows = false, swapped = false;
+    bool atomic_rows = false, swapped = false, reduced = false;
     int64_t count = 0;
     int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
     int64_t min_cost = INT64_MAX, max_cost = 0;
     bool same(const Shape& s) const {
         return waves == s.waves && ept == s.ept && chunks == s.chunks && sell_regs == s.sell_regs &&
-               atomic_rows == s.atomic_rows && swapped == s.swapped;
+               atomic_rows == s.atomic_rows && swapped == s.swapped && reduced == s.reduced;
     }
     // padded vectors in the LDS plan of each solver (the owner-computes one also has a
     // schedule word per wavefront and slot; 4 words of alignment slack)
     int64_t vector_words() const {
-        const int vectors = sell_regs > 0 ? 3 : chunks > 0 ? 4 : 2;
+        const int vectors = sell_regs > 0 ? 3 : chunks > 0 && !reduced ? 4 : 2;
         return (int64_t)vectors * waves * 64 * ept + (sell_regs > 0 ? waves * ept + 4 : 0);
     }
     int64_t lds_bytes() const { return (base_words + vector_words()) * 4; }
@@ -671,8 +798,9 @@ struct JobPlan {
         s.sell_regs = (int16_t)pl.sell_regs;
         s.atomic_rows = pl.atomic_rows;
         s.swapped = swapped;
+        s.reduced = pl.reduced;
         const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
-                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21;
+                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22;
         uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
         while (table[slot] >= 0 && !shapes[(size_t)table[slot]].same(s)) slot = (slot + 1) % kTable;
         if (table[slot] < 0) {
@@ -692,12 +820,12 @@ private:
     int16_t table[kTable];
 };
 
+constexpr int64_t kMinJobsPerLaunch = 4096;
 // A launch shape with few jobs costs more in launch and drain time than its pairs
 // gain from the exact fit: such jobs move to the closest larger shape that can run
 // them (same solver and workgroup size, at least as many elements per thread and
 // inner chunks).  Only the vector blocks grow, so the LDS need grows by the
 // difference of the padded vector lengths.  Returns the shape each shape's jobs end up in.
-constexpr int64_t kMinJobsPerLaunch = 4096;
 
 std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
     std::vector<int> into(shapes.size());
@@ -714,7 +842,7 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
             for (size_t q = 0; q < shapes.size(); ++q) {
                 const Shape& b = shapes[q];
                 if (q == k || b.count == 0 || a.waves != b.waves || a.atomic_rows != b.atomic_rows || a.swapped != b.swapped ||
-                    (a.chunks > 0) != (b.chunks > 0) || b.chunks < a.chunks || b.ept < a.ept ||
+                    a.reduced != b.reduced || (a.chunks > 0) != (b.chunks > 0) || b.chunks < a.chunks || b.ept < a.ept ||
                     (a.sell_regs > 0) != (b.sell_regs > 0) || b.sell_regs < a.sell_regs)
                     continue;
                 if (best < 0 || size((int)q) < size(best)) best = (int)q;
@@ -777,6 +905,7 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
         b.waves = s.waves;
         b.ept = s.ept;
         b.chunks = s.chunks;
+        b.reduced = s.reduced;
         b.sell_regs = s.sell_regs;
         b.atomic_rows = s.atomic_rows;
         b.swapped = s.swapped;
@@ -1519,6 +1648,8 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     for (const JobBin& b : jl.bins) {
         if (b.sell_regs > 0)
             log_launch(ctx, "mgk_pcg_sell<%d, %d, %d> pairs=%lld entries_cached=1", b.waves, b.ept, b.sell_regs, (long long)b.count);
+        else if (b.reduced)
+            log_launch(ctx, "mgk_pcg_reduced<%d, %d, %d> pairs=%lld entries_cached=1", b.waves, b.ept, b.chunks, (long long)b.count);
         else if (b.chunks > 0)
             log_launch(ctx, "mgk_pcg_regs<%d, %d, %d, %d> pairs=%lld entries_cached=1", b.waves,
                        b.waves == 4 ? MGK_REGS_SMAX_W4 : MGK_REGS_SMAX_W8, b.ept, b.chunks, (long long)b.count);
@@ -1533,6 +1664,9 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             hipError_t e = b.sell_regs > 0
                 ? mgk_launch_sell(b.waves, b.ept, b.sell_regs, o, i, jl.dev + b.first + done, (int)chunk, prm,
                                   b.lds_bytes, out, stream)
+                : b.reduced
+                ? mgk_launch_reduced(b.waves, b.chunks, b.ept, weighted, o, i, jl.dev + b.first + done, (int)chunk,
+                                     prm, b.lds_bytes, out, stream)
                 : b.chunks > 0
                 ? mgk_launch_regs(b.waves, b.chunks, b.ept, weighted, o, i, jl.dev + b.first + done, (int)chunk,
                                   prm, b.lds_bytes, out, stream)
@@ -1832,6 +1966,13 @@ mgk_status mgk_set_product_cache(mgk_ctx* ctx, int32_t enable) {
     return MGK_OK;
 }
 
+mgk_status mgk_set_reduced_system(mgk_ctx* ctx, int32_t mode) {
+    if (!ctx) return MGK_EINVAL;
+    if (mode < 0 || mode > 2) return fail(ctx, MGK_EINVAL, "reduced system must be 0 to 2, got %d", mode);
+    ctx->reduced_system = mode;
+    return MGK_OK;
+}
+
 mgk_status mgk_set_schedule(mgk_ctx* ctx, int32_t cost_sorted) {
     if (!ctx) return MGK_EINVAL;
     if (cost_sorted != 0 && cost_sorted != 1) return fail(ctx, MGK_EINVAL, "schedule must be 0 or 1, got %d", cost_sorted);
@@ -1945,6 +2086,12 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->label_lo = INFINITY;
     B->label_hi = -INFINITY;
     std::vector<int32_t> regs_split;                // its division of every graph's rows among wavefronts
+    std::vector<uint16_t> red_split, red_order((size_t)(3 * tot_v));   // schedules of the reduced solver
+    std::vector<uint32_t> list_sched;
+    std::vector<uint8_t> black;
+    std::vector<int32_t> red_pos, rows_of[2], of_wave[2][8], undecided, open;
+    if (tot_e <= MGK_RED_MAX_NNZ / 2 * (int64_t)n_graphs) list_sched.reserve((size_t)(6 * tot_e));
+    red_split.reserve((size_t)n_graphs * MGK_RED_SPLIT_STRIDE);
     list_outer.reserve((size_t)(2 * tot_e));
     // label attributes in the order of the two lists, attribute-major; filled after the loop
     // (the plane stride is the batch total): (position, edge) pairs collected meanwhile
@@ -2207,6 +2354,55 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         }
         tile_graph.resize(B->tiles.size(), g);
 
+        // ---- schedule of the graph as outer operand of the reduced solver
+        {
+            uint16_t split[MGK_RED_SPLIT_STRIDE] = {};
+            gd.n_red = n;
+            gd.soff = (int32_t)list_sched.size();
+            memset(gd.red_need, 255, sizeof gd.red_need);
+            if (gd.nnz <= MGK_RED_MAX_NNZ && n < 65536 && list_sched.size() < ((size_t)1 << 31) - 3 * MGK_RED_MAX_NNZ) {
+                const MgkEntry* list = list_outer.data() + gd.zoff;
+                gd.n_red = colour_vertices(n, deg, rowptr.data() + v0, list, black, undecided, open);
+                for (auto& r : rows_of) r.clear();
+                for (int k = 0; k < n; ++k) {   // by descending number of nonzeros
+                    const int i = deg_order[(size_t)v0 + k];
+                    rows_of[black[(size_t)i]].push_back(i);
+                }
+                red_pos.resize((size_t)n);
+                for (int waves = 2; waves <= 8; waves *= 2) {
+                    const int which = MGK_RED_LIST(waves);
+                    uint16_t* sp = split + MGK_RED_SPLIT(waves);
+                    uint16_t* order = red_order.data() + 3 * v0 + (int64_t)which * n;
+                    int32_t at = 0;
+                    for (int colour = 0; colour < 2; ++colour) {
+                        const int most = divide_rows(rows_of[colour], deg, waves, of_wave[colour]);
+                        gd.red_need[2 * which + 1 - colour] = (uint8_t)std::min(most, 255);
+                        for (int w = 0; w < waves; ++w) {
+                            sp[(3 - colour) * waves + 1 + w] = (uint16_t)at;
+                            for (int32_t i : of_wave[colour][w]) {
+                                red_pos[(size_t)i] = at;
+                                order[at++] = (uint16_t)i;
+                            }
+                        }
+                    }
+                    const size_t base = list_sched.size();
+                    for (int w = 0; w < waves; ++w) {
+                        sp[w] = (uint16_t)(list_sched.size() - base);
+                        for (int colour = 1; colour >= 0; --colour) {
+                            for (int32_t i : of_wave[colour][w])
+                                for (int a = 0; a < deg[i]; ++a) {
+                                    const int32_t k = rowptr[v0 + i] + a;
+                                    list_sched.push_back((uint32_t)k | (uint32_t)red_pos[list[k].y] << 16);
+                                }
+                            if (colour) sp[waves + 1 + w] = (uint16_t)(list_sched.size() - base - sp[w]);
+                        }
+                    }
+                    sp[waves] = (uint16_t)(list_sched.size() - base);
+                }
+            }
+            red_split.insert(red_split.end(), split, split + MGK_RED_SPLIT_STRIDE);
+        }
+
         // ---- records of the owner-computes solver: vertices sorted by degree (descending),
         //      four neighbour records per vertex
         {
@@ -2270,7 +2466,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     const size_t o_ip = blob.add(iperm);
     const size_t o_lo = blob.add(list_outer);
     const size_t o_li = blob.add(list_inner);
-    const size_t o_sp = blob.add(regs_split);
+    const size_t o_sp = blob.add(regs_split), o_rd = blob.add(red_split), o_ls = blob.add(list_sched), o_ro = blob.add(red_order);
     std::vector<float> attr_outer, attr_inner;
     {
         attr_outer.assign((size_t)D * B->w.size(), 0.f);
@@ -2330,6 +2526,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->dev.list_outer = reinterpret_cast<const MgkEntry*>(base + o_lo);
     B->dev.list_inner = reinterpret_cast<const MgkEntry*>(base + o_li);
     B->dev.regs_split = reinterpret_cast<const int32_t*>(base + o_sp);
+    B->dev.red_split = reinterpret_cast<const uint16_t*>(base + o_rd);
+    B->dev.list_sched = reinterpret_cast<const uint32_t*>(base + o_ls);
+    B->dev.red_order = reinterpret_cast<const uint16_t*>(base + o_ro);
     B->dev.attr_outer = reinterpret_cast<const float*>(base + o_ao);
     B->dev.attr_inner = reinterpret_cast<const float*>(base + o_ai);
     for (int q = 0; q < 2; ++q) {
@@ -2353,8 +2552,9 @@ void mgk_free_batch(mgk_ctx*, mgk_batch* batch) {   // the context may be gone
     if (batch->blob) {
         try { kept = keep_blob(batch); } catch (...) {}
     }
-    if ((batch->blob && !kept) || batch->gram_jobs.dev) (void)hipDeviceSynchronize();
-    if (batch->gram_jobs.dev) (void)hipFree(batch->gram_jobs.dev);
+    if ((batch->blob && !kept) || batch->gram_jobs[0].list.dev || batch->gram_jobs[1].list.dev) (void)hipDeviceSynchronize();
+    for (auto& g : batch->gram_jobs)
+        if (g.list.dev) (void)hipFree(g.list.dev);
     if (batch->blob && !kept) (void)hipFree(batch->blob);
     delete batch;
 }
@@ -2413,22 +2613,27 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     MGK_HIP(ctx, hipSetDevice(ctx->device));
     const int64_t G = batch->n_graphs;
     if (G * G >= (int64_t)1 << 31) return fail(ctx, MGK_ELIMIT, "Gram matrix too large for 32-bit output indices");
-    if (batch->gram_jobs.dev != nullptr &&
-        (batch->gram_jobs_waves != ctx->waves || batch->gram_jobs_max_iter != ctx->max_iter ||
-         batch->gram_jobs_limit != ctx->onchip_limit ||
-         batch->gram_jobs_cache != ctx->product_cache || batch->gram_jobs_sorted != ctx->cost_sorted ||
-         batch->gram_jobs_attr_dim != attr_dim_of(ctx))) {
+    auto built = [&](const mgk_batch::GramJobs& g) {
+        return g.list.dev != nullptr && g.waves == ctx->waves && g.max_iter == ctx->max_iter && g.limit == ctx->onchip_limit &&
+               g.cache == ctx->product_cache && g.sorted == ctx->cost_sorted && g.attr_dim == attr_dim_of(ctx);
+    };
+    bool reduced = solve_reduced(ctx, iters_dev);
+    const int waves = reduced_waves(G * (G + 1) / 2);
+    // a graph that is recorded takes the list that is there
+    if (!built(batch->gram_jobs[reduced]) && built(batch->gram_jobs[!reduced]) && capturing(stream)) reduced = !reduced;
+    mgk_batch::GramJobs& jobs = batch->gram_jobs[reduced];
+    if (jobs.list.dev != nullptr && !built(jobs)) {
         if (mgk_status st = refuse_capture(ctx, stream)) return st;
         MGK_HIP(ctx, hipStreamSynchronize(stream));  // launch shape changed: rebuild the job list
-        MGK_HIP(ctx, hipFree(batch->gram_jobs.dev));
-        batch->gram_jobs.dev = nullptr;
+        MGK_HIP(ctx, hipFree(jobs.list.dev));
+        jobs.list.dev = nullptr;
     }
-    if (batch->gram_jobs.dev == nullptr && G > 0) {
+    if (jobs.list.dev == nullptr && G > 0) {
         if (mgk_status st = refuse_capture(ctx, stream)) return st;   // the list is copied and waited for
         // a4: job list, one job per unordered pair, kept with the batch
         JobPlan plan;
         plan.jobs.reserve((size_t)(G * (G + 1) / 2));
-        for (auto& v : batch->gram_jobs.large) v.clear();
+        for (auto& v : jobs.list.large) v.clear();
         // the plans of the G (G + 1) / 2 pairs are independent: rows of the triangle in turn on
         // several threads, row i starting at pair i G - i (i - 1) / 2
         std::vector<PairPlan> plans((size_t)(G * (G + 1) / 2));
@@ -2442,9 +2647,17 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                     PairPlan* row = plans.data() + (i * G - i * (i - 1) / 2);
                     for (int64_t j = i; j < G; ++j)
                         row[j - i] = plan_pair(batch->graphs[i], batch->graphs[j], &batch->sell_desc[(size_t)i],
-                                               &batch->sell_desc[(size_t)j], true, forced, limit, cache, attr_dim);
+                                               &batch->sell_desc[(size_t)j], true, forced, limit, cache, attr_dim, reduced ? waves : 0);
                 }
             });
+        }
+        if (reduced) {
+            std::vector<int64_t> row((size_t)G);   // first pair of each row of the triangle
+            for (int64_t i = 0; i < G; ++i) row[(size_t)i] = i * G - i * (i - 1) / 2;
+            join_few(plans, [&](size_t k) {
+                const int64_t i = std::upper_bound(row.begin(), row.end(), (int64_t)k) - row.begin() - 1;
+                return std::make_pair(&batch->graphs[(size_t)i], &batch->graphs[(size_t)(i + (int64_t)k - row[(size_t)i])]);
+            }, ctx->onchip_limit, attr_dim_of(ctx));
         }
         size_t next_plan = 0;
         for (int64_t i = 0; i < G; ++i)
@@ -2462,25 +2675,25 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                     MgkLargePair P = plan_large(batch->graphs[i], batch->graphs[j], (int32_t)i, (int32_t)j, &sw, ctx->max_iter);
                     P.out0 = hj.job.out0;
                     P.out1 = hj.job.out1;
-                    batch->gram_jobs.large[0].push_back(P);
+                    jobs.list.large[0].push_back(P);
                     continue;
                 }
                 hj.cost = pl.cost;
                 hj.shape = plan.shape_of(pl, false);   // one batch: swapping is done through the indices
                 plan.jobs.push_back(hj);
             }
-        mgk_status st = build_job_list(ctx, plan, batch->gram_jobs, stream, nullptr);
-        batch->gram_jobs_waves = ctx->waves;
-        batch->gram_jobs_max_iter = ctx->max_iter;
-        batch->gram_jobs_limit = ctx->onchip_limit;
-        batch->gram_jobs_cache = ctx->product_cache;
-        batch->gram_jobs_sorted = ctx->cost_sorted;
-        batch->gram_jobs_attr_dim = attr_dim_of(ctx);
+        mgk_status st = build_job_list(ctx, plan, jobs.list, stream, nullptr);
+        jobs.waves = ctx->waves;
+        jobs.max_iter = ctx->max_iter;
+        jobs.limit = ctx->onchip_limit;
+        jobs.cache = ctx->product_cache;
+        jobs.sorted = ctx->cost_sorted;
+        jobs.attr_dim = attr_dim_of(ctx);
         if (st != MGK_OK) return st;
     }
     batch->untracked = true;   // its job list has freeing wait as well
     const MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
-    return launch_jobs(ctx, batch, batch, batch->gram_jobs, out, stream);
+    return launch_jobs(ctx, batch, batch, jobs.list, out, stream);
 }
 
 // no_alloc: the job list goes to the fixed device array of mgk_noalloc.hip, pairs that need
@@ -2509,15 +2722,19 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     {
         constexpr int64_t kPart = 1024;   // about 20 us of planning
         const int attr_dim = attr_dim_of(ctx);
+        const int reduced = solve_reduced(ctx, iters_dev) ? reduced_waves(n_pairs) : 0;
         ctx->workers.run((int)((n_pairs + kPart - 1) / kPart), [&](int t) {   // allocates nothing, cannot throw
             const int64_t end = std::min(n_pairs, (t + 1) * kPart);
             for (int64_t k = t * kPart; k < end; ++k) {
                 const int32_t i = i_host[k], j = j_host[k];
                 plans[(size_t)k] = plan_pair(X->graphs[i], Y->graphs[j], &X->sell_desc[(size_t)i], &Y->sell_desc[(size_t)j], true,
-                                             ctx->waves, ctx->onchip_limit, ctx->product_cache, attr_dim);
+                                             ctx->waves, ctx->onchip_limit, ctx->product_cache, attr_dim, reduced);
             }
         });
     }
+    if (solve_reduced(ctx, iters_dev))
+        join_few(plans, [&](size_t k) { return std::make_pair(&X->graphs[(size_t)i_host[k]], &Y->graphs[(size_t)j_host[k]]); },
+                      ctx->onchip_limit, attr_dim_of(ctx));
     JobPlan plan;
     plan.jobs.reserve((size_t)n_pairs);
     std::vector<MgkLargePair> large[2];
@@ -2543,7 +2760,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         hj.job.out0 = (int32_t)k;
         hj.job.out1 = pl.swap ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
         hj.cost = pl.cost;
-        hj.shape = plan.shape_of(pl, pl.swap && X != Y);
+        hj.shape = plan.shape_of(pl, pl.swap && X != Y && !pl.reduced);
         plan.jobs.push_back(hj);
     }
     // The previous call's kernels may still read the job buffer: on the same stream the copy below

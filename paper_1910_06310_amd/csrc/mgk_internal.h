@@ -27,6 +27,10 @@ struct MgkGraphDesc {
     int32_t loff;         // first lane slot of the graph in batch-wide expanded inner lists
     int32_t regs_runs;    // longest run of outer nonzeros of one wavefront under regs_split:
                           // 4 wavefronts in bits 0-15, 8 wavefronts in bits 16-31
+    int32_t n_red;        // vertices that stay in the reduced system (see MgkReducedPlan)
+    int32_t soff;         // first of the graph's 3 nnz entries in list_sched, if it has a schedule
+    uint8_t red_need[8];  // most nonzeros of a wavefront in black and in red rows, with 2, with 4 and with 8
+                          // wavefronts; 255 where there is no schedule
 };
 
 // Lane layout of a graph used as the inner operand of the on-chip XMV: the
@@ -81,6 +85,10 @@ struct MgkBatchDev {
     const struct MgkEntry* list_outer;  // per nonzero (CSR order, index zoff + k), see MgkEntry
     const struct MgkEntry* list_inner;  // per lane slot (index loff + slot)
     const int32_t* regs_split;  // per graph MGK_REGS_SPLIT_STRIDE row boundaries, see below
+    const uint32_t* list_sched;  // nonzeros in the order of the wavefronts of the reduced solver, see below
+    const uint16_t* red_split;  // per graph MGK_RED_SPLIT_STRIDE numbers, see below
+    const uint16_t* red_order;  // the vertices of a graph (index 3 voff) in the order of the reduced solver, red ones
+                                // first, for 2, 4 and 8 wavefronts
     const float* attr_outer;  // label attribute a of nonzero k (CSR order): attr_outer[a * nnz_total + zoff + k]
     const float* attr_inner;  // the same in lane order: attr_inner[a * lanes_total + loff + slot], 0 on idle slots
     const struct MgkSellDesc* sell_desc;    // per graph, see MgkSellDesc
@@ -222,6 +230,41 @@ static inline MGK_HD MgkRegsPlan mgk_regs_plan(int32_t n1, int32_t n2, int32_t w
     L.x = 2 * np;
     L.dump = 3 * np;   // same shape as y, 2 np behind it: where lanes that hold no row sum store
     L.vtx1 = 4 * np;
+    L.vtx2 = L.vtx1 + 3 * n1;
+    L.red = (L.vtx2 + 3 * n2 + 3) & ~3;
+    L.total = L.red + 64;
+    return L;
+}
+
+// ---- register-resident solver of the reduced system -------------------------------
+// The vertices of the outer graph are divided into "black" ones, no two of them adjacent, and "red" ones.
+// Elements (i, i') of black i are not coupled to each other, so they are eliminated exactly and Alg. 1
+// runs on the others,
+//     (M_r - W_rr - W_rb M_b^-1 W_br) x_r = b_r + W_rb M_b^-1 b_b,   x_b = M_b^-1 (b_b + W_br x_r).
+// One product of this matrix reads every entry of W once, as one of the full system does: first the black
+// rows, whose sums (entries scaled by M_b^-1) go to the black part of p, then the red ones.  The stop test is the
+// one of the full system: the eliminated elements have no residual.  Two, four or eight wavefronts per pair;
+// each owns whole outer rows of both colours, at most MGK_RED_BLACK and MGK_RED_RED nonzeros, and
+// keeps their entries in registers as the solver of the full system does.  LDS holds p (the red part padded to
+// the register blocks), y of the red rows, 64 words that lanes without a row sum store to, the
+// per-vertex data of both graphs and the reduction scratch.
+#define MGK_RED_BLACK(waves) ((waves) == 2 ? 16 : (waves) == 4 ? 12 : 8)   // multiples of 4: the fill takes four nonzeros a step
+#define MGK_RED_RED(waves) ((waves) == 2 ? 20 : (waves) == 4 ? 16 : 12)
+#define MGK_RED_MAX_NNZ 160      // of the outer graph: 8 x (8 + 12)
+#define MGK_RED_MAX_P 16384      // words of p: byte offsets of its rows are kept in 16 bits
+
+struct MgkReducedPlan {
+    int32_t p, black, y, dump, vtx1, vtx2, red, total;  // words
+};
+
+static inline MGK_HD MgkReducedPlan mgk_reduced_plan(int32_t n1, int32_t n_red, int32_t n2, int32_t waves, int32_t ept) {
+    MgkReducedPlan L;
+    const int32_t np = waves * 64 * ept;   // >= n_red n2
+    L.p = 0;
+    L.black = np;
+    L.y = L.black + (n1 - n_red) * n2;
+    L.dump = L.y + np;
+    L.vtx1 = L.dump + 64;
     L.vtx2 = L.vtx1 + 3 * n1;
     L.red = (L.vtx2 + 3 * n2 + 3) & ~3;
     L.total = L.red + 64;
@@ -456,6 +499,17 @@ struct alignas(16) MgkEntry {
 // rows [b[w], b[w+1]); k = 5..13: the same for 8 wavefronts.
 #define MGK_REGS_SPLIT_STRIDE 14
 #define MGK_REGS_SPLIT_W8 5
+
+//   list_sched, for graphs that can be outer operand of the reduced solver: for 2, for 4 and for 8
+//     wavefronts the graph's nnz nonzeros, wavefront after wavefront, its black rows, then its red rows;
+//     k of list_outer | position of the column in red_order << 16
+//
+// red_split[g * MGK_RED_SPLIT_STRIDE + MGK_RED_SPLIT(waves) + ..]: waves + 1 numbers where the wavefronts' parts of
+// list_sched begin, then for every wavefront the number of its nonzeros in black rows, and the positions in
+// red_order of its first black row and its first red row (its rows follow there in the order of the list).
+#define MGK_RED_SPLIT_STRIDE 59
+#define MGK_RED_SPLIT(waves) ((waves) == 2 ? 0 : (waves) == 4 ? 9 : 26)
+#define MGK_RED_LIST(waves) ((waves) == 2 ? 0 : (waves) == 4 ? 1 : 2)   // which of the three lists and orders
 
 struct MgkExpanded {
     const MgkEntry* outer;

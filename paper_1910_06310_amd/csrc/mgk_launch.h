@@ -75,6 +75,35 @@ static inline hipError_t mgk_launch_regs(int waves, int chunks, int ept, bool we
     }
 }
 
+// Register-resident solver of the reduced system (mgk_reduced.hip): 2 (one chunk only), 4 or 8 wavefronts
+// per job, ept * waves * 64 >= n_red n' of every job; jobs of both orientations (MGK_OUT1_SWAPPED: outer
+// graph from Y).  Weak: without these kernels the full system is solved.
+#define MGK_DECL_REDUCED(W, C)                                                                       \
+    __attribute__((weak)) hipError_t mgk_launch_reduced_w##W##_c##C(int ept, bool weighted, const MgkBatchDev& X, \
+                                           const MgkBatchDev& Y, const MgkJob* jobs_dev,          \
+                                           int n_jobs, const MgkParams& prm, size_t lds_bytes,    \
+                                           const MgkOutputs& out, hipStream_t stream);
+MGK_DECL_REDUCED(2, 1)
+MGK_DECL_REDUCED(4, 1)
+MGK_DECL_REDUCED(4, 2)
+MGK_DECL_REDUCED(8, 1)
+MGK_DECL_REDUCED(8, 2)
+#undef MGK_DECL_REDUCED
+
+static inline hipError_t mgk_launch_reduced(int waves, int chunks, int ept, bool weighted,
+                                            const MgkBatchDev& X, const MgkBatchDev& Y,
+                                            const MgkJob* jobs_dev, int n_jobs, const MgkParams& prm,
+                                            size_t lds_bytes, const MgkOutputs& out, hipStream_t stream) {
+    switch (waves * 10 + chunks) {
+        case 21: return mgk_launch_reduced_w2_c1(ept, weighted, X, Y, jobs_dev, n_jobs, prm, lds_bytes, out, stream);
+        case 41: return mgk_launch_reduced_w4_c1(ept, weighted, X, Y, jobs_dev, n_jobs, prm, lds_bytes, out, stream);
+        case 42: return mgk_launch_reduced_w4_c2(ept, weighted, X, Y, jobs_dev, n_jobs, prm, lds_bytes, out, stream);
+        case 81: return mgk_launch_reduced_w8_c1(ept, weighted, X, Y, jobs_dev, n_jobs, prm, lds_bytes, out, stream);
+        case 82: return mgk_launch_reduced_w8_c2(ept, weighted, X, Y, jobs_dev, n_jobs, prm, lds_bytes, out, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 // Owner-computes on-chip solver (mgk_sell.hip): `waves` (4, 8 or 16) wavefronts per job,
 // `ept` vector slots per lane (2 waves ept >= tiles of every job), `regs` entry registers
 // per lane (>= what mgk_sell_need returns for every job), `lds_bytes` the largest

@@ -16,155 +16,18 @@
 // the lanes of an inner row at the end of an outer row (DPP shift-and-add) and
 // the vector part of the iteration follow the streaming kernel; the edge base
 // kernel appears only in the one-off fill of the registers, so every base
-// kernel runs the same iteration.  x is kept in LDS beside p and y (it is
+// kernel runs the same iteration.  This is the solver of the full system, with the iterates of Alg. 1, for calls
+// that see them (iteration counts, an iteration limit); the others take mgk_reduced.hip.  x is kept in LDS beside p and y (it is
 // touched once per iteration), r, M, the owner's p and z in registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "mgk_internal.h"
 #include "mgk_launch.h"
+#include "mgk_regs_dev.h"
 #include "mgk_wave.h"
 
 namespace {
-
-// value of v in lane k (k a compile-time constant after unrolling)
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, int k) {
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, k);
-}
-__device__ __forceinline__ float lane_value(float v, int k) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
-}
-
-// The loops over the wave's outer nonzeros are unrolled by template recursion,
-// four nonzeros per step, so that every index into the register array kap is a
-// compile-time constant.
-
-// Matrix entries of outer nonzeros K0 .. SMAX-1 (lanes K0.. of e1s / l1) against this
-// lane's inner nonzeros: square-exponential kernel on prescaled labels,
-// exp2(log2 A + log2 A' - (e - e')^2).  Lanes of e1s past the wave's run hold a huge
-// label and idle inner slots hold l2 = -inf, so both give exactly 0.
-template <int K0, int SMAX, int C, bool WEIGHTED>
-__device__ __forceinline__ void fill_se(float (&kap)[C][SMAX], int S, const float (&e2s)[C],
-                                        const float (&l2)[C], float e1s, float l1) {
-    if constexpr (K0 < SMAX) {
-        if (K0 < S) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float e1 = lane_value(e1s, K0 + u);
-                const float la = WEIGHTED ? lane_value(l1, K0 + u) : 0.f;
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const float d = e2s[c] - e1;
-                    kap[c][K0 + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(-d, d, WEIGHTED ? l2[c] + la : l2[c]));
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int c = 0; c < C; ++c) kap[c][K0 + u] = 0.f;
-        }
-        fill_se<K0 + 4, SMAX, C, WEIGHTED>(kap, S, e2s, l2, e1s, l1);
-    }
-}
-
-// the same for the constant edge kernel: A_ij * (A'_i'j' kappa_e); w1 is 0 past the run
-template <int K0, int SMAX, int C>
-__device__ __forceinline__ void fill_const(float (&kap)[C][SMAX], int S, const float (&w2c)[C], float w1) {
-    if constexpr (K0 < SMAX) {
-        if (K0 < S) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float wa = lane_value(w1, K0 + u);
-#pragma unroll
-                for (int c = 0; c < C; ++c) kap[c][K0 + u] = w2c[c] * wa;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int c = 0; c < C; ++c) kap[c][K0 + u] = 0.f;
-        }
-        fill_const<K0 + 4, SMAX, C>(kap, S, w2c, w1);
-    }
-}
-
-// compact polynomial kernel on labels prescaled by 1 / rho; wprod = A_ij A'_i'j' per lane
-// pair (0 on idle slots and past the run)
-template <int K0, int SMAX, int C>
-__device__ __forceinline__ void fill_poly(float (&kap)[C][SMAX], int S, const float (&e2s)[C],
-                                          const float (&w2)[C], float e1s, float w1, const float* pc) {
-    if constexpr (K0 < SMAX) {
-        if (K0 < S) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float e1 = lane_value(e1s, K0 + u);
-                const float wa = lane_value(w1, K0 + u);
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    kap[c][K0 + u] = mgk_poly_kernel(e2s[c] - e1, pc) * (w2[c] * wa);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int c = 0; c < C; ++c) kap[c][K0 + u] = 0.f;
-        }
-        fill_poly<K0 + 4, SMAX, C>(kap, S, e2s, w2, e1s, w1, pc);
-    }
-}
-
-// Kernels over labels with D attributes, each prescaled by sqrt(log2(e) / (2 l_a^2)).
-// RCONV false: Kronecker product of square exponentials, exp2(log2 A + log2 A' -
-// sum_a (e_a - e'_a)^2), with l1 / l2 the log2 weights (-inf on idle slots; lanes past
-// the run carry a huge attribute 0).  RCONV true: (A A' / D^2) sum_a sum_b
-// exp2(-(e_a - e'_b)^2), with l1 / l2 the weights themselves (0 where there is no entry).
-template <int K0, int SMAX, int C, bool RCONV>
-__device__ __forceinline__ void fill_attr(float (&kap)[C][SMAX], int S, int D,
-                                          const float (&e2a)[C][MGK_MAX_LABEL_DIM], const float (&l2)[C],
-                                          const float (&e1a)[MGK_MAX_LABEL_DIM], float l1) {
-    if constexpr (K0 < SMAX) {
-        if (K0 < S) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float e1[MGK_MAX_LABEL_DIM];
-#pragma unroll
-                for (int a = 0; a < MGK_MAX_LABEL_DIM; ++a) e1[a] = a < D ? lane_value(e1a[a], K0 + u) : 0.f;
-                const float la = lane_value(l1, K0 + u);
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    if (RCONV) {
-                        float sum = 0.f;
-#pragma unroll
-                        for (int a = 0; a < MGK_MAX_LABEL_DIM; ++a)
-#pragma unroll
-                            for (int b = 0; b < MGK_MAX_LABEL_DIM; ++b)
-                                if (a < D && b < D) {
-                                    const float d = e2a[c][a] - e1[b];
-                                    sum += __builtin_amdgcn_exp2f(-d * d);
-                                }
-                        kap[c][K0 + u] = sum * (l2[c] * la);
-                    } else {
-                        float t = l2[c] + la;
-#pragma unroll
-                        for (int a = 0; a < MGK_MAX_LABEL_DIM; ++a)
-                            if (a < D) {
-                                const float d = e2a[c][a] - e1[a];
-                                t = __builtin_fmaf(-d, d, t);
-                            }
-                        kap[c][K0 + u] = __builtin_amdgcn_exp2f(t);
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int c = 0; c < C; ++c) kap[c][K0 + u] = 0.f;
-        }
-        fill_attr<K0 + 4, SMAX, C, RCONV>(kap, S, D, e2a, l2, e1a, l1);
-    }
-}
 
 // per-lane constants of the inner nonzeros, one set per chunk
 template <int C>
@@ -189,30 +52,6 @@ __device__ __forceinline__ void gather4(float (&pv)[4][C], const InnerLanes<C>& 
     }
 }
 
-// acc[c] += m1 * (acc[c] one lane down) and then += m2 * (two lanes down), inside rows of
-// 16 lanes: the sum over an inner row of at most 4 nonzeros arrives in its last lane.
-// The DPP reads need two wait states after the write of the register they read; with two
-// chunks the steps of one chunk fill part of the other's.
-template <int C>
-__device__ __forceinline__ void row_sums(float (&acc)[C], const InnerLanes<C>& in) {
-    static_assert(C == 1 || C == 2, "one or two chunks");
-    if constexpr (C == 1) {
-        asm volatile(
-            "s_nop 1\n\tv_fmac_f32_dpp %0, %0, %1 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "s_nop 1\n\tv_fmac_f32_dpp %0, %0, %2 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "+v"(acc[0])
-            : "v"(in.m1[0]), "v"(in.m2[0]));
-    } else {
-        asm volatile(
-            "s_nop 1\n\tv_fmac_f32_dpp %0, %0, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %1, %1, %3 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "s_nop 0\n\tv_fmac_f32_dpp %0, %0, %4 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-            "v_fmac_f32_dpp %1, %1, %5 row_shr:2 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "+v"(acc[0]), "+v"(acc[1])
-            : "v"(in.m1[0]), "v"(in.m1[1]), "v"(in.m2[0]), "v"(in.m2[1]));
-    }
-}
-
 // Multiply-add of outer nonzeros K0 .. K0+3 (p values already read into pv); at the
 // end of an outer row (wave-uniform test) each inner row is summed over its lanes
 // (rows of at most 4 nonzeros: two shift-and-add steps) and y_ii' stored from the
@@ -227,7 +66,7 @@ __device__ __forceinline__ void use4(const float (&kap)[C][SMAX], const InnerLan
         for (int c = 0; c < C; ++c) acc[c] = __builtin_fmaf(kap[c][K0 + u], pv[u][c], acc[c]);
         if ((rowmask >> (K0 + u)) & 1ull) {
             const uint32_t yo = lane_value(v_yoff, K0 + u);
-            row_sums<C>(acc, in);
+            row_sums<C>(acc, in.m1, in.m2);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 // every lane stores: the last lane of an inner row to y_ii', the others to
@@ -348,12 +187,12 @@ __global__ __launch_bounds__(W * 64) void mgk_pcg_regs(MgkBatchDev X, MgkBatchDe
             w2r[c] = w2;
         }
         if (prm.edge_kernel == MGK_EK_SE) {
-            if (weighted) fill_se<0, SMAX, C, true>(kap, S, e2s, l2, e1s, l1);
-            else fill_se<0, SMAX, C, false>(kap, S, e2s, l2, e1s, l1);
+            if (weighted) fill_se<0, SMAX, SMAX, C, true>(kap, S, e2s, l2, e1s, l1);
+            else fill_se<0, SMAX, SMAX, C, false>(kap, S, e2s, l2, e1s, l1);
         } else if (prm.edge_kernel == MGK_EK_CONST) {
-            fill_const<0, SMAX, C>(kap, S, w2c, w1);
+            fill_const<0, SMAX, SMAX, C>(kap, S, w2c, w1);
         } else if (prm.edge_kernel == MGK_EK_POLY) {
-            fill_poly<0, SMAX, C>(kap, S, e2s, w2r, e1s, w1, prm.poly_c);
+            fill_poly<0, SMAX, SMAX, C>(kap, S, e2s, w2r, e1s, w1, prm.poly_c);
         } else {
             // labels with D attributes, from the attribute planes of the two lists
             const int D = prm.label_dim;
@@ -375,11 +214,11 @@ __global__ __launch_bounds__(W * 64) void mgk_pcg_regs(MgkBatchDev X, MgkBatchDe
                 const float inv = 1.0f / (float)(D * D);
 #pragma unroll
                 for (int c = 0; c < C; ++c) f2[c] = w2r[c] * inv;   // 0 on idle slots
-                fill_attr<0, SMAX, C, true>(kap, S, D, e2a, f2, e1a, w1);   // w1 is 0 past the run
+                fill_attr<0, SMAX, SMAX, C, true>(kap, S, D, e2a, f2, e1a, w1);   // w1 is 0 past the run
             } else {
                 if (!live1) e1a[0] = 1e18f;   // past the run: kappa_e underflows to exactly 0
                 const float la = weighted ? __log2f(live1 ? w1 : 1.f) : 0.f;
-                fill_attr<0, SMAX, C, false>(kap, S, D, e2a, l2, e1a, la);
+                fill_attr<0, SMAX, SMAX, C, false>(kap, S, D, e2a, l2, e1a, la);
             }
         }
     }
