@@ -31,6 +31,23 @@ namespace {
 
 constexpr int kTile = 8;
 
+// What the separable product of a streaming on-chip solve would take, for the choice at launch (the edge
+// kernel's parameters and label ranges are not known before); of a pair, or over the pairs of a launch.
+struct SepWork {
+    int32_t rows = 0, cols = 0, elements = 0;   // most vertices of a larger and of a smaller graph, most n n'
+    int64_t entries = 0;                        // pairs of nonzeros, nnz nnz'
+    int64_t halves = 0;                         // nnz n' + n nnz'
+    int64_t blocks = 0;                         // of 16 rows
+    void add(const SepWork& s) {
+        rows = std::max(rows, s.rows);
+        cols = std::max(cols, s.cols);
+        elements = std::max(elements, s.elements);
+        entries += s.entries;
+        halves += s.halves;
+        blocks += s.blocks;
+    }
+};
+
 struct JobBin {
     int64_t first = 0;   // index of the bin's first job in the job array
     int64_t count = 0;
@@ -41,6 +58,7 @@ struct JobBin {
     int sell_regs = 0;         // > 0: owner-computes solver with this many entry registers per lane
     bool atomic_rows = false;  // an inner graph has a row longer than one lane group
     bool swapped = false;      // outer graphs come from batch Y, inner from X
+    SepWork sep;
 };
 
 struct JobList {
@@ -269,6 +287,9 @@ struct mgk_ctx {
     DevBuf dense_tiles[2][3];           // dense 8x8 expansions (weight, label, log2 weight)
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
+    DevBuf onchip_packets[2];           // packets of the separable product on chip
+    hipEvent_t onchip_packets_end = nullptr;   // of the last kernel that reads them, and its stream
+    hipStream_t onchip_packets_stream = nullptr;
     bool features_in_use = false;       // by the call under way
     KeptBasis bases[4];                 // of the last label ranges and edge kernels, see sep_basis_for
     int next_basis = 0;
@@ -587,6 +608,7 @@ struct PairPlan {
     int chunks = 0;          // > 0: register-resident solver
     bool reduced = false;    // of the reduced system
     int sell_regs = 0;       // > 0: owner-computes solver
+    SepWork sep;             // streaming solver
 };
 
 // Register-resident solver for (outer o, inner i) with `waves` wavefronts: every
@@ -734,6 +756,12 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
     const MgkGraphDesc& i = pl.swap ? a : b;
     pl.lds_words = mgk_small_plan(o.n, i.n, o.nnz, i.lane_len, o.n_tiles, i.n_tiles, pl.waves, pl.ept, attr_dim).total;
     if (pl.lds_words * 4 > MGK_LDS_LIMIT_BYTES) pl.waves = pl.ept = 0;
+    pl.sep.rows = std::max(a.n, b.n);
+    pl.sep.cols = std::min(a.n, b.n);
+    pl.sep.elements = (int32_t)N;
+    pl.sep.entries = (int64_t)a.nnz * b.nnz;
+    pl.sep.halves = (int64_t)a.nnz * b.n + (int64_t)a.n * b.nnz;
+    pl.sep.blocks = (pl.sep.rows + 15) / 16;
     return pl;
 }
 
@@ -762,12 +790,14 @@ void join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_lim
 struct Shape {
     int16_t waves = 0, ept = 0, chunks = 0, sell_regs = 0;
     bool atomic_rows = false, swapped = false, reduced = false;
+    bool big = false;          // too large for the separable product on chip
+    SepWork sep;
     int64_t count = 0;
     int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
     int64_t min_cost = INT64_MAX, max_cost = 0;
     bool same(const Shape& s) const {
         return waves == s.waves && ept == s.ept && chunks == s.chunks && sell_regs == s.sell_regs &&
-               atomic_rows == s.atomic_rows && swapped == s.swapped && reduced == s.reduced;
+               atomic_rows == s.atomic_rows && swapped == s.swapped && reduced == s.reduced && big == s.big;
     }
     // padded vectors in the LDS plan of each solver (the owner-computes one also has a
     // schedule word per wavefront and slot; 4 words of alignment slack)
@@ -799,8 +829,9 @@ struct JobPlan {
         s.atomic_rows = pl.atomic_rows;
         s.swapped = swapped;
         s.reduced = pl.reduced;
+        s.big = pl.sep.elements > MGK_PCG_SEP_MAX_N;
         const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
-                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22;
+                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22 | (uint32_t)s.big << 23;
         uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
         while (table[slot] >= 0 && !shapes[(size_t)table[slot]].same(s)) slot = (slot + 1) % kTable;
         if (table[slot] < 0) {
@@ -809,6 +840,7 @@ struct JobPlan {
         }
         Shape& t = shapes[(size_t)table[slot]];
         t.count++;
+        t.sep.add(pl.sep);
         t.base_words = std::max(t.base_words, pl.lds_words - t.vector_words());
         t.min_cost = std::min(t.min_cost, pl.cost);
         t.max_cost = std::max(t.max_cost, pl.cost);
@@ -842,7 +874,7 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
             for (size_t q = 0; q < shapes.size(); ++q) {
                 const Shape& b = shapes[q];
                 if (q == k || b.count == 0 || a.waves != b.waves || a.atomic_rows != b.atomic_rows || a.swapped != b.swapped ||
-                    a.reduced != b.reduced || (a.chunks > 0) != (b.chunks > 0) || b.chunks < a.chunks || b.ept < a.ept ||
+                    a.reduced != b.reduced || a.big != b.big || (a.chunks > 0) != (b.chunks > 0) || b.chunks < a.chunks || b.ept < a.ept ||
                     (a.sell_regs > 0) != (b.sell_regs > 0) || b.sell_regs < a.sell_regs)
                     continue;
                 if (best < 0 || size((int)q) < size(best)) best = (int)q;
@@ -856,6 +888,7 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
         Shape &a = shapes[from], &b = shapes[to];
         if ((a.base_words + b.vector_words()) * 4 > MGK_LDS_LIMIT_BYTES) { frozen[from] = 1; continue; }
         b.count += a.count;
+        b.sep.add(a.sep);
         b.base_words = std::max(b.base_words, a.base_words);
         b.min_cost = std::min(b.min_cost, a.min_cost);
         b.max_cost = std::max(b.max_cost, a.max_cost);
@@ -909,6 +942,7 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
         b.sell_regs = s.sell_regs;
         b.atomic_rows = s.atomic_rows;
         b.swapped = s.swapped;
+        b.sep = s.sep;
         out.bins.push_back(b);
         first += s.count;
     }
@@ -952,7 +986,8 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
 // Gives back what the context keeps for later calls: features and blocks of freed batches.
 bool release_spare(mgk_ctx* ctx) {
     bool any = false;
-    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1]})
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets[0],
+                      &ctx->onchip_packets[1]})
         if (b->p && !ctx->features_in_use) {
             (void)hipFree(b->p);   // waits for the work that reads it
             *b = DevBuf{};
@@ -1126,12 +1161,12 @@ const MgkSepBasis* make_basis(mgk_ctx* ctx, float lo, float hi) {
 // How the sparse separable product of a pair with n2 columns divides its rank: the fewest
 // features executed, then the fewest passes; rk = 0 when no column count fits in LDS.
 MgkSepLayout sep_layout(int rank, int n2) {
-    MgkSepLayout L{0, 0, 0, 0};
+    MgkSepLayout L{};
     for (int rk : {7, 6, 5, 4, 1}) {
         if (mgk_sep_lds_bytes(rk, n2) > MGK_LDS_LIMIT_BYTES || (rk == 1) != (rank == 1)) continue;
         const int passes = (rank + rk - 1) / rk;
         if (L.rk == 0 || passes * rk < L.passes * L.rk || (passes * rk == L.passes * L.rk && passes < L.passes))
-            L = MgkSepLayout{rk, passes, mgk_sep_per_packet(rk), MGK_SEP_SLAB(rk) * 4};
+            L = MgkSepLayout{rk, passes, mgk_sep_per_packet(rk), MGK_SEP_SLAB(rk) * 4, 0};
     }
     return L;
 }
@@ -1635,8 +1670,125 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     return MGK_OK;
 }
 
+// Launch shape of the separable product for a bin of the streaming on-chip solver; waves 0: its pairs do not fit.
+// Eight wavefronts for pairs of which two workgroups share a compute unit, else sixteen.
+struct OnchipSep {
+    int waves = 0, ept = 0, rb = 0;
+    size_t lds_bytes = 0;
+};
+OnchipSep onchip_sep_shape(const JobBin& b, int rk) {
+    static const struct { int waves, ept; } kShapes[] = {{8, 4}, {8, 8}, {16, 6}, {16, 8}, {16, 10}, {16, 12}, {16, 14}};
+    OnchipSep s;
+    for (const auto& c : kShapes) {
+        const int np = c.waves * 64 * c.ept;
+        if (np < b.sep.elements) continue;
+        // most words over its pairs: p and y have a word per element and row at most, the rest grows with either graph
+        const int64_t base = mgk_pcg_sep_plan(b.sep.rows, b.sep.cols, rk, 0).total +
+                             2 * ((int64_t)b.sep.elements + b.sep.rows - (int64_t)b.sep.rows * (b.sep.cols | 1)) + 8;
+        const int64_t slab = (int64_t)MGK_PCG_SEP_SLAB(rk) * b.sep.cols;
+        const int64_t limit = (c.waves == 8 ? MGK_LDS_LIMIT_BYTES / 2 : MGK_LDS_LIMIT_BYTES) / 4;
+        const int rb = (int)std::min<int64_t>((limit - base) / slab, c.waves == 8 ? 2 : 4);
+        if (base + slab > limit) continue;
+        s.waves = c.waves;
+        s.ept = c.ept;
+        s.rb = std::min(rb, (b.sep.rows + 15) / 16);
+        s.lds_bytes = (size_t)(base + slab * s.rb) * 4;
+        return s;
+    }
+    return s;
+}
+
+// Clocks of a compute unit that the separable product saves the pairs of a bin of the streaming on-chip solver in eight
+// iterations.  The streaming solver evaluates 6 to 7 entries a clock, the separable one does 18 multiply-adds and waits
+// about 300 clocks for a block of 16 rows (160 scale-free graphs of 96 vertices, 1080 nonzeros: 169 000 and 59 000
+// clocks an iteration).
+double onchip_sep_gain(const JobBin& b, int rank_executed, int passes) {
+    const double rounds = (double)((b.count + 255) / 256) / (double)b.count;
+    return 8.0 * rounds * ((double)b.sep.entries / 6.0 - (double)b.sep.halves * rank_executed / 18.0 - 300.0 * passes * (double)b.sep.blocks);
+}
+
+// The bins of a call that take the separable product on chip (use[k].waves > 0), and its packets in sl[].
+// Not while a graph is recorded (the packets belong to the context), nor where the caller asked for
+// the streaming solver or allows no allocation.
+mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl, bool may_allocate, hipStream_t stream,
+                              std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2]) {
+    const bool kernel_ok = ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST;
+    if (!mgk_launch_pcg_sep_rk5 || !may_allocate || !kernel_ok || ctx->tile_path != MGK_TILE_AUTO || ctx->product_cache == 0 || ctx->waves != 0)
+        return MGK_OK;
+    // Features of all graphs of the batches, formed before the kernels: 20 us with the basis and the launch, and 6 clocks of
+    // a unit per nonzero and feature (23 us for 160 graphs of 1080 nonzeros).  At the lowest rank first: the basis takes time.
+    auto total_gain = [&](int rank) {
+        double gain = 0.0;
+        for (const JobBin& b : jl.bins)
+            if (b.chunks == 0 && b.sell_regs == 0 && b.sep.elements > 0 && b.sep.elements <= MGK_PCG_SEP_MAX_N)
+                gain += std::max(0.0, onchip_sep_gain(b, rank, 1));
+        return gain;
+    };
+    const int64_t nnz = X->nnz + (X == Y ? 0 : Y->nnz);
+    auto cost = [&](int rank) { return 50e3 + (double)nnz * rank * 6.0 / 256.0; };
+    if (total_gain(1) <= cost(1) || capturing(stream)) return MGK_OK;
+    const float lo = std::min(X->label_lo, Y->label_lo), hi = std::max(X->label_hi, Y->label_hi);
+    const MgkSepBasis* basis = kept_basis(ctx, lo, hi);
+    if (!basis) basis = make_basis(ctx, lo, hi);
+    if (basis->rank <= 0) return MGK_OK;
+    const MgkSepBasis S = *basis;
+    L = MgkSepLayout{};
+    for (int rk : {7, 6, 5, 4, 1}) {
+        if ((rk == 1) != (S.rank == 1)) continue;
+        const int passes = (S.rank + rk - 1) / rk;
+        if (L.rk == 0 || passes * rk < L.passes * L.rk || (passes * rk == L.passes * L.rk && passes < L.passes))
+            L = mgk_pcg_sep_numbers(rk) ? MgkSepLayout{rk, passes, mgk_sep_per_packet(rk), MGK_PCG_SEP_SLAB(rk) * 4, 1}
+                                        : MgkSepLayout{rk, passes, mgk_sep_per_packet(rk), 1, 0};
+    }
+    double gain = 0.0;
+    for (size_t k = 0; k < jl.bins.size(); ++k) {
+        const JobBin& b = jl.bins[k];
+        if (b.chunks > 0 || b.sell_regs > 0 || b.sep.elements == 0) continue;
+        const double g = onchip_sep_gain(b, L.rk * L.passes, L.passes);
+        if (g <= 0.0) continue;
+        use[k] = onchip_sep_shape(b, L.rk);
+        if (use[k].waves > 0) gain += g;
+    }
+    constexpr int64_t kMaxPacketBytes = (int64_t)256 << 20;
+    const int gi = L.per_packet == 8 ? 1 : 0, sides = X == Y ? 1 : 2;
+    const mgk_batch* bt[2] = {X, Y};
+    int64_t bytes = 0;
+    for (int k = 0; k < sides; ++k) bytes += ((int64_t)L.passes * bt[k]->packet_off[gi].back() + 8) * 256;
+    if (gain <= cost(L.rk * L.passes) || bytes > kMaxPacketBytes) {
+        std::fill(use.begin(), use.end(), OnchipSep{});
+        return MGK_OK;
+    }
+    struct InUse {   // what is allocated for one side does not free the other
+        bool& flag;
+        ~InUse() { flag = false; }
+    } in_use{ctx->features_in_use};
+    ctx->features_in_use = true;
+    // a call on another stream may still read the packets
+    if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
+    else if (ctx->onchip_packets_stream != stream) MGK_HIP(ctx, hipEventSynchronize(ctx->onchip_packets_end));
+    ctx->onchip_packets_stream = stream;
+    for (int k = 0; k < sides; ++k) {
+        const mgk_batch* b = bt[k];
+        sl[k] = b->sep[gi];
+        sl[k].total = b->packet_off[gi].back();
+        const size_t need = ((size_t)L.passes * sl[k].total + 8) * 256;   // a stage loads eight steps at a time
+        DevBuf& buf = ctx->onchip_packets[k];
+        if (buf.cap < need && ensure(ctx, buf, need) != MGK_OK) {   // short memory: the streaming solver
+            std::fill(use.begin(), use.end(), OnchipSep{});
+            return MGK_OK;
+        }
+        sl[k].packets = (const float*)buf.p;
+        int32_t max_n = 1;
+        for (const MgkGraphDesc& g : b->graphs) max_n = std::max(max_n, g.n);
+        hipError_t e = mgk_launch_sep_pack(b->dev, S, L, sl[k], sl[k].whole, b->n_graphs, max_n, (float*)buf.p, stream);
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
+    }
+    if (sides == 1) sl[1] = sl[0];
+    return MGK_OK;
+}
+
 mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl,
-                       const MgkOutputs& out, hipStream_t stream) {
+                       const MgkOutputs& out, hipStream_t stream, bool may_allocate = true) {
     const MgkParams prm = make_params(ctx, X);
     const bool weighted = X->weighted || Y->weighted;
     const bool any_large = !jl.large[0].empty() || !jl.large[1].empty();
@@ -1645,8 +1797,17 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     ctx->calls++;
     ctx->idle = false;
     ctx->launch_log.clear();
+    std::vector<OnchipSep> sep(jl.bins.size());
+    MgkSepLayout onchip_layout{};
+    MgkSepList onchip_lists[2] = {};
+    if (mgk_status st = prepare_onchip_sep(ctx, X, Y, jl, may_allocate, stream, sep, onchip_layout, onchip_lists)) return st;
+    bool any_sep = false;
     for (const JobBin& b : jl.bins) {
-        if (b.sell_regs > 0)
+        const OnchipSep& s = sep[(size_t)(&b - jl.bins.data())];
+        if (s.waves > 0)
+            log_launch(ctx, "mgk_pcg_sep<%d, %d, %d> passes=%d pairs=%lld entries_cached=0", onchip_layout.rk, s.ept, s.waves, onchip_layout.passes,
+                       (long long)b.count);
+        else if (b.sell_regs > 0)
             log_launch(ctx, "mgk_pcg_sell<%d, %d, %d> pairs=%lld entries_cached=1", b.waves, b.ept, b.sell_regs, (long long)b.count);
         else if (b.reduced)
             log_launch(ctx, "mgk_pcg_reduced<%d, %d, %d> pairs=%lld entries_cached=1", b.waves, b.ept, b.chunks, (long long)b.count);
@@ -1661,7 +1822,11 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             const int64_t chunk = std::min<int64_t>(b.count - done, (int64_t)1 << 30);
             const MgkBatchDev& o = b.swapped ? Y->dev : X->dev;
             const MgkBatchDev& i = b.swapped ? X->dev : Y->dev;
-            hipError_t e = b.sell_regs > 0
+            any_sep = any_sep || s.waves > 0;
+            hipError_t e = s.waves > 0
+                ? mgk_launch_pcg_sep(onchip_layout.rk, s.waves, s.ept, onchip_layout.passes, o, i, onchip_lists[b.swapped ? 1 : 0],
+                                     onchip_lists[b.swapped ? 0 : 1], jl.dev + b.first + done, (int)chunk, prm, s.rb, s.lds_bytes, out, stream)
+                : b.sell_regs > 0
                 ? mgk_launch_sell(b.waves, b.ept, b.sell_regs, o, i, jl.dev + b.first + done, (int)chunk, prm,
                                   b.lds_bytes, out, stream)
                 : b.reduced
@@ -1677,6 +1842,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             done += chunk;
         }
     }
+    if (any_sep) MGK_HIP(ctx, hipEventRecord(ctx->onchip_packets_end, stream));
     if (!any_large) return MGK_OK;
     // ---- pairs with vectors in global memory: the product of each from the current edge kernel
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);
@@ -1835,11 +2001,12 @@ void mgk_destroy(mgk_ctx* ctx) {
     if (!ctx) return;
     if (ctx->pair_jobs.dev) (void)hipFree(ctx->pair_jobs.dev);
     for (DevBuf* b : {&ctx->exp_outer[0], &ctx->exp_outer[1], &ctx->exp_inner[0], &ctx->exp_inner[1],
-                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
+                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets[0], &ctx->onchip_packets[1], &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
                       &ctx->dense_tiles[0][0], &ctx->dense_tiles[0][1], &ctx->dense_tiles[0][2],
                       &ctx->dense_tiles[1][0], &ctx->dense_tiles[1][1], &ctx->dense_tiles[1][2]})
         if (b->p) (void)hipFree(b->p);
     if (ctx->active_host) (void)hipHostFree(ctx->active_host);
+    if (ctx->onchip_packets_end) (void)hipEventDestroy(ctx->onchip_packets_end);
     for (Staging::Slot& s : ctx->staging.slot) {
         if (s.open) (void)hipDeviceSynchronize();
         if (s.end) (void)hipEventSynchronize(s.end->event);
@@ -2787,7 +2954,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if (st != MGK_OK) return st;
         ctx->fixed_jobs_stream = stream;
         ctx->fixed_jobs_busy = true;
-        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream)) == MGK_OK) reads.done(ctx->staging, stream, false, ctx->idle);
+        if ((st = launch_jobs(ctx, X, Y, fixed, out, stream, false)) == MGK_OK) reads.done(ctx->staging, stream, false, ctx->idle);
         return st;
     }
     mgk_status st = build_job_list(ctx, plan, ctx->pair_jobs, stream, &ctx->pair_jobs_cap);

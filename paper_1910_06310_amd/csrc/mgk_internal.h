@@ -426,9 +426,11 @@ struct MgkSepBasis {
 // How the rank is divided for the sparse product: `passes` passes of `rk` (1, 4, 5, 6 or 7)
 // features each, per_packet nonzeros to a packet of 16 words (rk coefficients and one offset
 // per nonzero).  slab_bytes: LDS bytes of one column of T.
+// numbers: packets (of at most 14 words) also hold the numbers of the columns, from word MGK_SEP_NUMBER_SLOT on.
 struct MgkSepLayout {
-    int32_t rk, passes, per_packet, slab_bytes;
+    int32_t rk, passes, per_packet, slab_bytes, numbers;
 };
+#define MGK_SEP_NUMBER_SLOT 14
 #define MGK_SEP_ROWS 16       // outer rows per workgroup: one row of 16 lanes
 #define MGK_SEP_THREADS 1024
 #define MGK_SEP_DENSE_ROWS 32 // the same of the dense form: one tile
@@ -471,6 +473,26 @@ struct MgkSepGraph {
 struct MgkSepAt {
     int64_t f1, f2;
 };
+
+// ---- whole solve on chip with the separable product (mgk_pcg_sep.hip) ----------
+// Columns are the vertices of the smaller graph (n2 <= n1).  p and y with rows of n2 | 1 words, T of rb blocks of 16 rows, per-vertex data, first packet steps and reduction scratch.
+#define MGK_PCG_SEP_SLAB(rk) ((rk) == 1 ? 17 : 16 * (rk) + 4)   // words of one column of T for 16 rows
+static inline MGK_HD bool mgk_pcg_sep_numbers(int32_t rk) { return rk >= 4 && rk <= 6; }   // see MgkSepLayout
+#define MGK_PCG_SEP_MAX_N (16 * 64 * 14)
+struct MgkPcgSepPlan {
+    int32_t y, t, vtx1, vtx2, gptr, red, total;  // words; p at 0
+};
+static inline MGK_HD MgkPcgSepPlan mgk_pcg_sep_plan(int32_t n1, int32_t n2, int32_t rk, int32_t rb) {
+    MgkPcgSepPlan L;
+    L.y = n1 * (n2 | 1);
+    L.t = (2 * L.y + 3) & ~3;
+    L.vtx1 = L.t + MGK_PCG_SEP_SLAB(rk) * n2 * rb;
+    L.vtx2 = L.vtx1 + 3 * n1;
+    L.gptr = L.vtx2 + 3 * n2;
+    L.red = L.gptr + (n1 + 3) / 4 + (n2 + 3) / 4 + 2;
+    L.total = L.red + 64;
+    return L;
+}
 
 // ---- solver with vectors in global memory (pairs too large for LDS) ---------
 // Expanded nonzero lists of a whole batch, rebuilt per call because the label

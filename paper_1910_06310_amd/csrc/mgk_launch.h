@@ -201,6 +201,31 @@ MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const
                                                      int rank, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec,
                                                      const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                      bool check_only, hipStream_t stream);
+// Whole solves on chip with that product (mgk_pcg_sep.hip) by `waves` wavefronts of ept elements a thread, T of rb
+// blocks of 16 rows at a time; packets (layout with slab_bytes 1) of all graphs of the two batches.
+#define MGK_DECL_PCG_SEP(RK)                                                                                                       \
+    MGK_KERNELS_OPTIONAL hipError_t mgk_launch_pcg_sep_rk##RK(int waves, int ept, int passes, const MgkBatchDev& X, const MgkBatchDev& Y, \
+                                                              const MgkSepList& SX, const MgkSepList& SY, const MgkJob* jobs_dev,   \
+                                                              int n_jobs, const MgkParams& prm, int rb, size_t lds_bytes,           \
+                                                              const MgkOutputs& out, hipStream_t stream);
+MGK_DECL_PCG_SEP(1)
+MGK_DECL_PCG_SEP(4)
+MGK_DECL_PCG_SEP(5)
+MGK_DECL_PCG_SEP(6)
+MGK_DECL_PCG_SEP(7)
+#undef MGK_DECL_PCG_SEP
+static inline hipError_t mgk_launch_pcg_sep(int rk, int waves, int ept, int passes, const MgkBatchDev& X, const MgkBatchDev& Y,
+                                            const MgkSepList& SX, const MgkSepList& SY, const MgkJob* jobs_dev, int n_jobs,
+                                            const MgkParams& prm, int rb, size_t lds_bytes, const MgkOutputs& out, hipStream_t stream) {
+    switch (rk) {
+        case 1: return mgk_launch_pcg_sep_rk1(waves, ept, passes, X, Y, SX, SY, jobs_dev, n_jobs, prm, rb, lds_bytes, out, stream);
+        case 4: return mgk_launch_pcg_sep_rk4(waves, ept, passes, X, Y, SX, SY, jobs_dev, n_jobs, prm, rb, lds_bytes, out, stream);
+        case 5: return mgk_launch_pcg_sep_rk5(waves, ept, passes, X, Y, SX, SY, jobs_dev, n_jobs, prm, rb, lds_bytes, out, stream);
+        case 6: return mgk_launch_pcg_sep_rk6(waves, ept, passes, X, Y, SX, SY, jobs_dev, n_jobs, prm, rb, lds_bytes, out, stream);
+        case 7: return mgk_launch_pcg_sep_rk7(waves, ept, passes, X, Y, SX, SY, jobs_dev, n_jobs, prm, rb, lds_bytes, out, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
 // The two kernels over the vectors that follow a product which has already formed p^T a and
 // overwrites y.
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_large_vectors(const MgkLargePair* pairs, MgkPairState* state, float* vec, int n_pairs,

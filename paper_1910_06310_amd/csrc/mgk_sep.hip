@@ -46,7 +46,8 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
     const MgkGraphDesc g = B.graphs[sg.graph];
     const int32_t* gptr = list.gptr + list.qoff[sg.graph];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int slot = lane & 15, u = slot / (L.rk + 1), kk = slot - u * (L.rk + 1);
+    const int slot = lane & 15, number = L.numbers ? slot - MGK_SEP_NUMBER_SLOT : -1;   // >= 0: word of a column's number
+    const int u = number >= 0 ? number : slot / (L.rk + 1), kk = number >= 0 ? L.rk : slot - u * (L.rk + 1);
     for (int grp = blockIdx.x * 4 + wave; grp * 4 < g.n; grp += gridDim.x * 4) {
         const int p0 = gptr[grp], p1 = gptr[grp + 1];
         const int pos = grp * 4 + (lane >> 4);
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
                 float v = 0.f;
                 if (on && kk < L.rk && k < S.rank) v = w * sep_feature(S, coef, __uint_as_float(e.z), k);
                 if (on && kk == L.rk) v = __uint_as_float(e.y * (uint32_t)L.slab_bytes);
+                if (number >= 0) v = __uint_as_float(on ? e.y : 0u);
                 out[((int64_t)q * list.total + at + p) * 64 + lane] = v;
             }
         }
