@@ -48,6 +48,17 @@ struct SepWork {
     }
 };
 
+SepWork sep_work(const MgkGraphDesc& a, const MgkGraphDesc& b) {
+    SepWork s;
+    s.rows = std::max(a.n, b.n);
+    s.cols = std::min(a.n, b.n);
+    s.elements = (int32_t)((int64_t)a.n * b.n);
+    s.entries = (int64_t)a.nnz * b.nnz;
+    s.halves = (int64_t)a.nnz * b.n + (int64_t)a.n * b.nnz;
+    s.blocks = (s.rows + 15) / 16;
+    return s;
+}
+
 struct JobBin {
     int64_t first = 0;   // index of the bin's first job in the job array
     int64_t count = 0;
@@ -389,6 +400,10 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
     auto row_cost = [&](int i) { return (int64_t)4 * deg[i] + 9; };
     int64_t lo = 0, hi = 0;
     for (int i = 0; i < n; ++i) { lo = std::max(lo, row_cost(i)); hi += row_cost(i); }
+    // no bound below the mean will do, and the mean and the longest row always do
+    const int64_t mean = (hi + waves - 1) / waves;
+    hi = std::min(hi, mean + lo);
+    lo = std::max(lo, mean);
     auto parts_needed = [&](int64_t bound) {
         int parts = 1;
         int64_t cur = 0;
@@ -417,36 +432,38 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
 // Colours of the vertices of a graph for the reduced solver (see MgkReducedPlan): black[i] = 1 for a
 // set of vertices of which no two are adjacent, found greedily (a vertex with the fewest undecided
 // neighbours next; neighbours of a black vertex are red), at least one vertex red.  Molecule-like graphs have
-// 55 % black vertices, rings 50 %.  Returns the number of red ones.
+// 55 % black vertices, rings 50 %.  Returns the number of red ones.  New graphs are often few and compared at once, so
+// that their schedules count: keys of the vertices with edges lie side by side, and the next one is a plain minimum.
 int colour_vertices(int n, const std::vector<int32_t>& deg, const int32_t* rowptr, const MgkEntry* list, std::vector<uint8_t>& black,
-                    std::vector<int32_t>& undecided, std::vector<int32_t>& open) {
+                    std::vector<int32_t>& slot) {
+    constexpr int32_t kDecided = INT32_MAX;
+    int32_t key[MGK_RED_MAX_NNZ], vertex[MGK_RED_MAX_NNZ];   // undecided neighbours << 16 | position
+    int count = 0;
     black.assign((size_t)n, 1);   // as those without a neighbour stay
-    undecided.clear();            // vertices
-    open.assign(deg.begin(), deg.end());   // undecided neighbours; -1: decided
+    slot.resize((size_t)n);
     for (int i = 0; i < n; ++i)
-        if (deg[i] > 0) undecided.push_back(i);
+        if (deg[i] > 0) {
+            slot[(size_t)i] = count;
+            vertex[count] = i;
+            key[count] = deg[i] << 16 | count;
+            ++count;
+        }
     int reds = 0;
-    while (!undecided.empty()) {
-        size_t kept = 0, next = 0;
-        for (int32_t v : undecided)
-            if (open[(size_t)v] >= 0) {
-                undecided[kept] = v;
-                if (open[(size_t)v] < open[(size_t)undecided[next]]) next = kept;
-                ++kept;
-            }
-        undecided.resize(kept);
-        if (kept == 0) break;
-        const int v = undecided[next];
-        open[(size_t)v] = -1;
+    while (true) {
+        int32_t next = kDecided;
+        for (int c = 0; c < count; ++c) next = std::min(next, key[c]);
+        if (next == kDecided) break;
+        const int v = vertex[next & 0xffff];
+        key[next & 0xffff] = kDecided;
         for (int a = 0; a < deg[v]; ++a) {
-            const int u = (int)list[rowptr[v] + a].y;
-            if (open[(size_t)u] < 0) continue;
-            open[(size_t)u] = -1;
+            const int u = (int)list[rowptr[v] + a].y, su = slot[(size_t)u];
+            if (key[su] == kDecided) continue;
+            key[su] = kDecided;
             black[(size_t)u] = 0;
             ++reds;
             for (int b = 0; b < deg[u]; ++b) {
-                const int t = (int)list[rowptr[u] + b].y;
-                if (open[(size_t)t] > 0) --open[(size_t)t];
+                int32_t& k = key[slot[list[rowptr[u] + b].y]];
+                if (k != kDecided && k >> 16 > 0) k -= 1 << 16;
             }
         }
     }
@@ -460,16 +477,20 @@ int colour_vertices(int n, const std::vector<int32_t>& deg, const int32_t* rowpt
 // Rows of one colour (by descending number of nonzeros) divided among `waves` wavefronts: each row goes to the
 // one with the least work so far.  A row of deg nonzeros costs about 4 deg + 9 wave instructions of a product
 // (two inner chunks: an address add and a multiply-add per nonzero and chunk, the row sums and the
-// store at its end).  Returns the most nonzeros a wavefront gets.
-int divide_rows(const std::vector<int32_t>& rows, const std::vector<int32_t>& deg, int waves, std::vector<int32_t>* of_wave) {
+// store at its end).  of_wave[k]: the wavefront of row k; rows_in[w]: rows wavefront w gets.  Returns the most nonzeros
+// a wavefront gets.
+int divide_rows(const std::vector<int32_t>& rows, const std::vector<int32_t>& deg, int waves, uint8_t* of_wave, int* rows_in) {
     int cost[8] = {}, nnz[8] = {}, most = 0;
-    for (int w = 0; w < waves; ++w) of_wave[w].clear();
-    for (int32_t i : rows) {   // those without any come last: nothing is stored for them
-        const int w = (int)(std::min_element(cost, cost + waves) - cost);
-        cost[w] += 4 * deg[i] + 9;
-        nnz[w] += deg[i];
+    std::fill_n(rows_in, waves, 0);
+    for (size_t k = 0; k < rows.size(); ++k) {   // those without any come last: nothing is stored for them
+        const int d = deg[(size_t)rows[k]];
+        int w = 0;
+        for (int v = 1; v < waves; ++v) w = cost[v] < cost[w] ? v : w;
+        cost[w] += 4 * d + 9;
+        nnz[w] += d;
         most = std::max(most, nnz[w]);
-        of_wave[w].push_back(i);
+        of_wave[k] = (uint8_t)w;
+        rows_in[w]++;
     }
     return most;
 }
@@ -608,7 +629,6 @@ struct PairPlan {
     int chunks = 0;          // > 0: register-resident solver
     bool reduced = false;    // of the reduced system
     int sell_regs = 0;       // > 0: owner-computes solver
-    SepWork sep;             // streaming solver
 };
 
 // Register-resident solver for (outer o, inner i) with `waves` wavefronts: every
@@ -756,12 +776,6 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
     const MgkGraphDesc& i = pl.swap ? a : b;
     pl.lds_words = mgk_small_plan(o.n, i.n, o.nnz, i.lane_len, o.n_tiles, i.n_tiles, pl.waves, pl.ept, attr_dim).total;
     if (pl.lds_words * 4 > MGK_LDS_LIMIT_BYTES) pl.waves = pl.ept = 0;
-    pl.sep.rows = std::max(a.n, b.n);
-    pl.sep.cols = std::min(a.n, b.n);
-    pl.sep.elements = (int32_t)N;
-    pl.sep.entries = (int64_t)a.nnz * b.nnz;
-    pl.sep.halves = (int64_t)a.nnz * b.n + (int64_t)a.n * b.nnz;
-    pl.sep.blocks = (pl.sep.rows + 15) / 16;
     return pl;
 }
 
@@ -819,8 +833,9 @@ struct JobPlan {
     std::vector<HostJob> jobs;
     std::vector<Shape> shapes;
     JobPlan() { std::fill(table, table + kTable, (int16_t)-1); }
-    // index of the shape of a planned pair; counts the pair in
-    int shape_of(const PairPlan& pl, bool swapped) {
+    // index of the shape of a planned pair of graphs a and b; counts the pair in
+    int shape_of(const PairPlan& pl, bool swapped, const MgkGraphDesc& a, const MgkGraphDesc& b) {
+        const bool streaming = pl.chunks == 0 && pl.sell_regs == 0;
         Shape s;
         s.waves = (int16_t)pl.waves;
         s.ept = (int16_t)pl.ept;
@@ -829,7 +844,7 @@ struct JobPlan {
         s.atomic_rows = pl.atomic_rows;
         s.swapped = swapped;
         s.reduced = pl.reduced;
-        s.big = pl.sep.elements > MGK_PCG_SEP_MAX_N;
+        s.big = streaming && (int64_t)a.n * b.n > MGK_PCG_SEP_MAX_N;
         const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
                              (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22 | (uint32_t)s.big << 23;
         uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
@@ -840,7 +855,7 @@ struct JobPlan {
         }
         Shape& t = shapes[(size_t)table[slot]];
         t.count++;
-        t.sep.add(pl.sep);
+        if (streaming) t.sep.add(sep_work(a, b));
         t.base_words = std::max(t.base_words, pl.lds_words - t.vector_words());
         t.min_cost = std::min(t.min_cost, pl.cost);
         t.max_cost = std::max(t.max_cost, pl.cost);
@@ -2256,7 +2271,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     std::vector<uint16_t> red_split, red_order((size_t)(3 * tot_v));   // schedules of the reduced solver
     std::vector<uint32_t> list_sched;
     std::vector<uint8_t> black;
-    std::vector<int32_t> red_pos, rows_of[2], of_wave[2][8], undecided, open;
+    std::vector<uint8_t> of_wave;
+    std::vector<int32_t> red_pos, rows_of[2], red_slot;
     if (tot_e <= MGK_RED_MAX_NNZ / 2 * (int64_t)n_graphs) list_sched.reserve((size_t)(6 * tot_e));
     red_split.reserve((size_t)n_graphs * MGK_RED_SPLIT_STRIDE);
     list_outer.reserve((size_t)(2 * tot_e));
@@ -2529,42 +2545,53 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             memset(gd.red_need, 255, sizeof gd.red_need);
             if (gd.nnz <= MGK_RED_MAX_NNZ && n < 65536 && list_sched.size() < ((size_t)1 << 31) - 3 * MGK_RED_MAX_NNZ) {
                 const MgkEntry* list = list_outer.data() + gd.zoff;
-                gd.n_red = colour_vertices(n, deg, rowptr.data() + v0, list, black, undecided, open);
+                gd.n_red = colour_vertices(n, deg, rowptr.data() + v0, list, black, red_slot);
                 for (auto& r : rows_of) r.clear();
+                int nnz_of[2] = {};
                 for (int k = 0; k < n; ++k) {   // by descending number of nonzeros
                     const int i = deg_order[(size_t)v0 + k];
                     rows_of[black[(size_t)i]].push_back(i);
+                    nnz_of[black[(size_t)i]] += deg[i];
                 }
                 red_pos.resize((size_t)n);
+                of_wave.resize((size_t)n);
                 for (int waves = 2; waves <= 8; waves *= 2) {
                     const int which = MGK_RED_LIST(waves);
+                    const size_t base = list_sched.size();
+                    list_sched.resize(base + (size_t)gd.nnz);
+                    // more nonzeros than the wavefronts hold: no need to divide them (the place stays, unread)
+                    if (nnz_of[0] > waves * MGK_RED_RED(waves) || nnz_of[1] > waves * MGK_RED_BLACK(waves)) continue;
                     uint16_t* sp = split + MGK_RED_SPLIT(waves);
                     uint16_t* order = red_order.data() + 3 * v0 + (int64_t)which * n;
-                    int32_t at = 0;
+                    int32_t at = 0, rows_in[2][8];
                     for (int colour = 0; colour < 2; ++colour) {
-                        const int most = divide_rows(rows_of[colour], deg, waves, of_wave[colour]);
+                        const std::vector<int32_t>& rows = rows_of[colour];
+                        const int most = divide_rows(rows, deg, waves, of_wave.data(), rows_in[colour]);
                         gd.red_need[2 * which + 1 - colour] = (uint8_t)std::min(most, 255);
+                        int32_t next[8];
                         for (int w = 0; w < waves; ++w) {
-                            sp[(3 - colour) * waves + 1 + w] = (uint16_t)at;
-                            for (int32_t i : of_wave[colour][w]) {
-                                red_pos[(size_t)i] = at;
-                                order[at++] = (uint16_t)i;
-                            }
+                            sp[(3 - colour) * waves + 1 + w] = (uint16_t)(next[w] = at);
+                            at += rows_in[colour][w];
+                        }
+                        for (size_t k = 0; k < rows.size(); ++k) {
+                            const int32_t to = next[of_wave[k]]++;
+                            red_pos[(size_t)rows[k]] = to;
+                            order[to] = (uint16_t)rows[k];
                         }
                     }
-                    const size_t base = list_sched.size();
+                    uint32_t* sched = list_sched.data() + base;
+                    int32_t done = 0;
                     for (int w = 0; w < waves; ++w) {
-                        sp[w] = (uint16_t)(list_sched.size() - base);
+                        sp[w] = (uint16_t)done;
                         for (int colour = 1; colour >= 0; --colour) {
-                            for (int32_t i : of_wave[colour][w])
-                                for (int a = 0; a < deg[i]; ++a) {
-                                    const int32_t k = rowptr[v0 + i] + a;
-                                    list_sched.push_back((uint32_t)k | (uint32_t)red_pos[list[k].y] << 16);
-                                }
-                            if (colour) sp[waves + 1 + w] = (uint16_t)(list_sched.size() - base - sp[w]);
+                            const uint16_t* row = order + sp[(3 - colour) * waves + 1 + w];
+                            for (int r = 0; r < rows_in[colour][w]; ++r)
+                                for (int32_t k = rowptr[v0 + row[r]], end = k + deg[row[r]]; k < end; ++k)
+                                    sched[done++] = (uint32_t)k | (uint32_t)red_pos[list[k].y] << 16;
+                            if (colour) sp[waves + 1 + w] = (uint16_t)(done - sp[w]);
                         }
                     }
-                    sp[waves] = (uint16_t)(list_sched.size() - base);
+                    sp[waves] = (uint16_t)done;
                 }
             }
             red_split.insert(red_split.end(), split, split + MGK_RED_SPLIT_STRIDE);
@@ -2576,9 +2603,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             MgkSellDesc sd{};
             sd.voff = (int32_t)sell_vtx.size();
             if (n <= MGK_SELL_MAX_N && max_deg <= MGK_SELL_MAX_DEG) {
-                std::vector<int32_t> order(n), pos(n);
-                std::iota(order.begin(), order.end(), 0);
-                std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return deg[x] > deg[y]; });
+                const int32_t* order = deg_order.data() + v0;
+                int32_t pos[MGK_SELL_MAX_N];
                 for (int k = 0; k < n; ++k) pos[order[k]] = k;
                 const int r8 = (n + 7) & ~7;
                 for (int k = 0; k < r8; ++k) {
@@ -2846,7 +2872,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                     continue;
                 }
                 hj.cost = pl.cost;
-                hj.shape = plan.shape_of(pl, false);   // one batch: swapping is done through the indices
+                hj.shape = plan.shape_of(pl, false, batch->graphs[i], batch->graphs[j]);   // one batch: swapping is done through the indices
                 plan.jobs.push_back(hj);
             }
         mgk_status st = build_job_list(ctx, plan, jobs.list, stream, nullptr);
@@ -2927,7 +2953,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         hj.job.out0 = (int32_t)k;
         hj.job.out1 = pl.swap ? MGK_OUT1_SWAPPED : MGK_OUT1_NONE;
         hj.cost = pl.cost;
-        hj.shape = plan.shape_of(pl, pl.swap && X != Y && !pl.reduced);
+        hj.shape = plan.shape_of(pl, pl.swap && X != Y && !pl.reduced, X->graphs[(size_t)i], Y->graphs[(size_t)j]);
         plan.jobs.push_back(hj);
     }
     // The previous call's kernels may still read the job buffer: on the same stream the copy below
