@@ -390,7 +390,9 @@ def main() -> int:
     traffic = hbm_traffic(wl, args)
     cflops = counted_flops(wl, args)
     ranks = {int(r) for r in re.findall(r"mgk_sep_\S+ rank=(\d+)", "\n".join(launches))}
-    separable = len(ranks) == 1 and all(f.startswith("mgk_sep") for f in families)
+    # on chip: features executed, those of a pass times the passes
+    ranks |= {int(k) * int(p) for k, p in re.findall(r"mgk_pcg_sep<(\d+),[^>]*> passes=(\d+)", "\n".join(launches))}
+    separable = len(ranks) == 1 and all(f.startswith(("mgk_sep", "mgk_pcg_sep")) for f in families)
     if ranks:   # the counters were taken with the direct products
         traffic = cflops = None
         executed_flops = executed_per_pair_iter = None
