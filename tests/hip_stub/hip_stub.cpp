@@ -4,9 +4,12 @@
 // lifetimes, memory that runs out, how pairs are grouped) can be tested without a GPU.
 //
 // Work on a stream ends at once, unless the test holds the stream: then it ends when something waits
-// for it.  A test can also set a limit on device memory, and mark streams as recording.
+// for it.  A stream that waits for an event of such work is held too, and ordered behind it.  A test can also set a limit
+// on device memory, mark streams as recording and have launches of a kernel fail.  Launches of the on-chip solvers are
+// looked over as the kernels do it: every job has to fit the launch shape.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -20,18 +23,23 @@
 
 namespace {
 
-struct Event { void* stream; bool done; };
+typedef std::map<void*, uint64_t> Behind;            // stream -> what was enqueued on it up to there
+struct Event { void* stream; bool done; Behind behind; };
 
 std::map<char*, size_t> device_memory;              // block -> bytes
 size_t in_use = 0, limit = SIZE_MAX, pinned_bytes = 0;
 std::set<void*> held, recording;                    // streams
-std::map<void*, std::set<char*>> readers;           // held stream -> blocks its work reads
+std::map<void*, std::map<char*, uint64_t>> readers; // held stream -> blocks its work uses, the last time each
+std::map<void*, Behind> waited;                     // stream -> what its work is ordered behind
+uint64_t now = 0;
 std::set<Event*> events;
 std::string log_text;
 std::vector<std::string> violations;
 std::map<std::string, int> counts;
 int device = 0;
 int converge_after = 3;
+std::string failing;                                // kernel whose launches fail
+hipStreamCaptureMode capture_mode = hipStreamCaptureModeGlobal;   // of the calling thread
 
 void say(const char* fmt, ...) {
     char buf[256];
@@ -53,6 +61,11 @@ char* block_of(const void* p) {
 void finish(void* stream) {
     held.erase(stream);
     readers.erase(stream);
+    if (waited.count(stream)) {
+        const Behind before = waited[stream];
+        waited.erase(stream);
+        for (auto& b : before) finish(b.first);
+    }
     for (Event* e : events)
         if (e->stream == stream) e->done = true;
 }
@@ -63,21 +76,44 @@ void finish_all() {
 
 void reads(void* stream, const void* p) {
     if (char* b = block_of(p))
-        if (held.count(stream)) readers[stream].insert(b);
+        if (held.count(stream)) readers[stream][b] = ++now;
 }
 
-void check_write(const void* p) {   // a block that unfinished work reads must not be written or freed
+void* const no_stream = (void*)-1;
+void check_write(const void* p, void* stream = no_stream) {   // not what unfinished work uses, unless behind it
     char* b = block_of(p);
     if (!b) { violations.push_back("write outside device memory"); return; }
     for (auto& r : readers)
-        if (r.second.count(b)) violations.push_back("write to a block that work under way reads");
+        if (r.first != stream && r.second.count(b) && (!waited.count(stream) || waited[stream][r.first] < r.second[b]))
+            violations.push_back("write to a block that work under way reads");
+}
+
+bool breaks_recording() {   // what a thread may not do while any stream is recording, unless it has relaxed its mode
+    if (recording.empty() || capture_mode == hipStreamCaptureModeRelaxed) return false;
+    counts["broken recordings"]++;
+    return true;
 }
 
 hipError_t launched(const char* name, void* stream, const MgkBatchDev* X = nullptr, const MgkBatchDev* Y = nullptr, int pairs = 0) {
+    if (failing == name) return hipErrorLaunchFailure;
     say("%s pairs=%d%s", name, pairs, recording.count(stream) ? " recorded" : "");
     if (X) reads(stream, X->graphs);
     if (Y) reads(stream, Y->graphs);
     return hipSuccess;
+}
+
+// Launches of the on-chip solvers: fits(job, g1, g2) for the graphs of every job, those of a swapped one
+// from the other batch if the kernel takes both orientations.
+template <class Fits>
+hipError_t launched_jobs(const char* name, void* stream, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n,
+                         size_t lds_bytes, bool both, const Fits& fits) {
+    if (lds_bytes > MGK_LDS_LIMIT_BYTES) return hipErrorInvalidValue;
+    for (int k = 0; k < n; ++k) {
+        const bool other = both && jobs[k].out1 == MGK_OUT1_SWAPPED;
+        if (!fits((other ? Y : X).graphs[jobs[k].g1], (other ? X : Y).graphs[jobs[k].g2]))
+            violations.push_back(std::string("a job of ") + name + " does not fit its launch");
+    }
+    return launched(name, stream, &X, &Y, n);
 }
 
 }  // namespace
@@ -93,7 +129,10 @@ void stub_reset() {
     counts.clear();
     limit = SIZE_MAX;
     converge_after = 3;
+    failing.clear();
+    capture_mode = hipStreamCaptureModeGlobal;
 }
+void stub_fail(const char* kernel) { failing = kernel; }
 void stub_clear_log() { log_text.clear(); }
 const char* stub_log() { return log_text.c_str(); }
 int stub_count(const char* what) { return counts[what]; }
@@ -112,8 +151,18 @@ void stub_replace_stream(void* stream) {
     void* name = new char;
     held.insert(name);
     readers[name].swap(readers[stream]);
+    waited[name].swap(waited[stream]);
+    auto rename = [&](Behind& b) {
+        if (!b.count(stream)) return;
+        b[name] = b[stream];
+        b.erase(stream);
+    };
+    for (auto& w : waited) rename(w.second);
     for (Event* e : events)
-        if (e->stream == stream && !e->done) e->stream = name;
+        if (!e->done) {
+            if (e->stream == stream) e->stream = name;
+            rename(e->behind);
+        }
 }
 void stub_set_limit(int64_t bytes) { limit = bytes < 0 ? SIZE_MAX : (size_t)bytes; }
 int64_t stub_in_use() { return (int64_t)in_use; }
@@ -130,6 +179,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "stub error"; }
 hipError_t hipMalloc(void** p, size_t bytes) {
     counts["malloc"]++;
+    if (breaks_recording()) return hipErrorStreamCaptureUnsupported;
     if (bytes > limit || in_use + bytes > limit) return hipErrorOutOfMemory;
     *p = malloc(bytes ? bytes : 1);
     device_memory[(char*)*p] = bytes;
@@ -137,6 +187,7 @@ hipError_t hipMalloc(void** p, size_t bytes) {
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void* p) {
+    if (breaks_recording()) return hipErrorStreamCaptureUnsupported;
     finish_all();   // waits for the device
     counts["free"]++;
     auto it = device_memory.find((char*)p);
@@ -155,24 +206,27 @@ hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
 }
 hipError_t hipHostFree(void* p) { pinned_bytes -= pinned[p]; pinned.erase(p); free(p); return hipSuccess; }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) {
+    if (breaks_recording()) return hipErrorStreamCaptureUnsupported;
     if (k == hipMemcpyHostToDevice) check_write(d);
     memcpy(d, s, n);
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
     if (recording.count(st)) counts["recorded copies"]++;
-    if (k == hipMemcpyHostToDevice) check_write(d);
+    if (k == hipMemcpyHostToDevice) check_write(d, st);
     memcpy(d, s, n);
     return hipSuccess;
 }
-hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { check_write(d); memset(d, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) { check_write(d, st); memset(d, v, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) {
     counts["stream waits"]++;
     if (recording.count(s)) { counts["broken recordings"]++; return hipErrorStreamCaptureUnsupported; }
+    if (breaks_recording()) return hipErrorStreamCaptureUnsupported;
     finish(s);
     return hipSuccess;
 }
-hipError_t hipDeviceSynchronize() { counts["device waits"]++; finish_all(); return hipSuccess; }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) { std::swap(*m, capture_mode); return hipSuccess; }
+hipError_t hipDeviceSynchronize() { counts["device waits"]++; if (breaks_recording()) return hipErrorStreamCaptureUnsupported; finish_all(); return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
     *st = recording.count(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
@@ -180,35 +234,84 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-    Event* ev = new Event{nullptr, true};
+    Event* ev = new Event{nullptr, true, {}};
     events.insert(ev);
     *e = (hipEvent_t)ev;
     return hipSuccess;
 }
 hipError_t hipEventDestroy(hipEvent_t e) { events.erase((Event*)e); delete (Event*)e; return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-    ((Event*)e)->stream = s;
-    ((Event*)e)->done = held.count(s) == 0;
+    Event* ev = (Event*)e;
+    if (recording.count(s)) counts["recorded events"]++;
+    ev->stream = s;
+    ev->done = held.count(s) == 0;
+    ev->behind.clear();
+    if (waited.count(s)) ev->behind = waited[s];
+    ev->behind[s] = ++now;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    Event* ev = (Event*)e;
+    if (recording.count(s)) counts["recorded waits"]++;
+    if (ev->done || ev->stream == s) return hipSuccess;
+    for (auto& b : ev->behind)
+        if (b.first != s) waited[s][b.first] = std::max(waited[s][b.first], b.second);
+    held.insert(s);
     return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t e) { return ((Event*)e)->done ? hipSuccess : hipErrorNotReady; }
-hipError_t hipEventSynchronize(hipEvent_t e) { if (!((Event*)e)->done) finish(((Event*)e)->stream); return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { counts["event waits"]++; if (!((Event*)e)->done) finish(((Event*)e)->stream); return hipSuccess; }
 
 }  // extern "C"
 
 // ---- the launchers
-#define STUB_SMALL(NAME)                                                                                          \
-    hipError_t NAME(int, bool, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n, const MgkParams&, \
-                    size_t, const MgkOutputs&, hipStream_t s) { return launched("small", s, &X, &Y, n); }
-STUB_SMALL(mgk_launch_small_w1) STUB_SMALL(mgk_launch_small_w2) STUB_SMALL(mgk_launch_small_w4)
-STUB_SMALL(mgk_launch_small_w8) STUB_SMALL(mgk_launch_small_w16) STUB_SMALL(mgk_launch_small_w4_fine)
+#define STUB_SMALL(NAME, W)                                                                                       \
+    hipError_t NAME(int ept, bool, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, const MgkParams&, \
+                    size_t lds, const MgkOutputs&, hipStream_t s) {                                               \
+        return launched_jobs("small", s, X, Y, jobs, n, lds, false,                                               \
+                             [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { return a.n * b.n <= W * 64 * ept; }); \
+    }
+STUB_SMALL(mgk_launch_small_w1, 1) STUB_SMALL(mgk_launch_small_w2, 2) STUB_SMALL(mgk_launch_small_w4, 4)
+STUB_SMALL(mgk_launch_small_w8, 8) STUB_SMALL(mgk_launch_small_w16, 16) STUB_SMALL(mgk_launch_small_w4_fine, 4)
 #define STUB_REGS(W, C)                                                                                           \
-    hipError_t mgk_launch_regs_w##W##_c##C(int, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n, \
-                                           const MgkParams&, size_t, const MgkOutputs&, hipStream_t s) { return launched("regs", s, &X, &Y, n); }
+    hipError_t mgk_launch_regs_w##W##_c##C(int ept, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
+                                           const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {      \
+        return launched_jobs("regs", s, X, Y, jobs, n, lds, false, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+            const int run = W == 4 ? a.regs_runs & 0xffff : (int)((uint32_t)a.regs_runs >> 16);                   \
+            return a.n * b.n <= W * 64 * ept && b.lane_len <= 64 * C && b.max_deg <= MGK_REGS_MAX_DEG &&           \
+                   run <= (W == 4 ? MGK_REGS_SMAX_W4 : MGK_REGS_SMAX_W8);                                         \
+        });                                                                                                       \
+    }
 STUB_REGS(4, 1) STUB_REGS(4, 2) STUB_REGS(8, 1) STUB_REGS(8, 2)
+#define STUB_REDUCED(W, C)                                                                                        \
+    hipError_t mgk_launch_reduced_w##W##_c##C(int ept, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
+                                              const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {   \
+        return launched_jobs("reduced", s, X, Y, jobs, n, lds, true, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+            const uint8_t* need = a.red_need + 2 * MGK_RED_LIST(W);                                               \
+            return need[0] <= MGK_RED_BLACK(W) && need[1] <= MGK_RED_RED(W) && b.lane_len <= 64 * C &&            \
+                   b.max_deg <= MGK_REGS_MAX_DEG && a.n_red * b.n <= W * 64 * ept &&                              \
+                   W * 64 * ept + (a.n - a.n_red) * b.n <= MGK_RED_MAX_P &&                                       \
+                   (size_t)mgk_reduced_plan(a.n, a.n_red, b.n, W, ept).total * 4 <= lds;                          \
+        });                                                                                                       \
+    }
+STUB_REDUCED(2, 1) STUB_REDUCED(4, 1) STUB_REDUCED(4, 2) STUB_REDUCED(8, 1) STUB_REDUCED(8, 2)
+#define STUB_PCG_SEP(RK)                                                                                          \
+    hipError_t mgk_launch_pcg_sep_rk##RK(int waves, int ept, int, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, \
+                                         const MgkSepList& SY, const MgkJob* jobs, int n, const MgkParams&, int rb, size_t lds, \
+                                         const MgkOutputs&, hipStream_t s) {                                      \
+        reads(s, SX.packets);                                                                                     \
+        reads(s, SY.packets);                                                                                     \
+        return launched_jobs("pcg_sep", s, X, Y, jobs, n, lds, false, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+            return a.n * b.n <= waves * 64 * ept &&                                                               \
+                   (size_t)mgk_pcg_sep_plan(std::max(a.n, b.n), std::min(a.n, b.n), RK, rb).total * 4 <= lds;     \
+        });                                                                                                       \
+    }
+STUB_PCG_SEP(1) STUB_PCG_SEP(4) STUB_PCG_SEP(5) STUB_PCG_SEP(6) STUB_PCG_SEP(7)
 #define STUB_SELL(W)                                                                                              \
-    hipError_t mgk_launch_sell_w##W(int, int, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob*, int n,    \
-                                    const MgkParams&, size_t, const MgkOutputs&, hipStream_t s) { return launched("sell", s, &X, &Y, n); }
+    hipError_t mgk_launch_sell_w##W(int, int, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
+                                    const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {             \
+        return launched_jobs("sell", s, X, Y, jobs, n, lds, false, [](const MgkGraphDesc&, const MgkGraphDesc&) { return true; }); \
+    }
 STUB_SELL(4) STUB_SELL(8) STUB_SELL(16)
 hipError_t mgk_noalloc_job_storage(int, MgkJob** jobs, int64_t* capacity) {
     static MgkJob* storage = nullptr;
@@ -236,7 +339,12 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
 static MgkSepBasis basis;
 extern "C" const MgkSepBasis* stub_basis() { return &basis; }   // of the last features
 hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepLayout&, const MgkSepList&, const MgkSepGraph*,
-                               int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep pack", s, &B, nullptr, n_used); }
+                               int n_used, int, float* packets, hipStream_t s) {
+    basis = S;
+    check_write(packets, s);
+    reads(s, packets);   // as under way as a reader
+    return launched("sep pack", s, &B, nullptr, n_used);
+}
 hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph*, int n_used, int, float*, hipStream_t s) { basis = S; return launched("sep dense pack", s, &B, nullptr, n_used); }
 hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&,
                               const MgkSepLayout&, const MgkLargePair*, const MgkSepAt*, MgkPairState*, float*, const MgkParams&, int n, int max_n1,
