@@ -299,8 +299,7 @@ struct mgk_ctx {
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
     DevBuf onchip_packets[2];           // packets of the separable product on chip
-    hipEvent_t onchip_packets_end = nullptr;   // of the last kernel that reads them, and its stream
-    hipStream_t onchip_packets_stream = nullptr;
+    hipEvent_t onchip_packets_end = nullptr;   // of the last kernel that reads them
     bool features_in_use = false;       // by the call under way
     KeptBasis bases[4];                 // of the last label ranges and edge kernels, see sep_basis_for
     int next_basis = 0;
@@ -1778,10 +1777,10 @@ mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch*
         ~InUse() { flag = false; }
     } in_use{ctx->features_in_use};
     ctx->features_in_use = true;
-    // a call on another stream may still read the packets
+    // An earlier call may still read the packets, also one on a stream of the same handle: destroyed since, or the
+    // per-thread stream of another thread.  The stream waits, not the host.
     if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
-    else if (ctx->onchip_packets_stream != stream) MGK_HIP(ctx, hipEventSynchronize(ctx->onchip_packets_end));
-    ctx->onchip_packets_stream = stream;
+    else MGK_HIP(ctx, hipStreamWaitEvent(stream, ctx->onchip_packets_end, 0));
     for (int k = 0; k < sides; ++k) {
         const mgk_batch* b = bt[k];
         sl[k] = b->sep[gi];

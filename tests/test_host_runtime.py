@@ -343,3 +343,35 @@ def test_label_range_at_which_the_form_is_first_looked_for(host):
         paths.append(host.launch_log().split(" ")[0])
     assert paths[0] == paths[1] and paths[2] == paths[3], paths
     host.free(B)
+
+
+def streaming(host, labels=(0.0, 1.0), n=90, k=8, count=24):
+    """Graphs whose pairs take the separable product on chip."""
+    host.set("edge_kernel_se", 1.0)
+    return host.load(graphs(*[ring(n, k, np.linspace(*labels, n * k))] * count))
+
+
+def test_packets_on_chip_wait_for_calls_that_read_them(host):
+    """Also for those on a stream of the same handle that is gone."""
+    B = streaming(host)
+    assert host.gram(B) == 0   # makes the list
+    for stream in (5, 5, 6):
+        host.hold(stream)
+        assert host.gram(B, stream) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
+        host.lib.stub_replace_stream(C.c_void_p(5))
+    assert host.violations() == ""
+    host.free(B)
+
+
+def test_calls_on_two_streams_do_not_wait_on_the_host(host):
+    """A Gram of pairs solved on chip is enqueued while another stream still solves one."""
+    B = streaming(host)
+    for stream in (5, 6):   # memory is allocated by the first call
+        assert host.gram(B, stream) == 0
+    waits = ("stream waits", "device waits", "event waits", "free")
+    before = [host.count(w) for w in waits]
+    for stream in (5, 6, 5, 6):
+        host.hold(stream)
+        assert host.gram(B, stream) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
+    assert [host.count(w) for w in waits] == before and host.violations() == ""
+    host.free(B)
