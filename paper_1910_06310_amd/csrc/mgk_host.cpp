@@ -1721,11 +1721,27 @@ double onchip_sep_gain(const JobBin& b, int rank_executed, int passes) {
     return 8.0 * rounds * ((double)b.sep.entries / 6.0 - (double)b.sep.halves * rank_executed / 18.0 - 300.0 * passes * (double)b.sep.blocks);
 }
 
+// Writing and reading the packets of a call: its end is recorded on every way out once something may be enqueued.
+struct PacketUse {
+    mgk_ctx* ctx;
+    hipStream_t stream;
+    bool open = false;
+    hipError_t end() {
+        open = false;
+        return hipEventRecord(ctx->onchip_packets_end, stream);
+    }
+    ~PacketUse() {
+        if (!open || end() == hipSuccess) return;
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(stream);   // nothing to wait for is left, then
+    }
+};
+
 // The bins of a call that take the separable product on chip (use[k].waves > 0), and its packets in sl[].
 // Not while a graph is recorded (the packets belong to the context), nor where the caller asked for
 // the streaming solver or allows no allocation.
 mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl, bool may_allocate, hipStream_t stream,
-                              std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2]) {
+                              std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2], PacketUse& packets) {
     const bool kernel_ok = ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST;
     if (!mgk_launch_pcg_sep_rk5 || !may_allocate || !kernel_ok || ctx->tile_path != MGK_TILE_AUTO || ctx->product_cache == 0 || ctx->waves != 0)
         return MGK_OK;
@@ -1794,6 +1810,7 @@ mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch*
         sl[k].packets = (const float*)buf.p;
         int32_t max_n = 1;
         for (const MgkGraphDesc& g : b->graphs) max_n = std::max(max_n, g.n);
+        packets.open = true;
         hipError_t e = mgk_launch_sep_pack(b->dev, S, L, sl[k], sl[k].whole, b->n_graphs, max_n, (float*)buf.p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
@@ -1814,8 +1831,8 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     std::vector<OnchipSep> sep(jl.bins.size());
     MgkSepLayout onchip_layout{};
     MgkSepList onchip_lists[2] = {};
-    if (mgk_status st = prepare_onchip_sep(ctx, X, Y, jl, may_allocate, stream, sep, onchip_layout, onchip_lists)) return st;
-    bool any_sep = false;
+    PacketUse packets{ctx, stream};
+    if (mgk_status st = prepare_onchip_sep(ctx, X, Y, jl, may_allocate, stream, sep, onchip_layout, onchip_lists, packets)) return st;
     for (const JobBin& b : jl.bins) {
         const OnchipSep& s = sep[(size_t)(&b - jl.bins.data())];
         if (s.waves > 0)
@@ -1836,7 +1853,6 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             const int64_t chunk = std::min<int64_t>(b.count - done, (int64_t)1 << 30);
             const MgkBatchDev& o = b.swapped ? Y->dev : X->dev;
             const MgkBatchDev& i = b.swapped ? X->dev : Y->dev;
-            any_sep = any_sep || s.waves > 0;
             hipError_t e = s.waves > 0
                 ? mgk_launch_pcg_sep(onchip_layout.rk, s.waves, s.ept, onchip_layout.passes, o, i, onchip_lists[b.swapped ? 1 : 0],
                                      onchip_lists[b.swapped ? 0 : 1], jl.dev + b.first + done, (int)chunk, prm, s.rb, s.lds_bytes, out, stream)
@@ -1856,7 +1872,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             done += chunk;
         }
     }
-    if (any_sep) MGK_HIP(ctx, hipEventRecord(ctx->onchip_packets_end, stream));
+    if (packets.open) MGK_HIP(ctx, packets.end());
     if (!any_large) return MGK_OK;
     // ---- pairs with vectors in global memory: the product of each from the current edge kernel
     const bool may_sep = ctx->tile_path == MGK_TILE_AUTO && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST);

@@ -375,3 +375,26 @@ def test_calls_on_two_streams_do_not_wait_on_the_host(host):
         assert host.gram(B, stream) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
     assert [host.count(w) for w in waits] == before and host.violations() == ""
     host.free(B)
+
+
+@pytest.mark.parametrize("way", ["short memory for the second side", "a launch behind it fails"])
+def test_packets_of_a_call_that_leaves_early_have_an_end(host, way):
+    """What it has enqueued by then writes or reads them."""
+    X, Y = streaming(host), streaming(host, (0.0, 0.9), n=96)
+    i = np.arange(24).repeat(12)
+    assert host.gram(X, stream=6) == 0 and host.pairs(X, X, i, i, stream=5) == 0, host.error()
+    if way == "a launch behind it fails":
+        assert host.pairs(X, Y, i, i, stream=5) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
+        host.lib.stub_fail(b"pcg_sep")
+    else:
+        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use()))
+    try:
+        host.hold(5)
+        st = host.pairs(X, Y, i, i, stream=5)
+        assert (st, "mgk_pcg_sep" in host.launch_log()) == ((3, True) if way == "a launch behind it fails" else (0, False))
+        host.lib.stub_fail(b"")
+        host.lib.stub_set_limit(C.c_int64(-1))
+        assert host.gram(X, stream=6) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
+        assert host.violations() == ""
+    finally:
+        host.lib.stub_set_limit(C.c_int64(-1))
