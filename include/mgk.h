@@ -161,7 +161,7 @@ mgk_status mgk_set_product_cache(mgk_ctx* ctx, int32_t enable);
  * residual.  Its iterates, and their number, are not those of Alg. 1 on the
  * full system.  1 (default): the reduced system is solved by calls that pass no
  * iters_dev while max_iter is automatic, the full one by the others (a recorded mgk_gram
- * takes the job list an earlier call has left).  0: always the full system, 2: always the
+ * of the first kind takes the job list of the second where only that is there).  0: always the full system, 2: always the
  * reduced one, whose iterations are then counted and limited.  Values agree to
  * rounding and to what the stop test leaves, flags are the same. */
 mgk_status mgk_set_reduced_system(mgk_ctx* ctx, int32_t mode);

@@ -14,6 +14,7 @@
 #include <mutex>
 #include <new>
 #include <numeric>
+#include <optional>
 #include <stdexcept>
 #include <string>
 #include <system_error>
@@ -262,6 +263,7 @@ struct mgk_batch {
         int sorted = 0;      // schedule
         int attr_dim = -1;   // label attributes of the edge kernel (LDS plan)
     } gram_jobs[2];          // small pairs by the full system, by the reduced one
+    std::vector<void*> old_jobs;   // lists replaced while a graph was recorded, when none may be freed
 };
 
 struct KeptBasis {
@@ -527,6 +529,16 @@ mgk_status refuse_capture(mgk_ctx* ctx, hipStream_t stream) {
     if (!capturing(stream)) return MGK_OK;
     return fail(ctx, MGK_EDEVICE, "operation not permitted when stream is capturing");
 }
+
+// While it lives the thread may allocate, and wait for streams that take no part in a recording, while a graph is recorded.
+class RelaxedCapture {
+public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
 
 // What a call reads.  done() records its end, one event a call (4 us; a second one, behind the copies of the
 // lists, took as long again); a batch of a call that fails on the way, that is part of a recorded graph, or
@@ -2763,6 +2775,7 @@ void mgk_free_batch(mgk_ctx*, mgk_batch* batch) {   // the context may be gone
     if ((batch->blob && !kept) || batch->gram_jobs[0].list.dev || batch->gram_jobs[1].list.dev) (void)hipDeviceSynchronize();
     for (auto& g : batch->gram_jobs)
         if (g.list.dev) (void)hipFree(g.list.dev);
+    for (void* p : batch->old_jobs) (void)hipFree(p);
     if (batch->blob && !kept) (void)hipFree(batch->blob);
     delete batch;
 }
@@ -2827,17 +2840,35 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     };
     bool reduced = solve_reduced(ctx, iters_dev);
     const int waves = reduced_waves(G * (G + 1) / 2);
-    // a graph that is recorded takes the list that is there
-    if (!built(batch->gram_jobs[reduced]) && built(batch->gram_jobs[!reduced]) && capturing(stream)) reduced = !reduced;
+    // While a graph is recorded the list has to be there.  The one of the other system will do if the call shows no iterates and the
+    // system was not asked for; otherwise it says that a list of the batch was made with these settings, and the one wanted is made now,
+    // on a stream that takes no part in the recording.
+    bool beside = false;
+    if (!built(batch->gram_jobs[reduced]) && built(batch->gram_jobs[!reduced]) && capturing(stream)) {
+        if (reduced && ctx->reduced_system == 1) reduced = false;
+        else beside = true;
+    }
     mgk_batch::GramJobs& jobs = batch->gram_jobs[reduced];
+    std::optional<RelaxedCapture> relaxed;
+    if (beside) {
+        relaxed.emplace();
+        if (!ctx->upload) MGK_HIP(ctx, hipStreamCreateWithFlags(&ctx->upload, hipStreamNonBlocking));
+        if (jobs.list.dev) {
+            batch->old_jobs.push_back(jobs.list.dev);
+            jobs.list.dev = nullptr;
+        }
+    }
     if (jobs.list.dev != nullptr && !built(jobs)) {
         if (mgk_status st = refuse_capture(ctx, stream)) return st;
         MGK_HIP(ctx, hipStreamSynchronize(stream));  // launch shape changed: rebuild the job list
         MGK_HIP(ctx, hipFree(jobs.list.dev));
         jobs.list.dev = nullptr;
+        for (void* p : batch->old_jobs) (void)hipFree(p);
+        batch->old_jobs.clear();
     }
     if (jobs.list.dev == nullptr && G > 0) {
-        if (mgk_status st = refuse_capture(ctx, stream)) return st;   // the list is copied and waited for
+        if (!beside)   // the list is copied and waited for
+            if (mgk_status st = refuse_capture(ctx, stream)) return st;
         // a4: job list, one job per unordered pair, kept with the batch
         JobPlan plan;
         plan.jobs.reserve((size_t)(G * (G + 1) / 2));
@@ -2890,7 +2921,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                 hj.shape = plan.shape_of(pl, false, batch->graphs[i], batch->graphs[j]);   // one batch: swapping is done through the indices
                 plan.jobs.push_back(hj);
             }
-        mgk_status st = build_job_list(ctx, plan, jobs.list, stream, nullptr);
+        mgk_status st = build_job_list(ctx, plan, jobs.list, beside ? ctx->upload : stream, nullptr);
         jobs.waves = ctx->waves;
         jobs.max_iter = ctx->max_iter;
         jobs.limit = ctx->onchip_limit;
@@ -2899,6 +2930,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         jobs.attr_dim = attr_dim_of(ctx);
         if (st != MGK_OK) return st;
     }
+    relaxed.reset();
     batch->untracked = true;   // its job list has freeing wait as well
     const MgkOutputs out{K_dev, iters_dev, flag_dev, nullptr, nullptr};
     return launch_jobs(ctx, batch, batch, jobs.list, out, stream);

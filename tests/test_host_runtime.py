@@ -398,3 +398,46 @@ def test_packets_of_a_call_that_leaves_early_have_an_end(host, way):
         assert host.violations() == ""
     finally:
         host.lib.stub_set_limit(C.c_int64(-1))
+
+
+def gram(host, batch, stream=0, counts=False):
+    return host.lib.mgk_gram(host.ctx, batch, host.out(), host.out() if counts else None, None, C.c_void_p(stream))
+
+
+@pytest.mark.parametrize("first,mode,counts,kernel", [
+    (False, 1, True, "regs"), (False, 0, False, "regs"), (False, 0, True, "regs"), (False, 2, True, "reduced"),
+    (True, 2, False, "reduced"), (True, 2, True, "reduced"), (True, 1, False, "regs"), (False, 1, False, "reduced")])
+def test_recorded_gram_solves_the_system_it_says(host, first, mode, counts, kernel):
+    """After an eager Gram with (first) or without iteration counts: whose counts are asked for, or whose mode names the
+    system, gets that system, also if its list has to be made; nothing of that is recorded."""
+    host.set("edge_kernel_se", 0.1)
+    B = host.load(W.config1(12))
+    assert gram(host, B, 3, first) == 0
+    host.set("reduced_system", mode)
+    host.lib.stub_clear_log()
+    with host.recording(3):
+        for _ in range(2):
+            assert gram(host, B, 3, counts) == 0, host.error()
+    assert re.findall(r"^(\w+) .* recorded$", host.log(), re.M) == [kernel] * (len(host.log().split("\n")) - 1) and kernel in host.log()
+    assert host.count("recorded copies") == host.count("broken recordings") == 0 and host.violations() == ""
+    host.free(B)
+
+
+def test_recorded_gram_of_a_batch_with_an_older_list(host):
+    """The list that is wanted was made with other settings, the other one with these; no list with these is refused."""
+    host.set("edge_kernel_se", 0.1)
+    B = host.load(W.config1(12))
+    before = host.lib.stub_in_use()
+    for k in range(3):
+        host.set("schedule", k % 2)
+        with host.recording(3):
+            assert gram(host, B, 3, k % 2 == 0) == 3 and "captur" in host.error()
+        assert gram(host, B) == 0
+        with host.recording(3):
+            assert gram(host, B, 3, True) == 0, host.error()
+        assert gram(host, B, 0, True) == 0
+        if k == 0:
+            kept = host.lib.stub_in_use()
+    assert host.count("recorded copies") == host.count("broken recordings") == 0 and host.violations() == ""
+    assert host.lib.stub_in_use() - before <= 2 * (kept - before)
+    host.free(B)
