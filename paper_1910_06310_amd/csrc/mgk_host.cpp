@@ -409,7 +409,9 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
         int parts = 1;
         int64_t cur = 0;
         for (int i = 0; i < n; ++i) {
-            if (cur + row_cost(i) > bound) { ++parts; cur = row_cost(i); } else cur += row_cost(i);
+            const bool over = cur + row_cost(i) > bound;   // without a branch: rows of molecules are hard to foresee
+            parts += over;
+            cur = (over ? 0 : cur) + row_cost(i);
         }
         return parts;
     };
@@ -430,71 +432,182 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
     return longest;
 }
 
-// Colours of the vertices of a graph for the reduced solver (see MgkReducedPlan): black[i] = 1 for a
-// set of vertices of which no two are adjacent, found greedily (a vertex with the fewest undecided
-// neighbours next; neighbours of a black vertex are red), at least one vertex red.  Molecule-like graphs have
-// 55 % black vertices, rings 50 %.  Returns the number of red ones.  New graphs are often few and compared at once, so
-// that their schedules count: keys of the vertices with edges lie side by side, and the next one is a plain minimum.
-int colour_vertices(int n, const std::vector<int32_t>& deg, const int32_t* rowptr, const MgkEntry* list, std::vector<uint8_t>& black,
-                    std::vector<int32_t>& slot) {
-    constexpr int32_t kDecided = INT32_MAX;
-    int32_t key[MGK_RED_MAX_NNZ], vertex[MGK_RED_MAX_NNZ];   // undecided neighbours << 16 | position
-    int count = 0;
-    black.assign((size_t)n, 1);   // as those without a neighbour stay
-    slot.resize((size_t)n);
-    for (int i = 0; i < n; ++i)
-        if (deg[i] > 0) {
-            slot[(size_t)i] = count;
-            vertex[count] = i;
-            key[count] = deg[i] << 16 | count;
-            ++count;
+// Schedule of a graph as outer operand of the reduced solver (see MgkReducedPlan), one graph after another.  New graphs
+// are often few and compared at once, so that the schedules count: 4.4 us a molecule-like graph of 35 vertices with a
+// scan over all vertices for the next one to colour and a branch for every row and nonzero, 2.6 us like this.
+class ReducedSchedule {
+public:
+    static bool makes(const MgkGraphDesc& gd) { return gd.nnz <= MGK_RED_MAX_NNZ && gd.n < 65536; }
+
+    // The graph's n vertices (deg_order: by descending degree) and nonzeros by rows; what is filled: its parts of list_sched,
+    // red_split and red_order of MgkBatchDev.
+    void make(MgkGraphDesc& gd, const int32_t* rowptr, const MgkEntry* entries, const int32_t* deg_order, uint32_t* list, uint16_t* split,
+              uint16_t* order) {
+        const int n = gd.n;
+        for (int k = 0; k < gd.nnz; ++k) col_[k] = (uint16_t)entries[k].y;
+        std::fill_n(col_ + gd.nnz, 4, (uint16_t)0);
+        deg_.resize((size_t)n);
+        for (int i = 0; i < n; ++i) deg_[(size_t)i] = (i + 1 < n ? rowptr[i + 1] : gd.nnz) - rowptr[i];
+        gd.n_red = colour(n, rowptr);
+        int count[2] = {}, nnz[2] = {};
+        for (auto& r : rows_) r.resize((size_t)n);
+        for (int k = 0; k < n; ++k) {   // by descending number of nonzeros
+            const int i = deg_order[k], c = black_[(size_t)i];
+            rows_[0][(size_t)count[0]] = rows_[1][(size_t)count[1]] = i;
+            count[c]++;
+            nnz[c] += deg_[(size_t)i];
         }
-    int reds = 0;
-    while (true) {
-        int32_t next = kDecided;
-        for (int c = 0; c < count; ++c) next = std::min(next, key[c]);
-        if (next == kDecided) break;
-        const int v = vertex[next & 0xffff];
-        key[next & 0xffff] = kDecided;
-        for (int a = 0; a < deg[v]; ++a) {
-            const int u = (int)list[rowptr[v] + a].y, su = slot[(size_t)u];
-            if (key[su] == kDecided) continue;
-            key[su] = kDecided;
-            black[(size_t)u] = 0;
-            ++reds;
-            for (int b = 0; b < deg[u]; ++b) {
-                int32_t& k = key[slot[list[rowptr[u] + b].y]];
-                if (k != kDecided && k >> 16 > 0) k -= 1 << 16;
+        pos_.resize((size_t)n);
+        of_wave_.resize((size_t)n);
+        divide<2>(gd, rowptr, count, nnz, list, split, order);
+        divide<4>(gd, rowptr, count, nnz, list, split, order);
+        divide<8>(gd, rowptr, count, nnz, list, split, order);
+    }
+
+private:
+    // black_[i] = 1 for a set of vertices of which no two are adjacent, found greedily (a vertex with the fewest undecided
+    // neighbours next, the first of them; neighbours of a black vertex are red), at least one vertex red.
+    // Molecule-like graphs have 55 % black vertices, rings 50 %.  Returns the number of red ones.
+    int colour(int n, const int32_t* rowptr) {
+        int count = 0, most = 0;
+        slot_.resize((size_t)n);
+        black_.assign((size_t)n, 1);   // as those without a neighbour stay
+        for (int i = 0; i < n; ++i)
+            if (deg_[(size_t)i] > 0) {
+                slot_[(size_t)i] = (uint8_t)count;
+                vertex_[count++] = i;
+                most = std::max(most, deg_[(size_t)i]);
+            }
+        const int reds = count <= 64 ? colour_sets<1>(count, most, rowptr) : colour_sets<3>(count, most, rowptr);
+        if (reds > 0) return reds;
+        black_[0] = 0;   // no edges
+        return 1;
+    }
+    // Sets of vertices as Q words of 64; plane p: bit p of the number of undecided neighbours.
+    template <int Q>
+    int colour_sets(int count, int most, const int32_t* rowptr) {
+        static_assert(MGK_RED_MAX_NNZ <= 192, "a vertex with edges has one nonzero at least");
+        uint64_t adj[64 * Q][Q], left[Q] = {}, plane[8][Q] = {};
+        int planes = 0;
+        while (most >> planes) ++planes;
+        for (int c = 0; c < count; ++c) {
+            const int i = vertex_[c], d = deg_[(size_t)i];
+            for (int q = 0; q < Q; ++q) adj[c][q] = 0;
+            for (int k = rowptr[i]; k < rowptr[i] + d; ++k) {
+                const int u = slot_[col_[k]];
+                adj[c][u >> 6] |= 1ull << (u & 63);
+            }
+            left[c >> 6] |= 1ull << (c & 63);
+            for (int p = 0; p < planes; ++p) plane[p][c >> 6] |= (uint64_t)(d >> p & 1) << (c & 63);
+        }
+        int reds = 0;
+        while (true) {
+            uint64_t fewest[Q], any = 0;
+            for (int q = 0; q < Q; ++q) any |= fewest[q] = left[q];
+            if (any == 0) return reds;
+            for (int p = planes - 1; p >= 0; --p) {   // those without the bit, if there are any
+                uint64_t without[Q], some = 0;
+                for (int q = 0; q < Q; ++q) some |= without[q] = fewest[q] & ~plane[p][q];
+                for (int q = 0; q < Q; ++q) fewest[q] = some ? without[q] : fewest[q];
+            }
+            int v = 0;
+            for (int q = Q - 1; q >= 0; --q)
+                if (fewest[q]) v = 64 * q + __builtin_ctzll(fewest[q]);
+            left[v >> 6] &= ~(1ull << (v & 63));
+            uint64_t red[Q];
+            for (int q = 0; q < Q; ++q) {
+                red[q] = adj[v][q] & left[q];
+                left[q] &= ~red[q];
+            }
+            for (int q = 0; q < Q; ++q)
+                for (; red[q]; red[q] &= red[q] - 1) {
+                    const int u = 64 * q + __builtin_ctzll(red[q]);
+                    black_[(size_t)vertex_[u]] = 0;
+                    ++reds;
+                    for (int w = 0; w < Q; ++w) {   // one undecided neighbour less
+                        uint64_t borrow = adj[u][w] & left[w];
+                        for (int p = 0; p < planes; ++p) {
+                            const uint64_t was = plane[p][w];
+                            plane[p][w] = was ^ borrow;
+                            borrow &= ~was;
+                        }
+                    }
+                }
+        }
+    }
+
+    // Rows of one colour (by descending number of nonzeros) divided among W wavefronts: each row goes to the
+    // one with the least work so far.  A row of deg nonzeros costs about 4 deg + 9 wave instructions of a product
+    // (two inner chunks: an address add and a multiply-add per nonzero and chunk, the row sums and the
+    // store at its end).  rows_in[w]: rows wavefront w gets.  Returns the most nonzeros a wavefront gets.
+    template <int W>
+    int divide_rows(const std::vector<int32_t>& rows, int count, int* rows_in) {
+        int32_t cost[W];   // times 8, and the wavefront
+        int nnz[W] = {};
+        for (int w = 0; w < W; ++w) cost[w] = w;
+        std::fill_n(rows_in, W, 0);
+        for (int k = 0; k < count; ++k) {   // those without any come last: nothing is stored for them
+            const int d = deg_[(size_t)rows[(size_t)k]];
+            int32_t least = cost[0];
+            for (int w = 1; w < W; ++w) least = std::min(least, cost[w]);
+            const int w = least & 7;
+            cost[w] = least + 8 * (4 * d + 9);
+            nnz[w] += d;
+            of_wave_[(size_t)k] = (uint8_t)w;
+            rows_in[w]++;
+        }
+        return *std::max_element(nnz, nnz + W);
+    }
+
+    template <int W>
+    void divide(MgkGraphDesc& gd, const int32_t* rowptr, const int* count, const int* nnz, uint32_t* list, uint16_t* split, uint16_t* order) {
+        constexpr int which = MGK_RED_LIST(W);
+        // more nonzeros than the wavefronts hold: no need to divide them (the place stays, unread)
+        if (nnz[0] > W * MGK_RED_RED(W) || nnz[1] > W * MGK_RED_BLACK(W)) return;
+        uint16_t* sp = split + MGK_RED_SPLIT(W);
+        uint16_t* ord = order + (int64_t)which * gd.n;
+        int at = 0, rows_in[2][W];
+        for (int c = 0; c < 2; ++c) {
+            const int most = divide_rows<W>(rows_[c], count[c], rows_in[c]);
+            gd.red_need[2 * which + 1 - c] = (uint8_t)std::min(most, 255);
+            int next[W];
+            for (int w = 0; w < W; ++w) {
+                sp[(3 - c) * W + 1 + w] = (uint16_t)(next[w] = at);
+                at += rows_in[c][w];
+            }
+            for (int k = 0; k < count[c]; ++k) {
+                const int to = next[of_wave_[(size_t)k]]++, i = rows_[c][(size_t)k];
+                pos_[(size_t)i] = (uint16_t)to;
+                ord[to] = (uint16_t)i;
             }
         }
+        uint32_t* out = sched_;
+        for (int w = 0; w < W; ++w) {
+            uint32_t* const begin = out;
+            sp[w] = (uint16_t)(begin - sched_);
+            for (int c = 1; c >= 0; --c) {
+                const uint16_t* row = ord + sp[(3 - c) * W + 1 + w];
+                for (int r = 0; r < rows_in[c][w]; ++r) {
+                    const int k = rowptr[row[r]], d = deg_[row[r]];
+                    for (int a = 0; a < 4; ++a)   // most rows have no more; the next one overwrites what is none of this row's
+                        out[a] = (uint32_t)(k + a) | (uint32_t)pos_[col_[k + a]] << 16;
+                    for (int a = 4; a < d; ++a) out[a] = (uint32_t)(k + a) | (uint32_t)pos_[col_[k + a]] << 16;
+                    out += d;
+                }
+                if (c) sp[W + 1 + w] = (uint16_t)(out - begin);
+            }
+        }
+        sp[W] = (uint16_t)(out - sched_);
+        std::copy_n(sched_, gd.nnz, list + (int64_t)which * gd.nnz);
     }
-    if (reds == 0) {   // no edges
-        black[0] = 0;
-        reds = 1;
-    }
-    return reds;
-}
 
-// Rows of one colour (by descending number of nonzeros) divided among `waves` wavefronts: each row goes to the
-// one with the least work so far.  A row of deg nonzeros costs about 4 deg + 9 wave instructions of a product
-// (two inner chunks: an address add and a multiply-add per nonzero and chunk, the row sums and the
-// store at its end).  of_wave[k]: the wavefront of row k; rows_in[w]: rows wavefront w gets.  Returns the most nonzeros
-// a wavefront gets.
-int divide_rows(const std::vector<int32_t>& rows, const std::vector<int32_t>& deg, int waves, uint8_t* of_wave, int* rows_in) {
-    int cost[8] = {}, nnz[8] = {}, most = 0;
-    std::fill_n(rows_in, waves, 0);
-    for (size_t k = 0; k < rows.size(); ++k) {   // those without any come last: nothing is stored for them
-        const int d = deg[(size_t)rows[k]];
-        int w = 0;
-        for (int v = 1; v < waves; ++v) w = cost[v] < cost[w] ? v : w;
-        cost[w] += 4 * d + 9;
-        nnz[w] += d;
-        most = std::max(most, nnz[w]);
-        of_wave[k] = (uint8_t)w;
-        rows_in[w]++;
-    }
-    return most;
-}
+    uint16_t col_[MGK_RED_MAX_NNZ + 4];        // columns of the nonzeros, then four zeros
+    int32_t vertex_[MGK_RED_MAX_NNZ];          // those with edges
+    uint32_t sched_[MGK_RED_MAX_NNZ + 4];
+    std::vector<uint8_t> slot_, black_, of_wave_;
+    std::vector<int32_t> deg_, rows_[2];
+    std::vector<uint16_t> pos_;                // places of the vertices in the order
+};
 
 // attributes per edge label that the edge kernel reads (0 for the kernels on plain
 // scalar labels); the streaming on-chip solver keeps them in LDS for the outer graph
@@ -2295,13 +2408,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->label_lo = INFINITY;
     B->label_hi = -INFINITY;
     std::vector<int32_t> regs_split;                // its division of every graph's rows among wavefronts
-    std::vector<uint16_t> red_split, red_order((size_t)(3 * tot_v));   // schedules of the reduced solver
-    std::vector<uint32_t> list_sched;
-    std::vector<uint8_t> black;
-    std::vector<uint8_t> of_wave;
-    std::vector<int32_t> red_pos, rows_of[2], red_slot;
-    if (tot_e <= MGK_RED_MAX_NNZ / 2 * (int64_t)n_graphs) list_sched.reserve((size_t)(6 * tot_e));
-    red_split.reserve((size_t)n_graphs * MGK_RED_SPLIT_STRIDE);
+    size_t list_sched_size = 0;
     list_outer.reserve((size_t)(2 * tot_e));
     // label attributes in the order of the two lists, attribute-major; filled after the loop
     // (the plane stride is the batch total): (position, edge) pairs collected meanwhile
@@ -2313,8 +2420,9 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->e.reserve((size_t)(2 * tot_e));
     double label_sum = 0.0;
 
-    struct Nz { uint64_t key; float w, e; int64_t edge; };
-    std::vector<Nz> nz;
+    struct Nz { uint32_t i, j; float w, e; int64_t edge; };
+    std::vector<Nz> nz, given;
+    std::vector<int32_t> sorted[2], bucket, seen;
     MgkAdj adj;
     std::vector<int32_t> cursor;
 
@@ -2400,11 +2508,14 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             adj.idx[cursor[src[k]]++] = dst[k];
             adj.idx[cursor[dst[k]]++] = src[k];
         }
+        seen.assign((size_t)n, -1);
         for (int i = 0; i < n; ++i) {  // duplicate edges
-            std::sort(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]);
-            if (std::adjacent_find(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]) !=
-                adj.idx.begin() + adj.ptr[i + 1])
-                return fail(ctx, MGK_EINVAL, "graph %d: duplicate edge at vertex %d", g, i);
+            bool twice = false;
+            for (int k = adj.ptr[i]; k < adj.ptr[i + 1]; ++k) {
+                twice |= seen[(size_t)adj.idx[(size_t)k]] == i;
+                seen[(size_t)adj.idx[(size_t)k]] = i;
+            }
+            if (twice) return fail(ctx, MGK_EINVAL, "graph %d: duplicate edge at vertex %d", g, i);
         }
         if (start_prob)
             for (int i = 0; i < n; ++i)
@@ -2413,6 +2524,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
 
         // ---- a2: vertex order
         std::vector<int32_t> perm;
+        if (pre_perm[(size_t)g].empty() && (reorder == MGK_REORDER_PBR || reorder == MGK_REORDER_RCM))
+            for (int i = 0; i < n; ++i) std::sort(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]);
         if (!pre_perm[(size_t)g].empty()) perm = std::move(pre_perm[(size_t)g]);
         else if (reorder == MGK_REORDER_PBR) perm = mgk_order_pbr(adj, kTile);
         else if (reorder == MGK_REORDER_RCM) perm = mgk_order_rcm(adj);
@@ -2440,8 +2553,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
 
         // ---- a3: cut into octiles, drop empty ones, bitmap-pack
         const int ntr = (n + kTile - 1) / kTile;
-        nz.clear();
-        nz.reserve((size_t)(2 * m));
+        given.clear();
+        given.reserve((size_t)(2 * m));
         for (int64_t k = e0; k < e1; ++k) {
             const float wv = weight ? weight[k] : 1.f;
             const float ev = edge_label ? edge_label[k * D] : 0.f;
@@ -2452,11 +2565,27 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             const int a = perm[src[k]], b = perm[dst[k]];
             for (int dir = 0; dir < 2; ++dir) {
                 const int i = dir ? b : a, j = dir ? a : b;
-                const uint64_t tile_id = (uint64_t)(i / kTile) * ntr + (uint64_t)(j / kTile);
-                nz.push_back({tile_id * 64 + (uint64_t)((i % kTile) * 8 + (j % kTile)), wv, ev, k});
+                given.push_back({(uint32_t)i, (uint32_t)j, wv, ev, k});
             }
         }
-        std::sort(nz.begin(), nz.end(), [](const Nz& x, const Nz& y) { return x.key < y.key; });
+        // by octile, then by bit of its bitmap: counting sorts by the bit, the octile's column and its row
+        {
+            auto by = [&](int buckets, const int32_t* from, std::vector<int32_t>& to, const auto& key) {
+                bucket.assign((size_t)buckets + 1, 0);
+                to.resize(given.size());
+                for (const Nz& z : given) bucket[key(z) + 1]++;
+                for (int q = 0; q < buckets; ++q) bucket[(size_t)q + 1] += bucket[(size_t)q];
+                for (size_t k = 0; k < given.size(); ++k) {
+                    const int32_t z = from ? from[k] : (int32_t)k;
+                    to[(size_t)bucket[key(given[(size_t)z])]++] = z;
+                }
+            };
+            by(64, nullptr, sorted[0], [](const Nz& z) { return (size_t)(z.i % kTile * kTile + z.j % kTile); });
+            by(ntr, sorted[0].data(), sorted[1], [](const Nz& z) { return (size_t)(z.j / kTile); });
+            by(ntr, sorted[1].data(), sorted[0], [](const Nz& z) { return (size_t)(z.i / kTile); });
+            nz.resize(given.size());
+            for (size_t k = 0; k < nz.size(); ++k) nz[k] = given[(size_t)sorted[0][k]];
+        }
 
         MgkGraphDesc& gd = B->graphs[g];
         gd.n = n;
@@ -2470,10 +2599,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         trow_ptr.resize(trow_ptr.size() + ntr + 1, 0);
         int32_t* trp = trow_ptr.data() + gd.roff;
         for (size_t k = 0; k < nz.size(); ++k) {
-            const uint64_t tile_id = nz[k].key >> 6;
-            const int bit = (int)(nz[k].key & 63);
-            const int tr = (int)(tile_id / ntr), tc = (int)(tile_id % ntr);
-            if (k == 0 || (nz[k - 1].key >> 6) != tile_id) {
+            const int tr = (int)(nz[k].i / kTile), tc = (int)(nz[k].j / kTile), bit = (int)(nz[k].i % kTile * kTile + nz[k].j % kTile);
+            if (k == 0 || (int)(nz[k - 1].i / kTile) != tr || (int)(nz[k - 1].j / kTile) != tc) {
                 MgkTile t;
                 t.tr = (uint16_t)tr;
                 t.tc = (uint16_t)tc;
@@ -2486,7 +2613,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             B->tiles.back().bitmap |= 1ull << bit;
             B->w.push_back(nz[k].w);
             B->e.push_back(nz[k].e);
-            deg[tr * kTile + bit / 8]++;
+            deg[nz[k].i]++;
         }
         for (int r = 0; r < ntr; ++r) trp[r + 1] += trp[r];
         gd.n_tiles = (int32_t)B->tiles.size() - gd.toff;
@@ -2543,10 +2670,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         list_inner.resize((size_t)gd.loff + gd.lane_len, MgkEntry{0u, 0u, 0u, 0u});
         std::vector<int32_t> filled(n, 0);
         for (size_t k = 0; k < nz.size(); ++k) {
-            const uint64_t tile_id = nz[k].key >> 6;
-            const int bit = (int)(nz[k].key & 63);
-            const uint32_t i = (uint32_t)(tile_id / ntr) * kTile + bit / 8;
-            const uint32_t j = (uint32_t)(tile_id % ntr) * kTile + bit % 8;
+            const uint32_t i = nz[k].i, j = nz[k].j;
             const int rank = filled[i]++;
             uint32_t wbits, ebits;
             memcpy(&wbits, &nz[k].w, 4);
@@ -2557,72 +2681,18 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             const MgkRunPos rp = mgk_run_pos(lanepos[v0 + i], rank, deg[i]);
             list_inner[(size_t)gd.loff + lanepos[v0 + i] + rank] =
                 MgkEntry{i | (rp.rank << 20) | (rp.cut << 30) | (rp.last << 31), j, ebits, wbits};
-            {
+            if (D > 1) {
                 attr_pos_outer.push_back({(int64_t)gd.zoff + rowptr[v0 + i] + rank, nz[k].edge});
                 attr_pos_inner.push_back({(int64_t)gd.loff + lanepos[v0 + i] + rank, nz[k].edge});
             }
         }
         tile_graph.resize(B->tiles.size(), g);
 
-        // ---- schedule of the graph as outer operand of the reduced solver
-        {
-            uint16_t split[MGK_RED_SPLIT_STRIDE] = {};
-            gd.n_red = n;
-            gd.soff = (int32_t)list_sched.size();
-            memset(gd.red_need, 255, sizeof gd.red_need);
-            if (gd.nnz <= MGK_RED_MAX_NNZ && n < 65536 && list_sched.size() < ((size_t)1 << 31) - 3 * MGK_RED_MAX_NNZ) {
-                const MgkEntry* list = list_outer.data() + gd.zoff;
-                gd.n_red = colour_vertices(n, deg, rowptr.data() + v0, list, black, red_slot);
-                for (auto& r : rows_of) r.clear();
-                int nnz_of[2] = {};
-                for (int k = 0; k < n; ++k) {   // by descending number of nonzeros
-                    const int i = deg_order[(size_t)v0 + k];
-                    rows_of[black[(size_t)i]].push_back(i);
-                    nnz_of[black[(size_t)i]] += deg[i];
-                }
-                red_pos.resize((size_t)n);
-                of_wave.resize((size_t)n);
-                for (int waves = 2; waves <= 8; waves *= 2) {
-                    const int which = MGK_RED_LIST(waves);
-                    const size_t base = list_sched.size();
-                    list_sched.resize(base + (size_t)gd.nnz);
-                    // more nonzeros than the wavefronts hold: no need to divide them (the place stays, unread)
-                    if (nnz_of[0] > waves * MGK_RED_RED(waves) || nnz_of[1] > waves * MGK_RED_BLACK(waves)) continue;
-                    uint16_t* sp = split + MGK_RED_SPLIT(waves);
-                    uint16_t* order = red_order.data() + 3 * v0 + (int64_t)which * n;
-                    int32_t at = 0, rows_in[2][8];
-                    for (int colour = 0; colour < 2; ++colour) {
-                        const std::vector<int32_t>& rows = rows_of[colour];
-                        const int most = divide_rows(rows, deg, waves, of_wave.data(), rows_in[colour]);
-                        gd.red_need[2 * which + 1 - colour] = (uint8_t)std::min(most, 255);
-                        int32_t next[8];
-                        for (int w = 0; w < waves; ++w) {
-                            sp[(3 - colour) * waves + 1 + w] = (uint16_t)(next[w] = at);
-                            at += rows_in[colour][w];
-                        }
-                        for (size_t k = 0; k < rows.size(); ++k) {
-                            const int32_t to = next[of_wave[k]]++;
-                            red_pos[(size_t)rows[k]] = to;
-                            order[to] = (uint16_t)rows[k];
-                        }
-                    }
-                    uint32_t* sched = list_sched.data() + base;
-                    int32_t done = 0;
-                    for (int w = 0; w < waves; ++w) {
-                        sp[w] = (uint16_t)done;
-                        for (int colour = 1; colour >= 0; --colour) {
-                            const uint16_t* row = order + sp[(3 - colour) * waves + 1 + w];
-                            for (int r = 0; r < rows_in[colour][w]; ++r)
-                                for (int32_t k = rowptr[v0 + row[r]], end = k + deg[row[r]]; k < end; ++k)
-                                    sched[done++] = (uint32_t)k | (uint32_t)red_pos[list[k].y] << 16;
-                            if (colour) sp[waves + 1 + w] = (uint16_t)(done - sp[w]);
-                        }
-                    }
-                    sp[waves] = (uint16_t)done;
-                }
-            }
-            red_split.insert(red_split.end(), split, split + MGK_RED_SPLIT_STRIDE);
-        }
+        // ---- place of the schedule as outer operand of the reduced solver
+        gd.n_red = n;
+        memset(gd.red_need, 255, sizeof gd.red_need);
+        gd.soff = ReducedSchedule::makes(gd) && list_sched_size < ((size_t)1 << 31) - 3 * MGK_RED_MAX_NNZ ? (int32_t)list_sched_size : -1;
+        if (gd.soff >= 0) list_sched_size += 3 * (size_t)gd.nnz;
 
         // ---- records of the owner-computes solver: vertices sorted by degree (descending),
         //      four neighbour records per vertex
@@ -2664,6 +2734,28 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             B->sell_desc.push_back(sd);
         }
     }
+    std::vector<uint16_t> red_split((size_t)n_graphs * MGK_RED_SPLIT_STRIDE), red_order((size_t)(3 * tot_v));
+    std::vector<uint32_t> list_sched(list_sched_size);
+    {
+        constexpr int kPerTask = 16;   // graphs; 40 us
+        std::atomic<bool> failed{false};
+        // waking the threads a second time takes as long as the schedules of some 30 graphs
+        const int tasks = (n_graphs + kPerTask - 1) / kPerTask, helpers = n_graphs < 64 ? 0 : tasks - 1;
+        ctx->workers.run(tasks, [&](int t) {
+            try {
+                ReducedSchedule schedule;
+                for (int32_t g = t * kPerTask; g < std::min(n_graphs, (t + 1) * kPerTask); ++g) {
+                    MgkGraphDesc& gd = B->graphs[(size_t)g];
+                    if (gd.soff >= 0)
+                        schedule.make(gd, rowptr.data() + gd.voff, list_outer.data() + gd.zoff, deg_order.data() + gd.voff, list_sched.data() + gd.soff,
+                                      red_split.data() + (int64_t)g * MGK_RED_SPLIT_STRIDE, red_order.data() + 3 * (int64_t)gd.voff);
+                }
+            } catch (...) {
+                failed = true;
+            }
+        }, helpers);
+        if (failed) return fail(ctx, MGK_ENOMEM, "out of host memory");
+    }
     if (!(B->label_lo <= B->label_hi)) B->label_lo = B->label_hi = 0.f;   // no edges
     B->n_vertices = tot_v;
     B->nnz = (int64_t)B->w.size();
@@ -2688,7 +2780,12 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     const size_t o_li = blob.add(list_inner);
     const size_t o_sp = blob.add(regs_split), o_rd = blob.add(red_split), o_ls = blob.add(list_sched), o_ro = blob.add(red_order);
     std::vector<float> attr_outer, attr_inner;
-    {
+    if (D == 1) {   // the labels of the lists
+        attr_outer.resize(list_outer.size());
+        attr_inner.resize(list_inner.size());
+        for (size_t k = 0; k < list_outer.size(); ++k) memcpy(&attr_outer[k], &list_outer[k].z, 4);
+        for (size_t k = 0; k < list_inner.size(); ++k) memcpy(&attr_inner[k], &list_inner[k].z, 4);
+    } else {
         attr_outer.assign((size_t)D * B->w.size(), 0.f);
         attr_inner.assign((size_t)D * (size_t)lanes_total, 0.f);
         for (const auto& pe : attr_pos_outer)

@@ -102,15 +102,50 @@ hipError_t launched(const char* name, void* stream, const MgkBatchDev* X = nullp
     return hipSuccess;
 }
 
-// Launches of the on-chip solvers: fits(job, g1, g2) for the graphs of every job, those of a swapped one
-// from the other batch if the kernel takes both orientations.
+// The schedule of a graph as outer operand of the reduced solver with W wavefronts, read as the kernel does: every row and
+// every nonzero once, rows whole, black vertices not joined to each other, as many nonzeros as the descriptor says at most.
+bool schedule_ok(const MgkBatchDev& X, int g, int W) {
+    const MgkGraphDesc& d = X.graphs[g];
+    const uint16_t* split = X.red_split + (int64_t)g * MGK_RED_SPLIT_STRIDE + MGK_RED_SPLIT(W);
+    const uint16_t* order = X.red_order + 3 * (int64_t)d.voff + MGK_RED_LIST(W) * d.n;
+    const uint32_t* sched = X.list_sched + d.soff + MGK_RED_LIST(W) * d.nnz;
+    const MgkEntry* list = X.list_outer + d.zoff;
+    std::vector<int> place(d.n, -1), nonzero(d.nnz, 0), row(d.n, 0);
+    for (int k = 0; k < d.n; ++k) {
+        if (order[k] >= d.n || place[order[k]] >= 0) return false;
+        place[order[k]] = k;
+    }
+    for (int w = 0; w < W; ++w) {
+        const int begin = split[w], end = split[w + 1], blacks = split[W + 1 + w];
+        if (begin > end || begin + blacks > end || end > d.nnz) return false;
+        if (blacks > d.red_need[2 * MGK_RED_LIST(W)] || end - begin - blacks > d.red_need[2 * MGK_RED_LIST(W) + 1]) return false;
+        int at[2] = {split[2 * W + 1 + w], split[3 * W + 1 + w]};   // place of the first row
+        for (int k = begin; k < end; ++k) {
+            const bool red = k >= begin + blacks;
+            const int from = sched[k] & 0xffff, col = sched[k] >> 16;
+            if (from >= d.nnz || nonzero[from]++) return false;
+            const MgkEntry& e = list[from];
+            if ((int)e.x != order[at[red]] || place[e.y] != col) return false;
+            if ((place[e.x] < d.n_red) != red || (!red && col >= d.n_red)) return false;
+            if (e.w >> 31) row[at[red]++]++;
+        }
+    }
+    if (split[W] != d.nnz) return false;
+    std::vector<int> ends(d.n, 0);
+    for (int k = 0; k < d.nnz; ++k) ends[place[list[k].x]] |= list[k].w >> 31;
+    return ends == row;
+}
+
+// Launches of the on-chip solvers: fits(batch and number of the outer graph, outer graph, inner graph) for every job, those
+// of a swapped one from the other batch if the kernel takes both orientations.
 template <class Fits>
 hipError_t launched_jobs(const char* name, void* stream, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n,
                          size_t lds_bytes, bool both, const Fits& fits) {
     if (lds_bytes > MGK_LDS_LIMIT_BYTES) return hipErrorInvalidValue;
     for (int k = 0; k < n; ++k) {
         const bool other = both && jobs[k].out1 == MGK_OUT1_SWAPPED;
-        if (!fits((other ? Y : X).graphs[jobs[k].g1], (other ? X : Y).graphs[jobs[k].g2]))
+        const MgkBatchDev &O = other ? Y : X, &I = other ? X : Y;
+        if (!fits(O, jobs[k].g1, O.graphs[jobs[k].g1], I.graphs[jobs[k].g2]))
             violations.push_back(std::string("a job of ") + name + " does not fit its launch");
     }
     return launched(name, stream, &X, &Y, n);
@@ -269,14 +304,14 @@ hipError_t hipEventSynchronize(hipEvent_t e) { counts["event waits"]++; if (!((E
     hipError_t NAME(int ept, bool, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, const MgkParams&, \
                     size_t lds, const MgkOutputs&, hipStream_t s) {                                               \
         return launched_jobs("small", s, X, Y, jobs, n, lds, false,                                               \
-                             [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { return a.n * b.n <= W * 64 * ept; }); \
+                             [=](const MgkBatchDev& O, int g, const MgkGraphDesc& a, const MgkGraphDesc& b) { return a.n * b.n <= W * 64 * ept; }); \
     }
 STUB_SMALL(mgk_launch_small_w1, 1) STUB_SMALL(mgk_launch_small_w2, 2) STUB_SMALL(mgk_launch_small_w4, 4)
 STUB_SMALL(mgk_launch_small_w8, 8) STUB_SMALL(mgk_launch_small_w16, 16) STUB_SMALL(mgk_launch_small_w4_fine, 4)
 #define STUB_REGS(W, C)                                                                                           \
     hipError_t mgk_launch_regs_w##W##_c##C(int ept, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
                                            const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {      \
-        return launched_jobs("regs", s, X, Y, jobs, n, lds, false, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+        return launched_jobs("regs", s, X, Y, jobs, n, lds, false, [=](const MgkBatchDev& O, int g, const MgkGraphDesc& a, const MgkGraphDesc& b) { \
             const int run = W == 4 ? a.regs_runs & 0xffff : (int)((uint32_t)a.regs_runs >> 16);                   \
             return a.n * b.n <= W * 64 * ept && b.lane_len <= 64 * C && b.max_deg <= MGK_REGS_MAX_DEG &&           \
                    run <= (W == 4 ? MGK_REGS_SMAX_W4 : MGK_REGS_SMAX_W8);                                         \
@@ -286,12 +321,13 @@ STUB_REGS(4, 1) STUB_REGS(4, 2) STUB_REGS(8, 1) STUB_REGS(8, 2)
 #define STUB_REDUCED(W, C)                                                                                        \
     hipError_t mgk_launch_reduced_w##W##_c##C(int ept, bool, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
                                               const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {   \
-        return launched_jobs("reduced", s, X, Y, jobs, n, lds, true, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+        return launched_jobs("reduced", s, X, Y, jobs, n, lds, true, [=](const MgkBatchDev& O, int g, const MgkGraphDesc& a, const MgkGraphDesc& b) { \
             const uint8_t* need = a.red_need + 2 * MGK_RED_LIST(W);                                               \
             return need[0] <= MGK_RED_BLACK(W) && need[1] <= MGK_RED_RED(W) && b.lane_len <= 64 * C &&            \
                    b.max_deg <= MGK_REGS_MAX_DEG && a.n_red * b.n <= W * 64 * ept &&                              \
                    W * 64 * ept + (a.n - a.n_red) * b.n <= MGK_RED_MAX_P &&                                       \
-                   (size_t)mgk_reduced_plan(a.n, a.n_red, b.n, W, ept).total * 4 <= lds;                          \
+                   (size_t)mgk_reduced_plan(a.n, a.n_red, b.n, W, ept).total * 4 <= lds &&                        \
+                   schedule_ok(O, g, W);                                                                          \
         });                                                                                                       \
     }
 STUB_REDUCED(2, 1) STUB_REDUCED(4, 1) STUB_REDUCED(4, 2) STUB_REDUCED(8, 1) STUB_REDUCED(8, 2)
@@ -301,7 +337,7 @@ STUB_REDUCED(2, 1) STUB_REDUCED(4, 1) STUB_REDUCED(4, 2) STUB_REDUCED(8, 1) STUB
                                          const MgkOutputs&, hipStream_t s) {                                      \
         reads(s, SX.packets);                                                                                     \
         reads(s, SY.packets);                                                                                     \
-        return launched_jobs("pcg_sep", s, X, Y, jobs, n, lds, false, [=](const MgkGraphDesc& a, const MgkGraphDesc& b) { \
+        return launched_jobs("pcg_sep", s, X, Y, jobs, n, lds, false, [=](const MgkBatchDev& O, int g, const MgkGraphDesc& a, const MgkGraphDesc& b) { \
             return a.n * b.n <= waves * 64 * ept &&                                                               \
                    (size_t)mgk_pcg_sep_plan(std::max(a.n, b.n), std::min(a.n, b.n), RK, rb).total * 4 <= lds;     \
         });                                                                                                       \
@@ -310,7 +346,7 @@ STUB_PCG_SEP(1) STUB_PCG_SEP(4) STUB_PCG_SEP(5) STUB_PCG_SEP(6) STUB_PCG_SEP(7)
 #define STUB_SELL(W)                                                                                              \
     hipError_t mgk_launch_sell_w##W(int, int, const MgkBatchDev& X, const MgkBatchDev& Y, const MgkJob* jobs, int n, \
                                     const MgkParams&, size_t lds, const MgkOutputs&, hipStream_t s) {             \
-        return launched_jobs("sell", s, X, Y, jobs, n, lds, false, [](const MgkGraphDesc&, const MgkGraphDesc&) { return true; }); \
+        return launched_jobs("sell", s, X, Y, jobs, n, lds, false, [](const MgkBatchDev&, int, const MgkGraphDesc&, const MgkGraphDesc&) { return true; }); \
     }
 STUB_SELL(4) STUB_SELL(8) STUB_SELL(16)
 hipError_t mgk_noalloc_job_storage(int, MgkJob** jobs, int64_t* capacity) {

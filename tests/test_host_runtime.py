@@ -441,3 +441,34 @@ def test_recorded_gram_of_a_batch_with_an_older_list(host):
     assert host.count("recorded copies") == host.count("broken recordings") == 0 and host.violations() == ""
     assert host.lib.stub_in_use() - before <= 2 * (kept - before)
     host.free(B)
+
+
+def star(n):
+    return n, np.stack([np.zeros(n - 1, int), np.arange(1, n)], 1), 0.0
+
+
+def random_graph(rng, n, edges, vertices=None):
+    """Any graph: isolated vertices, hubs, several parts; among the first `vertices` of n."""
+    a, b = np.triu_indices(vertices or n, 1)
+    pick = rng.choice(len(a), min(edges, len(a)), replace=False)
+    return n, np.stack([a[pick], b[pick]], 1), 0.0
+
+
+def test_schedules_of_the_reduced_solver(host):
+    """As the kernel reads them (the stand-in looks them over at every launch), for graphs of all kinds: up to 160 nonzeros,
+    up to 160 vertices with edges, rows longer than four, no edges; as outer graph against a small inner one."""
+    rng = np.random.default_rng(8)
+    parts = [path(2), path(64), path(65), path(81), star(17), star(21), ring(20, 3), ring(9, 4), (1, [], 0.0), (7, [], 0.0),
+             (160, np.arange(160).reshape(-1, 2), 0.0)]
+    parts += [random_graph(rng, int(n), int(e), int(v)) for n, e, v in
+              zip(rng.integers(12, 150, 60), rng.integers(1, 81, 60), rng.integers(3, 13, 60))]
+    parts += [random_graph(rng, int(n), int(e)) for n, e in zip(rng.integers(5, 90, 150), rng.integers(1, 81, 150))]
+    host.set("reduced_system", 2)
+    B, inner = host.load(graphs(*parts)), host.load(graphs(path(3), ring(6, 1), path(40)))
+    i, j, log = np.arange(len(parts)).repeat(3), np.tile([0, 1, 2], len(parts)), ""
+    for many in (8, 1):   # two wavefronts where there are thousands of pairs
+        assert host.pairs(B, inner, np.tile(i, many), np.tile(j, many)) == 0, host.error()
+        log += host.launch_log()
+    assert host.violations() == "" and all("mgk_pcg_reduced<%d" % w in log for w in (2, 4, 8))
+    host.free(B)
+    host.free(inner)
