@@ -864,19 +864,20 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
             return pl;
         }
     }
-    if (product_cache && forced_waves == 0) {
+    // the reduced system first; pairs that fit the full one only are solved with that
+    for (int system = reduced ? 1 : 0; product_cache && forced_waves == 0 && system >= 0; --system) {
         int64_t best = -1;
-        for (int w = reduced ? reduced : 4; w <= 8; w *= 2)
+        for (int w = system ? reduced : 4; w <= 8; w *= 2)
             for (int sw = 0; sw < (may_swap ? 2 : 1); ++sw) {
                 const MgkGraphDesc &o = sw ? b : a, &i = sw ? a : b;
-                const int64_t c = reduced ? reduced_cost(o, i, w, std::max(1, i.lane_len / 64)) : regs_cost(o, i, w);
+                const int64_t c = system ? reduced_cost(o, i, w, std::max(1, i.lane_len / 64)) : regs_cost(o, i, w);
                 if (c >= 0 && (best < 0 || c < best)) { best = c; pl.waves = w; pl.swap = sw != 0; }
             }
         if (best >= 0) {
             const MgkGraphDesc& o = pl.swap ? b : a;
             const MgkGraphDesc& i = pl.swap ? a : b;
             pl.atomic_rows = false;
-            if (reduced) {
+            if (system) {
                 set_reduced(pl, o, i, pl.waves, std::max(1, i.lane_len / 64), best);
                 return pl;
             }

@@ -447,6 +447,11 @@ def star(n):
     return n, np.stack([np.zeros(n - 1, int), np.arange(1, n)], 1), 0.0
 
 
+def grid(a, b):
+    i = np.arange(a * b).reshape(a, b)
+    return a * b, np.concatenate([np.stack([i[:, :-1].ravel(), i[:, 1:].ravel()], 1), np.stack([i[:-1].ravel(), i[1:].ravel()], 1)]), 0.0
+
+
 def random_graph(rng, n, edges, vertices=None):
     """Any graph: isolated vertices, hubs, several parts; among the first `vertices` of n."""
     a, b = np.triu_indices(vertices or n, 1)
@@ -472,3 +477,17 @@ def test_schedules_of_the_reduced_solver(host):
     assert host.violations() == "" and all("mgk_pcg_reduced<%d" % w in log for w in (2, 4, 8))
     host.free(B)
     host.free(inner)
+
+
+@pytest.mark.parametrize("parts", [[grid(a, b) for a in range(4, 7) for b in range(a, 7)], [grid(2, n) for n in range(8, 27)]], ids=["grids", "ladders"])
+def test_pairs_that_fit_the_full_system_only_stay_register_resident(host, parts):
+    """A graph of whole rows may fit the wavefronts of the solver of the full system and not those of the reduced one."""
+    streaming = []
+    for mode in (0, 1):
+        host.set("reduced_system", mode)
+        B = host.load(graphs(*parts))
+        assert host.gram(B) == 0, host.error()
+        streaming.append(sum(int(k) for k in re.findall(r"mgk_pcg_small\S* \S* *pairs=(\d+)", host.launch_log())))
+        assert ("mgk_pcg_reduced" in host.launch_log()) == (mode == 1) and "mgk_pcg_regs" in host.launch_log()
+        host.free(B)
+    assert streaming[0] == streaming[1] and host.violations() == ""
