@@ -785,6 +785,7 @@ int64_t reduced_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, in
         return -1;
     const int ept = reduced_ept(o, i, waves);
     if (ept > MGK_REGS_MAX_EPT || waves * 64 * ept + (int64_t)(o.n - o.n_red) * i.n > MGK_RED_MAX_P) return -1;
+    if (mgk_reduced_plan(o.n, o.n_red, i.n, waves, ept).total * 4 > MGK_LDS_LIMIT_BYTES) return -1;   // many isolated vertices
     return o.nnz * (2 * chunks) + o.n * (1 + 4 * chunks) + waves * (9 * ept + 90);
 }
 void set_reduced(PairPlan& pl, const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, int chunks, int64_t cost) {

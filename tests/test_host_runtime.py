@@ -491,3 +491,18 @@ def test_pairs_that_fit_the_full_system_only_stay_register_resident(host, parts)
         assert ("mgk_pcg_reduced" in host.launch_log()) == (mode == 1) and "mgk_pcg_regs" in host.launch_log()
         host.free(B)
     assert streaming[0] == streaming[1] and host.violations() == ""
+
+
+@pytest.mark.parametrize("n,inner", [(9000, 1), (10300, 1), (12000, 1), (16000, 1), (1, 12000), (2, 8000)])
+def test_pairs_of_many_isolated_vertices_stay_within_lds(host, n, inner):
+    """The reduced solver holds the vertices of both graphs and all eliminated elements in LDS: beyond it the pair goes where it went
+    without that solver."""
+    B = host.load(graphs((n, [(0, 1)] if n > 1 else [], 0.0), (inner, [(0, 1)] if inner > 1 else [], 0.0)))
+    kernels = []
+    for mode in (0, 1):
+        host.set("reduced_system", mode)
+        assert host.pairs(B, B, [0, 1], [1, 0]) == 0, host.error()
+        kernels.append(host.launch_log().split("<")[0])
+    assert kernels[0] == kernels[1] or kernels[1] == "mgk_pcg_reduced"
+    assert host.violations() == ""
+    host.free(B)
