@@ -753,6 +753,7 @@ struct PairPlan {
     int chunks = 0;          // > 0: register-resident solver
     bool reduced = false;    // of the reduced system
     int sell_regs = 0;       // > 0: owner-computes solver
+    int eliminated = 0;      // elements of the reduced system's black vertices
 };
 
 // Register-resident solver for (outer o, inner i) with `waves` wavefronts: every
@@ -796,6 +797,7 @@ void set_reduced(PairPlan& pl, const MgkGraphDesc& o, const MgkGraphDesc& i, int
     pl.ept = reduced_ept(o, i, waves);
     pl.cost = cost * 16;
     pl.lds_words = mgk_reduced_plan(o.n, o.n_red, i.n, waves, pl.ept).total;
+    pl.eliminated = (o.n - o.n_red) * i.n;
 }
 
 // Owner-computes solver for (outer o, inner i): the cheapest launch shape that holds the
@@ -934,6 +936,7 @@ struct Shape {
     SepWork sep;
     int64_t count = 0;
     int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
+    int32_t eliminated = 0;    // most of a job
     int64_t min_cost = INT64_MAX, max_cost = 0;
     bool same(const Shape& s) const {
         return waves == s.waves && ept == s.ept && chunks == s.chunks && sell_regs == s.sell_regs &&
@@ -983,6 +986,7 @@ struct JobPlan {
         t.count++;
         if (streaming) t.sep.add(sep_work(a, b));
         t.base_words = std::max(t.base_words, pl.lds_words - t.vector_words());
+        t.eliminated = std::max(t.eliminated, pl.eliminated);
         t.min_cost = std::min(t.min_cost, pl.cost);
         t.max_cost = std::max(t.max_cost, pl.cost);
         return table[slot];
@@ -1027,10 +1031,15 @@ std::vector<int> merge_small_shapes(std::vector<Shape>& shapes) {
         }
         if (from < 0) break;
         Shape &a = shapes[from], &b = shapes[to];
-        if ((a.base_words + b.vector_words()) * 4 > MGK_LDS_LIMIT_BYTES) { frozen[from] = 1; continue; }
+        if ((a.base_words + b.vector_words()) * 4 > MGK_LDS_LIMIT_BYTES ||
+            (a.reduced && b.waves * 64 * b.ept + a.eliminated > MGK_RED_MAX_P)) {   // of which the kernel keeps 16-bit offsets
+            frozen[from] = 1;
+            continue;
+        }
         b.count += a.count;
         b.sep.add(a.sep);
         b.base_words = std::max(b.base_words, a.base_words);
+        b.eliminated = std::max(b.eliminated, a.eliminated);
         b.min_cost = std::min(b.min_cost, a.min_cost);
         b.max_cost = std::max(b.max_cost, a.max_cost);
         a.count = 0;

@@ -506,3 +506,12 @@ def test_pairs_of_many_isolated_vertices_stay_within_lds(host, n, inner):
     assert kernels[0] == kernels[1] or kernels[1] == "mgk_pcg_reduced"
     assert host.violations() == ""
     host.free(B)
+
+
+def test_merged_launches_keep_the_offsets_of_the_reduced_solver(host):
+    """A pair with many eliminated elements fits its own launch shape and not the larger one that few pairs are moved to."""
+    edge = lambda n: (n, [(0, 1)], 0.0)
+    B = host.load(graphs(star(13), edge(1200), path(2), edge(2000)))
+    assert host.pairs(B, B, [0, 2], [1, 3]) == 0, host.error()
+    assert "mgk_pcg_reduced<4, 8, 1> pairs=1" in host.launch_log() and host.violations() == ""
+    host.free(B)
