@@ -262,6 +262,7 @@ struct mgk_batch {
         int cache = 0;       // product cache
         int sorted = 0;      // schedule
         int attr_dim = -1;   // label attributes of the edge kernel (LDS plan)
+        bool joined = false; // pairs of the reduced solver are with the streaming one, see join_few
     } gram_jobs[2];          // small pairs by the full system, by the reduced one
     std::vector<void*> old_jobs;   // lists replaced while a graph was recorded, when none may be freed
 };
@@ -909,23 +910,27 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
 
 // Launches of a call follow each other, and one with a few pairs takes as long as a pair does.  Where one of a few
 // pairs needs the streaming solver with one wavefront (n n' <= 256), those of the reduced one go there too if they are
-// as small: 36 + 9 pairs of 8 or 9 vertices 40.8 us in two launches, 25.0 in one.  graphs(k): the two graphs of pair k.
+// as small: 36 + 9 pairs of 8 or 9 vertices 40.8 us in two launches, 25.0 in one.  Not where the caller has asked for
+// the reduced system, whose iterations are then counted.  graphs(k): the two graphs of pair k.
 constexpr size_t kFewPairs = 256;
 template <class Graphs>
-void join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_limit, int attr_dim) {
-    if (plans.size() > kFewPairs) return;
+bool join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_limit, int attr_dim) {   // whether any pair is moved
+    if (plans.size() > kFewPairs) return false;
     bool one_wave[2] = {};   // [atomic rows]
     for (const PairPlan& pl : plans)
         if (pl.waves == 1) one_wave[pl.atomic_rows] = true;
-    if (!one_wave[0] && !one_wave[1]) return;
+    if (!one_wave[0] && !one_wave[1]) return false;
+    bool any = false;
     std::vector<PairPlan> moved(plans);
     for (size_t k = 0; k < plans.size(); ++k) {
         if (!plans[k].reduced) continue;
         const auto g = graphs(k);
         moved[k] = plan_pair(*g.first, *g.second, nullptr, nullptr, true, 0, onchip_limit, 0, attr_dim, 0);
-        if (moved[k].waves != 1 || !one_wave[moved[k].atomic_rows]) return;
+        if (moved[k].waves != 1 || !one_wave[moved[k].atomic_rows]) return false;
+        any = true;
     }
     plans.swap(moved);
+    return any;
 }
 
 // A launch shape: jobs of one shape go into one kernel launch.
@@ -2944,7 +2949,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     if (G * G >= (int64_t)1 << 31) return fail(ctx, MGK_ELIMIT, "Gram matrix too large for 32-bit output indices");
     auto built = [&](const mgk_batch::GramJobs& g) {
         return g.list.dev != nullptr && g.waves == ctx->waves && g.max_iter == ctx->max_iter && g.limit == ctx->onchip_limit &&
-               g.cache == ctx->product_cache && g.sorted == ctx->cost_sorted && g.attr_dim == attr_dim_of(ctx);
+               g.cache == ctx->product_cache && g.sorted == ctx->cost_sorted && g.attr_dim == attr_dim_of(ctx) && !(g.joined && ctx->reduced_system == 2);
     };
     bool reduced = solve_reduced(ctx, iters_dev);
     const int waves = reduced_waves(G * (G + 1) / 2);
@@ -2998,10 +3003,11 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
                 }
             });
         }
-        if (reduced) {
+        jobs.joined = false;
+        if (reduced && ctx->reduced_system == 1) {
             std::vector<int64_t> row((size_t)G);   // first pair of each row of the triangle
             for (int64_t i = 0; i < G; ++i) row[(size_t)i] = i * G - i * (i - 1) / 2;
-            join_few(plans, [&](size_t k) {
+            jobs.joined = join_few(plans, [&](size_t k) {
                 const int64_t i = std::upper_bound(row.begin(), row.end(), (int64_t)k) - row.begin() - 1;
                 return std::make_pair(&batch->graphs[(size_t)i], &batch->graphs[(size_t)(i + (int64_t)k - row[(size_t)i])]);
             }, ctx->onchip_limit, attr_dim_of(ctx));
@@ -3080,7 +3086,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
             }
         });
     }
-    if (solve_reduced(ctx, iters_dev))
+    if (solve_reduced(ctx, iters_dev) && ctx->reduced_system == 1)
         join_few(plans, [&](size_t k) { return std::make_pair(&X->graphs[(size_t)i_host[k]], &Y->graphs[(size_t)j_host[k]]); },
                       ctx->onchip_limit, attr_dim_of(ctx));
     JobPlan plan;

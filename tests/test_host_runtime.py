@@ -515,3 +515,17 @@ def test_merged_launches_keep_the_offsets_of_the_reduced_solver(host):
     assert host.pairs(B, B, [0, 2], [1, 3]) == 0, host.error()
     assert "mgk_pcg_reduced<4, 8, 1> pairs=1" in host.launch_log() and host.violations() == ""
     host.free(B)
+
+
+@pytest.mark.parametrize("entry", ["gram", "pairs"])
+@pytest.mark.parametrize("mode", [1, 2])
+def test_few_pairs_leave_the_reduced_system_only_where_nobody_asked_for_it(host, entry, mode):
+    """A few tiny pairs of which one needs the streaming solver go there together, unless the mode says always reduced."""
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(path(6), path(7), ring(9, 4), path(8)))
+    i, j = np.triu_indices(4)
+    assert host.gram(B) == 0   # its list is not that of mode 2
+    host.set("reduced_system", mode)
+    assert (host.gram(B) if entry == "gram" else host.pairs(B, B, i, j)) == 0, host.error()
+    assert "mgk_pcg_small" in host.launch_log() and ("mgk_pcg_reduced" in host.launch_log()) == (mode == 2)
+    host.free(B)
