@@ -262,6 +262,7 @@ struct mgk_batch {
         int cache = 0;       // product cache
         int sorted = 0;      // schedule
         int attr_dim = -1;   // label attributes of the edge kernel (LDS plan)
+        bool any_big = false, separable = false;   // streaming pairs too large for the separable product on chip; whether that might be taken
         bool joined = false; // pairs of the reduced solver are with the streaming one, see join_few
     } gram_jobs[2];          // small pairs by the full system, by the reduced one
     std::vector<void*> old_jobs;   // lists replaced while a graph was recorded, when none may be freed
@@ -623,6 +624,12 @@ bool solve_reduced(const mgk_ctx* ctx, const int32_t* iters_dev) {
     return ctx->reduced_system == 2 || (ctx->reduced_system == 1 && !iters_dev && ctx->max_iter <= 0);
 }
 
+// Whether launches of the streaming on-chip solver may take the separable product on chip (mgk_pcg_sep.hip).
+bool separable_on_chip(const mgk_ctx* ctx) {
+    return mgk_launch_pcg_sep_rk5 && (ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST) && ctx->tile_path == MGK_TILE_AUTO &&
+           ctx->product_cache != 0 && ctx->waves == 0;
+}
+
 // Fewest wavefronts of its pairs.  Two do less work for a pair whose inner graph fits one chunk, but make a launch of their
 // own: 5050 molecule-like pairs (2679 of them with two) 95 us, all with four 111; with fewer than a launch should have
 // (kMinJobsPerLaunch) a launch more costs more.
@@ -937,7 +944,7 @@ bool join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_lim
 struct Shape {
     int16_t waves = 0, ept = 0, chunks = 0, sell_regs = 0;
     bool atomic_rows = false, swapped = false, reduced = false;
-    bool big = false;          // too large for the separable product on chip
+    bool big = false;          // too large for the separable product on chip, where that may be taken
     SepWork sep;
     int64_t count = 0;
     int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
@@ -966,7 +973,9 @@ struct HostJob {
 struct JobPlan {
     std::vector<HostJob> jobs;
     std::vector<Shape> shapes;
-    JobPlan() { std::fill(table, table + kTable, (int16_t)-1); }
+    const bool separable;      // separable_on_chip()
+    bool any_big = false;      // streaming pairs beyond it
+    explicit JobPlan(bool sep) : separable(sep) { std::fill(table, table + kTable, (int16_t)-1); }
     // index of the shape of a planned pair of graphs a and b; counts the pair in
     int shape_of(const PairPlan& pl, bool swapped, const MgkGraphDesc& a, const MgkGraphDesc& b) {
         const bool streaming = pl.chunks == 0 && pl.sell_regs == 0;
@@ -978,7 +987,9 @@ struct JobPlan {
         s.atomic_rows = pl.atomic_rows;
         s.swapped = swapped;
         s.reduced = pl.reduced;
-        s.big = streaming && (int64_t)a.n * b.n > MGK_PCG_SEP_MAX_N;
+        const bool big = streaming && (int64_t)a.n * b.n > MGK_PCG_SEP_MAX_N;
+        any_big = any_big || big;
+        s.big = big && separable;
         const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
                              (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22 | (uint32_t)s.big << 23;
         uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
@@ -1883,9 +1894,7 @@ struct PacketUse {
 // the streaming solver or allows no allocation.
 mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl, bool may_allocate, hipStream_t stream,
                               std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2], PacketUse& packets) {
-    const bool kernel_ok = ctx->edge_kernel == MGK_EK_SE || ctx->edge_kernel == MGK_EK_CONST;
-    if (!mgk_launch_pcg_sep_rk5 || !may_allocate || !kernel_ok || ctx->tile_path != MGK_TILE_AUTO || ctx->product_cache == 0 || ctx->waves != 0)
-        return MGK_OK;
+    if (!may_allocate || !separable_on_chip(ctx)) return MGK_OK;
     // Features of all graphs of the batches, formed before the kernels: 20 us with the basis and the launch, and 6 clocks of
     // a unit per nonzero and feature (23 us for 160 graphs of 1080 nonzeros).  At the lowest rank first: the basis takes time.
     auto total_gain = [&](int rank) {
@@ -2949,7 +2958,9 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
     if (G * G >= (int64_t)1 << 31) return fail(ctx, MGK_ELIMIT, "Gram matrix too large for 32-bit output indices");
     auto built = [&](const mgk_batch::GramJobs& g) {
         return g.list.dev != nullptr && g.waves == ctx->waves && g.max_iter == ctx->max_iter && g.limit == ctx->onchip_limit &&
-               g.cache == ctx->product_cache && g.sorted == ctx->cost_sorted && g.attr_dim == attr_dim_of(ctx) && !(g.joined && ctx->reduced_system == 2);
+               g.cache == ctx->product_cache && g.sorted == ctx->cost_sorted && g.attr_dim == attr_dim_of(ctx) && !(g.joined && ctx->reduced_system == 2) &&
+               // other launches, but the same pairs: good enough while a graph is recorded
+               (!g.any_big || g.separable == separable_on_chip(ctx) || capturing(stream));
     };
     bool reduced = solve_reduced(ctx, iters_dev);
     const int waves = reduced_waves(G * (G + 1) / 2);
@@ -2983,7 +2994,7 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         if (!beside)   // the list is copied and waited for
             if (mgk_status st = refuse_capture(ctx, stream)) return st;
         // a4: job list, one job per unordered pair, kept with the batch
-        JobPlan plan;
+        JobPlan plan(separable_on_chip(ctx));
         plan.jobs.reserve((size_t)(G * (G + 1) / 2));
         for (auto& v : jobs.list.large) v.clear();
         // the plans of the G (G + 1) / 2 pairs are independent: rows of the triangle in turn on
@@ -3042,6 +3053,8 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         jobs.cache = ctx->product_cache;
         jobs.sorted = ctx->cost_sorted;
         jobs.attr_dim = attr_dim_of(ctx);
+        jobs.any_big = plan.any_big;
+        jobs.separable = plan.separable;
         if (st != MGK_OK) return st;
     }
     relaxed.reset();
@@ -3089,7 +3102,7 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
     if (solve_reduced(ctx, iters_dev) && ctx->reduced_system == 1)
         join_few(plans, [&](size_t k) { return std::make_pair(&X->graphs[(size_t)i_host[k]], &Y->graphs[(size_t)j_host[k]]); },
                       ctx->onchip_limit, attr_dim_of(ctx));
-    JobPlan plan;
+    JobPlan plan(separable_on_chip(ctx));
     plan.jobs.reserve((size_t)n_pairs);
     std::vector<MgkLargePair> large[2];
     for (int64_t k = 0; k < n_pairs; ++k) {

@@ -529,3 +529,26 @@ def test_few_pairs_leave_the_reduced_system_only_where_nobody_asked_for_it(host,
     assert (host.gram(B) if entry == "gram" else host.pairs(B, B, i, j)) == 0, host.error()
     assert "mgk_pcg_small" in host.launch_log() and ("mgk_pcg_reduced" in host.launch_log()) == (mode == 2)
     host.free(B)
+
+
+def test_only_kernels_with_a_separable_form_have_a_launch_for_pairs_beyond_it(host):
+    """Streaming pairs of up to and of more than 14336 elements go in one launch where nothing takes the separable product, also
+    if the list of the batch was made when it might; a recorded Gram takes the list that is there."""
+    poly = (C.c_float * 6)(1.0, 0.0, -10.0, 20.0, -15.0, 4.0)
+    B = host.load(graphs(*[ring(n, 2, np.linspace(0, 1, n * 2)) for n in (123, 122, 121, 118, 117, 116)]))
+    i, j = np.triu_indices(6)
+    launches = {}
+    for kernel in ("poly", "se", "poly", "se"):
+        if kernel == "se":
+            host.set("edge_kernel_se", 1.0)
+        else:
+            assert host.lib.mgk_set_edge_kernel_poly(host.ctx, 6, poly, C.c_float(1.2)) == 0
+        assert host.gram(B, 3) == 0, host.error()
+        of_gram = host.launch_log()
+        assert host.pairs(B, B, i, j) == 0, host.error()
+        assert launches.setdefault(kernel, host.launch_log()) == host.launch_log() == of_gram
+    assert launches["poly"].count("pairs=") == 1 and launches["se"].count("pairs=") == 2
+    with host.recording(3):
+        assert host.lib.mgk_set_edge_kernel_poly(host.ctx, 6, poly, C.c_float(1.2)) == 0
+        assert host.gram(B, 3) == 0 and host.launch_log().count("pairs=") == 2
+    host.free(B)
