@@ -1891,10 +1891,11 @@ struct PacketUse {
 
 // The bins of a call that take the separable product on chip (use[k].waves > 0), and its packets in sl[].
 // Not while a graph is recorded (the packets belong to the context), nor where the caller asked for
-// the streaming solver or allows no allocation.
+// the streaming solver.  A call that allows no allocation has its packets in the fixed array beside its jobs, which
+// holds as much as a call may use: it takes the same kernels as one that does.
 mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl, bool may_allocate, hipStream_t stream,
                               std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2], PacketUse& packets) {
-    if (!may_allocate || !separable_on_chip(ctx)) return MGK_OK;
+    if (!separable_on_chip(ctx) || (!may_allocate && !mgk_noalloc_packet_storage)) return MGK_OK;
     // Features of all graphs of the batches, formed before the kernels: 20 us with the basis and the launch, and 6 clocks of
     // a unit per nonzero and feature (23 us for 160 graphs of 1080 nonzeros).  At the lowest rank first: the basis takes time.
     auto total_gain = [&](int rank) {
@@ -1929,12 +1930,11 @@ mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch*
         use[k] = onchip_sep_shape(b, L.rk);
         if (use[k].waves > 0) gain += g;
     }
-    constexpr int64_t kMaxPacketBytes = (int64_t)256 << 20;
     const int gi = L.per_packet == 8 ? 1 : 0, sides = X == Y ? 1 : 2;
     const mgk_batch* bt[2] = {X, Y};
     int64_t bytes = 0;
     for (int k = 0; k < sides; ++k) bytes += ((int64_t)L.passes * bt[k]->packet_off[gi].back() + 8) * 256;
-    if (gain <= cost(L.rk * L.passes) || bytes > kMaxPacketBytes) {
+    if (gain <= cost(L.rk * L.passes) || bytes > MGK_ONCHIP_PACKET_BYTES) {
         std::fill(use.begin(), use.end(), OnchipSep{});
         return MGK_OK;
     }
@@ -1943,25 +1943,37 @@ mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch*
         ~InUse() { flag = false; }
     } in_use{ctx->features_in_use};
     ctx->features_in_use = true;
+    float* fixed = nullptr;
+    if (!may_allocate) {
+        hipError_t e = mgk_noalloc_packet_storage(ctx->device, &fixed);
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "fixed packet storage: %s", hipGetErrorString(e));
+    }
     // An earlier call may still read the packets, also one on a stream of the same handle: destroyed since, or the
     // per-thread stream of another thread.  The stream waits, not the host.
-    if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
+    if (fixed) {}   // the call has waited for the last one that used the fixed arrays
+    else if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
     else MGK_HIP(ctx, hipStreamWaitEvent(stream, ctx->onchip_packets_end, 0));
     for (int k = 0; k < sides; ++k) {
         const mgk_batch* b = bt[k];
         sl[k] = b->sep[gi];
         sl[k].total = b->packet_off[gi].back();
         const size_t need = ((size_t)L.passes * sl[k].total + 8) * 256;   // a stage loads eight steps at a time
-        DevBuf& buf = ctx->onchip_packets[k];
-        if (buf.cap < need && ensure(ctx, buf, need) != MGK_OK) {   // short memory: the streaming solver
-            std::fill(use.begin(), use.end(), OnchipSep{});
-            return MGK_OK;
+        float* to = fixed;
+        if (fixed) {
+            fixed += need / 4;
+        } else {
+            DevBuf& buf = ctx->onchip_packets[k];
+            if (buf.cap < need && ensure(ctx, buf, need) != MGK_OK) {   // short memory: the streaming solver
+                std::fill(use.begin(), use.end(), OnchipSep{});
+                return MGK_OK;
+            }
+            to = (float*)buf.p;
+            packets.open = true;
         }
-        sl[k].packets = (const float*)buf.p;
+        sl[k].packets = to;
         int32_t max_n = 1;
         for (const MgkGraphDesc& g : b->graphs) max_n = std::max(max_n, g.n);
-        packets.open = true;
-        hipError_t e = mgk_launch_sep_pack(b->dev, S, L, sl[k], sl[k].whole, b->n_graphs, max_n, (float*)buf.p, stream);
+        hipError_t e = mgk_launch_sep_pack(b->dev, S, L, sl[k], sl[k].whole, b->n_graphs, max_n, to, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
     }
     if (sides == 1) sl[1] = sl[0];

@@ -479,6 +479,7 @@ struct MgkSepAt {
 #define MGK_PCG_SEP_SLAB(rk) ((rk) == 1 ? 17 : 16 * (rk) + 4)   // words of one column of T for 16 rows
 static inline MGK_HD bool mgk_pcg_sep_numbers(int32_t rk) { return rk >= 4 && rk <= 6; }   // see MgkSepLayout
 #define MGK_PCG_SEP_MAX_N (16 * 64 * 14)
+#define MGK_ONCHIP_PACKET_BYTES ((int64_t)256 << 20)   // of packets of both batches of a call; beyond, the streaming solver
 struct MgkPcgSepPlan {
     int32_t y, t, vtx1, vtx2, gptr, red, total;  // words; p at 0
 };

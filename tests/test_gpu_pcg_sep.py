@@ -156,3 +156,44 @@ def test_gram_with_iteration_counts_and_calls_on_two_streams(torch, solver):
     for b in range(2):
         for k in range(4):
             np.testing.assert_array_equal(out[b][k].cpu().numpy(), want[b])
+
+
+@pytest.mark.parametrize("length_scale,sides", [(1.0, 1), (0.44, 2), (None, 2)])
+def test_without_allocation(torch, solver, length_scale, sides):
+    """mgk_pairs_noalloc has its packets in a fixed array: the same kernels and bits as mgk_pairs, call after call."""
+    rng = np.random.default_rng(31)
+    ba = [W.concat_batches([W.barabasi_albert_batch(rng, 1, int(n), 6, 4, PARAMS) for n in rng.integers(60, 97, 24)], PARAMS, "ba") for _ in range(2)]
+    solver.configure(dataclasses.replace(PARAMS, length_scale=length_scale or 1.0))
+    if length_scale is None:
+        solver.set_edge_kernel_const(0.7)
+    solver.set_solver(1e-6, 0)
+    X, Y = solver.load_batch(ba[0]), solver.load_batch(ba[1])
+    if sides == 1:
+        Y = X
+    for n in (3000, 700):
+        pi, pj = rng.integers(0, 24, n).astype(np.int32), rng.integers(0, 24, n).astype(np.int32)
+        got = []
+        for entry in (solver.pairs_noalloc, solver.pairs, solver.pairs_noalloc):
+            K = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+            it, fl = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+            entry(X, Y, pi, pj, K, it, fl)
+            torch.cuda.synchronize()
+            assert shapes(solver.launch_log())
+            got.append([t.cpu().numpy() for t in (K, it, fl)])
+        for k in (0, 2):
+            for a, b in zip(got[1], got[k]):
+                np.testing.assert_array_equal(a, b)
+        assert np.isfinite(got[0][0]).all() and (got[0][2] == 0).all()
+
+
+@pytest.mark.parametrize("lo,hi,weight,separable", [(0.0, 1e30, 1.0, False), (1e6, 1e6 + 1.0, 1.0, True), (-3e-30, 3e-30, 1.0, True), (5.0, 5.0, 1.0, True),
+                                                    (0.0, 1.0, 1e15, True), (0.0, 1.0, 1e-15, True)])
+def test_extreme_labels_and_weights(torch, solver, lo, hi, weight, separable):
+    """Label ranges without a separable form, far from zero, tiny or empty, and weights near the ends of what fp32 holds of
+    their products: the values of the streaming solver."""
+    wb = er(6, (80, 88, 96), 0.3)
+    wb.edge_label = np.float32(lo) + (wb.edge_label * np.float32(hi - lo)).astype(np.float32)
+    wb.weight = (wb.weight * np.float32(weight)).astype(np.float32)
+    wb.params = dataclasses.replace(PARAMS, length_scale=1.0)
+    *_, log = compare(torch, solver, wb, wb, repeat=4)
+    assert bool(shapes(log)) == separable

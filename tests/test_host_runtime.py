@@ -552,3 +552,19 @@ def test_only_kernels_with_a_separable_form_have_a_launch_for_pairs_beyond_it(ho
         assert host.lib.mgk_set_edge_kernel_poly(host.ctx, 6, poly, C.c_float(1.2)) == 0
         assert host.gram(B, 3) == 0 and host.launch_log().count("pairs=") == 2
     host.free(B)
+
+
+def test_pairs_without_allocation_take_the_same_kernels(host):
+    """Also those whose packets another call would allocate; streams in turn wait as before, and nothing is allocated."""
+    X, Y = streaming(host), streaming(host, (0.0, 0.9), n=96)
+    i = np.arange(24).repeat(12)
+    assert host.pairs(X, Y, i, i) == 0
+    same = host.launch_log()
+    assert "mgk_pcg_sep" in same
+    before = host.count("malloc"), host.count("free"), host.lib.stub_in_use()
+    for stream in (5, 6, 5):
+        host.hold(stream)
+        assert host.pairs(X, Y, i, i, stream=stream, entry="mgk_pairs_noalloc") == 0 and host.launch_log() == same, host.error()
+    assert (host.count("malloc"), host.count("free"), host.lib.stub_in_use()) == before and host.violations() == ""
+    host.free(X)
+    host.free(Y)
