@@ -161,8 +161,9 @@ def test_full_system_where_iterates_are_seen(torch, solver):
     assert "mgk_pcg_reduced" in solver.launch_log() and (it4 == 3).all() and (fl4 == 1).all()
 
 
-@pytest.mark.parametrize("first,then", [(False, True), (True, False)])
-def test_recorded_gram_takes_the_list_that_is_there(torch, solver, first, then):
+@pytest.mark.parametrize("first,then", [(False, True), (True, False), (False, False), (True, True)])
+def test_recorded_gram_gives_what_the_eager_one_does(torch, solver, first, then):
+    """Also if the list of the system it asks for has to be made meanwhile; without counts the list that is there will do."""
     wb = W.config1(12)
     solver.configure(wb.params)
     B = solver.load_batch(wb)
@@ -179,4 +180,67 @@ def test_recorded_gram_takes_the_list_that_is_there(torch, solver, first, then):
         it.zero_()
         g.replay()
         torch.cuda.synchronize()
-        assert (K.cpu().numpy() == ref).all() and (not then or (it > 0).all())
+        if first == then or not then:
+            assert (K.cpu().numpy() == ref).all()
+        replayed = K.cpu().numpy(), it.cpu().numpy()
+        if then:   # of Alg. 1 on the full system, as the eager call counts them
+            solver.gram(B, K, it)
+            torch.cuda.synchronize()
+            assert (replayed[0] == K.cpu().numpy()).all() and (replayed[1] == it.cpu().numpy()).all()
+
+
+def test_recorded_gram_follows_the_mode(torch, solver):
+    wb = W.config1(12)
+    solver.configure(wb.params)
+    B = solver.load_batch(wb)
+    K = torch.zeros((12, 12), dtype=torch.float32, device="cuda")
+    it = torch.zeros((12, 12), dtype=torch.int32, device="cuda")
+    solver.gram(B, K)
+    for mode, kernel in ((0, "mgk_pcg_regs"), (2, "mgk_pcg_reduced")):
+        solver.set_reduced_system(mode)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            solver.gram(B, K, it)
+        assert kernel in solver.launch_log() and solver.launch_log().count("mgk_pcg") == solver.launch_log().count(kernel)
+        for _ in range(3):
+            K.zero_()
+            it.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            got = K.cpu().numpy(), it.cpu().numpy()
+            solver.gram(B, K, it)
+            torch.cuda.synchronize()
+            assert (got[0] == K.cpu().numpy()).all() and (got[1] == it.cpu().numpy()).all()
+
+
+def test_pairs_that_fit_one_of_the_systems_only(torch, solver):
+    """Grids and ladders: some fit the wavefronts of the solver of the full system and not those of the reduced one, in
+    either orientation and beside others; two batches."""
+    rng = np.random.default_rng(23)
+    grid = lambda a, b: (a * b, [(i * b + j, i * b + j + 1) for i in range(a) for j in range(b - 1)] +
+                         [(i * b + j, (i + 1) * b + j) for i in range(a - 1) for j in range(b)])
+    X = W.concat_batches([graph(*grid(a, b), rng) for a in range(4, 7) for b in range(a, 7)], PRM, "grids")
+    Y = W.concat_batches([graph(*grid(2, n), rng) for n in range(8, 27, 2)], PRM, "ladders")
+    both = W.concat_batches([X, Y], PRM, "both")
+    solver.configure(PRM)
+    BX, BY = solver.load_batch(X), solver.load_batch(Y)
+    for A, B, wa, wb, oa, ob in ((BX, BX, X, X, 0, 0), (BY, BY, Y, Y, X.n_graphs, X.n_graphs), (BX, BY, X, Y, 0, X.n_graphs), (BY, BX, Y, X, X.n_graphs, 0)):
+        pi = np.repeat(np.arange(wa.n_graphs), wb.n_graphs).astype(np.int32)
+        pj = np.tile(np.arange(wb.n_graphs), wa.n_graphs).astype(np.int32)
+        K, fl, _ = solve(torch, solver, A, B, pi, pj)
+        np.testing.assert_allclose(K, C.pairs(both, pi + oa, pj + ob, tier=0), rtol=RTOL)
+        assert (fl == 0).all() and "mgk_pcg_reduced" in solver.launch_log() and "mgk_pcg_regs" in solver.launch_log()
+
+
+def test_many_isolated_vertices(torch, solver):
+    """Pairs that fit their own launch shape only, and pairs whose vertices do not fit beside the eliminated elements."""
+    rng = np.random.default_rng(29)
+    wb = W.concat_batches([graph(n, e, rng) for n, e in ((13, [(0, i) for i in range(1, 13)]), (1200, [(0, 1)]), (2, [(0, 1)]), (2000, [(0, 1)]),
+                                                         (1, []), (9000, [(0, 1)]), (12000, [(0, 1)]))], PRM, "isolated")
+    solver.configure(PRM)
+    B = solver.load_batch(wb)
+    for pi, pj in (([0, 2], [1, 3]), ([4, 5], [5, 4]), ([4, 6], [6, 4]), ([0, 2, 4, 4], [1, 3, 5, 6])):
+        pi, pj = np.array(pi, np.int32), np.array(pj, np.int32)
+        K, fl, _ = solve(torch, solver, B, B, pi, pj)
+        np.testing.assert_allclose(K, C.pairs(wb, pi, pj, tier=1), rtol=RTOL)
+        assert (fl == 0).all()
