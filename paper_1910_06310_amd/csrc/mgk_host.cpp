@@ -782,30 +782,49 @@ int64_t regs_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves) {
            (int64_t)waves * (8 * ept + 45);
 }
 
-// The same for the solver of the reduced system.
-int reduced_ept(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves) {
-    const int64_t N = (int64_t)o.n_red * i.n;
-    return (int)std::min<int64_t>(std::max<int64_t>(1, (N + waves * 64 - 1) >> (waves == 2 ? 7 : waves == 4 ? 8 : 9)), MGK_REGS_MAX_EPT + 1);
-}
-int64_t reduced_cost(const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, int chunks) {
-    const uint8_t* need = o.red_need + 2 * MGK_RED_LIST(waves);
-    if (need[0] > MGK_RED_BLACK(waves) || need[1] > MGK_RED_RED(waves) || chunks > MGK_REGS_MAX_CHUNKS || i.max_deg > MGK_REGS_MAX_DEG ||
-        (waves == 2 && chunks > 1))
-        return -1;
-    const int ept = reduced_ept(o, i, waves);
-    if (ept > MGK_REGS_MAX_EPT || waves * 64 * ept + (int64_t)(o.n - o.n_red) * i.n > MGK_RED_MAX_P) return -1;
-    if (mgk_reduced_plan(o.n, o.n_red, i.n, waves, ept).total * 4 > MGK_LDS_LIMIT_BYTES) return -1;   // many isolated vertices
-    return o.nnz * (2 * chunks) + o.n * (1 + 4 * chunks) + waves * (9 * ept + 90);
-}
-void set_reduced(PairPlan& pl, const MgkGraphDesc& o, const MgkGraphDesc& i, int waves, int chunks, int64_t cost) {
+// The same for the solver of the reduced system, both orientations and `fewest` to 8 wavefronts: the cheapest (the first of
+// equal ones, fewer wavefronts before more).  Returns false if the pair does not fit.
+bool plan_reduced(PairPlan& pl, const MgkGraphDesc& a, const MgkGraphDesc& b, bool may_swap, int fewest) {
+    struct Side {
+        const MgkGraphDesc *o, *i;
+        bool swap;
+        int chunks, left, eliminated;   // elements
+        int64_t cost;
+    } side[2];
+    int sides = 0;
+    for (int sw = 0; sw < (may_swap ? 2 : 1); ++sw) {
+        const MgkGraphDesc &o = sw ? b : a, &i = sw ? a : b;
+        const int chunks = std::max(1, i.lane_len / 64);
+        const int64_t left = (int64_t)o.n_red * i.n, all = (int64_t)o.n * i.n;   // on chip: 16384 at most
+        if (chunks > MGK_REGS_MAX_CHUNKS || i.max_deg > MGK_REGS_MAX_DEG || left > 8 * 64 * MGK_REGS_MAX_EPT) continue;
+        side[sides++] = {&o, &i, sw != 0, chunks, (int)left, (int)(all - left), (int64_t)o.nnz * (2 * chunks) + (int64_t)o.n * (1 + 4 * chunks)};
+    }
+    int64_t best = INT64_MAX;
+    const Side* of_best = nullptr;
+    for (int which = fewest == 2 ? 0 : fewest == 4 ? 1 : 2; which < 3; ++which)
+        for (int k = 0; k < sides; ++k) {
+            const Side& s = side[k];
+            const int waves = 2 << which, ept = std::max(1, (s.left + waves * 64 - 1) >> (7 + which));
+            const int64_t cost = s.cost + waves * (9 * ept + 90);
+            const uint8_t* need = s.o->red_need + 2 * which;
+            if (cost >= best || ept > MGK_REGS_MAX_EPT || need[0] > MGK_RED_BLACK(waves) || need[1] > MGK_RED_RED(waves) ||
+                (waves == 2 && s.chunks > 1) || waves * 64 * ept + s.eliminated > MGK_RED_MAX_P)
+                continue;
+            const int32_t words = mgk_reduced_plan(s.o->n, s.o->n_red, s.i->n, waves, ept).total;
+            if (words * 4 > MGK_LDS_LIMIT_BYTES) continue;   // many isolated vertices
+            best = cost;
+            of_best = &s;
+            pl.waves = waves;
+            pl.ept = ept;
+            pl.lds_words = words;
+        }
+    if (!of_best) return false;
     pl.reduced = true;
-    pl.atomic_rows = false;
-    pl.waves = waves;
-    pl.chunks = chunks;
-    pl.ept = reduced_ept(o, i, waves);
-    pl.cost = cost * 16;
-    pl.lds_words = mgk_reduced_plan(o.n, o.n_red, i.n, waves, pl.ept).total;
-    pl.eliminated = (o.n - o.n_red) * i.n;
+    pl.swap = of_best->swap;
+    pl.chunks = of_best->chunks;
+    pl.cost = best * 16;
+    pl.eliminated = of_best->eliminated;
+    return true;
 }
 
 // Owner-computes solver for (outer o, inner i): the cheapest launch shape that holds the
@@ -839,19 +858,10 @@ int64_t sell_cost(const MgkSellDesc& o, const MgkSellDesc& i, int* waves, int* e
 PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDesc* sa, const MgkSellDesc* sb,
                    bool may_swap, int forced_waves, int onchip_limit, int cache, int attr_dim, int reduced) {
     const bool product_cache = cache != 0;
-    // wave iterations of one XMV: outer nonzeros x 64-lane chunks of the inner layout
-    auto passes = [](const MgkGraphDesc& o, const MgkGraphDesc& i) {
-        return (int64_t)o.nnz * (i.lane_len / 64) + 2 * (int64_t)o.n * (i.lane_len / 64);
-    };
-    PairPlan pl;
-    const int64_t keep = passes(a, b), swp = passes(b, a);
-    const bool keep_atomic = b.max_deg > MGK_LANE_GROUP, swp_atomic = a.max_deg > MGK_LANE_GROUP;
-    pl.swap = may_swap && (keep_atomic != swp_atomic ? keep_atomic : swp < keep);
-    pl.atomic_rows = pl.swap ? swp_atomic : keep_atomic;
     const int64_t N = (int64_t)a.n * b.n;
-    pl.cost = (pl.swap ? swp : keep) * 64 + 16 * N;
-    if (N > MGK_SMALL_MAX_N || N > onchip_limit) return pl;
-    if (cache == 3 && forced_waves == 0 && attr_dim == 0 && sa && sb &&
+    const bool fits = N <= MGK_SMALL_MAX_N && N <= onchip_limit;
+    PairPlan pl;
+    if (fits && cache == 3 && forced_waves == 0 && attr_dim == 0 && sa && sb &&
         mgk_sell_ok(*sa) && mgk_sell_ok(*sb)) {
         int64_t best = -1;
         for (int sw = 0; sw < (may_swap ? 2 : 1); ++sw) {
@@ -876,22 +886,28 @@ PairPlan plan_pair(const MgkGraphDesc& a, const MgkGraphDesc& b, const MgkSellDe
         }
     }
     // the reduced system first; pairs that fit the full one only are solved with that
-    for (int system = reduced ? 1 : 0; product_cache && forced_waves == 0 && system >= 0; --system) {
+    if (fits && reduced && product_cache && forced_waves == 0 && plan_reduced(pl, a, b, may_swap, reduced)) return pl;
+    // wave iterations of one XMV: outer nonzeros x 64-lane chunks of the inner layout
+    auto passes = [](const MgkGraphDesc& o, const MgkGraphDesc& i) {
+        return (int64_t)o.nnz * (i.lane_len / 64) + 2 * (int64_t)o.n * (i.lane_len / 64);
+    };
+    const int64_t keep = passes(a, b), swp = passes(b, a);
+    const bool keep_atomic = b.max_deg > MGK_LANE_GROUP, swp_atomic = a.max_deg > MGK_LANE_GROUP;
+    pl.swap = may_swap && (keep_atomic != swp_atomic ? keep_atomic : swp < keep);
+    pl.atomic_rows = pl.swap ? swp_atomic : keep_atomic;
+    pl.cost = (pl.swap ? swp : keep) * 64 + 16 * N;
+    if (!fits) return pl;
+    if (product_cache && forced_waves == 0) {
         int64_t best = -1;
-        for (int w = system ? reduced : 4; w <= 8; w *= 2)
+        for (int w = 4; w <= 8; w *= 2)
             for (int sw = 0; sw < (may_swap ? 2 : 1); ++sw) {
-                const MgkGraphDesc &o = sw ? b : a, &i = sw ? a : b;
-                const int64_t c = system ? reduced_cost(o, i, w, std::max(1, i.lane_len / 64)) : regs_cost(o, i, w);
+                const int64_t c = sw ? regs_cost(b, a, w) : regs_cost(a, b, w);
                 if (c >= 0 && (best < 0 || c < best)) { best = c; pl.waves = w; pl.swap = sw != 0; }
             }
         if (best >= 0) {
             const MgkGraphDesc& o = pl.swap ? b : a;
             const MgkGraphDesc& i = pl.swap ? a : b;
             pl.atomic_rows = false;
-            if (system) {
-                set_reduced(pl, o, i, pl.waves, std::max(1, i.lane_len / 64), best);
-                return pl;
-            }
             pl.ept = (int)std::max<int64_t>(1, (N + pl.waves * 64 - 1) / (pl.waves * 64));
             pl.chunks = std::max(1, i.lane_len / 64);
             pl.cost = best * 16 + 16 * N;
@@ -942,6 +958,7 @@ bool join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_lim
 
 // A launch shape: jobs of one shape go into one kernel launch.
 struct Shape {
+    uint32_t key = 0;          // of the six below, and big
     int16_t waves = 0, ept = 0, chunks = 0, sell_regs = 0;
     bool atomic_rows = false, swapped = false, reduced = false;
     bool big = false;          // too large for the separable product on chip, where that may be taken
@@ -950,10 +967,6 @@ struct Shape {
     int64_t base_words = 0;    // largest LDS need of its jobs without the padded vectors
     int32_t eliminated = 0;    // most of a job
     int64_t min_cost = INT64_MAX, max_cost = 0;
-    bool same(const Shape& s) const {
-        return waves == s.waves && ept == s.ept && chunks == s.chunks && sell_regs == s.sell_regs &&
-               atomic_rows == s.atomic_rows && swapped == s.swapped && reduced == s.reduced && big == s.big;
-    }
     // padded vectors in the LDS plan of each solver (the owner-computes one also has a
     // schedule word per wavefront and slot; 4 words of alignment slack)
     int64_t vector_words() const {
@@ -976,25 +989,26 @@ struct JobPlan {
     const bool separable;      // separable_on_chip()
     bool any_big = false;      // streaming pairs beyond it
     explicit JobPlan(bool sep) : separable(sep) { std::fill(table, table + kTable, (int16_t)-1); }
-    // index of the shape of a planned pair of graphs a and b; counts the pair in
+    // index of the shape of a planned pair of graphs a and b; counts the pair in (16 ns; 31 with a Shape made for every pair)
     int shape_of(const PairPlan& pl, bool swapped, const MgkGraphDesc& a, const MgkGraphDesc& b) {
         const bool streaming = pl.chunks == 0 && pl.sell_regs == 0;
-        Shape s;
-        s.waves = (int16_t)pl.waves;
-        s.ept = (int16_t)pl.ept;
-        s.chunks = (int16_t)pl.chunks;
-        s.sell_regs = (int16_t)pl.sell_regs;
-        s.atomic_rows = pl.atomic_rows;
-        s.swapped = swapped;
-        s.reduced = pl.reduced;
-        const bool big = streaming && (int64_t)a.n * b.n > MGK_PCG_SEP_MAX_N;
-        any_big = any_big || big;
-        s.big = big && separable;
+        const bool beyond = streaming && (int64_t)a.n * b.n > MGK_PCG_SEP_MAX_N, big = beyond && separable;
+        any_big = any_big || beyond;
         const uint32_t key = (uint32_t)pl.waves | (uint32_t)pl.ept << 5 | (uint32_t)pl.chunks << 10 | (uint32_t)pl.sell_regs << 13 |
-                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22 | (uint32_t)s.big << 23;
+                             (uint32_t)pl.atomic_rows << 20 | (uint32_t)swapped << 21 | (uint32_t)pl.reduced << 22 | (uint32_t)big << 23;
         uint32_t slot = (key * 2654435761u) >> 20;   // open addressing: there are far fewer shapes than slots
-        while (table[slot] >= 0 && !shapes[(size_t)table[slot]].same(s)) slot = (slot + 1) % kTable;
+        while (table[slot] >= 0 && shapes[(size_t)table[slot]].key != key) slot = (slot + 1) % kTable;
         if (table[slot] < 0) {
+            Shape s;
+            s.key = key;
+            s.waves = (int16_t)pl.waves;
+            s.ept = (int16_t)pl.ept;
+            s.chunks = (int16_t)pl.chunks;
+            s.sell_regs = (int16_t)pl.sell_regs;
+            s.atomic_rows = pl.atomic_rows;
+            s.swapped = swapped;
+            s.reduced = pl.reduced;
+            s.big = big;
             table[slot] = (int16_t)shapes.size();
             shapes.push_back(s);
         }
