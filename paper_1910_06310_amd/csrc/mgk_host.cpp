@@ -436,7 +436,7 @@ int balanced_split(const std::vector<int32_t>& deg, int n, int waves, int32_t* b
 
 // Schedule of a graph as outer operand of the reduced solver (see MgkReducedPlan), one graph after another.  New graphs
 // are often few and compared at once, so that the schedules count: 4.4 us a molecule-like graph of 35 vertices with a
-// scan over all vertices for the next one to colour and a branch for every row and nonzero, 2.6 us like this.
+// scan over all vertices for the next one to colour, a branch for every row and nonzero and all three divisions, 2.0 us like this.
 class ReducedSchedule {
 public:
     static bool makes(const MgkGraphDesc& gd) { return gd.nnz <= MGK_RED_MAX_NNZ && gd.n < 65536; }
@@ -463,7 +463,8 @@ public:
         of_wave_.resize((size_t)n);
         divide<2>(gd, rowptr, count, nnz, list, split, order);
         divide<4>(gd, rowptr, count, nnz, list, split, order);
-        divide<8>(gd, rowptr, count, nnz, list, split, order);
+        // eight cost more than four wherever both fit, but for elements that only eight hold: more than 64 vertices against 32 red ones
+        if (gd.red_need[2] > MGK_RED_BLACK(4) || gd.red_need[3] > MGK_RED_RED(4)) divide<8>(gd, rowptr, count, nnz, list, split, order);
     }
 
 private:
@@ -2473,7 +2474,8 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
 
     struct Nz { uint32_t i, j; float w, e; int64_t edge; };
     std::vector<Nz> nz, given;
-    std::vector<int32_t> sorted[2], bucket, seen;
+    std::vector<int32_t> sorted[2], bucket, deg, filled;
+    std::vector<double> rs;
     MgkAdj adj;
     std::vector<int32_t> cursor;
 
@@ -2535,9 +2537,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         if (n64 > 65535 * (int64_t)kTile) return fail(ctx, MGK_ELIMIT, "graph %d has too many vertices", g);
         const int n = (int)n64;
 
-        // ---- validate edges, build adjacency (both directions)
-        adj.n = n;
-        adj.ptr.assign(n + 1, 0);
+        // ---- validate edges
         for (int64_t k = e0; k < e1; ++k) {
             const int32_t s = src[k], d = dst[k];
             if (s < 0 || s >= n || d < 0 || d >= n)
@@ -2549,46 +2549,54 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             for (int a = 0; edge_label && a < D; ++a)
                 if (!std::isfinite(edge_label[k * D + a]))
                     return fail(ctx, MGK_EINVAL, "graph %d edge %lld: label is not finite", g, (long long)(k - e0));
-            adj.ptr[s + 1]++;
-            adj.ptr[d + 1]++;
         }
-        for (int i = 0; i < n; ++i) adj.ptr[i + 1] += adj.ptr[i];
-        adj.idx.assign((size_t)(2 * m), 0);
-        cursor.assign(adj.ptr.begin(), adj.ptr.end() - 1);
-        for (int64_t k = e0; k < e1; ++k) {
-            adj.idx[cursor[src[k]]++] = dst[k];
-            adj.idx[cursor[dst[k]]++] = src[k];
-        }
-        seen.assign((size_t)n, -1);
-        for (int i = 0; i < n; ++i) {  // duplicate edges
-            bool twice = false;
-            for (int k = adj.ptr[i]; k < adj.ptr[i + 1]; ++k) {
-                twice |= seen[(size_t)adj.idx[(size_t)k]] == i;
-                seen[(size_t)adj.idx[(size_t)k]] = i;
+        // Adjacency (both directions) and the first vertex with an edge given twice.  A graph whose order is there does without: an edge given
+        // twice shows among the sorted nonzeros below.
+        auto first_twice = [&] {
+            adj.n = n;
+            adj.ptr.assign(n + 1, 0);
+            for (int64_t k = e0; k < e1; ++k) {
+                adj.ptr[src[k] + 1]++;
+                adj.ptr[dst[k] + 1]++;
             }
-            if (twice) return fail(ctx, MGK_EINVAL, "graph %d: duplicate edge at vertex %d", g, i);
+            for (int i = 0; i < n; ++i) adj.ptr[i + 1] += adj.ptr[i];
+            adj.idx.assign((size_t)(2 * m), 0);
+            cursor.assign(adj.ptr.begin(), adj.ptr.end() - 1);
+            for (int64_t k = e0; k < e1; ++k) {
+                adj.idx[cursor[src[k]]++] = dst[k];
+                adj.idx[cursor[dst[k]]++] = src[k];
+            }
+            int first = -1;
+            for (int i = n - 1; i >= 0; --i) {
+                std::sort(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]);
+                if (std::adjacent_find(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]) != adj.idx.begin() + adj.ptr[i + 1]) first = i;
+            }
+            return first;
+        };
+        int bad_prob = -1;
+        for (int i = n - 1; start_prob && i >= 0; --i)
+            if (!std::isfinite(start_prob[v0 + i]) || start_prob[v0 + i] < 0.f) bad_prob = i;
+        bool bad_coord = false;
+        for (int64_t k = v0 * coord_dim; reorder == MGK_REORDER_MORTON && k < v1 * coord_dim; ++k) bad_coord = bad_coord || !std::isfinite(coords[k]);
+        const bool has_order = !pre_perm[(size_t)g].empty();
+        if (bad_prob >= 0 || bad_coord || (!has_order && (reorder == MGK_REORDER_PBR || reorder == MGK_REORDER_RCM))) {
+            const int i = first_twice();
+            if (i >= 0) return fail(ctx, MGK_EINVAL, "graph %d: duplicate edge at vertex %d", g, i);
         }
-        if (start_prob)
-            for (int i = 0; i < n; ++i)
-                if (!std::isfinite(start_prob[v0 + i]) || start_prob[v0 + i] < 0.f)
-                    return fail(ctx, MGK_EINVAL, "graph %d vertex %d: bad starting probability", g, i);
+        if (bad_prob >= 0) return fail(ctx, MGK_EINVAL, "graph %d vertex %d: bad starting probability", g, bad_prob);
+        if (bad_coord) return fail(ctx, MGK_EINVAL, "graph %d: coordinate is not finite", g);
 
         // ---- a2: vertex order
         std::vector<int32_t> perm;
-        if (pre_perm[(size_t)g].empty() && (reorder == MGK_REORDER_PBR || reorder == MGK_REORDER_RCM))
-            for (int i = 0; i < n; ++i) std::sort(adj.idx.begin() + adj.ptr[i], adj.idx.begin() + adj.ptr[i + 1]);
-        if (!pre_perm[(size_t)g].empty()) perm = std::move(pre_perm[(size_t)g]);
+        if (has_order) perm = std::move(pre_perm[(size_t)g]);
         else if (reorder == MGK_REORDER_PBR) perm = mgk_order_pbr(adj, kTile);
         else if (reorder == MGK_REORDER_RCM) perm = mgk_order_rcm(adj);
-        else if (reorder == MGK_REORDER_MORTON) {
-            for (int64_t k = v0 * coord_dim; k < v1 * coord_dim; ++k)
-                if (!std::isfinite(coords[k])) return fail(ctx, MGK_EINVAL, "graph %d: coordinate is not finite", g);
-            perm = mgk_order_morton(n, coord_dim, coords + v0 * coord_dim);
-        } else perm = mgk_order_identity(n);
+        else if (reorder == MGK_REORDER_MORTON) perm = mgk_order_morton(n, coord_dim, coords + v0 * coord_dim);
+        else perm = mgk_order_identity(n);
         std::copy(perm.begin(), perm.end(), B->perm.begin() + v0);
 
         // ---- per-vertex data in stored order; a1: row sums for d_i = sum_j A_ij + q
-        std::vector<double> rs(n, 0.0);
+        rs.assign((size_t)n, 0.0);
         for (int64_t k = e0; k < e1; ++k) {
             const double wv = weight ? weight[k] : 1.0;
             rs[perm[src[k]]] += wv;
@@ -2635,7 +2643,12 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
             by(ntr, sorted[0].data(), sorted[1], [](const Nz& z) { return (size_t)(z.j / kTile); });
             by(ntr, sorted[1].data(), sorted[0], [](const Nz& z) { return (size_t)(z.i / kTile); });
             nz.resize(given.size());
-            for (size_t k = 0; k < nz.size(); ++k) nz[k] = given[(size_t)sorted[0][k]];
+            bool twice = false;
+            for (size_t k = 0; k < nz.size(); ++k) {
+                nz[k] = given[(size_t)sorted[0][k]];
+                twice |= k > 0 && nz[k].i == nz[k - 1].i && nz[k].j == nz[k - 1].j;
+            }
+            if (twice) return fail(ctx, MGK_EINVAL, "graph %d: duplicate edge at vertex %d", g, first_twice());
         }
 
         MgkGraphDesc& gd = B->graphs[g];
@@ -2646,7 +2659,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         gd.zoff = (int32_t)B->w.size();
         gd.toff = (int32_t)B->tiles.size();
         gd.roff = (int32_t)trow_ptr.size();
-        std::vector<int32_t> deg(n, 0);
+        deg.assign((size_t)n, 0);
         trow_ptr.resize(trow_ptr.size() + ntr + 1, 0);
         int32_t* trp = trow_ptr.data() + gd.roff;
         for (size_t k = 0; k < nz.size(); ++k) {
@@ -2719,7 +2732,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
         // the order the octiles hold them in) and lane order
         list_outer.resize((size_t)gd.zoff + nz.size());
         list_inner.resize((size_t)gd.loff + gd.lane_len, MgkEntry{0u, 0u, 0u, 0u});
-        std::vector<int32_t> filled(n, 0);
+        filled.assign((size_t)n, 0);
         for (size_t k = 0; k < nz.size(); ++k) {
             const uint32_t i = nz[k].i, j = nz[k].j;
             const int rank = filled[i]++;
