@@ -957,6 +957,46 @@ bool join_few(std::vector<PairPlan>& plans, const Graphs& graphs, int onchip_lim
     return any;
 }
 
+// Pairs that the reduced solver does not take and the register-resident one of the full system does have a launch of their own.
+// Where a few pairs need the streaming solver anyway, up to kFewFull of them go there too if that needs no other
+// workgroup size: 60 ladders of 16 to 50 vertices (1830 pairs, 696 of that kind) 159 us in four launches, 118 in three; by
+// themselves they are better off where their entries are kept (100 000 of them 4.68 and 5.26 ms, 250 50 and 74 us).
+constexpr int kFewFull = 1024;
+struct PlanKinds {   // of the pairs of a call
+    std::atomic<int> full{0};
+    std::atomic<uint32_t> streaming{0};   // launches of the streaming solver, see launch()
+    static uint32_t launch(const PairPlan& pl, bool two_batches) {
+        int size = 0;
+        while (1 << size < pl.waves) ++size;
+        return 1u << (4 * size + 2 * pl.atomic_rows + (pl.swap && two_batches));
+    }
+    struct Part {   // counted by one task
+        int full = 0;
+        uint32_t streaming = 0;
+        void add(const PairPlan& pl, bool two_batches) {
+            if (pl.reduced || pl.sell_regs > 0 || pl.waves == 0) return;
+            if (pl.chunks > 0) ++full;
+            else streaming |= launch(pl, two_batches);
+        }
+    };
+    void add(const Part& p) {
+        full += p.full;
+        streaming |= p.streaming;
+    }
+};
+template <class Graphs>
+void join_full(std::vector<PairPlan>& plans, const PlanKinds& kinds, bool two_batches, const Graphs& graphs, int onchip_limit, int attr_dim) {
+    if (kinds.full == 0 || kinds.full > kFewFull || kinds.streaming == 0 || plans.size() > 65536) return;   // more pairs: a launch does not count
+    std::vector<std::pair<size_t, PairPlan>> moved;
+    for (size_t k = 0; k < plans.size(); ++k) {
+        if (plans[k].reduced || plans[k].chunks == 0) continue;
+        const auto g = graphs(k);
+        moved.emplace_back(k, plan_pair(*g.first, *g.second, nullptr, nullptr, true, 0, onchip_limit, 0, attr_dim, 0));
+        if (moved.back().second.waves == 0 || !(kinds.streaming & PlanKinds::launch(moved.back().second, two_batches))) return;
+    }
+    for (const auto& m : moved) plans[m.first] = m.second;
+}
+
 // A launch shape: jobs of one shape go into one kernel launch.
 struct Shape {
     uint32_t key = 0;          // of the six below, and big
@@ -3039,28 +3079,35 @@ static mgk_status gram_body(mgk_ctx* ctx, mgk_batch* batch, float* K_dev, int32_
         // the plans of the G (G + 1) / 2 pairs are independent: rows of the triangle in turn on
         // several threads, row i starting at pair i G - i (i - 1) / 2
         std::vector<PairPlan> plans((size_t)(G * (G + 1) / 2));
+        PlanKinds kinds;
         {
             const int cache = ctx->product_cache;
             const int attr_dim = attr_dim_of(ctx);
             const int forced = ctx->waves, limit = ctx->onchip_limit;
             const int T = (int)std::max<int64_t>(1, std::min<int64_t>(64, G / 64));
             ctx->workers.run(T, [&](int t) {   // allocates nothing, cannot throw
+                PlanKinds::Part kinds_here;
                 for (int64_t i = t; i < G; i += T) {
                     PairPlan* row = plans.data() + (i * G - i * (i - 1) / 2);
-                    for (int64_t j = i; j < G; ++j)
+                    for (int64_t j = i; j < G; ++j) {
                         row[j - i] = plan_pair(batch->graphs[i], batch->graphs[j], &batch->sell_desc[(size_t)i],
                                                &batch->sell_desc[(size_t)j], true, forced, limit, cache, attr_dim, reduced ? waves : 0);
+                        kinds_here.add(row[j - i], false);
+                    }
                 }
+                kinds.add(kinds_here);
             });
         }
         jobs.joined = false;
-        if (reduced && ctx->reduced_system == 1) {
+        if (reduced) {
             std::vector<int64_t> row((size_t)G);   // first pair of each row of the triangle
             for (int64_t i = 0; i < G; ++i) row[(size_t)i] = i * G - i * (i - 1) / 2;
-            jobs.joined = join_few(plans, [&](size_t k) {
+            auto graphs_of = [&](size_t k) {
                 const int64_t i = std::upper_bound(row.begin(), row.end(), (int64_t)k) - row.begin() - 1;
                 return std::make_pair(&batch->graphs[(size_t)i], &batch->graphs[(size_t)(i + (int64_t)k - row[(size_t)i])]);
-            }, ctx->onchip_limit, attr_dim_of(ctx));
+            };
+            if (ctx->reduced_system == 1) jobs.joined = join_few(plans, graphs_of, ctx->onchip_limit, attr_dim_of(ctx));
+            join_full(plans, kinds, false, graphs_of, ctx->onchip_limit, attr_dim_of(ctx));
         }
         size_t next_plan = 0;
         for (int64_t i = 0; i < G; ++i)
@@ -3125,22 +3172,28 @@ static mgk_status pairs_impl(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n
         if (i_host[k] < 0 || i_host[k] >= X->n_graphs || j_host[k] < 0 || j_host[k] >= Y->n_graphs)
             return fail(ctx, MGK_EINVAL, "pair %lld: graph index out of range", (long long)k);
     std::vector<PairPlan> plans((size_t)n_pairs);
+    PlanKinds kinds;
     {
         constexpr int64_t kPart = 1024;   // about 20 us of planning
         const int attr_dim = attr_dim_of(ctx);
         const int reduced = solve_reduced(ctx, iters_dev) ? reduced_waves(n_pairs) : 0;
         ctx->workers.run((int)((n_pairs + kPart - 1) / kPart), [&](int t) {   // allocates nothing, cannot throw
             const int64_t end = std::min(n_pairs, (t + 1) * kPart);
+            PlanKinds::Part kinds_here;
             for (int64_t k = t * kPart; k < end; ++k) {
                 const int32_t i = i_host[k], j = j_host[k];
                 plans[(size_t)k] = plan_pair(X->graphs[i], Y->graphs[j], &X->sell_desc[(size_t)i], &Y->sell_desc[(size_t)j], true,
                                              ctx->waves, ctx->onchip_limit, ctx->product_cache, attr_dim, reduced);
+                kinds_here.add(plans[(size_t)k], X != Y);
             }
+            kinds.add(kinds_here);
         });
     }
-    if (solve_reduced(ctx, iters_dev) && ctx->reduced_system == 1)
-        join_few(plans, [&](size_t k) { return std::make_pair(&X->graphs[(size_t)i_host[k]], &Y->graphs[(size_t)j_host[k]]); },
-                      ctx->onchip_limit, attr_dim_of(ctx));
+    if (solve_reduced(ctx, iters_dev)) {
+        auto graphs_of = [&](size_t k) { return std::make_pair(&X->graphs[(size_t)i_host[k]], &Y->graphs[(size_t)j_host[k]]); };
+        if (ctx->reduced_system == 1) join_few(plans, graphs_of, ctx->onchip_limit, attr_dim_of(ctx));
+        join_full(plans, kinds, X != Y, graphs_of, ctx->onchip_limit, attr_dim_of(ctx));
+    }
     JobPlan plan(separable_on_chip(ctx));
     plan.jobs.reserve((size_t)n_pairs);
     std::vector<MgkLargePair> large[2];

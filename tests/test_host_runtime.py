@@ -479,18 +479,46 @@ def test_schedules_of_the_reduced_solver(host):
     host.free(inner)
 
 
-@pytest.mark.parametrize("parts", [[grid(a, b) for a in range(4, 7) for b in range(a, 7)], [grid(2, n) for n in range(8, 27)]], ids=["grids", "ladders"])
-def test_pairs_that_fit_the_full_system_only_stay_register_resident(host, parts):
-    """A graph of whole rows may fit the wavefronts of the solver of the full system and not those of the reduced one."""
-    streaming = []
+def kinds(host):
+    """Pairs by kernel of the last call."""
+    got = {}
+    for kernel, n in re.findall(r"mgk_pcg_(\w+)<.*> pairs=(\d+)", host.launch_log()):
+        got[kernel] = got.get(kernel, 0) + int(n)
+    return got
+
+
+LATTICES = {"grids": [grid(a, b) for a in range(4, 7) for b in range(a, 7)], "ladders": [grid(2, n) for n in range(8, 27)]}
+
+
+@pytest.mark.parametrize("name,full,streaming", [("grids", True, False), ("ladders", False, True)])
+def test_pairs_that_fit_the_full_system_only_stay_register_resident(host, name, full, streaming):
+    """A graph of whole rows may fit the wavefronts of the solver of the full system and not those of the reduced one.  A few of
+    those go with others that need the streaming solver, if there are any."""
+    got = []
     for mode in (0, 1):
         host.set("reduced_system", mode)
-        B = host.load(graphs(*parts))
+        B = host.load(graphs(*LATTICES[name]))
         assert host.gram(B) == 0, host.error()
-        streaming.append(sum(int(k) for k in re.findall(r"mgk_pcg_small\S* \S* *pairs=(\d+)", host.launch_log())))
-        assert ("mgk_pcg_reduced" in host.launch_log()) == (mode == 1) and "mgk_pcg_regs" in host.launch_log()
+        got.append(kinds(host))
+        i, j = np.triu_indices(len(LATTICES[name]))
+        assert host.pairs(B, B, i, j) == 0 and kinds(host) == got[-1]
         host.free(B)
-    assert streaming[0] == streaming[1] and host.violations() == ""
+    assert host.violations() == "" and got[1]["reduced"] > 0
+    assert (got[1].get("regs", 0) > 0, got[1].get("small", 0) > 0) == (full, streaming)
+    assert (got[0].get("small", 0) > 0) == streaming
+    assert got[1].get("regs", 0) + got[1].get("small", 0) + got[1]["reduced"] == sum(got[0].values())
+
+
+def test_pairs_of_the_full_system_join_launches_of_their_size_only(host):
+    """Not where they would need another workgroup size, and not more than a thousand of them."""
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(path(12), grid(6, 6), grid(2, 21), ring(24, 5)))
+    stream = (1, 3)   # needs the streaming solver, four wavefronts
+    for pair, count, stays in (((1, 1), 1, False), ((1, 1), 1000, False), ((0, 2), 1, True), ((1, 1), 1100, True)):   # the path: two wavefronts
+        i, j = np.array([pair] * count + [stream]).T
+        assert host.pairs(B, B, i, j) == 0, host.error()
+        assert kinds(host) == ({"regs": count, "small": 1} if stays else {"small": count + 1}) and host.violations() == ""
+    host.free(B)
 
 
 @pytest.mark.parametrize("n,inner", [(9000, 1), (10300, 1), (12000, 1), (16000, 1), (1, 12000), (2, 8000)])
