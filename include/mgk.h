@@ -42,10 +42,10 @@
  *    8 GiB of features.  Between calls at most 1 GiB of features of one kind and
  *    side is kept; where memory for features is short the pairs are solved
  *    without them.
- *  - Calls whose on-chip pairs take the separable form of the edge kernel allocate features
- *    of the graphs of both batches, 32 bytes per nonzero and up to seven terms, 256 MiB
- *    at most, which the ctx keeps; where memory is short they are solved without.  Such calls do not wait on
- *    the host, but on the device each one's stream waits for the last one's.
+ *  - On-chip pairs of graphs too large to keep their entries in registers may take the separable
+ *    form of the edge kernel.  Its features are in memory that the ctx reserves when such graphs are loaded, 256
+ *    bytes per nonzero, 256 MiB at most; where memory is short they are solved without.  Such calls do not wait
+ *    on the host, but on the device each one's stream waits for the last one's.
  *  - Non-convergence is data, not an error: the pair's flag is set to 1 and the
  *    value of the last iterate is still written.  Flag 2 with a NaN value marks
  *    a pair that a kernel refused because it did not fit the launch shape the
@@ -262,12 +262,12 @@ mgk_status mgk_pairs_dev(mgk_ctx* ctx, mgk_batch* X, mgk_batch* Y, int64_t n_pai
  * serving loops, harnesses that forbid hipMalloc).  Same
  * arguments, same kernels and bit-identical values, but the call makes no hipMalloc /
  * hipFree (nor any other allocating HIP or library call): the job list its kernels read
- * lives in a fixed 1 MiB array in device memory that every GPU it is called on holds
- * until the process ends, and where the call takes the separable product on chip its features in another one of
- * 256 MiB.  Limits: at most 65536 pairs per call, and every pair must be
+ * lives in a fixed 1 MiB array in device memory that every GPU the library runs on holds
+ * until the process ends (features of the separable form are in memory that loading the graphs has
+ * reserved; if that was short, other kernels may be taken than mgk_pairs finds memory for).  Limits: at most 65536 pairs per call, and every pair must be
  * solvable on chip (n n' <= the on-chip limit); otherwise MGK_ELIMIT and nothing is
- * enqueued.  All calls on a GPU share these arrays, which keep what the last
- * call left: calls that overlap in time on the same GPU (other streams, other contexts,
+ * enqueued.  All calls on a GPU share that one array, which keeps the jobs of the last
+ * call: calls that overlap in time on the same GPU (other streams, other contexts,
  * other threads) race on it; within one context a call first waits for the previous
  * mgk_pairs_noalloc call's stream.  The index arrays are read before the call
  * returns, as in mgk_pairs.  While a graph is recorded on `stream` the call is refused

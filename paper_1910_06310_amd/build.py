@@ -27,7 +27,7 @@ DEVICE_SOURCES += [("mgk_sell.hip", "w%d" % w, ["-DMGK_SELL_WAVES=%d" % w]) for 
 DEVICE_SOURCES.append(("mgk_large.hip", "all", []))
 DEVICE_SOURCES.append(("mgk_sep.hip", "all", []))
 DEVICE_SOURCES += [("mgk_pcg_sep.hip", "rk%d" % k, ["-DMGK_PCG_SEP_RK=%d" % k]) for k in (5, 7, 6, 4, 1)]
-DEVICE_SOURCES += [("mgk_noalloc.hip", part.lower(), ["-DMGK_NOALLOC_" + part]) for part in ("JOBS", "PACKETS")]
+DEVICE_SOURCES.append(("mgk_noalloc.hip", "all", []))
 HOST_SOURCES = ["mgk_host.cpp", "mgk_reorder.cpp"]
 
 # packed fp32 instructions are switched off on purpose for the test machines

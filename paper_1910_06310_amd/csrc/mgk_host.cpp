@@ -302,7 +302,8 @@ struct mgk_ctx {
     DevBuf dense_tiles[2][3];           // dense 8x8 expansions (weight, label, log2 weight)
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
-    DevBuf onchip_packets[2];           // packets of the separable product on chip
+    DevBuf onchip_packets;              // packets of the separable product on chip, of both batches of a call
+    std::vector<void*> old_packets;     // smaller ones before it, half as large each: kernels may still read them
     hipEvent_t onchip_packets_end = nullptr;   // of the last kernel that reads them
     bool features_in_use = false;       // by the call under way
     KeptBasis bases[4];                 // of the last label ranges and edge kernels, see sep_basis_for
@@ -1207,13 +1208,17 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
 // Gives back what the context keeps for later calls: features and blocks of freed batches.
 bool release_spare(mgk_ctx* ctx) {
     bool any = false;
-    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets[0],
-                      &ctx->onchip_packets[1]})
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets})
         if (b->p && !ctx->features_in_use) {
             (void)hipFree(b->p);   // waits for the work that reads it
             *b = DevBuf{};
             any = true;
         }
+    for (void* p : ctx->old_packets) {
+        (void)hipFree(p);
+        any = true;
+    }
+    ctx->old_packets.clear();
     std::vector<FreeBlob> blobs;
     {
         std::lock_guard<std::mutex> lock(ctx->memory->m);
@@ -1928,6 +1933,35 @@ double onchip_sep_gain(const JobBin& b, int rank_executed, int passes) {
     return 8.0 * rounds * ((double)b.sep.entries / 6.0 - (double)b.sep.halves * rank_executed / 18.0 - 300.0 * passes * (double)b.sep.blocks);
 }
 
+// Memory for the packets of calls that read this batch, and another one no larger: reserved when it is loaded, so that solve
+// calls, also those that may not allocate, find it.  Not where every pair fits the register-resident solver.  Sizes are
+// powers of two, a smaller block stays (loading waits for no call); without memory the solve calls do without.
+void reserve_packets(mgk_ctx* ctx, const mgk_batch* b) {
+    if (!mgk_launch_pcg_sep_rk5 || std::none_of(b->graphs.begin(), b->graphs.end(), [](const MgkGraphDesc& g) {
+            return g.n > 64 || g.max_deg > MGK_REGS_MAX_DEG || g.lane_len > 64 * MGK_REGS_MAX_CHUNKS || (int)((uint32_t)g.regs_runs >> 16) > MGK_REGS_SMAX_W8;
+        }))
+        return;
+    static_assert(64 * 64 <= 8 * 64 * MGK_REGS_MAX_EPT, "two graphs of 64 vertices");
+    constexpr int kPasses = MGK_SEP_MAX_RANK / 4;   // at most, of four features
+    const int64_t need = std::min<int64_t>(MGK_ONCHIP_PACKET_BYTES, 2 * ((int64_t)kPasses * b->packet_off[0].back() + 8) * 256);
+    if (!ctx->onchip_packets_end && hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming) != hipSuccess) {
+        ctx->onchip_packets_end = nullptr;
+        (void)hipGetLastError();
+        return;
+    }
+    if ((int64_t)ctx->onchip_packets.cap >= need) return;
+    size_t size = (size_t)64 << 10;
+    while ((int64_t)size < need) size *= 2;
+    ctx->old_packets.reserve(ctx->old_packets.size() + 1);
+    void* p = nullptr;
+    if (hipMalloc(&p, size) != hipSuccess) {
+        (void)hipGetLastError();   // no error of a later launch
+        return;
+    }
+    if (ctx->onchip_packets.p) ctx->old_packets.push_back(ctx->onchip_packets.p);
+    ctx->onchip_packets = DevBuf{p, size};
+}
+
 // Writing and reading the packets of a call: its end is recorded on every way out once something may be enqueued.
 struct PacketUse {
     mgk_ctx* ctx;
@@ -1946,11 +1980,10 @@ struct PacketUse {
 
 // The bins of a call that take the separable product on chip (use[k].waves > 0), and its packets in sl[].
 // Not while a graph is recorded (the packets belong to the context), nor where the caller asked for
-// the streaming solver.  A call that allows no allocation has its packets in the fixed array beside its jobs, which
-// holds as much as a call may use: it takes the same kernels as one that does.
+// the streaming solver.  A call that may not allocate takes the same kernels: the memory is there (reserve_packets).
 mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, const JobList& jl, bool may_allocate, hipStream_t stream,
                               std::vector<OnchipSep>& use, MgkSepLayout& L, MgkSepList (&sl)[2], PacketUse& packets) {
-    if (!separable_on_chip(ctx) || (!may_allocate && !mgk_noalloc_packet_storage)) return MGK_OK;
+    if (!separable_on_chip(ctx)) return MGK_OK;
     // Features of all graphs of the batches, formed before the kernels: 20 us with the basis and the launch, and 6 clocks of
     // a unit per nonzero and feature (23 us for 160 graphs of 1080 nonzeros).  At the lowest rank first: the basis takes time.
     auto total_gain = [&](int rank) {
@@ -1993,43 +2026,27 @@ mgk_status prepare_onchip_sep(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch*
         std::fill(use.begin(), use.end(), OnchipSep{});
         return MGK_OK;
     }
-    struct InUse {   // what is allocated for one side does not free the other
-        bool& flag;
-        ~InUse() { flag = false; }
-    } in_use{ctx->features_in_use};
-    ctx->features_in_use = true;
-    float* fixed = nullptr;
-    if (!may_allocate) {
-        hipError_t e = mgk_noalloc_packet_storage(ctx->device, &fixed);
-        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "fixed packet storage: %s", hipGetErrorString(e));
+    // Reserved when the graphs were loaded; a call that may allocate makes up for what was not to be had then.
+    if (ctx->onchip_packets.cap < (size_t)bytes && (!may_allocate || ensure(ctx, ctx->onchip_packets, (size_t)bytes) != MGK_OK)) {
+        std::fill(use.begin(), use.end(), OnchipSep{});   // short memory: the streaming solver
+        return MGK_OK;
     }
+    if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
     // An earlier call may still read the packets, also one on a stream of the same handle: destroyed since, or the
     // per-thread stream of another thread.  The stream waits, not the host.
-    if (fixed) {}   // the call has waited for the last one that used the fixed arrays
-    else if (!ctx->onchip_packets_end) MGK_HIP(ctx, hipEventCreateWithFlags(&ctx->onchip_packets_end, hipEventDisableTiming));
-    else MGK_HIP(ctx, hipStreamWaitEvent(stream, ctx->onchip_packets_end, 0));
+    MGK_HIP(ctx, hipStreamWaitEvent(stream, ctx->onchip_packets_end, 0));
+    float* to = (float*)ctx->onchip_packets.p;
     for (int k = 0; k < sides; ++k) {
         const mgk_batch* b = bt[k];
         sl[k] = b->sep[gi];
         sl[k].total = b->packet_off[gi].back();
-        const size_t need = ((size_t)L.passes * sl[k].total + 8) * 256;   // a stage loads eight steps at a time
-        float* to = fixed;
-        if (fixed) {
-            fixed += need / 4;
-        } else {
-            DevBuf& buf = ctx->onchip_packets[k];
-            if (buf.cap < need && ensure(ctx, buf, need) != MGK_OK) {   // short memory: the streaming solver
-                std::fill(use.begin(), use.end(), OnchipSep{});
-                return MGK_OK;
-            }
-            to = (float*)buf.p;
-            packets.open = true;
-        }
         sl[k].packets = to;
         int32_t max_n = 1;
         for (const MgkGraphDesc& g : b->graphs) max_n = std::max(max_n, g.n);
+        packets.open = true;
         hipError_t e = mgk_launch_sep_pack(b->dev, S, L, sl[k], sl[k].whole, b->n_graphs, max_n, to, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
+        to += ((size_t)L.passes * sl[k].total + 8) * 64;   // a stage loads eight steps at a time
     }
     if (sides == 1) sl[1] = sl[0];
     return MGK_OK;
@@ -2248,10 +2265,11 @@ void mgk_destroy(mgk_ctx* ctx) {
     if (!ctx) return;
     if (ctx->pair_jobs.dev) (void)hipFree(ctx->pair_jobs.dev);
     for (DevBuf* b : {&ctx->exp_outer[0], &ctx->exp_outer[1], &ctx->exp_inner[0], &ctx->exp_inner[1],
-                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets[0], &ctx->onchip_packets[1], &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
+                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets, &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
                       &ctx->dense_tiles[0][0], &ctx->dense_tiles[0][1], &ctx->dense_tiles[0][2],
                       &ctx->dense_tiles[1][0], &ctx->dense_tiles[1][1], &ctx->dense_tiles[1][2]})
         if (b->p) (void)hipFree(b->p);
+    for (void* p : ctx->old_packets) (void)hipFree(p);
     if (ctx->active_host) (void)hipHostFree(ctx->active_host);
     if (ctx->onchip_packets_end) (void)hipEventDestroy(ctx->onchip_packets_end);
     for (Staging::Slot& s : ctx->staging.slot) {
@@ -2961,6 +2979,7 @@ static mgk_status load_graphs_body(mgk_ctx* ctx, int32_t n_graphs, const int64_t
     B->dev.sell_desc = reinterpret_cast<const MgkSellDesc*>(base + o_sd);
     B->dev.sell_vtx = reinterpret_cast<const MgkSellVertex*>(base + o_sv);
     B->dev.sell_nbr = reinterpret_cast<const MgkSellNbr*>(base + o_sn);
+    reserve_packets(ctx, B);
 
     guard.b = nullptr;
     *out = B;

@@ -141,8 +141,6 @@ static inline hipError_t mgk_launch_sell(int waves, int ept, int regs, const Mgk
 // (mgk_noalloc.hip): its device address on `device` and how many jobs it holds.
 #define MGK_NOALLOC_MAX_PAIRS 65536
 hipError_t mgk_noalloc_job_storage(int device, MgkJob** jobs, int64_t* capacity);
-// The same for the packets of the separable product on chip, MGK_ONCHIP_PACKET_BYTES of them.
-__attribute__((weak)) hipError_t mgk_noalloc_packet_storage(int device, float** packets);
 
 // ---- solver with vectors in global memory (mgk_large.hip) --------------------
 // Expand every octile of batch B into the outer (CSR order) and inner (lane

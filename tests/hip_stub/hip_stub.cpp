@@ -359,15 +359,6 @@ hipError_t mgk_noalloc_job_storage(int, MgkJob** jobs, int64_t* capacity) {
     *capacity = MGK_NOALLOC_MAX_PAIRS;
     return hipSuccess;
 }
-hipError_t mgk_noalloc_packet_storage(int, float** packets) {
-    static float* storage = nullptr;
-    if (!storage) {   // never touched: no memory behind it
-        storage = (float*)malloc(MGK_ONCHIP_PACKET_BYTES);
-        device_memory[(char*)storage] = MGK_ONCHIP_PACKET_BYTES;
-    }
-    *packets = storage;
-    return hipSuccess;
-}
 hipError_t mgk_launch_expand(const MgkBatchDev& B, const MgkParams&, MgkEntry*, MgkEntry*, hipStream_t s) { return launched("expand", s, &B); }
 hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams&, float*, float*, float*, hipStream_t s) { return launched("expand_dense", s, &B); }
 hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair*, MgkPairState*, float*,

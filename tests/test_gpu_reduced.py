@@ -215,7 +215,7 @@ def test_recorded_gram_follows_the_mode(torch, solver):
 
 def test_pairs_that_fit_one_of_the_systems_only(torch, solver):
     """Grids and ladders: some fit the wavefronts of the solver of the full system and not those of the reduced one, in
-    either orientation and beside others; two batches."""
+    either orientation and beside others; two batches, few and many pairs."""
     rng = np.random.default_rng(23)
     grid = lambda a, b: (a * b, [(i * b + j, i * b + j + 1) for i in range(a) for j in range(b - 1)] +
                          [(i * b + j, (i + 1) * b + j) for i in range(a - 1) for j in range(b)])
@@ -227,9 +227,11 @@ def test_pairs_that_fit_one_of_the_systems_only(torch, solver):
     for A, B, wa, wb, oa, ob in ((BX, BX, X, X, 0, 0), (BY, BY, Y, Y, X.n_graphs, X.n_graphs), (BX, BY, X, Y, 0, X.n_graphs), (BY, BX, Y, X, X.n_graphs, 0)):
         pi = np.repeat(np.arange(wa.n_graphs), wb.n_graphs).astype(np.int32)
         pj = np.tile(np.arange(wb.n_graphs), wa.n_graphs).astype(np.int32)
-        K, fl, _ = solve(torch, solver, A, B, pi, pj)
-        np.testing.assert_allclose(K, C.pairs(both, pi + oa, pj + ob, tier=0), rtol=RTOL)
-        assert (fl == 0).all() and "mgk_pcg_reduced" in solver.launch_log() and "mgk_pcg_regs" in solver.launch_log()
+        ref = C.pairs(both, pi + oa, pj + ob, tier=0)
+        for many, other in ((1, "mgk_pcg_small"), (250, "mgk_pcg_regs")):   # a few join those that need the streaming solver
+            K, fl, _ = solve(torch, solver, A, B, np.tile(pi, many), np.tile(pj, many))
+            np.testing.assert_allclose(K, np.tile(ref, many), rtol=RTOL)
+            assert (fl == 0).all() and "mgk_pcg_reduced" in solver.launch_log() and other in solver.launch_log()
 
 
 def test_many_isolated_vertices(torch, solver):

@@ -377,27 +377,48 @@ def test_calls_on_two_streams_do_not_wait_on_the_host(host):
     host.free(B)
 
 
-@pytest.mark.parametrize("way", ["short memory for the second side", "a launch behind it fails"])
-def test_packets_of_a_call_that_leaves_early_have_an_end(host, way):
+def test_packets_of_a_call_that_fails_have_an_end(host):
     """What it has enqueued by then writes or reads them."""
     X, Y = streaming(host), streaming(host, (0.0, 0.9), n=96)
     i = np.arange(24).repeat(12)
-    assert host.gram(X, stream=6) == 0 and host.pairs(X, X, i, i, stream=5) == 0, host.error()
-    if way == "a launch behind it fails":
-        assert host.pairs(X, Y, i, i, stream=5) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
-        host.lib.stub_fail(b"pcg_sep")
-    else:
-        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use()))
+    assert host.gram(X, stream=6) == 0 and host.pairs(X, Y, i, i, stream=5) == 0, host.error()
+    host.hold(5)
+    host.lib.stub_fail(b"pcg_sep")
+    assert host.pairs(X, Y, i, i, stream=5) == 3 and "mgk_pcg_sep" in host.launch_log()
+    host.lib.stub_fail(b"")
+    assert host.gram(X, stream=6) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
+    assert host.violations() == ""
+
+
+def test_memory_of_the_packets(host):
+    """Reserved when graphs are loaded that may need them, for any two batches of a call; given back where memory is short, when
+    the pairs are solved without packets, by the call that may not allocate as well."""
+    i = np.arange(24).repeat(12)
+    both = ("mgk_pairs", "mgk_pairs_noalloc")
+    separable = lambda A, B, entry: host.pairs(A, B, i, i, entry=entry) == 0 and "mgk_pcg_sep" in host.launch_log()
+    before = host.lib.stub_in_use()
+    host.free(host.load(W.config1(12)))   # every pair fits the registers
+    assert host.lib.stub_in_use() - before < 1 << 20
+    Y = streaming(host)
+    X = streaming(host, n=92, count=48)   # more than twice as many nonzeros: a larger block
+    assert separable(Y, Y, "mgk_pairs")   # makes the list
+    before = host.count("malloc")
+    for entry in both:
+        for A, B in ((X, X), (X, Y), (Y, X), (Y, Y)):
+            assert separable(A, B, entry), host.launch_log()
+    assert host.count("malloc") == before
     try:
-        host.hold(5)
-        st = host.pairs(X, Y, i, i, stream=5)
-        assert (st, "mgk_pcg_sep" in host.launch_log()) == ((3, True) if way == "a launch behind it fails" else (0, False))
-        host.lib.stub_fail(b"")
-        host.lib.stub_set_limit(C.c_int64(-1))
-        assert host.gram(X, stream=6) == 0 and "mgk_pcg_sep" in host.launch_log(), host.error()
-        assert host.violations() == ""
+        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use() + 65536))
+        Z = host.load(W.config1(2000))   # needs the memory of the packets
+        host.lib.stub_set_limit(C.c_int64(host.lib.stub_in_use()))
+        for entry in both:
+            assert not separable(Y, Y, entry) and "mgk_pcg_small" in host.launch_log()
     finally:
         host.lib.stub_set_limit(C.c_int64(-1))
+    for entry in both:
+        assert separable(X, Y, entry)
+    assert host.violations() == ""
+    host.free(Z)
 
 
 def gram(host, batch, stream=0, counts=False):
