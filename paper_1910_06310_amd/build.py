@@ -30,7 +30,7 @@ DEVICE_SOURCES += [("mgk_pcg_sep.hip", "rk%d" % k, ["-DMGK_PCG_SEP_RK=%d" % k]) 
 DEVICE_SOURCES.append(("mgk_noalloc.hip", "all", []))
 HOST_SOURCES = ["mgk_host.cpp", "mgk_reorder.cpp"]
 
-# packed fp32 instructions are switched off on purpose for the test machines
+# packed fp32 instructions are switched off on purpose: some of their forms have given wrong results
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function"]

@@ -9,8 +9,8 @@
 //
 // Per nonzero and 64 results a stage does RK multiply-adds and 2 address additions, stage 2 also reads 4 RK bytes x 64 of
 // T.  Gram matrix of 160 scale-free graphs of 96 vertices (12 880 pairs, rank 5): 28.4 ms with the streaming solver (one
-// exponential per pair of nonzeros), 9.9 ms with this.  Bound by the vector ALUs (68 % of their slots, 46 % of the
-// instructions are multiply-adds, the others addresses, the vector part and the ends of tasks) and LDS (51 %, a third of it
+// exponential per pair of nonzeros), 9.9 ms with this.  Bound by the vector ALUs (67 % of their slots, 47 % of the
+// instructions are multiply-adds, the others addresses, the vector part and the ends of tasks) and LDS (52 %, 38 % of it
 // bank conflicts) in turn: stage 1 by the first, stage 2 by both.  Tried without gain: long tasks divided among wavefronts
 // (11.0 ms; the wavefronts of a SIMD even out by themselves), T with 64 words to a column so that 16-byte reads never
 // conflict (10.1 ms; the writes then do).

@@ -14,7 +14,8 @@
 // Gram of the first, 2.96e10 with the full system; 75 % of their slots at four wavefronts per SIMD, LDS 50 %) and by what
 // waits at five barriers an iteration.  What holds fewer registers counts twice, for the fourth wavefront: offsets of two
 // rows of p in one scalar register, conditions and addresses formed in the iteration and not before it, rows of a
-// wavefront that follow each other in y so that their address is a scalar sum (together 56 -> 43 ms).
+// wavefront that follow each other in y so that their address is a scalar sum (together 56 -> 43 ms).  <8, 8, 2> and <2, 5, 1> spill
+// 32 and 10 vector registers to keep four and five wavefronts, the other shapes none.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
