@@ -1760,8 +1760,9 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
 // the host looks whether any pair still iterates, so that the GPU does not wait for that.  If any does,
 // they are formed once more when none does.
 mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, bool dense,
-                     const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, const MgkParams& prm) {
+                     const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, MgkParams prm) {
     const int n_pairs = (int)pairs.size();
+    prm.lean_vectors = 1;
     if (n_pairs == 0) return MGK_OK;
     if (!mgk_launch_sep_xmv) return fail(ctx, MGK_ESTATE, "the library was linked without the kernels of the separable product");
     int64_t total = 0;
@@ -1773,8 +1774,11 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         total += 5 * (int64_t)P.npad;
         max_npad = std::max(max_npad, P.npad);
         max_iter = std::max(max_iter, P.max_iter);
+        P.nsteps = A->graphs[(size_t)P.g1].voff;
+        P.atomic_rows = Bb->graphs[(size_t)P.g2].voff;
     }
-    const int vec_blocks = std::max(1, std::min(2048, (max_npad + 1023) / 1024));
+    // at most some thousand workgroups: each adds to the sums of its pair
+    const int vec_blocks = std::max(1, std::min(std::max(64, 8192 / n_pairs), (max_npad + MGK_LEAN_ELEMENTS - 1) / MGK_LEAN_ELEMENTS));
     // the graphs in use and where their features go, from A and from Bb (the same list when it is A)
     const int gi = L.per_packet == 8 ? 1 : 0, sides = Bb == A ? 1 : 2;
     const mgk_batch* bt[2] = {A, Bb};
@@ -1805,7 +1809,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     // the graph lists follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
     const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
-    const size_t feat_at = active_at + 64, copied = feat_at + feat.size() * sizeof(MgkSepAt);
+    const size_t env_at = active_at + MGK_COUNTERS_BYTES, feat_at = (env_at + sizeof(MgkVectorEnv) + 63) & ~(size_t)63, copied = feat_at + feat.size() * sizeof(MgkSepAt);
     const size_t used_at[2] = {copied, copied + used[0].size() * sizeof(MgkSepGraph)};
     const size_t rec_bytes = used_at[1] + used[1].size() * sizeof(MgkSepGraph);
     mgk_status st;
@@ -1846,6 +1850,8 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     memset(rec, 0, feat_at);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
     memcpy(rec + feat_at, feat.data(), feat.size() * sizeof(MgkSepAt));
+    const MgkVectorEnv env{A->dev.rowsum, Bb->dev.rowsum, A->dev.vlabel, Bb->dev.vlabel, prm.q, prm.h};
+    memcpy(rec + env_at, &env, sizeof env);
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
     MGK_HIP(ctx, hipMemcpyAsync(ctx->lpairs.p, rec, copied, hipMemcpyHostToDevice, stream));
     MgkLargePair* dpairs = (MgkLargePair*)ctx->lpairs.p;

@@ -139,6 +139,7 @@ struct MgkParams {
     int32_t label_dim;                     // attributes per edge label the kernel reads
     float attr_scale[MGK_MAX_LABEL_DIM];   // KRON_SE: sqrt(alpha_a log2(e)) per attribute; RCONV_SE: [0] for all parts
     float poly_c[MGK_POLY_MAX_COEF];       // POLY: sum_i poly_c[i] r^i on r = |e-e'| / rho < 1, zero-padded
+    int32_t lean_vectors;                  // global-memory solver: M is not kept (separable product)
 };
 
 #if defined(__HIPCC__)
@@ -547,7 +548,8 @@ struct MgkDenseTiles {
 };
 
 // One pair solved with global-memory vectors.  Vector v of the pair starts at
-// vec + v * npad floats: 0 x, 1 r, 2 p, 3 M, 4 y (also holds z).
+// vec + v * npad floats: 0 x, 1 r, 2 p, 3 M, 4 y (also holds z).  With the separable product 3 is
+// not used and 4 is a = M p - y.
 struct MgkLargePair {
     int32_t g1, g2;        // outer graph (batch X), inner graph (batch Y)
     int32_t n1, n2;
@@ -555,9 +557,20 @@ struct MgkLargePair {
     int32_t npad;          // n1 * n2 rounded up to 64
     int32_t out0, out1;
     int32_t max_iter;
-    int32_t nsteps;        // DPP steps for the inner row sums
-    int32_t atomic_rows;   // inner graph has rows longer than a lane group
+    int32_t nsteps;        // DPP steps for the inner row sums; with the separable product the outer graph's voff,
+    int32_t atomic_rows;   // inner graph has rows longer than a lane group; the inner graph's voff
 };
+
+// What the vector kernels of the separable product read beside the pairs: it follows the two counters of a call
+// (MGK_COUNTERS_BYTES from them), so that M is formed from the vertex data where it is used.
+struct MgkVectorEnv {
+    const float *rowsum1, *rowsum2;
+    const int32_t *vlabel1, *vlabel2;
+    float q, h;
+};
+#define MGK_LEAN_THREADS 512       // of its workgroups,
+#define MGK_LEAN_ELEMENTS 4096     // which take as many elements at a time
+#define MGK_COUNTERS_BYTES 64
 
 // Scalars of one pair in the global-memory solver.  The three sums of iteration `it` go
 // to slot it & 1 of their pair of accumulators; the other slot is cleared meanwhile, by a
@@ -566,6 +579,7 @@ struct MgkLargePair {
 //                     of the iteration before (rho of Alg. 1; the set-up puts it in rz[1])
 //   pa[it & 1]        p^T a of iteration it
 //   rr[it & 1]        r^T r after the update of iteration it
+// done: 0 while the pair iterates, else 1 + its last iteration (the separable product's solver; 1 in the other).
 struct MgkPairState {
     float rz[2], pa[2], rr[2];
     float bb;       // b^T b

@@ -54,6 +54,55 @@ __device__ __forceinline__ float row_shr(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x110 + DIST, 0xf, 0xf, true));
 }
 
+// ---- vectors with the separable product --------------------------------------------------------
+// Vertex data of a pair.  M_ii' = d_i d'_i' where the labels agree, else (d_i / h) d'_i', everywhere the same.
+// quad: M and d d' of the four elements from idx (a multiple of 4) on; elements past the last one repeat it.
+#define MGK_GLOBAL __attribute__((address_space(1)))   // pointers read from memory: without it their loads are flat ones
+struct VertexTerms {
+    const MGK_GLOBAL float *rowsum1, *rowsum2;
+    const MGK_GLOBAL int32_t *vlabel1, *vlabel2;
+    float q, h;
+    int n2, N;
+    __device__ __forceinline__ VertexTerms(const MgkVectorEnv& E, const MgkLargePair& P)   // voff1 = nsteps, voff2 = atomic_rows
+        : rowsum1((const MGK_GLOBAL float*)E.rowsum1 + P.nsteps), rowsum2((const MGK_GLOBAL float*)E.rowsum2 + P.atomic_rows),
+          vlabel1((const MGK_GLOBAL int32_t*)E.vlabel1 + P.nsteps), vlabel2((const MGK_GLOBAL int32_t*)E.vlabel2 + P.atomic_rows),
+          q(E.q), h(E.h), n2(P.n2), N(P.n1 * P.n2) {}
+    __device__ __forceinline__ void quad(int idx, float (&m)[4], float (&dd)[4]) const {
+        const int i = (int)((uint32_t)min(idx, N - 1) / (uint32_t)n2), ip = min(idx, N - 1) - i * n2;
+        if (ip + 3 < n2) {
+            const float d1 = rowsum1[i] + q, d1h = d1 / h;
+            const int lab = vlabel1[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float d2 = rowsum2[ip + e] + q;
+                dd[e] = d1 * d2;
+                m[e] = (lab == vlabel2[ip + e] ? d1 : d1h) * d2;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t at = (uint32_t)min(idx + e, N - 1);
+                const int a = (int)(at / (uint32_t)n2), b = (int)at - a * n2;
+                const float d1 = rowsum1[a] + q, d2 = rowsum2[b] + q;
+                dd[e] = d1 * d2;
+                m[e] = (vlabel1[a] == vlabel2[b] ? d1 : d1 / h) * d2;
+            }
+        }
+    }
+};
+__device__ __forceinline__ MgkVectorEnv env_of(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkParams& prm) {
+    return MgkVectorEnv{X.rowsum, Y.rowsum, X.vlabel, Y.vlabel, prm.q, prm.h};
+}
+// body(first element) for every four elements of the calling thread; two at a time, so that their loads are in flight together
+template <class F>
+__device__ __forceinline__ void each_quad(int end, const F& body) {
+    static_assert(MGK_LEAN_ELEMENTS == 8 * MGK_LEAN_THREADS, "two quads to a thread and step");
+    for (int at = (int)blockIdx.x * MGK_LEAN_ELEMENTS + 4 * (int)threadIdx.x; at < end; at += (int)gridDim.x * MGK_LEAN_ELEMENTS) {
+        body(at);
+        if (at + MGK_LEAN_ELEMENTS / 2 < end) body(at + MGK_LEAN_ELEMENTS / 2);
+    }
+}
+
 // ---- expansion of the octiles of a whole batch --------------------------------
 // idle lane slots of the inner lists: weight 0 (`aux` = its log2, -inf, or the weight
 // itself for the kernels that multiply by it), never the end of a run
@@ -126,6 +175,34 @@ __global__ __launch_bounds__(256) void mgk_large_init_kernel(MgkBatchDev X, MgkB
         s_rz = __builtin_fmaf(b, z0, s_rz);
         s_bb = __builtin_fmaf(b, b, s_bb);
     }
+    block_accumulate(s_rz, &state[blockIdx.y].rz[1], red);   // rho of iteration 0
+    block_accumulate(s_bb, &state[blockIdx.y].bb, red);
+}
+
+// The same where M is not kept: r and p alone (x is first written with the first new direction).
+__global__ __launch_bounds__(MGK_LEAN_THREADS) void mgk_lean_init_kernel(MgkBatchDev X, MgkBatchDev Y, const MgkLargePair* pairs,
+                                                                         MgkPairState* state, float* vec, MgkParams prm) {
+    __shared__ float red[MGK_LEAN_THREADS / 64];
+    const MgkLargePair P = pairs[blockIdx.y];
+    const VertexTerms V(env_of(X, Y, prm), P);
+    float* r = vec + P.vec + P.npad;
+    float* p = r + P.npad;
+    const float qq = prm.q * prm.q;
+    float s_rz = 0.f, s_bb = 0.f;
+    each_quad(V.N, [&](int idx) {
+        float m[4], dd[4], b[4], z[4];
+        V.quad(idx, m, dd);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool on = idx + e < V.N;
+            b[e] = on ? dd[e] * qq : 0.f;
+            z[e] = on ? b[e] / m[e] : 0.f;
+            s_rz = __builtin_fmaf(b[e], z[e], s_rz);
+            s_bb = __builtin_fmaf(b[e], b[e], s_bb);
+        }
+        *reinterpret_cast<float4*>(r + idx) = make_float4(b[0], b[1], b[2], b[3]);
+        *reinterpret_cast<float4*>(p + idx) = make_float4(z[0], z[1], z[2], z[3]);
+    });
     block_accumulate(s_rz, &state[blockIdx.y].rz[1], red);   // rho of iteration 0
     block_accumulate(s_bb, &state[blockIdx.y].bb, red);
 }
@@ -705,8 +782,6 @@ __global__ __launch_bounds__(256) void mgk_large_update_kernel(const MgkLargePai
 // Every workgroup takes the same decision from the sums of this iteration, which no one
 // writes during this kernel; one thread per pair records it (a workgroup that starts after
 // that and sees the pair marked done would have stopped anyway).
-// CLEAR: the next product adds to y or leaves parts of it alone.
-template <bool CLEAR>
 __global__ __launch_bounds__(256) void mgk_large_pupdate_kernel(const MgkLargePair* pairs,
                                                                 MgkPairState* state, float* vec, int it,
                                                                 float rtol2, int* n_active) {
@@ -731,8 +806,89 @@ __global__ __launch_bounds__(256) void mgk_large_pupdate_kernel(const MgkLargePa
     float* y = p + 2 * (int64_t)P.npad;
     for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
         p[idx] = __builtin_fmaf(beta, p[idx], y[idx]);
-        if (CLEAR) y[idx] = 0.f;
+        y[idx] = 0.f;
     }
+}
+
+// ---- the two kernels over the vectors with the separable product, which leaves a = M p - y and p^T a ----------
+// Bound by memory: 3 and 5 vectors are read or written where M kept, z stored for the second kernel and x updated
+// by the first took 8 and 3.  M^{-1} is the hardware's reciprocal (1 ulp: it only preconditions).  What a workgroup needs to know of its pair is loaded at once, before anything depends on it.
+// 64 pairs of 65 536 elements: 20 + 8 us with 11 vectors, 64 workgroups a pair; 11 + 12 with these, 16 workgroups a pair
+// (an empty launch takes 4).
+// alpha = rho / p^T a; r -= alpha a; rho' = r^T M^{-1} r; r^T r.  Clears the accumulator of the next iteration's p^T a.
+__global__ __launch_bounds__(MGK_LEAN_THREADS) void mgk_lean_update_kernel(const MgkLargePair* pairs, MgkPairState* state, float* vec,
+                                                                           const MgkVectorEnv* env, int it) {
+    __shared__ float red[MGK_LEAN_THREADS / 64];
+    MgkPairState& st = state[blockIdx.y];
+    const int done = st.done;
+    const float rho = st.rz[(it + 1) & 1], pa = st.pa[it & 1];
+    const MgkLargePair P = pairs[blockIdx.y];
+    const VertexTerms V(*env, P);
+    if (done) return;
+    const float alpha = rho / pa;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st.pa[(it + 1) & 1] = 0.f;
+    float* r = vec + P.vec + P.npad;
+    const float* a = r + 3 * (int64_t)P.npad;
+    float s_rz = 0.f, s_rr = 0.f;
+    each_quad(V.N, [&](int idx) {
+        const float4 r4 = *reinterpret_cast<const float4*>(r + idx), a4 = *reinterpret_cast<const float4*>(a + idx);
+        float m[4], dd[4], rv[4] = {r4.x, r4.y, r4.z, r4.w};
+        const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+        V.quad(idx, m, dd);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            rv[e] = idx + e < V.N ? __builtin_fmaf(-alpha, av[e], rv[e]) : 0.f;
+            s_rz = __builtin_fmaf(rv[e], rv[e] * __builtin_amdgcn_rcpf(m[e]), s_rz);
+            s_rr = __builtin_fmaf(rv[e], rv[e], s_rr);
+        }
+        *reinterpret_cast<float4*>(r + idx) = make_float4(rv[0], rv[1], rv[2], rv[3]);
+    });
+    block_accumulate(s_rz, &st.rz[it & 1], red);
+    block_accumulate(s_rr, &st.rr[it & 1], red);
+}
+
+// x += alpha p; stop test; beta = rho' / rho; p = M^{-1} r + beta p.  Every workgroup takes the same decision from
+// sums that no one writes during this kernel; one that finds the pair marked as stopped in this very
+// iteration still has its part of x to add.
+__global__ __launch_bounds__(MGK_LEAN_THREADS) void mgk_lean_pupdate_kernel(const MgkLargePair* pairs, MgkPairState* state, float* vec,
+                                                                            const MgkVectorEnv* env, int it, float rtol2, int* n_active) {
+    MgkPairState& st = state[blockIdx.y];
+    const int done = st.done;
+    const float rz = st.rz[it & 1], rho = st.rz[(it + 1) & 1], pa = st.pa[it & 1];
+    const bool converged = st.rr[it & 1] <= rtol2 * st.bb;
+    const MgkLargePair P = pairs[blockIdx.y];
+    const VertexTerms V(*env, P);
+    if (done != 0 && done != it + 1) return;
+    const bool stop = converged || it + 1 >= P.max_iter;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st.iters = it + 1;
+        if (stop) {
+            st.flag = converged ? 0 : 1;
+            st.done = it + 1;
+            atomicSub(n_active, 1);
+            atomicMax(n_active + 1, it + 1);   // most iterations any pair of the call needed
+        }
+    }
+    const float alpha = rho / pa, beta = rz / rho;
+    float* x = vec + P.vec;
+    const float* r = x + P.npad;
+    float* p = x + 2 * (int64_t)P.npad;
+    each_quad(V.N, [&](int idx) {
+        const float4 p4 = *reinterpret_cast<const float4*>(p + idx);
+        float pv[4] = {p4.x, p4.y, p4.z, p4.w};
+        float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (it > 0) x4 = *reinterpret_cast<const float4*>(x + idx);
+        *reinterpret_cast<float4*>(x + idx) = make_float4(__builtin_fmaf(alpha, pv[0], x4.x), __builtin_fmaf(alpha, pv[1], x4.y),
+                                                          __builtin_fmaf(alpha, pv[2], x4.z), __builtin_fmaf(alpha, pv[3], x4.w));
+        if (stop) return;
+        const float4 r4 = *reinterpret_cast<const float4*>(r + idx);
+        const float rv[4] = {r4.x, r4.y, r4.z, r4.w};
+        float m[4], dd[4];
+        V.quad(idx, m, dd);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pv[e] = __builtin_fmaf(beta, pv[e], rv[e] * __builtin_amdgcn_rcpf(m[e]));
+        *reinterpret_cast<float4*>(p + idx) = make_float4(pv[0], pv[1], pv[2], pv[3]);
+    });
 }
 
 // ---- K = p_x^T x; the nodal solution; how far x exceeds the Jacobi guess M^{-1} b ------------
@@ -764,7 +920,13 @@ __global__ __launch_bounds__(256) void mgk_large_final_kernel(MgkBatchDev X, Mgk
     // positive floats order like their bit patterns
     growth = fmaxf(growth, 0.f);
     for (int off = 32; off > 0; off >>= 1) growth = fmaxf(growth, __shfl_xor(growth, off));
-    if ((threadIdx.x & 63) == 0 && growth > 0.f) atomicMax(&state[blockIdx.y].growth, __float_as_int(growth));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = growth;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) growth = fmaxf(growth, red[w]);
+        if (growth > 0.f) atomicMax(&state[blockIdx.y].growth, __float_as_int(growth));
+    }
+    __syncthreads();
     block_accumulate(s, &state[blockIdx.y].kval, red);
 }
 
@@ -815,6 +977,29 @@ __global__ __launch_bounds__(256) void mgk_large_verify_residual_kernel(MgkBatch
         const float rho = b - __builtin_fmaf(m, x[idx], -y[idx]);
         s = __builtin_fmaf(rho, rho, s);
     }
+    block_accumulate(s, &st.rr[0], red);
+}
+
+// The same with a = M x - y in place of y, where M is not kept.
+__global__ __launch_bounds__(MGK_LEAN_THREADS) void mgk_lean_residual_kernel(MgkBatchDev X, MgkBatchDev Y, const MgkLargePair* pairs,
+                                                                             MgkPairState* state, const float* vec, MgkParams prm) {
+    __shared__ float red[MGK_LEAN_THREADS / 64];
+    MgkPairState& st = state[blockIdx.y];
+    if (!st.check) return;
+    const MgkLargePair P = pairs[blockIdx.y];
+    const VertexTerms V(env_of(X, Y, prm), P);
+    const float* a = vec + P.vec + 4 * (int64_t)P.npad;
+    const float qq = prm.q * prm.q;
+    float s = 0.f;
+    each_quad(V.N, [&](int idx) {
+        float m[4], dd[4];
+        V.quad(idx, m, dd);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float rho = idx + e < V.N ? dd[e] * qq - a[idx + e] : 0.f;
+            s = __builtin_fmaf(rho, rho, s);
+        }
+    });
     block_accumulate(s, &st.rr[0], red);
 }
 
@@ -898,8 +1083,11 @@ hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams& prm, f
 hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair* pairs,
                                  MgkPairState* state, float* vec, const MgkParams& prm, int n_pairs,
                                  int vec_blocks, hipStream_t stream) {
-    hipLaunchKernelGGL(mgk_large_init_kernel, dim3(vec_blocks, n_pairs), dim3(256), 0, stream, X, Y, pairs,
-                       state, vec, prm);
+    if (prm.lean_vectors)
+        hipLaunchKernelGGL(mgk_lean_init_kernel, dim3(vec_blocks, n_pairs), dim3(MGK_LEAN_THREADS), 0, stream, X, Y, pairs, state, vec, prm);
+    else
+        hipLaunchKernelGGL(mgk_large_init_kernel, dim3(vec_blocks, n_pairs), dim3(256), 0, stream, X, Y, pairs,
+                           state, vec, prm);
     return hipGetLastError();
 }
 
@@ -923,7 +1111,7 @@ hipError_t mgk_launch_large_iteration(const MgkBatchDev& X, const MgkBatchDev& Y
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mgk_large_dot_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
     hipLaunchKernelGGL(mgk_large_update_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
-    hipLaunchKernelGGL(mgk_large_pupdate_kernel<true>, gv, dim3(256), 0, stream, pairs, state, vec, it, prm.rtol2, n_active);
+    hipLaunchKernelGGL(mgk_large_pupdate_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it, prm.rtol2, n_active);
     return hipGetLastError();
 }
 
@@ -1009,8 +1197,9 @@ hipError_t mgk_launch_large_final(const MgkBatchDev& X, const MgkBatchDev& Y, co
 hipError_t mgk_launch_large_vectors(const MgkLargePair* pairs, MgkPairState* state, float* vec, int n_pairs, int vec_blocks,
                                     int it, float rtol2, int* n_active, hipStream_t stream) {
     const dim3 gv(vec_blocks, n_pairs);
-    hipLaunchKernelGGL(mgk_large_update_kernel, gv, dim3(256), 0, stream, pairs, state, vec, it);
-    hipLaunchKernelGGL(mgk_large_pupdate_kernel<false>, gv, dim3(256), 0, stream, pairs, state, vec, it, rtol2, n_active);
+    const MgkVectorEnv* env = reinterpret_cast<const MgkVectorEnv*>(reinterpret_cast<const char*>(n_active) + MGK_COUNTERS_BYTES);
+    hipLaunchKernelGGL(mgk_lean_update_kernel, gv, dim3(MGK_LEAN_THREADS), 0, stream, pairs, state, vec, env, it);
+    hipLaunchKernelGGL(mgk_lean_pupdate_kernel, gv, dim3(MGK_LEAN_THREADS), 0, stream, pairs, state, vec, env, it, rtol2, n_active);
     return hipGetLastError();
 }
 
@@ -1022,7 +1211,7 @@ hipError_t mgk_launch_large_outputs(const MgkBatchDev& X, const MgkBatchDev& Y, 
         hipLaunchKernelGGL(mgk_large_final_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, out, prm);
         hipLaunchKernelGGL(mgk_large_verify_prepare_kernel, gv, dim3(256), 0, stream, pairs, state, vec, 0);
     } else {
-        hipLaunchKernelGGL(mgk_large_verify_residual_kernel, gv, dim3(256), 0, stream, X, Y, pairs, state, vec, prm);
+        hipLaunchKernelGGL(mgk_lean_residual_kernel, gv, dim3(MGK_LEAN_THREADS), 0, stream, X, Y, pairs, state, vec, prm);
         hipLaunchKernelGGL(mgk_large_store_kernel, dim3((n_pairs + 63) / 64), dim3(64), 0, stream, pairs, state, n_pairs, out);
     }
     return hipGetLastError();

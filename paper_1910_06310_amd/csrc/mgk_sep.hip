@@ -11,7 +11,7 @@
 //  * mgk_sep_dense_kernel: well-filled graphs.  F_k and F'_k as dense matrices, both
 //    stages on the matrix cores (v_mfma_f32_32x32x2_f32), T_k of 32 outer rows in LDS.
 //
-// Both also form the workgroup's share of p^T (M p - y).
+// Both store a = M p - y and form the workgroup's share of p^T a.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -109,10 +109,18 @@ __device__ __forceinline__ void sep_block(int b, int blocks, int* pair, int* blk
     *blk = slot - q * blocks;
 }
 
-// One partial sum per wavefront into *dst (several wavefronts of the pair add to it).
-__device__ __forceinline__ void wave_accumulate(float v, float* dst, int lane) {
+// The workgroup's sum into *dst; red: a word of LDS per wavefront.  One addition per workgroup: those of a pair
+// to its sum come one after the other, about 70 ns each (64 pairs of n = 256 at density 0.01, 256 wavefronts a pair:
+// 51 us a product with one addition per wavefront, 34 with this).
+template <int NW>
+__device__ __forceinline__ void block_accumulate(float v, float* dst, float* red, int wave, int lane) {
     v = wave_sum(v);
-    if (lane == 0) atomicAdd(dst, v);
+    if (lane == 0) red[wave] = v;
+    __syncthreads();
+    if (wave == 0) {
+        const float s = wave_sum(lane < NW ? red[lane] : 0.f);
+        if (lane == 0) atomicAdd(dst, s);
+    }
 }
 
 // Clears the accumulators of r^T z and r^T r that the update of this iteration adds to (their
@@ -153,7 +161,7 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
     const MgkGraphDesc g1 = X.graphs[P.g1], g2 = Y.graphs[P.g2];
     const int n1 = P.n1, n2 = P.n2, rows = min(MGK_SEP_ROWS, n1 - i0);
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
-    float* y = vec + P.vec + 4 * (int64_t)P.npad;
+    float* a = vec + P.vec + 4 * (int64_t)P.npad;
     const int32_t* order1 = SX.deg_order + g1.voff;
     const int32_t* order2 = SY.deg_order + g2.voff;
     float* tile = lds + SLAB * n2;                    // y of the 16 rows, row stride n2 | 1
@@ -201,24 +209,23 @@ __global__ __launch_bounds__(MGK_SEP_THREADS) void mgk_sep_xmv_kernel(MgkBatchDe
         }
         __syncthreads();
     }
-    // ---- y and this workgroup's share of p^T a, a = M p - y
+    // ---- a = M p - y and this workgroup's share of p^T a
     float s_pa = 0.f;
-    const float inv_h = 1.0f / prm.h;
     for (int ii = wave; ii < rows; ii += NW) {
         const int i = __builtin_amdgcn_readfirstlane(order1[i0 + ii]);
-        const float d1 = X.rowsum[g1.voff + i] + prm.q;
+        const float d1 = X.rowsum[g1.voff + i] + prm.q, d1h = d1 / prm.h;
         const int lab1 = X.vlabel[g1.voff + i];
         for (int col = lane; col < n2; col += 64) {
             const float yv = tile[ii * tp + col];
             const int64_t at = (int64_t)i * n2 + col;
             const float pv = p[at];
-            const float dd = d1 * (Y.rowsum[g2.voff + col] + prm.q);
-            const float m = lab1 == Y.vlabel[g2.voff + col] ? dd : dd * inv_h;
-            s_pa = __builtin_fmaf(pv, __builtin_fmaf(m, pv, -yv), s_pa);
-            y[at] = yv;
+            const float m = (lab1 == Y.vlabel[g2.voff + col] ? d1 : d1h) * (Y.rowsum[g2.voff + col] + prm.q);
+            const float av = __builtin_fmaf(m, pv, -yv);
+            s_pa = __builtin_fmaf(pv, av, s_pa);
+            a[at] = av;
         }
     }
-    if (!check_only) wave_accumulate(s_pa, &st.pa[it & 1], lane);
+    if (!check_only) block_accumulate<NW>(s_pa, &st.pa[it & 1], lds, wave, lane);   // T is no longer read
 }
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -253,7 +260,7 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
     const float* F1 = SX.dense + F.f1 + i0;
     const float* F2 = SY.dense + F.f2;
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;
-    float* y = vec + P.vec + 4 * (int64_t)P.npad;
+    float* a = vec + P.vec + 4 * (int64_t)P.npad;
     const int tp = np2 + 1;
     const int r = lane & 31, half = lane >> 5;
     f32x16 yacc[NT][2];
@@ -350,9 +357,8 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
         }
         __syncthreads();
     }
-    // ---- y and this workgroup's share of p^T a, a = M p - y
+    // ---- a = M p - y and this workgroup's share of p^T a
     float s_pa = 0.f;
-    const float inv_h = 1.0f / prm.h;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -367,14 +373,15 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
                 if (i < n1) {
                     const int64_t at = (int64_t)i * n2 + col;
                     const float yv = yacc[t][b][v], pv = p[at];
-                    const float dd = (X.rowsum[g1.voff + i] + prm.q) * d2;
-                    const float m = lab2 == X.vlabel[g1.voff + i] ? dd : dd * inv_h;
-                    s_pa = __builtin_fmaf(pv, __builtin_fmaf(m, pv, -yv), s_pa);
-                    y[at] = yv;
+                    const float d1 = X.rowsum[g1.voff + i] + prm.q;
+                    const float m = (lab2 == X.vlabel[g1.voff + i] ? d1 : d1 / prm.h) * d2;
+                    const float av = __builtin_fmaf(m, pv, -yv);
+                    s_pa = __builtin_fmaf(pv, av, s_pa);
+                    a[at] = av;
                 }
             }
         }
-    if (!check_only) wave_accumulate(s_pa, &st.pa[it & 1], lane);
+    if (!check_only) block_accumulate<MGK_SEP_DENSE_THREADS / 64>(s_pa, &st.pa[it & 1], lds, wave, lane);   // T is no longer read
 }
 
 hipError_t set_lds(const void* kern, bool* configured) {
