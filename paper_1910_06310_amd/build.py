@@ -26,6 +26,7 @@ DEVICE_SOURCES += [("mgk_reduced.hip", "w%dc%d" % (w, c), ["-DMGK_REDUCED_WAVES=
 DEVICE_SOURCES += [("mgk_sell.hip", "w%d" % w, ["-DMGK_SELL_WAVES=%d" % w]) for w in (8, 4, 16)]
 DEVICE_SOURCES.append(("mgk_large.hip", "all", []))
 DEVICE_SOURCES.append(("mgk_sep.hip", "all", []))
+DEVICE_SOURCES.append(("mgk_sep_wide.hip", "all", []))
 DEVICE_SOURCES += [("mgk_pcg_sep.hip", "rk%d" % k, ["-DMGK_PCG_SEP_RK=%d" % k]) for k in (5, 7, 6, 4, 1)]
 DEVICE_SOURCES.append(("mgk_noalloc.hip", "all", []))
 HOST_SOURCES = ["mgk_host.cpp", "mgk_reorder.cpp"]

@@ -272,6 +272,8 @@ struct KeptBasis {
     int kernel = -1;
     float param = 0.f, lo = 0.f, hi = 0.f;
     MgkSepBasis basis{};
+    bool has_wide = false;
+    MgkWideBasis wide{};   // for graphs of many vertices
 };
 
 struct mgk_ctx {
@@ -302,6 +304,7 @@ struct mgk_ctx {
     DevBuf dense_tiles[2][3];           // dense 8x8 expansions (weight, label, log2 weight)
     DevBuf sep_packets[2];              // packets of the separable product, batch X / batch Y
     DevBuf sep_dense[2];                // dense F_k of the graphs of batch X / batch Y
+    DevBuf wide_outer, wide_inner;      // features of graphs of many vertices as outer and as inner ones
     DevBuf onchip_packets;              // packets of the separable product on chip, of both batches of a call
     std::vector<void*> old_packets;     // smaller ones before it, half as large each: kernels may still read them
     hipEvent_t onchip_packets_end = nullptr;   // of the last kernel that reads them
@@ -1208,7 +1211,7 @@ mgk_status build_job_list(mgk_ctx* ctx, JobPlan& plan, JobList& out,
 // Gives back what the context keeps for later calls: features and blocks of freed batches.
 bool release_spare(mgk_ctx* ctx) {
     bool any = false;
-    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets})
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->wide_outer, &ctx->wide_inner, &ctx->onchip_packets})
         if (b->p && !ctx->features_in_use) {
             (void)hipFree(b->p);   // waits for the work that reads it
             *b = DevBuf{};
@@ -1359,6 +1362,75 @@ MgkSepBasis sep_basis_se(double center, double R, double t) {
     return S;
 }
 
+// The same in powers of the second label (see MgkWideBasis).  kappa_e / g at a Chebyshev node s has in s' the Chebyshev
+// coefficients c_n(s); those below the rank, as powers of s', are the functions, each even or odd.  The exponent of g is
+// free: a little below t / 2 balances what the sum leaves at the middle and at the ends of the range, one to three terms fewer than t / 2
+// itself (t = 0.5, 1.3, 2.3, 5: 6, 9, 10, 13 terms where that needs 7, 10, 12, 16).  35 to 60 us, when pairs first may take it.
+MgkWideBasis wide_basis_se(double center, double R, double t) {
+    static const SepTables T;
+    constexpr int H = T.H, D = T.D, E = T.E, MaxR = MGK_SEP_MAX_RANK;
+    MgkWideBasis S{};
+    S.outer.center = center;
+    S.outer.inv_r = R > 0.0 ? 1.0 / R : 0.0;
+    S.half_t = 0.5 * t * (t <= 1.0 ? 0.95 : t <= 2.5 ? 0.9 : 0.85);
+    if (!(t <= 8.0)) return S;
+    double c[H][D] = {};
+    for (int i = 0; i < H; ++i)
+        for (int j = 0; j < H; ++j) {
+            const double s = T.node[i], r = T.node[j], weight = S.half_t * r * r;
+            const double u = std::exp(weight - 0.5 * t * (s - r) * (s - r)), v = std::exp(weight - 0.5 * t * (s + r) * (s + r));
+            for (int m = 0; m < D; m += 2) {
+                c[i][m] += (u + v) * T.cosm[j][m];
+                c[i][m + 1] += (u - v) * T.cosm[j][m + 1];
+            }
+        }
+    double inner[E][MaxR];   // g(s') s'^l
+    for (int e = 0; e < E; ++e) {
+        inner[e][0] = std::exp(-S.half_t * T.grid[e] * T.grid[e]);
+        for (int l = 1; l < MaxR; ++l) inner[e][l] = inner[e][l - 1] * T.grid[e];
+    }
+    int first = 1;   // exp(t s s') has c_r of about 2 (t / 2)^r / r!
+    for (double left = t; first < MaxR && left > (t <= 2.0 ? 32.0 : t <= 4.0 ? 1000.0 : 4000.0) * MGK_SEP_TOLERANCE; left *= 0.5 * t / ++first) {}
+    for (int rank = first; rank <= MaxR; ++rank) {
+        std::fill(std::begin(S.outer.coef), std::end(S.outer.coef), 0.0);
+        double feat[E][MaxR];
+        for (int l = 0; l < rank; ++l) {
+            const int odd = l & 1;
+            double cheb[D] = {}, poly[D] = {};
+            for (int i = 0; i < H; ++i) {
+                double v = 0.0;
+                for (int n = l; n < rank; n += 2) v += c[i][n] * T.mono[n][l];
+                for (int m = odd; m < D; m += 2) cheb[m] += 2.0 * v * T.cosm[i][m];
+            }
+            int last = D - 1;   // what is left above is rounding noise, which the monomials would amplify
+            while (last > 0 && std::fabs(cheb[last]) < 1e-12) --last;
+            for (int m = odd; m <= last; m += 2)
+                for (int j = odd; j <= m; j += 2) poly[j] += cheb[m] * T.mono[m][j];
+            for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m) S.outer.coef[m * MaxR + l] = poly[2 * m + odd];
+            for (int e = 0; e < E; ++e) {
+                double v = 0.0;
+                for (int m = MGK_SEP_MAX_TERMS - 1; m >= 0; --m) v = v * T.grid[e] * T.grid[e] + S.outer.coef[m * MaxR + l];
+                feat[e][l] = odd ? v * T.grid[e] : v;
+            }
+        }
+        double err = 0.0;
+        for (int e = 0; e < E; ++e)
+            for (int f = 0; f < E; ++f) {
+                double v = std::exp(-0.5 * t * (T.grid[e] - T.grid[f]) * (T.grid[e] - T.grid[f]));
+                for (int l = 0; l < rank; ++l) v -= feat[e][l] * inner[f][l];
+                err = std::max(err, std::fabs(v));
+            }
+        if (err > MGK_SEP_TOLERANCE) continue;
+        S.outer.rank = rank;
+        S.outer.terms = 1;
+        for (int m = 0; m < MGK_SEP_MAX_TERMS; ++m)
+            for (int l = 0; l < rank; ++l)
+                if (S.outer.coef[m * MaxR + l] != 0.0) S.outer.terms = m + 1;
+        return S;
+    }
+    return S;
+}
+
 // Separable form of the edge kernel on the label range [lo, hi] (see MgkSepBasis).  rank 0: the kernel
 // has none (short length scale against the range, or a kernel that is not smooth).  The last few are kept
 // with the context: batches compared in turn have ranges of their own.
@@ -1372,7 +1444,11 @@ const MgkSepBasis* make_basis(mgk_ctx* ctx, float lo, float hi) {
     const float param = ctx->edge_kernel == MGK_EK_SE ? ctx->length_scale : ctx->ke_const;
     KeptBasis& b = ctx->bases[ctx->next_basis];
     ctx->next_basis = (ctx->next_basis + 1) % (int)(sizeof(ctx->bases) / sizeof(ctx->bases[0]));
-    b = KeptBasis{ctx->edge_kernel, param, lo, hi, MgkSepBasis{}};
+    b = KeptBasis{};
+    b.kernel = ctx->edge_kernel;
+    b.param = param;
+    b.lo = lo;
+    b.hi = hi;
     if (ctx->edge_kernel == MGK_EK_CONST) {
         b.basis.rank = b.basis.terms = 1;
         b.basis.coef[0] = std::sqrt((double)ctx->ke_const);
@@ -1397,9 +1473,29 @@ MgkSepLayout sep_layout(int rank, int n2) {
     return L;
 }
 
+// The same for graphs of many vertices: one pass with 8 rows where two workgroups share a compute unit with it (contact graphs of 256 and 300
+// vertices, rank 9, 64 pairs: one pass 993 and 1584 us, two 1080 and 1429), else the fewest features executed, then the
+// fewest passes, with 8 rows where two workgroups share a compute unit; rows = 0 where no division fits.
+MgkWideLayout wide_layout(int rank, int n2) {
+    MgkWideLayout best{};
+    static const struct { int hi, lo; } kForms[] = {{4, 4}, {5, 5}, {6, 6}, {8, 8}, {9, 9}, {10, 10}, {4, 5}};   // single passes by size
+    for (const auto& f : kForms) {
+        MgkWideLayout L{8, f.hi, f.lo, 1 + std::max(0, (rank - f.hi + f.lo - 1) / f.lo)};
+        if (rank <= 0 || (f.hi > 6 && L.passes > 1) || (f.hi != f.lo && L.passes == 1)) continue;
+        if (!mgk_wide_two(L, n2)) {
+            L.rows = 4;
+            if (f.hi > 6 || L.rows * n2 > MGK_WIDE_MAX_ELEMENTS || mgk_wide_lds_bytes(L, n2) > MGK_LDS_LIMIT_BYTES) continue;
+        }
+        if (L.passes == 1 && L.rows == 8) return L;
+        const int all = f.hi + (L.passes - 1) * f.lo, least = best.hi + (best.passes - 1) * best.lo;
+        if (best.rows == 0 || all < least || (all == least && L.passes < best.passes)) best = L;
+    }
+    return best;
+}
+
 // Product of the global-memory solver for one pair.
-enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPaths = 4 };
-bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
+enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPathWide = 4, kPaths = 5 };
+bool is_sep(int path) { return path == kPathSep || path == kPathSepDense || path == kPathWide; }
 
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot run.
 // Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01
@@ -1413,6 +1509,12 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 // and 1.05 times its share), 32 rows (dense: 60 multiply-adds per clk).  The direct products expand the lists
 // of both batches, whichever graphs the pairs have: 0.4 ns per nonzero or 1.2 per octile, over about 12
 // iterations.
+// The form for graphs of many vertices does 33 multiply-adds per clk, 5 clk per element go to the vectors and 6000 to a
+// workgroup's trips to memory and barriers a pass, more than half of a small one's time; a workgroup alone takes 8 clk per element of T.
+// Us per call, row-staged or sparse / that, contact graphs of rank 9, 1, 4, 16 and 64 pairs: n = 132 225 / 244, 240 / 256, 328 / 313, 571 / 590;
+// 256 264 / 274, 371 / 280, 416 / 391, 1121 / 956; 300 282 / 314, 413 / 341, 564 / 580, 1367 / 1453; 480 388 / 372, 575 / 425, 986 / 982, 2928 / 2924;
+// 600 522 / 395, 1230 / 610, 3796 / 1379; 1000 1107 / 537, 3086 / 1081, 9940 / 3100; 2048 3347 / 1303, 11149 / 3821, 40577 / 13426.  Random graphs of
+// n = 256, rank 6, 1, 8 and 64 pairs: density 0.01 307 / 304, 514 / 465, 1360 / 1225; 0.12 326 / 253, 338 / 290, 1004 / 859.
 // Measured, us per call, row-staged / sparse / dense, rank 5, one batch of 128 graphs: 1 pair of n = 256
 // density 0.01 420 / 478 / 3432, 0.03 388 / 296 / 1686, 0.2 660 / 375 / 1011, 1 3467 / 872 / 893; 64 pairs
 // 2090 / 1842 / 7344, 1899 / 1094 / 3630, 13540 / 1311 / 2215, 189182 / 2944 / 1677.  8 graphs of n = 600
@@ -1423,21 +1525,42 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense; }
 // = 480 rank 11 516 / 704, 773 / 744, 1207 / 913, 2091 / 1403.  Constant kernel, 37 pairs of n = 146 to 162,
 // density 0.011: 711 / 798, whence its 10 clk per element of the sparse form where others have 8.
 struct LargeCost {
-    double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY};
+    double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
 };
 // Bytes the features of a graph take at most, whatever the layout.
 constexpr int64_t kMaxFeatureBytes = (int64_t)8 << 30;   // of the pairs solved together
+constexpr int64_t kWideMaxDegree = 32;   // mean; beyond, stage 1 was not measured, and from 50 on the dense form is near
+constexpr int kWideMinColumns = 24;      // an absent nonzero may point at column 9
+int64_t wide_feature_bytes(const mgk_batch* b, int32_t g) {   // as outer and as inner graph
+    constexpr int kPasses = MGK_SEP_MAX_RANK / 4;
+    return (int64_t)kPasses * 32 * b->graphs[(size_t)g].nnz + 4 * mgk_wide_inner_words(b->graphs[(size_t)g], kPasses);
+}
 int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
     const int64_t np = (b->graphs[(size_t)g].n + 63) & ~63;
     const auto& off = b->packet_off[rank == 1 ? 1 : 0];
     return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
 }
 
-// rank 0: no separable form.  L: sep_layout of the pair.  n_pairs: pairs of the call that may run beside this one.  n_tiles: octiles of
+// The form for graphs of many vertices, made once for every kept one.
+const MgkWideBasis& wide_basis(mgk_ctx* ctx, const MgkSepBasis* kept) {
+    for (KeptBasis& b : ctx->bases)
+        if (&b.basis == kept) {
+            if (!b.has_wide) {
+                const double R = kept->inv_r > 0.0 ? 1.0 / kept->inv_r : 0.0, l = (double)ctx->length_scale;
+                b.wide = wide_basis_se(kept->center, R, R * R / (l * l));
+                b.has_wide = true;
+            }
+            return b.wide;
+        }
+    static const MgkWideBasis none{};
+    return none;
+}
+
+// rank 0: no separable form.  L, W: the division of the pairs that are solved together.  n_pairs: pairs of the call that may run beside this one.  n_tiles: octiles of
 // both batches, or a third of the nonzeros where that is less.  Forming the features is left out: only the graphs of the pairs get them, which takes 1 % of
 // what the products of a pair take.
-LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb,
+LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const MgkWideLayout& W, const mgk_batch* A, int32_t ga, const mgk_batch* B, int32_t gb,
                      int64_t n_pairs, int64_t n_tiles) {
     constexpr double kUnits = 256;   // compute units
     const MgkGraphDesc &o = A->graphs[(size_t)ga], &i = B->graphs[(size_t)gb];
@@ -1450,7 +1573,7 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     }
     // Pairs small enough for the on-chip solver come here where the caller has lowered its limit; their
     // workgroups take less time than the launches of an iteration: throughput alone decides.
-    const double pairs = o.n * (int64_t)i.n <= MGK_SMALL_MAX_N ? INFINITY : (double)n_pairs;
+    const double pairs = o.n * (int64_t)i.n <= MGK_SMALL_MAX_N && ctx->onchip_limit < MGK_SMALL_MAX_N ? INFINITY : (double)n_pairs;
     const double N = (double)o.n * i.n, one_sided = (double)o.nnz * i.n + (double)o.n * i.nnz;
     const double entries = (double)o.nnz * i.nnz * (1.0 / 7.0) + 0.5 * (double)o.nnz * i.n;
     const double short_rows = std::isinf(pairs) ? 0.0 : std::min(0.35, 5.0 * o.n / std::max(o.nnz, 1));
@@ -1467,12 +1590,18 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
     if (may_sparse) {
         const double blocks = (o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
-        C.clk[kPathSep] = std::max(sparse + elements, workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
+        C.clk[kPathSep] = std::max(sparse + elements + (std::isinf(pairs) ? 0.0 : 6000.0 * blocks * (L.passes - 1)), workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
                                                                 45.0 * i.n * L.passes + 1.05 * sparse / blocks));
     }
     if (may_dense) {
         const double blocks = op / MGK_SEP_DENSE_ROWS;
         C.clk[kPathSepDense] = std::max(dense * (1.0 / 42.0), workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, dense / 60.0 / blocks));
+    }
+    if (W.rows > 0 && !std::isinf(pairs) && i.n >= kWideMinColumns && o.nnz <= kWideMaxDegree * (int64_t)o.n && i.nnz <= kWideMaxDegree * (int64_t)i.n) {
+        const double blocks = (o.n + W.rows - 1) / W.rows, products = (W.hi + (W.passes - 1) * W.lo) * one_sided * (1.0 / 33.0);
+        C.clk[kPathWide] = std::max(products + 5.0 * N + 6000.0 * blocks * W.passes,
+                                    workgroups(blocks, mgk_wide_lds_bytes(W, i.n), 2, 8.0 * W.rows * i.n + products / blocks));
+        if (C.clk[kPathWide] < C.clk[C.best]) C.best = kPathWide;
     }
     if (!may_sparse && !may_dense) return C;
     // of the two forms the one with the higher throughput
@@ -1759,8 +1888,9 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
 // new direction); the outputs are formed behind the iterations the last such call needed, before
 // the host looks whether any pair still iterates, so that the GPU does not wait for that.  If any does,
 // they are formed once more when none does.
-mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, bool dense,
-                     const MgkSepBasis& S, const MgkSepLayout& L, const MgkOutputs& out, hipStream_t stream, MgkParams prm) {
+mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, int path, const MgkSepBasis& S,
+                     const MgkSepLayout& L, const MgkWideBasis& SW, const MgkWideLayout& W, const MgkOutputs& out, hipStream_t stream, MgkParams prm) {
+    const bool dense = path == kPathSepDense, wide = path == kPathWide;
     const int n_pairs = (int)pairs.size();
     prm.lean_vectors = 1;
     if (n_pairs == 0) return MGK_OK;
@@ -1791,10 +1921,29 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         place[0][(size_t)P.g1] = 0;
         place[sides - 1][(size_t)P.g2] = 0;
     }
+    std::vector<MgkSepGraph> wide_inner;   // the graphs of used[sides - 1] as inner ones
+    std::vector<int64_t> wide_place;
+    int64_t wide_words = 0;
+    if (wide) wide_place.assign((size_t)Bb->n_graphs, 0);
     for (int k = 0; k < sides; ++k)
         for (int32_t g = 0; g < bt[k]->n_graphs; ++g) {
             int64_t& at = place[k][(size_t)g];
             if (at < 0) continue;
+            if (wide) {   // records of the nonzeros of outer graphs; steps of inner ones
+                const MgkGraphDesc& desc = bt[k]->graphs[(size_t)g];
+                max_n[k] = std::max(max_n[k], desc.n);
+                if (k == 0) {
+                    at = size[0];
+                    used[0].push_back({at, g, 0});
+                    size[0] += desc.nnz;
+                }
+                if (k == sides - 1) {
+                    wide_place[(size_t)g] = wide_words;
+                    wide_inner.push_back({wide_words, g, 0});
+                    wide_words += mgk_wide_inner_words(desc, W.passes);
+                }
+                continue;
+            }
             const int32_t n = bt[k]->graphs[(size_t)g].n;
             const int64_t np = (n + 63) & ~63, steps0 = bt[k]->packet_off[gi][(size_t)g], steps1 = bt[k]->packet_off[gi][(size_t)g + 1];
             at = dense ? size[k] * S.rank : size[k] - steps0;
@@ -1803,13 +1952,24 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
             max_n[k] = std::max(max_n[k], n);
         }
     std::vector<MgkSepAt> feat;
-    feat.reserve(pairs.size());
-    for (const MgkLargePair& P : pairs) feat.push_back({place[0][(size_t)P.g1], place[sides - 1][(size_t)P.g2]});
+    std::vector<MgkWidePair> wide_pairs;
+    feat.reserve(wide ? 0 : pairs.size());
+    wide_pairs.reserve(wide ? pairs.size() : 0);
+    for (const MgkLargePair& P : pairs) {
+        const MgkGraphDesc &o = A->graphs[(size_t)P.g1], &i = Bb->graphs[(size_t)P.g2];
+        if (wide)
+            wide_pairs.push_back({P.vec, place[0][(size_t)P.g1], wide_place[(size_t)P.g2], P.n1, P.n2, P.npad, o.nnz, o.voff, i.voff, mgk_wide_steps(i), {}});
+        else
+            feat.push_back({place[0][(size_t)P.g1], place[sides - 1][(size_t)P.g2]});
+    }
+    const void* const feat_data = wide ? (const void*)wide_pairs.data() : feat.data();
+    const size_t feat_bytes = wide ? wide_pairs.size() * sizeof(MgkWidePair) : feat.size() * sizeof(MgkSepAt);
+    if (wide) used[1] = std::move(wide_inner);
     // pair records, their zeroed states, the counters and the places of the features are one block and one copy;
     // the graph lists follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
     const size_t active_at = (state_at + (size_t)n_pairs * sizeof(MgkPairState) + 63) & ~(size_t)63;
-    const size_t env_at = active_at + MGK_COUNTERS_BYTES, feat_at = (env_at + sizeof(MgkVectorEnv) + 63) & ~(size_t)63, copied = feat_at + feat.size() * sizeof(MgkSepAt);
+    const size_t env_at = active_at + MGK_COUNTERS_BYTES, feat_at = (env_at + sizeof(MgkVectorEnv) + 63) & ~(size_t)63, copied = feat_at + feat_bytes;
     const size_t used_at[2] = {copied, copied + used[0].size() * sizeof(MgkSepGraph)};
     const size_t rec_bytes = used_at[1] + used[1].size() * sizeof(MgkSepGraph);
     mgk_status st;
@@ -1822,7 +1982,13 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     } in_use{ctx->features_in_use};
     ctx->features_in_use = true;
     MgkSepList sl[2] = {};
-    for (int k = 0; k < sides; ++k) {
+    MgkWideFeatures wf{};
+    if (wide) {
+        if ((st = ensure(ctx, ctx->wide_outer, std::max<size_t>(256, (size_t)W.passes * size[0] * 4 * mgk_wide_record(W.hi)))) != MGK_OK) return st;
+        if ((st = ensure(ctx, ctx->wide_inner, std::max<size_t>(256, (size_t)wide_words * 4))) != MGK_OK) return st;
+        wf = MgkWideFeatures{(const float*)ctx->wide_outer.p, (const float*)ctx->wide_inner.p, Bb->sep[0].deg_order, size[0]};
+    }
+    for (int k = 0; k < sides && !wide; ++k) {
         sl[k] = bt[k]->sep[gi];
         sl[k].total = dense ? 0 : (int32_t)size[k];
         DevBuf& buf = dense ? ctx->sep_dense[k] : ctx->sep_packets[k];
@@ -1835,12 +2001,21 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     Staging::Slot* slot;
     if ((st = staging_slot(ctx, rec_bytes, true, stream, &slot)) != MGK_OK) return st;
     char* rec = static_cast<char*>(slot->p);
-    for (int k = 0; k < sides; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
+    for (int k = 0; k < 2; ++k) memcpy(rec + used_at[k], used[k].data(), used[k].size() * sizeof(MgkSepGraph));
     staging_copied(slot, stream);
     // features of the graphs' nonzeros (they depend on the edge kernel's parameters).  The kernels do not wait
     // for the copy: they read the list of all graphs from the batch, or one of some of them from pinned memory
     // (for all 128 graphs of 64 pairs that took 15 us more).
-    for (int k = 0; k < sides; ++k) {
+    if (wide) {
+        const MgkSepGraph *outer = (const MgkSepGraph*)(rec + used_at[0]), *inner = (const MgkSepGraph*)(rec + used_at[1]);
+        hipError_t e = mgk_launch_wide_pack(A->dev, SW, W, A->sep[0].deg_order, outer, (int)used[0].size(), inner, A == Bb ? (int)used[1].size() : 0, max_n[0],
+                                            size[0], (float*)ctx->wide_outer.p, (float*)ctx->wide_inner.p, stream);
+        if (e == hipSuccess && A != Bb)
+            e = mgk_launch_wide_pack(Bb->dev, SW, W, Bb->sep[0].deg_order, outer, 0, inner, (int)used[1].size(), max_n[1], size[0],
+                                     (float*)ctx->wide_outer.p, (float*)ctx->wide_inner.p, stream);
+        if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));
+    }
+    for (int k = 0; k < sides && !wide; ++k) {
         const bool whole = (int32_t)used[k].size() == bt[k]->n_graphs;
         const MgkSepGraph* list = whole ? sl[k].whole : (const MgkSepGraph*)(rec + used_at[k]);
         hipError_t e = dense ? mgk_launch_sep_dense_pack(bt[k]->dev, S, list, (int)used[k].size(), max_n[k], (float*)ctx->sep_dense[k].p, stream)
@@ -1849,7 +2024,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     }
     memset(rec, 0, feat_at);
     memcpy(rec, pairs.data(), (size_t)n_pairs * sizeof(MgkLargePair));
-    memcpy(rec + feat_at, feat.data(), feat.size() * sizeof(MgkSepAt));
+    memcpy(rec + feat_at, feat_data, feat_bytes);
     const MgkVectorEnv env{A->dev.rowsum, Bb->dev.rowsum, A->dev.vlabel, Bb->dev.vlabel, prm.q, prm.h};
     memcpy(rec + env_at, &env, sizeof env);
     reinterpret_cast<int*>(rec + active_at)[0] = n_pairs;   // pairs still iterating, then the most iterations any needed
@@ -1861,7 +2036,8 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
 
     const MgkSepAt* dfeat = (const MgkSepAt*)((char*)ctx->lpairs.p + feat_at);
     auto product = [&](int it, bool check_only) {
-        return dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dfeat, dstate, vec, prm, n_pairs,
+        return wide  ? mgk_launch_wide_xmv(A->dev, Bb->dev, wf, W, (const MgkWidePair*)dfeat, dstate, vec, prm, n_pairs, max_n1, max_n2, it, check_only, stream)
+             : dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                             max_n1, max_n2, it, check_only, stream)
                      : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                           max_n1, max_n2, it, check_only, stream);
@@ -1896,7 +2072,8 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     ctx->idle = true;
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
     char form[64];
-    if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
+    if (wide) snprintf(form, sizeof form, "mgk_wide_xmv_kernel<%d, %d, %d> rank=%d passes=%d", W.rows, W.hi, W.lo, SW.outer.rank, W.passes);
+    else if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
     else snprintf(form, sizeof form, "mgk_sep_xmv_kernel<%d> rank=%d passes=%d", L.rk, S.rank, L.passes);
     log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)", form, n_pairs, it);
     return MGK_OK;
@@ -2135,29 +2312,45 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             choices.push_back(c);
         }
     const int64_t n_tiles = std::min(X->n_tiles, X->nnz / 3) + (X == Y ? 0 : std::min(Y->n_tiles, Y->nnz / 3));
-    auto costs_at = [&](int rank) {
+    auto costs_at = [&](int rank, int wide_rank) {
         std::vector<LargeCost> costs;
         costs.reserve(choices.size());
+        // pairs that are solved together have the division of the largest one that has any
         MgkSepLayout L{};
-        int32_t n2 = -1;   // of L: pairs often come with the same
+        MgkWideLayout W{};
+        int32_t sep_n2 = 0, wide_n2 = 0;
         for (const Choice& c : choices) {
-            if (rank > 0 && c.sep.n2 != n2) L = sep_layout(rank, n2 = c.sep.n2);
-            costs.push_back(large_cost(ctx, rank, L, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size(),
-                                       n_tiles));
+            if (rank > 0 && c.sep.n2 > sep_n2)
+                if (const MgkSepLayout one = sep_layout(rank, c.sep.n2); one.rk > 0) {
+                    L = one;
+                    sep_n2 = c.sep.n2;
+                }
+            if (wide_rank > 0 && c.sep.n2 > wide_n2)
+                if (const MgkWideLayout one = wide_layout(wide_rank, c.sep.n2); one.rows > 0) {
+                    W = one;
+                    wide_n2 = c.sep.n2;
+                }
         }
+        for (const Choice& c : choices)
+            costs.push_back(large_cost(ctx, rank, c.sep.n2 <= sep_n2 ? L : MgkSepLayout{}, c.sep.n2 <= wide_n2 ? W : MgkWideLayout{},
+                                       c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size(), n_tiles));
         return costs;
     };
+    const bool may_wide = may_sep && ctx->edge_kernel == MGK_EK_SE && mgk_launch_wide_xmv &&
+                          std::any_of(choices.begin(), choices.end(), [](const Choice& c) { return c.sep.n2 >= kWideMinColumns; });
     const MgkSepBasis none{}, *basis = &none;
     std::vector<LargeCost> costs;
     if (may_sep) {
         const float lo = std::min(X->label_lo, Y->label_lo), hi = std::max(X->label_hi, Y->label_hi);
         basis = kept_basis(ctx, lo, hi);
         if (!basis) {   // it takes time: made if any pair would take the separable product at the lowest rank
-            costs = costs_at(1);
+            costs = costs_at(1, may_wide ? 1 : 0);
             basis = std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); }) ? make_basis(ctx, lo, hi) : &none;
         }
     }
-    costs = costs_at(basis->rank);
+    static const MgkWideBasis no_wide{};
+    const MgkWideBasis& wide = may_wide && basis->rank > 0 ? wide_basis(ctx, basis) : no_wide;
+    costs = costs_at(basis->rank, wide.outer.rank);
     const MgkSepBasis& S = *basis;
     merge_paths(costs);
     std::vector<const Choice*> lists[2][kPaths];
@@ -2181,7 +2374,8 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     for (int path = 0; path < kPaths; ++path)
         for (int swapped = 0; swapped < 2; ++swapped) {
             auto grid_threads = [&](int64_t n_pairs, int max_n1) {
-                return path == kPathSep ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS) * MGK_SEP_THREADS
+                return path == kPathWide ? mgk_wide_grid(n_pairs, max_n1, 4) * MGK_WIDE_THREADS
+                     : path == kPathSep ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS) * MGK_SEP_THREADS
                      : path == kPathSepDense ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS) * MGK_SEP_DENSE_THREADS : 0;
             };
             const std::vector<const Choice*>& all = lists[swapped][path];
@@ -2199,7 +2393,8 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                     const MgkLargePair& P = pair(last);
                     floats += 5 * (int64_t)P.npad;
                     if (is_sep(path))   // graphs that pairs share are counted for each
-                        features += feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
+                        features += path == kPathWide ? wide_feature_bytes(A, P.g1) + wide_feature_bytes(B, P.g2)
+                                    : feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
                     max_n1 = std::max(max_n1, P.n1);
                     if (last > first && (floats > kMaxScratchFloats || features > kMaxFeatureBytes ||
                                          grid_threads((int64_t)(last - first) + 1, max_n1) >= kMaxGridThreads))
@@ -2209,7 +2404,8 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                 }
                 mgk_status st;
                 if (is_sep(path)) {
-                    st = solve_sep(ctx, A, B, std::move(group), path == kPathSepDense, S, sep_layout(S.rank, max_n2), out, stream, prm);
+                    st = solve_sep(ctx, A, B, std::move(group), path, S, sep_layout(S.rank, max_n2), wide, wide_layout(wide.outer.rank, max_n2), out,
+                                   stream, prm);
                     if (st == MGK_ENOMEM) {   // the direct product needs less
                         std::vector<MgkLargePair> again[2][2];
                         for (size_t k = first; k < last; ++k) {
@@ -2229,7 +2425,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             }
         }
     constexpr size_t kKeptFeatureBytes = (size_t)1 << 30;   // of each buffer; forming more takes longer than allocating it
-    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1]})
+    for (DevBuf* b : {&ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->wide_outer, &ctx->wide_inner})
         if (b->cap > kKeptFeatureBytes) {
             (void)hipFree(b->p);
             *b = DevBuf{};
@@ -2271,7 +2467,7 @@ void mgk_destroy(mgk_ctx* ctx) {
     if (!ctx) return;
     if (ctx->pair_jobs.dev) (void)hipFree(ctx->pair_jobs.dev);
     for (DevBuf* b : {&ctx->exp_outer[0], &ctx->exp_outer[1], &ctx->exp_inner[0], &ctx->exp_inner[1],
-                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->onchip_packets, &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
+                      &ctx->sep_packets[0], &ctx->sep_packets[1], &ctx->sep_dense[0], &ctx->sep_dense[1], &ctx->wide_outer, &ctx->wide_inner, &ctx->onchip_packets, &ctx->vec, &ctx->lpairs, &ctx->lstate, &ctx->lactive, &ctx->nodal_off, &ctx->diag,
                       &ctx->dense_tiles[0][0], &ctx->dense_tiles[0][1], &ctx->dense_tiles[0][2],
                       &ctx->dense_tiles[1][0], &ctx->dense_tiles[1][1], &ctx->dense_tiles[1][2]})
         if (b->p) (void)hipFree(b->p);

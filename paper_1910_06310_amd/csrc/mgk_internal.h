@@ -475,6 +475,60 @@ struct MgkSepAt {
     int64_t f1, f2;
 };
 
+// ---- the same for graphs of many vertices (mgk_sep_wide.hip) ---------------------
+// kappa_e(e, e') = g(e') sum_{l < rank} psi_l(e) s'^l: psi_l is function l of `outer`, g(e') = exp(-half_t s'^2), s' = (e' - center) / R.
+// kappa_e / g has a Chebyshev sum in s' of `rank` terms, whose powers of s' have the psi_l as coefficients.  Tolerance as above.
+struct MgkWideBasis {
+    MgkSepBasis outer;
+    double half_t;
+};
+// Pass 0 takes the `hi` highest functions, every other one the next `lo`; 4 and 4, 4 and 5 or 5 and 5, or all (4 to 6, 8 to 10) in one
+// pass.  rows: outer rows of a workgroup, 4 or 8.
+struct MgkWideLayout {
+    int32_t rows, hi, lo, passes;
+};
+#define MGK_WIDE_THREADS 1024
+#define MGK_WIDE_MAX_N 2048
+#define MGK_WIDE_MAX_ELEMENTS 8192   // rows by columns of a workgroup: eight results to a thread, or four where two workgroups share a CU
+static inline MGK_HD int32_t mgk_wide_first(const MgkWideLayout& L, int32_t q) { return (L.passes - 1 - q) * L.lo; }
+static inline MGK_HD int64_t mgk_wide_lds_bytes(const MgkWideLayout& L, int32_t n2) {
+    const int64_t t = (int64_t)n2 * L.rows * 4 * (L.passes > 1 && L.lo > L.hi ? L.lo : L.hi), y = 4 * ((int64_t)L.rows * (n2 | 1) + MGK_WIDE_THREADS / 64);
+    return t > y ? t : y;
+}
+static inline MGK_HD constexpr int32_t mgk_wide_record(int32_t hi) { return hi > 6 ? 12 : 8; }   // words of a nonzero of an outer graph, per pass
+// Byte offset of the four first values of column j of T, row 0; row r's are at that ^ 16 r.
+static inline MGK_HD uint32_t mgk_wide_column(int32_t rows, uint32_t j) {
+    return rows == 4 ? j * 64u + ((j >> 2) & 3u) * 16u : j * 128u + ((j >> 1) & 7u) * 16u;
+}
+// Words in front of the steps of an inner graph, and the most steps it can have (groups of 16 vertices by descending
+// degree, four nonzeros to a step: the largest of a group is at most the mean of the group before).
+static inline MGK_HD int32_t mgk_wide_head(int32_t n) { return ((n + 15) / 16 + 1 + 63) & ~63; }
+static inline MGK_HD int32_t mgk_wide_steps(const MgkGraphDesc& g) { return (g.n + 15) / 16 + (g.max_deg + 3) / 4 + g.nnz / 64 + 1; }
+static inline MGK_HD int64_t mgk_wide_inner_words(const MgkGraphDesc& g, int32_t passes) {
+    return mgk_wide_head(g.n) + (int64_t)passes * mgk_wide_steps(g) * 192;
+}
+static inline MGK_HD int64_t mgk_wide_grid(int64_t n_pairs, int32_t max_n1, int32_t rows) {
+    return n_pairs * ((((max_n1 + rows - 1) / rows + 7) >> 3) << 3);
+}
+// Two workgroups of this layout share a compute unit (the kernel for that has fewer registers).
+static inline MGK_HD bool mgk_wide_two(const MgkWideLayout& L, int32_t n2) {
+    return 2 * L.rows * n2 <= MGK_WIDE_MAX_ELEMENTS && 2 * mgk_wide_lds_bytes(L, n2) <= MGK_LDS_LIMIT_BYTES;
+}
+// What a workgroup needs to know of its pair, in one place: every further record to look up is one more trip to memory
+// before the work begins.
+struct alignas(64) MgkWidePair {
+    int64_t vec, f1, f2;   // vectors; first record of the outer graph; first word of the inner one
+    int32_t n1, n2, npad, nnz1, voff1, voff2, cap2, unused[3];
+};
+// Features of the graphs of a call: records of the outer graphs' nonzeros (mgk_wide_record words each, pass after pass of outer_total
+// records, a graph's from MgkWidePair::f1 on) and steps of the inner ones (from word MgkWidePair::f2 on).
+struct MgkWideFeatures {
+    const float* outer;
+    const float* inner;
+    const int32_t* deg_order2;
+    int64_t outer_total;
+};
+
 // ---- whole solve on chip with the separable product (mgk_pcg_sep.hip) ----------
 // Columns are the vertices of the smaller graph (n2 <= n1).  p and y with rows of n2 | 1 words, T of rb blocks of 16 rows, per-vertex data, first packet steps and reduction scratch.
 #define MGK_PCG_SEP_SLAB(rk) ((rk) == 1 ? 17 : 16 * (rk) + 4)   // words of one column of T for 16 rows

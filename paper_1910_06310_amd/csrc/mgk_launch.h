@@ -201,6 +201,14 @@ MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const
                                                      int rank, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec,
                                                      const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                      bool check_only, hipStream_t stream);
+// The same for sparse graphs of many vertices (mgk_sep_wide.hip): features of the graphs listed (memory the device can read;
+// MgkSepGraph::at a record or a word) as outer and as inner ones, and the product.
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_wide_pack(const MgkBatchDev& B, const MgkWideBasis& S, const MgkWideLayout& L, const int32_t* deg_order,
+                                                     const MgkSepGraph* outer_used, int n_outer, const MgkSepGraph* inner_used, int n_inner,
+                                                     int max_n, int64_t outer_total, float* outer, float* inner, hipStream_t stream);
+MGK_KERNELS_OPTIONAL hipError_t mgk_launch_wide_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkWideFeatures& F, const MgkWideLayout& L,
+                                                    const MgkWidePair* pairs, MgkPairState* state, float* vec, const MgkParams& prm, int n_pairs,
+                                                    int max_n1, int max_n2, int it, bool check_only, hipStream_t stream);
 // Whole solves on chip with that product (mgk_pcg_sep.hip) by `waves` wavefronts of ept elements a thread, T of rb
 // blocks of 16 rows at a time; packets (layout with slab_bytes 1) of all graphs of the two batches.
 #define MGK_DECL_PCG_SEP(RK)                                                                                                       \
