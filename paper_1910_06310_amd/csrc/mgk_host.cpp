@@ -1510,7 +1510,7 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense || path
 // of both batches, whichever graphs the pairs have: 0.4 ns per nonzero or 1.2 per octile, over about 12
 // iterations.
 // The form for graphs of many vertices does 33 multiply-adds per clk, 5 clk per element go to the vectors and 6000 to a
-// workgroup's trips to memory and barriers a pass, more than half of a small one's time; a workgroup alone takes 8 clk per element of T.
+// workgroup's trips to memory and barriers a pass, more than half of a small one's time; a workgroup alone takes 8 clk per element of T and 1000 per nonzero of a row.
 // Us per call, row-staged or sparse / that, contact graphs of rank 9, 1, 4, 16 and 64 pairs: n = 132 225 / 244, 240 / 256, 328 / 313, 571 / 590;
 // 256 264 / 274, 371 / 280, 416 / 391, 1121 / 956; 300 282 / 314, 413 / 341, 564 / 580, 1367 / 1453; 480 388 / 372, 575 / 425, 986 / 982, 2928 / 2924;
 // 600 522 / 395, 1230 / 610, 3796 / 1379; 1000 1107 / 537, 3086 / 1081, 9940 / 3100; 2048 3347 / 1303, 11149 / 3821, 40577 / 13426.  Random graphs of
@@ -1585,7 +1585,12 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
         return std::isinf(pairs) ? 0.0 : kUnits / pairs * std::max(1.0, 0.5 * (rounds + std::ceil(rounds))) * clk;
     };
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255, np = (i.n + 63) & ~63;
-    const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0), dense = rank * op * ip * ((double)o.n + i.n);
+    // With operands in 16-bit parts (64 columns to a workgroup, one to a compute unit) 145 multiply-adds per clk: 64 pairs of n = 256, density
+    // 0.2 sparse / dense 1179 / 985 us, 1 2944 / 819; 24 pairs of n = 230, 0.2 620 / 839, 0.5 1022 / 721; not
+    // measured for smaller pairs.
+    const bool in_parts = std::max(o.n, i.n) <= MGK_SEP_PARTS_MAX_N && N >= 20000.0;
+    const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0);
+    const double dense = rank * op * (in_parts ? np : ip) * ((double)o.n + i.n) * (in_parts ? 42.0 / 145.0 : 1.0);   // in products at the rate of the fp32 instructions
     const double elements = (ctx->edge_kernel == MGK_EK_CONST ? 10.0 : 8.0) * N;   // rank 1 stays a bound of higher ones
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
     if (may_sparse) {
@@ -1594,18 +1599,20 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
                                                                 45.0 * i.n * L.passes + 1.05 * sparse / blocks));
     }
     if (may_dense) {
-        const double blocks = op / MGK_SEP_DENSE_ROWS;
-        C.clk[kPathSepDense] = std::max(dense * (1.0 / 42.0), workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, dense / 60.0 / blocks));
+        const double blocks = in_parts ? np / 64 : op / MGK_SEP_DENSE_ROWS;
+        C.clk[kPathSepDense] = std::max(dense * (1.0 / 42.0) + (in_parts ? elements : 0.0), in_parts ? workgroups(blocks, MGK_SEP_PARTS_LDS, 1, rank * (15700.0 + 63.0 * ((double)o.n + i.n)))
+                                                                       : workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, dense / 60.0 / blocks));
     }
     if (W.rows > 0 && !std::isinf(pairs) && i.n >= kWideMinColumns && o.nnz <= kWideMaxDegree * (int64_t)o.n && i.nnz <= kWideMaxDegree * (int64_t)i.n) {
         const double blocks = (o.n + W.rows - 1) / W.rows, products = (W.hi + (W.passes - 1) * W.lo) * one_sided * (1.0 / 33.0);
         C.clk[kPathWide] = std::max(products + 5.0 * N + 6000.0 * blocks * W.passes,
-                                    workgroups(blocks, mgk_wide_lds_bytes(W, i.n), 2, 8.0 * W.rows * i.n + products / blocks));
+                                    workgroups(blocks, mgk_wide_lds_bytes(W, i.n), 2, 8.0 * W.rows * i.n + products / blocks + 1000.0 * W.passes * o.nnz / o.n));
         if (C.clk[kPathWide] < C.clk[C.best]) C.best = kPathWide;
     }
     if (!may_sparse && !may_dense) return C;
-    // of the two forms the one with the higher throughput
-    const int form = may_dense && (!may_sparse || dense * (1.0 / 42.0) < sparse + elements) ? kPathSepDense : kPathSep;
+    // of the two forms the one with the higher throughput, or, with a few pairs in 16-bit parts, the sooner end
+    const bool denser = in_parts ? C.clk[kPathSepDense] < C.clk[kPathSep] : dense * (1.0 / 42.0) < sparse + elements;
+    const int form = may_dense && (!may_sparse || denser) ? kPathSepDense : kPathSep;
     if (C.clk[form] < C.clk[C.best]) C.best = form;
     return C;
 }
@@ -1907,8 +1914,8 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         P.nsteps = A->graphs[(size_t)P.g1].voff;
         P.atomic_rows = Bb->graphs[(size_t)P.g2].voff;
     }
-    // at most some thousand workgroups: each adds to the sums of its pair
-    const int vec_blocks = std::max(1, std::min(std::max(64, 8192 / n_pairs), (max_npad + MGK_LEAN_ELEMENTS - 1) / MGK_LEAN_ELEMENTS));
+    // at most about a thousand workgroups: each adds to the sums of its pair
+    const int vec_blocks = std::max(1, std::min(std::max(16, 1024 / n_pairs), (max_npad + MGK_LEAN_ELEMENTS - 1) / MGK_LEAN_ELEMENTS));
     // the graphs in use and where their features go, from A and from Bb (the same list when it is A)
     const int gi = L.per_packet == 8 ? 1 : 0, sides = Bb == A ? 1 : 2;
     const mgk_batch* bt[2] = {A, Bb};

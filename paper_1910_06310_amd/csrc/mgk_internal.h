@@ -438,6 +438,8 @@ struct MgkSepLayout {
 #define MGK_SEP_DENSE_THREADS 256
 #define MGK_SEP_SLAB(rk) ((rk) == 1 ? 17 : 64 * (((rk) + 3) / 4) + 4)   // words per column of T
 #define MGK_SEP_DENSE_MAX_N 1024
+#define MGK_SEP_PARTS_MAX_N 256   // of the dense form with operands in three 16-bit parts
+#define MGK_SEP_PARTS_LDS 101376
 static inline MGK_HD int32_t mgk_sep_per_packet(int32_t rk) { return rk == 1 ? 8 : 2; }
 static inline MGK_HD int64_t mgk_sep_lds_bytes(int32_t rk, int32_t n2) {
     return 4 * ((int64_t)MGK_SEP_SLAB(rk) * n2 + (int64_t)MGK_SEP_ROWS * (n2 | 1));
@@ -622,8 +624,8 @@ struct MgkVectorEnv {
     const int32_t *vlabel1, *vlabel2;
     float q, h;
 };
-#define MGK_LEAN_THREADS 512       // of its workgroups,
-#define MGK_LEAN_ELEMENTS 4096     // which take as many elements at a time
+#define MGK_LEAN_THREADS 512       // of their workgroups,
+#define MGK_LEAN_ELEMENTS 2048     // which take as many elements at a time
 #define MGK_COUNTERS_BYTES 64
 
 // Scalars of one pair in the global-memory solver.  The three sums of iteration `it` go

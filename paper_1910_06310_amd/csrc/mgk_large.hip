@@ -93,13 +93,15 @@ struct VertexTerms {
 __device__ __forceinline__ MgkVectorEnv env_of(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkParams& prm) {
     return MgkVectorEnv{X.rowsum, Y.rowsum, X.vlabel, Y.vlabel, prm.q, prm.h};
 }
-// body(first element) for every four elements of the calling thread; two at a time, so that their loads are in flight together
+// body(first element) for every four elements of the calling thread; two at a time where there are as many, so that their loads
+// are in flight together
 template <class F>
 __device__ __forceinline__ void each_quad(int end, const F& body) {
-    static_assert(MGK_LEAN_ELEMENTS == 8 * MGK_LEAN_THREADS, "two quads to a thread and step");
-    for (int at = (int)blockIdx.x * MGK_LEAN_ELEMENTS + 4 * (int)threadIdx.x; at < end; at += (int)gridDim.x * MGK_LEAN_ELEMENTS) {
+    static_assert(MGK_LEAN_ELEMENTS == 4 * MGK_LEAN_THREADS, "four elements to a thread");
+    const int step = (int)gridDim.x * MGK_LEAN_ELEMENTS;
+    for (int at = (int)blockIdx.x * MGK_LEAN_ELEMENTS + 4 * (int)threadIdx.x; at < end; at += 2 * step) {
         body(at);
-        if (at + MGK_LEAN_ELEMENTS / 2 < end) body(at + MGK_LEAN_ELEMENTS / 2);
+        if (at + step < end) body(at + step);
     }
 }
 

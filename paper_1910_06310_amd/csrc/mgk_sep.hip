@@ -72,9 +72,13 @@ __global__ __launch_bounds__(256) void mgk_sep_pack_kernel(MgkBatchDev B, MgkSep
 }
 
 // Dense F_k of the graphs a call uses: F[at + (k np + i) np + j], np = n rounded up to 64,
-// zero where there is no edge.  One wavefront per (row, graph): clears the row, then fills it.
+// zero where there is no edge.  One wavefront per (row, graph): the rows of as many features as there is room for, up to 1024 columns of them,
+// are put together in LDS and written once (128 graphs of 256 vertices, density 0.2: 46 us, 80 cleared in memory and then filled; complete
+// ones 123 and 112).
 __global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, MgkSepBasis S, const MgkSepGraph* used, float* out) {
+    constexpr int kRoom = 2048, kWindow = 1024;   // words of a wavefront, columns at a time
     __shared__ double coef[MGK_SEP_MAX_TERMS * MGK_SEP_MAX_RANK];
+    __shared__ __align__(16) float room[4][kRoom];
     for (int k = threadIdx.x; k < S.terms * MGK_SEP_MAX_RANK; k += blockDim.x) coef[k] = S.coef[k];
     __syncthreads();
     const MgkSepGraph sg = used[blockIdx.y];
@@ -82,19 +86,30 @@ __global__ __launch_bounds__(256) void mgk_sep_dense_pack_kernel(MgkBatchDev B, 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int np = (g.n + 63) & ~63;
     float* F = out + sg.at * S.rank;
+    float* mine = room[wave];
     for (int row = blockIdx.x * 4 + wave; row < np; row += gridDim.x * 4) {
-        for (int k = 0; k < S.rank; ++k)
-            for (int c = lane; c < np; c += 64) F[((int64_t)k * np + row) * np + c] = 0.f;
-        if (row >= g.n) continue;
-        __threadfence_block();   // the stores below go to addresses other lanes have just cleared
-        __builtin_amdgcn_wave_barrier();
-        const int z0 = B.rowptr[g.voff + row];
-        const int z1 = row + 1 < g.n ? B.rowptr[g.voff + row + 1] : g.nnz;
-        for (int z = z0 + lane; z < z1; z += 64) {
-            const MgkEntry e = B.list_outer[g.zoff + z];
-            const float w = __uint_as_float(e.w & 0x7fffffffu);
-            for (int k = 0; k < S.rank; ++k)
-                F[((int64_t)k * np + row) * np + e.y] = w * sep_feature(S, coef, __uint_as_float(e.z), k);
+        const int z0 = row < g.n ? B.rowptr[g.voff + row] : 0;
+        const int z1 = row >= g.n ? 0 : row + 1 < g.n ? B.rowptr[g.voff + row + 1] : g.nnz;
+        for (int c0 = 0; c0 < np; c0 += kWindow) {
+            const int width = min(kWindow, np - c0), features = kRoom / width;
+            for (int k0 = 0; k0 < S.rank; k0 += features) {
+                const int k1 = min(S.rank, k0 + features);
+                for (int c = lane * 4; c < (k1 - k0) * width; c += 256) *reinterpret_cast<float4*>(mine + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int z = z0 + lane; z < z1; z += 64) {
+                    const MgkEntry e = B.list_outer[g.zoff + z];
+                    const int c = (int)e.y - c0;
+                    if (c < 0 || c >= width) continue;
+                    const float w = __uint_as_float(e.w & 0x7fffffffu);
+                    for (int k = k0; k < k1; ++k) mine[(k - k0) * width + c] = w * sep_feature(S, coef, __uint_as_float(e.z), k);
+                }
+                __threadfence_block();   // read by other lanes
+                __builtin_amdgcn_wave_barrier();
+                for (int k = k0; k < k1; ++k)
+                    for (int c = lane * 4; c < width; c += 256)
+                        *reinterpret_cast<float4*>(F + ((int64_t)k * np + row) * np + c0 + c) = *reinterpret_cast<const float4*>(mine + (k - k0) * width + c);
+                __threadfence_block();   // and written again
+                __builtin_amdgcn_wave_barrier();
+            }
         }
     }
 }
@@ -384,6 +399,200 @@ __global__ __launch_bounds__(MGK_SEP_DENSE_THREADS) void mgk_sep_dense_kernel(Mg
     if (!check_only) block_accumulate<MGK_SEP_DENSE_THREADS / 64>(s_pa, &st.pa[it & 1], lds, wave, lane);   // T is no longer read
 }
 
+// ---- the same for pairs of at most 256 by 256 vertices, with every operand as three bfloat16 parts -----------------
+// x = hi + mid + lo exactly (8 bits each), and the six products of parts above 2^-24 of a b on the 16-bit matrix cores, which do
+// 16 times as many multiply-adds a clk as the fp32 ones; sums are in fp32, those of hi hi apart from the rest, whose roundings
+// then are 2^-8 as large: error against fp64 as with the fp32 instructions or less (values 0.8e-7 and 0.7e-7 rms).
+// 64 pairs of complete 256-vertex graphs: 101 us a product, 236 with the fp32 matrix instructions; per call 1668 -> 819 us.  Bound by what the
+// matrix cores (half of their time) and the vector ALUs that take operands apart leave each other with two wavefronts to a SIMD.
+// One workgroup of eight wavefronts takes 64 inner columns.  Per k: F'_k of its columns to LDS, T_k = P F'_k
+// (a wavefront 32 rows), T_k to LDS in its place, y += F_k T_k.  P and F_k are read from L2 as they are and taken apart
+// in registers; every wavefront reads its rows only, what all share comes from LDS.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));   // rows of p begin anywhere
+
+constexpr int kPartsThreads = 512, kPartsStride = MGK_SEP_PARTS_MAX_N + 8;   // 16-bit words of a column's part in LDS: columns 4 banks apart
+constexpr int kPartsLds = 3 * 64 * kPartsStride * 2;
+static_assert(kPartsLds == MGK_SEP_PARTS_LDS && kPartsThreads / 64 * 32 == MGK_SEP_PARTS_MAX_N, "a wavefront per 32 rows");
+
+// Two numbers into three parts each.
+__device__ __forceinline__ void split2(float x, float y, uint32_t (&part)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+        part[k] = w;
+        x -= __uint_as_float(w << 16);
+        y -= __uint_as_float(w & 0xffff0000u);
+    }
+}
+struct Parts {   // eight numbers
+    u32x4 w[3];
+    __device__ __forceinline__ void set(const float (&x)[8]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t part[3];
+            split2(x[2 * q], x[2 * q + 1], part);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) w[k][q] = part[k];
+        }
+    }
+};
+__device__ __forceinline__ f32x16 mfma_parts(u32x4 a, u32x4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ void load8(float (&x)[8], const float* from) {
+    const f32x4_dword a = *reinterpret_cast<const f32x4_dword*>(from), b = *reinterpret_cast<const f32x4_dword*>(from + 4);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        x[q] = a[q];
+        x[4 + q] = b[q];
+    }
+}
+
+// 32 rows by 64 columns: hi[t] + rest[t] = rows (row: this lane's, of K numbers) times what is in LDS, K in steps of 16.  The
+// numbers of the last step that a row does not have are its last one.  Loads one step ahead (two: 107
+// instead of 101 us a product of 64 pairs of 256 by 256).
+__device__ __forceinline__ void product_parts(f32x16 (&hi)[2], f32x16 (&rest)[2], const float* row, int K, const uint16_t* lds, int r, int half) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) hi[t][v] = rest[t][v] = 0.f;
+    auto step = [&](const float (&x)[8], int k0) {
+        Parts a;
+        a.set(x);
+        const uint16_t* from = lds + r * kPartsStride + k0 + 8 * half;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            u32x4 b[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) b[k] = *reinterpret_cast<const u32x4*>(from + (k * 64 + 32 * t) * kPartsStride);
+            hi[t] = mfma_parts(a.w[0], b[0], hi[t]);
+            rest[t] = mfma_parts(a.w[0], b[1], rest[t]);
+            rest[t] = mfma_parts(a.w[1], b[0], rest[t]);
+            rest[t] = mfma_parts(a.w[1], b[1], rest[t]);
+            rest[t] = mfma_parts(a.w[0], b[2], rest[t]);
+            rest[t] = mfma_parts(a.w[2], b[0], rest[t]);
+        }
+    };
+    const int full = K & ~15;
+    if (full > 0) {
+        float next[8];
+        load8(next, row + 8 * half);
+        for (int k0 = 0; k0 < full; k0 += 16) {
+            float now[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) now[q] = next[q];
+            load8(next, row + min(k0 + 16, full - 16) + 8 * half);
+            step(now, k0);
+        }
+    }
+    if (full < K) {
+        float x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = row[min(full + 8 * half + q, K - 1)];
+        step(x, full);
+    }
+}
+
+__global__ __launch_bounds__(kPartsThreads, 2) void mgk_sep_dense_parts_kernel(MgkBatchDev X, MgkBatchDev Y, MgkSepList SX, MgkSepList SY, int rank,
+                                                                               const MgkLargePair* pairs, const MgkSepAt* feat,
+                                                                               MgkPairState* state, float* vec, MgkParams prm, int n_pairs,
+                                                                               int blocks, int it, int check_only) {
+    extern __shared__ __align__(16) float lds[];
+    uint16_t* const part = reinterpret_cast<uint16_t*>(lds);
+    int pair, blk;
+    sep_block(blockIdx.x, blocks, &pair, &blk);
+    if (pair >= n_pairs) return;
+    MgkPairState& st = state[pair];
+    if (check_only ? !st.check : st.done) return;
+    const MgkLargePair P = pairs[pair];
+    const MgkSepAt F = feat[pair];
+    const int c0 = blk * 64;
+    if (c0 >= P.n2) return;
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
+    const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
+    const int voff1 = P.nsteps, voff2 = P.atomic_rows;   // as the vector kernels have them
+    const float* F1 = SX.dense + F.f1;
+    const float* F2 = SY.dense + F.f2;
+    const float* p = vec + P.vec + 2 * (int64_t)P.npad;
+    float* a = vec + P.vec + 4 * (int64_t)P.npad;
+    const int i0 = wave * 32, K1 = (n1 + 15) & ~15, K2 = (n2 + 15) & ~15;
+    const bool on = i0 < n1;   // wave-uniform
+    f32x16 y[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) y[t][v] = 0.f;
+    for (int k = 0; k < rank; ++k) {
+        // ---- F'_k of the columns (symmetric: its rows), zero beyond n2
+        const float* B = F2 + ((int64_t)k * np2 + c0) * np2;
+        for (int e = tid; e < 64 * (K2 / 8); e += kPartsThreads) {
+            const int c = e / (K2 / 8), j = (e - c * (K2 / 8)) * 8;
+            float x[8];
+            load8(x, B + (int64_t)c * np2 + j);
+            Parts s;
+            s.set(x);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(part + (q * 64 + c) * kPartsStride + j) = s.w[q];
+        }
+        __syncthreads();
+        f32x16 hi[2], rest[2];
+        if (on) product_parts(hi, rest, p + (int64_t)min(i0 + r, n1 - 1) * n2, n2, part, r, half);
+        __syncthreads();
+        // ---- T_k: this lane has rows i0 + 8 (v / 4) + 4 half + v % 4 of a column
+        if (on) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t s0[3], s1[3];
+                    split2(hi[t][4 * q] + rest[t][4 * q], hi[t][4 * q + 1] + rest[t][4 * q + 1], s0);
+                    split2(hi[t][4 * q + 2] + rest[t][4 * q + 2], hi[t][4 * q + 3] + rest[t][4 * q + 3], s1);
+#pragma unroll
+                    for (int m = 0; m < 3; ++m)
+                        *reinterpret_cast<u32x2*>(part + (m * 64 + 32 * t + r) * kPartsStride + i0 + 8 * q + 4 * half) = u32x2{s0[m], s1[m]};
+                }
+        }
+        __syncthreads();
+        if (on) {   // columns of F_k beyond n1 are zero, rows of T_k there finite
+            product_parts(hi, rest, F1 + ((int64_t)k * np1 + min(i0 + r, np1 - 1)) * np1, K1, part, r, half);
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) y[t][v] += hi[t][v] + rest[t][v];
+        }
+        __syncthreads();
+    }
+    // ---- a = M p - y and this workgroup's share of p^T a
+    float s_pa = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int col = c0 + 32 * t + r;
+        if (col >= n2) continue;
+        const float d2 = Y.rowsum[voff2 + col] + prm.q;
+        const int lab2 = Y.vlabel[voff2 + col];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int i = i0 + 8 * (v >> 2) + 4 * half + (v & 3);
+            if (i < n1) {
+                const int64_t at = (int64_t)i * n2 + col;
+                const float pv = p[at], d1 = X.rowsum[voff1 + i] + prm.q;
+                const float m = (lab2 == X.vlabel[voff1 + i] ? d1 : d1 / prm.h) * d2;
+                const float av = __builtin_fmaf(m, pv, -y[t][v]);
+                s_pa = __builtin_fmaf(pv, av, s_pa);
+                a[at] = av;
+            }
+        }
+    }
+    if (!check_only) block_accumulate<kPartsThreads / 64>(s_pa, &st.pa[it & 1], lds, wave, lane);   // T is no longer read
+}
+
 hipError_t set_lds(const void* kern, bool* configured) {
     if (*configured) return hipSuccess;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, MGK_LDS_LIMIT_BYTES);
@@ -405,7 +614,7 @@ hipError_t mgk_launch_sep_pack(const MgkBatchDev& B, const MgkSepBasis& S, const
 
 hipError_t mgk_launch_sep_dense_pack(const MgkBatchDev& B, const MgkSepBasis& S, const MgkSepGraph* used, int n_used, int max_n,
                                      float* F, hipStream_t stream) {
-    const int gx = (max_n + 63) / 16;
+    const int gx = (max_n + 63) / 64 * 16;   // a row to a wavefront
     for (int g0 = 0; g0 < n_used; g0 += 65535)
         hipLaunchKernelGGL(mgk_sep_dense_pack_kernel, dim3(gx, n_used - g0 < 65535 ? n_used - g0 : 65535), dim3(256), 0,
                            stream, B, S, used + g0, F);
@@ -439,6 +648,14 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
                                 const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
+    if (max_n1 <= MGK_SEP_PARTS_MAX_N && max_n2 <= MGK_SEP_PARTS_MAX_N) {   // a wavefront per 32 rows
+        static bool configured = false;
+        const hipError_t e = set_lds(reinterpret_cast<const void*>(mgk_sep_dense_parts_kernel), &configured);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(mgk_sep_dense_parts_kernel, dim3((unsigned)mgk_sep_grid(n_pairs, max_n2, 64)), dim3(kPartsThreads), kPartsLds, stream, X, Y, SX,
+                           SY, rank, pairs, feat, state, vec, prm, n_pairs, (max_n2 + 63) / 64, it, check_only ? 1 : 0);
+        return hipGetLastError();
+    }
     const int blocks = (max_n1 + MGK_SEP_DENSE_ROWS - 1) / MGK_SEP_DENSE_ROWS;
     const dim3 grid((unsigned)mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS));
     const int np2 = (max_n2 + 63) & ~63;
