@@ -197,28 +197,23 @@ __global__ __launch_bounds__(W * 64) void mgk_pcg_regs(MgkBatchDev X, MgkBatchDe
             // labels with D attributes, from the attribute planes of the two lists
             const int D = prm.label_dim;
             const bool rconv = prm.edge_kernel == MGK_EK_RCONV_SE;
-            float e1a[MGK_MAX_LABEL_DIM], e2a[C][MGK_MAX_LABEL_DIM], f2[C];
-#pragma unroll
-            for (int a = 0; a < MGK_MAX_LABEL_DIM; ++a) {
-                const bool on = a < D;
-                const float raw1 = on && live1 ? X.attr_outer[(int64_t)a * X.nnz_total + g1.zoff + kbeg + lane] : 0.f;
-                e1a[a] = raw1 * prm.attr_scale[a];
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const int slot = c * 64 + lane;
-                    const float raw2 = on && slot < len2 ? Y.attr_inner[(int64_t)a * Y.lanes_total + g2.loff + slot] : 0.f;
-                    e2a[c][a] = raw2 * prm.attr_scale[a];
-                }
-            }
+            auto outer = [&](int a) {
+                // past the run: kappa_e underflows to exactly 0 (the R-convolution's weight is 0 there)
+                return live1 ? X.attr_outer[(int64_t)a * X.nnz_total + g1.zoff + kbeg + lane] * prm.attr_scale[a] : a == 0 && !rconv ? 1e18f : 0.f;
+            };
+            auto inner = [&](int a, int c) {
+                const int slot = c * 64 + lane;
+                return slot < len2 ? Y.attr_inner[(int64_t)a * Y.lanes_total + g2.loff + slot] * prm.attr_scale[a] : 0.f;
+            };
             if (rconv) {
                 const float inv = 1.0f / (float)(D * D);
+                float f2[C];
 #pragma unroll
                 for (int c = 0; c < C; ++c) f2[c] = w2r[c] * inv;   // 0 on idle slots
-                fill_attr<0, SMAX, SMAX, C, true>(kap, S, D, e2a, f2, e1a, w1);   // w1 is 0 past the run
+                fill_attr<SMAX, SMAX, C, true>(kap, S, 0, D, f2, w1, outer, inner);   // w1 is 0 past the run
             } else {
-                if (!live1) e1a[0] = 1e18f;   // past the run: kappa_e underflows to exactly 0
                 const float la = weighted ? __log2f(live1 ? w1 : 1.f) : 0.f;
-                fill_attr<0, SMAX, SMAX, C, false>(kap, S, D, e2a, l2, e1a, la);
+                fill_attr<SMAX, SMAX, C, false>(kap, S, 0, D, l2, la, outer, inner);
             }
         }
     }
