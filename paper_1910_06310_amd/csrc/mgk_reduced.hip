@@ -99,13 +99,13 @@ constexpr int STEP = 2;   // outer nonzeros per step of a product
 // offset 0, so the reads stay inside p).
 template <int K0, int C, int SMAX>
 __device__ __forceinline__ void gather_step(float (&pv)[STEP][C], const InnerLanes<C>& in,
-                                        const uint32_t (&s_poff)[SMAX / 2], const char* ldsbytes) {
+                                        const uint32_t (&s_poff)[SMAX / 2]) {
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
         const uint32_t two = s_poff[(K0 + u) / 2], po = u & 1 ? two >> 16 : two & 0xffffu;
 #pragma unroll
         for (int c = 0; c < C; ++c)
-            pv[u][c] = *reinterpret_cast<const float*>(ldsbytes + (po + in.jp[c]));
+            pv[u][c] = *(const __attribute__((address_space(3))) float*)(uintptr_t)(po + in.jp[c]);   // p is at address 0 of LDS
     }
 }
 
@@ -113,15 +113,15 @@ __device__ __forceinline__ void gather_step(float (&pv)[STEP][C], const InnerLan
 // end of an outer row (wave-uniform test) each inner row is summed over its lanes
 // (rows of at most 4 nonzeros: two shift-and-add steps) and the sum stored from the
 // last lane of the row.  row_at: byte address the row's sums go to; the rows of a wavefront follow each other.
-template <int K0, int SMAX, int C>
+template <int K0, int KBEG, int SMAX, int C>
 __device__ __forceinline__ void use_step(const float (&kap)[C][SMAX], const InnerLanes<C>& in,
-                                     float (&acc)[C], const float (&pv)[STEP][C], uint64_t rowmask,
+                                     float (&acc)[C], const float (&pv)[STEP][C], uint32_t rowmask,
                                      uint32_t& row_at, uint32_t row_bytes) {
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] = __builtin_fmaf(kap[c][K0 + u], pv[u][c], acc[c]);
-        if ((rowmask >> (K0 + u)) & 1ull) {
+        if ((rowmask >> (K0 - KBEG + u)) & 1u) {
             row_sums<C>(acc, in.m1, in.m2);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
@@ -138,34 +138,31 @@ __device__ __forceinline__ void use_step(const float (&kap)[C][SMAX], const Inne
 
 // Steps of a product from outer nonzero K0 (K0 < stop on entry): the reads of p for the next STEP
 // outer nonzeros are issued before those already read are used, so that the LDS
-// latency overlaps the arithmetic.
-template <int K0, int KEND, int SMAX, int C>
+// latency overlaps the arithmetic.  They are issued in the last step too (where there are registers for them): with a
+// condition around them the compiler made two copies of every step and did the first multiply-adds of both.
+template <int K0, int KBEG, int KEND, int SMAX, int C>
 __device__ __forceinline__ void xmv_steps(const float (&kap)[C][SMAX], const InnerLanes<C>& in,
                                           float (&acc)[C], const float (&pv)[STEP][C], int stop,
-                                          uint64_t rowmask, const uint32_t (&s_poff)[SMAX / 2],
-                                          uint32_t row_at, uint32_t row_bytes, const char* ldsbytes) {
-    if constexpr (K0 + STEP < KEND) {
-        if (K0 + STEP < stop) {   // wave-uniform
-            float nx[STEP][C];
-            gather_step<K0 + STEP, C, SMAX>(nx, in, s_poff, ldsbytes);
-            use_step<K0, SMAX, C>(kap, in, acc, pv, rowmask, row_at, row_bytes);
-            xmv_steps<K0 + STEP, KEND, SMAX, C>(kap, in, acc, nx, stop, rowmask, s_poff, row_at, row_bytes, ldsbytes);
-            return;
-        }
-    }
-    use_step<K0, SMAX, C>(kap, in, acc, pv, rowmask, row_at, row_bytes);
+                                          uint32_t rowmask, const uint32_t (&s_poff)[SMAX / 2],
+                                          uint32_t row_at, uint32_t row_bytes) {
+    float nx[STEP][C];
+    if constexpr (K0 + STEP < KEND) gather_step<K0 + STEP, C, SMAX>(nx, in, s_poff);
+    use_step<K0, KBEG, SMAX, C>(kap, in, acc, pv, rowmask, row_at, row_bytes);
+    if constexpr (K0 + STEP < KEND)
+        if (K0 + STEP < stop)   // wave-uniform
+            xmv_steps<K0 + STEP, KBEG, KEND, SMAX, C>(kap, in, acc, nx, stop, rowmask, s_poff, row_at, row_bytes);
 }
 
-// The rows of one colour: outer nonzeros KBEG .. stop-1.
+// The rows of one colour: outer nonzeros KBEG .. stop-1; bit k of rowmask: nonzero KBEG + k is the last of its row.
 template <int KBEG, int KEND, int SMAX, int C>
-__device__ __forceinline__ void xmv_rows(const float (&kap)[C][SMAX], const InnerLanes<C>& in, int stop, uint64_t rowmask,
-                                         const uint32_t (&s_poff)[SMAX / 2], uint32_t row_at, uint32_t row_bytes, const char* ldsbytes) {
+__device__ __forceinline__ void xmv_rows(const float (&kap)[C][SMAX], const InnerLanes<C>& in, int stop, uint32_t rowmask,
+                                         const uint32_t (&s_poff)[SMAX / 2], uint32_t row_at, uint32_t row_bytes) {
     if (KBEG >= stop) return;   // wave-uniform
     float acc[C], pv[STEP][C];
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[c] = 0.f;
-    gather_step<KBEG, C, SMAX>(pv, in, s_poff, ldsbytes);
-    xmv_steps<KBEG, KEND, SMAX, C>(kap, in, acc, pv, stop, rowmask, s_poff, row_at, row_bytes, ldsbytes);
+    gather_step<KBEG, C, SMAX>(pv, in, s_poff);
+    xmv_steps<KBEG, KBEG, KEND, SMAX, C>(kap, in, acc, pv, stop, rowmask, s_poff, row_at, row_bytes);
 }
 
 template <int W, int EPT, int C>
@@ -246,7 +243,7 @@ __global__ __launch_bounds__(W * 64, C == 1 ? (EPT <= 5 ? 5 : 3) : W * EPT <= 20
     const MgkEntry o = live1 ? X.list_outer[g1.zoff + (at1 & 0xffffu)] : MgkEntry{0u, 0u, 0u, 0u};
     const int col1 = (int)(at1 >> 16);   // position in red_order
     const uint32_t v_poff = 4u * (uint32_t)(col1 < nr ? col1 * n2 : NP + (col1 - nr) * n2);   // byte offset of row j of p
-    uint64_t rowmask = __ballot(live1 && (o.w >> 31) != 0u);
+    const uint64_t rowmask = __ballot(live1 && (o.w >> 31) != 0u);
     const float w1 = live1 ? __uint_as_float(o.w & 0x7fffffffu) : 0.f;
     // lanes past the run: a label so far away that kappa_e underflows to exactly 0
     const float e1s = live1 ? (__uint_as_float(o.z) - prm.e_shift) * prm.e_scale : 1e18f;
@@ -362,7 +359,8 @@ __global__ __launch_bounds__(W * 64, C == 1 ? (EPT <= 5 ? 5 : 3) : W * EPT <= 20
     int max_iter = prm.max_iter;
     if (max_iter <= 0) max_iter = min(2 * n1 * n2, 1000);
 
-    const char* ldsbytes = reinterpret_cast<const char*>(lds);
+    uint32_t black_ends = (uint32_t)rowmask, red_ends = (uint32_t)(rowmask >> SB);   // ends of rows of either colour
+    static_assert(SB <= 32 && SMAX - SB <= 32, "a word each");
     // byte offset of row j of p for each of the wave's outer nonzeros (entries past the run read row 0), in
     // scalar registers for the whole solve, two to a register
     uint32_t s_poff[SMAX / 2];
@@ -376,16 +374,16 @@ __global__ __launch_bounds__(W * 64, C == 1 ? (EPT <= 5 ? 5 : 3) : W * EPT <= 20
     while (true) {
         // what is derived from these (lane addresses of the first reads, one condition per nonzero) stays out of
         // registers between the iterations
-        asm volatile("" : "+s"(rowmask));
+        asm volatile("" : "+s"(black_ends), "+s"(red_ends));
 #pragma unroll
         for (int k = 0; k < SMAX / 2; ++k) asm volatile("" : "+s"(s_poff[k]));
         __syncthreads();   // the red part of p is complete (at first: all of it, and the cleared y)
         // ---- p_b = M_b^{-1} W_br p_r, entries from registers
-        if (it >= 0) xmv_rows<0, SB, SMAX, C>(kap, in, bstop, rowmask, s_poff, brow_at, row_bytes, ldsbytes);
+        if (it >= 0) xmv_rows<0, SB, SMAX, C>(kap, in, bstop, black_ends, s_poff, brow_at, row_bytes);
         __syncthreads();
         if (over) break;
         // ---- y = W_rr p_r + W_rb p_b
-        xmv_rows<SB, SMAX, SMAX, C>(kap, in, rstop, rowmask, s_poff, rrow_at, row_bytes, ldsbytes);
+        xmv_rows<SB, SMAX, SMAX, C>(kap, in, rstop, red_ends, s_poff, rrow_at, row_bytes);
         __syncthreads();
         float alpha = 0.f;
         if (it < 0) {
