@@ -114,6 +114,29 @@ def test_attribute_kernels_on_chip_and_in_global_memory(torch, solver, kind, wei
         np.testing.assert_allclose(got, ref, rtol=RTOL, err_msg=str(kw))
 
 
+@pytest.mark.parametrize("kind", ["kron_se", "rconv_se"])
+@pytest.mark.parametrize("dim", [1, 2, 4])
+def test_attribute_counts_in_registers(torch, solver, kind, dim):
+    """One pass over the entries per attribute: the first, one more, the most; both register-resident solvers, one column of the inner
+    graph per lane and two."""
+    wb, rng = molecules(61 + dim, 9, 9, 60, True)
+    prm = dataclasses.replace(wb.params, edge_kernel=kind, label_dim=dim,
+                              length_scales=tuple(np.linspace(0.3, 0.6, dim)) if kind == "kron_se" else (0.3,))
+    wa = W.with_label_attributes(wb, rng, dim, 0.2, prm)
+    pi, pj = W.gram_pairs(9)
+    ref = C.pairs(wa, pi, pj, tier=0)
+    got = pairs_on(torch, solver, wa, pi, pj)
+    assert "mgk_pcg_reduced" in solver.launch_log()
+    np.testing.assert_allclose(got, ref, rtol=RTOL)
+    solver.set_reduced_system(0)
+    try:
+        got = pairs_on(torch, solver, wa, pi, pj)
+        assert "mgk_pcg_regs" in solver.launch_log()
+    finally:
+        solver.set_reduced_system(1)
+    np.testing.assert_allclose(got, ref, rtol=RTOL)
+
+
 def test_attribute_kernel_needs_matching_batch(torch, solver):
     wb, rng = molecules(41, 3, 10, 20, False)
     solver.configure(wb.params)

@@ -116,6 +116,24 @@ def test_dense_form_at_edges_of_its_tiles(torch, solver, sizes, const, tiles):
     assert forms(log) == {("dense", tiles, 1 if const else 5, 1)}
 
 
+@pytest.mark.parametrize("sizes,length_scale,rank", [((145, 193, 255), 1.0, 5), ((256, 160, 225), 1.0, 5), ((249, 241, 32), 0.5, 7), ((255, 254, 17), 0.185, 15),
+                                                     ((257, 256), 1.0, 5)])
+def test_dense_form_on_parts_at_edges_of_its_tiles(torch, solver, sizes, length_scale, rank):
+    """Graphs of at most 256 vertices: columns that are no multiple of 16 or 64, rows of p at any alignment, the largest size and one
+    more, many features, small graphs and vertices without edges beside them, weights over eight decades, graphs of two batches."""
+    wx, wy = er(sum(sizes), sizes, 1.0), er(sum(sizes) + 1, sizes[::-1][:2], 1.0)
+    lone = er(9, (40,), 1.0)
+    keep = (lone.src < 9) & (lone.dst < 9)
+    lone.src, lone.dst, lone.weight, lone.edge_label = (a[keep] for a in (lone.src, lone.dst, lone.weight, lone.edge_label))
+    lone.edge_off = np.array([0, int(keep.sum())], lone.edge_off.dtype)
+    prm = dataclasses.replace(PARAMS, length_scale=length_scale)
+    wx, wy = W.concat_batches([wx, lone], prm, "x"), W.concat_batches([wy], prm, "y")
+    for wb in (wx, wy):
+        wb.weight = (wb.weight * 10.0 ** np.random.default_rng(7).uniform(-8, 0, len(wb.weight))).astype(np.float32)
+    *_, log = compare(torch, solver, wx, wy)
+    assert ("dense", rank) in {(f[0], f[2]) for f in forms(log)}   # the small graphs beside them may take the sparse form
+
+
 def test_dense_form_at_its_largest_size(torch, solver):
     """1024 columns: all four tiles of every wavefront, the most LDS.  One column more has no dense form."""
     wx, wy = er(11, (1030,), 0.2), er(12, (1024, 1025), 0.2)
