@@ -389,12 +389,11 @@ def main() -> int:
                       + cached_share * (flops_per_element_pair - 2) * zz)
     traffic = hbm_traffic(wl, args)
     cflops = counted_flops(wl, args)
-    ranks = {int(r) for r in re.findall(r"mgk_sep_\S+ rank=(\d+)", "\n".join(launches))}
+    ranks = {int(r) for r in re.findall(r"mgk_(?:sep|wide)_[^=]*rank=(\d+)", "\n".join(launches))}
     # on chip: features executed, those of a pass times the passes
     ranks |= {int(k) * int(p) for k, p in re.findall(r"mgk_pcg_sep<(\d+),[^>]*> passes=(\d+)", "\n".join(launches))}
-    separable = len(ranks) == 1 and all(f.startswith(("mgk_sep", "mgk_pcg_sep")) for f in families)
-    if ranks:   # the counters were taken with the direct products
-        traffic = cflops = None
+    separable = len(ranks) == 1 and all(f.startswith(("mgk_sep", "mgk_wide", "mgk_pcg_sep")) for f in families)
+    if ranks:
         executed_flops = executed_per_pair_iter = None
     if separable:   # multiply-adds of the two one-sided products of every term, nonzeros only
         n_vtx = wb.sizes().astype(np.float64)

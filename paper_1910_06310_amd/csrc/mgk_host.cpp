@@ -2082,7 +2082,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     if (wide) snprintf(form, sizeof form, "mgk_wide_xmv_kernel<%d, %d, %d> rank=%d passes=%d", W.rows, W.hi, W.lo, SW.outer.rank, W.passes);
     else if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
     else snprintf(form, sizeof form, "mgk_sep_xmv_kernel<%d> rank=%d passes=%d", L.rk, S.rank, L.passes);
-    log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_large_update / pupdate per iteration)", form, n_pairs, it);
+    log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_lean_update / pupdate per iteration)", form, n_pairs, it);
     return MGK_OK;
 }
 

@@ -10,8 +10,8 @@
 // Molecule-like graphs have 55 % black vertices, and the reduced system takes about 7 iterations to the same
 // residual where the full one takes 11: the products of an iteration cost the same (every entry once),
 // the vector part 45 %.  Gram matrix of 2000 graphs of 20 to 60 vertices (2 001 000 pairs): 62.7 ms with the full
-// system, 42.7 ms with this; of 100 graphs of 10 to 40: 133 and 85 us.  Bound by the vector instructions (1.96e10 per
-// Gram of the first, 2.96e10 with the full system; 75 % of their slots at four wavefronts per SIMD, LDS 50 %) and by what
+// system, 39.4 ms with this; of 100 graphs of 10 to 40: 133 and 80 us.  Bound by the vector instructions (2.0e10 per
+// Gram of the first, 2.96e10 with the full system; 86 % of their slots at four wavefronts per SIMD, LDS 55 %) and by what
 // waits at five barriers an iteration.  What holds fewer registers counts twice, for the fourth wavefront: offsets of two
 // rows of p in one scalar register, conditions and addresses formed in the iteration and not before it, rows of a
 // wavefront that follow each other in y so that their address is a scalar sum (together 56 -> 43 ms).  <8, 8, 2> spills
