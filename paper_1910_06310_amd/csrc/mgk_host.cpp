@@ -1928,29 +1928,24 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         place[0][(size_t)P.g1] = 0;
         place[sides - 1][(size_t)P.g2] = 0;
     }
-    std::vector<MgkSepGraph> wide_inner;   // the graphs of used[sides - 1] as inner ones
-    std::vector<int64_t> wide_place;
-    int64_t wide_words = 0;
-    if (wide) wide_place.assign((size_t)Bb->n_graphs, 0);
-    for (int k = 0; k < sides; ++k)
+    if (wide) {   // by the part a graph has in the pairs: records of the nonzeros of outer ones, steps of inner ones
+        if (max_n2 > MGK_WIDE_MAX_N) return fail(ctx, MGK_ESTATE, "an inner graph of %d vertices", max_n2);   // the limit is theirs alone
+        for (int k = 0; k < 2; ++k) place[k].assign((size_t)bt[k]->n_graphs, -1);
+        for (const MgkLargePair& P : pairs) place[0][(size_t)P.g1] = place[1][(size_t)P.g2] = 0;
+        for (int k = 0; k < 2; ++k)
+            for (int32_t g = 0; g < bt[k]->n_graphs; ++g) {
+                if (place[k][(size_t)g] < 0) continue;
+                const MgkGraphDesc& desc = bt[k]->graphs[(size_t)g];
+                place[k][(size_t)g] = size[k];
+                used[k].push_back({size[k], g, 0});
+                size[k] += k == 0 ? desc.nnz : mgk_wide_inner_words(desc, W.passes);
+                max_n[k] = std::max(max_n[k], desc.n);
+            }
+    }
+    for (int k = 0; k < sides && !wide; ++k)
         for (int32_t g = 0; g < bt[k]->n_graphs; ++g) {
             int64_t& at = place[k][(size_t)g];
             if (at < 0) continue;
-            if (wide) {   // records of the nonzeros of outer graphs; steps of inner ones
-                const MgkGraphDesc& desc = bt[k]->graphs[(size_t)g];
-                max_n[k] = std::max(max_n[k], desc.n);
-                if (k == 0) {
-                    at = size[0];
-                    used[0].push_back({at, g, 0});
-                    size[0] += desc.nnz;
-                }
-                if (k == sides - 1) {
-                    wide_place[(size_t)g] = wide_words;
-                    wide_inner.push_back({wide_words, g, 0});
-                    wide_words += mgk_wide_inner_words(desc, W.passes);
-                }
-                continue;
-            }
             const int32_t n = bt[k]->graphs[(size_t)g].n;
             const int64_t np = (n + 63) & ~63, steps0 = bt[k]->packet_off[gi][(size_t)g], steps1 = bt[k]->packet_off[gi][(size_t)g + 1];
             at = dense ? size[k] * S.rank : size[k] - steps0;
@@ -1965,13 +1960,12 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     for (const MgkLargePair& P : pairs) {
         const MgkGraphDesc &o = A->graphs[(size_t)P.g1], &i = Bb->graphs[(size_t)P.g2];
         if (wide)
-            wide_pairs.push_back({P.vec, place[0][(size_t)P.g1], wide_place[(size_t)P.g2], P.n1, P.n2, P.npad, o.nnz, o.voff, i.voff, mgk_wide_steps(i), {}});
+            wide_pairs.push_back({P.vec, place[0][(size_t)P.g1], place[1][(size_t)P.g2], P.n1, P.n2, P.npad, o.nnz, o.voff, i.voff, mgk_wide_steps(i), {}});
         else
             feat.push_back({place[0][(size_t)P.g1], place[sides - 1][(size_t)P.g2]});
     }
     const void* const feat_data = wide ? (const void*)wide_pairs.data() : feat.data();
     const size_t feat_bytes = wide ? wide_pairs.size() * sizeof(MgkWidePair) : feat.size() * sizeof(MgkSepAt);
-    if (wide) used[1] = std::move(wide_inner);
     // pair records, their zeroed states, the counters and the places of the features are one block and one copy;
     // the graph lists follow them in pinned memory
     const size_t state_at = ((size_t)n_pairs * sizeof(MgkLargePair) + 63) & ~(size_t)63;
@@ -1992,7 +1986,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     MgkWideFeatures wf{};
     if (wide) {
         if ((st = ensure(ctx, ctx->wide_outer, std::max<size_t>(256, (size_t)W.passes * size[0] * 4 * mgk_wide_record(W.hi)))) != MGK_OK) return st;
-        if ((st = ensure(ctx, ctx->wide_inner, std::max<size_t>(256, (size_t)wide_words * 4))) != MGK_OK) return st;
+        if ((st = ensure(ctx, ctx->wide_inner, std::max<size_t>(256, (size_t)size[1] * 4))) != MGK_OK) return st;
         wf = MgkWideFeatures{(const float*)ctx->wide_outer.p, (const float*)ctx->wide_inner.p, Bb->sep[0].deg_order, size[0]};
     }
     for (int k = 0; k < sides && !wide; ++k) {
@@ -2015,9 +2009,9 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     // (for all 128 graphs of 64 pairs that took 15 us more).
     if (wide) {
         const MgkSepGraph *outer = (const MgkSepGraph*)(rec + used_at[0]), *inner = (const MgkSepGraph*)(rec + used_at[1]);
-        hipError_t e = mgk_launch_wide_pack(A->dev, SW, W, A->sep[0].deg_order, outer, (int)used[0].size(), inner, A == Bb ? (int)used[1].size() : 0, max_n[0],
-                                            size[0], (float*)ctx->wide_outer.p, (float*)ctx->wide_inner.p, stream);
-        if (e == hipSuccess && A != Bb)
+        hipError_t e = mgk_launch_wide_pack(A->dev, SW, W, A->sep[0].deg_order, outer, (int)used[0].size(), inner, 0, max_n[0], size[0],
+                                            (float*)ctx->wide_outer.p, (float*)ctx->wide_inner.p, stream);
+        if (e == hipSuccess)
             e = mgk_launch_wide_pack(Bb->dev, SW, W, Bb->sep[0].deg_order, outer, 0, inner, (int)used[1].size(), max_n[1], size[0],
                                      (float*)ctx->wide_outer.p, (float*)ctx->wide_inner.p, stream);
         if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "feature launch failed: %s", hipGetErrorString(e));

@@ -393,6 +393,58 @@ hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, cons
     if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 31) / 32) * 256 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
     return launched("sep dense", s, &X, &Y, n);
 }
+#ifdef STUB_WIDE   // the library does without these kernels where they are not linked
+// Features of the form for graphs of many vertices where the last call put them: first record (outer graphs) or word (inner ones) -> graph
+// and end.
+struct WidePlace { int32_t graph; int64_t end; };
+typedef std::map<int64_t, WidePlace> WidePlaces;
+static WidePlaces wide_outer, wide_inner;
+static void wide_place(WidePlaces& places, int64_t at, int64_t size, int64_t total, int32_t graph) {
+    const auto next = places.lower_bound(at);
+    if (at < 0 || at + size > total || (next != places.end() && next->first < at + size) || (next != places.begin() && std::prev(next)->second.end > at))
+        violations.push_back("features of a graph overlap others or leave their buffer");
+    places[at] = {graph, at + size};
+}
+hipError_t mgk_launch_wide_pack(const MgkBatchDev& B, const MgkWideBasis&, const MgkWideLayout& L, const int32_t*, const MgkSepGraph* outer_used,
+                                int n_outer, const MgkSepGraph* inner_used, int n_inner, int max_n, int64_t outer_total, float* outer, float* inner,
+                                hipStream_t s) {
+    if (n_outer > 0) {
+        wide_outer.clear();
+        wide_inner.clear();
+    }
+    for (const float* to : {outer, inner}) check_write(to, s);
+    auto words = [](const float* to) { return (int64_t)(device_memory[block_of(to)] / 4); };
+    if (outer_total * L.passes * mgk_wide_record(L.hi) > words(outer)) violations.push_back("records of outer graphs leave their buffer");
+    for (int k = 0; k < n_outer + n_inner; ++k) {
+        const MgkSepGraph& u = k < n_outer ? outer_used[k] : inner_used[k - n_outer];
+        const MgkGraphDesc& g = B.graphs[u.graph];
+        if (g.n > max_n) violations.push_back("a graph of more vertices than the launch says");
+        if (k < n_outer) wide_place(wide_outer, u.at, g.nnz, outer_total, u.graph);
+        else if (g.n > MGK_WIDE_MAX_N) violations.push_back("an inner graph of more vertices than the kernel's table of groups");
+        else wide_place(wide_inner, u.at, mgk_wide_inner_words(g, L.passes), words(inner), u.graph);
+    }
+    if (n_outer > 0) launched("wide outer", s, &B, nullptr, n_outer);
+    return n_inner > 0 ? launched("wide inner", s, &B, nullptr, n_inner) : hipSuccess;
+}
+hipError_t mgk_launch_wide_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkWideFeatures& F, const MgkWideLayout& L, const MgkWidePair* pairs,
+                               MgkPairState*, float*, const MgkParams&, int n, int max_n1, int max_n2, int, bool, hipStream_t s) {
+    if (L.rows <= 0 || max_n2 > MGK_WIDE_MAX_ELEMENTS / L.rows || mgk_wide_lds_bytes(L, max_n2) > MGK_LDS_LIMIT_BYTES ||
+        mgk_wide_grid(n, max_n1, L.rows) * MGK_WIDE_THREADS >= (int64_t)1 << 32)
+        return hipErrorInvalidConfiguration;
+    for (int k = 0; k < n; ++k) {
+        const MgkWidePair& P = pairs[k];
+        const auto o = wide_outer.find(P.f1), i = wide_inner.find(P.f2);
+        if (o == wide_outer.end() || i == wide_inner.end()) { violations.push_back("a pair without features"); continue; }
+        const MgkGraphDesc &a = X.graphs[o->second.graph], &b = Y.graphs[i->second.graph];
+        if (P.n1 != a.n || P.n2 != b.n || P.n1 > max_n1 || P.n2 > max_n2 || P.nnz1 != a.nnz || P.voff1 != a.voff || P.voff2 != b.voff ||
+            P.cap2 != mgk_wide_steps(b) || P.npad < a.n * b.n)
+            violations.push_back("a pair with features of other graphs");
+    }
+    reads(s, F.outer);
+    reads(s, F.inner);
+    return launched("wide", s, &X, &Y, n);
+}
+#endif
 hipError_t mgk_launch_large_vectors(const MgkLargePair*, MgkPairState*, float*, int n, int, int it, float, int* n_active, hipStream_t s) {
     if (it + 1 >= converge_after) { n_active[0] = 0; n_active[1] = it + 1; }
     return launched("vectors", s, nullptr, nullptr, n);

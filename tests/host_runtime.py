@@ -12,11 +12,13 @@ CSRC = os.path.join(ROOT, "paper_1910_06310_amd", "csrc")
 BIG = 1 << 20   # floats of an output buffer
 
 
-def build(folder):
-    so = os.path.join(str(folder), "libmgk_hoststub.so")
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-pthread", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__=1",
-           "-I/opt/rocm/include", os.path.join(ROOT, "tests", "hip_stub", "hip_stub.cpp"),
-           os.path.join(CSRC, "mgk_host.cpp"), os.path.join(CSRC, "mgk_reorder.cpp"), "-o", so]
+def build(folder, wide=False):
+    """wide: with the separable product for graphs of many vertices, which takes pairs from the other forms."""
+    so = os.path.join(str(folder), "libmgk_hoststub%s.so" % ("_wide" if wide else ""))
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-pthread", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__=1"]
+    cmd += ["-DSTUB_WIDE"] if wide else []
+    cmd += ["-I/opt/rocm/include", os.path.join(ROOT, "tests", "hip_stub", "hip_stub.cpp"),
+            os.path.join(CSRC, "mgk_host.cpp"), os.path.join(CSRC, "mgk_reorder.cpp"), "-o", so]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert res.returncode == 0, res.stdout[-4000:]
     return so

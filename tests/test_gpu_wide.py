@@ -94,6 +94,16 @@ def test_graphs_larger_than_that_take_the_direct_product(torch, solver):
     assert compare(torch, solver, wb, wb, [0], [1]) == []
 
 
+@pytest.mark.parametrize("inner", [300, 2048])
+def test_outer_graphs_may_be_larger(torch, solver, inner):
+    """The limit is that of an inner graph: features as an inner one are formed for no other graph, also of one batch."""
+    rng = np.random.default_rng(inner)
+    wb = batch([ring(2100, 6, rng), ring(3000, 8, rng, hub=40), ring(9000, 6, rng, lone=30), ring(inner, 8, rng, hub=30)], 0.42)
+    assert len(compare(torch, solver, wb, wb, [0, 3, 2, 1], [3, 1, 3, 3])) == 1
+    forms = compare(torch, solver, wb, batch([ring(inner, 6, rng)], 0.42), [0, 1, 2, 1], [0, 0, 0, 0])
+    assert len(forms) == 1
+
+
 def test_small_graphs_beside_large_ones(torch, solver):
     """The smallest inner graph that the form takes, and one smaller, in a call with larger ones."""
     rng = np.random.default_rng(2)

@@ -30,6 +30,18 @@ def host(so):
         h.destroy()
 
 
+@pytest.fixture(scope="module")
+def so_wide(tmp_path_factory):
+    return host_runtime.build(tmp_path_factory.mktemp("host_runtime_wide"), wide=True)
+
+
+@pytest.fixture
+def host_wide(so_wide):
+    h = host_runtime.Host(so_wide)
+    yield h
+    h.destroy()
+
+
 def in_child(f, seconds=20):
     """Exit status of a forked child that calls f; None if it does not end."""
     pid = os.fork()
@@ -187,6 +199,23 @@ def test_features_are_formed_for_the_graphs_of_the_pairs(host, k, kernel):
     one = 192 * 192 * 4 if kernel == "sep dense" else 151 * k * 256   # a 192 x 192 matrix; a step of 64 words to two nonzeros of four rows
     assert host.lib.stub_in_use() - in_use < 3 * one + 60 * 5 * 4 * (151 * 151 + 63) + (1 << 20)
     host.free(B)
+
+
+@pytest.mark.parametrize("sizes,i,j,outer,inner", [
+    ((300, 2100, 3000, 9000), (1, 2, 3, 2), (0, 0, 0, 0), 3, 1),   # larger than an inner graph may be, as outer ones
+    ((2048, 2049, 24, 2047), (1, 0, 0), (0, 2, 3), 2, 3),          # the limit, both roles, the smallest
+    ((700, 650, 600, 2500), (0, 0, 3), (1, 2, 1), 2, 2)])
+def test_features_of_graphs_of_many_vertices_by_their_part_in_the_pairs(host_wide, sizes, i, j, outer, inner):
+    """Records for the outer graphs, steps for the inner ones, which alone have a limit: of one batch and of two."""
+    host = host_wide
+    host.set("edge_kernel_se", 0.42)
+    wb = graphs(*[ring(n, 3, np.linspace(0, 1, 3 * n)) for n in sizes])
+    X, Y = host.load(wb), host.load(wb)
+    for pair in ((X, X, j, i), (X, Y, i, j)):   # the larger graph second, too
+        host.lib.stub_clear_log()
+        assert host.pairs(*pair) == 0, host.error()
+        assert launched(host.log(), "wide") and launched(host.log(), "wide outer") == [outer] and launched(host.log(), "wide inner") == [inner]
+        assert host.violations() == ""
 
 
 def test_pairs_are_solved_without_features_where_memory_is_short(host):
