@@ -2074,6 +2074,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
     char form[64];
     if (wide) snprintf(form, sizeof form, "mgk_wide_xmv_kernel<%d, %d, %d> rank=%d passes=%d", W.rows, W.hi, W.lo, SW.outer.rank, W.passes);
+    else if (dense && mgk_sep_in_parts(max_n1, max_n2)) snprintf(form, sizeof form, "mgk_sep_dense_parts_kernel rank=%d", S.rank);
     else if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
     else snprintf(form, sizeof form, "mgk_sep_xmv_kernel<%d> rank=%d passes=%d", L.rk, S.rank, L.passes);
     log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_lean_update / pupdate per iteration)", form, n_pairs, it);

@@ -648,7 +648,7 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
                                 const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
-    if (max_n1 <= MGK_SEP_PARTS_MAX_N && max_n2 <= MGK_SEP_PARTS_MAX_N) {   // a wavefront per 32 rows
+    if (mgk_sep_in_parts(max_n1, max_n2)) {
         static bool configured = false;
         const hipError_t e = set_lds(reinterpret_cast<const void*>(mgk_sep_dense_parts_kernel), &configured);
         if (e != hipSuccess) return e;

@@ -73,9 +73,9 @@ def compare(torch, solver, wx, wy, const=False, onchip=0):
 
 
 def forms(log):
-    """Features per pass (sparse form) or tiles per wavefront (dense form), rank and passes of every launch."""
-    return {(k, int(a), int(r), int(p or 1)) for k, a, r, p in
-            re.findall(r"mgk_sep_(xmv|dense)_kernel<(\d+)> rank=(\d+)(?: passes=(\d+))?", log)}
+    """Features per pass (sparse form) or tiles per wavefront (dense form; 0 on parts), rank and passes of every launch."""
+    return {(k, int(a or 0), int(r), int(p or 1)) for k, a, r, p in
+            re.findall(r"mgk_sep_(xmv|dense|dense_parts)_kernel(?:<(\d+)>)? rank=(\d+)(?: passes=(\d+))?", log)}
 
 
 @pytest.mark.parametrize("length_scale,division", [(20.0, (4, 2, 1)), (4.0, (4, 3, 1)), (1.7, (4, 4, 1)), (1.0, (5, 5, 1)), (0.7, (6, 6, 1)),
@@ -107,13 +107,22 @@ def test_edges_of_tiles_against_the_oracle(torch, solver, sizes, density):
         assert forms(log) == (set() if density < 0.5 and max(sizes) < 100 else {("xmv", 5, 5, 1)})
 
 
-@pytest.mark.parametrize("sizes,const,tiles", [((145, 159, 161), False, 1), ((192, 193), False, 1), ((290,), False, 2), ((191, 225), True, 1),
+@pytest.mark.parametrize("sizes,const,tiles", [((145, 159, 161), False, 0), ((192, 193), False, 0), ((290,), False, 2), ((191, 225), True, 0),
                                                ((511, 449), False, 2), ((513,), False, 4), ((600, 577), True, 4)])
 def test_dense_form_at_edges_of_its_tiles(torch, solver, sizes, const, tiles):
-    """32 rows by 64 columns; one, two and four tiles of columns per wavefront."""
+    """32 rows by 64 columns; one, two and four tiles of columns per wavefront, or on parts."""
     wb = er(sum(sizes), sizes, 1.0 if max(sizes) < 500 else 0.6)
     *_, log = compare(torch, solver, wb, wb, const=const)
-    assert forms(log) == {("dense", tiles, 1 if const else 5, 1)}
+    assert forms(log) == {("dense" if tiles else "dense_parts", tiles, 1 if const else 5, 1)}
+
+
+@pytest.mark.parametrize("outer,inner,const", [((257, 289), (145, 159, 161), False), ((300,), (192, 193, 256), False), ((270, 261), (191, 225), True)])
+def test_dense_form_with_one_tile_per_wavefront(torch, solver, outer, inner, const):
+    """At most 256 columns of outer graphs that are too large for parts."""
+    wx, wy = er(sum(outer), outer, 1.0), er(sum(inner), inner, 1.0)
+    for a, b in ((wx, wy), (wy, wx)):
+        *_, log = compare(torch, solver, a, b, const=const)
+        assert forms(log) == {("dense", 1, 1 if const else 5, 1)}
 
 
 @pytest.mark.parametrize("sizes,length_scale,rank", [((145, 193, 255), 1.0, 5), ((256, 160, 225), 1.0, 5), ((249, 241, 32), 0.5, 7), ((255, 254, 17), 0.185, 15),
@@ -131,7 +140,9 @@ def test_dense_form_on_parts_at_edges_of_its_tiles(torch, solver, sizes, length_
     for wb in (wx, wy):
         wb.weight = (wb.weight * 10.0 ** np.random.default_rng(7).uniform(-8, 0, len(wb.weight))).astype(np.float32)
     *_, log = compare(torch, solver, wx, wy)
-    assert ("dense", rank) in {(f[0], f[2]) for f in forms(log)}   # the small graphs beside them may take the sparse form
+    kernels = {(f[0], f[2]) for f in forms(log)}   # the small graphs beside them may take the sparse form
+    assert ("dense" if max(sizes) > 256 else "dense_parts", rank) in kernels
+    assert (("dense_parts" if max(sizes) > 256 else "dense"), rank) not in kernels
 
 
 def test_dense_form_at_its_largest_size(torch, solver):

@@ -218,6 +218,15 @@ def test_features_of_graphs_of_many_vertices_by_their_part_in_the_pairs(host_wid
         assert host.violations() == ""
 
 
+@pytest.mark.parametrize("sizes,kernel", [((256, 251), "mgk_sep_dense_parts_kernel rank="), ((257, 256), "mgk_sep_dense_kernel<1> rank="),
+                                          ((513, 512), "mgk_sep_dense_kernel<2> rank=")])
+def test_launch_record_names_the_dense_kernel_that_runs(host, sizes, kernel):
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(*[ring(n, n // 2 - 1, np.linspace(0, 1, n * (n // 2 - 1))) for n in sizes]))
+    assert host.pairs(B, B, [0] * 16, [1] * 16) == 0, host.error()
+    assert launched(host.log(), "sep dense") and host.launch_log().startswith(kernel)
+
+
 def test_pairs_are_solved_without_features_where_memory_is_short(host):
     """Features of the separable product are an addition to what the direct product needs: neither forming
     them nor keeping them may make a call fail that the direct product can do."""
