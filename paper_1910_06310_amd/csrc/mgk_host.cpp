@@ -1494,8 +1494,9 @@ MgkWideLayout wide_layout(int rank, int n2) {
 }
 
 // Product of the global-memory solver for one pair.
-enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPathWide = 4, kPaths = 5 };
-bool is_sep(int path) { return path == kPathSep || path == kPathSepDense || path == kPathWide; }
+enum { kPathSparse = 0, kPathDenseTiles = 1, kPathSep = 2, kPathSepDense = 3, kPathWide = 4, kPathSepParts = 5, kPaths = 6 };
+bool is_sep_dense(int path) { return path == kPathSepDense || path == kPathSepParts; }   // the same features, two kernels
+bool is_sep(int path) { return path == kPathSep || path == kPathWide || is_sep_dense(path); }
 
 // Estimated clocks of one compute unit for one product of a pair on every path, infinite where it cannot run.
 // Throughput of a full chip, fitted to iterations of 64 pairs of random graphs (n = 128 to 256, densities 0.01
@@ -1525,8 +1526,9 @@ bool is_sep(int path) { return path == kPathSep || path == kPathSepDense || path
 // = 480 rank 11 516 / 704, 773 / 744, 1207 / 913, 2091 / 1403.  Constant kernel, 37 pairs of n = 146 to 162,
 // density 0.011: 711 / 798, whence its 10 clk per element of the sparse form where others have 8.
 struct LargeCost {
-    double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
+    double clk[kPaths] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};
     int best = kPathSparse;
+    struct { double share, workgroup; } fp32{}, parts{};   // of the dense forms: all compute units busy; one workgroup
 };
 // Bytes the features of a graph take at most, whatever the layout.
 constexpr int64_t kMaxFeatureBytes = (int64_t)8 << 30;   // of the pairs solved together
@@ -1585,23 +1587,28 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
         return std::isinf(pairs) ? 0.0 : kUnits / pairs * std::max(1.0, 0.5 * (rounds + std::ceil(rounds))) * clk;
     };
     const double op = (o.n + 31) & ~31, ip = (i.n + 255) & ~255, np = (i.n + 63) & ~63;
-    // With operands in 16-bit parts (64 columns to a workgroup, one to a compute unit) 145 multiply-adds per clk: 64 pairs of n = 256, density
-    // 0.2 sparse / dense 1179 / 985 us, 1 2944 / 819; 24 pairs of n = 230, 0.2 620 / 839, 0.5 1022 / 721; not
-    // measured for smaller pairs.
-    const bool in_parts = std::max(o.n, i.n) <= MGK_SEP_PARTS_MAX_N && N >= 20000.0;
-    const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0);
-    const double dense = rank * op * (in_parts ? np : ip) * ((double)o.n + i.n) * (in_parts ? 42.0 / 145.0 : 1.0);   // in products at the rate of the fp32 instructions
+    const double sparse = (double)L.rk * L.passes * one_sided * (1.0 / 20.0), dense = rank * op * ip * ((double)o.n + i.n);
     const double elements = (ctx->edge_kernel == MGK_EK_CONST ? 10.0 : 8.0) * N;   // rank 1 stays a bound of higher ones
     const bool may_sparse = L.rk > 0 && fits(false), may_dense = ip <= MGK_SEP_DENSE_MAX_N && fits(true);
+    // With operands in 16-bit parts (64 columns to a workgroup, one to a compute unit) 145 multiply-adds per clk.  Us per call, sparse / fp32 / parts: 64 pairs
+    // of n = 256, density 0.2 1179 / 2215 / 985, 1 2944 / 1668 / 819; n = 150, density 0.3, 0.5, 1 611 / 1041 / 592, 849 / 1051 / 609, 982 / 886 /
+    // 513; n = 130 548 / 1094 / 624, 668 / 944 / 555, 796 / 801 / 482; 8 pairs of n = 150 266 / 661 / 462, 347 / 666 / 461, 390 / 554 / 385.
+    // Never slower than the fp32 kernel, down to n = 40.
+    const bool in_parts = may_dense && mgk_sep_in_parts(o.n, i.n);
     if (may_sparse) {
         const double blocks = (o.n + MGK_SEP_ROWS - 1) / MGK_SEP_ROWS;
-        C.clk[kPathSep] = std::max(sparse + elements + (std::isinf(pairs) ? 0.0 : 6000.0 * blocks * (L.passes - 1)), workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS,
-                                                                45.0 * i.n * L.passes + 1.05 * sparse / blocks));
+        C.clk[kPathSep] = std::max(sparse + elements + (std::isinf(pairs) ? 0.0 : 6000.0 * blocks * (L.passes - 1)),
+                                   workgroups(blocks, mgk_sep_lds_bytes(L.rk, i.n), 2048 / MGK_SEP_THREADS, 45.0 * i.n * L.passes + 1.05 * sparse / blocks));
     }
     if (may_dense) {
-        const double blocks = in_parts ? np / 64 : op / MGK_SEP_DENSE_ROWS;
-        C.clk[kPathSepDense] = std::max(dense * (1.0 / 42.0) + (in_parts ? elements : 0.0), in_parts ? workgroups(blocks, MGK_SEP_PARTS_LDS, 1, rank * (15700.0 + 63.0 * ((double)o.n + i.n)))
-                                                                       : workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, dense / 60.0 / blocks));
+        const double blocks = op / MGK_SEP_DENSE_ROWS;
+        C.fp32 = {dense * (1.0 / 42.0), dense / 60.0 / blocks};
+        C.clk[kPathSepDense] = std::max(C.fp32.share, workgroups(blocks, (int64_t)(4 * MGK_SEP_DENSE_ROWS * (np + 1)), 2, C.fp32.workgroup));
+    }
+    if (in_parts) {
+        C.parts = {rank * op * np * ((double)o.n + i.n) * (1.0 / 145.0) + elements, rank * (15700.0 + 63.0 * ((double)o.n + i.n))};
+        // of small pairs (n = 40 to 100 at density 0.5) the sparse form takes less time by throughput too: the rate of the fp32 kernel
+        C.clk[kPathSepParts] = std::isinf(pairs) ? C.clk[kPathSepDense] : std::max(C.parts.share, workgroups(np / 64, MGK_SEP_PARTS_LDS, 1, C.parts.workgroup));
     }
     if (W.rows > 0 && !std::isinf(pairs) && i.n >= kWideMinColumns && o.nnz <= kWideMaxDegree * (int64_t)o.n && i.nnz <= kWideMaxDegree * (int64_t)i.n) {
         const double blocks = (o.n + W.rows - 1) / W.rows, products = (W.hi + (W.passes - 1) * W.lo) * one_sided * (1.0 / 33.0);
@@ -1611,8 +1618,8 @@ LargeCost large_cost(const mgk_ctx* ctx, int rank, const MgkSepLayout& L, const 
     }
     if (!may_sparse && !may_dense) return C;
     // of the two forms the one with the higher throughput, or, with a few pairs in 16-bit parts, the sooner end
-    const bool denser = in_parts ? C.clk[kPathSepDense] < C.clk[kPathSep] : dense * (1.0 / 42.0) < sparse + elements;
-    const int form = may_dense && (!may_sparse || denser) ? kPathSepDense : kPathSep;
+    const bool denser = in_parts && !std::isinf(pairs) ? C.clk[kPathSepParts] < C.clk[kPathSep] : C.fp32.share < sparse + elements;
+    const int form = may_dense && (!may_sparse || denser) ? in_parts ? kPathSepParts : kPathSepDense : kPathSep;
     if (C.clk[form] < C.clk[C.best]) C.best = form;
     return C;
 }
@@ -1641,6 +1648,30 @@ void merge_paths(std::vector<LargeCost>& costs) {
         for (LargeCost& C : costs)
             if (C.best == from) C.best = into;
     }
+}
+
+// The two dense forms in one call: pairs on parts run beside the others in the fp32 kernel unless launches of their own take less
+// time.  A launch takes what its longest workgroup takes, or its work on all compute units, or rather more than either where they are alike.  Us per
+// call, joined / apart, complete graphs, one pair of n = 290 and 8, 20, 60, 128 and 256 of n = 250: 2160 / 2620, 2318 / 2723, 3098 / 2967, 5444 /
+// 3991, 9570 / 5891; n = 500 and 250: 3312 / 3349, 3700 / 3435, 4256 / 3679, 5942 / 4743, 10101 / 6618; n = 270 and 140, 60, 128 and 256: 2175 /
+// 2278, 2584 / 2711, 3548 / 3432.
+void join_dense(std::vector<LargeCost>& costs) {
+    constexpr double kUnits = 256, kPathClk = 1e7 / kUnits;
+    double fp32 = 0.0, also = 0.0, parts = 0.0, longest = 0.0, longest_parts = 0.0;
+    for (const LargeCost& C : costs) {
+        if (C.best == kPathSepDense) {
+            fp32 += C.fp32.share / kUnits;
+            longest = std::max(longest, C.fp32.workgroup);
+        } else if (C.best == kPathSepParts) {
+            also += C.fp32.share / kUnits;
+            parts += C.parts.share / kUnits;
+            longest_parts = std::max(longest_parts, C.parts.workgroup);
+        }
+    }
+    if (fp32 == 0.0 || parts == 0.0) return;
+    if (std::hypot(fp32 + also, longest) < std::hypot(fp32, longest) + 0.7 * std::hypot(parts, longest_parts) + kPathClk)
+        for (LargeCost& C : costs)
+            if (C.best == kPathSepParts) C.best = kPathSepDense;
 }
 
 // Plan of one pair for the global-memory solver (any size).
@@ -1897,7 +1928,7 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
 // they are formed once more when none does.
 mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, int path, const MgkSepBasis& S,
                      const MgkSepLayout& L, const MgkWideBasis& SW, const MgkWideLayout& W, const MgkOutputs& out, hipStream_t stream, MgkParams prm) {
-    const bool dense = path == kPathSepDense, wide = path == kPathWide;
+    const bool dense = is_sep_dense(path), parts = path == kPathSepParts, wide = path == kPathWide;
     const int n_pairs = (int)pairs.size();
     prm.lean_vectors = 1;
     if (n_pairs == 0) return MGK_OK;
@@ -2038,7 +2069,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     const MgkSepAt* dfeat = (const MgkSepAt*)((char*)ctx->lpairs.p + feat_at);
     auto product = [&](int it, bool check_only) {
         return wide  ? mgk_launch_wide_xmv(A->dev, Bb->dev, wf, W, (const MgkWidePair*)dfeat, dstate, vec, prm, n_pairs, max_n1, max_n2, it, check_only, stream)
-             : dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, dpairs, dfeat, dstate, vec, prm, n_pairs,
+             : dense ? mgk_launch_sep_dense(A->dev, Bb->dev, sl[0], sl[1], S.rank, parts, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                             max_n1, max_n2, it, check_only, stream)
                      : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                           max_n1, max_n2, it, check_only, stream);
@@ -2074,7 +2105,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
     if (ctx->active_host[0] <= 0) ctx->large_iter_guess = std::max(1, ctx->active_host[1]);
     char form[64];
     if (wide) snprintf(form, sizeof form, "mgk_wide_xmv_kernel<%d, %d, %d> rank=%d passes=%d", W.rows, W.hi, W.lo, SW.outer.rank, W.passes);
-    else if (dense && mgk_sep_in_parts(max_n1, max_n2)) snprintf(form, sizeof form, "mgk_sep_dense_parts_kernel rank=%d", S.rank);
+    else if (parts) snprintf(form, sizeof form, "mgk_sep_dense_parts_kernel rank=%d", S.rank);
     else if (dense) snprintf(form, sizeof form, "mgk_sep_dense_kernel<%d> rank=%d", mgk_sep_dense_tiles(max_n2), S.rank);
     else snprintf(form, sizeof form, "mgk_sep_xmv_kernel<%d> rank=%d passes=%d", L.rk, S.rank, L.passes);
     log_launch(ctx, "%s pairs=%d iterations_enqueued=%d entries_cached=0 (+ mgk_lean_update / pupdate per iteration)", form, n_pairs, it);
@@ -2355,6 +2386,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
     costs = costs_at(basis->rank, wide.outer.rank);
     const MgkSepBasis& S = *basis;
     merge_paths(costs);
+    join_dense(costs);
     std::vector<const Choice*> lists[2][kPaths];
     for (size_t k = 0; k < choices.size(); ++k) {
         const Choice& c = choices[k];
@@ -2378,6 +2410,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             auto grid_threads = [&](int64_t n_pairs, int max_n1) {
                 return path == kPathWide ? mgk_wide_grid(n_pairs, max_n1, 4) * MGK_WIDE_THREADS
                      : path == kPathSep ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_ROWS) * MGK_SEP_THREADS
+                     : path == kPathSepParts ? mgk_sep_grid(n_pairs, MGK_SEP_PARTS_MAX_N, 64) * MGK_SEP_PARTS_THREADS
                      : path == kPathSepDense ? mgk_sep_grid(n_pairs, max_n1, MGK_SEP_DENSE_ROWS) * MGK_SEP_DENSE_THREADS : 0;
             };
             const std::vector<const Choice*>& all = lists[swapped][path];
@@ -2396,7 +2429,7 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
                     floats += 5 * (int64_t)P.npad;
                     if (is_sep(path))   // graphs that pairs share are counted for each
                         features += path == kPathWide ? wide_feature_bytes(A, P.g1) + wide_feature_bytes(B, P.g2)
-                                    : feature_bytes(A, P.g1, S.rank, path == kPathSepDense) + feature_bytes(B, P.g2, S.rank, path == kPathSepDense);
+                                    : feature_bytes(A, P.g1, S.rank, is_sep_dense(path)) + feature_bytes(B, P.g2, S.rank, is_sep_dense(path));
                     max_n1 = std::max(max_n1, P.n1);
                     if (last > first && (floats > kMaxScratchFloats || features > kMaxFeatureBytes ||
                                          grid_threads((int64_t)(last - first) + 1, max_n1) >= kMaxGridThreads))

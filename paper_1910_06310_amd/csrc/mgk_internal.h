@@ -439,6 +439,7 @@ struct MgkSepLayout {
 #define MGK_SEP_SLAB(rk) ((rk) == 1 ? 17 : 64 * (((rk) + 3) / 4) + 4)   // words per column of T
 #define MGK_SEP_DENSE_MAX_N 1024
 #define MGK_SEP_PARTS_MAX_N 256   // of the dense form with operands in three 16-bit parts: eight wavefronts of 32 rows
+#define MGK_SEP_PARTS_THREADS 512
 #define MGK_SEP_PARTS_LDS 101376
 static inline MGK_HD bool mgk_sep_in_parts(int32_t max_n1, int32_t max_n2) { return max_n1 <= MGK_SEP_PARTS_MAX_N && max_n2 <= MGK_SEP_PARTS_MAX_N; }
 static inline MGK_HD int32_t mgk_sep_per_packet(int32_t rk) { return rk == 1 ? 8 : 2; }

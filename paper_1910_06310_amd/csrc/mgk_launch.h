@@ -197,9 +197,10 @@ MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const M
                                                    const MgkSepLayout& L, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state,
                                                    float* vec, const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                    bool check_only, hipStream_t stream);
+// parts: operands in three 16-bit parts, for graphs that mgk_sep_in_parts allows
 MGK_KERNELS_OPTIONAL hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY,
-                                                     int rank, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec,
-                                                     const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
+                                                     int rank, bool parts, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state,
+                                                     float* vec, const MgkParams& prm, int n_pairs, int max_n1, int max_n2, int it,
                                                      bool check_only, hipStream_t stream);
 // The same for sparse graphs of many vertices (mgk_sep_wide.hip): features of the graphs listed (memory the device can read;
 // MgkSepGraph::at a record or a word) as outer and as inner ones, and the product.

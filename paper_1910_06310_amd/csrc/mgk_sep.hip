@@ -415,7 +415,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));   // rows of p begin anywhere
 
-constexpr int kPartsThreads = 512, kPartsStride = MGK_SEP_PARTS_MAX_N + 8;   // 16-bit words of a column's part in LDS: columns 4 banks apart
+constexpr int kPartsThreads = MGK_SEP_PARTS_THREADS, kPartsStride = MGK_SEP_PARTS_MAX_N + 8;   // 16-bit words of a column's part in LDS: columns 4 banks apart
 constexpr int kPartsLds = 3 * 64 * kPartsStride * 2;
 static_assert(kPartsLds == MGK_SEP_PARTS_LDS && kPartsThreads / 64 * 32 == MGK_SEP_PARTS_MAX_N, "a wavefront per 32 rows");
 
@@ -646,9 +646,10 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
 }
 
 hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList& SX, const MgkSepList& SY, int rank,
-                                const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec, const MgkParams& prm,
+                                bool parts, const MgkLargePair* pairs, const MgkSepAt* feat, MgkPairState* state, float* vec, const MgkParams& prm,
                                 int n_pairs, int max_n1, int max_n2, int it, bool check_only, hipStream_t stream) {
-    if (mgk_sep_in_parts(max_n1, max_n2)) {
+    if (parts) {
+        if (!mgk_sep_in_parts(max_n1, max_n2)) return hipErrorInvalidValue;
         static bool configured = false;
         const hipError_t e = set_lds(reinterpret_cast<const void*>(mgk_sep_dense_parts_kernel), &configured);
         if (e != hipSuccess) return e;

@@ -388,9 +388,10 @@ hipError_t mgk_launch_sep_xmv(const MgkBatchDev& X, const MgkBatchDev& Y, const 
     if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 15) / 16) * 1024 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
     return launched("sep", s, &X, &Y, n);
 }
-hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&, int,
-                                const MgkLargePair*, const MgkSepAt*, MgkPairState*, float*, const MgkParams&, int n, int max_n1, int, int, bool, hipStream_t s) {
+hipError_t mgk_launch_sep_dense(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkSepList&, const MgkSepList&, int, bool parts,
+                                const MgkLargePair*, const MgkSepAt*, MgkPairState*, float*, const MgkParams&, int n, int max_n1, int max_n2, int, bool, hipStream_t s) {
     if ((int64_t)((n + 7) / 8) * 8 * ((max_n1 + 31) / 32) * 256 >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;
+    if (parts && !mgk_sep_in_parts(max_n1, max_n2)) return hipErrorInvalidValue;
     return launched("sep dense", s, &X, &Y, n);
 }
 #ifdef STUB_WIDE   // the library does without these kernels where they are not linked

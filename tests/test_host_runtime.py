@@ -227,6 +227,23 @@ def test_launch_record_names_the_dense_kernel_that_runs(host, sizes, kernel):
     assert launched(host.log(), "sep dense") and host.launch_log().startswith(kernel)
 
 
+def records(log):
+    """Kernel and pairs of every launch of a call that the library records."""
+    return sorted((name, int(k)) for name, k in re.findall(r"^(\w+).*? pairs=(\d+)", log, re.M))
+
+
+@pytest.mark.parametrize("sizes,pairs,expected", [
+    ((290, 250, 240), 200, [("mgk_sep_dense_kernel", 1), ("mgk_sep_dense_parts_kernel", 200)]),   # not all with the kernel of the largest
+    ((290, 250, 240), 8, [("mgk_sep_dense_kernel", 9)]),                                          # too few for launches of their own
+    ((256, 250, 240), 60, [("mgk_sep_dense_parts_kernel", 61)]),
+    ((256, 250, 134), 60, [("mgk_sep_dense_parts_kernel", 61)])])     # small graphs beside large ones
+def test_dense_pairs_run_with_the_kernel_they_are_priced_for(host, sizes, pairs, expected):
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(*[ring(n, n // 2 - 1, np.linspace(0, 1, n * (n // 2 - 1))) for n in sizes]))
+    assert host.pairs(B, B, [0] + [1] * pairs, [0] + [2] * pairs) == 0, host.error()
+    assert records(host.launch_log()) == expected
+
+
 def test_pairs_are_solved_without_features_where_memory_is_short(host):
     """Features of the separable product are an addition to what the direct product needs: neither forming
     them nor keeping them may make a call fail that the direct product can do."""
