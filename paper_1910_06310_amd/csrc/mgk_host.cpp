@@ -2345,28 +2345,42 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             choices.push_back(c);
         }
     const int64_t n_tiles = std::min(X->n_tiles, X->nnz / 3) + (X == Y ? 0 : std::min(Y->n_tiles, Y->nnz / 3));
-    auto costs_at = [&](int rank, int wide_rank) {
-        std::vector<LargeCost> costs;
-        costs.reserve(choices.size());
-        // pairs that are solved together have the division of the largest one that has any
-        MgkSepLayout L{};
-        MgkWideLayout W{};
-        int32_t sep_n2 = 0, wide_n2 = 0;
-        for (const Choice& c : choices) {
-            if (rank > 0 && c.sep.n2 > sep_n2)
-                if (const MgkSepLayout one = sep_layout(rank, c.sep.n2); one.rk > 0) {
-                    L = one;
-                    sep_n2 = c.sep.n2;
-                }
-            if (wide_rank > 0 && c.sep.n2 > wide_n2)
-                if (const MgkWideLayout one = wide_layout(wide_rank, c.sep.n2); one.rows > 0) {
-                    W = one;
-                    wide_n2 = c.sep.n2;
-                }
+    // What the products of all pairs take, and the paths that they take then.  The pairs of a path are solved with the division of the largest
+    // inner graph among them: once it is known which that is they are priced with it, and again while that changes.  first_look: each for
+    // itself.
+    auto costs_at = [&](int rank, int wide_rank, bool first_look) {
+        std::vector<LargeCost> costs(choices.size());
+        int32_t sep_n2 = 0, wide_n2 = 0, least = INT32_MAX;   // at first every pair has its own
+        for (const Choice& c : choices) least = std::min(least, c.sep.n2);
+        for (int round = 0; round < 3; ++round) {
+            MgkSepLayout L{};
+            MgkWideLayout W{};
+            int32_t sep_at = -1, wide_at = -1;   // the inner graphs that L and W are for
+            for (size_t k = 0; k < choices.size(); ++k) {
+                const Choice& c = choices[k];
+                if (rank > 0 && sep_at != std::max(sep_n2, c.sep.n2)) L = sep_layout(rank, sep_at = std::max(sep_n2, c.sep.n2));
+                if (wide_rank > 0 && wide_at != std::max(wide_n2, c.sep.n2)) W = wide_layout(wide_rank, wide_at = std::max(wide_n2, c.sep.n2));
+                costs[k] = large_cost(ctx, rank, L, W, c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size(), n_tiles);
+            }
+            if (first_look) break;
+            merge_paths(costs);
+            join_dense(costs);
+            int32_t sep_now = 0, wide_now = 0;
+            for (size_t k = 0; k < choices.size(); ++k) {
+                if (costs[k].best == kPathSep) sep_now = std::max(sep_now, choices[k].sep.n2);
+                if (costs[k].best == kPathWide) wide_now = std::max(wide_now, choices[k].sep.n2);
+            }
+            if (sep_now == sep_n2 && wide_now == wide_n2) break;
+            if (round == 0) {   // often all have the same: fewer divisions fit more columns, so none between has another
+                const MgkSepLayout a = sep_layout(rank, least), b = sep_layout(rank, sep_now);
+                const MgkWideLayout c = wide_layout(wide_rank, least), d = wide_layout(wide_rank, wide_now);
+                if ((sep_now == 0 || (a.rk == b.rk && a.passes == b.passes)) &&
+                    (wide_now == 0 || (c.rows == d.rows && c.hi == d.hi && c.lo == d.lo && c.passes == d.passes)))
+                    break;
+            }
+            sep_n2 = sep_now;
+            wide_n2 = wide_now;
         }
-        for (const Choice& c : choices)
-            costs.push_back(large_cost(ctx, rank, c.sep.n2 <= sep_n2 ? L : MgkSepLayout{}, c.sep.n2 <= wide_n2 ? W : MgkWideLayout{},
-                                       c.sep_swapped ? Y : X, c.sep.g1, c.sep_swapped ? X : Y, c.sep.g2, (int64_t)choices.size(), n_tiles));
         return costs;
     };
     const bool may_wide = may_sep && ctx->edge_kernel == MGK_EK_SE && mgk_launch_wide_xmv &&
@@ -2377,16 +2391,14 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
         const float lo = std::min(X->label_lo, Y->label_lo), hi = std::max(X->label_hi, Y->label_hi);
         basis = kept_basis(ctx, lo, hi);
         if (!basis) {   // it takes time: made if any pair would take the separable product at the lowest rank
-            costs = costs_at(1, may_wide ? 1 : 0);
+            costs = costs_at(1, may_wide ? 1 : 0, true);
             basis = std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); }) ? make_basis(ctx, lo, hi) : &none;
         }
     }
     static const MgkWideBasis no_wide{};
     const MgkWideBasis& wide = may_wide && basis->rank > 0 ? wide_basis(ctx, basis) : no_wide;
-    costs = costs_at(basis->rank, wide.outer.rank);
+    costs = costs_at(basis->rank, wide.outer.rank, false);
     const MgkSepBasis& S = *basis;
-    merge_paths(costs);
-    join_dense(costs);
     std::vector<const Choice*> lists[2][kPaths];
     for (size_t k = 0; k < choices.size(); ++k) {
         const Choice& c = choices[k];

@@ -244,6 +244,25 @@ def test_dense_pairs_run_with_the_kernel_they_are_priced_for(host, sizes, pairs,
     assert records(host.launch_log()) == expected
 
 
+def test_pairs_are_priced_with_the_division_that_runs(host):
+    """Five features in one pass up to 276 columns: a larger pair that takes another product does not count."""
+    host.set("edge_kernel_se", 1.0)
+    B = host.load(graphs(ring(400, 199, np.linspace(0, 1, 400 * 199)), *[ring(250, 13, np.linspace(0, 1, 250 * 13))] * 2))
+    assert host.pairs(B, B, [0] + [1] * 60, [0] + [2] * 60) == 0, host.error()
+    assert records(host.launch_log()) == [("mgk_sep_dense_kernel", 1), ("mgk_sep_xmv_kernel", 60)]
+    assert "mgk_sep_xmv_kernel<5> rank=5 passes=1" in host.launch_log()
+
+
+@pytest.mark.parametrize("largest,division", [(283, "<8, 9, 9> rank=9 passes=1"), (290, "<8, 4, 5> rank=9 passes=2"), (600, "<4, 4, 5> rank=9 passes=2")])
+def test_division_of_many_vertices_is_that_of_the_largest_inner_graph(host_wide, largest, division):
+    host = host_wide
+    host.set("edge_kernel_se", 0.42)
+    B = host.load(graphs(*[ring(n, 3, np.linspace(0, 1, 3 * n)) for n in (3000, largest, 260)]))
+    assert host.pairs(B, B, [0] * 20, [1] * 2 + [2] * 18) == 0, host.error()
+    assert "mgk_wide_xmv_kernel" + division in host.launch_log()
+    assert host.violations() == ""
+
+
 def test_pairs_are_solved_without_features_where_memory_is_short(host):
     """Features of the separable product are an addition to what the direct product needs: neither forming
     them nor keeping them may make a call fail that the direct product can do."""
