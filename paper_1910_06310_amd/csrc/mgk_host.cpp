@@ -1833,7 +1833,7 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
         const int waves = rows_threads / 64;
         rows_chunks = large && min_chunks >= 4 * waves ? 4 : min_chunks >= 2 * waves ? 2 : 1;
     }
-    const int vec_blocks = std::max(1, std::min(2048, (max_npad + 1023) / 1024));
+    const int vec_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(2048, ((int64_t)max_npad + 1023) / 1024));
     mgk_status st;
     if ((st = ensure(ctx, ctx->vec, (size_t)total * sizeof(float))) != MGK_OK) return st;
     if ((st = ensure(ctx, ctx->lpairs, (size_t)n_pairs * sizeof(MgkLargePair))) != MGK_OK) return st;
@@ -1945,8 +1945,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         P.nsteps = A->graphs[(size_t)P.g1].voff;
         P.atomic_rows = Bb->graphs[(size_t)P.g2].voff;
     }
-    // at most about a thousand workgroups: each adds to the sums of its pair
-    const int vec_blocks = std::max(1, std::min(std::max(16, 1024 / n_pairs), (max_npad + MGK_LEAN_ELEMENTS - 1) / MGK_LEAN_ELEMENTS));
+    const int vec_blocks = mgk_lean_blocks(n_pairs, max_npad);
     // the graphs in use and where their features go, from A and from Bb (the same list when it is A)
     const int gi = L.per_packet == 8 ? 1 : 0, sides = Bb == A ? 1 : 2;
     const mgk_batch* bt[2] = {A, Bb};

@@ -627,7 +627,22 @@ struct MgkVectorEnv {
     float q, h;
 };
 #define MGK_LEAN_THREADS 512       // of their workgroups,
-#define MGK_LEAN_ELEMENTS 2048     // which take as many elements at a time
+#define MGK_LEAN_ELEMENTS 2048     // which take as many elements at a time, four to a thread
+// body(first element) for every four of the elements of thread `thread` of workgroup `block`; two at a time where there are as many, so
+// that their loads are in flight together.  `end` may be close to 2^31: a step past it stays positive.
+template <class F>
+MGK_HD inline void mgk_each_quad(uint32_t block, uint32_t blocks, uint32_t thread, int32_t end, const F& body) {
+    static_assert(MGK_LEAN_ELEMENTS == 4 * MGK_LEAN_THREADS, "four elements to a thread");
+    const uint32_t step = blocks * MGK_LEAN_ELEMENTS, last = (uint32_t)end;
+    for (uint32_t at = block * MGK_LEAN_ELEMENTS + 4 * thread; at < last; at += 2 * step) {
+        body((int32_t)at);
+        if (at + step < last) body((int32_t)(at + step));
+    }
+}
+static inline MGK_HD int32_t mgk_lean_blocks(int64_t n_pairs, int32_t max_npad) {   // at most about a thousand in all: each adds to the sums of its pair
+    const int64_t most = n_pairs < 64 ? 1024 / n_pairs : 16, all = ((int64_t)max_npad + MGK_LEAN_ELEMENTS - 1) / MGK_LEAN_ELEMENTS;
+    return (int32_t)(all < 1 ? 1 : all < most ? all : most);
+}
 #define MGK_COUNTERS_BYTES 64
 
 // Scalars of one pair in the global-memory solver.  The three sums of iteration `it` go

@@ -93,16 +93,9 @@ struct VertexTerms {
 __device__ __forceinline__ MgkVectorEnv env_of(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkParams& prm) {
     return MgkVectorEnv{X.rowsum, Y.rowsum, X.vlabel, Y.vlabel, prm.q, prm.h};
 }
-// body(first element) for every four elements of the calling thread; two at a time where there are as many, so that their loads
-// are in flight together
 template <class F>
 __device__ __forceinline__ void each_quad(int end, const F& body) {
-    static_assert(MGK_LEAN_ELEMENTS == 4 * MGK_LEAN_THREADS, "four elements to a thread");
-    const int step = (int)gridDim.x * MGK_LEAN_ELEMENTS;
-    for (int at = (int)blockIdx.x * MGK_LEAN_ELEMENTS + 4 * (int)threadIdx.x; at < end; at += 2 * step) {
-        body(at);
-        if (at + step < end) body(at + step);
-    }
+    mgk_each_quad(blockIdx.x, gridDim.x, threadIdx.x, end, body);
 }
 
 // ---- expansion of the octiles of a whole batch --------------------------------
@@ -162,7 +155,7 @@ __global__ __launch_bounds__(256) void mgk_large_init_kernel(MgkBatchDev X, MgkB
     float* y = M + P.npad;
     const float qq = prm.q * prm.q;
     float s_rz = 0.f, s_bb = 0.f;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)P.npad; idx += gridDim.x * blockDim.x) {
         float b = 0.f, z0 = 0.f, m = 1.f;
         if (idx < N) {
             const int i = idx / P.n2, ip = idx - i * P.n2;
@@ -742,7 +735,7 @@ __global__ __launch_bounds__(256) void mgk_large_dot_kernel(const MgkLargePair* 
     const float* M = p + P.npad;
     const float* y = M + P.npad;
     float s = 0.f;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)P.npad; idx += gridDim.x * blockDim.x) {
         const float pv = p[idx];
         s = __builtin_fmaf(pv, __builtin_fmaf(M[idx], pv, -y[idx]), s);
     }
@@ -765,7 +758,7 @@ __global__ __launch_bounds__(256) void mgk_large_update_kernel(const MgkLargePai
     const float* M = p + P.npad;
     float* y = const_cast<float*>(M) + P.npad;
     float s_rz = 0.f, s_rr = 0.f;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)P.npad; idx += gridDim.x * blockDim.x) {
         const float pv = p[idx], m = M[idx];
         const float av = __builtin_fmaf(m, pv, -y[idx]);
         x[idx] = __builtin_fmaf(alpha, pv, x[idx]);
@@ -806,7 +799,7 @@ __global__ __launch_bounds__(256) void mgk_large_pupdate_kernel(const MgkLargePa
     const float beta = rz / rho;
     float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = p + 2 * (int64_t)P.npad;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)P.npad; idx += gridDim.x * blockDim.x) {
         p[idx] = __builtin_fmaf(beta, p[idx], y[idx]);
         y[idx] = 0.f;
     }
@@ -907,7 +900,7 @@ __global__ __launch_bounds__(256) void mgk_large_final_kernel(MgkBatchDev X, Mgk
     const bool swapped = P.out1 == MGK_OUT1_SWAPPED;
     const float inv_qq = 1.0f / (prm.q * prm.q), inv_h = 1.0f / prm.h;
     float s = 0.f, growth = 0.f;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)N; idx += gridDim.x * blockDim.x) {
         const int i = idx / P.n2, ip = idx - i * P.n2;
         const float xv = x[idx];
         s = __builtin_fmaf(X.start[g1.voff + i] * Y.start[g2.voff + ip], xv, s);
@@ -944,7 +937,7 @@ __global__ __launch_bounds__(256) void mgk_large_verify_prepare_kernel(const Mgk
     const float* x = vec + P.vec;
     float* p = vec + P.vec + 2 * (int64_t)P.npad;
     float* y = p + 2 * (int64_t)P.npad;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < P.npad; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)P.npad; idx += gridDim.x * blockDim.x) {
         p[idx] = x[idx];
         y[idx] = 0.f;
     }
@@ -971,7 +964,7 @@ __global__ __launch_bounds__(256) void mgk_large_verify_residual_kernel(MgkBatch
     const float* y = M + P.npad;
     const float qq = prm.q * prm.q;
     float s = 0.f;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
+    for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (uint32_t)N; idx += gridDim.x * blockDim.x) {
         const int i = idx / P.n2, ip = idx - i * P.n2;
         const bool same = X.vlabel[g1.voff + i] == Y.vlabel[g2.voff + ip];
         const float m = M[idx];

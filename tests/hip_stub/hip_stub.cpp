@@ -205,6 +205,19 @@ int64_t stub_pinned() { return (int64_t)pinned_bytes; }
 void stub_converge_after(int iterations) { converge_after = iterations; }
 void stub_set_device(int d) { device = d; }
 int stub_device() { return device; }
+// First elements that a thread of the vector kernels is given: how many, the smallest and the largest.
+int64_t stub_quads(int block, int blocks, int thread, int end, int64_t* range) {
+    int64_t n = 0;
+    range[0] = INT64_MAX;
+    range[1] = INT64_MIN;
+    mgk_each_quad(block, blocks, thread, end, [&](int32_t at) {
+        ++n;
+        range[0] = std::min<int64_t>(range[0], at);
+        range[1] = std::max<int64_t>(range[1], at);
+    });
+    return n;
+}
+int stub_lean_blocks(int64_t n_pairs, int max_npad) { return mgk_lean_blocks(n_pairs, max_npad); }
 
 // ---- the runtime
 hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }

@@ -263,6 +263,22 @@ def test_division_of_many_vertices_is_that_of_the_largest_inner_graph(host_wide,
     assert host.violations() == ""
 
 
+@pytest.mark.parametrize("n_pairs", [1, 3, 100])
+@pytest.mark.parametrize("elements", [1, 2049, 4096 * 1024 + 5, 2 ** 31 - 65, 2 ** 31 - 64 - 4 * 2 ** 20])
+def test_elements_of_a_thread_of_the_vector_kernels(so, n_pairs, elements):
+    """Pairs have fewer than 2^31 - 64 elements: the steps past the last one stay within 32 bits."""
+    lib = C.CDLL(so)
+    lib.stub_quads.restype = C.c_int64
+    blocks = lib.stub_lean_blocks(C.c_int64(n_pairs), (elements + 63) & ~63)
+    assert 1 <= blocks <= 1024
+    for block in {0, blocks // 2, blocks - 1}:
+        for thread in (0, 511):
+            expected = range(block * 2048 + 4 * thread, elements, blocks * 2048)
+            got = (C.c_int64 * 2)()
+            assert lib.stub_quads(block, blocks, thread, elements, got) == len(expected)
+            assert not expected or tuple(got) == (expected[0], expected[-1])
+
+
 def test_pairs_are_solved_without_features_where_memory_is_short(host):
     """Features of the separable product are an addition to what the direct product needs: neither forming
     them nor keeping them may make a call fail that the direct product can do."""
