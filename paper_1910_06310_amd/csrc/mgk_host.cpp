@@ -1888,7 +1888,7 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
     ctx->active_host[0] = n_pairs;   // pairs still iterating
     ctx->active_host[1] = 0;         // most iterations any pair needed
     MGK_HIP(ctx, hipMemcpyAsync(dactive, ctx->active_host, 2 * sizeof(int), hipMemcpyHostToDevice, stream));
-    hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, stream);
+    hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, false, n_pairs, vec_blocks, stream);
     if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "init launch failed: %s", hipGetErrorString(e));
     // The kernels of an iteration return at once for pairs that have stopped, so iterations
     // are enqueued without waiting: as many as the previous call of this kind needed, then
@@ -1927,10 +1927,9 @@ mgk_status solve_large(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, in
 // the host looks whether any pair still iterates, so that the GPU does not wait for that.  If any does,
 // they are formed once more when none does.
 mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std::vector<MgkLargePair> pairs, int path, const MgkSepBasis& S,
-                     const MgkSepLayout& L, const MgkWideBasis& SW, const MgkWideLayout& W, const MgkOutputs& out, hipStream_t stream, MgkParams prm) {
+                     const MgkSepLayout& L, const MgkWideBasis& SW, const MgkWideLayout& W, const MgkOutputs& out, hipStream_t stream, const MgkParams& prm) {
     const bool dense = is_sep_dense(path), parts = path == kPathSepParts, wide = path == kPathWide;
     const int n_pairs = (int)pairs.size();
-    prm.lean_vectors = 1;
     if (n_pairs == 0) return MGK_OK;
     if (!mgk_launch_sep_xmv) return fail(ctx, MGK_ESTATE, "the library was linked without the kernels of the separable product");
     int64_t total = 0;
@@ -1942,8 +1941,8 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
         total += 5 * (int64_t)P.npad;
         max_npad = std::max(max_npad, P.npad);
         max_iter = std::max(max_iter, P.max_iter);
-        P.nsteps = A->graphs[(size_t)P.g1].voff;
-        P.atomic_rows = Bb->graphs[(size_t)P.g2].voff;
+        P.voff1 = A->graphs[(size_t)P.g1].voff;
+        P.voff2 = Bb->graphs[(size_t)P.g2].voff;
     }
     const int vec_blocks = mgk_lean_blocks(n_pairs, max_npad);
     // the graphs in use and where their features go, from A and from Bb (the same list when it is A)
@@ -2073,7 +2072,7 @@ mgk_status solve_sep(mgk_ctx* ctx, const mgk_batch* A, const mgk_batch* Bb, std:
                      : mgk_launch_sep_xmv(A->dev, Bb->dev, sl[0], sl[1], L, dpairs, dfeat, dstate, vec, prm, n_pairs,
                                           max_n1, max_n2, it, check_only, stream);
     };
-    hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, n_pairs, vec_blocks, stream);
+    hipError_t e = mgk_launch_large_init(A->dev, Bb->dev, dpairs, dstate, vec, prm, true, n_pairs, vec_blocks, stream);
     if (e != hipSuccess) return fail(ctx, MGK_EDEVICE, "init launch failed: %s", hipGetErrorString(e));
     int it = 0;
     const int first_batch = std::max(1, std::min(max_iter, ctx->large_iter_guess));

@@ -139,7 +139,6 @@ struct MgkParams {
     int32_t label_dim;                     // attributes per edge label the kernel reads
     float attr_scale[MGK_MAX_LABEL_DIM];   // KRON_SE: sqrt(alpha_a log2(e)) per attribute; RCONV_SE: [0] for all parts
     float poly_c[MGK_POLY_MAX_COEF];       // POLY: sum_i poly_c[i] r^i on r = |e-e'| / rho < 1, zero-padded
-    int32_t lean_vectors;                  // global-memory solver: M is not kept (separable product)
 };
 
 #if defined(__HIPCC__)
@@ -615,8 +614,15 @@ struct MgkLargePair {
     int32_t npad;          // n1 * n2 rounded up to 64
     int32_t out0, out1;
     int32_t max_iter;
-    int32_t nsteps;        // DPP steps for the inner row sums; with the separable product the outer graph's voff,
-    int32_t atomic_rows;   // inner graph has rows longer than a lane group; the inner graph's voff
+    union {
+        struct {
+            int32_t nsteps;        // direct product: DPP steps for the inner row sums
+            int32_t atomic_rows;   // inner graph has rows longer than a lane group
+        };
+        struct {
+            int32_t voff1, voff2;  // separable product: first vertices of the two graphs
+        };
+    };
 };
 
 // What the vector kernels of the separable product read beside the pairs: it follows the two counters of a call

@@ -63,9 +63,9 @@ struct VertexTerms {
     const MGK_GLOBAL int32_t *vlabel1, *vlabel2;
     float q, h;
     int n2, N;
-    __device__ __forceinline__ VertexTerms(const MgkVectorEnv& E, const MgkLargePair& P)   // voff1 = nsteps, voff2 = atomic_rows
-        : rowsum1((const MGK_GLOBAL float*)E.rowsum1 + P.nsteps), rowsum2((const MGK_GLOBAL float*)E.rowsum2 + P.atomic_rows),
-          vlabel1((const MGK_GLOBAL int32_t*)E.vlabel1 + P.nsteps), vlabel2((const MGK_GLOBAL int32_t*)E.vlabel2 + P.atomic_rows),
+    __device__ __forceinline__ VertexTerms(const MgkVectorEnv& E, const MgkLargePair& P)
+        : rowsum1((const MGK_GLOBAL float*)E.rowsum1 + P.voff1), rowsum2((const MGK_GLOBAL float*)E.rowsum2 + P.voff2),
+          vlabel1((const MGK_GLOBAL int32_t*)E.vlabel1 + P.voff1), vlabel2((const MGK_GLOBAL int32_t*)E.vlabel2 + P.voff2),
           q(E.q), h(E.h), n2(P.n2), N(P.n1 * P.n2) {}
     __device__ __forceinline__ void quad(int idx, float (&m)[4], float (&dd)[4]) const {
         const int i = (int)((uint32_t)min(idx, N - 1) / (uint32_t)n2), ip = min(idx, N - 1) - i * n2;
@@ -1076,9 +1076,9 @@ hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams& prm, f
 }
 
 hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair* pairs,
-                                 MgkPairState* state, float* vec, const MgkParams& prm, int n_pairs,
+                                 MgkPairState* state, float* vec, const MgkParams& prm, bool lean, int n_pairs,
                                  int vec_blocks, hipStream_t stream) {
-    if (prm.lean_vectors)
+    if (lean)
         hipLaunchKernelGGL(mgk_lean_init_kernel, dim3(vec_blocks, n_pairs), dim3(MGK_LEAN_THREADS), 0, stream, X, Y, pairs, state, vec, prm);
     else
         hipLaunchKernelGGL(mgk_large_init_kernel, dim3(vec_blocks, n_pairs), dim3(256), 0, stream, X, Y, pairs,

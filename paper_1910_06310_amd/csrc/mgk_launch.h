@@ -150,9 +150,9 @@ hipError_t mgk_launch_expand(const MgkBatchDev& B, const MgkParams& prm, MgkEntr
 // Expand every octile of B to dense 8x8 blocks (64 * B.n_tiles_total floats per array).
 hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams& prm, float* dw, float* de,
                                    float* dlw, hipStream_t stream);
-// Set-up of Alg. 1 for n_pairs pairs (state must be zero-filled before).
+// Set-up of Alg. 1 for n_pairs pairs (state must be zero-filled before).  lean: for the separable product, M is not kept.
 hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair* pairs,
-                                 MgkPairState* state, float* vec, const MgkParams& prm, int n_pairs,
+                                 MgkPairState* state, float* vec, const MgkParams& prm, bool lean, int n_pairs,
                                  int vec_blocks, hipStream_t stream);
 // Iteration `it` (0, 1, ...) of Alg. 1 for all pairs that have not stopped: the product, then
 // three kernels over the vectors that also do the scalar steps and the stop test.  n_active[0]

@@ -116,7 +116,7 @@ __device__ __forceinline__ void attr_pass(float (&kap)[C][SMAX], int stop, const
         if (K0 < stop) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float v = PASS == kAttrBegin && RCONV || PASS == kAttrEnd && !RCONV ? 0.f : lane_value(v1, K0 + u);
+                const float v = (PASS == kAttrBegin && RCONV) || (PASS == kAttrEnd && !RCONV) ? 0.f : lane_value(v1, K0 + u);
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     float& k = kap[c][K0 + u];

@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void mgk_sep_dense_parts_kernel(M
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (blk == 0 && tid == 0 && !check_only) clear_sums(st, it);
     const int n1 = P.n1, n2 = P.n2, np1 = (n1 + 63) & ~63, np2 = (n2 + 63) & ~63;
-    const int voff1 = P.nsteps, voff2 = P.atomic_rows;   // as the vector kernels have them
+    const int voff1 = P.voff1, voff2 = P.voff2;
     const float* F1 = SX.dense + F.f1;
     const float* F2 = SY.dense + F.f2;
     const float* p = vec + P.vec + 2 * (int64_t)P.npad;

@@ -375,7 +375,7 @@ hipError_t mgk_noalloc_job_storage(int, MgkJob** jobs, int64_t* capacity) {
 hipError_t mgk_launch_expand(const MgkBatchDev& B, const MgkParams&, MgkEntry*, MgkEntry*, hipStream_t s) { return launched("expand", s, &B); }
 hipError_t mgk_launch_expand_dense(const MgkBatchDev& B, const MgkParams&, float*, float*, float*, hipStream_t s) { return launched("expand_dense", s, &B); }
 hipError_t mgk_launch_large_init(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkLargePair*, MgkPairState*, float*,
-                                 const MgkParams&, int n, int, hipStream_t s) { return launched("init", s, &X, &Y, n); }
+                                 const MgkParams&, bool, int n, int, hipStream_t s) { return launched("init", s, &X, &Y, n); }
 hipError_t mgk_launch_large_iteration(const MgkBatchDev& X, const MgkBatchDev& Y, const MgkExpanded&, const MgkExpanded&,
                                       const MgkLargePair*, MgkPairState*, float*, const MgkParams&, bool, int n, int, int,
                                       int* n_active, int it, const MgkDenseTiles* D, const MgkDenseTiles*, int rows, int, int, hipStream_t s) {

@@ -34,7 +34,7 @@ hipError_t mgk_noalloc_job_storage(int, MgkJob**, int64_t*) { return hipErrorUnk
 hipError_t mgk_launch_expand(const MgkBatchDev&, const MgkParams&, MgkEntry*, MgkEntry*, hipStream_t) { return hipErrorUnknown; }
 hipError_t mgk_launch_expand_dense(const MgkBatchDev&, const MgkParams&, float*, float*, float*, hipStream_t) { return hipErrorUnknown; }
 hipError_t mgk_launch_large_init(const MgkBatchDev&, const MgkBatchDev&, const MgkLargePair*, MgkPairState*, float*,
-                                 const MgkParams&, int, int, hipStream_t) { return hipErrorUnknown; }
+                                 const MgkParams&, bool, int, int, hipStream_t) { return hipErrorUnknown; }
 hipError_t mgk_launch_large_iteration(const MgkBatchDev&, const MgkBatchDev&, const MgkExpanded&, const MgkExpanded&,
                                       const MgkLargePair*, MgkPairState*, float*, const MgkParams&, bool, int, int, int,
                                       int*, int, const MgkDenseTiles*, const MgkDenseTiles*, int, int, int, hipStream_t) { return hipErrorUnknown; }
