@@ -1533,7 +1533,9 @@ struct LargeCost {
 // Bytes the features of a graph take at most, whatever the layout.
 constexpr int64_t kMaxFeatureBytes = (int64_t)8 << 30;   // of the pairs solved together
 constexpr int64_t kWideMaxDegree = 32;   // mean; beyond, stage 1 was not measured, and from 50 on the dense form is near
-constexpr int kWideMinColumns = 24;      // an absent nonzero may point at column 9
+// An absent nonzero may point at columns 0 to 3.  Below 24 columns the row-staged product takes the less time: outer graphs of 4000 vertices, degree 8, 1,
+// 8 and 64 pairs, row-staged / this: n = 20 403 / 285, 447 / 704, 1633 / 4063 us; n = 10 349 / 269, 418 / 745, 906 / 3650.
+constexpr int kWideMinColumns = 24;
 int64_t wide_feature_bytes(const mgk_batch* b, int32_t g) {   // as outer and as inner graph
     constexpr int kPasses = MGK_SEP_MAX_RANK / 4;
     return (int64_t)kPasses * 32 * b->graphs[(size_t)g].nnz + 4 * mgk_wide_inner_words(b->graphs[(size_t)g], kPasses);

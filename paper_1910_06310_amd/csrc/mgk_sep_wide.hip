@@ -45,21 +45,14 @@ __global__ __launch_bounds__(256) void mgk_wide_outer_kernel(MgkBatchDev B, MgkW
     }
 }
 
-// Which of the four 64-byte parts of all LDS banks the quadruples of column j lie in that lanes of one cycle read with
-// a 16-byte read.  A cycle takes 16 lanes, of the columns at places {0, 3, 5, 6}, {1, 2, 4, 7}, {8, 11, 13, 14} or {9, 10, 12, 15} of a
-// group of 16 (4 rows), or of four adjacent columns, the lower rows of the two outer and the upper rows of the two inner ones or
-// the other way round (8 rows; `inner` then: the column is one of the inner two).
-__device__ __forceinline__ int wide_part(int rows, uint32_t j, bool inner) {
-    return rows == 4 ? (int)(j & 3u) : (int)((j & 1u) * 2u + (((j >> 3) & 1u) ^ (inner ? 1u : 0u)));
-}
-__device__ __forceinline__ uint32_t wide_column_of_part(int rows, int part, bool inner) {
-    return rows == 4 ? (uint32_t)part : (uint32_t)(part >> 1) + 8u * (uint32_t)((part & 1) ^ (inner ? 1 : 0));
-}
+// Which of the four 64-byte parts of all LDS banks the quadruples of column j lie in that lanes of one cycle read with a 16-byte
+// read, with 4 rows: a cycle takes 16 lanes, of the columns at places {0, 3, 5, 6}, {1, 2, 4, 7}, {8, 11, 13, 14} or {9, 10, 12, 15} of a group of 16.
+__device__ __forceinline__ int wide_part(uint32_t j) { return (int)(j & 3u); }   // column j < 4 lies in part j
 
 // Inner side: the columns by descending degree in groups of 16; step p of a group holds nonzeros 4p .. 4p + 3 of every
 // column, column after column: 64 words with the byte offset of the column's T, 64 with s', 64 with A' g s'^first.
 // In front of a graph's steps the first step of every group.  Absent nonzeros are zeros.
-// With 4 rows, where a call is long enough to pay for it, the nonzeros of a column come in an order in which the four columns read
+// With 4 rows the nonzeros of a column (of up to 64) come in an order in which the four columns read
 // together rarely meet in a bank: the part with the most left that the others do not take.  2048 columns of degree 12: conflicts are 28 % of the
 // product's LDS cycles, 45 % in the order of the rows (1074 -> 1039 us a product); this kernel 78 us, 18 without.
 __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkWideBasis S, MgkWideLayout L, const int32_t* deg_order,
@@ -93,7 +86,6 @@ __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkW
         for (int t = threadIdx.x; t <= groups; t += blockDim.x) to[t] = __int_as_float(first[t]);
     const int head = mgk_wide_head(g.n), cap = mgk_wide_steps(g);
     const int c = lane >> 2, u = lane & 3;
-    const bool inner = (c & 3) == 1 || (c & 3) == 2;
     for (int t = blockIdx.x * 4 + wave; t < groups; t += gridDim.x * 4) {
         const int pos = t * 16 + c, row = order[min(pos, g.n - 1)];
         const int z0 = rowptr[row], z1 = pos < g.n ? row_end(row) : z0;
@@ -102,7 +94,7 @@ __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkW
         if (ordered) {
             // a column's nonzeros by part: lane u of the column collects part u
             int n = 0;
-            for (int z = z0; z < z1; ++z) n += wide_part(L.rows, list[z].y, inner) == u;
+            for (int z = z0; z < z1; ++z) n += wide_part(list[z].y) == u;
             parts[wave][c][u] = (uint8_t)n;
             int at = 0;
             for (int v = 0; v < 3; ++v) {
@@ -110,7 +102,7 @@ __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkW
                 at += v < u ? m : 0;
             }
             for (int z = z0; z < z1; ++z)
-                if (wide_part(L.rows, list[z].y, inner) == u) by_part[wave][c][at++] = (uint8_t)(z - z0);
+                if (wide_part(list[z].y) == u) by_part[wave][c][at++] = (uint8_t)(z - z0);
             __threadfence_block();
             __builtin_amdgcn_wave_barrier();
             if (lane < 4) {   // one lane for the four columns of a cycle
@@ -118,7 +110,7 @@ __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkW
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int places = lane & 1 ? 0x7421 : 0x6530;
-                    col[k] = L.rows == 4 ? (lane & 2) * 4 + ((places >> (4 * k)) & 15) : lane * 4 + k;
+                    col[k] = (lane & 2) * 4 + ((places >> (4 * k)) & 15);
                     int sum = 0;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -164,7 +156,7 @@ __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkW
             const MgkEntry e = list[on ? z : 0];
             const double s = ((double)__uint_as_float(e.z) - S.outer.center) * S.outer.inv_r;
             const double w = (double)__uint_as_float(e.w & 0x7fffffffu) * exp(-S.half_t * s * s);
-            const uint32_t at = mgk_wide_column(L.rows, on ? e.y : ordered ? wide_column_of_part(L.rows, i & 3, inner) : 0u);
+            const uint32_t at = mgk_wide_column(L.rows, on ? e.y : ordered ? (uint32_t)(i & 3) : 0u);
             for (int q = 0; q < L.passes; ++q) {
                 double power = 1.0;
                 for (int k = mgk_wide_first(L, q); k > 0; --k) power *= s;
@@ -300,7 +292,7 @@ __device__ __forceinline__ float wide_step(float y, uint32_t o, float s, float w
     const uint32_t o2 = o + part, o3 = (RK % 4 == 2 ? o >> 1 : o >> 2) + RK / 4 * part;
     wide_read<RK, 0>(t0, o, o2, o3, row16);
     wide_read<RK, 1>(t1, o, o2, o3, row16);
-    if constexpr (RK < 8) {   // all four reads in flight; with more features two at a time keep the registers for eight wavefronts
+    if constexpr (RK < 8) {   // all four reads in flight; with more features two at a time, or more registers are spilled
         wide_read<RK, 2>(t2, o, o2, o3, row16);
         wide_read<RK, 3>(t3, o, o2, o3, row16);
     }
@@ -352,7 +344,8 @@ struct Features {
 };
 
 // Sixteen wavefronts.  TWO: two workgroups share a CU and overlap each other's barriers and trips to memory, half as many results and
-// registers to a thread; else T takes more than half of LDS (2048 columns, 4 rows and 5 features: all of it).  A wavefront of stage
+// registers (64) to a thread, which spills 1 to 10 of them with up to six features and 15, 24 and 35 with eight, nine and ten (still the shorter
+// call than two passes, at the sizes that wide_layout takes them for); else T takes more than half of LDS (2048 columns, 4 rows and 5 features: all of it).  A wavefront of stage
 // 1 takes C chunks of 64 columns of a row, so that rows of unlike degrees are divided evenly.  What the stages
 // and the end read first is loaded ahead of the barrier in front of them.
 template <int R, int HI, int LO, bool TWO>
