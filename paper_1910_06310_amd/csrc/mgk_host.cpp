@@ -1546,19 +1546,19 @@ int64_t feature_bytes(const mgk_batch* b, int32_t g, int rank, bool dense) {
     return dense ? 4 * np * np * rank : 256 * (int64_t)((rank + 3) / 4) * (off[(size_t)g + 1] - off[(size_t)g]);
 }
 
-// The form for graphs of many vertices, made once for every kept one.
-const MgkWideBasis& wide_basis(mgk_ctx* ctx, const MgkSepBasis* kept) {
+// The form for graphs of many vertices, made once for every kept one; without `make` what there is, or null.
+const MgkWideBasis* wide_basis(mgk_ctx* ctx, const MgkSepBasis* kept, bool make) {
     for (KeptBasis& b : ctx->bases)
         if (&b.basis == kept) {
+            if (!b.has_wide && !make) return nullptr;
             if (!b.has_wide) {
                 const double R = kept->inv_r > 0.0 ? 1.0 / kept->inv_r : 0.0, l = (double)ctx->length_scale;
                 b.wide = wide_basis_se(kept->center, R, R * R / (l * l));
                 b.has_wide = true;
             }
-            return b.wide;
+            return &b.wide;
         }
-    static const MgkWideBasis none{};
-    return none;
+    return nullptr;
 }
 
 // rank 0: no separable form.  L, W: the division of the pairs that are solved together.  n_pairs: pairs of the call that may run beside this one.  n_tiles: octiles of
@@ -2395,9 +2395,18 @@ mgk_status launch_jobs(mgk_ctx* ctx, const mgk_batch* X, const mgk_batch* Y, con
             basis = std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return is_sep(C.best); }) ? make_basis(ctx, lo, hi) : &none;
         }
     }
+    // The form for graphs of many vertices takes as long to make again: only if a pair would take it with as many terms as the other form
+    // has (over 120 length scales it had as many or one more).  Another length scale every call: 64 pairs of n = 256, density 0.3, 927 -> 914 us.
     static const MgkWideBasis no_wide{};
-    const MgkWideBasis& wide = may_wide && basis->rank > 0 ? wide_basis(ctx, basis) : no_wide;
-    costs = costs_at(basis->rank, wide.outer.rank, false);
+    const bool any_wide = may_wide && basis->rank > 0;
+    const MgkWideBasis* made = any_wide ? wide_basis(ctx, basis, false) : &no_wide;
+    costs = costs_at(basis->rank, made ? made->outer.rank : basis->rank, false);
+    if (!made) {
+        const bool taken = std::any_of(costs.begin(), costs.end(), [](const LargeCost& C) { return C.best == kPathWide; });
+        made = taken ? wide_basis(ctx, basis, true) : &no_wide;
+        if (taken) costs = costs_at(basis->rank, made->outer.rank, false);
+    }
+    const MgkWideBasis& wide = *made;
     const MgkSepBasis& S = *basis;
     std::vector<const Choice*> lists[2][kPaths];
     for (size_t k = 0; k < choices.size(); ++k) {

@@ -253,6 +253,19 @@ def test_pairs_are_priced_with_the_division_that_runs(host):
     assert "mgk_sep_xmv_kernel<5> rank=5 passes=1" in host.launch_log()
 
 
+def test_form_of_many_vertices_has_no_fewer_terms_than_the_other(host, host_wide):
+    """What it would take is first priced with the other form's rank."""
+    labels = lambda n, k: ring(n, k, np.linspace(0, 1, n * k))
+    A, B = host.load(graphs(labels(300, 6), labels(290, 6))), host_wide.load(graphs(labels(900, 3), labels(890, 3)))
+    for length in np.geomspace(0.25, 20, 25):
+        ranks = []
+        for h, batch in ((host, A), (host_wide, B)):
+            h.set("edge_kernel_se", float(length))
+            assert h.pairs(batch, batch, [0] * 64, [1] * 64) == 0, h.error()
+            ranks.append(int(re.search(r"rank=(\d+)", h.launch_log()).group(1)))
+        assert "mgk_wide" in host_wide.launch_log() and ranks[0] <= ranks[1] <= ranks[0] + 1
+
+
 @pytest.mark.parametrize("largest,division", [(283, "<8, 9, 9> rank=9 passes=1"), (290, "<8, 4, 5> rank=9 passes=2"), (600, "<4, 4, 5> rank=9 passes=2")])
 def test_division_of_many_vertices_is_that_of_the_largest_inner_graph(host_wide, largest, division):
     host = host_wide
