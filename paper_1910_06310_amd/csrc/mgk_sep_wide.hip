@@ -54,7 +54,7 @@ __device__ __forceinline__ int wide_part(uint32_t j) { return (int)(j & 3u); }  
 // In front of a graph's steps the first step of every group.  Absent nonzeros are zeros.
 // With 4 rows the nonzeros of a column (of up to 64) come in an order in which the four columns read
 // together rarely meet in a bank: the part with the most left that the others do not take.  2048 columns of degree 12: conflicts are 28 % of the
-// product's LDS cycles, 45 % in the order of the rows (1074 -> 1039 us a product); this kernel 78 us, 18 without.
+// product's LDS cycles, 45 % in the order of the rows (1074 -> 1039 us a product); this kernel takes 58 us for 16 such graphs, most of them for the order.
 __global__ __launch_bounds__(256) void mgk_wide_inner_kernel(MgkBatchDev B, MgkWideBasis S, MgkWideLayout L, const int32_t* deg_order,
                                                              const MgkSepGraph* used, float* out) {
     constexpr int kMost = 64;   // nonzeros of a row that is ordered

@@ -116,8 +116,8 @@ def test_small_graphs_beside_large_ones(torch, solver):
                                                    (0.4, ("4", "5", "9", "2")), (0.35, ("5", "5", "10", "2")), (0.25, ("6", "6", "12", "2")),
                                                    (0.224, ("4", "5", "13", "3")), (0.2, ("5", "5", "15", "3")), (0.19, ("4", "4", "16", "4"))])
 def test_every_division_of_the_rank(torch, solver, length_scale, division):
-    rng = np.random.default_rng(3)
     """Features in one pass or more of four to six; graphs of two batches."""
+    rng = np.random.default_rng(3)
     wx, wy = batch([ring(900, 6, rng), ring(700, 8, rng)], length_scale), batch([ring(640, 10, rng), ring(777, 6, rng)], length_scale)
     forms = compare(torch, solver, wx, wy, [0, 1, 1, 0, 1, 1, 0, 0], [0, 0, 1, 1, 0, 1, 0, 1])
     assert {f[1:] for f in forms} == {division}
