@@ -145,6 +145,14 @@ def test_dense_form_on_parts_at_edges_of_its_tiles(torch, solver, sizes, length_
     assert (("dense_parts" if max(sizes) > 256 else "dense"), rank) not in kernels
 
 
+def test_both_dense_kernels_in_one_call(torch, solver):
+    """Pairs beyond 256 vertices and enough others for launches of their own: two groups, one after the other in the same buffers."""
+    wb = er(31, (290,) + (250, 241, 256, 233, 248) * 3, 1.0)
+    pi, pj, K, log = compare(torch, solver, wb, wb)
+    assert forms(log) == {("dense", 1, 5, 1), ("dense", 2, 5, 1), ("dense_parts", 0, 5, 1)}   # 290 vertices as inner graph once
+    np.testing.assert_allclose(K.reshape(16, 16), K.reshape(16, 16).T, rtol=RTOL_PATHS)
+
+
 def test_dense_form_at_its_largest_size(torch, solver):
     """1024 columns: all four tiles of every wavefront, the most LDS.  One column more has no dense form."""
     wx, wy = er(11, (1030,), 0.2), er(12, (1024, 1025), 0.2)
